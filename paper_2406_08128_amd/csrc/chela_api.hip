@@ -175,8 +175,11 @@ TrainPlans make_train_plans(long BH, int N, int dk, int dv, int chunk)
     return t;
 }
 
-// Non-causal form: the pre-pass is the only part that is split, and only to fill the GPU (two workgroups per compute
-// unit measured best: every further segment is a state to write, scan and read), in pieces of at least 256 tokens.
+// Non-causal form: the pre-pass is the only part that is split, and only to fill the GPU: one workgroup per compute
+// unit, in pieces of at least 256 tokens.  Every further segment is a state to write, add up and read, and more than a
+// few need the scan kernel: with two workgroups per unit 96 heads x 4096 tokens, 64 x 128, took 70.6 / 134.6 us
+// (forward / backward) against 65.6 / 123.2, 48 heads x 6553 tokens, 128 x 128, 83 / 202 against 75 / 193, and half a
+// workgroup per unit loses as much again (48 heads x 16384 tokens: forward 102 against 74 us).
 Plan make_noncausal_plan(long BH, int N, int dk, int dv, bool is_bwd)
 {
     Plan p{};
@@ -184,7 +187,7 @@ Plan make_noncausal_plan(long BH, int N, int dk, int dv, bool is_bwd)
     p.state_elems = (size_t)dk * dv;
     if (BH <= 0 || N <= 0) { p.seg_len = 64; p.n_seg = 0; p.ws_bytes = 0; return p; }
     const int pairs = is_bwd ? 2 : 1;
-    long n_seg = (512 + BH * pairs - 1) / (BH * pairs);
+    long n_seg = 256 / (BH * pairs);
     const long max_seg = N / 256 > 0 ? N / 256 : 1;
     const int forced = env_int("CHELA_NC_SEGS", 0);     // tuning aid: segments per (b,h) of the non-causal pre-pass
     if (forced > 0) n_seg = forced;

@@ -1964,10 +1964,16 @@ static hipError_t bwd_impl(const bf16* Q, const bf16* K, const bf16* V, const bf
 // matrix per head, given either as it is (M_IS_T = false) or transposed, [DB][DA] (true).  The matrix becomes the
 // A operand (M^T, bf16, read from LDS once and kept in registers), a 64-token tile of X the B operand, the result
 // tile is Y^T and leaves through 16-byte stores.  The X tile is double-buffered in LDS: one barrier per chunk.
+// Bound by memory: one tensor in, one out per product.  What the calls cost beyond their bytes were launches (three
+// products of the backward one after the other, a scan in front of them) and two-byte LDS stores that turned M: with
+// one launch for the three products, the totals added up here (fold_totals) and M turned by the transposing read,
+// forward / backward went from 89.5 / 194 to 82 / 181 us (256 heads x 3517 tokens, 64 x 64), 73.9 / 161 to 66 / 122 us
+// (96 x 4096, 64 x 128), 96.7 / 255 to 74 / 191 us (48 x 6553, 128 x 128) and 17 / 24.5 to 14.2 / 16 us (32 x 512).
 template <int DA, int DB, bool GATE = false>
 struct ApplyLds {
     static constexpr int LDA = DA + PAD;
-    static constexpr int TILES = (2 * 64 * LDA + DB * LDA) * 2;
+    static constexpr int MAT = DB * LDA > DA * (DB + PAD) ? DB * LDA : DA * (DB + PAD);     // either storage order
+    static constexpr int TILES = (2 * 64 * LDA + MAT) * 2;
     static constexpr int SUMS = GATE ? 2 * 2 * 64 * 4 : 0;                  // [2][2][64] floats
     // not gated, 64 features out: the output leaves as whole rows through two staging tiles used in turn
     static constexpr bool STAGE = !GATE && DB == 64;
@@ -1980,16 +1986,15 @@ struct ApplyLds {
 // sets, used in turn) and the gated tile of chunk c leaves after the barrier of chunk c + 1, so the kernel still
 // meets at one barrier per chunk.
 template <int DA, int DB, bool M_IS_T, bool GATE>
-__global__ __launch_bounds__(256) void bf16_apply_state_kernel(const bf16* __restrict__ X, bf16* __restrict__ Y,
-                                                              const float* __restrict__ M, size_t m_stride, int N,
-                                                              int rows_per_wg, const bf16* __restrict__ G,
-                                                              bf16* __restrict__ Yg, float eps)
+__device__ __forceinline__ void apply_body(const bf16* __restrict__ X, bf16* __restrict__ Y, const float* __restrict__ M,
+                                           size_t m_stride, int n_sum, int N, int rows_per_wg,
+                                           const bf16* __restrict__ G, bf16* __restrict__ Yg, float eps,
+                                           unsigned char* lds)
 {
     constexpr int C = 64, LDA = DA + PAD;
     constexpr int JB = DB / 32, NJ = JB / 2;
-    __shared__ __attribute__((aligned(16))) unsigned char lds[ApplyLds<DA, DB, GATE>::BYTES];
     bf16* sX = reinterpret_cast<bf16*>(lds);          // two buffers of C x LDA
-    bf16* sMT = sX + 2 * C * LDA;                      // M^T: [DB][LDA]
+    bf16* sM = sX + 2 * C * LDA;                       // M^T [DB][LDA] or M [DA][LDB]
     float* sSq = reinterpret_cast<float*>(lds + ApplyLds<DA, DB, false>::TILES);   // GATE: [2][2][C]
     constexpr int LDB = DB + PAD;
     bf16* sG = reinterpret_cast<bf16*>(lds + ApplyLds<DA, DB, false>::TILES + ApplyLds<DA, DB, true>::SUMS);   // [2][C][LDB]
@@ -2008,28 +2013,29 @@ __global__ __launch_bounds__(256) void bf16_apply_state_kernel(const bf16* __res
     TileRegs<C, DB, true> rg;   // GATE: the gate tile travels like X (full lines in, LDS, then the order the tile is stored in)
     rx.load(Xb, DA, ntok, tid);
     if (GATE) rg.load(Gb, DB, ntok, tid);
+    // M is the sum of n_sum states, one behind the other (the pre-pass's segment totals, added up in their order).
+    // Either storage order goes to LDS row by row; M itself is turned by the transposing read.
+#pragma unroll 4
     for (int x = tid; x < DA * DB / 4; x += 256) {
-        const float4 v = M4[x];
-        if (M_IS_T) {
-            const int j = (4 * x) / DA, i = (4 * x) % DA;
-            u32x2 pk;
-            pk[0] = pack2(v.x, v.y);
-            pk[1] = pack2(v.z, v.w);
-            *reinterpret_cast<u32x2*>(sMT + j * LDA + i) = pk;
-        } else {
-            const int i = (4 * x) / DB, j = (4 * x) % DB;
-            sMT[(j + 0) * LDA + i] = (bf16)v.x;
-            sMT[(j + 1) * LDA + i] = (bf16)v.y;
-            sMT[(j + 2) * LDA + i] = (bf16)v.z;
-            sMT[(j + 3) * LDA + i] = (bf16)v.w;
+        float4 v = M4[x];
+        for (int k = 1; k < n_sum; ++k) {
+            const float4 u = M4[x + k * (DA * DB / 4)];
+            v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
         }
+        constexpr int W = M_IS_T ? DA : DB;
+        u32x2 pk;
+        pk[0] = pack2(v.x, v.y);
+        pk[1] = pack2(v.z, v.w);
+        *reinterpret_cast<u32x2*>(sM + (4 * x) / W * (W + PAD) + (4 * x) % W) = pk;
     }
     __syncthreads();
     bf16x8 aM[NJ][DA / 16];
 #pragma unroll
     for (int n = 0; n < NJ; ++n)
 #pragma unroll
-        for (int kk = 0; kk < DA / 16; ++kk) aM[n][kk] = ld_nat(sMT, LDA, (jg * NJ + n) * 32, kk * 16, lane);
+        for (int kk = 0; kk < DA / 16; ++kk)
+            aM[n][kk] = M_IS_T ? ld_nat(sM, LDA, (jg * NJ + n) * 32, kk * 16, lane)
+                               : ld_tr(sM, LDB, kk * 16, (jg * NJ + n) * 32, lane);
 
     // GATE: the tile of the previous chunk, its gate and where it goes, waiting for that chunk's sums of squares
     f32x16 held[GATE ? NJ : 1];
@@ -2113,21 +2119,57 @@ __global__ __launch_bounds__(256) void bf16_apply_state_kernel(const bf16* __res
     }
 }
 
-constexpr int kApplyRows = 512;   // tokens per workgroup of the apply kernel
-
-template <int DA, int DB, bool M_IS_T>
-static hipError_t run_apply(const bf16* X, bf16* Y, const float* M, size_t m_stride, long BH, int N, hipStream_t st,
-                            const bf16* G = nullptr, bf16* Yg = nullptr, float eps = 0.f)
+// One product Y = X M (forward call).
+template <int DA, int DB, bool M_IS_T, bool GATE>
+__global__ __launch_bounds__(256) void bf16_apply_state_kernel(const bf16* __restrict__ X, bf16* __restrict__ Y,
+                                                              const float* __restrict__ M, size_t m_stride, int n_sum,
+                                                              int N, int rows_per_wg, const bf16* __restrict__ G,
+                                                              bf16* __restrict__ Yg, float eps)
 {
-    dim3 grid((unsigned)BH, (N + kApplyRows - 1) / kApplyRows);
-    ProfScope prof(KID_APPLY_BF16, st);
-    if (G != nullptr)
-        hipLaunchKernelGGL((bf16_apply_state_kernel<DA, DB, M_IS_T, true>), grid, dim3(256), 0, st, X, Y, M, m_stride, N,
-                           kApplyRows, G, Yg, eps);
-    else
-        hipLaunchKernelGGL((bf16_apply_state_kernel<DA, DB, M_IS_T, false>), grid, dim3(256), 0, st, X, Y, M, m_stride,
-                           N, kApplyRows, G, Yg, eps);
-    return hipGetLastError();
+    __shared__ __attribute__((aligned(16))) unsigned char lds[ApplyLds<DA, DB, GATE>::BYTES];
+    apply_body<DA, DB, M_IS_T, GATE>(X, Y, M, m_stride, n_sum, N, rows_per_wg, G, Yg, eps, lds);
+}
+
+// The three products of the backward in one launch, one after the other on grid.z (in the order in which the pre-pass
+// leaves their inputs in the memory-side cache): dQ = dO S^T, dK = V R^T, dV = K R, with S^T, R^T stored [dv][dk].
+template <int DK, int DV>
+__global__ __launch_bounds__(256) void bf16_apply_grads_kernel(const bf16* __restrict__ K, const bf16* __restrict__ V,
+                                                              const bf16* __restrict__ dO, bf16* __restrict__ dQ,
+                                                              bf16* __restrict__ dK, bf16* __restrict__ dV,
+                                                              const float* __restrict__ ST, const float* __restrict__ RT,
+                                                              size_t m_stride, int n_sum, int N, int rows_per_wg)
+{
+    constexpr int LA = ApplyLds<DV, DK>::BYTES, LB = ApplyLds<DK, DV>::BYTES;
+    __shared__ __attribute__((aligned(16))) unsigned char lds[LA > LB ? LA : LB];
+    if (blockIdx.z < 2) {
+        const bool first = blockIdx.z == 0;
+        apply_body<DV, DK, false, false>(first ? dO : V, first ? dQ : dK, first ? ST : RT, m_stride, n_sum, N,
+                                         rows_per_wg, nullptr, nullptr, 0.f, lds);
+    } else {
+        apply_body<DK, DV, true, false>(K, dV, RT, m_stride, n_sum, N, rows_per_wg, nullptr, nullptr, 0.f, lds);
+    }
+}
+
+// Tokens per workgroup of the apply kernels.  A workgroup first reads its matrix (16 .. 64 KB, once or n_sum times), so
+// few and long ones are cheap, but whole rounds of what the GPU holds at once matter more: two rounds, with at most
+// 128 KB of X per workgroup so that very long sequences stay spread over the memory channels.  Against 512 tokens
+// always (which left 256 sequences of 3517 tokens with two and a third rounds): 84 -> 82 us forward there; one round:
+// the same within 1 % but 620 against 551 us for the 128 x 128 backward of 16 x 65536 tokens.
+static int apply_rows(long BH, int N, int lds_bytes, int row_bytes)
+{
+    long nb = 2 * 256L * (163840 / lds_bytes) / BH;
+    const long min_nb = ((long)N * row_bytes + (128 << 10) - 1) / (128 << 10), max_nb = (N + 255) / 256;
+    if (nb < min_nb) nb = min_nb;
+    if (nb > max_nb) nb = max_nb;
+    return (int)(((N + nb - 1) / nb + 63) / 64 * 64);
+}
+
+// Few segments: the apply kernels add the totals up while they read their matrix, and no scan kernel runs (5 .. 8 us of
+// latency).  Every workgroup reads all of them, so this stops at 96 KB: 72 heads x 975 tokens, 128 x 64, three
+// segments: 20.2 -> 18.3 us; 48 heads x 6553 tokens, 128 x 128, five segments (320 KB): 81 -> 103 us, so not there.
+static bool fold_totals(const Plan& plan)
+{
+    return (size_t)plan.n_seg * plan.state_elems * sizeof(float) <= ((size_t)96 << 10);
 }
 
 // plan.n_seg / seg_len describe the pre-pass split here; the totals end up in the last segment's slot.
@@ -2140,11 +2182,23 @@ static hipError_t noncausal_fwd_impl(const bf16* Q, const bf16* K, const bf16* V
     SegStateArgs a{};
     a.X[0] = V; a.Y[0] = K; a.out[0] = ws; a.skip_seg[0] = -1;       // S^T = V^T K, [dv][dk]
     const int mode = SCAN_INCL_PREFIX;
+    const bool fold = fold_totals(plan);
     // (K and V are not read again in this call: streaming loads)
-    if ((e = run_seg_state<DV, DK, 0, false, true>(a, 1, &mode, nullptr, false, BH, N, plan, st, plan.n_seg > 1)) != hipSuccess)
+    if ((e = run_seg_state<DV, DK, 0, false, true>(a, 1, &mode, nullptr, false, BH, N, plan, st, !fold)) != hipSuccess)
         return e;
     const size_t el = (size_t)DK * DV;
-    return run_apply<DK, DV, true>(Q, O, ws + (size_t)(plan.n_seg - 1) * el, plan.n_seg * el, BH, N, st, G, Y, eps);
+    const float* M = fold ? ws : ws + (size_t)(plan.n_seg - 1) * el;
+    const int n_sum = fold ? plan.n_seg : 1, rows = apply_rows(BH, N, G ? ApplyLds<DK, DV, true>::BYTES : ApplyLds<DK, DV, false>::BYTES,
+                                                                        DK * 2);
+    dim3 grid((unsigned)BH, (N + rows - 1) / rows);
+    ProfScope prof(KID_APPLY_BF16, st);
+    if (G != nullptr)
+        hipLaunchKernelGGL((bf16_apply_state_kernel<DK, DV, true, true>), grid, dim3(256), 0, st, Q, O, M, plan.n_seg * el,
+                           n_sum, N, rows, G, Y, eps);
+    else
+        hipLaunchKernelGGL((bf16_apply_state_kernel<DK, DV, true, false>), grid, dim3(256), 0, st, Q, O, M,
+                           plan.n_seg * el, n_sum, N, rows, G, Y, eps);
+    return hipGetLastError();
 }
 
 template <int DK, int DV>
@@ -2159,16 +2213,20 @@ static hipError_t noncausal_bwd_impl(const bf16* Q, const bf16* K, const bf16* V
     a.X[0] = V;  a.Y[0] = K; a.out[0] = wsS; a.skip_seg[0] = -1;
     a.X[1] = dO; a.Y[1] = Q; a.out[1] = wsR; a.skip_seg[1] = -1;
     const int modes[2] = {SCAN_INCL_PREFIX, SCAN_INCL_PREFIX};
+    const bool fold = fold_totals(plan);
     // (as in the causal backward: once the four tensors exceed the memory-side cache, dO and Q go through it with the
-    // streaming hint, so that V and K are still there for the second and third of the kernels below)
+    // streaming hint, so that V and K are still there for the second and third of the products below)
     const bool stream_dO_Q = (size_t)BH * N * (2 * DK + 2 * DV) * sizeof(bf16) > kStreamPairAboveBytes;
-    if ((e = run_seg_state<DV, DK>(a, 2, modes, nullptr, false, BH, N, plan, st, plan.n_seg > 1, stream_dO_Q)) != hipSuccess)
+    if ((e = run_seg_state<DV, DK>(a, 2, modes, nullptr, false, BH, N, plan, st, !fold, stream_dO_Q)) != hipSuccess)
         return e;
-    const size_t last = (size_t)(plan.n_seg - 1) * el, stride = plan.n_seg * el;
-    // dQ = dO S^T, dK = V R^T, dV = K R
-    if ((e = run_apply<DV, DK, false>(dO, dQ, wsS + last, stride, BH, N, st)) != hipSuccess) return e;
-    if ((e = run_apply<DV, DK, false>(V, dK, wsR + last, stride, BH, N, st)) != hipSuccess) return e;
-    return run_apply<DK, DV, true>(K, dV, wsR + last, stride, BH, N, st);
+    const size_t last = fold ? 0 : (size_t)(plan.n_seg - 1) * el, stride = plan.n_seg * el;
+    constexpr int LDS = ApplyLds<DK, DV>::BYTES > ApplyLds<DV, DK>::BYTES ? ApplyLds<DK, DV>::BYTES : ApplyLds<DV, DK>::BYTES;
+    const int rows = apply_rows(BH, N, LDS, (DK > DV ? DK : DV) * 2);
+    dim3 grid((unsigned)BH, (N + rows - 1) / rows, 3);
+    ProfScope prof(KID_APPLY_BF16, st);
+    hipLaunchKernelGGL((bf16_apply_grads_kernel<DK, DV>), grid, dim3(256), 0, st, K, V, dO, dQ, dK, dV, wsS + last,
+                       wsR + last, stride, fold ? plan.n_seg : 1, N, rows);
+    return hipGetLastError();
 }
 
 hipError_t launch_bf16_noncausal_fwd(const void* Q, const void* K, const void* V, void* O, long BH, int N, int dk,

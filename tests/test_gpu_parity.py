@@ -744,6 +744,17 @@ def test_noncausal_fwd_bwd_small(shape):
     _run_nc_case(shrink(WORKLOADS["lra_bf16"], B=B, H=H, N=N, dk=dk, dv=dv, seed=90 + N))
 
 
+@pytest.mark.parametrize("shape", [(1, 1, 512, 64, 64), (1, 2, 1536, 64, 64), (1, 2, 1793, 64, 64), (1, 1, 770, 64, 128),
+                                   (1, 1, 1025, 128, 64), (1, 1, 2049, 128, 128), (3, 43, 257, 64, 64),
+                                   (1, 260, 65, 64, 64), (1, 65, 1025, 64, 128), (2, 130, 600, 128, 128)])
+def test_noncausal_segment_totals_and_row_blocks(shape):
+    # the totals added up by the apply kernels (2, 6, 3 segments: up to 96 KB of states) or by the scan (7, 4, 8
+    # segments), row blocks of every kind: one per head, a last one of a single row, heads on either side of 256
+    B, H, N, dk, dv = shape
+    heads = None if B * H <= 4 else [0, 1, B * H // 2, B * H - 1]
+    _run_nc_case(shrink(WORKLOADS["lra_bf16"], B=B, H=H, N=N, dk=dk, dv=dv, seed=190 + N), heads)
+
+
 def test_noncausal_lra_full_size():
     w = WORKLOADS["lra_bf16"]       # the shape of the paper's byte-level classification runs, where no mask is used
     _run_nc_case(w)
