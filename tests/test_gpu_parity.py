@@ -1215,6 +1215,20 @@ def test_gate_norm_alone(rows_dv):
     assert dO2.data_ptr() == dY2.data_ptr() and torch.equal(dO2, dO) and torch.equal(dG2, dG)
 
 
+@pytest.mark.parametrize("rows_dv", [(367003, 64), (183502, 128)])
+def test_gate_norm_gradient_streaming_outputs_equal_the_small_call(rows_dv):
+    # just beyond the size from which dO leaves with the streaming hint: every row bit for bit as in smaller calls
+    rows, dv = rows_dv
+    g = torch.Generator(device="cuda")
+    g.manual_seed(rows)
+    O, G, dY = (torch.randn(rows, dv, generator=g, device="cuda").bfloat16() for _ in range(3))
+    dO, dG = binding.chela_gate_norm_bwd(O, G, dY, EPS)
+    cut = rows // 2 + 5
+    for sl in (slice(0, cut), slice(cut, rows)):
+        a, b = binding.chela_gate_norm_bwd(O[sl].contiguous(), G[sl].contiguous(), dY[sl].contiguous(), EPS)
+        assert torch.equal(a, dO[sl]) and torch.equal(b, dG[sl])
+
+
 def test_gate_norm_eps_enters_under_the_root_and_empty_input():
     O = torch.full((64, 64), 2.0, dtype=torch.bfloat16, device="cuda")
     G = torch.ones_like(O)
