@@ -29,40 +29,82 @@ __device__ __forceinline__ cplx conj(cplx a) { return mk(a.x, -a.y); }
 __device__ __forceinline__ cplx mul_neg_i(cplx a) { return mk(a.y, -a.x); }   // a * (-i)
 __device__ __forceinline__ cplx mul_pos_i(cplx a) { return mk(-a.y, a.x); }   // a * (+i)
 
-// 4-point DFT, kernel exp(-2 pi i p q / 4) (INV: the conjugate kernel), in place: (a,b,c,d) = x_0..x_3 -> X_0..X_3.
-template <bool INV>
-__device__ __forceinline__ void dft4(cplx& a, cplx& b, cplx& c, cplx& d)
+// a + t b and a - t b in place (a, b), t = tx + i ty: four fused multiply-adds for the sum and 2a - (a + t b) for the
+// difference, six instructions where a product and two additions take eight.
+__device__ __forceinline__ void bfly(cplx& a, cplx& b, float tx, float ty)
 {
-    const cplx s0 = cadd(a, c), d0 = csub(a, c), s1 = cadd(b, d), d1 = csub(b, d);
-    const cplx r = INV ? mul_pos_i(d1) : mul_neg_i(d1);
-    a = cadd(s0, s1);
-    c = csub(s0, s1);
-    b = cadd(d0, r);
-    d = csub(d0, r);
+    const cplx m = mk(fmaf(-ty, b.y, fmaf(tx, b.x, a.x)), fmaf(ty, b.x, fmaf(tx, b.y, a.y)));
+    b = mk(fmaf(2.f, a.x, -m.x), fmaf(2.f, a.y, -m.y));
+    a = m;
+}
+__device__ __forceinline__ void bfly1(cplx& a, cplx& b) { const cplx m = cadd(a, b); b = csub(a, b); a = m; }
+// the same with t turned by a quarter (forward: -i t, inverse: +i t); QT: t = 1
+template <bool INV> __device__ __forceinline__ void bfly_q(cplx& a, cplx& b, float tx, float ty)
+{
+    if (INV) bfly(a, b, -ty, tx); else bfly(a, b, ty, -tx);
+}
+template <bool INV> __device__ __forceinline__ void bfly1_q(cplx& a, cplx& b)
+{
+    const cplx r = INV ? mul_pos_i(b) : mul_neg_i(b);
+    b = csub(a, r);
+    a = cadd(a, r);
 }
 
-// 16-point DFT in registers.  In: v[q] = x_q.  Out: X_p sits in slot (p >> 2) + 4 * (p & 3).
-// q = q0 + 4 q1, p = p1 + 4 p0:  X_p = sum_q0 w4^(p0 q0) w16^(p1 q0) [ sum_q1 x_(q0 + 4 q1) w4^(p1 q1) ].
-template <bool INV>
-__device__ __forceinline__ void dft16(cplx (&v)[16])
+// 16-point DFT in registers with the twiddles of its INPUTS taken along:  X_p = sum_q x_q (w w16^p)^q, w16 =
+// exp(-2 pi i / 16) (INV: conjugate).  In: v[q] = x_q.  Out: X_p sits in slot rev4(p) (the four bits of p reversed).
+// Radix 2 over q: 16 values of a polynomial, and level by level only the powers w^8, w^4, w^2 and w of the base are met,
+// times eighth and sixteenth roots: eight distinct complex twiddles (28 instructions from w) for 32 butterflies of six
+// instructions, 220 in all, where a plain 16-point transform with fifteen twiddles in front of or behind it takes 290
+// (its chain of powers 56, its products 60).  UNIT: w = 1 (148 instructions).  HALF_IN: x_8 .. x_15 are zero (not read).
+// HALF_OUT: only X_0 .. X_7 are wanted.
+__host__ __device__ constexpr int rev4(int p) { return ((p & 1) << 3) | ((p & 2) << 1) | ((p & 4) >> 1) | ((p & 8) >> 3); }
+template <bool INV, bool UNIT, bool HALF_IN = false, bool HALF_OUT = false>
+__device__ __forceinline__ void dft16(cplx (&v)[16], cplx w)
 {
-#pragma unroll
-    for (int q0 = 0; q0 < 4; ++q0) dft4<INV>(v[q0], v[q0 + 4], v[q0 + 8], v[q0 + 12]);     // slot q0 + 4 p1
     constexpr float C1 = 0.92387953251128674f, S1 = 0.38268343236508977f, R2 = 0.70710678118654752f;
-    // w16^k = exp(-2 pi i k / 16) for the products q0 * p1 in {1, 2, 3, 4, 6, 9}
-    const cplx w1 = mk(C1, INV ? S1 : -S1), w2 = mk(R2, INV ? R2 : -R2), w3 = mk(S1, INV ? C1 : -C1);
-    const cplx w6 = mk(-R2, INV ? R2 : -R2), w9 = mk(-C1, INV ? -S1 : S1);
-    v[1 + 4 * 1] = cmul(v[1 + 4 * 1], w1);
-    v[2 + 4 * 1] = cmul(v[2 + 4 * 1], w2);
-    v[3 + 4 * 1] = cmul(v[3 + 4 * 1], w3);
-    v[1 + 4 * 2] = cmul(v[1 + 4 * 2], w2);
-    v[2 + 4 * 2] = INV ? mul_pos_i(v[2 + 4 * 2]) : mul_neg_i(v[2 + 4 * 2]);                 // w16^4 = -i
-    v[3 + 4 * 2] = cmul(v[3 + 4 * 2], w6);
-    v[1 + 4 * 3] = cmul(v[1 + 4 * 3], w3);
-    v[2 + 4 * 3] = cmul(v[2 + 4 * 3], w6);
-    v[3 + 4 * 3] = cmul(v[3 + 4 * 3], w9);
+    constexpr float SG = INV ? 1.f : -1.f;
+    const cplx w2 = UNIT ? mk(1.f, 0.f) : mk(fmaf(w.x, w.x, -w.y * w.y), 2.f * w.x * w.y);
+    if (HALF_IN) {
 #pragma unroll
-    for (int p1 = 0; p1 < 4; ++p1) dft4<INV>(v[4 * p1], v[4 * p1 + 1], v[4 * p1 + 2], v[4 * p1 + 3]);   // slot p0 + 4 p1
+        for (int q = 0; q < 8; ++q) v[q + 8] = v[q];
+    } else if (UNIT) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) bfly1(v[q], v[q + 8]);
+    }
+    if (UNIT) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) { bfly1(v[q], v[q + 4]); bfly1_q<INV>(v[q + 8], v[q + 12]); }
+    } else {
+        const cplx w4 = mk(fmaf(w2.x, w2.x, -w2.y * w2.y), 2.f * w2.x * w2.y);
+        if (!HALF_IN) {
+            const cplx w8 = mk(fmaf(w4.x, w4.x, -w4.y * w4.y), 2.f * w4.x * w4.y);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) bfly(v[q], v[q + 8], w8.x, w8.y);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) { bfly(v[q], v[q + 4], w4.x, w4.y); bfly_q<INV>(v[q + 8], v[q + 12], w4.x, w4.y); }
+    }
+    // slots now: x_q sums with the bits of p seen so far (lowest first) in the top bits of the slot
+    const cplx w2b = UNIT ? mk(R2, SG * R2) : cmul(w2, mk(R2, SG * R2));             // w^2 w8
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+        if (UNIT) { bfly1(v[q], v[q + 2]); bfly1_q<INV>(v[q + 4], v[q + 6]); }
+        else { bfly(v[q], v[q + 2], w2.x, w2.y); bfly_q<INV>(v[q + 4], v[q + 6], w2.x, w2.y); }
+        bfly(v[q + 8], v[q + 10], w2b.x, w2b.y);
+        bfly_q<INV>(v[q + 12], v[q + 14], w2b.x, w2b.y);
+    }
+    const cplx d1 = UNIT ? mk(C1, SG * S1) : cmul(w, mk(C1, SG * S1));
+    const cplx d2 = UNIT ? mk(R2, SG * R2) : cmul(w, mk(R2, SG * R2));
+    const cplx d3 = UNIT ? mk(S1, SG * C1) : cmul(w, mk(S1, SG * C1));
+    // (HALF_OUT: the differences, X_(p+8), are dead and the compiler drops them)
+    if (UNIT) { bfly1(v[0], v[1]); bfly1_q<INV>(v[2], v[3]); }
+    else { bfly(v[0], v[1], w.x, w.y); bfly_q<INV>(v[2], v[3], w.x, w.y); }
+    bfly(v[8], v[9], d1.x, d1.y);
+    bfly_q<INV>(v[10], v[11], d1.x, d1.y);
+    bfly(v[4], v[5], d2.x, d2.y);
+    bfly_q<INV>(v[6], v[7], d2.x, d2.y);
+    bfly(v[12], v[13], d3.x, d3.y);
+    bfly_q<INV>(v[14], v[15], d3.x, d3.y);
 }
 
 __host__ __device__ constexpr int conv_threads(int M) { return M / 16 < 64 ? 64 : M / 16; }
@@ -94,92 +136,87 @@ __device__ __forceinline__ int spectrum_pos(int k)
     return pos;
 }
 
+// The number of the bins (their low digits) that the blocks of length N16 hold after the forward passes before: block
+// index in storage order -> digits reversed.
+template <int M, int N16>
+__device__ __forceinline__ int block_bin(int block)
+{
+    constexpr int NB = M / N16;                    // blocks: 1, 4, 16, 64, 256 or 1024
+    if (NB <= 16) return block;                    // one digit
+    if (NB == 64) return (block >> 4) | (block & 15) << 2;
+    if (NB == 256) return (block >> 4) | (block & 15) << 4;
+    return (block >> 8) | (block & 0xf0) >> 2 | (block & 15) << 6;
+}
+
 // One radix-16 pass over sub-transforms of length N16 (stride N16 / 16), forward or inverse, 16-point transforms
 // in registers, T threads.  With the length fixed at compile time the 16 LDS addresses are one base plus constants
-// (the padding of a multiple of 16 is itself a constant), and the last pass (N16 = 16) has no twiddles at all.
-template <int M, int T, int N16, bool INV>
+// (the padding of a multiple of 16 is itself a constant).  Both directions take their twiddles at the inputs, as the
+// powers of ONE number per transform that dft16 works into its butterflies:
+//   forward, digits of k found so far = K:   sum_q x_q W_(16 NB)^(q K) w16^(p q),  NB = M / N16 blocks
+//   inverse, point j of the sub-transform:   sum_q X_q conj(W_N16^(q j)) conj(w16^(p q))
+// so the first pass either way has none.  HALF: forward, inputs 8 .. 15 are zero; inverse, outputs 8 .. 15 are not wanted.
+template <int M, int T, int N16, bool INV, bool HALF>
 __device__ __forceinline__ void pass16(cplx* a, const cplx* lo, const cplx* hi, int tid)
 {
     constexpr int S = N16 / 16;
     constexpr int STEP = S >= 16 ? S + S / 16 : 1;                 // padded distance between the transform's points
+    constexpr bool UNIT = INV ? S == 1 : N16 == M;
     for (int g = tid; g < M / 16; g += T) {
         const int block = g / S, j = g - block * S;
         cplx* p0 = a + (S >= 16 ? conv_pad(block * N16 + j) : 17 * g);
         cplx v[16];
-        cplx w1 = mk(1.f, 0.f);
-        if (S > 1) {
-            const cplx w1f = twiddle<M>(lo, hi, j * (M / N16));   // W_N16^j
-            w1 = INV ? conj(w1f) : w1f;
-        }
-        if (INV) {
-            // undo the forward pass: strip the twiddles, then the conjugate 16-point transform (the factor 1/16 is
-            // left to the final scaling); inputs X_p in natural order p, outputs x_q in slot order
-            cplx w = w1;
-            v[0] = p0[0];
+        cplx w = mk(1.f, 0.f);
+        if (!UNIT) w = INV ? conj(twiddle<M>(lo, hi, j * (M / N16))) : twiddle<M>(lo, hi, block_bin<M, N16>(block) * S);
 #pragma unroll
-            for (int p = 1; p < 16; ++p) {
-                v[p] = S > 1 ? cmul(p0[p * STEP], w) : p0[p * STEP];
-                if (S > 1) w = cmul(w, w1);
-            }
-            dft16<true>(v);
+        for (int q = 0; q < (HALF && !INV ? 8 : 16); ++q) v[q] = p0[q * STEP];
+        dft16<INV, UNIT, HALF && !INV, HALF && INV>(v, w);
 #pragma unroll
-            for (int q = 0; q < 16; ++q) p0[q * STEP] = v[(q >> 2) + 4 * (q & 3)];
-        } else {
-#pragma unroll
-            for (int q = 0; q < 16; ++q) v[q] = p0[q * STEP];
-            dft16<false>(v);
-            cplx w = w1;
-            p0[0] = v[0];
-#pragma unroll
-            for (int p = 1; p < 16; ++p) {
-                p0[p * STEP] = S > 1 ? cmul(v[(p >> 2) + 4 * (p & 3)], w) : v[(p >> 2) + 4 * (p & 3)];
-                if (S > 1) w = cmul(w, w1);
-            }
-        }
+        for (int p = 0; p < (HALF && INV ? 8 : 16); ++p) p0[p * STEP] = v[rev4(p)];
     }
 }
 
 // All forward passes (INV = false) or all inverse passes in reverse order (INV = true) over a[] in LDS.
 // A __syncthreads() separates the passes; the caller synchronises before and after.
+// The packed sequence has at most M/2 non-zero entries (L <= M real steps) and only its first M/2 entries are ever read
+// back: the first pass forward does not read the upper half, the last one back does not write it.
 template <int M, int T, bool INV>
 __device__ __forceinline__ void fft_passes(cplx* a, const cplx* lo, const cplx* hi, int tid)
 {
-    constexpr int M16 = conv_lead4(M) ? M / 4 : M;     // what the radix-16 passes transform (blocks of this length)
+    constexpr bool L4 = conv_lead4(M);
+    constexpr int M16 = L4 ? M / 4 : M;     // what the radix-16 passes transform (blocks of this length)
     static_assert(M16 == 256 || M16 == 4096, "radix-16 part must be 16^2 or 16^3");
-    // The packed sequence has at most M/2 non-zero entries (L <= M real steps) and only its first M/2 entries are
-    // ever read back: the leading radix-4 pass sees two zero inputs going forward and owes only two outputs coming back.
     auto lead4 = [&]() __attribute__((always_inline)) {
         constexpr int s = M / 4, sp = s + s / 16;
         for (int g = tid; g < s; g += T) {
             cplx* p0 = a + conv_pad(g);
-            const cplx w1 = twiddle<M>(lo, hi, g);
-            const cplx t1 = INV ? conj(w1) : w1, t2 = cmul(t1, t1), t3 = cmul(t2, t1);
             if (!INV) {
                 const cplx v0 = p0[0], v1 = p0[sp], r = mul_neg_i(v1);
                 p0[0] = cadd(v0, v1);
-                p0[sp] = cmul(cadd(v0, r), t1);
-                p0[2 * sp] = cmul(csub(v0, v1), t2);
-                p0[3 * sp] = cmul(csub(v0, r), t3);
+                p0[sp] = cadd(v0, r);
+                p0[2 * sp] = csub(v0, v1);
+                p0[3 * sp] = csub(v0, r);
             } else {
-                const cplx v0 = p0[0], v1 = cmul(p0[sp], t1), v2 = cmul(p0[2 * sp], t2), v3 = cmul(p0[3 * sp], t3);
-                const cplx s02 = cadd(v0, v2), d02 = csub(v0, v2), s13 = cadd(v1, v3), d13 = csub(v1, v3);
-                p0[0] = cadd(s02, s13);
-                p0[sp] = cadd(d02, mul_pos_i(d13));
+                const cplx t1 = conj(twiddle<M>(lo, hi, g)), t2 = cmul(t1, t1), t3 = cmul(t2, t1);
+                cplx v0 = p0[0], v1 = cmul(p0[sp], t1), v2 = p0[2 * sp], v3 = p0[3 * sp];
+                bfly(v0, v2, t2.x, t2.y);
+                bfly(v1, v3, t3.x, t3.y);
+                p0[0] = cadd(v0, v1);
+                p0[sp] = cadd(v2, mul_pos_i(v3));
             }
         }
     };
     if (!INV) {
-        if (conv_lead4(M)) { lead4(); __syncthreads(); }
-        if (M16 == 4096) { pass16<M, T, 4096, false>(a, lo, hi, tid); __syncthreads(); }
-        pass16<M, T, 256, false>(a, lo, hi, tid);
+        if (L4) { lead4(); __syncthreads(); }
+        if (M16 == 4096) { pass16<M, T, 4096, false, !L4>(a, lo, hi, tid); __syncthreads(); }
+        pass16<M, T, 256, false, !L4 && M16 == 256>(a, lo, hi, tid);
         __syncthreads();
-        pass16<M, T, 16, false>(a, lo, hi, tid);
+        pass16<M, T, 16, false, false>(a, lo, hi, tid);
     } else {
-        pass16<M, T, 16, true>(a, lo, hi, tid);
+        pass16<M, T, 16, true, false>(a, lo, hi, tid);
         __syncthreads();
-        pass16<M, T, 256, true>(a, lo, hi, tid);
-        if (M16 == 4096) { __syncthreads(); pass16<M, T, 4096, true>(a, lo, hi, tid); }
-        if (conv_lead4(M)) { __syncthreads(); lead4(); }
+        pass16<M, T, 256, true, !L4 && M16 == 256>(a, lo, hi, tid);
+        if (M16 == 4096) { __syncthreads(); pass16<M, T, 4096, true, !L4>(a, lo, hi, tid); }
+        if (L4) { __syncthreads(); lead4(); }
     }
 }
 
@@ -356,14 +393,15 @@ struct SeqRegs {
 };
 
 // x (one sequence of L steps, in registers) -> optional short kernel and activation -> packed complex
-// z[n] = v[2n] + i v[2n+1] in a[], zero beyond L.  Ends with the data in place but NOT synchronised.
+// z[n] = v[2n] + i v[2n+1], n < M/2, in a[], zero beyond L (the upper half, all zeros, is never read).  Ends with the
+// data in place but NOT synchronised.
 // hist (only read with a short kernel): null for a sequence's first step (zero history), else a pointer at the first
 // of these L steps inside a longer row, whose 32 predecessors are then the history.
 template <int M, int T, typename IO>
 __device__ __forceinline__ void stage_input(const SeqRegs<M, T, IO>& x, const float* __restrict__ wc, int m, int L,
                                             cplx* a, int tid, const IO* __restrict__ hist = nullptr)
 {
-    constexpr int PER = M / T, HELD = PER / 2;
+    constexpr int HELD = M / T / 2;
     if (wc != nullptr) {
         // raw x as floats behind 32 steps of history (zeros at a sequence's start), so that no tap needs a bounds check
         float* sx = reinterpret_cast<float*>(a);
@@ -405,12 +443,12 @@ __device__ __forceinline__ void stage_input(const SeqRegs<M, T, IO>& x, const fl
         }
         __syncthreads();
 #pragma unroll
-        for (int i = 0; i < PER; ++i) a[conv_pad(tid + T * i)] = i < HELD ? z[i < HELD ? i : 0] : mk(0.f, 0.f);
+        for (int i = 0; i < HELD; ++i) a[conv_pad(tid + T * i)] = z[i];
     } else {
 #pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            float v0 = 0.f, v1 = 0.f;
-            if (i < HELD) IoPair<IO>::unpack(x.r[i < HELD ? i : 0], v0, v1);
+        for (int i = 0; i < HELD; ++i) {
+            float v0, v1;
+            IoPair<IO>::unpack(x.r[i], v0, v1);
             a[conv_pad(tid + T * i)] = mk(v0, v1);
         }
     }
