@@ -3,6 +3,7 @@
 #include "../../include/chela.h"
 #include "../../include/chela_bench.h"
 #include "chela_internal.h"
+#include <algorithm>
 #include <cmath>
 
 #include <cstdlib>
@@ -124,7 +125,7 @@ Plan make_plan(long BH, int N, int dk, int dv, int chunk, int dtype, bool is_bwd
     if ((n_chunks + cps - 1) / cps > 32768) cps = (n_chunks + 32767) / 32768;   // segments ride on grid.y
     p.seg_len = (int)(cps * chunk);
     p.n_seg = (int)((n_chunks + cps - 1) / cps);
-    const int n_states = (dtype == CHELA_DTYPE_BF16 && is_bwd) ? 2 : 1;   // fp32 bwd reuses one array 3 times
+    const int n_states = (dtype == CHELA_DTYPE_BF16 && is_bwd) ? 2 : 1;   // (the fp32 backward: make_f32_bwd_plan)
     // a carried-in state goes through the scan even when there is a single segment
     if (p.n_seg > 1 || stateful) {
         p.ckpt_every = 0;
@@ -132,6 +133,27 @@ Plan make_plan(long BH, int N, int dk, int dv, int chunk, int dtype, bool is_bwd
     } else {
         p.ws_bytes = (size_t)BH * (size_t)plan_n_ckpt(p, N) * p.state_elems * sizeof(float);
     }
+    return p;
+}
+
+// The fp32 backward is one launch of three forward-shaped sweeps: three workgroups per segment share the GPU, so it is
+// split like a forward over three times as many sequences, with two states per segment and sequence.  The scratch it
+// insists on is what one array of states takes when the sequences are split on their own; a caller-owned buffer between
+// that and the full need gets fewer segments.
+Plan make_f32_bwd_plan(long BH, int N, int dk, int dv, int chunk, size_t ws_limit)
+{
+    Plan p = make_plan(3 * BH, N, dk, dv, chunk, CHELA_DTYPE_F32, false, false);
+    const size_t least = make_plan(BH, N, dk, dv, chunk, CHELA_DTYPE_F32, true, false).ws_bytes;
+    const size_t state = BH > 0 ? (size_t)BH * p.state_elems * sizeof(float) : 0;
+    // (and never more than one state per sequence and 32 tokens)
+    const size_t room = std::max(least, std::min(ws_limit, state * (((size_t)(N > 0 ? N : 0) + 31) / 32)));
+    if (p.n_seg > 1 && (size_t)p.n_seg * 2 * state > room) {
+        const long n_chunks = ((long)N + chunk - 1) / chunk, n = std::max(1L, (long)(room / (2 * state)));
+        const long cps = (n_chunks + n - 1) / n;
+        p.seg_len = (int)(cps * chunk);
+        p.n_seg = (int)((n_chunks + cps - 1) / cps);
+    }
+    p.ws_bytes = std::max(least, p.n_seg > 1 ? (size_t)p.n_seg * 2 * state : 0);
     return p;
 }
 
@@ -240,6 +262,9 @@ static constexpr int kMaxDev = 64;
 struct OwnWs { hipStream_t stream; void* ptr; size_t bytes; };
 static constexpr size_t kMaxOwnStreams = 64;    // per device
 static std::vector<OwnWs> g_own_ws[kMaxDev];
+
+// What a call may ask get_workspace() for without being refused on account of a caller-owned buffer.
+static size_t workspace_limit() { return t_user_ws ? t_user_bytes : ~(size_t)0; }
 
 static int get_workspace(size_t bytes, void* stream, float** out)
 {
@@ -398,8 +423,8 @@ static int fwd_common(const void* Q, const void* K, const void* V, void* O, cons
     if (rc != CHELA_OK) return rc;
     hipError_t e = dtype == CHELA_DTYPE_BF16
         ? launch_bf16_fwd(Q, K, V, O, S_in, S_out, nullptr, 1, BH, N, dk, dv, plan, ws, (hipStream_t)stream)
-        : launch_f32((const float*)Q, (const float*)K, (const float*)V, (float*)O, BH, N, dk, dv, plan, false, ws,
-                     (hipStream_t)stream);
+        : launch_f32_fwd((const float*)Q, (const float*)K, (const float*)V, (float*)O, BH, N, dk, dv, plan, ws,
+                         (hipStream_t)stream);
     return e == hipSuccess ? CHELA_OK : CHELA_ERR_HIP;
 }
 
@@ -438,26 +463,12 @@ static int bwd_common(const void* Q, const void* K, const void* V, const void* d
         hipError_t e = launch_bf16_bwd(Q, K, V, dO, S_in, dS_out, dQ, dK, dV, dS_in, nullptr, BH, N, dk, dv, plan, ws, st);
         return e == hipSuccess ? CHELA_OK : CHELA_ERR_HIP;
     }
-    // fp32: the gradient is three instances of the forward map (time-reversal duality):
-    //   dQ = LinAttn(query dO, key V, value K)             causal
-    //   dV = LinAttn(query K,  key Q, value dO)            anti-causal
-    //   dK = LinAttn(query V,  key dO, value Q)            anti-causal
-    const int c1 = f32_effective_chunk(dv, dk, chunk);   // query/key width dv, value width dk
-    const int c2 = f32_effective_chunk(dk, dv, chunk);
-    Plan p1 = make_plan(BH, N, dv, dk, c1, dtype, true, false);
-    Plan p2 = make_plan(BH, N, dk, dv, c2, dtype, true, false);
+    const Plan plan = make_f32_bwd_plan(BH, N, dk, dv, f32_effective_chunk(dk, dv, chunk), workspace_limit());
     float* ws = nullptr;
-    rc = get_workspace(p1.ws_bytes > p2.ws_bytes ? p1.ws_bytes : p2.ws_bytes, stream, &ws);
+    rc = get_workspace(plan.ws_bytes, stream, &ws);
     if (rc != CHELA_OK) return rc;
-    hipError_t e = launch_f32((const float*)dO, (const float*)V, (const float*)K, (float*)dQ, BH, N, dv, dk, p1,
-                              false, ws, st);
-    if (e == hipSuccess)
-        e = launch_f32((const float*)K, (const float*)Q, (const float*)dO, (float*)dV, BH, N, dk, dv, p2, true, ws, st);
-    // the third call's segment states dO^T Q are the transposes of the second call's Q^T dO, which are still there
-    const bool same_split = p1.n_seg == p2.n_seg && p1.seg_len == p2.seg_len;
-    if (e == hipSuccess)
-        e = launch_f32((const float*)V, (const float*)dO, (const float*)Q, (float*)dK, BH, N, dv, dk, p1, true, ws, st,
-                       same_split);
+    hipError_t e = launch_f32_bwd((const float*)Q, (const float*)K, (const float*)V, (const float*)dO, (float*)dQ,
+                                  (float*)dK, (float*)dV, BH, N, dk, dv, plan, ws, st);
     return e == hipSuccess ? CHELA_OK : CHELA_ERR_HIP;
 }
 
@@ -1026,12 +1037,9 @@ size_t chela_linattn_workspace_bytes(int B, int H, int N, int dk, int dv, int ch
     }
     if (dtype != CHELA_DTYPE_F32) return 0;
     if (!(chunk == 16 || chunk == 32 || chunk == 64)) return 0;
-    size_t a = make_plan((long)B * H, N, dk, dv, f32_effective_chunk(dk, dv, chunk), dtype, is_bwd != 0, false).ws_bytes;
-    if (is_bwd) {
-        size_t b = make_plan((long)B * H, N, dv, dk, f32_effective_chunk(dv, dk, chunk), dtype, true, false).ws_bytes;
-        if (b > a) a = b;
-    }
-    return a;
+    const int c = f32_effective_chunk(dk, dv, chunk);
+    return is_bwd ? make_f32_bwd_plan((long)B * H, N, dk, dv, c, ~(size_t)0).ws_bytes
+                  : make_plan((long)B * H, N, dk, dv, c, dtype, false, false).ws_bytes;
 }
 
 size_t chela_linattn_train_workspace_bytes(int B, int H, int N, int dk, int dv, int chunk, int is_bwd)

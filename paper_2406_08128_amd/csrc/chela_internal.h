@@ -59,10 +59,13 @@ hipError_t launch_stream_probe(const void* const* in, int n_in, void* const* out
 // Matrix-core rate probe: blocks * 4 waves, each issuing iters * 16 bf16 32x32x16 matrix instructions; out: blocks * 256 floats.
 hipError_t launch_mfma_probe(float* out, int blocks, int iters, hipStream_t st);
 
-// fp32 path.  `rev` runs the same map on the time-reversed sequence (anti-causal mask), which is what the
-// gradient with respect to K and V is (the backward is three calls of this launcher).
-hipError_t launch_f32(const float* Q, const float* K, const float* V, float* O, long BH, int N, int dk, int dv,
-                      const Plan& plan, bool rev, float* ws, hipStream_t st, bool reuse_states_T = false);
+// fp32 path.  The backward's three maps share one plan (make_f32_bwd_plan) and, with more than one segment, two arrays of
+// states.  ws_limit: scratch there is.
+Plan make_f32_bwd_plan(long BH, int N, int dk, int dv, int chunk, size_t ws_limit);
+hipError_t launch_f32_fwd(const float* Q, const float* K, const float* V, float* O, long BH, int N, int dk, int dv,
+                          const Plan& plan, float* ws, hipStream_t st);
+hipError_t launch_f32_bwd(const float* Q, const float* K, const float* V, const float* dO, float* dQ, float* dK, float* dV,
+                          long BH, int N, int dk, int dv, const Plan& plan, float* ws, hipStream_t st);
 
 // bf16 path.  S_in / S_out / dS_out / dS_in: optional carried states and their gradients, [BH][dk][dv] fp32.
 // saved (optional): the forward writes the running state at the end of every save_every-th of its segments and of

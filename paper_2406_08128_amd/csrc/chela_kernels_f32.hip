@@ -247,17 +247,36 @@ __device__ __forceinline__ f32x16 zero16f()
 // Logical position p (0 = first token the causal sum sees) to physical row of the [N, d] matrix.
 __device__ __forceinline__ int phys_row(int p, int N, bool rev) { return rev ? (N - 1 - p) : p; }
 
-// acc[32x32] += A B over K2 values of k.
+// acc[32x32] += A B over K2 values of k (a multiple of 16).
 //   A element (m, k): a_base[(m) * a_rs + (k) * a_ks]   B element (k, n): b_base[(k) * b_ks + (n) * b_ns]
 // with m = lane%32 (+ tile offset folded into the base), n = lane%32, k = k0 + lane/32, k0 stepping by 2.
+// The operands of the next eight instructions are read while the current eight run: a wave has one or two others
+// on its SIMD to hide behind, and an LDS round trip costs as much as two of the instructions.
+template <int K2>
 __device__ __forceinline__ f32x16 gemm_tile(f32x16 acc, const float* a_base, int a_rs, int a_ks, const float* b_base,
-                                            int b_ks, int b_ns, int K2, int lane)
+                                            int b_ks, int b_ns, int lane)
 {
+    constexpr int G = 8, NG = K2 / (2 * G);
     const int r = lane & 31, h = lane >> 5;
     const float* pa = a_base + r * a_rs + h * a_ks;
     const float* pb = b_base + h * b_ks + r * b_ns;
-#pragma unroll 8
-    for (int k0 = 0; k0 < K2; k0 += 2) acc = mfma_f32(pa[k0 * a_ks], pb[k0 * b_ks], acc);
+    float a[2][G], b[2][G];
+#pragma unroll
+    for (int u = 0; u < G; ++u) { a[0][u] = pa[2 * u * a_ks]; b[0][u] = pb[2 * u * b_ks]; }
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+        if (g + 1 < NG) {
+#pragma unroll
+            for (int u = 0; u < G; ++u) {
+                a[(g + 1) & 1][u] = pa[2 * (G * (g + 1) + u) * a_ks];
+                b[(g + 1) & 1][u] = pb[2 * (G * (g + 1) + u) * b_ks];
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int u = 0; u < G; ++u) acc = mfma_f32(a[g & 1][u], b[g & 1][u], acc);
+        __builtin_amdgcn_sched_barrier(0);
+    }
     return acc;
 }
 
@@ -291,15 +310,18 @@ struct TileRegsF32 {
 // ------------------------------------------------------------------------------------------------ segment totals
 // out[bh][seg][i*DV + j] = sum over the segment's tokens of K[t][i] * V[t][j].  The last segment's total is never
 // used by an exclusive prefix, so its workgroups leave at once.  Wave w owns output tiles w, w+4, ...
+constexpr int kF32SegRows = 64;                 // tokens staged per step
+constexpr int f32_seg_lds(int dk, int dv) { return kF32SegRows * (dk + dv + 2); }     // floats
+
 template <int DK, int DV>
-__global__ __launch_bounds__(256) void f32_seg_state_kernel(const float* __restrict__ K, const float* __restrict__ V,
-                                                           float* __restrict__ out, int N, int seg_len, int n_seg,
-                                                           int rev)
+__device__ __forceinline__ void f32_seg_state_body(const float* __restrict__ K, const float* __restrict__ V,
+                                                   float* __restrict__ out, int N, int seg_len, int n_seg, bool rev,
+                                                   float* lds)
 {
-    constexpr int R = 32;                         // tokens staged per step
+    constexpr int R = kF32SegRows;
     constexpr int LDK = DK + 1, LDV = DV + 1;
-    __shared__ float sK[R * LDK];
-    __shared__ float sV[R * LDV];
+    float* sK = lds;
+    float* sV = lds + R * LDK;
     const int seg = blockIdx.y;
     const long bh = blockIdx.x;
     if (seg == n_seg - 1) return;
@@ -312,24 +334,30 @@ __global__ __launch_bounds__(256) void f32_seg_state_kernel(const float* __restr
     f32x16 acc[NT];
 #pragma unroll
     for (int n = 0; n < NT; ++n) acc[n] = zero16f();
-    TileRegsF32<R, DK> rk;
-    TileRegsF32<R, DV> rv;
-    rk.fetch(Kb, p0, p1, N, rev, tid);
-    rv.fetch(Vb, p0, p1, N, rev, tid);
-    for (int c0 = p0; c0 < p1; c0 += R) {
-        __syncthreads();
-        rk.stash(sK, tid);
-        rv.stash(sV, tid);
-        __syncthreads();
-        if (c0 + R < p1) {     // the next step's rows, in flight during the products
-            rk.fetch(Kb, c0 + R, p1, N, rev, tid);
-            rv.fetch(Vb, c0 + R, p1, N, rev, tid);
-        }
+    // two steps' rows in flight: a step's products are over before one round trip to memory is
+    TileRegsF32<R, DK> rk[2];
+    TileRegsF32<R, DV> rv[2];
 #pragma unroll
-        for (int n = 0; n < NT; ++n) {
-            const int id = w + 4 * n, ib = id / JB, jb = id % JB;
-            // A[m=i][k=s] = K[s][i]: contiguous in i;  B[k=s][n=j] = V[s][j]: contiguous in j
-            acc[n] = gemm_tile(acc[n], sK + ib * 32, 1, LDK, sV + jb * 32, LDV, 1, R, lane);
+    for (int u = 0; u < 2; ++u) { rk[u].fetch(Kb, p0 + u * R, p1, N, rev, tid); rv[u].fetch(Vb, p0 + u * R, p1, N, rev, tid); }
+    for (int cc = p0; cc < p1; cc += 2 * R) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const int c0 = cc + u * R;
+            if (c0 >= p1) break;
+            __syncthreads();
+            rk[u].stash(sK, tid);
+            rv[u].stash(sV, tid);
+            __syncthreads();
+            if (c0 + 2 * R < p1) {
+                rk[u].fetch(Kb, c0 + 2 * R, p1, N, rev, tid);
+                rv[u].fetch(Vb, c0 + 2 * R, p1, N, rev, tid);
+            }
+#pragma unroll
+            for (int n = 0; n < NT; ++n) {
+                const int id = w + 4 * n, ib = id / JB, jb = id % JB;
+                // A[m=i][k=s] = K[s][i]: contiguous in i;  B[k=s][n=j] = V[s][j]: contiguous in j
+                acc[n] = gemm_tile<R>(acc[n], sK + ib * 32, 1, LDK, sV + jb * 32, LDV, 1, lane);
+            }
         }
     }
     float* o = out + ((size_t)bh * n_seg + seg) * DK * DV;
@@ -344,27 +372,54 @@ __global__ __launch_bounds__(256) void f32_seg_state_kernel(const float* __restr
     }
 }
 
+template <int DK, int DV>
+__global__ __launch_bounds__(256) void f32_seg_state_kernel(const float* __restrict__ K, const float* __restrict__ V,
+                                                           float* __restrict__ out, int N, int seg_len, int n_seg)
+{
+    __shared__ float lds[f32_seg_lds(DK, DV)];
+    f32_seg_state_body<DK, DV>(K, V, out, N, seg_len, n_seg, false, lds);
+}
+
+// The backward's two sets of totals, V^T K in reading order and Q^T dO from the end, side by side on grid.z.
+template <int DK, int DV>
+__global__ __launch_bounds__(256) void f32_bwd_seg_state_kernel(const float* __restrict__ Q, const float* __restrict__ K,
+                                                               const float* __restrict__ V, const float* __restrict__ dO,
+                                                               float* __restrict__ out, size_t array_stride, int N,
+                                                               int seg_len, int n_seg)
+{
+    __shared__ float lds[f32_seg_lds(DK, DV)];
+    if (blockIdx.z == 0) f32_seg_state_body<DV, DK>(V, K, out, N, seg_len, n_seg, false, lds);
+    else f32_seg_state_body<DK, DV>(Q, dO, out + array_stride, N, seg_len, n_seg, true, lds);
+}
+
 // ------------------------------------------------------------------------------------------------ main sweep
 // One workgroup (4 waves) per (segment, bh).  Wave w owns output rows [32*tb, +32) with tb = w % WT and NJ column
 // tiles, and the state tiles w, w+4, ...  LDS: Q, K [C][DK+1]; V [C][DV+1]; S [DK][DV+1]; P [C][C+1] in K's place.
+constexpr int f32_sweep_chunk(int dk, int dv) { return dk == 128 && dv == 128 ? 32 : 64; }   // what fits 160 KB of LDS
+// The score tile P takes over K's place once K has done its two jobs (scores, state update): five tiles would be
+// 83 KB at the 64-wide shape and leave a compute unit to a single workgroup, four leave room for two.
+constexpr int f32_sweep_kp(int c, int dk) { return c * (dk + 1) > c * (c + 1) ? c * (dk + 1) : c * (c + 1); }
+constexpr int f32_sweep_lds(int dk, int dv)                                                  // floats
+{
+    const int c = f32_sweep_chunk(dk, dv);
+    return c * (dk + 1) + f32_sweep_kp(c, dk) + c * (dv + 1) + dk * (dv + 1);
+}
+
 template <int C, int DK, int DV>
-__global__ __launch_bounds__(256) void f32_sweep_kernel(const float* __restrict__ Q, const float* __restrict__ K,
-                                                       const float* __restrict__ V, float* __restrict__ O,
-                                                       const float* __restrict__ S0, int N, int seg_len, int n_seg,
-                                                       int rev, int s0_transposed)
+__device__ __forceinline__ void f32_sweep_body(const float* __restrict__ Q, const float* __restrict__ K,
+                                               const float* __restrict__ V, float* __restrict__ O,
+                                               const float* __restrict__ S0, int N, int seg_len, int n_seg, bool rev,
+                                               bool s0_transposed, float* lds)
 {
     constexpr int LDK = DK + 1, LDV = DV + 1, LDP = C + 1;
     constexpr int TB = C / 32, JB = DV / 32, IB = DK / 32;
     constexpr int WT = TB < 4 ? TB : 4, WJ = 4 / WT, NJ = JB / WJ;
     constexpr int NS = IB * JB / 4;
     static_assert(JB % WJ == 0, "unsupported tile shape");
-    // The score tile P takes over K's place once K has done its two jobs (scores, state update): five tiles would be
-    // 83 KB at the 64-wide shape and leave a compute unit to a single workgroup, four leave room for two.
-    constexpr int KP = C * LDK > C * LDP ? C * LDK : C * LDP;
-    __shared__ float sQ[C * LDK];
-    __shared__ float sKP[KP];
-    __shared__ float sV[C * LDV];
-    __shared__ float sS[DK * LDV];
+    float* sQ = lds;
+    float* sKP = sQ + C * LDK;
+    float* sV = sKP + f32_sweep_kp(C, DK);
+    float* sS = sV + C * LDV;
     float* sK = sKP;
     float* sP = sKP;
     const int seg = blockIdx.y;
@@ -438,7 +493,7 @@ __global__ __launch_bounds__(256) void f32_sweep_kernel(const float* __restrict_
         for (int sb = 0; sb < TB; ++sb) {
             // A[m=t][k=i] = Q[t][i] (row walk), B[k=i][n=s] = K[s][i] (row walk)
             if (sb <= tb && sb % WJ == jg)
-                pt[sb / WJ] = gemm_tile(zero16f(), sQ + tb * 32 * LDK, LDK, 1, sK + sb * 32 * LDK, 1, LDK, DK, lane);
+                pt[sb / WJ] = gemm_tile<DK>(zero16f(), sQ + tb * 32 * LDK, LDK, 1, sK + sb * 32 * LDK, 1, LDK, lane);
         }
         // state update S += K^T V (not needed after the segment's last chunk); the published copy in sS is the state
         // BEFORE this chunk, which is what the output below needs
@@ -446,7 +501,7 @@ __global__ __launch_bounds__(256) void f32_sweep_kernel(const float* __restrict_
 #pragma unroll
             for (int n = 0; n < NS; ++n) {
                 const int id = w + 4 * n, ib = id / JB, jb = id % JB;
-                accS[n] = gemm_tile(accS[n], sK + ib * 32, 1, LDK, sV + jb * 32, LDV, 1, C, lane);
+                accS[n] = gemm_tile<C>(accS[n], sK + ib * 32, 1, LDK, sV + jb * 32, LDV, 1, lane);
             }
         }
         __syncthreads();   // K has been read for the last time: its place now takes the scores
@@ -469,9 +524,12 @@ __global__ __launch_bounds__(256) void f32_sweep_kernel(const float* __restrict_
         for (int n = 0; n < NJ; ++n) {
             const int j0 = (jg * NJ + n) * 32;
             // inter-chunk part Q S_prev: A = Q rows (row walk), B[k=i][n=j] = S[i][j] (contiguous)
-            accO[n] = gemm_tile(zero16f(), sQ + tb * 32 * LDK, LDK, 1, sS + j0, LDV, 1, DK, lane);
+            accO[n] = gemm_tile<DK>(zero16f(), sQ + tb * 32 * LDK, LDK, 1, sS + j0, LDV, 1, lane);
             // intra-chunk part P V over the key blocks sb <= tb: A = P rows (row walk), B[k=s][n=j] = V[s][j]
-            accO[n] = gemm_tile(accO[n], sP + tb * 32 * LDP, LDP, 1, sV + j0, LDV, 1, (tb + 1) * 32, lane);
+            #pragma unroll
+            for (int sb = 0; sb < TB; ++sb)
+                if (sb <= tb)
+                    accO[n] = gemm_tile<32>(accO[n], sP + tb * 32 * LDP + sb * 32, LDP, 1, sV + sb * 32 * LDV + j0, LDV, 1, lane);
 #pragma unroll
             for (int a = 0; a < 4; ++a)
 #pragma unroll
@@ -486,40 +544,107 @@ __global__ __launch_bounds__(256) void f32_sweep_kernel(const float* __restrict_
 }
 
 template <int DK, int DV>
-static hipError_t launch_f32_impl(const float* Q, const float* K, const float* V, float* O, long BH, int N,
-                                  const Plan& plan, bool rev, bool reuse_states_T, float* ws, hipStream_t st)
+__global__ __launch_bounds__(256) void f32_sweep_kernel(const float* __restrict__ Q, const float* __restrict__ K,
+                                                       const float* __restrict__ V, float* __restrict__ O,
+                                                       const float* __restrict__ S0, int N, int seg_len, int n_seg)
+{
+    __shared__ float lds[f32_sweep_lds(DK, DV)];
+    f32_sweep_body<f32_sweep_chunk(DK, DV), DK, DV>(Q, K, V, O, S0, N, seg_len, n_seg, false, false, lds);
+}
+
+// The gradient is three instances of the forward map (time-reversal duality), independent of one another, so they ride
+// on grid.z of one launch:
+//   dQ = LinAttn(query dO, key V, value K)             causal          states V^T K   (first array)
+//   dK = LinAttn(query V,  key dO, value Q)            anti-causal     states dO^T Q  (the second array, transposed)
+//   dV = LinAttn(query K,  key Q, value dO)            anti-causal     states Q^T dO  (second array)
+// Bound by the fp32 matrix rate (24 heads x 3001 tokens, 64 x 64: 97 M matrix cycles of 197 M that the launch lasts; the
+// rest is barriers and the unequal shares of the causal triangle): as three launches, each with its own pre-pass and
+// scan and 240 workgroups for 512 places, the gradient took 148 us, side by side with 504 workgroups 104 us.
+template <int DK, int DV>
+__global__ __launch_bounds__(256) void f32_bwd_sweep_kernel(const float* __restrict__ Q, const float* __restrict__ K,
+                                                           const float* __restrict__ V, const float* __restrict__ dO,
+                                                           float* __restrict__ dQ, float* __restrict__ dK,
+                                                           float* __restrict__ dV, const float* __restrict__ S0,
+                                                           size_t array_stride, int N, int seg_len, int n_seg)
+{
+    constexpr int C = f32_sweep_chunk(DK, DV);
+    constexpr int LA = f32_sweep_lds(DK, DV), LB = f32_sweep_lds(DV, DK);
+    __shared__ float lds[LA > LB ? LA : LB];
+    const int z = blockIdx.z;
+    const float* S1 = S0 != nullptr ? S0 + array_stride : nullptr;
+    if constexpr (DK == DV) {
+        f32_sweep_body<C, DK, DV>(z == 0 ? dO : z == 1 ? V : K, z == 0 ? V : z == 1 ? dO : Q, z == 0 ? K : z == 1 ? Q : dO,
+                                  z == 0 ? dQ : z == 1 ? dK : dV, z == 0 ? S0 : S1, N, seg_len, n_seg, z != 0, z == 1, lds);
+    } else if (z < 2) {
+        f32_sweep_body<C, DV, DK>(z == 0 ? dO : V, z == 0 ? V : dO, z == 0 ? K : Q, z == 0 ? dQ : dK, z == 0 ? S0 : S1, N,
+                                  seg_len, n_seg, z != 0, z == 1, lds);
+    } else {
+        f32_sweep_body<C, DK, DV>(K, Q, dO, dV, S1, N, seg_len, n_seg, true, false, lds);
+    }
+}
+
+template <int DK, int DV>
+static hipError_t f32_fwd_impl(const float* Q, const float* K, const float* V, float* O, long BH, int N, const Plan& plan,
+                               float* ws, hipStream_t st)
 {
     hipError_t e;
-    constexpr int C = (DK == 128 && DV == 128) ? 32 : 64;   // what fits 160 KB of LDS
-    if (plan.n_seg > 1 && !reuse_states_T) {
-        dim3 grid((unsigned)BH, plan.n_seg);
+    const dim3 grid((unsigned)BH, plan.n_seg);
+    if (plan.n_seg > 1) {
         {
             ProfScope prof(KID_SEG_STATE_F32, st);
             hipLaunchKernelGGL((f32_seg_state_kernel<DK, DV>), grid, dim3(256), 0, st, K, V, ws, N, plan.seg_len,
-                               plan.n_seg, (int)rev);
+                               plan.n_seg);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
         const int mode = SCAN_EXCL_PREFIX;
         if ((e = scan_states(ws, 0, 1, &mode, nullptr, 0, BH, plan.n_seg, DK * DV, st)) != hipSuccess) return e;
     }
-    dim3 grid((unsigned)BH, plan.n_seg);
     ProfScope prof(KID_SWEEP_F32, st);
-    hipLaunchKernelGGL((f32_sweep_kernel<C, DK, DV>), grid, dim3(256), 0, st, Q, K, V, O, plan.n_seg > 1 ? ws : nullptr,
-                       N, plan.seg_len, plan.n_seg, (int)rev, (int)reuse_states_T);
+    hipLaunchKernelGGL((f32_sweep_kernel<DK, DV>), grid, dim3(256), 0, st, Q, K, V, O, plan.n_seg > 1 ? ws : nullptr, N,
+                       plan.seg_len, plan.n_seg);
     return hipGetLastError();
 }
 
-// reuse_states_T: the workspace already holds the scanned segment states of a call with the same split whose keys
-// and values were this call's values and keys (so each state is the transpose of what this call needs): no pre-pass,
-// no scan, the sweep reads them transposed.
-hipError_t launch_f32(const float* Q, const float* K, const float* V, float* O, long BH, int N, int dk, int dv,
-                      const Plan& plan, bool rev, float* ws, hipStream_t st, bool reuse_states_T)
+template <int DK, int DV>
+static hipError_t f32_bwd_impl(const float* Q, const float* K, const float* V, const float* dO, float* dQ, float* dK,
+                               float* dV, long BH, int N, const Plan& plan, float* ws, hipStream_t st)
 {
-    if (dk == 64 && dv == 64) return launch_f32_impl<64, 64>(Q, K, V, O, BH, N, plan, rev, reuse_states_T, ws, st);
-    if (dk == 64 && dv == 128) return launch_f32_impl<64, 128>(Q, K, V, O, BH, N, plan, rev, reuse_states_T, ws, st);
-    if (dk == 128 && dv == 64) return launch_f32_impl<128, 64>(Q, K, V, O, BH, N, plan, rev, reuse_states_T, ws, st);
-    if (dk == 128 && dv == 128) return launch_f32_impl<128, 128>(Q, K, V, O, BH, N, plan, rev, reuse_states_T, ws, st);
-    return hipErrorInvalidValue;
+    hipError_t e;
+    const size_t stride = (size_t)BH * plan.n_seg * DK * DV;
+    if (plan.n_seg > 1) {
+        {
+            ProfScope prof(KID_SEG_STATE_F32, st);
+            hipLaunchKernelGGL((f32_bwd_seg_state_kernel<DK, DV>), dim3((unsigned)BH, plan.n_seg, 2), dim3(256), 0, st, Q, K,
+                               V, dO, ws, stride, N, plan.seg_len, plan.n_seg);
+        }
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        const int modes[2] = {SCAN_EXCL_PREFIX, SCAN_EXCL_PREFIX};
+        if ((e = scan_states(ws, stride, 2, modes, nullptr, 0, BH, plan.n_seg, DK * DV, st)) != hipSuccess) return e;
+    }
+    ProfScope prof(KID_SWEEP_F32, st);
+    hipLaunchKernelGGL((f32_bwd_sweep_kernel<DK, DV>), dim3((unsigned)BH, plan.n_seg, 3), dim3(256), 0, st, Q, K, V, dO, dQ,
+                       dK, dV, plan.n_seg > 1 ? ws : nullptr, stride, N, plan.seg_len, plan.n_seg);
+    return hipGetLastError();
 }
+
+#define CHELA_F32_DIMS(F_, ...)                                                                                        \
+    if (dk == 64 && dv == 64) return F_<64, 64>(__VA_ARGS__);                                                          \
+    if (dk == 64 && dv == 128) return F_<64, 128>(__VA_ARGS__);                                                        \
+    if (dk == 128 && dv == 64) return F_<128, 64>(__VA_ARGS__);                                                        \
+    if (dk == 128 && dv == 128) return F_<128, 128>(__VA_ARGS__);                                                      \
+    return hipErrorInvalidValue;
+
+hipError_t launch_f32_fwd(const float* Q, const float* K, const float* V, float* O, long BH, int N, int dk, int dv,
+                          const Plan& plan, float* ws, hipStream_t st)
+{
+    CHELA_F32_DIMS(f32_fwd_impl, Q, K, V, O, BH, N, plan, ws, st)
+}
+
+hipError_t launch_f32_bwd(const float* Q, const float* K, const float* V, const float* dO, float* dQ, float* dK, float* dV,
+                          long BH, int N, int dk, int dv, const Plan& plan, float* ws, hipStream_t st)
+{
+    CHELA_F32_DIMS(f32_bwd_impl, Q, K, V, dO, dQ, dK, dV, BH, N, plan, ws, st)
+}
+#undef CHELA_F32_DIMS
 
 }  // namespace chela

@@ -410,6 +410,34 @@ def test_caller_workspace_and_side_stream():
         binding.chela_set_workspace(None)
 
 
+@pytest.mark.parametrize("dims", [(64, 64), (64, 128), (128, 64), (128, 128)])
+def test_f32_backward_takes_fewer_segments_in_a_smaller_scratch_buffer(dims):
+    # the full need and ever less: fewer segments and the same gradient, down to where the call is refused
+    w = _small("f32", N=3001, B=2, H=12, dk=dims[0], dv=dims[1], seed=77)
+    x = make_inputs(w)
+    d = _dev(x)
+    full = binding.chela_linattn_workspace_bytes(w.B, w.H, w.N, w.dk, w.dv, 64, True, binding.DTYPE_F32)
+    state = w.B * w.H * w.dk * w.dv * 4
+    refs = oracle.bwd_recurrent(*(to_f64_numpy(x[n]) for n in ("Q", "K", "V", "dO")))
+    refused = 0
+    buf = torch.empty(full, dtype=torch.uint8, device="cuda")
+    try:
+        for n in (full, full - 1, full - 2 * state, full * 3 // 4, full // 2, state):
+            binding.chela_set_workspace(buf[:n])
+            try:
+                got = binding.chela_linattn_bwd(d["Q"], d["K"], d["V"], d["dO"])
+            except binding.ChelaError as e:
+                assert e.status == -7 and n < full
+                refused += 1
+                continue
+            assert not refused
+            for name, g, r in zip(("dQ", "dK", "dV"), got, refs):
+                _check(name, g, r, "f32")
+    finally:
+        binding.chela_set_workspace(None)
+    assert refused >= 1
+
+
 def test_two_streams_with_a_scratch_buffer_each():
     # calls that overlap in time on two streams, each enqueued while its own buffer is the one in force
     wa, wb = _small("bf16", N=5000, B=2, H=3, seed=41), _small("bf16", N=7000, B=1, H=5, seed=42)
