@@ -867,7 +867,7 @@ size_t chela_longconv_spectrum_bytes(int d, int L)
 {
     const int M = (d > 0 && L > 0) ? conv_fft_size(L) : 0;
     if (d > 0 && L > 0 && conv_blocks(L)) return conv_blocked_spectrum_bytes(d, L);
-    // one (K[k], K[M-k]) pair per 16 bytes; behind them, for the sizes the matrix-core kernel serves, its own copy
+    // 16 bytes per pair of bins (k, M - k); behind them, for the sizes the matrix-core kernel serves, its own copy
     if (!M) return 0;
     const size_t extra = convmx_spectrum_bytes(d, L);
     return extra ? conv_pairs_bytes(d, L) + extra : (size_t)d * (size_t)(M / 2 + 1) * 4 * sizeof(float);
@@ -883,9 +883,6 @@ int chela_longconv_spectrum(const float* k_long, void* spectrum, int d, int L, v
     if (overlap(Range{(const char*)k_long, (size_t)d * L * 4}, Range{(const char*)spectrum, chela_longconv_spectrum_bytes(d, L)}))
         return CHELA_ERR_ALIASING;
     if (launch_longconv_spectrum(k_long, spectrum, d, L, (hipStream_t)stream) != hipSuccess) return CHELA_ERR_HIP;
-    if (convmx_spectrum_bytes(d, L) &&
-        launch_convmx_spectrum(k_long, spectrum, (char*)spectrum + conv_pairs_bytes(d, L), d, L, (hipStream_t)stream) != hipSuccess)
-        return CHELA_ERR_HIP;
     return CHELA_OK;
 }
 

@@ -122,7 +122,7 @@ hipError_t launch_bf16_step(const void* q, const void* k, const void* v, float* 
                             long BH, int dk, int dv, hipStream_t st);
 
 // Short-long convolutions (Sec. 4.2).  conv_fft_size(L): length M of the complex transform used for sequences of
-// L steps (0: L too long); the kernel spectrum is [d][M/2 + 1] pairs of complex fp32.  dtype 0: bf16 I/O, 1: fp32 I/O.
+// L steps (0: L too long); the kernel spectrum is [d][M/2 + 1] float4, one per pair of bins.  dtype 0: bf16 I/O, 1: fp32 I/O.
 int conv_fft_size(int L);
 // Longer sequences (16384 < L <= kConvMaxL) are convolved block by block, 16384 steps per block: the number of
 // blocks (0: L is served by one transform, or too long).  The spectrum buffer then holds one spectrum per channel
@@ -135,17 +135,16 @@ inline size_t conv_blocked_spectrum_bytes(int d, int L)
 }
 hipError_t launch_longconv_spectrum(const float* k, void* Kf, int d, int L, hipStream_t st);
 // The forward convolution on the matrix cores (bf16 I/O, 4096 < L <= 16384): its own copy of the kernel spectrum
-// (convmx_spectrum_bytes, derived from the pairs above) lives behind them in the caller's spectrum buffer.
+// (convmx_spectrum_bytes, written by launch_longconv_spectrum) lives behind the pairs in the caller's spectrum buffer.
 bool convmx_applies(int L, int dtype);
 size_t convmx_spectrum_bytes(int d, int L);
-hipError_t launch_convmx_spectrum(const float* k_long, const void* pairs, void* extra, int d, int L, hipStream_t st);
 hipError_t launch_convmx_fwd(const void* X, const float* w_short, int m, const void* extra, void* Y, int B, int d, int L,
                              hipStream_t st);
 // The two long-stage gradients (dV: fp32 for the short-stage kernel, or dX itself in bf16 when there is no short stage;
 // Hs: 32768 words of scratch for each of up to kConvMxMaxWgs workgroups).
 hipError_t launch_convmx_longbwd(const void* X, const float* w_short, int m, const void* extra, const void* dZ, void* dV,
                                  bool dv_is_f32, float* dk, float* Hs, int B, int d, int L, hipStream_t st);
-inline size_t conv_pairs_bytes(int d, int L)       // the (K[k], K[M-k]) pairs: where the matrix-core copy starts
+inline size_t conv_pairs_bytes(int d, int L)       // the pairs: where the matrix-core copy starts
 {
     const int M = conv_fft_size(L);
     return M ? (((size_t)d * (size_t)(M / 2 + 1) * 4 * sizeof(float)) + 255) & ~(size_t)255 : 0;
@@ -163,8 +162,8 @@ inline int conv_bwd_groups(int B, int d, int L)
 {
     const int M = conv_fft_size(L);
     if (M == 0 || B <= 1 || d <= 0) return 1;
-    // resident workgroups of that kernel: 256 compute units x what its registers allow per unit (workgroups of 1, 1, 4
-    // and 16 waves at M = 256, 1024, 4096, 16384)
+    // two rounds of: 256 compute units x the workgroups per unit (of 1, 1, 4 and 16 waves at M = 256, 1024, 4096, 16384);
+    // three rounds of the two per unit that the short stage's gradient, in the same kernel, leaves room for at 4096
     const long slots = 256L * (M >= 16384 ? 1 : M >= 4096 ? 3 : M >= 1024 ? 12 : 20);
     long g = (2 * slots + d - 1) / d;
     if (g > B) g = B;

@@ -113,7 +113,8 @@ __host__ __device__ constexpr int conv_pad(int i) { return i + (i >> 4); }
 
 template <int M>
 struct ConvLds {
-    static constexpr int DATA = conv_pad(M);                 // complex slots
+    // complex slots; 16 more than the transform needs, so that two real sequences with 32 steps of margin each fit
+    static constexpr int DATA = conv_pad(M) + 16;
     static constexpr int BYTES = DATA * 8 + 2 * 128 * 8;     // + two twiddle tables of 128
 };
 
@@ -175,48 +176,86 @@ __device__ __forceinline__ void pass16(cplx* a, const cplx* lo, const cplx* hi, 
     }
 }
 
-// All forward passes (INV = false) or all inverse passes in reverse order (INV = true) over a[] in LDS.
-// A __syncthreads() separates the passes; the caller synchronises before and after.
-// The packed sequence has at most M/2 non-zero entries (L <= M real steps) and only its first M/2 entries are ever read
-// back: the first pass forward does not read the upper half, the last one back does not write it.
-template <int M, int T, bool INV>
-__device__ __forceinline__ void fft_passes(cplx* a, const cplx* lo, const cplx* hi, int tid)
+// The forward transform of the packed sequence z[n], n = tid + T i < M/2 (its upper half is zero: L <= M real steps), from
+// registers into a[], and the way back, of which only the first M/2 results are wanted, into registers again: the first
+// pass forward and the last one back never go through LDS.  A __syncthreads() separates the passes; the caller
+// synchronises before and after.
+template <int M, int T>
+__device__ __forceinline__ void fft_forward(const cplx (&z)[M / T / 2], cplx* a, const cplx* lo, const cplx* hi, int tid)
 {
-    constexpr bool L4 = conv_lead4(M);
-    constexpr int M16 = L4 ? M / 4 : M;     // what the radix-16 passes transform (blocks of this length)
-    static_assert(M16 == 256 || M16 == 4096, "radix-16 part must be 16^2 or 16^3");
-    auto lead4 = [&]() __attribute__((always_inline)) {
-        constexpr int s = M / 4, sp = s + s / 16;
-        for (int g = tid; g < s; g += T) {
-            cplx* p0 = a + conv_pad(g);
-            if (!INV) {
-                const cplx v0 = p0[0], v1 = p0[sp], r = mul_neg_i(v1);
+    if constexpr (M == 256) {               // (16 of a wave's threads work in a pass: the input is dealt out again)
+#pragma unroll
+        for (int i = 0; i < M / T / 2; ++i) a[conv_pad(tid + T * i)] = z[i];
+        __syncthreads();
+        pass16<M, T, 256, false, true>(a, lo, hi, tid);
+    } else {
+        static_assert(M / T == 16, "sixteen points per thread");
+        if constexpr (conv_lead4(M)) {
+            constexpr int s = M / 4, sp = s + s / 16;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                cplx* p0 = a + conv_pad(tid + T * j);
+                const cplx v0 = z[j], v1 = z[j + 4], r = mul_neg_i(v1);
                 p0[0] = cadd(v0, v1);
                 p0[sp] = cadd(v0, r);
                 p0[2 * sp] = csub(v0, v1);
                 p0[3 * sp] = csub(v0, r);
-            } else {
-                const cplx t1 = conj(twiddle<M>(lo, hi, g)), t2 = cmul(t1, t1), t3 = cmul(t2, t1);
+            }
+            __syncthreads();
+            if constexpr (M == 16384) { pass16<M, T, 4096, false, false>(a, lo, hi, tid); __syncthreads(); }
+        } else {
+            constexpr int S = M / 16, STEP = S + S / 16;
+            cplx v[16];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = z[q];
+            dft16<false, true, true>(v, mk(1.f, 0.f));
+            cplx* p0 = a + conv_pad(tid);
+#pragma unroll
+            for (int p = 0; p < 16; ++p) p0[p * STEP] = v[rev4(p)];
+            __syncthreads();
+        }
+        pass16<M, T, 256, false, false>(a, lo, hi, tid);
+    }
+    __syncthreads();
+    pass16<M, T, 16, false, false>(a, lo, hi, tid);
+}
+
+template <int M, int T>
+__device__ __forceinline__ void fft_inverse(cplx* a, cplx (&y)[M / T / 2], const cplx* lo, const cplx* hi, int tid)
+{
+    pass16<M, T, 16, true, false>(a, lo, hi, tid);
+    __syncthreads();
+    if constexpr (M == 256) {
+        pass16<M, T, 256, true, true>(a, lo, hi, tid);
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < M / T / 2; ++i) y[i] = a[conv_pad(tid + T * i)];
+    } else {
+        pass16<M, T, 256, true, false>(a, lo, hi, tid);
+        __syncthreads();
+        if constexpr (conv_lead4(M)) {
+            if constexpr (M == 16384) { pass16<M, T, 4096, true, false>(a, lo, hi, tid); __syncthreads(); }
+            constexpr int s = M / 4, sp = s + s / 16;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const cplx* p0 = a + conv_pad(tid + T * j);
+                const cplx t1 = conj(twiddle<M>(lo, hi, tid + T * j)), t2 = cmul(t1, t1), t3 = cmul(t2, t1);
                 cplx v0 = p0[0], v1 = cmul(p0[sp], t1), v2 = p0[2 * sp], v3 = p0[3 * sp];
                 bfly(v0, v2, t2.x, t2.y);
                 bfly(v1, v3, t3.x, t3.y);
-                p0[0] = cadd(v0, v1);
-                p0[sp] = cadd(v2, mul_pos_i(v3));
+                y[j] = cadd(v0, v1);
+                y[j + 4] = cadd(v2, mul_pos_i(v3));
             }
+        } else {
+            constexpr int S = M / 16, STEP = S + S / 16;
+            const cplx* p0 = a + conv_pad(tid);
+            cplx v[16];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) v[q] = p0[q * STEP];
+            dft16<true, false, false, true>(v, conj(twiddle<M>(lo, hi, tid)));
+#pragma unroll
+            for (int p = 0; p < 8; ++p) y[p] = v[rev4(p)];
         }
-    };
-    if (!INV) {
-        if (L4) { lead4(); __syncthreads(); }
-        if (M16 == 4096) { pass16<M, T, 4096, false, !L4>(a, lo, hi, tid); __syncthreads(); }
-        pass16<M, T, 256, false, !L4 && M16 == 256>(a, lo, hi, tid);
-        __syncthreads();
-        pass16<M, T, 16, false, false>(a, lo, hi, tid);
-    } else {
-        pass16<M, T, 16, true, false>(a, lo, hi, tid);
-        __syncthreads();
-        pass16<M, T, 256, true, !L4 && M16 == 256>(a, lo, hi, tid);
-        if (M16 == 4096) { __syncthreads(); pass16<M, T, 4096, true, !L4>(a, lo, hi, tid); }
-        if (L4) { __syncthreads(); lead4(); }
     }
 }
 
@@ -305,71 +344,144 @@ __device__ __forceinline__ void build_tables(cplx* lo, cplx* hi, int tid)
     }
 }
 
-// Order in which the point-wise stages walk the bin pairs (k, M - k), 0 <= k <= M/2.  The forward passes leave
+// Order in which the point-wise stages walk the bin pairs (k, M - k), 0 <= k < M/2.  The forward passes leave
 // bin k at a digit-reversed position, so lanes that took consecutive k would all hit the same LDS banks (strides of
 // M/4 and M/64 complex).  Pair l takes k = ((l & 63) << HB) | (l >> 6) instead: the 64 lanes of a wave then differ
-// in the HIGH bits of k, i.e. in the low digits of the storage position.  l = M/2 stands for the self-paired bin
-// M/2.  The kernel spectrum is stored in the same order, one float4 (K[k], K[M-k]) per pair, so its loads coalesce.
+// in the HIGH bits of k, i.e. in the low digits of the storage position.  Pair 0 stands for the two self-paired bins 0
+// and M/2.  The kernel spectrum is stored in the same order, one float4 per pair, so its loads coalesce.
 template <int M>
 __device__ __forceinline__ int pair_bin(int l)
 {
-    constexpr int HALF = M / 2;
     int hb = 0;
 #pragma unroll
-    for (int x = HALF / 64; x > 1; x >>= 1) ++hb;
-    return l >= HALF ? HALF : (((l & 63) << hb) | (l >> 6));
+    for (int x = M / 128; x > 1; x >>= 1) ++hb;
+    return ((l & 63) << hb) | (l >> 6);
 }
 
-__device__ __forceinline__ cplx w2m(int k, int M)      // W_2M^k = exp(-i pi k / M)
-{
-    float s, c;
-    sincospif(-(float)k / (float)M, &s, &c);
-    return mk(c, s);
-}
-
-// W_2M^k for the bins a thread meets when it walks the pairs l = tid, tid + T, ... in pair order: k = (lane << HB) |
-// (l >> 6), so W^k = W^(lane << HB) * W^(tid >> 6) * (W^(T/64))^i: two sincospi per thread and one rotation per pair
-// instead of one sincospi per pair.  The self-paired bin M/2 (l = M/2) is -i.
+// Positions in a[] of the pairs l = tid + T i of a thread.  With sixteen points per thread the eight pairs of a thread
+// differ in two digits of k only, k = k(0) + (T/64) i: bins k lie at constant distances from the first one, bins M - k at
+// the same distances backwards, except where no lower digit borrows (the first wave's i = 0 and 4).  Four registers and
+// constant offsets, where working each position out took some 40 instructions per pair and sequence.
 template <int M, int T>
-struct PairTwiddle {
-    cplx cur, step;
-    __device__ __forceinline__ PairTwiddle(int tid)
+struct PairPos {
+    static constexpr int NP = M / 2 / T;                  // pairs per thread: 8 (2 at M = 256)
+    static constexpr bool LIN = NP == 8;
+    static constexpr int SA = M == 1024 ? 272 : 1088;     // padded distance of i and i + 1; 17 of i and i + 4
+    int a1[LIN ? 1 : NP], a2[LIN ? 3 : NP];
+    static __device__ __forceinline__ int bin_pos(int k) { return conv_pad(spectrum_pos<M>(k & (M - 1))); }
+    __device__ __forceinline__ PairPos(int tid)
     {
-        cur = w2m(pair_bin<M>(tid < M / 2 ? tid : 0), M);
-        step = w2m(T / 64, M);
+        if constexpr (LIN) {
+            a1[0] = bin_pos(pair_bin<M>(tid));
+            a2[0] = bin_pos(tid == 0 ? M / 2 : M - pair_bin<M>(tid));
+            a2[1] = bin_pos(M - pair_bin<M>(tid + 4 * T));
+            a2[2] = bin_pos(M - pair_bin<M>(tid + T)) + SA;
+        } else {
+#pragma unroll
+            for (int i = 0; i < NP; ++i) {
+                const int k = pair_bin<M>(tid + T * i);
+                a1[i] = bin_pos(k);
+                a2[i] = bin_pos(k == 0 ? M / 2 : M - k);
+            }
+        }
     }
-    __device__ __forceinline__ cplx next(int l)
+    __device__ __forceinline__ int first(int i) const { return LIN ? a1[0] + (i & 3) * SA + (i >> 2) * 17 : a1[LIN ? 0 : i]; }
+    __device__ __forceinline__ int second(int i) const
     {
-        const cplx w = l >= M / 2 ? mk(0.f, -1.f) : cur;
-        cur = cmul(cur, step);
-        return w;
+        if (!LIN) return a2[LIN ? 0 : i];
+        return i == 0 ? a2[0] : i == 4 ? a2[1] : a2[2] - (i & 3) * SA - (i >> 2) * 17;
     }
 };
 
-// Bins k and M - k of the spectrum of a real sequence of length 2M from the length-M transform Z of its even/odd
-// packing:  X[k] = (Z[k] + conj Z[M-k]) / 2 + W_2M^k (Z[k] - conj Z[M-k]) / (2i),  k = 0 .. M  (Z[M] = Z[0]).
-// A = Z[k], Bc = conj Z[M-k], w = W_2M^k.  For k = 0 this gives X[0] and X[M] (both real).
-__device__ __forceinline__ void untangle(cplx A, cplx Bc, cplx w, cplx& Xk, cplx& Xmk)
+// W_2M^k = exp(-i pi k / M) for the bins a thread meets when it walks its pairs: k = k(0) + (T/64) i, two sincospi per
+// thread and one rotation per pair.
+template <int M, int T>
+struct PairTwiddle {
+    cplx first, step;
+    __device__ __forceinline__ PairTwiddle(int tid)
+    {
+        float s, c;
+        sincospif(-(float)pair_bin<M>(tid) / (float)M, &s, &c);
+        first = mk(c, s);
+        sincospif(-(float)(T / 64) / (float)M, &s, &c);
+        step = mk(c, s);
+    }
+};
+
+// A real sequence v of length 2M packed as z[n] = v[2n] + i v[2n+1] has the spectrum
+//     V[k] = E + w O,  conj V[M-k] = E - w O,   E = (A + B)/2,  O = (A - B)/(2i),   A = Z[k], B = conj Z[M-k], w = W_2M^k.
+// The product with a kernel's spectrum K, packed again, is linear in (A, B).  With P = (K[k] + conj K[M-k])/2, D =
+// (K[k] - conj K[M-k])/2 and w = c - i s it comes to
+//     A' = P A + D r,  r = -s A + i c B;      B' = P B + D q,  q = s B - i c A
+// -- 24 multiply-adds per pair; untangling to V, multiplying and packing again took over 50.  (P, D) of a kernel are E and
+// w O of its own packed transform.  Correlation: conj P, conj D.
+// Gradient of the kernel, sums over sequences of G conj(V) for two packed spectra (A, B) and (a, b), r and q of (a, b):
+//     2 al = A conj(a) + B conj(b),  2 be = A conj(r) + B conj(q);   packed: A' = al + i be conj(w), B' = al - i be conj(w).
+// Pair 0 holds the self-paired bins 0 and M/2 (A = Z[0] = x + i y, B = conj Z[M/2]): kernel entries (P, D) of bin 0, both
+// real, then K[M/2];  A' = (P x + D y) + i (P y + D x), B' = K[M/2] B;  sums (x x' + y y') + i (x y' + y x') and B conj(b).
+__device__ __forceinline__ void pair_rot(cplx A, cplx B, cplx w, cplx& r, cplx& q)
 {
-    const cplx xe = mk(0.5f * (A.x + Bc.x), 0.5f * (A.y + Bc.y));
-    const cplx xo = mul_neg_i(mk(0.5f * (A.x - Bc.x), 0.5f * (A.y - Bc.y)));
-    const cplx wx = cmul(w, xo);
-    Xk = cadd(xe, wx);
-    Xmk = conj(csub(xe, wx));
+    r = mk(fmaf(w.y, A.x, -w.x * B.y), fmaf(w.y, A.y, w.x * B.x));
+    q = mk(fmaf(-w.y, B.x, w.x * A.y), fmaf(-w.y, B.y, -w.x * A.x));
+}
+// s + a b and s + a conj(b)
+__device__ __forceinline__ cplx cfma(cplx a, cplx b, cplx s)
+{
+    return mk(fmaf(-a.y, b.y, fmaf(a.x, b.x, s.x)), fmaf(a.y, b.x, fmaf(a.x, b.y, s.y)));
+}
+__device__ __forceinline__ cplx cfmac(cplx a, cplx b, cplx s)
+{
+    return mk(fmaf(a.y, b.y, fmaf(a.x, b.x, s.x)), fmaf(a.y, b.x, fmaf(-a.x, b.y, s.y)));
 }
 
-// The inverse: from bins Y[k], Y[M-k] of a real sequence's spectrum to Z[k], Z[M-k] of its packing.
-//   Ye = (Y[k] + conj Y[M-k]) / 2, Yo = (Y[k] - conj Y[M-k]) / 2 * conj(W_2M^k); Z[k] = Ye + i Yo,
-//   Z[M-k] = conj(Ye) + i conj(Yo).  For k = 0 (Y[0], Y[M] real) Z[0] = (Y0 + YM)/2 + i (Y0 - YM)/2.
-__device__ __forceinline__ void tangle(cplx Yk, cplx Ymk, cplx w, cplx& Zk, cplx& Zmk)
+// (A, B) times the kernel entry K; self: pair 0.
+template <bool CORR>
+__device__ __forceinline__ void pair_mul(cplx& A, cplx& B, cplx w, float4 K, bool self)
 {
-    const cplx Yc = conj(Ymk);
-    const cplx ye = mk(0.5f * (Yk.x + Yc.x), 0.5f * (Yk.y + Yc.y));
-    const cplx yo = cmul(mk(0.5f * (Yk.x - Yc.x), 0.5f * (Yk.y - Yc.y)), conj(w));
-    Zk = cadd(ye, mul_pos_i(yo));
-    Zmk = cadd(conj(ye), mul_pos_i(conj(yo)));
+    const cplx P = mk(K.x, CORR ? -K.y : K.y), D = mk(K.z, CORR ? -K.w : K.w);
+    if (self) {
+        A = mk(fmaf(K.x, A.x, K.y * A.y), fmaf(K.x, A.y, K.y * A.x));
+        B = cmul(D, B);
+        return;
+    }
+    cplx r, q;
+    pair_rot(A, B, w, r, q);
+    A = cfma(D, r, cmul(P, A));
+    B = cfma(D, q, cmul(P, B));
 }
 
+// Adds the share of (A, B) conj (a, b) to a pair's sums (twice al and be; pair 0: the two self-paired bins' own).
+__device__ __forceinline__ void pair_acc(float4& S, cplx A, cplx B, cplx a, cplx b, cplx w, bool self)
+{
+    cplx al = mk(S.x, S.y), be = mk(S.z, S.w);
+    if (self) {
+        al = mk(fmaf(A.x, a.x, fmaf(A.y, a.y, al.x)), fmaf(A.x, a.y, fmaf(A.y, a.x, al.y)));
+        be = cfmac(B, b, be);
+    } else {
+        cplx r, q;
+        pair_rot(a, b, w, r, q);
+        al = cfmac(A, a, cfmac(B, b, al));
+        be = cfmac(A, r, cfmac(B, q, be));
+    }
+    S = make_float4(al.x, al.y, be.x, be.y);
+}
+
+// A pair's sums, packed for the transform back.
+__device__ __forceinline__ void pair_pack(float4 S, cplx w, bool self, cplx& A, cplx& B)
+{
+    if (self) { A = mk(S.x, S.y); B = mk(S.z, S.w); return; }
+    const cplx al = mk(0.5f * S.x, 0.5f * S.y), be = mul_pos_i(cmul(mk(0.5f * S.z, 0.5f * S.w), conj(w)));
+    A = cadd(al, be);
+    B = csub(al, be);
+}
+
+// The kernel's entry from its own packed transform.
+__device__ __forceinline__ float4 pair_kernel(cplx A, cplx B, cplx w, bool self)
+{
+    if (self) return make_float4(A.x, A.y, B.x, B.y);
+    const cplx D = cmul(w, mul_neg_i(mk(0.5f * (A.x - B.x), 0.5f * (A.y - B.y))));
+    return make_float4(0.5f * (A.x + B.x), 0.5f * (A.y + B.y), D.x, D.y);
+}
 
 // One sequence of L <= M steps in registers: the pairs (x[2n], x[2n+1]) for n = tid + T i.  Only n < M/2 can lie
 // inside the sequence, so half of a thread's M/T slots are enough.  A kernel that walks several sequences fetches the
@@ -392,75 +504,107 @@ struct SeqRegs {
     }
 };
 
-// x (one sequence of L steps, in registers) -> optional short kernel and activation -> packed complex
-// z[n] = v[2n] + i v[2n+1], n < M/2, in a[], zero beyond L (the upper half, all zeros, is never read).  Ends with the
-// data in place but NOT synchronised.
-// hist (only read with a short kernel): null for a sequence's first step (zero history), else a pointer at the first
-// of these L steps inside a longer row, whose 32 predecessors are then the history.
+// x (one sequence of L <= M steps, in registers) as M floats, zeros beyond L, behind 32 steps of history, zeros at a
+// sequence's start, so that no tap needs a bounds check.
+// hist: null for a sequence's first step, else a pointer at the first of these L steps inside a longer row, whose 32
+// predecessors are then the history.
+constexpr int kHist = 32;
 template <int M, int T, typename IO>
-__device__ __forceinline__ void stage_input(const SeqRegs<M, T, IO>& x, const float* __restrict__ wc, int m, int L,
-                                            cplx* a, int tid, const IO* __restrict__ hist = nullptr)
+__device__ __forceinline__ void stage_raw(const SeqRegs<M, T, IO>& x, float* sx, int tid, const IO* __restrict__ hist)
 {
-    constexpr int HELD = M / T / 2;
-    if (wc != nullptr) {
-        // raw x as floats behind 32 steps of history (zeros at a sequence's start), so that no tap needs a bounds check
-        float* sx = reinterpret_cast<float*>(a);
-        constexpr int ZP = 32;
-        if (tid < ZP) sx[tid] = hist != nullptr ? (float)hist[tid - ZP] : 0.f;
+    if (tid < kHist) sx[tid] = hist != nullptr ? (float)hist[tid - kHist] : 0.f;
 #pragma unroll
-        for (int i = 0; i < HELD; ++i) {
-            const int t = 2 * (tid + T * i);
-            if (t < L) {
-                float v0, v1;
-                IoPair<IO>::unpack(x.r[i], v0, v1);
-                *reinterpret_cast<float2*>(sx + ZP + t) = make_float2(v0, v1);
-            }
-        }
-        __syncthreads();
-        cplx z[HELD];
+    for (int i = 0; i < M / T / 2; ++i) {
+        float v0, v1;
+        IoPair<IO>::unpack(x.r[i], v0, v1);
+        *reinterpret_cast<float2*>(sx + kHist + 2 * (tid + T * i)) = make_float2(v0, v1);
+    }
+}
+
+// u = K_s x at a thread's steps.  Outputs t and t+1 share all but one of their inputs; x is read in aligned pairs
+// (x[t-2p], x[t-2p+1]): x[t-2p+1] meets taps 2p (for t+1) and 2p-1 (for t), x[t-2p] meets taps 2p+1 (for t+1) and 2p (t).
+// (steps beyond the sequence's end are worked out too, for the caller to drop: a branch around each read would keep the
+// reads from being issued together)
+template <int M, int T>
+__device__ __forceinline__ void short_conv(const float* sx, const float* __restrict__ wc, int m, int tid,
+                                           cplx (&z)[M / T / 2])
+{
 #pragma unroll
-        for (int i = 0; i < HELD; ++i) z[i] = mk(0.f, 0.f);
-        // outputs t and t+1 share all but one of their inputs; x is read in aligned pairs (x[t-2p], x[t-2p+1]):
-        // x[t-2p+1] meets taps 2p (for t+1) and 2p-1 (for t), x[t-2p] meets taps 2p+1 (for t+1) and 2p (for t)
-        for (int p = 0; 2 * p <= m; ++p) {
-            const float w2p = 2 * p < m ? wc[2 * p] : 0.f, w2pm1 = p > 0 ? wc[2 * p - 1] : 0.f;
-            const float w2pp1 = 2 * p + 1 < m ? wc[2 * p + 1] : 0.f;
+    for (int i = 0; i < M / T / 2; ++i) z[i] = mk(0.f, 0.f);
+    for (int p = 0; 2 * p <= m; ++p) {
+        const float w2p = 2 * p < m ? wc[2 * p] : 0.f, w2pm1 = p > 0 ? wc[2 * p - 1] : 0.f;
+        const float w2pp1 = 2 * p + 1 < m ? wc[2 * p + 1] : 0.f;
 #pragma unroll
-            for (int i = 0; i < HELD; ++i) {
-                const int t = 2 * (tid + T * i);
-                if (t < L) {
-                    const float2 xv = *reinterpret_cast<const float2*>(sx + ZP + t - 2 * p);
-                    z[i].y = fmaf(w2p, xv.y, fmaf(w2pp1, xv.x, z[i].y));
-                    z[i].x = fmaf(w2pm1, xv.y, fmaf(w2p, xv.x, z[i].x));
-                }
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < HELD; ++i) {
-            const int t = 2 * (tid + T * i);
-            z[i].x = z[i].x * __builtin_amdgcn_rcpf(1.f + __expf(-z[i].x));
-            z[i].y = (t + 1 < L) ? z[i].y * __builtin_amdgcn_rcpf(1.f + __expf(-z[i].y)) : 0.f;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < HELD; ++i) a[conv_pad(tid + T * i)] = z[i];
-    } else {
-#pragma unroll
-        for (int i = 0; i < HELD; ++i) {
-            float v0, v1;
-            IoPair<IO>::unpack(x.r[i], v0, v1);
-            a[conv_pad(tid + T * i)] = mk(v0, v1);
+        for (int i = 0; i < M / T / 2; ++i) {
+            const float2 xv = *reinterpret_cast<const float2*>(sx + kHist + 2 * (tid + T * i) - 2 * p);
+            z[i].y = fmaf(w2p, xv.y, fmaf(w2pp1, xv.x, z[i].y));
+            z[i].x = fmaf(w2pm1, xv.y, fmaf(w2p, xv.x, z[i].x));
         }
     }
 }
 
-// Kernel spectrum of one channel: (K[k], K[M-k]) for the M/2 + 1 bin pairs in pair order, complex fp32.
-template <int M>
-__global__ __launch_bounds__(conv_threads(M)) void longconv_spectrum_kernel(const float* __restrict__ k,
-                                                                           float4* __restrict__ Kf, int L)
+// x -> optional short kernel and activation (wc) -> packed complex z[n] = v[2n] + i v[2n+1] in registers, zero beyond L.
+// With a short kernel a[] serves as staging room; it is free again (synchronised) at the end.
+template <int M, int T, typename IO>
+__device__ __forceinline__ void stage_input(const SeqRegs<M, T, IO>& x, const float* __restrict__ wc, int m, int L,
+                                            cplx* a, int tid, cplx (&z)[M / T / 2], const IO* __restrict__ hist = nullptr)
 {
-    constexpr int T = conv_threads(M);
+    constexpr int HELD = M / T / 2;
+    if (wc != nullptr) {
+        float* sx = reinterpret_cast<float*>(a);
+        stage_raw<M, T, IO>(x, sx, tid, hist);
+        __syncthreads();
+        short_conv<M, T>(sx, wc, m, tid, z);
+#pragma unroll
+        for (int i = 0; i < HELD; ++i) {
+            const int t = 2 * (tid + T * i);
+            z[i].x = t < L ? z[i].x * __builtin_amdgcn_rcpf(1.f + __expf(-z[i].x)) : 0.f;
+            z[i].y = (t + 1 < L) ? z[i].y * __builtin_amdgcn_rcpf(1.f + __expf(-z[i].y)) : 0.f;
+        }
+        __syncthreads();
+    } else {
+#pragma unroll
+        for (int i = 0; i < HELD; ++i) IoPair<IO>::unpack(x.r[i], z[i].x, z[i].y);
+    }
+}
+
+// A thread's results out to y[t], t = 2 (tid + T i) < L.
+template <int M, int T, typename OUT>
+__device__ __forceinline__ void store_steps(const cplx (&v)[M / T / 2], OUT* __restrict__ y, int L, bool vec_ok, float scale,
+                                            int tid)
+{
+#pragma unroll
+    for (int i = 0; i < M / T / 2; ++i) {
+        const int t = 2 * (tid + T * i);
+        const float v0 = v[i].x * scale, v1 = v[i].y * scale;
+        if (t < L) {
+            if (vec_ok) IoPair<OUT>::store2(y + t, v0, v1);
+            else { y[t] = (OUT)v0; if (t + 1 < L) y[t + 1] = (OUT)v1; }
+        }
+    }
+}
+
+// What depends on the thread but not on the sequence (LDS addresses, bin positions, twiddles) is recomputed per sequence
+// behind an opaque copy of the thread index: hoisted out of the loop over sequences it would fill the register file.
+// Every stage takes a fresh copy, so that values shared between stages do not stay live in between.
+__device__ __forceinline__ int fresh(int tid) { asm volatile("" : "+v"(tid)); return tid; }
+
+// Kernel spectrum of one channel: the entries of the M/2 pairs in pair order (the buffer has room for one more).
+// MX (M = 16384): also the copy that the matrix-core kernels read, bin k = k1 + 32 k2 + 1024 k3 of the 32768-point
+// transform, divided by 4 |k|_1, as half-precision (re, im) words, stored where the lane that holds it after their forward
+// passes will look: word ((k1 * 4 + s) * 64 + lane) * 4 + i with lane = k2 + 32 h and k3 = 8 s + 4 h + i (the upper half of
+// the bins are the conjugates of the lower); scale[c] = 4 |k|_1.  The words change order through LDS: a kernel of its own
+// that gathered them from the pairs in memory took 77 us for 768 channels (the pairs alone 51); together: 63.
+template <int M, bool MX>
+__global__ __launch_bounds__(conv_threads(M)) void longconv_spectrum_kernel(const float* __restrict__ k,
+                                                                           float4* __restrict__ Kf,
+                                                                           uint4* __restrict__ Ks,
+                                                                           float* __restrict__ scale, int L)
+{
+    static_assert(!MX || M == 16384, "the matrix-core kernels' transform has 2 x 16384 points");
+    constexpr int T = conv_threads(M), NP = PairPos<M, T>::NP;
     __shared__ __attribute__((aligned(16))) unsigned char lds[ConvLds<M>::BYTES];
+    __shared__ float red[MX ? T / 64 : 1];
     cplx* a = reinterpret_cast<cplx*>(lds);
     cplx* lo = a + ConvLds<M>::DATA;
     cplx* hi = lo + 128;
@@ -469,20 +613,86 @@ __global__ __launch_bounds__(conv_threads(M)) void longconv_spectrum_kernel(cons
     build_tables<M, T>(lo, hi, tid);
     SeqRegs<M, T, float> kr;
     kr.load(k + c * (long)L, L, tid);
-    stage_input<M, T, float>(kr, nullptr, 0, L, a, tid);
+    cplx z[M / T / 2];
+    stage_input<M, T, float>(kr, nullptr, 0, L, a, tid, z);
+    if constexpr (MX) {
+        float n1 = 0.f;
+#pragma unroll
+        for (int i = 0; i < M / T / 2; ++i) n1 += fabsf(z[i].x) + fabsf(z[i].y);
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) n1 += __shfl_xor(n1, o);
+        if ((tid & 63) == 0) red[tid >> 6] = n1;
+    }
     __syncthreads();
-    fft_passes<M, T, false>(a, lo, hi, tid);
+    fft_forward<M, T>(z, a, lo, hi, tid);
     __syncthreads();
+    float inv = 0.f;
+    if constexpr (MX) {
+        float n1 = 0.f;
+        for (int i = 0; i < T / 64; ++i) n1 += red[i];
+        inv = n1 > 0.f ? 0.25f / n1 : 0.f;
+        if (tid == 0) scale[c] = n1 > 0.f ? 4.f * n1 : 0.f;
+    }
+    typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
+    auto half2 = [&](float re, float im) __attribute__((always_inline)) {
+        f16x2 v;
+        v[0] = (_Float16)(re * inv);
+        v[1] = (_Float16)(im * inv);
+        return __builtin_bit_cast(unsigned, v);
+    };
+    unsigned h1[MX ? NP : 1], h2[MX ? NP : 1], hm = 0;          // K[k], K[M - k]; K[M/2]
     float4* out = Kf + c * (long)(M / 2 + 1);
-    for (int l = tid; l <= M / 2; l += T) {
-        const int kk = pair_bin<M>(l);
-        cplx Xk, Xmk;
-        untangle(a[conv_pad(spectrum_pos<M>(kk))], conj(a[conv_pad(spectrum_pos<M>((M - kk) & (M - 1)))]), w2m(kk, M), Xk,
-                 Xmk);
-        out[l] = make_float4(Xk.x, Xk.y, Xmk.x, Xmk.y);
+    const PairPos<M, T> pos(tid);
+    const PairTwiddle<M, T> pw(tid);
+    cplx w = pw.first;
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+        const float4 e = pair_kernel(a[pos.first(i)], conj(a[pos.second(i)]), w, i == 0 && tid == 0);
+        out[tid + T * i] = e;
+        if constexpr (MX) {
+            if (i == 0 && tid == 0) {
+                h1[i] = half2(e.x + e.y, 0.f);
+                h2[i] = half2(e.x - e.y, 0.f);
+                hm = half2(e.z, e.w);
+            } else {
+                h1[i] = half2(e.x + e.z, e.y + e.w);
+                h2[i] = half2(e.x - e.z, e.w - e.y);
+            }
+        }
+        w = cmul(w, pw.step);
+    }
+    if constexpr (MX) {
+        // (padded so that neither the writers, 128 bins from lane to lane, nor the readers, 32, share banks)
+        auto at = [](int kk) __attribute__((always_inline)) { return kk + (kk >> 5) + (kk >> 7); };
+        unsigned* H = reinterpret_cast<unsigned*>(lds);
+        __syncthreads();                                            // a[] has been read out
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            const int kk = pair_bin<M>(tid + T * i);
+            H[at(kk)] = h1[i];
+            H[at(M - kk)] = h2[i];
+        }
+        if (tid == 0) H[at(M / 2)] = hm;
+        __syncthreads();
+        uint4* dst = Ks + c * (long)(2 * M / 4);
+#pragma unroll
+        for (int j = 0; j < 2 * M / 4 / T; ++j) {
+            const int o = tid + T * j, ln = o & 63, k0 = (o >> 8) + 32 * (ln & 31) + 1024 * (8 * ((o >> 6) & 3) + 4 * (ln >> 5));
+            unsigned v[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int kk = k0 + 1024 * i;
+                const bool upper = kk > M;
+                v[i] = H[at(upper ? 2 * M - kk : kk)] ^ (upper ? 0x80000000u : 0u);
+            }
+            dst[o] = make_uint4(v[0], v[1], v[2], v[3]);
+        }
     }
 }
 
+// Bound by vector instruction issue: 1881 instructions per wave and sequence of 4096 steps (2900 before the pairs became
+// linear in the packed bins, their places constant offsets, and the outer passes stayed in registers), issuing 92 % of the
+// time: 512 channels x 32 sequences, bf16, 320 -> 255 us.
 // Workgroup g takes the sequences (b, c) = g, g + gridDim.x, ... of the B d in turn (w_short == nullptr: no short
 // kernel and no activation, the plain long convolution).  The launch holds no more workgroups than are resident
 // at once, so that the tables are built once per workgroup, a sequence's input is fetched while the inverse transform
@@ -490,122 +700,85 @@ __global__ __launch_bounds__(conv_threads(M)) void longconv_spectrum_kernel(cons
 // each of those latencies was exposed once per sequence, since at the larger sizes a compute unit holds one
 // workgroup only.
 template <int M, typename IN, typename OUT>
-__global__ __launch_bounds__(conv_threads(M)) void shortlong_conv_kernel(const IN* __restrict__ X,
+__global__ __launch_bounds__(conv_threads(M)) __attribute__((amdgpu_waves_per_eu(4)))
+void shortlong_conv_kernel(const IN* __restrict__ X,
                                                                         const float* __restrict__ w_short, int m,
                                                                         const float4* __restrict__ Kf,
                                                                         OUT* __restrict__ Y, int d, int L, long total)
 {
-    constexpr int T = conv_threads(M);
-    constexpr int NP = (M / 2) / T + 1;          // bin pairs per thread (the last one only exists for l = M/2)
-    constexpr bool FRESH = true;
+    constexpr int T = conv_threads(M), NP = PairPos<M, T>::NP;
     __shared__ __attribute__((aligned(16))) unsigned char lds[ConvLds<M>::BYTES];
     cplx* a = reinterpret_cast<cplx*>(lds);
     cplx* lo = a + ConvLds<M>::DATA;
     cplx* hi = lo + 128;
     const int tid = threadIdx.x;
     build_tables<M, T>(lo, hi, tid);
-    // The storage positions of a thread's bin pairs (k, M - k), packed two to a register: the one thing that does not
-    // depend on the sequence and is worth its registers (some 40 instructions per pair and sequence otherwise).
-    unsigned pos[NP];
-#pragma unroll
-    for (int i = 0; i < NP; ++i) {
-        const int l = tid + T * i, kk = pair_bin<M>(l <= M / 2 ? l : 0);
-        pos[i] = (unsigned)conv_pad(spectrum_pos<M>(kk)) | (unsigned)conv_pad(spectrum_pos<M>((M - kk) & (M - 1))) << 16;
-    }
+    const PairPos<M, T> pos(tid);
+    const PairTwiddle<M, T> pw(tid);
     SeqRegs<M, T, IN> xr;
     long bc = blockIdx.x;
     if (bc < total) xr.load(X + bc * (long)L, L, tid);
     for (; bc < total; bc += gridDim.x) {
         const int c = (int)(bc % d);
-        OUT* y = Y + bc * (long)L;
-        // what depends on the thread but not on the sequence (LDS addresses, bin positions, twiddles) is recomputed
-        // per sequence behind an opaque copy of the thread index: hoisted out of this loop it would fill the
-        // register file.  Every stage takes a fresh copy, so that values shared between stages do not stay live in
-        // between (the registers go to the bin-pair positions above instead).
-        int tp = tid;
-        asm volatile("" : "+v"(tp));
+        int tp = fresh(tid);
         __syncthreads();        // the tables are built / the previous sequence has been read out of a[]
-        stage_input<M, T, IN>(xr, w_short ? w_short + (long)c * m : nullptr, m, L, a, tp);
+        cplx z[M / T / 2];
+        stage_input<M, T, IN>(xr, w_short ? w_short + (long)c * m : nullptr, m, L, a, tp, z);
         const float4* Kc = Kf + (long)c * (M / 2 + 1);
         float4 kq[NP];
 #pragma unroll
-        for (int i = 0; i < NP; ++i) {
-            const int l = tp + T * i;
-            if (l <= M / 2) kq[i] = Kc[l];
-        }
+        for (int i = 0; i < NP; ++i) kq[i] = Kc[tp + T * i];
+        tp = fresh(tid);
+        fft_forward<M, T>(z, a, lo, hi, tp);
         __syncthreads();
-
-        if constexpr (FRESH) { tp = tid; asm volatile("" : "+v"(tp)); }
-        fft_passes<M, T, false>(a, lo, hi, tp);
-        __syncthreads();
-
-        // ---- spectrum of v times spectrum of the kernel, re-packed for the inverse transform (pairs k, M - k)
-        if constexpr (FRESH) { tp = tid; asm volatile("" : "+v"(tp)); }
-        {
-            PairTwiddle<M, T> pw(tp);
+        cplx w = pw.first;
 #pragma unroll
-            for (int i = 0; i < NP; ++i) {
-                const int l = tp + T * i;
-                if (l <= M / 2) {
-                    const int p1 = pos[i] & 0xffffu, p2 = pos[i] >> 16;
-                    const cplx w = pw.next(l);
-                    cplx Xk, Xmk, Zk, Zmk;
-                    untangle(a[p1], conj(a[p2]), w, Xk, Xmk);
-                    const cplx K1 = mk(kq[i].x, kq[i].y), K2 = mk(kq[i].z, kq[i].w);
-                    if (l == 0) {       // (pair 0 is bin 0)
-                        // bins 0 and M are real and share storage slot 0
-                        const float y0 = Xk.x * K1.x, ym = Xmk.x * K2.x;
-                        a[p1] = mk(0.5f * (y0 + ym), 0.5f * (y0 - ym));
-                    } else {
-                        tangle(cmul(Xk, K1), cmul(Xmk, K2), w, Zk, Zmk);
-                        a[p1] = Zk;
-                        if (p2 != p1) a[p2] = Zmk;
-                    }
-                }
-            }
+        for (int i = 0; i < NP; ++i) {
+            cplx &p1 = a[pos.first(i)], &p2 = a[pos.second(i)];
+            cplx A = p1, B = conj(p2);
+            pair_mul<false>(A, B, w, kq[i], i == 0 && tid == 0);
+            p1 = A;
+            p2 = conj(B);
+            w = cmul(w, pw.step);
         }
         if (bc + gridDim.x < total) xr.load(X + (bc + gridDim.x) * (long)L, L, tp);     // the next sequence, in flight
         __syncthreads();
-
-        if constexpr (FRESH) { tp = tid; asm volatile("" : "+v"(tp)); }
-        fft_passes<M, T, true>(a, lo, hi, tp);
-        __syncthreads();
-
-        // ---- unpack, scale, store
-        const bool vec_ok = (L & 1) == 0;
-        const float scale = 1.0f / (float)M;
-#pragma unroll
-        for (int i = 0; i < M / T / 2; ++i) {
-            const int n = tp + T * i, t = 2 * n;
-            if (t < L) {
-                const cplx v = a[conv_pad(n)];
-                if (vec_ok) IoPair<OUT>::store2(y + t, v.x * scale, v.y * scale);
-                else { y[t] = (OUT)(v.x * scale); if (t + 1 < L) y[t + 1] = (OUT)(v.y * scale); }
-            }
-        }
+        tp = fresh(tid);
+        fft_inverse<M, T>(a, z, lo, hi, tp);
+        store_steps<M, T, OUT>(z, Y + bc * (long)L, L, (L & 1) == 0, 1.0f / (float)M, tp);
     }
 }
 
-// The two long-stage gradients in one kernel: they share the spectrum of dZ.  One workgroup per channel walks the
-// batch; per sequence it transforms dZ once, keeps the untangled bins of its own bin pairs in registers, multiplies
+// The long-stage gradients in one kernel: they share the spectrum of dZ.  One workgroup per channel walks the
+// batch; per sequence it transforms dZ once, keeps the packed bins of its own bin pairs in registers, multiplies
 // by the CONJUGATE kernel spectrum (correlation instead of convolution: dV[t] = sum_{s >= t} k[s - t] dZ[s]) and
-// transforms back (out as DVT: fp32 scratch for the short-stage kernel, or dX itself when there is no short stage),
-// then transforms v = silu(K_s x) (recomputed from x) and adds DZ conj(V) to the running sums of its bin pairs (in
-// registers, at the largest size in memory); after the last sequence the sums are transformed back once (dk).  Three
-// transforms per sequence, where a correlation kernel and a kernel-gradient kernel of their own would need four.
+// transforms back (out as DVT: dX itself when there is no short stage, fp32 scratch for the short-stage kernel, or on into
+// the short stage below), then transforms v = silu(K_s x) (recomputed from x) and adds DZ conj(V) to the running sums of
+// its bin pairs (in registers, at the largest size in memory); after the last sequence the sums are transformed back once
+// (dk).  Three transforms per sequence, where a correlation kernel and a kernel-gradient kernel of their own would need
+// four.
 // SPLIT: grid.y workgroups share a channel, each takes every grid.y-th sequence and leaves its sums in its own slice
 // of the scratch array ([grid.y][d][M/2 + 1] pairs); longconv_dk_finish_kernel adds the slices up and transforms back.
 // Used when there are too few channels to fill the GPU.
-template <int M, typename IO, typename DVT, bool SPLIT>
-__global__ __launch_bounds__(conv_threads(M)) void longconv_bwd_kernel(const IO* __restrict__ X,
+// SHORT: the short stage's gradient as well (m <= kFuseTaps): dV stays in registers, u = K_s x is there already for v,
+// dU = dV silu'(u) meets its neighbours through LDS: dX out (dV is DVT = IO dX here), the taps' sums into `part`
+// ([d][grid.y][kShortMaxTaps]).  As a kernel of its own that stage reads x again, and dV, 4 bytes a step written here and
+// read there, and works u out once more: 512 channels x 32 sequences of 4096 steps, bf16, the two kernels 527 + 150 us,
+// in one 570.  Two workgroups of 212 registers per compute unit; made to fit three, with 50 values spilled, it takes 760
+// (and 690 with V first and u and the taps' sums out of the registers).  Vector instructions issue 63 % of the time.
+constexpr int kFuseTaps = 16, kShortMaxTaps = 32;
+
+template <int M, typename IO, typename DVT, bool SPLIT, bool SHORT>
+__global__ __launch_bounds__(conv_threads(M)) __attribute__((amdgpu_waves_per_eu(M == 1024 || M == 4096 ? 2 : 4)))
+void longconv_bwd_kernel(const IO* __restrict__ X,
                                                                       const float* __restrict__ w_short, int m,
                                                                       const float4* __restrict__ Kf,
                                                                       const IO* __restrict__ dZ,
                                                                       DVT* __restrict__ dV, float* __restrict__ dk,
-                                                                      float4* __restrict__ acc_ws, int B, int d, int L)
+                                                                      float4* __restrict__ acc_ws, float* __restrict__ part,
+                                                                      int B, int d, int L)
 {
-    constexpr int T = conv_threads(M);
-    constexpr int NP = (M / 2) / T + 1;                  // bin pairs per thread
+    constexpr int T = conv_threads(M), NP = PairPos<M, T>::NP, HELD = M / T / 2;
     // At the largest size 1024 threads share the register file: the running sums then live in a scratch array in
     // memory ([d][M/2 + 1] pairs; every thread only ever touches its own pairs, between uses they sit in the caches).
     constexpr bool ACC_MEM = M >= 16384;
@@ -617,14 +790,22 @@ __global__ __launch_bounds__(conv_threads(M)) void longconv_bwd_kernel(const IO*
     const int tid = threadIdx.x;
     const int c = blockIdx.x;
     build_tables<M, T>(lo, hi, tid);
+    const PairPos<M, T> pos(tid);
+    const PairTwiddle<M, T> pw(tid);
     const float4* Kc = Kf + (long)c * (M / 2 + 1);
     const float* wc = w_short ? w_short + (long)c * m : nullptr;
     const bool vec_ok = (L & 1) == 0;
     const float scale = 1.0f / (float)M;
-    cplx accK[ACC_MEM ? 1 : NP], accMK[ACC_MEM ? 1 : NP], Gk[NP], Gmk[NP];
+    float4 sums[ACC_MEM ? 1 : NP];
+    cplx GA[NP], GB[NP], z[HELD];
+    float tap[SHORT ? kFuseTaps : 1];
     if constexpr (!ACC_MEM) {
 #pragma unroll
-        for (int i = 0; i < NP; ++i) { accK[i] = mk(0.f, 0.f); accMK[i] = mk(0.f, 0.f); }
+        for (int i = 0; i < NP; ++i) sums[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    if constexpr (SHORT) {
+#pragma unroll
+        for (int j = 0; j < kFuseTaps; ++j) tap[j] = 0.f;
     }
 
     // Inputs are fetched one stage ahead, into registers: dZ of the next sequence while v is transformed, x while the
@@ -633,96 +814,163 @@ __global__ __launch_bounds__(conv_threads(M)) void longconv_bwd_kernel(const IO*
     if ((int)blockIdx.y < B) zr.load(dZ + ((long)blockIdx.y * d + c) * L, L, tid);
     for (int b = blockIdx.y; b < B; b += gridDim.y) {
         const long row = ((long)b * d + c) * L;
-        // what depends on the thread but not on the sequence (LDS addresses, bin positions, twiddles) is recomputed per
-        // sequence behind an opaque copy of the thread index: left visible, the compiler keeps all of it in registers
-        // across the transforms and spills
-        // (a fresh copy per stage, or positions shared between stages stay live across the transforms between them)
-        int tp = tid;
-        asm volatile("" : "+v"(tp));
+        int tp = fresh(tid);
         // ---- spectrum of dZ; correlation with the kernel: DZ conj(K)
-        stage_input<M, T, IO>(zr, nullptr, 0, L, a, tp);
+        stage_input<M, T, IO>(zr, nullptr, 0, L, a, tp, z);
+        float4 kq[NP];
+#pragma unroll
+        for (int i = 0; i < NP; ++i) kq[i] = Kc[tp + T * i];
+        __syncthreads();        // the tables are built / a[] has been read out
+        fft_forward<M, T>(z, a, lo, hi, tp);
         __syncthreads();
-        fft_passes<M, T, false>(a, lo, hi, tp);
-        __syncthreads();
-        tp = tid;
-        asm volatile("" : "+v"(tp));
+        tp = fresh(tid);
         xr.load(X + row, L, tp);
         {
-            PairTwiddle<M, T> pw(tp);
+#pragma unroll
+            for (int i = 0; i < NP; ++i) { GA[i] = a[pos.first(i)]; GB[i] = conj(a[pos.second(i)]); }
+            cplx w = pw.first;
 #pragma unroll
             for (int i = 0; i < NP; ++i) {
-                const int l = tp + T * i;
-                if (l <= M / 2) {
-                    const int kk = pair_bin<M>(l);
-                    const int p1 = conv_pad(spectrum_pos<M>(kk)), p2 = conv_pad(spectrum_pos<M>((M - kk) & (M - 1)));
-                    const cplx w = pw.next(l);
-                    untangle(a[p1], conj(a[p2]), w, Gk[i], Gmk[i]);
-                    const float4 kq = Kc[l];
-                    const cplx K1 = mk(kq.x, -kq.y), K2 = mk(kq.z, -kq.w);
-                    if (kk == 0) {
-                        const float y0 = Gk[i].x * K1.x, ym = Gmk[i].x * K2.x;
-                        a[p1] = mk(0.5f * (y0 + ym), 0.5f * (y0 - ym));
-                    } else {
-                        cplx Zk, Zmk;
-                        tangle(cmul(Gk[i], K1), cmul(Gmk[i], K2), w, Zk, Zmk);
-                        a[p1] = Zk;
-                        if (p2 != p1) a[p2] = Zmk;
-                    }
-                }
+                cplx A = GA[i], B = GB[i];
+                pair_mul<true>(A, B, w, kq[i], i == 0 && tid == 0);
+                a[pos.first(i)] = A;
+                a[pos.second(i)] = conj(B);
+                w = cmul(w, pw.step);
                 __builtin_amdgcn_sched_barrier(0);   // one pair at a time: the unrolled pairs must not pile up in registers
             }
         }
         __syncthreads();
-        tp = tid;
-        asm volatile("" : "+v"(tp));
-        fft_passes<M, T, true>(a, lo, hi, tp);
-        __syncthreads();
-        {
-            DVT* y = dV + row;
+        tp = fresh(tid);
+        fft_inverse<M, T>(a, z, lo, hi, tp);
+        tp = fresh(tid);
+        if constexpr (SHORT) {
+            float* sx = reinterpret_cast<float*>(a);
+            float* su = sx + kHist + M;              // dU, zeros beyond L
+            cplx u[HELD];
+            __syncthreads();                         // a[] has been read out
+            stage_raw<M, T, IO>(xr, sx, tp, nullptr);
+            if (tp < kHist) su[M + tp] = 0.f;
+            __syncthreads();
+            short_conv<M, T>(sx, wc, m, tp, u);
 #pragma unroll
-            for (int i = 0; i < M / T / 2; ++i) {
-                const int n = tp + T * i, t = 2 * n;
-                if (t < L) {
-                    const cplx v = a[conv_pad(n)];
-                    if (vec_ok) IoPair<DVT>::store2(y + t, v.x * scale, v.y * scale);
-                    else { y[t] = (DVT)(v.x * scale); if (t + 1 < L) y[t + 1] = (DVT)(v.y * scale); }
+            for (int i = 0; i < HELD; ++i) {
+                const int t = 2 * (tp + T * i);
+                const float s0 = __builtin_amdgcn_rcpf(1.f + __expf(-u[i].x)), s1 = __builtin_amdgcn_rcpf(1.f + __expf(-u[i].y));
+                const bool two = t + 1 < L;
+                z[i].x = t < L ? z[i].x * scale * s0 * (1.f + u[i].x * (1.f - s0)) : 0.f;
+                z[i].y = two ? z[i].y * scale * s1 * (1.f + u[i].y * (1.f - s1)) : 0.f;
+                *reinterpret_cast<float2*>(su + t) = make_float2(z[i].x, z[i].y);
+                u[i].x = t < L ? u[i].x * s0 : 0.f;
+                u[i].y = two ? u[i].y * s1 : 0.f;
+            }
+            __syncthreads();
+            // dX[t] = sum_j w[j] dU[t + j], shares of dw[j] = sum_t dU[t] x[t - j], in aligned pairs as in short_conv
+            cplx dx[HELD];
+#pragma unroll
+            for (int i = 0; i < HELD; ++i) dx[i] = mk(0.f, 0.f);
+#pragma unroll
+            for (int p = 0; 2 * p <= kFuseTaps; ++p) {
+                if (2 * p <= m) {
+                    const bool ev = 2 * p < m, above = 2 * p + 1 < m;
+                    const float w2p = ev ? wc[2 * p] : 0.f, w2pm1 = p > 0 ? wc[p > 0 ? 2 * p - 1 : 0] : 0.f;
+                    const float w2pp1 = above ? wc[2 * p + 1] : 0.f;
+constexpr int U = HELD < 4 ? HELD : 4;       // steps read together
+#pragma unroll
+                    for (int i0 = 0; i0 < HELD; i0 += U) {
+                        float2 dv[U], xv[U];
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            const int t = 2 * (tp + T * (i0 + u));
+                            dv[u] = *reinterpret_cast<const float2*>(su + t + 2 * p);
+                            xv[u] = *reinterpret_cast<const float2*>(sx + kHist + t - 2 * p);
+                        }
+                        if (p > 0) {
+#pragma unroll
+                            for (int u = 0; u < U; ++u) {
+                                const int i = i0 + u;
+                                dx[i].y = fmaf(w2pm1, dv[u].x, dx[i].y);
+                                tap[p > 0 ? 2 * p - 1 : 0] = fmaf(z[i].x, xv[u].y, tap[p > 0 ? 2 * p - 1 : 0]);
+                            }
+                        }
+                        if (ev && 2 * p < kFuseTaps) {
+#pragma unroll
+                            for (int u = 0; u < U; ++u) {
+                                const int i = i0 + u;
+                                float& tp2 = tap[2 * p < kFuseTaps ? 2 * p : 0];
+                                dx[i] = mk(fmaf(w2p, dv[u].x, dx[i].x), fmaf(w2p, dv[u].y, dx[i].y));
+                                tp2 = fmaf(z[i].x, xv[u].x, fmaf(z[i].y, xv[u].y, tp2));
+                            }
+                        }
+                        if (above && 2 * p + 1 < kFuseTaps) {
+#pragma unroll
+                            for (int u = 0; u < U; ++u) {
+                                const int i = i0 + u;
+                                float& tp1 = tap[2 * p + 1 < kFuseTaps ? 2 * p + 1 : 0];
+                                dx[i].x = fmaf(w2pp1, dv[u].y, dx[i].x);
+                                tp1 = fmaf(z[i].y, xv[u].x, tp1);
+                            }
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
                 }
             }
+            store_steps<M, T, DVT>(dx, dV + row, L, vec_ok, 1.0f, tp);
+#pragma unroll
+            for (int i = 0; i < HELD; ++i) z[i] = u[i];
+        } else {
+            store_steps<M, T, DVT>(z, dV + row, L, vec_ok, scale, tp);
+            if (wc != nullptr) __syncthreads();      // a[] has been read out
+            // ---- v = silu(K_s x) (x itself without a short stage)
+            stage_input<M, T, IO>(xr, wc, m, L, a, tp, z);
         }
-        __syncthreads();
-        // ---- spectrum of v = silu(K_s x) (x itself without a short stage); running sums of DZ conj(V)
-        tp = tid;
-        asm volatile("" : "+v"(tp));
-        stage_input<M, T, IO>(xr, wc, m, L, a, tp);
         if (b + (int)gridDim.y < B) zr.load(dZ + ((long)(b + gridDim.y) * d + c) * L, L, tp);
         __syncthreads();
-        fft_passes<M, T, false>(a, lo, hi, tp);
+        tp = fresh(tid);
+        // ---- its spectrum; running sums of DZ conj(V)
+        fft_forward<M, T>(z, a, lo, hi, tp);
         __syncthreads();
-        tp = tid;
-        asm volatile("" : "+v"(tp));
         {
-            PairTwiddle<M, T> pw(tp);
+            cplx w = pw.first;
+            constexpr int U = NP < 4 ? NP : 4;       // pairs read together
 #pragma unroll
-            for (int i = 0; i < NP; ++i) {
-                const int l = tp + T * i;
-                if (l <= M / 2) {
-                    const int kk = pair_bin<M>(l);
-                    const cplx w = pw.next(l);
-                    cplx Vk, Vmk;
-                    untangle(a[conv_pad(spectrum_pos<M>(kk))], conj(a[conv_pad(spectrum_pos<M>((M - kk) & (M - 1)))]), w,
-                             Vk, Vmk);
-                    const cplx pk = cmul(Gk[i], conj(Vk)), pmk = cmul(Gmk[i], conj(Vmk));
+            for (int i0 = 0; i0 < NP; i0 += U) {
+                cplx A[U], Bc[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) { A[u] = a[pos.first(i0 + u)]; Bc[u] = conj(a[pos.second(i0 + u)]); }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int i = i0 + u;
+                    const bool self = i == 0 && tid == 0;
                     if constexpr (ACC_MEM) {
-                        float4 t = make_float4(pk.x, pk.y, pmk.x, pmk.y);
-                        if (b != (int)blockIdx.y) { const float4 o = accm[l]; t.x += o.x; t.y += o.y; t.z += o.z; t.w += o.w; }
-                        accm[l] = t;
+                        float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+                        if (b != (int)blockIdx.y) t = accm[tid + T * i];
+                        pair_acc(t, GA[i], GB[i], A[u], Bc[u], w, self);
+                        accm[tid + T * i] = t;
                     } else {
-                        accK[i] = cadd(accK[i], pk);
-                        accMK[i] = cadd(accMK[i], pmk);
+                        pair_acc(sums[i], GA[i], GB[i], A[u], Bc[u], w, self);
                     }
+                    w = cmul(w, pw.step);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
+        }
+        __syncthreads();
+    }
+    if constexpr (SHORT) {
+        // this workgroup's tap sums: wave reduction, then across the waves
+        float* red = reinterpret_cast<float*>(a);
+#pragma unroll
+        for (int j = 0; j < kFuseTaps; ++j) {
+            float v = tap[j];
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+            if ((tid & 63) == 0) red[j * (T / 64) + (tid >> 6)] = v;
+        }
+        __syncthreads();
+        if (tid < m) {
+            float v = 0.f;
+            for (int k = 0; k < T / 64; ++k) v += red[tid * (T / 64) + k];
+            part[((long)c * gridDim.y + blockIdx.y) * kShortMaxTaps + tid] = v;
         }
         __syncthreads();
     }
@@ -731,54 +979,27 @@ __global__ __launch_bounds__(conv_threads(M)) void longconv_bwd_kernel(const IO*
         // sums were kept in memory)
         if constexpr (!ACC_MEM) {
 #pragma unroll
-            for (int i = 0; i < NP; ++i) {
-                const int l = tid + T * i;
-                if (l <= M / 2) accm[l] = make_float4(accK[i].x, accK[i].y, accMK[i].x, accMK[i].y);
-            }
+            for (int i = 0; i < NP; ++i) accm[tid + T * i] = sums[i];
         }
         return;
     }
     {
-        PairTwiddle<M, T> pw(tid);
+        cplx w = pw.first;
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
-            const int l = tid + T * i;
-            if (l <= M / 2) {
-                const int kk = pair_bin<M>(l);
-                const int p1 = conv_pad(spectrum_pos<M>(kk)), p2 = conv_pad(spectrum_pos<M>((M - kk) & (M - 1)));
-                const cplx w = pw.next(l);
-                cplx sk, smk;
-                if constexpr (ACC_MEM) {
-                    const float4 t = B > 0 ? accm[l] : make_float4(0.f, 0.f, 0.f, 0.f);
-                    sk = mk(t.x, t.y);
-                    smk = mk(t.z, t.w);
-                } else {
-                    sk = accK[i];
-                    smk = accMK[i];
-                }
-                if (kk == 0) {
-                    a[p1] = mk(0.5f * (sk.x + smk.x), 0.5f * (sk.x - smk.x));
-                } else {
-                    cplx Zk, Zmk;
-                    tangle(sk, smk, w, Zk, Zmk);
-                    a[p1] = Zk;
-                    if (p2 != p1) a[p2] = Zmk;
-                }
-            }
+            float4 t;
+            if constexpr (ACC_MEM) t = B > 0 ? accm[tid + T * i] : make_float4(0.f, 0.f, 0.f, 0.f);
+            else t = sums[i];
+            cplx A, Bc;
+            pair_pack(t, w, i == 0 && tid == 0, A, Bc);
+            a[pos.first(i)] = A;
+            a[pos.second(i)] = conj(Bc);
+            w = cmul(w, pw.step);
         }
     }
     __syncthreads();
-    fft_passes<M, T, true>(a, lo, hi, tid);
-    __syncthreads();
-    float* out = dk + (long)c * L;
-    for (int n = tid; n < M; n += T) {
-        const int t = 2 * n;
-        if (t < L) {
-            const cplx v = a[conv_pad(n)];
-            out[t] = v.x * scale;
-            if (t + 1 < L) out[t + 1] = v.y * scale;
-        }
-    }
+    fft_inverse<M, T>(a, z, lo, hi, tid);
+    store_steps<M, T, float>(z, dk + (long)c * L, L, vec_ok, scale, tid);
 }
 
 // Gradient through the activation and the short kernel.  dV is the gradient with respect to v = silu(u), u = K_s x:
@@ -787,7 +1008,7 @@ __global__ __launch_bounds__(conv_threads(M)) void longconv_bwd_kernel(const IO*
 // (a run may cross from one sequence into the next); x is staged with MT steps of history and dU with MT steps of
 // look-ahead.  Each workgroup leaves its share of the tap sums in `part` ([d][n_share][MT]); shortconv_dw_kernel
 // adds the shares of a channel in a fixed order.
-constexpr int kShortTile = 2048, kShortMaxTaps = 32, kShortTilesPerWg = 4;
+constexpr int kShortTile = 2048, kShortTilesPerWg = 4;
 
 // TAPS: compile-time bound on the number of taps (m <= TAPS <= 32): the tap loops are as long as the kernel needs.
 // Up to 16 taps every count has its own instantiation (the paper's sizes, 3 and 2 log10 L + 1, stay below 16 for any
@@ -945,7 +1166,7 @@ __global__ __launch_bounds__(kBlkT) void longconv_spectrum_blocked_kernel(const 
                                                                                        float4* __restrict__ Gf, int L,
                                                                                        int nb)
 {
-    constexpr int M = kBlkM, T = kBlkT, NP = (M / 2) / T + 1;
+    constexpr int M = kBlkM, T = kBlkT, NP = PairPos<M, T>::NP;
     __shared__ __attribute__((aligned(16))) unsigned char lds[ConvLds<M>::BYTES];
     cplx* a = reinterpret_cast<cplx*>(lds);
     cplx* lo = a + ConvLds<M>::DATA;
@@ -955,6 +1176,10 @@ __global__ __launch_bounds__(kBlkT) void longconv_spectrum_blocked_kernel(const 
     const int mb = blockIdx.y;
     const bool row_vec = (L & 1) == 0;
     build_tables<M, T>(lo, hi, tid);
+    const PairPos<M, T> pos(tid);
+    const PairTwiddle<M, T> pw(tid);
+    // the block before sits in the upper half of the period: (-1)^bin (a thread's bins, k and M - k, all have one parity)
+    const float odd = (pair_bin<M>(tid) & 1) ? -1.f : 1.f;
     float4 sum[NP];
 #pragma unroll
     for (int i = 0; i < NP; ++i) sum[i] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -962,31 +1187,23 @@ __global__ __launch_bounds__(kBlkT) void longconv_spectrum_blocked_kernel(const 
         const int len = min(M, L - which * M);
         SeqRegs<M, T, float> kr;
         kr.load(k + c * (long)L + (long)which * M, len, tid, row_vec);
+        cplx z[M / T / 2];
+        stage_input<M, T, float>(kr, nullptr, 0, len, a, tid, z);
         __syncthreads();                  // tables built / the block before has been read out of a[]
-        stage_input<M, T, float>(kr, nullptr, 0, len, a, tid);
+        fft_forward<M, T>(z, a, lo, hi, tid);
         __syncthreads();
-        fft_passes<M, T, false>(a, lo, hi, tid);
-        __syncthreads();
+        const float sg = which < mb ? odd : 1.f;
+        cplx w = pw.first;
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
-            const int l = tid + T * i;
-            if (l <= M / 2) {
-                const int kk = pair_bin<M>(l);
-                cplx Xk, Xmk;
-                untangle(a[conv_pad(spectrum_pos<M>(kk))], conj(a[conv_pad(spectrum_pos<M>((M - kk) & (M - 1)))]),
-                         w2m(kk, M), Xk, Xmk);
-                // the block before sits in the upper half of the period: (-1)^bin (bins kk and M - kk: same parity)
-                const float sg = (which < mb && (kk & 1)) ? -1.f : 1.f;
-                sum[i].x += sg * Xk.x; sum[i].y += sg * Xk.y; sum[i].z += sg * Xmk.x; sum[i].w += sg * Xmk.y;
-            }
+            const float4 v = pair_kernel(a[pos.first(i)], conj(a[pos.second(i)]), w, i == 0 && tid == 0);
+            sum[i].x += sg * v.x; sum[i].y += sg * v.y; sum[i].z += sg * v.z; sum[i].w += sg * v.w;
+            w = cmul(w, pw.step);
         }
     }
     float4* out = Gf + (c * nb + mb) * (long)(M / 2 + 1);
 #pragma unroll
-    for (int i = 0; i < NP; ++i) {
-        const int l = tid + T * i;
-        if (l <= M / 2) out[l] = sum[i];
-    }
+    for (int i = 0; i < NP; ++i) out[tid + T * i] = sum[i];
 }
 
 // Forward (CORR = false: X -> optional short kernel and activation -> causal sum with the long kernel, block `blk` of
@@ -1000,7 +1217,7 @@ __global__ __launch_bounds__(kBlkT) void longconv_blocked_kernel(const IN* __res
                                                                               OUT* __restrict__ Y, int d, int L, int nb,
                                                                               long BD)
 {
-    constexpr int M = kBlkM, T = kBlkT, NP = (M / 2) / T + 1;
+    constexpr int M = kBlkM, T = kBlkT, NP = PairPos<M, T>::NP;
     __shared__ __attribute__((aligned(16))) unsigned char lds[ConvLds<M>::BYTES];
     cplx* a = reinterpret_cast<cplx*>(lds);
     cplx* lo = a + ConvLds<M>::DATA;
@@ -1009,6 +1226,8 @@ __global__ __launch_bounds__(kBlkT) void longconv_blocked_kernel(const IN* __res
     const bool row_vec = (L & 1) == 0;
     const float scale = 1.0f / (float)M;
     build_tables<M, T>(lo, hi, tid);
+    const PairPos<M, T> pos(tid);
+    const PairTwiddle<M, T> pw(tid);
     const long items = BD * nb;
     for (long id = blockIdx.x; id < items; id += gridDim.x) {
         const int r = (int)(id / BD);
@@ -1018,89 +1237,46 @@ __global__ __launch_bounds__(kBlkT) void longconv_blocked_kernel(const IN* __res
         const int o0 = CORR ? blk : 0, o1 = CORR ? nb - 1 : blk;
         const IN* xrow = X + bc * (long)L;
         const float* wc = (!CORR && w_short) ? w_short + (long)c * m : nullptr;
-        cplx accK[NP], accMK[NP];                           // sums over the input blocks of X_o G_|o - blk|, bins k and M - k
+        cplx accA[NP], accB[NP];                            // sums over the input blocks of X_o G_|o - blk|, packed
 #pragma unroll
-        for (int i = 0; i < NP; ++i) { accK[i] = mk(0.f, 0.f); accMK[i] = mk(0.f, 0.f); }
+        for (int i = 0; i < NP; ++i) { accA[i] = mk(0.f, 0.f); accB[i] = mk(0.f, 0.f); }
         SeqRegs<M, T, IN> xr;
+        cplx z[M / T / 2];
         xr.load(xrow + (long)o0 * M, min(M, L - o0 * M), tid, row_vec);
         for (int o = o0; o <= o1; ++o) {
-            int tp = tid;
-            asm volatile("" : "+v"(tp));
+            int tp = fresh(tid);
             __syncthreads();    // tables built / a[] has been read out
-            stage_input<M, T, IN>(xr, wc, m, min(M, L - o * M), a, tp, (wc && o > 0) ? xrow + (long)o * M : nullptr);
+            stage_input<M, T, IN>(xr, wc, m, min(M, L - o * M), a, tp, z, (wc && o > 0) ? xrow + (long)o * M : nullptr);
             if (o < o1) xr.load(xrow + (long)(o + 1) * M, min(M, L - (o + 1) * M), tp, row_vec);   // the next block, in flight
+            tp = fresh(tid);
+            fft_forward<M, T>(z, a, lo, hi, tp);
             __syncthreads();
-            tp = tid;
-            asm volatile("" : "+v"(tp));
-            fft_passes<M, T, false>(a, lo, hi, tp);
-            __syncthreads();
-            tp = tid;
-            asm volatile("" : "+v"(tp));
+            tp = fresh(tid);
             const float4* Gc = Gf + ((long)c * nb + (CORR ? o - blk : blk - o)) * (long)(M / 2 + 1);
             float4 kq[NP];
 #pragma unroll
-            for (int i = 0; i < NP; ++i) {
-                const int l = tp + T * i;
-                if (l <= M / 2) kq[i] = Gc[l];
-            }
-            PairTwiddle<M, T> pw(tp);
+            for (int i = 0; i < NP; ++i) kq[i] = Gc[tp + T * i];
+            cplx w = pw.first;
 #pragma unroll
             for (int i = 0; i < NP; ++i) {
-                const int l = tp + T * i;
-                if (l <= M / 2) {
-                    const int kk = pair_bin<M>(l);
-                    const cplx w = pw.next(l);
-                    cplx Xk, Xmk;
-                    untangle(a[conv_pad(spectrum_pos<M>(kk))], conj(a[conv_pad(spectrum_pos<M>((M - kk) & (M - 1)))]), w,
-                             Xk, Xmk);
-                    const cplx K1 = mk(kq[i].x, CORR ? -kq[i].y : kq[i].y), K2 = mk(kq[i].z, CORR ? -kq[i].w : kq[i].w);
-                    accK[i] = cadd(accK[i], cmul(Xk, K1));
-                    accMK[i] = cadd(accMK[i], cmul(Xmk, K2));
-                }
+                cplx A = a[pos.first(i)], B = conj(a[pos.second(i)]);
+                pair_mul<CORR>(A, B, w, kq[i], i == 0 && tid == 0);
+                accA[i] = cadd(accA[i], A);
+                accB[i] = cadd(accB[i], B);
+                w = cmul(w, pw.step);
                 __builtin_amdgcn_sched_barrier(0);   // one pair at a time: the unrolled pairs must not pile up in registers
             }
         }
         __syncthreads();        // every thread has read its bins of the last input block
-        {
-            int tp = tid;
-            asm volatile("" : "+v"(tp));
-            PairTwiddle<M, T> pw(tp);
 #pragma unroll
-            for (int i = 0; i < NP; ++i) {
-                const int l = tp + T * i;
-                if (l <= M / 2) {
-                    const int kk = pair_bin<M>(l);
-                    const int p1 = conv_pad(spectrum_pos<M>(kk)), p2 = conv_pad(spectrum_pos<M>((M - kk) & (M - 1)));
-                    const cplx w = pw.next(l);
-                    if (kk == 0) {      // bins 0 and M are real and share storage slot 0
-                        a[p1] = mk(0.5f * (accK[i].x + accMK[i].x), 0.5f * (accK[i].x - accMK[i].x));
-                    } else {
-                        cplx Zk, Zmk;
-                        tangle(accK[i], accMK[i], w, Zk, Zmk);
-                        a[p1] = Zk;
-                        if (p2 != p1) a[p2] = Zmk;
-                    }
-                }
-            }
+        for (int i = 0; i < NP; ++i) {
+            a[pos.first(i)] = accA[i];
+            a[pos.second(i)] = conj(accB[i]);
         }
         __syncthreads();
-        {
-            int tp = tid;
-            asm volatile("" : "+v"(tp));
-            fft_passes<M, T, true>(a, lo, hi, tp);
-            __syncthreads();
-            OUT* y = Y + bc * (long)L + (long)blk * M;
-            const int len = min(M, L - blk * M);
-#pragma unroll
-            for (int i = 0; i < M / T / 2; ++i) {
-                const int n = tp + T * i, t = 2 * n;
-                if (t < len) {
-                    const cplx v = a[conv_pad(n)];
-                    if (row_vec) IoPair<OUT>::store2(y + t, v.x * scale, v.y * scale);
-                    else { y[t] = (OUT)(v.x * scale); if (t + 1 < len) y[t + 1] = (OUT)(v.y * scale); }
-                }
-            }
-        }
+        const int tp = fresh(tid);
+        fft_inverse<M, T>(a, z, lo, hi, tp);
+        store_steps<M, T, OUT>(z, Y + bc * (long)L + (long)blk * M, min(M, L - blk * M), row_vec, scale, tp);
     }
 }
 
@@ -1114,7 +1290,7 @@ __global__ __launch_bounds__(kBlkT) void longconv_dk_blocked_kernel(const IO* __
                                                                                  float4* __restrict__ acc_ws, int B, int d,
                                                                                  int L, int nb)
 {
-    constexpr int M = kBlkM, T = kBlkT, NP = (M / 2) / T + 1;
+    constexpr int M = kBlkM, T = kBlkT, NP = PairPos<M, T>::NP;
     __shared__ __attribute__((aligned(16))) unsigned char lds[ConvLds<M>::BYTES];
     cplx* a = reinterpret_cast<cplx*>(lds);
     cplx* lo = a + ConvLds<M>::DATA;
@@ -1127,65 +1303,41 @@ __global__ __launch_bounds__(kBlkT) void longconv_dk_blocked_kernel(const IO* __
     const float* wc = w_short ? w_short + (long)c * m : nullptr;
     const int n_i = nb - mb;                     // block pairs (i, i + mb) per sequence
     const long n_pairs = (long)B * n_i;
-    cplx Gk[NP], Gmk[NP];
+    const PairPos<M, T> pos(tid);
+    const PairTwiddle<M, T> pw(tid);
+    cplx GA[NP], GB[NP], z[M / T / 2];
     SeqRegs<M, T, IO> zr, xr;
     zr.load(dZ + (long)c * L + (long)mb * M, min(M, L - mb * M), tid, row_vec);      // pair 0: b = 0, i = 0
     for (long pr = 0; pr < n_pairs; ++pr) {
         const int b = (int)(pr / n_i), i = (int)(pr - (long)b * n_i), j = i + mb;
         const long row = ((long)b * d + c) * (long)L;
-        int tp = tid;
-        asm volatile("" : "+v"(tp));
-        __syncthreads();        // tables built / a[] has been read out
-        stage_input<M, T, IO>(zr, nullptr, 0, min(M, L - j * M), a, tp);
+        int tp = fresh(tid);
+        stage_input<M, T, IO>(zr, nullptr, 0, min(M, L - j * M), a, tp, z);
         xr.load(X + row + (long)i * M, min(M, L - i * M), tp, row_vec);
+        __syncthreads();        // tables built / a[] has been read out
+        fft_forward<M, T>(z, a, lo, hi, tp);
         __syncthreads();
-        fft_passes<M, T, false>(a, lo, hi, tp);
-        __syncthreads();
-        tp = tid;
-        asm volatile("" : "+v"(tp));
-        {
-            PairTwiddle<M, T> pw(tp);
 #pragma unroll
-            for (int q = 0; q < NP; ++q) {
-                const int l = tp + T * q;
-                if (l <= M / 2) {
-                    const int kk = pair_bin<M>(l);
-                    untangle(a[conv_pad(spectrum_pos<M>(kk))], conj(a[conv_pad(spectrum_pos<M>((M - kk) & (M - 1)))]),
-                             pw.next(l), Gk[q], Gmk[q]);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
+        for (int q = 0; q < NP; ++q) { GA[q] = a[pos.first(q)]; GB[q] = conj(a[pos.second(q)]); }
         __syncthreads();
-        tp = tid;
-        asm volatile("" : "+v"(tp));
-        stage_input<M, T, IO>(xr, wc, m, min(M, L - i * M), a, tp, (wc && i > 0) ? X + row + (long)i * M : nullptr);
+        tp = fresh(tid);
+        stage_input<M, T, IO>(xr, wc, m, min(M, L - i * M), a, tp, z, (wc && i > 0) ? X + row + (long)i * M : nullptr);
         if (pr + 1 < n_pairs) {
             const int b2 = (int)((pr + 1) / n_i), i2 = (int)(pr + 1 - (long)b2 * n_i);
             zr.load(dZ + ((long)b2 * d + c) * (long)L + (long)(i2 + mb) * M, min(M, L - (i2 + mb) * M), tp, row_vec);
         }
+        tp = fresh(tid);
+        fft_forward<M, T>(z, a, lo, hi, tp);
         __syncthreads();
-        fft_passes<M, T, false>(a, lo, hi, tp);
-        __syncthreads();
-        tp = tid;
-        asm volatile("" : "+v"(tp));
-        {
-            PairTwiddle<M, T> pw(tp);
+        cplx w = pw.first;
 #pragma unroll
-            for (int q = 0; q < NP; ++q) {
-                const int l = tp + T * q;
-                if (l <= M / 2) {
-                    const int kk = pair_bin<M>(l);
-                    cplx Vk, Vmk;
-                    untangle(a[conv_pad(spectrum_pos<M>(kk))], conj(a[conv_pad(spectrum_pos<M>((M - kk) & (M - 1)))]),
-                             pw.next(l), Vk, Vmk);
-                    const cplx pk = cmul(Gk[q], conj(Vk)), pmk = cmul(Gmk[q], conj(Vmk));
-                    float4 t = make_float4(pk.x, pk.y, pmk.x, pmk.y);
-                    if (pr > 0) { const float4 o = accm[l]; t.x += o.x; t.y += o.y; t.z += o.z; t.w += o.w; }
-                    accm[l] = t;
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
+        for (int q = 0; q < NP; ++q) {
+            float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+            if (pr > 0) t = accm[tid + T * q];
+            pair_acc(t, GA[q], GB[q], a[pos.first(q)], conj(a[pos.second(q)]), w, q == 0 && tid == 0);
+            accm[tid + T * q] = t;
+            w = cmul(w, pw.step);
+            __builtin_amdgcn_sched_barrier(0);
         }
     }
 }
@@ -1205,41 +1357,27 @@ __global__ __launch_bounds__(kBlkT) void longconv_dk_blocked_finish_kernel(const
     build_tables<M, T>(lo, hi, tid);
     const float4* D0 = acc_ws + ((long)c * nb + mb) * (long)(M / 2 + 1);
     const float4* D1 = mb + 1 < nb ? D0 + (M / 2 + 1) : nullptr;
-    PairTwiddle<M, T> pw(tid);
-    for (int l = tid; l <= M / 2; l += T) {
-        const int kk = pair_bin<M>(l);
-        const int p1 = conv_pad(spectrum_pos<M>(kk)), p2 = conv_pad(spectrum_pos<M>((M - kk) & (M - 1)));
-        const cplx w = pw.next(l);
-        float4 t = D0[l];
+    const PairPos<M, T> pos(tid);
+    const PairTwiddle<M, T> pw(tid);
+    const float odd = (pair_bin<M>(tid) & 1) ? -1.f : 1.f;
+    cplx w = pw.first;
+#pragma unroll
+    for (int i = 0; i < PairPos<M, T>::NP; ++i) {
+        float4 t = D0[tid + T * i];
         if (D1 != nullptr) {
-            const float4 o = D1[l];
-            const float sg = (kk & 1) ? -1.f : 1.f;
-            t.x += sg * o.x; t.y += sg * o.y; t.z += sg * o.z; t.w += sg * o.w;
+            const float4 o = D1[tid + T * i];
+            t.x += odd * o.x; t.y += odd * o.y; t.z += odd * o.z; t.w += odd * o.w;
         }
-        const cplx sk = mk(t.x, t.y), smk = mk(t.z, t.w);
-        if (kk == 0) {
-            a[p1] = mk(0.5f * (sk.x + smk.x), 0.5f * (sk.x - smk.x));
-        } else {
-            cplx Zk, Zmk;
-            tangle(sk, smk, w, Zk, Zmk);
-            a[p1] = Zk;
-            if (p2 != p1) a[p2] = Zmk;
-        }
+        cplx A, B;
+        pair_pack(t, w, i == 0 && tid == 0, A, B);
+        a[pos.first(i)] = A;
+        a[pos.second(i)] = conj(B);
+        w = cmul(w, pw.step);
     }
     __syncthreads();
-    fft_passes<M, T, true>(a, lo, hi, tid);
-    __syncthreads();
-    float* out = dk + (long)c * L + (long)mb * M;
-    const int len = min(M, L - mb * M);
-    const float scale = 1.0f / (float)M;
-    for (int n = tid; n < M / 2; n += T) {
-        const int t = 2 * n;
-        if (t < len) {
-            const cplx v = a[conv_pad(n)];
-            out[t] = v.x * scale;
-            if (t + 1 < len) out[t + 1] = v.y * scale;
-        }
-    }
+    cplx z[M / T / 2];
+    fft_inverse<M, T>(a, z, lo, hi, tid);
+    store_steps<M, T, float>(z, dk + (long)c * L + (long)mb * M, min(M, L - mb * M), (L & 1) == 0, 1.0f / (float)M, tid);
 }
 
 int conv_fft_size(int L)
@@ -1260,13 +1398,16 @@ hipError_t launch_longconv_spectrum(const float* k, void* Kf, int d, int L, hipS
         hipLaunchKernelGGL(longconv_spectrum_blocked_kernel, dim3(d, nb), dim3(kBlkT), 0, st, k, out, L, nb);
         return hipGetLastError();
     }
+    uint4* mx = (uint4*)((char*)Kf + conv_pairs_bytes(d, L));
+    float* scale = (float*)((char*)mx + (size_t)d * 32768 * sizeof(unsigned));
+#define CHELA_SPECTRUM(M_, MX_)                                                                                         \
+    case M_: hipLaunchKernelGGL((longconv_spectrum_kernel<M_, MX_>), dim3(d), dim3(conv_threads(M_)), 0, st, k, out, mx,  \
+                                scale, L); break;
     switch (M) {
-        case 256: hipLaunchKernelGGL((longconv_spectrum_kernel<256>), dim3(d), dim3(conv_threads(256)), 0, st, k, out, L); break;
-        case 1024: hipLaunchKernelGGL((longconv_spectrum_kernel<1024>), dim3(d), dim3(conv_threads(1024)), 0, st, k, out, L); break;
-        case 4096: hipLaunchKernelGGL((longconv_spectrum_kernel<4096>), dim3(d), dim3(conv_threads(4096)), 0, st, k, out, L); break;
-        case 16384: hipLaunchKernelGGL((longconv_spectrum_kernel<16384>), dim3(d), dim3(conv_threads(16384)), 0, st, k, out, L); break;
+        CHELA_SPECTRUM(256, false) CHELA_SPECTRUM(1024, false) CHELA_SPECTRUM(4096, false) CHELA_SPECTRUM(16384, true)
         default: return hipErrorInvalidValue;
     }
+#undef CHELA_SPECTRUM
     return hipGetLastError();
 }
 
@@ -1342,44 +1483,32 @@ __global__ __launch_bounds__(conv_threads(M)) void longconv_dk_finish_kernel(con
     const int tid = threadIdx.x;
     const int c = blockIdx.x;
     build_tables<M, T>(lo, hi, tid);
-    PairTwiddle<M, T> pw(tid);
-    for (int l = tid; l <= M / 2; l += T) {
-        const int kk = pair_bin<M>(l);
-        const int p1 = conv_pad(spectrum_pos<M>(kk)), p2 = conv_pad(spectrum_pos<M>((M - kk) & (M - 1)));
-        const cplx w = pw.next(l);
+    const PairPos<M, T> pos(tid);
+    const PairTwiddle<M, T> pw(tid);
+    cplx w = pw.first;
+#pragma unroll
+    for (int i = 0; i < PairPos<M, T>::NP; ++i) {
         float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
         for (int g = 0; g < G; ++g) {      // fixed order: deterministic
-            const float4 o = part[((long)g * d + c) * (M / 2 + 1) + l];
+            const float4 o = part[((long)g * d + c) * (M / 2 + 1) + tid + T * i];
             t.x += o.x; t.y += o.y; t.z += o.z; t.w += o.w;
         }
-        const cplx sk = mk(t.x, t.y), smk = mk(t.z, t.w);
-        if (kk == 0) {
-            a[p1] = mk(0.5f * (sk.x + smk.x), 0.5f * (sk.x - smk.x));
-        } else {
-            cplx Zk, Zmk;
-            tangle(sk, smk, w, Zk, Zmk);
-            a[p1] = Zk;
-            if (p2 != p1) a[p2] = Zmk;
-        }
+        cplx A, B;
+        pair_pack(t, w, i == 0 && tid == 0, A, B);
+        a[pos.first(i)] = A;
+        a[pos.second(i)] = conj(B);
+        w = cmul(w, pw.step);
     }
     __syncthreads();
-    fft_passes<M, T, true>(a, lo, hi, tid);
-    __syncthreads();
-    float* out = dk + (long)c * L;
-    const float scale = 1.0f / (float)M;
-    for (int n = tid; n < M; n += T) {
-        const int t = 2 * n;
-        if (t < L) {
-            const cplx v = a[conv_pad(n)];
-            out[t] = v.x * scale;
-            if (t + 1 < L) out[t + 1] = v.y * scale;
-        }
-    }
+    cplx z[M / T / 2];
+    fft_inverse<M, T>(a, z, lo, hi, tid);
+    store_steps<M, T, float>(z, dk + (long)c * L, L, (L & 1) == 0, 1.0f / (float)M, tid);
 }
 
-template <typename IO, typename DVT>
+// SHORT: the short stage's gradient in the same kernel (dV is dX then, `part` takes the tap sums).
+template <typename IO, typename DVT, bool SHORT>
 static hipError_t conv_longbwd_dispatch(const IO* X, const float* w, int m, const float4* Kf, const IO* dZ, DVT* dV,
-                                        float* dk, float4* acc_ws, int B, int d, int L, hipStream_t st)
+                                        float* dk, float4* acc_ws, float* part, int B, int d, int L, hipStream_t st)
 {
     const int M = conv_fft_size(L), G = conv_bwd_groups(B, d, L);
     ProfScope prof(KID_CONV_LONG_BWD, st);
@@ -1396,18 +1525,18 @@ static hipError_t conv_longbwd_dispatch(const IO* X, const float* w, int m, cons
         return hipGetLastError();
     }
     const dim3 grid(d, G);
-#define CHELA_LONGBWD(M_)                                                                                               \
+#define CHELA_LONGBWD(M_, SHORT_)                                                                                       \
     case M_:                                                                                                            \
         if (G > 1) {                                                                                                    \
-            hipLaunchKernelGGL((longconv_bwd_kernel<M_, IO, DVT, true>), grid, dim3(conv_threads(M_)), 0, st, X, w, m, Kf, \
-                               dZ, dV, dk, acc_ws, B, d, L);                                                            \
+            hipLaunchKernelGGL((longconv_bwd_kernel<M_, IO, DVT, true, SHORT_>), grid, dim3(conv_threads(M_)), 0, st, X, w, \
+                               m, Kf, dZ, dV, dk, acc_ws, part, B, d, L);                                               \
             hipLaunchKernelGGL((longconv_dk_finish_kernel<M_>), dim3(d), dim3(conv_threads(M_)), 0, st, acc_ws, dk, G, d, L); \
         } else                                                                                                          \
-            hipLaunchKernelGGL((longconv_bwd_kernel<M_, IO, DVT, false>), grid, dim3(conv_threads(M_)), 0, st, X, w, m, Kf, \
-                               dZ, dV, dk, acc_ws, B, d, L);                                                            \
+            hipLaunchKernelGGL((longconv_bwd_kernel<M_, IO, DVT, false, SHORT_>), grid, dim3(conv_threads(M_)), 0, st, X, w, \
+                               m, Kf, dZ, dV, dk, acc_ws, part, B, d, L);                                               \
         break;
     switch (M) {
-        CHELA_LONGBWD(256) CHELA_LONGBWD(1024) CHELA_LONGBWD(4096) CHELA_LONGBWD(16384)
+        CHELA_LONGBWD(256, SHORT) CHELA_LONGBWD(1024, SHORT) CHELA_LONGBWD(4096, SHORT) CHELA_LONGBWD(16384, false)
         default: return hipErrorInvalidValue;
     }
 #undef CHELA_LONGBWD
@@ -1429,15 +1558,23 @@ static hipError_t conv_bwd_impl(const IO* X, const float* w_short, int m, const 
     const void* mx_spec = (const char*)Kf + conv_pairs_bytes(d, L);
     if (w_short == nullptr) { // no short stage: v = x and dX is the correlation of dZ with the long kernel itself
         if (mx) return launch_convmx_longbwd(X, nullptr, 0, mx_spec, dZ, dX, false, dk, (float*)acc_ws, B, d, L, st);
-        return conv_longbwd_dispatch<IO, IO>(X, nullptr, 0, Kf, dZ, dX, dk, acc_ws, B, d, L, st);
+        return conv_longbwd_dispatch<IO, IO, false>(X, nullptr, 0, Kf, dZ, dX, dk, acc_ws, nullptr, B, d, L, st);
     }
     float* ws_dV = ws;
     const long n_items = (long)B * ((L + kShortTile - 1) / kShortTile);                     // (batch entry, tile) pairs
     const int n_share = (int)((n_items + kShortTilesPerWg - 1) / kShortTilesPerWg);         // workgroups per channel
     if ((long)d * n_share > 0x7fffffffL) return hipErrorInvalidValue;
     float* ws_part = ws + (size_t)BD * L;                                   // [d][n_share][32] (room for [d][B * tiles][32])
+    if (m <= kFuseTaps && L <= 4096) {
+        const int G = conv_bwd_groups(B, d, L);                             // workgroups that share a channel (<= B)
+        e = conv_longbwd_dispatch<IO, IO, true>(X, w_short, m, Kf, dZ, dX, dk, acc_ws, ws_part, B, d, L, st);
+        if (e != hipSuccess) return e;
+        ProfScope prof(KID_CONV_SHORT_BWD, st);
+        hipLaunchKernelGGL(shortconv_dw_kernel, dim3(d), dim3(64), 0, st, ws_part, dw, m, G);
+        return hipGetLastError();
+    }
     e = mx ? launch_convmx_longbwd(X, w_short, m, mx_spec, dZ, ws_dV, true, dk, (float*)acc_ws, B, d, L, st)
-           : conv_longbwd_dispatch<IO, float>(X, w_short, m, Kf, dZ, ws_dV, dk, acc_ws, B, d, L, st);
+           : conv_longbwd_dispatch<IO, float, false>(X, w_short, m, Kf, dZ, ws_dV, dk, acc_ws, nullptr, B, d, L, st);
     if (e != hipSuccess) return e;
     {
         ProfScope prof(KID_CONV_SHORT_BWD, st);

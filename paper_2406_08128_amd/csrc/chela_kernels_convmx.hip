@@ -237,47 +237,6 @@ __device__ __forceinline__ void mx_pass(unsigned* cube, const f16x8 (&A)[2][4], 
     }
 }
 
-// Spectrum of one channel's long kernel for these passes: bin k = k1 + 32 k2 + 1024 k3 of the 32768-point transform,
-// divided by 4 |k|_1, as half-precision (re, im) pairs, stored where the lane that holds it after the forward passes
-// will look:
-// index ((k1 * 4 + s) * 64 + lane) * 4 + i with lane = k2 + 32 h and k3 = 8 s + 4 h + i.  Taken from the array of
-// (K[k], K[16384 - k]) pairs, k = 0 .. 8192, that the spectrum kernel of the other convolution kernels leaves (the
-// spectrum of a real sequence: the upper half is the conjugate of the lower).  scale[c] = 4 |k|_1.
-__global__ __launch_bounds__(1024) void convmx_spectrum_kernel(const float* __restrict__ k_long,
-                                                               const float4* __restrict__ pairs, unsigned* __restrict__ Ks,
-                                                               float* __restrict__ scale, int L)
-{
-    __shared__ float red[16];
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    const long c = blockIdx.x;
-    float sum = 0.f;
-    for (int t = tid; t < L; t += 1024) sum += fabsf(k_long[c * L + t]);
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) sum += __shfl_xor(sum, o);
-    if (lane == 0) red[w] = sum;
-    __syncthreads();
-    float n1 = 0.f;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) n1 += red[i];
-    const float inv = n1 > 0.f ? 0.25f / n1 : 0.f;
-    if (tid == 0) scale[c] = n1 > 0.f ? 4.f * n1 : 0.f;
-    const float4* pc = pairs + c * (long)(8192 + 1);
-    unsigned* out = Ks + c * (long)MX_N;
-    for (int o = tid; o < MX_N; o += 1024) {
-        const int t = o >> 10, s = (o >> 8) & 3, ln = (o >> 2) & 63, i = o & 3;
-        const int k = t + 32 * (ln & 31) + 1024 * (8 * s + 4 * (ln >> 5) + i);
-        const bool upper = k > 16384;
-        const int kk = upper ? MX_N - k : k;                 // 0 .. 16384
-        const bool second = kk > 8192;
-        const int kp = second ? 16384 - kk : kk;             // 0 .. 8192: the pair that holds bin kk
-        const int l = kp == 8192 ? 8192 : (((kp & 127) << 6) | (kp >> 7));
-        const float4 v = pc[l];
-        float re = second ? v.z : v.x, im = second ? v.w : v.y;
-        if (upper) im = -im;
-        out[o] = mx_pack(re * inv, im * inv);
-    }
-}
-
 // 32 consecutive steps [t0, t0 + 32) of one sequence (t0 = 32 tid: one row of the cube) through the short kernel and
 // the activation, from registers only: the steps themselves and the HALO steps in front of them (the taps' history;
 // zero in front of the sequence) come in as 16-byte pieces.  L is a multiple of 8 (so are the rows' starts), pieces
@@ -726,14 +685,6 @@ size_t convmx_spectrum_bytes(int d, int L)
 {
     if (d <= 0 || L <= 4096 || L > MX_L_MAX) return 0;
     return (size_t)d * MX_N * sizeof(unsigned) + (((size_t)d * sizeof(float) + 255) & ~(size_t)255);
-}
-
-hipError_t launch_convmx_spectrum(const float* k_long, const void* pairs, void* extra, int d, int L, hipStream_t st)
-{
-    unsigned* Ks = (unsigned*)extra;
-    float* scale = (float*)((char*)extra + (size_t)d * MX_N * sizeof(unsigned));
-    hipLaunchKernelGGL(convmx_spectrum_kernel, dim3(d), dim3(1024), 0, st, k_long, (const float4*)pairs, Ks, scale, L);
-    return hipGetLastError();
 }
 
 hipError_t launch_convmx_fwd(const void* X, const float* w_short, int m, const void* extra, void* Y, int B, int d, int L,

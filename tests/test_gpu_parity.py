@@ -1000,6 +1000,14 @@ def test_zqk_training_pair_lm_full_size():
 
 
 # ------------------------------------------------------------------------------------------ short-long convolution, gradient
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("Lm", [(1, 1), (33, 16), (255, 1), (256, 16), (257, 17), (1023, 2), (1024, 16), (1025, 15),
+                                (4095, 16), (4096, 3), (4090, 17), (4097, 16)])
+def test_conv_gradient_short_stage_in_and_out_of_the_transform_kernel(Lm, dtype):
+    # up to 16 taps and 4096 steps the short stage's gradient is part of the transform kernel: both sides of both limits
+    _run_conv_bwd_case(3, 2, Lm[0], Lm[1], dtype, seed=Lm[0] + Lm[1])
+
+
 def _run_conv_bwd_case(B, d, L, m, dtype, seed, short=True):
     print("\nconv bwd B%d d%d L%d m%d %s short=%s" % (B, d, L, m, dtype, short), flush=True)
     x = make_conv_inputs(B, d, L, m, seed, dtype)
