@@ -612,6 +612,26 @@ def test_state_carry_forward_and_backward(shape):
         assert err <= 1e-5, (name, err)
 
 
+@pytest.mark.parametrize("shape", [(1, 2, 64, 64, 64), (3, 12, 1531, 64, 64), (1, 3, 9000, 64, 64), (2, 3, 1000, 64, 128),
+                                   (2, 3, 1000, 128, 64), (1, 2, 1500, 128, 128), (300, 1, 130, 64, 64)])
+def test_state_carried_in_place_or_not_gives_the_same(shape):
+    # one segment, segments whose totals the sweeps add up (not in place), scanned ones (in place; many segments): the
+    # sums are added in one order either way, so the results agree bit for bit, and the untouched state stays as it was
+    B, H, N, dk, dv = shape
+    w = shrink(WORKLOADS["lm_bf16"], B=B, H=H, N=N, dk=dk, dv=dv, seed=500 + N)
+    x = make_inputs(w)
+    d = _dev(x)
+    S_in = _state((B, H, dk, dv), 13, 2.0).cuda()
+    keep, S = S_in.clone(), S_in.clone()
+    O1, S1 = binding.chela_linattn_fwd_state(d["Q"], d["K"], d["V"], S_in=S_in)
+    O2, S2 = binding.chela_linattn_fwd_state(d["Q"], d["K"], d["V"], S_in=S, S_out=S)
+    assert S2 is S and torch.equal(S_in, keep)
+    assert torch.equal(O1, O2) and torch.equal(S1, S2)
+    rO, rS = oracle.fwd_state(*(to_f64_numpy(x[n][:2]) for n in "QKV"), S_in=keep[:2].cpu().double().numpy())
+    _check("O", O1[:2], rO, "bf16")
+    assert oracle.rel_l2(to_f64_numpy(S1[:2]), rS) <= 1e-5
+
+
 def test_state_outputs_without_state_inputs():
     # S_out and dS_in alone (no carried-in state): the stateless kernels with one extra store
     w = shrink(WORKLOADS["lm_bf16"], B=1, H=2, N=1300, seed=77)
