@@ -1002,23 +1002,162 @@ constexpr int U = HELD < 4 ? HELD : 4;       // steps read together
     store_steps<M, T, float>(z, dk + (long)c * L, L, vec_ok, scale, tid);
 }
 
-// Gradient through the activation and the short kernel.  dV is the gradient with respect to v = silu(u), u = K_s x:
+// Gradient through the activation and the short kernel, where the transform kernel does not work it out itself.  dV is the
+// gradient with respect to v = silu(u), u = K_s x:
 //   dU = dV silu'(u),  dX[t] = sum_j w[j] dU[t+j],  dw[c][j] = sum_b sum_t dU[b,c,t] x[b,c,t-j].
-// The (batch entry, tile of TL steps) pairs of a channel are dealt out to workgroups in runs of kShortTilesPerWg
-// (a run may cross from one sequence into the next); x is staged with MT steps of history and dU with MT steps of
-// look-ahead.  Each workgroup leaves its share of the tap sums in `part` ([d][n_share][MT]); shortconv_dw_kernel
-// adds the shares of a channel in a fixed order.
+// Up to 16 taps (the paper's sizes, 3 and 2 log10 L + 1, stay below that for any L up to 10^7): every wave for itself, no
+// LDS and no barrier.  A lane holds 8 consecutive steps; x's history it reads along (a line its neighbour reads too), dU
+// ahead it gets from the next lanes' registers, so that the last one or two lanes of a strip only supply: 63 (62) x 8 steps
+// per strip.  A wave walks kStripsPerWave strips of a channel, the next strip's loads in flight.  Each workgroup leaves its
+// share of the tap sums in `part` ([d][n_share][kShortMaxTaps]); shortconv_dw_kernel adds the shares of a channel in a fixed
+// order.  TAPS: the number of taps, the tap loops are as long as the kernel needs.
+// 4 x 768 sequences of 16384 steps, bf16, 9 taps (403 MB): 86 us; staged through LDS by 2048 steps, x twice and dU once
+// with two-way bank conflicts and three barriers, 117; with branches around plain loads 97.
+constexpr int kStripsPerWave = 8;
+__host__ __device__ constexpr int strip_steps(int taps) { return (64 - (taps + 6) / 8) * 8; }
+
+// Eight consecutive elements as they sit in memory.
+template <typename IO> struct Raw8 {
+    static constexpr int NR = sizeof(IO) / 2;
+    uint4 r[NR];
+    // Steps t .. t + 7 of a row of L (a multiple of 8, as t is: whole or empty), zero outside it.  Buffer loads: the bounds
+    // check is theirs, where branches around plain loads cost a third of the kernel's instructions in selects and copies.
+    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t row, int t)
+    {
+#pragma unroll
+        for (int k = 0; k < NR; ++k)
+            r[k] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(row, t * (int)sizeof(IO) + 16 * k, 0, 0));
+    }
+    // any t and L
+    __device__ __forceinline__ void load(const IO* __restrict__ x, int t, int L)
+    {
+        IO v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = (t + e >= 0 && t + e < L) ? x[t + e] : (IO)0.f;
+        __builtin_memcpy(r, v, sizeof(v));
+    }
+    __device__ __forceinline__ void unpack(float* v) const
+    {
+        if constexpr (sizeof(IO) == 2) {
+            const unsigned w[4] = {r[0].x, r[0].y, r[0].z, r[0].w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                v[2 * e] = __builtin_bit_cast(float, w[e] << 16);
+                v[2 * e + 1] = __builtin_bit_cast(float, w[e] & 0xffff0000u);
+            }
+        } else {
+            __builtin_memcpy(v, r, 32);
+        }
+    }
+};
+
+__device__ __forceinline__ float from_next_lane(float v)        // lane i: the value of lane i + 1 (lane 63: anything)
+{
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x130, 0xf, 0xf, false));
+}
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void* row, int bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(row), 0, bytes, 0x00020000);     // (untyped, raw offsets)
+}
+
+// VEC: L is a multiple of 8 (every row starts on a 16-byte boundary).
+template <typename IO, int TAPS, bool VEC>
+__global__ __launch_bounds__(256) void shortconv_bwd_kernel(const IO* __restrict__ X, const float* __restrict__ w_short,
+                                                           const float* __restrict__ dV, IO* __restrict__ dX,
+                                                           float* __restrict__ part, int B, int d, int L, int n_share)
+{
+    constexpr int AHEAD = (TAPS + 6) / 8, STEPS = strip_steps(TAPS);      // lanes that supply; steps of a strip
+    constexpr int NH = AHEAD;                                             // pieces of 8 steps of history
+    __shared__ float red[TAPS][4];
+    const int tid = threadIdx.x, lane = tid & 63, c = blockIdx.x % d, share = blockIdx.x / d;      // channels fastest
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int per_row = (L + STEPS - 1) / STEPS, n_items = B * per_row;
+    float acc[TAPS];
+#pragma unroll
+    for (int j = 0; j < TAPS; ++j) acc[j] = 0.f;
+    Raw8<IO> xr[NH + 1];
+    Raw8<float> gr;
+    auto fetch = [&](int item) __attribute__((always_inline)) {
+        const int b = item / per_row, t = (item - b * per_row) * STEPS + 8 * lane;
+        const long row = ((long)b * d + c) * L;
+        if constexpr (VEC) {
+            const __amdgpu_buffer_rsrc_t rx = row_rsrc(X + row, L * (int)sizeof(IO)), rg = row_rsrc(dV + row, L * 4);
+#pragma unroll
+            for (int k = 0; k <= NH; ++k) xr[k].load(rx, t - 8 * (NH - k));
+            gr.load(rg, t);
+        } else {
+#pragma unroll
+            for (int k = 0; k <= NH; ++k) xr[k].load(X + row, t - 8 * (NH - k), L);
+            gr.load(dV + row, t, L);
+        }
+    };
+    const int first = (share * 4 + w) * kStripsPerWave, last = min(first + kStripsPerWave, n_items);
+    if (first < last) fetch(first);
+    for (int item = first; item < last; ++item) {
+        const int b = item / per_row, t = (item - b * per_row) * STEPS + 8 * lane;
+        float x[8 * (NH + 1)], g[8], du[8 * (AHEAD + 1)];
+#pragma unroll
+        for (int k = 0; k <= NH; ++k) xr[k].unpack(x + 8 * k);
+        gr.unpack(g);
+        if (item + 1 < last) fetch(item + 1);
+        float wj[TAPS];
+#pragma unroll
+        for (int j = 0; j < TAPS; ++j) wj[j] = w_short[(long)c * TAPS + j];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            float u = 0.f;
+#pragma unroll
+            for (int j = 0; j < TAPS; ++j) u = fmaf(wj[j], x[8 * NH + e - j], u);
+            const float sg = __builtin_amdgcn_rcpf(1.f + __expf(-u));
+            du[e] = t + (VEC ? 0 : e) < L ? g[e] * sg * (1.f + u * (1.f - sg)) : 0.f;
+        }
+#pragma unroll
+        for (int e = 0; e < 8 * AHEAD; ++e) du[8 + e] = from_next_lane(du[e]);
+        if (lane < 64 - AHEAD) {
+            float dx[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                float v = 0.f;
+#pragma unroll
+                for (int j = 0; j < TAPS; ++j) {
+                    v = fmaf(wj[j], du[e + j], v);
+                    acc[j] = fmaf(du[e], x[8 * NH + e - j], acc[j]);
+                }
+                dx[e] = v;
+            }
+            IO* y = dX + ((long)b * d + c) * L + t;
+            if constexpr (VEC) { if (t < L) store8(y, dx); }
+            else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) if (t + e < L) y[e] = (IO)dx[e];
+            }
+        }
+    }
+    // this workgroup's tap sums: wave reduction, then across the four waves
+#pragma unroll
+    for (int j = 0; j < TAPS; ++j) {
+        float v = acc[j];
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
+        if (lane == 0) red[j][w] = v;
+    }
+    __syncthreads();
+    if (tid < TAPS)
+        part[((long)c * n_share + share) * kShortMaxTaps + tid] = red[tid][0] + red[tid][1] + red[tid][2] + red[tid][3];
+}
+
+// More taps (m <= 32): the (batch entry, tile of TL steps) pairs of a channel are dealt out to workgroups in runs of
+// kShortTilesPerWg (a run may cross from one sequence into the next); x is staged with MT steps of history and dU with MT
+// steps of look-ahead.
 constexpr int kShortTile = 2048, kShortTilesPerWg = 4;
 
-// TAPS: compile-time bound on the number of taps (m <= TAPS <= 32): the tap loops are as long as the kernel needs.
-// Up to 16 taps every count has its own instantiation (the paper's sizes, 3 and 2 log10 L + 1, stay below 16 for any
-// L up to 10^7) with 16 steps of history and look-ahead; longer kernels share one with 32.
-template <typename IO, int TAPS>
-__global__ __launch_bounds__(256) void shortconv_bwd_kernel(const IO* __restrict__ X, const float* __restrict__ w_short,
+template <typename IO>
+__global__ __launch_bounds__(256) void shortconv_bwd_staged_kernel(const IO* __restrict__ X, const float* __restrict__ w_short,
                                                            int m, const float* __restrict__ dV, IO* __restrict__ dX,
                                                            float* __restrict__ part, int B, int d, int L, int n_share)
 {
-    constexpr int TL = kShortTile, MT = TAPS <= 16 ? 16 : 32, H = MT;  // H: halo on either side
+    constexpr int TL = kShortTile, TAPS = kShortMaxTaps, MT = TAPS, H = MT;  // H: halo on either side
     constexpr int NX = MT + 8;                                        // inputs behind eight consecutive outputs
     __shared__ __attribute__((aligned(16))) float sx[TL + 2 * H];      // x[t0 - H .. t0 + TL + H)
     __shared__ __attribute__((aligned(16))) float su[TL + H + 8];      // dU[t0 .. t0 + TL + H) (+ slack for 16-byte reads)
@@ -1561,9 +1700,12 @@ static hipError_t conv_bwd_impl(const IO* X, const float* w_short, int m, const 
         return conv_longbwd_dispatch<IO, IO, false>(X, nullptr, 0, Kf, dZ, dX, dk, acc_ws, nullptr, B, d, L, st);
     }
     float* ws_dV = ws;
-    const long n_items = (long)B * ((L + kShortTile - 1) / kShortTile);                     // (batch entry, tile) pairs
-    const int n_share = (int)((n_items + kShortTilesPerWg - 1) / kShortTilesPerWg);         // workgroups per channel
-    if ((long)d * n_share > 0x7fffffffL) return hipErrorInvalidValue;
+    // workgroups per channel: (batch entry, strip) or (batch entry, tile) pairs over what one takes
+    const bool strips = m <= 16;
+    const long n_items = (long)B * (strips ? (L + strip_steps(m) - 1) / strip_steps(m) : (L + kShortTile - 1) / kShortTile);
+    const long per_wg = strips ? 4 * kStripsPerWave : kShortTilesPerWg;
+    const int n_share = (int)((n_items + per_wg - 1) / per_wg);
+    if ((long)d * n_share > 0x7fffffffL || n_items > 0x7ffffff0L) return hipErrorInvalidValue;
     float* ws_part = ws + (size_t)BD * L;                                   // [d][n_share][32] (room for [d][B * tiles][32])
     if (m <= kFuseTaps && L <= 4096) {
         const int G = conv_bwd_groups(B, d, L);                             // workgroups that share a channel (<= B)
@@ -1579,11 +1721,15 @@ static hipError_t conv_bwd_impl(const IO* X, const float* w_short, int m, const 
     {
         ProfScope prof(KID_CONV_SHORT_BWD, st);
         const dim3 grid((unsigned)((long)d * n_share));
-        // one instantiation per tap count: the tap loops are a third of this kernel's instructions
+        // one instantiation per tap count: the tap loops are most of this kernel's instructions
 #define CHELA_SHORT_BWD(T_)                                                                                             \
     case T_:                                                                                                            \
-        hipLaunchKernelGGL((shortconv_bwd_kernel<IO, T_>), grid, dim3(256), 0, st, X, w_short, m, ws_dV, dX, ws_part, B, d,  \
-                           L, n_share);                                                                                 \
+        if ((L & 7) == 0)                                                                                               \
+            hipLaunchKernelGGL((shortconv_bwd_kernel<IO, T_, true>), grid, dim3(256), 0, st, X, w_short, ws_dV, dX, ws_part, \
+                               B, d, L, n_share);                                                                       \
+        else                                                                                                            \
+            hipLaunchKernelGGL((shortconv_bwd_kernel<IO, T_, false>), grid, dim3(256), 0, st, X, w_short, ws_dV, dX, ws_part, \
+                               B, d, L, n_share);                                                                       \
         break;
         switch (m) {
             CHELA_SHORT_BWD(1) CHELA_SHORT_BWD(2) CHELA_SHORT_BWD(3) CHELA_SHORT_BWD(4) CHELA_SHORT_BWD(5) CHELA_SHORT_BWD(6)
@@ -1591,7 +1737,7 @@ static hipError_t conv_bwd_impl(const IO* X, const float* w_short, int m, const 
             CHELA_SHORT_BWD(12) CHELA_SHORT_BWD(13) CHELA_SHORT_BWD(14) CHELA_SHORT_BWD(15) CHELA_SHORT_BWD(16)
             default:
                 if (m < 17 || m > kShortMaxTaps) return hipErrorInvalidValue;
-                hipLaunchKernelGGL((shortconv_bwd_kernel<IO, 32>), grid, dim3(256), 0, st, X, w_short, m, ws_dV, dX, ws_part,
+                hipLaunchKernelGGL((shortconv_bwd_staged_kernel<IO>), grid, dim3(256), 0, st, X, w_short, m, ws_dV, dX, ws_part,
                                    B, d, L, n_share);
         }
 #undef CHELA_SHORT_BWD

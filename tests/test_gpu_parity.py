@@ -1022,9 +1022,11 @@ def test_zqk_training_pair_lm_full_size():
 # ------------------------------------------------------------------------------------------ short-long convolution, gradient
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("Lm", [(1, 1), (33, 16), (255, 1), (256, 16), (257, 17), (1023, 2), (1024, 16), (1025, 15),
-                                (4095, 16), (4096, 3), (4090, 17), (4097, 16)])
+                                (4095, 16), (4096, 3), (4090, 17), (4097, 16), (4104, 1), (4104, 9), (4544, 10),
+                                (4969, 2)])
 def test_conv_gradient_short_stage_in_and_out_of_the_transform_kernel(Lm, dtype):
-    # up to 16 taps and 4096 steps the short stage's gradient is part of the transform kernel: both sides of both limits
+    # up to 16 taps and 4096 steps the short stage's gradient is part of the transform kernel: both sides of both limits;
+    # beyond, strips of 512, 504 or 496 steps: whole and ragged ones, rows on and off 16-byte boundaries
     _run_conv_bwd_case(3, 2, Lm[0], Lm[1], dtype, seed=Lm[0] + Lm[1])
 
 
