@@ -52,18 +52,17 @@ template <bool INV> __device__ __forceinline__ void bfly1_q(cplx& a, cplx& b)
 
 // 16-point DFT in registers with the twiddles of its INPUTS taken along:  X_p = sum_q x_q (w w16^p)^q, w16 =
 // exp(-2 pi i / 16) (INV: conjugate).  In: v[q] = x_q.  Out: X_p sits in slot rev4(p) (the four bits of p reversed).
-// Radix 2 over q: 16 values of a polynomial, and level by level only the powers w^8, w^4, w^2 and w of the base are met,
-// times eighth and sixteenth roots: eight distinct complex twiddles (28 instructions from w) for 32 butterflies of six
+// w2 = w^2.  Radix 2 over q: 16 values of a polynomial, and level by level only the powers w^8, w^4, w^2 and w of the base are met,
+// times eighth and sixteenth roots: eight distinct complex twiddles (25 instructions from w, w2) for 32 butterflies of six
 // instructions, 220 in all, where a plain 16-point transform with fifteen twiddles in front of or behind it takes 290
 // (its chain of powers 56, its products 60).  UNIT: w = 1 (148 instructions).  HALF_IN: x_8 .. x_15 are zero (not read).
 // HALF_OUT: only X_0 .. X_7 are wanted.
 __host__ __device__ constexpr int rev4(int p) { return ((p & 1) << 3) | ((p & 2) << 1) | ((p & 4) >> 1) | ((p & 8) >> 3); }
 template <bool INV, bool UNIT, bool HALF_IN = false, bool HALF_OUT = false>
-__device__ __forceinline__ void dft16(cplx (&v)[16], cplx w)
+__device__ __forceinline__ void dft16(cplx (&v)[16], cplx w, cplx w2)
 {
     constexpr float C1 = 0.92387953251128674f, S1 = 0.38268343236508977f, R2 = 0.70710678118654752f;
     constexpr float SG = INV ? 1.f : -1.f;
-    const cplx w2 = UNIT ? mk(1.f, 0.f) : mk(fmaf(w.x, w.x, -w.y * w.y), 2.f * w.x * w.y);
     if (HALF_IN) {
 #pragma unroll
         for (int q = 0; q < 8; ++q) v[q + 8] = v[q];
@@ -115,15 +114,25 @@ template <int M>
 struct ConvLds {
     // complex slots; 16 more than the transform needs, so that two real sequences with 32 steps of margin each fit
     static constexpr int DATA = conv_pad(M) + 16;
-    static constexpr int BYTES = DATA * 8 + 2 * 128 * 8;     // + two twiddle tables of 128
+    // + twiddles: up to M = 4096 the powers W^e that the passes ask for (e < M / 16), each with its square, which leaves
+    // room for four waves per SIMD; beyond that two tables of 128 to multiply up from
+    static constexpr int POWERS = M / 16;
+    static constexpr int BYTES = DATA * 8 + (M <= 4096 ? POWERS * 16 : 2 * 128 * 8);
 };
 
-// exp(-2 pi i e / M) for 0 <= e < M from two tables of 128: lo[x] = W^x, hi[y] = W^(128 y).
-template <int M>
-__device__ __forceinline__ cplx twiddle(const cplx* lo, const cplx* hi, int e)
+// w = exp(-2 pi i e / M) (INV: its conjugate) and w2 = w^2.
+template <int M, bool INV>
+__device__ __forceinline__ void twiddle(const cplx* lo, const cplx* hi, int e, cplx& w, cplx& w2)
 {
-    if (M <= 128) return lo[e];
-    return cmul(lo[e & 127], hi[e >> 7]);
+    if constexpr (M <= 4096) {
+        const float4 t = reinterpret_cast<const float4*>(lo)[e];
+        w = mk(t.x, INV ? -t.y : t.y);
+        w2 = mk(t.z, INV ? -t.w : t.w);
+    } else {
+        w = cmul(lo[e & 127], hi[e >> 7]);
+        if (INV) w = conj(w);
+        w2 = mk(fmaf(w.x, w.x, -w.y * w.y), 2.f * w.x * w.y);
+    }
 }
 
 // Storage position of spectrum bin k (0 <= k < M) after the forward passes.
@@ -166,11 +175,11 @@ __device__ __forceinline__ void pass16(cplx* a, const cplx* lo, const cplx* hi, 
         const int block = g / S, j = g - block * S;
         cplx* p0 = a + (S >= 16 ? conv_pad(block * N16 + j) : 17 * g);
         cplx v[16];
-        cplx w = mk(1.f, 0.f);
-        if (!UNIT) w = INV ? conj(twiddle<M>(lo, hi, j * (M / N16))) : twiddle<M>(lo, hi, block_bin<M, N16>(block) * S);
+        cplx w = mk(1.f, 0.f), w2 = w;
+        if (!UNIT) twiddle<M, INV>(lo, hi, INV ? j * (M / N16) : block_bin<M, N16>(block) * S, w, w2);
 #pragma unroll
         for (int q = 0; q < (HALF && !INV ? 8 : 16); ++q) v[q] = p0[q * STEP];
-        dft16<INV, UNIT, HALF && !INV, HALF && INV>(v, w);
+        dft16<INV, UNIT, HALF && !INV, HALF && INV>(v, w, w2);
 #pragma unroll
         for (int p = 0; p < (HALF && INV ? 8 : 16); ++p) p0[p * STEP] = v[rev4(p)];
     }
@@ -208,7 +217,7 @@ __device__ __forceinline__ void fft_forward(const cplx (&z)[M / T / 2], cplx* a,
             cplx v[16];
 #pragma unroll
             for (int q = 0; q < 8; ++q) v[q] = z[q];
-            dft16<false, true, true>(v, mk(1.f, 0.f));
+            dft16<false, true, true>(v, mk(1.f, 0.f), mk(1.f, 0.f));
             cplx* p0 = a + conv_pad(tid);
 #pragma unroll
             for (int p = 0; p < 16; ++p) p0[p * STEP] = v[rev4(p)];
@@ -239,7 +248,16 @@ __device__ __forceinline__ void fft_inverse(cplx* a, cplx (&y)[M / T / 2], const
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const cplx* p0 = a + conv_pad(tid + T * j);
-                const cplx t1 = conj(twiddle<M>(lo, hi, tid + T * j)), t2 = cmul(t1, t1), t3 = cmul(t2, t1);
+                cplx t1, t2;
+                if constexpr (M == 1024) {      // W^tid times sixteenth roots
+                    constexpr float C1 = 0.92387953251128674f, S1 = 0.38268343236508977f, R2 = 0.70710678118654752f;
+                    twiddle<M, true>(lo, hi, tid, t1, t2);
+                    t1 = j == 0 ? t1 : cmul(t1, j == 1 ? mk(C1, S1) : j == 2 ? mk(R2, R2) : mk(S1, C1));
+                    t2 = j == 0 ? t2 : j == 2 ? mul_pos_i(t2) : cmul(t2, j == 1 ? mk(R2, R2) : mk(-R2, R2));
+                } else {
+                    twiddle<M, true>(lo, hi, tid + T * j, t1, t2);
+                }
+                const cplx t3 = cmul(t2, t1);
                 cplx v0 = p0[0], v1 = cmul(p0[sp], t1), v2 = p0[2 * sp], v3 = p0[3 * sp];
                 bfly(v0, v2, t2.x, t2.y);
                 bfly(v1, v3, t3.x, t3.y);
@@ -252,53 +270,85 @@ __device__ __forceinline__ void fft_inverse(cplx* a, cplx (&y)[M / T / 2], const
             cplx v[16];
 #pragma unroll
             for (int q = 0; q < 16; ++q) v[q] = p0[q * STEP];
-            dft16<true, false, false, true>(v, conj(twiddle<M>(lo, hi, tid)));
+            cplx w, w2;
+            twiddle<M, true>(lo, hi, tid, w, w2);
+            dft16<true, false, false, true>(v, w, w2);
 #pragma unroll
             for (int p = 0; p < 8; ++p) y[p] = v[rev4(p)];
         }
     }
 }
 
+// A row for buffer loads and stores: what lies at or beyond its end reads as zero and is not written, which takes the
+// branches around single accesses out of the kernels.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void* row, int bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(row), 0, bytes, 0x00020000);     // (untyped, raw offsets)
+}
+
 // raw_t: the pair (x[t], x[t+1]) as it sits in memory, so that a sequence fetched ahead costs as few registers as it
-// costs bytes; raw_pair() reads an aligned pair, raw_scalars() builds one from single reads (odd row lengths, the
-// second element optional), unpack() converts.
+// costs bytes; load_pair() reads an aligned pair, load_single() builds one from single reads (odd row lengths), `off` and
+// `imm` being byte offsets of x[t] in the row; unpack() converts.
 template <typename T> struct IoPair;
 template <> struct IoPair<float> {
     typedef float2 raw_t;
-    static __device__ __forceinline__ raw_t raw_zero() { return make_float2(0.f, 0.f); }
-    static __device__ __forceinline__ raw_t raw_pair(const float* p) { return *reinterpret_cast<const float2*>(p); }
-    static __device__ __forceinline__ raw_t raw_scalars(const float* p, bool second) { return make_float2(p[0], second ? p[1] : 0.f); }
+    static __device__ __forceinline__ raw_t load_pair(__amdgpu_buffer_rsrc_t r, int off)
+    {
+        return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0));
+    }
+    static __device__ __forceinline__ raw_t load_single(__amdgpu_buffer_rsrc_t r, int off)
+    {
+        return make_float2(__builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0)),
+                           __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(r, off + 4, 0, 0)));
+    }
     static __device__ __forceinline__ void unpack(raw_t r, float& a, float& b) { a = r.x; b = r.y; }
-    static __device__ __forceinline__ void load2(const float* p, float& a, float& b) { const float2 v = *reinterpret_cast<const float2*>(p); a = v.x; b = v.y; }
-    static __device__ __forceinline__ void store2(float* p, float a, float b) { *reinterpret_cast<float2*>(p) = make_float2(a, b); }
+    static __device__ __forceinline__ void store_pair(__amdgpu_buffer_rsrc_t r, int off, float a, float b)
+    {
+        typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
+        u32x2 v;
+        v[0] = __builtin_bit_cast(unsigned, a);
+        v[1] = __builtin_bit_cast(unsigned, b);
+        __builtin_amdgcn_raw_buffer_store_b64(v, r, off, 0, 0);
+    }
+    static __device__ __forceinline__ void store_single(__amdgpu_buffer_rsrc_t r, int off, float a, float b)
+    {
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, a), r, off, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, b), r, off + 4, 0, 0);
+    }
 };
 template <> struct IoPair<bf16> {
     typedef unsigned raw_t;
-    static __device__ __forceinline__ raw_t raw_zero() { return 0u; }
-    static __device__ __forceinline__ raw_t raw_pair(const bf16* p) { return *reinterpret_cast<const unsigned*>(p); }
-    static __device__ __forceinline__ raw_t raw_scalars(const bf16* p, bool second)
+    static __device__ __forceinline__ raw_t load_pair(__amdgpu_buffer_rsrc_t r, int off)
     {
-        const unsigned short* q = reinterpret_cast<const unsigned short*>(p);
-        return (unsigned)q[0] | (second ? (unsigned)q[1] << 16 : 0u);
+        return __builtin_amdgcn_raw_buffer_load_b32(r, off, 0, 0);
+    }
+    static __device__ __forceinline__ raw_t load_single(__amdgpu_buffer_rsrc_t r, int off)
+    {
+        return (unsigned)__builtin_amdgcn_raw_buffer_load_b16(r, off, 0, 0) |
+               (unsigned)__builtin_amdgcn_raw_buffer_load_b16(r, off + 2, 0, 0) << 16;
     }
     static __device__ __forceinline__ void unpack(raw_t u, float& a, float& b)
     {
         a = __builtin_bit_cast(float, u << 16);
         b = __builtin_bit_cast(float, u & 0xffff0000u);
     }
-    static __device__ __forceinline__ void load2(const bf16* p, float& a, float& b)
-    {
-        const unsigned u = *reinterpret_cast<const unsigned*>(p);
-        a = __builtin_bit_cast(float, u << 16);
-        b = __builtin_bit_cast(float, u & 0xffff0000u);
-    }
-    static __device__ __forceinline__ void store2(bf16* p, float a, float b)
+    static __device__ __forceinline__ unsigned pack(float a, float b)
     {
         typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
         bf16x2 v;
         v[0] = (bf16)a;
         v[1] = (bf16)b;
-        *reinterpret_cast<bf16x2*>(p) = v;
+        return __builtin_bit_cast(unsigned, v);
+    }
+    static __device__ __forceinline__ void store_pair(__amdgpu_buffer_rsrc_t r, int off, float a, float b)
+    {
+        __builtin_amdgcn_raw_buffer_store_b32(pack(a, b), r, off, 0, 0);
+    }
+    static __device__ __forceinline__ void store_single(__amdgpu_buffer_rsrc_t r, int off, float a, float b)
+    {
+        const unsigned v = pack(a, b);
+        __builtin_amdgcn_raw_buffer_store_b16((unsigned short)v, r, off, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b16((unsigned short)(v >> 16), r, off + 2, 0, 0);
     }
 };
 
@@ -335,12 +385,20 @@ __device__ __forceinline__ void store8(bf16* p, const float (&v)[8])
 template <int M, int T>
 __device__ __forceinline__ void build_tables(cplx* lo, cplx* hi, int tid)
 {
-    for (int t = tid; t < 128; t += T) {
-        float s, c;
-        sincospif(-2.0f * (float)t / (float)M, &s, &c);
-        lo[t] = mk(c, s);
-        sincospif(-2.0f * (float)(t * 128 % M) / (float)M, &s, &c);
-        hi[t] = mk(c, s);
+    float s, c, s2, c2;
+    if constexpr (M <= 4096) {
+        for (int e = tid; e < ConvLds<M>::POWERS; e += T) {
+            sincospif(-2.0f * (float)e / (float)M, &s, &c);
+            sincospif(-4.0f * (float)e / (float)M, &s2, &c2);
+            reinterpret_cast<float4*>(lo)[e] = make_float4(c, s, c2, s2);
+        }
+    } else {
+        for (int t = tid; t < 128; t += T) {
+            sincospif(-2.0f * (float)t / (float)M, &s, &c);
+            lo[t] = mk(c, s);
+            sincospif(-2.0f * (float)(t * 128 % M) / (float)M, &s, &c);
+            hi[t] = mk(c, s);
+        }
     }
 }
 
@@ -413,6 +471,7 @@ struct PairTwiddle {
 // The product with a kernel's spectrum K, packed again, is linear in (A, B).  With P = (K[k] + conj K[M-k])/2, D =
 // (K[k] - conj K[M-k])/2 and w = c - i s it comes to
 //     A' = P A + D r,  r = -s A + i c B;      B' = P B + D q,  q = s B - i c A
+// (The entries (P, D) are stored divided by M, which closes the way back.)
 // -- 24 multiply-adds per pair; untangling to V, multiplying and packing again took over 50.  (P, D) of a kernel are E and
 // w O of its own packed transform.  Correlation: conj P, conj D.
 // Gradient of the kernel, sums over sequences of G conj(V) for two packed spectra (A, B) and (a, b), r and q of (a, b):
@@ -476,11 +535,13 @@ __device__ __forceinline__ void pair_pack(float4 S, cplx w, bool self, cplx& A, 
 }
 
 // The kernel's entry from its own packed transform.
+template <int M>
 __device__ __forceinline__ float4 pair_kernel(cplx A, cplx B, cplx w, bool self)
 {
-    if (self) return make_float4(A.x, A.y, B.x, B.y);
-    const cplx D = cmul(w, mul_neg_i(mk(0.5f * (A.x - B.x), 0.5f * (A.y - B.y))));
-    return make_float4(0.5f * (A.x + B.x), 0.5f * (A.y + B.y), D.x, D.y);
+    constexpr float S = 1.f / (float)M, H = 0.5f * S;
+    if (self) return make_float4(S * A.x, S * A.y, S * B.x, S * B.y);
+    const cplx D = cmul(w, mul_neg_i(mk(H * (A.x - B.x), H * (A.y - B.y))));
+    return make_float4(H * (A.x + B.x), H * (A.y + B.y), D.x, D.y);
 }
 
 // One sequence of L <= M steps in registers: the pairs (x[2n], x[2n+1]) for n = tid + T i.  Only n < M/2 can lie
@@ -495,11 +556,13 @@ struct SeqRegs {
     __device__ __forceinline__ void load(const IO* __restrict__ x, int L, int tid) { load(x, L, tid, (L & 1) == 0); }
     __device__ __forceinline__ void load(const IO* __restrict__ x, int L, int tid, bool vec_ok)
     {
+        const __amdgpu_buffer_rsrc_t row = row_rsrc(x, L * (int)sizeof(IO));
+        if (vec_ok && (L & 1) == 0) {
 #pragma unroll
-        for (int i = 0; i < HELD; ++i) {
-            const int t = 2 * (tid + T * i);
-            r[i] = IoPair<IO>::raw_zero();
-            if (t < L) r[i] = vec_ok ? IoPair<IO>::raw_pair(x + t) : IoPair<IO>::raw_scalars(x + t, t + 1 < L);
+            for (int i = 0; i < HELD; ++i) r[i] = IoPair<IO>::load_pair(row, 2 * (tid + T * i) * (int)sizeof(IO));
+        } else {
+#pragma unroll
+            for (int i = 0; i < HELD; ++i) r[i] = IoPair<IO>::load_single(row, 2 * (tid + T * i) * (int)sizeof(IO));
         }
     }
 };
@@ -573,14 +636,13 @@ template <int M, int T, typename OUT>
 __device__ __forceinline__ void store_steps(const cplx (&v)[M / T / 2], OUT* __restrict__ y, int L, bool vec_ok, float scale,
                                             int tid)
 {
+    const __amdgpu_buffer_rsrc_t row = row_rsrc(y, L * (int)sizeof(OUT));
+    const bool pairs = vec_ok && (L & 1) == 0;
 #pragma unroll
     for (int i = 0; i < M / T / 2; ++i) {
-        const int t = 2 * (tid + T * i);
-        const float v0 = v[i].x * scale, v1 = v[i].y * scale;
-        if (t < L) {
-            if (vec_ok) IoPair<OUT>::store2(y + t, v0, v1);
-            else { y[t] = (OUT)v0; if (t + 1 < L) y[t + 1] = (OUT)v1; }
-        }
+        const int off = 2 * (tid + T * i) * (int)sizeof(OUT);
+        if (pairs) IoPair<OUT>::store_pair(row, off, v[i].x * scale, v[i].y * scale);
+        else IoPair<OUT>::store_single(row, off, v[i].x * scale, v[i].y * scale);
     }
 }
 
@@ -630,7 +692,7 @@ __global__ __launch_bounds__(conv_threads(M)) void longconv_spectrum_kernel(cons
     if constexpr (MX) {
         float n1 = 0.f;
         for (int i = 0; i < T / 64; ++i) n1 += red[i];
-        inv = n1 > 0.f ? 0.25f / n1 : 0.f;
+        inv = n1 > 0.f ? 0.25f / n1 * (float)M : 0.f;           // (the entries are divided by M)
         if (tid == 0) scale[c] = n1 > 0.f ? 4.f * n1 : 0.f;
     }
     typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
@@ -647,7 +709,7 @@ __global__ __launch_bounds__(conv_threads(M)) void longconv_spectrum_kernel(cons
     cplx w = pw.first;
 #pragma unroll
     for (int i = 0; i < NP; ++i) {
-        const float4 e = pair_kernel(a[pos.first(i)], conj(a[pos.second(i)]), w, i == 0 && tid == 0);
+        const float4 e = pair_kernel<M>(a[pos.first(i)], conj(a[pos.second(i)]), w, i == 0 && tid == 0);
         out[tid + T * i] = e;
         if constexpr (MX) {
             if (i == 0 && tid == 0) {
@@ -745,7 +807,7 @@ void shortlong_conv_kernel(const IN* __restrict__ X,
         __syncthreads();
         tp = fresh(tid);
         fft_inverse<M, T>(a, z, lo, hi, tp);
-        store_steps<M, T, OUT>(z, Y + bc * (long)L, L, (L & 1) == 0, 1.0f / (float)M, tp);
+        store_steps<M, T, OUT>(z, Y + bc * (long)L, L, (L & 1) == 0, 1.0f, tp);
     }
 }
 
@@ -857,8 +919,8 @@ void longconv_bwd_kernel(const IO* __restrict__ X,
                 const int t = 2 * (tp + T * i);
                 const float s0 = __builtin_amdgcn_rcpf(1.f + __expf(-u[i].x)), s1 = __builtin_amdgcn_rcpf(1.f + __expf(-u[i].y));
                 const bool two = t + 1 < L;
-                z[i].x = t < L ? z[i].x * scale * s0 * (1.f + u[i].x * (1.f - s0)) : 0.f;
-                z[i].y = two ? z[i].y * scale * s1 * (1.f + u[i].y * (1.f - s1)) : 0.f;
+                z[i].x = t < L ? z[i].x * s0 * (1.f + u[i].x * (1.f - s0)) : 0.f;
+                z[i].y = two ? z[i].y * s1 * (1.f + u[i].y * (1.f - s1)) : 0.f;
                 *reinterpret_cast<float2*>(su + t) = make_float2(z[i].x, z[i].y);
                 u[i].x = t < L ? u[i].x * s0 : 0.f;
                 u[i].y = two ? u[i].y * s1 : 0.f;
@@ -918,7 +980,7 @@ constexpr int U = HELD < 4 ? HELD : 4;       // steps read together
 #pragma unroll
             for (int i = 0; i < HELD; ++i) z[i] = u[i];
         } else {
-            store_steps<M, T, DVT>(z, dV + row, L, vec_ok, scale, tp);
+            store_steps<M, T, DVT>(z, dV + row, L, vec_ok, 1.0f, tp);
             if (wc != nullptr) __syncthreads();      // a[] has been read out
             // ---- v = silu(K_s x) (x itself without a short stage)
             stage_input<M, T, IO>(xr, wc, m, L, a, tp, z);
@@ -1054,11 +1116,6 @@ template <typename IO> struct Raw8 {
 __device__ __forceinline__ float from_next_lane(float v)        // lane i: the value of lane i + 1 (lane 63: anything)
 {
     return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x130, 0xf, 0xf, false));
-}
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void* row, int bytes)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(row), 0, bytes, 0x00020000);     // (untyped, raw offsets)
 }
 
 // VEC: L is a multiple of 8 (every row starts on a 16-byte boundary).
@@ -1335,7 +1392,7 @@ __global__ __launch_bounds__(kBlkT) void longconv_spectrum_blocked_kernel(const 
         cplx w = pw.first;
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
-            const float4 v = pair_kernel(a[pos.first(i)], conj(a[pos.second(i)]), w, i == 0 && tid == 0);
+            const float4 v = pair_kernel<M>(a[pos.first(i)], conj(a[pos.second(i)]), w, i == 0 && tid == 0);
             sum[i].x += sg * v.x; sum[i].y += sg * v.y; sum[i].z += sg * v.z; sum[i].w += sg * v.w;
             w = cmul(w, pw.step);
         }
@@ -1363,7 +1420,6 @@ __global__ __launch_bounds__(kBlkT) void longconv_blocked_kernel(const IN* __res
     cplx* hi = lo + 128;
     const int tid = threadIdx.x;
     const bool row_vec = (L & 1) == 0;
-    const float scale = 1.0f / (float)M;
     build_tables<M, T>(lo, hi, tid);
     const PairPos<M, T> pos(tid);
     const PairTwiddle<M, T> pw(tid);
@@ -1415,7 +1471,7 @@ __global__ __launch_bounds__(kBlkT) void longconv_blocked_kernel(const IN* __res
         __syncthreads();
         const int tp = fresh(tid);
         fft_inverse<M, T>(a, z, lo, hi, tp);
-        store_steps<M, T, OUT>(z, Y + bc * (long)L + (long)blk * M, min(M, L - blk * M), row_vec, scale, tp);
+        store_steps<M, T, OUT>(z, Y + bc * (long)L + (long)blk * M, min(M, L - blk * M), row_vec, 1.0f, tp);
     }
 }
 
