@@ -116,7 +116,7 @@ struct ConvLds {
     static constexpr int DATA = conv_pad(M) + 16;
     // + twiddles: up to M = 4096 the powers W^e that the passes ask for (e < M / 16), each with its square, which leaves
     // room for four waves per SIMD; beyond that two tables of 128 to multiply up from
-    static constexpr int POWERS = M / 16;
+    static constexpr int POWERS = M / 16 + M / 256;          // one of padding per 16: the passes walk it by 1 or by 16
     static constexpr int BYTES = DATA * 8 + (M <= 4096 ? POWERS * 16 : 2 * 128 * 8);
 };
 
@@ -125,7 +125,7 @@ template <int M, bool INV>
 __device__ __forceinline__ void twiddle(const cplx* lo, const cplx* hi, int e, cplx& w, cplx& w2)
 {
     if constexpr (M <= 4096) {
-        const float4 t = reinterpret_cast<const float4*>(lo)[e];
+        const float4 t = reinterpret_cast<const float4*>(lo)[conv_pad(e)];
         w = mk(t.x, INV ? -t.y : t.y);
         w2 = mk(t.z, INV ? -t.w : t.w);
     } else {
@@ -387,10 +387,10 @@ __device__ __forceinline__ void build_tables(cplx* lo, cplx* hi, int tid)
 {
     float s, c, s2, c2;
     if constexpr (M <= 4096) {
-        for (int e = tid; e < ConvLds<M>::POWERS; e += T) {
+        for (int e = tid; e < M / 16; e += T) {
             sincospif(-2.0f * (float)e / (float)M, &s, &c);
             sincospif(-4.0f * (float)e / (float)M, &s2, &c2);
-            reinterpret_cast<float4*>(lo)[e] = make_float4(c, s, c2, s2);
+            reinterpret_cast<float4*>(lo)[conv_pad(e)] = make_float4(c, s, c2, s2);
         }
     } else {
         for (int t = tid; t < 128; t += T) {
@@ -451,18 +451,19 @@ struct PairPos {
     }
 };
 
-// W_2M^k = exp(-i pi k / M) for the bins a thread meets when it walks its pairs: k = k(0) + (T/64) i, two sincospi per
-// thread and one rotation per pair.
+// W_2M^k = exp(-i pi k / M) for the bins a thread meets when it walks its pairs: k = k(0) + (T/64) i, one sincospi per
+// thread and one rotation per pair, by exp(-i pi / 1024) (M = 256: exp(-i pi / 256)).
 template <int M, int T>
 struct PairTwiddle {
-    cplx first, step;
+    static_assert(M / T == 16 || (M == 256 && T == 64), "the rotation below");
+    cplx first;
+    static constexpr cplx step = M == 256 ? cplx{0.99992470183914454f, -0.012271538285719925f}
+                                          : cplx{0.99999529380957617f, -0.0030679567629659763f};
     __device__ __forceinline__ PairTwiddle(int tid)
     {
         float s, c;
         sincospif(-(float)pair_bin<M>(tid) / (float)M, &s, &c);
         first = mk(c, s);
-        sincospif(-(float)(T / 64) / (float)M, &s, &c);
-        step = mk(c, s);
     }
 };
 
@@ -646,6 +647,14 @@ __device__ __forceinline__ void store_steps(const cplx (&v)[M / T / 2], OUT* __r
     }
 }
 
+// Sum over the four lanes of a quad, in all of them.
+__device__ __forceinline__ float quad_sum(float v)
+{
+    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xb1, 0xf, 0xf, true));   // [1,0,3,2]
+    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4e, 0xf, 0xf, true));   // [2,3,0,1]
+    return v;
+}
+
 // What depends on the thread but not on the sequence (LDS addresses, bin positions, twiddles) is recomputed per sequence
 // behind an opaque copy of the thread index: hoisted out of the loop over sequences it would fill the register file.
 // Every stage takes a fresh copy, so that values shared between stages do not stay live in between.
@@ -721,7 +730,7 @@ __global__ __launch_bounds__(conv_threads(M)) void longconv_spectrum_kernel(cons
                 h2[i] = half2(e.x - e.z, e.w - e.y);
             }
         }
-        w = cmul(w, pw.step);
+        w = cmul(w, PairTwiddle<M, T>::step);
     }
     if constexpr (MX) {
         // (padded so that neither the writers, 128 bins from lane to lane, nor the readers, 32, share banks)
@@ -752,9 +761,9 @@ __global__ __launch_bounds__(conv_threads(M)) void longconv_spectrum_kernel(cons
     }
 }
 
-// Bound by vector instruction issue: 1881 instructions per wave and sequence of 4096 steps (2900 before the pairs became
-// linear in the packed bins, their places constant offsets, and the outer passes stayed in registers), issuing 92 % of the
-// time: 512 channels x 32 sequences, bf16, 320 -> 255 us.
+// Bound by vector instruction issue: 1770 instructions per wave and sequence of 4096 steps (2900 before the pairs became
+// linear in the packed bins, their places constant offsets, the outer passes stayed in registers and the rows' ends were
+// left to buffer loads and stores), issuing 95 % of the time: 512 channels x 32 sequences, bf16, 320 -> 242 us.
 // Workgroup g takes the sequences (b, c) = g, g + gridDim.x, ... of the B d in turn (w_short == nullptr: no short
 // kernel and no activation, the plain long convolution).  The launch holds no more workgroups than are resident
 // at once, so that the tables are built once per workgroup, a sequence's input is fetched while the inverse transform
@@ -801,7 +810,7 @@ void shortlong_conv_kernel(const IN* __restrict__ X,
             pair_mul<false>(A, B, w, kq[i], i == 0 && tid == 0);
             p1 = A;
             p2 = conj(B);
-            w = cmul(w, pw.step);
+            w = cmul(w, PairTwiddle<M, T>::step);
         }
         if (bc + gridDim.x < total) xr.load(X + (bc + gridDim.x) * (long)L, L, tp);     // the next sequence, in flight
         __syncthreads();
@@ -826,12 +835,13 @@ void shortlong_conv_kernel(const IN* __restrict__ X,
 // dU = dV silu'(u) meets its neighbours through LDS: dX out (dV is DVT = IO dX here), the taps' sums into `part`
 // ([d][grid.y][kShortMaxTaps]).  As a kernel of its own that stage reads x again, and dV, 4 bytes a step written here and
 // read there, and works u out once more: 512 channels x 32 sequences of 4096 steps, bf16, the two kernels 527 + 150 us,
-// in one 570.  Two workgroups of 212 registers per compute unit; made to fit three, with 50 values spilled, it takes 760
-// (and 690 with V first and u and the taps' sums out of the registers).  Vector instructions issue 63 % of the time.
+// in one 475.  bf16 I/O asks for three workgroups per compute unit (168 registers, 31 values spilled; training step 655 us
+// against 707 with two and nothing spilled), fp32 I/O, which holds twice the fetched words, for two (234 against 262 us at
+// 512 x 8 x 4000).
 constexpr int kFuseTaps = 16, kShortMaxTaps = 32;
 
 template <int M, typename IO, typename DVT, bool SPLIT, bool SHORT>
-__global__ __launch_bounds__(conv_threads(M)) __attribute__((amdgpu_waves_per_eu(M == 1024 || M == 4096 ? 2 : 4)))
+__global__ __launch_bounds__(conv_threads(M)) __attribute__((amdgpu_waves_per_eu(M == 256 || M == 16384 ? 4 : sizeof(IO) == 2 ? 3 : 2)))
 void longconv_bwd_kernel(const IO* __restrict__ X,
                                                                       const float* __restrict__ w_short, int m,
                                                                       const float4* __restrict__ Kf,
@@ -860,14 +870,14 @@ void longconv_bwd_kernel(const IO* __restrict__ X,
     const float scale = 1.0f / (float)M;
     float4 sums[ACC_MEM ? 1 : NP];
     cplx GA[NP], GB[NP], z[HELD];
-    float tap[SHORT ? kFuseTaps : 1];
+    // the taps' sums: one slot per tap and four lanes, so that they take no registers
+    __shared__ float taps[SHORT ? (kFuseTaps + 1) * (T / 4) : 1];
     if constexpr (!ACC_MEM) {
 #pragma unroll
         for (int i = 0; i < NP; ++i) sums[i] = make_float4(0.f, 0.f, 0.f, 0.f);
     }
     if constexpr (SHORT) {
-#pragma unroll
-        for (int j = 0; j < kFuseTaps; ++j) tap[j] = 0.f;
+        for (int x = tid; x < (kFuseTaps + 1) * (T / 4); x += T) taps[x] = 0.f;
     }
 
     // Inputs are fetched one stage ahead, into registers: dZ of the next sequence while v is transformed, x while the
@@ -897,7 +907,7 @@ void longconv_bwd_kernel(const IO* __restrict__ X,
                 pair_mul<true>(A, B, w, kq[i], i == 0 && tid == 0);
                 a[pos.first(i)] = A;
                 a[pos.second(i)] = conj(B);
-                w = cmul(w, pw.step);
+                w = cmul(w, PairTwiddle<M, T>::step);
                 __builtin_amdgcn_sched_barrier(0);   // one pair at a time: the unrolled pairs must not pile up in registers
             }
         }
@@ -930,50 +940,52 @@ void longconv_bwd_kernel(const IO* __restrict__ X,
             cplx dx[HELD];
 #pragma unroll
             for (int i = 0; i < HELD; ++i) dx[i] = mk(0.f, 0.f);
+            for (int p = 0; 2 * p <= m; ++p) {
+                const bool ev = 2 * p < m, above = 2 * p + 1 < m;
+                const float w2p = ev ? wc[2 * p] : 0.f, w2pm1 = p > 0 ? wc[2 * p - 1] : 0.f;
+                const float w2pp1 = above ? wc[2 * p + 1] : 0.f;
+                float ta = 0.f, tb = 0.f, tc = 0.f;          // taps 2p - 1, 2p, 2p + 1
+                constexpr int U = HELD < 4 ? HELD : 4;       // steps read together
 #pragma unroll
-            for (int p = 0; 2 * p <= kFuseTaps; ++p) {
-                if (2 * p <= m) {
-                    const bool ev = 2 * p < m, above = 2 * p + 1 < m;
-                    const float w2p = ev ? wc[2 * p] : 0.f, w2pm1 = p > 0 ? wc[p > 0 ? 2 * p - 1 : 0] : 0.f;
-                    const float w2pp1 = above ? wc[2 * p + 1] : 0.f;
-constexpr int U = HELD < 4 ? HELD : 4;       // steps read together
+                for (int i0 = 0; i0 < HELD; i0 += U) {
+                    float2 dv[U], xv[U];
 #pragma unroll
-                    for (int i0 = 0; i0 < HELD; i0 += U) {
-                        float2 dv[U], xv[U];
-#pragma unroll
-                        for (int u = 0; u < U; ++u) {
-                            const int t = 2 * (tp + T * (i0 + u));
-                            dv[u] = *reinterpret_cast<const float2*>(su + t + 2 * p);
-                            xv[u] = *reinterpret_cast<const float2*>(sx + kHist + t - 2 * p);
-                        }
-                        if (p > 0) {
-#pragma unroll
-                            for (int u = 0; u < U; ++u) {
-                                const int i = i0 + u;
-                                dx[i].y = fmaf(w2pm1, dv[u].x, dx[i].y);
-                                tap[p > 0 ? 2 * p - 1 : 0] = fmaf(z[i].x, xv[u].y, tap[p > 0 ? 2 * p - 1 : 0]);
-                            }
-                        }
-                        if (ev && 2 * p < kFuseTaps) {
-#pragma unroll
-                            for (int u = 0; u < U; ++u) {
-                                const int i = i0 + u;
-                                float& tp2 = tap[2 * p < kFuseTaps ? 2 * p : 0];
-                                dx[i] = mk(fmaf(w2p, dv[u].x, dx[i].x), fmaf(w2p, dv[u].y, dx[i].y));
-                                tp2 = fmaf(z[i].x, xv[u].x, fmaf(z[i].y, xv[u].y, tp2));
-                            }
-                        }
-                        if (above && 2 * p + 1 < kFuseTaps) {
-#pragma unroll
-                            for (int u = 0; u < U; ++u) {
-                                const int i = i0 + u;
-                                float& tp1 = tap[2 * p + 1 < kFuseTaps ? 2 * p + 1 : 0];
-                                dx[i].x = fmaf(w2pp1, dv[u].y, dx[i].x);
-                                tp1 = fmaf(z[i].y, xv[u].x, tp1);
-                            }
-                        }
-                        __builtin_amdgcn_sched_barrier(0);
+                    for (int q = 0; q < U; ++q) {
+                        const int t = 2 * (tp + T * (i0 + q));
+                        dv[q] = *reinterpret_cast<const float2*>(su + t + 2 * p);
+                        xv[q] = *reinterpret_cast<const float2*>(sx + kHist + t - 2 * p);
                     }
+                    if (p > 0) {
+#pragma unroll
+                        for (int q = 0; q < U; ++q) {
+                            dx[i0 + q].y = fmaf(w2pm1, dv[q].x, dx[i0 + q].y);
+                            ta = fmaf(z[i0 + q].x, xv[q].y, ta);
+                        }
+                    }
+                    if (ev) {
+#pragma unroll
+                        for (int q = 0; q < U; ++q) {
+                            cplx& o = dx[i0 + q];
+                            o = mk(fmaf(w2p, dv[q].x, o.x), fmaf(w2p, dv[q].y, o.y));
+                            tb = fmaf(z[i0 + q].x, xv[q].x, fmaf(z[i0 + q].y, xv[q].y, tb));
+                        }
+                    }
+                    if (above) {
+#pragma unroll
+                        for (int q = 0; q < U; ++q) {
+                            dx[i0 + q].x = fmaf(w2pp1, dv[q].y, dx[i0 + q].x);
+                            tc = fmaf(z[i0 + q].y, xv[q].x, tc);
+                        }
+                    }
+                }
+                ta = quad_sum(ta);
+                tb = quad_sum(tb);
+                tc = quad_sum(tc);
+                if ((tp & 3) == 0) {
+                    float* o = taps + tp / 4;
+                    if (p > 0) o[(2 * p - 1) * (T / 4)] += ta;
+                    o[2 * p * (T / 4)] += tb;
+                    if (above) o[(2 * p + 1) * (T / 4)] += tc;
                 }
             }
             store_steps<M, T, DVT>(dx, dV + row, L, vec_ok, 1.0f, tp);
@@ -1011,7 +1023,7 @@ constexpr int U = HELD < 4 ? HELD : 4;       // steps read together
                     } else {
                         pair_acc(sums[i], GA[i], GB[i], A[u], Bc[u], w, self);
                     }
-                    w = cmul(w, pw.step);
+                    w = cmul(w, PairTwiddle<M, T>::step);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -1019,22 +1031,14 @@ constexpr int U = HELD < 4 ? HELD : 4;       // steps read together
         __syncthreads();
     }
     if constexpr (SHORT) {
-        // this workgroup's tap sums: wave reduction, then across the waves
-        float* red = reinterpret_cast<float*>(a);
-#pragma unroll
-        for (int j = 0; j < kFuseTaps; ++j) {
-            float v = tap[j];
+        // this workgroup's tap sums (a barrier has passed since the last was added)
+        for (int j = tid / 64; j < m; j += T / 64) {
+            float v = 0.f;
+            for (int x = tid & 63; x < T / 4; x += 64) v += taps[j * (T / 4) + x];
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-            if ((tid & 63) == 0) red[j * (T / 64) + (tid >> 6)] = v;
+            if ((tid & 63) == 0) part[((long)c * gridDim.y + blockIdx.y) * kShortMaxTaps + j] = v;
         }
-        __syncthreads();
-        if (tid < m) {
-            float v = 0.f;
-            for (int k = 0; k < T / 64; ++k) v += red[tid * (T / 64) + k];
-            part[((long)c * gridDim.y + blockIdx.y) * kShortMaxTaps + tid] = v;
-        }
-        __syncthreads();
     }
     if constexpr (SPLIT) {
         // this workgroup's share of the sums stays in its slice of the scratch array (it is there already when the
@@ -1056,7 +1060,7 @@ constexpr int U = HELD < 4 ? HELD : 4;       // steps read together
             pair_pack(t, w, i == 0 && tid == 0, A, Bc);
             a[pos.first(i)] = A;
             a[pos.second(i)] = conj(Bc);
-            w = cmul(w, pw.step);
+            w = cmul(w, PairTwiddle<M, T>::step);
         }
     }
     __syncthreads();
@@ -1394,7 +1398,7 @@ __global__ __launch_bounds__(kBlkT) void longconv_spectrum_blocked_kernel(const 
         for (int i = 0; i < NP; ++i) {
             const float4 v = pair_kernel<M>(a[pos.first(i)], conj(a[pos.second(i)]), w, i == 0 && tid == 0);
             sum[i].x += sg * v.x; sum[i].y += sg * v.y; sum[i].z += sg * v.z; sum[i].w += sg * v.w;
-            w = cmul(w, pw.step);
+            w = cmul(w, PairTwiddle<M, T>::step);
         }
     }
     float4* out = Gf + (c * nb + mb) * (long)(M / 2 + 1);
@@ -1458,7 +1462,7 @@ __global__ __launch_bounds__(kBlkT) void longconv_blocked_kernel(const IN* __res
                 pair_mul<CORR>(A, B, w, kq[i], i == 0 && tid == 0);
                 accA[i] = cadd(accA[i], A);
                 accB[i] = cadd(accB[i], B);
-                w = cmul(w, pw.step);
+                w = cmul(w, PairTwiddle<M, T>::step);
                 __builtin_amdgcn_sched_barrier(0);   // one pair at a time: the unrolled pairs must not pile up in registers
             }
         }
@@ -1531,7 +1535,7 @@ __global__ __launch_bounds__(kBlkT) void longconv_dk_blocked_kernel(const IO* __
             if (pr > 0) t = accm[tid + T * q];
             pair_acc(t, GA[q], GB[q], a[pos.first(q)], conj(a[pos.second(q)]), w, q == 0 && tid == 0);
             accm[tid + T * q] = t;
-            w = cmul(w, pw.step);
+            w = cmul(w, PairTwiddle<M, T>::step);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
@@ -1567,7 +1571,7 @@ __global__ __launch_bounds__(kBlkT) void longconv_dk_blocked_finish_kernel(const
         pair_pack(t, w, i == 0 && tid == 0, A, B);
         a[pos.first(i)] = A;
         a[pos.second(i)] = conj(B);
-        w = cmul(w, pw.step);
+        w = cmul(w, PairTwiddle<M, T>::step);
     }
     __syncthreads();
     cplx z[M / T / 2];
@@ -1692,7 +1696,7 @@ __global__ __launch_bounds__(conv_threads(M)) void longconv_dk_finish_kernel(con
         pair_pack(t, w, i == 0 && tid == 0, A, B);
         a[pos.first(i)] = A;
         a[pos.second(i)] = conj(B);
-        w = cmul(w, pw.step);
+        w = cmul(w, PairTwiddle<M, T>::step);
     }
     __syncthreads();
     cplx z[M / T / 2];
