@@ -136,13 +136,41 @@ Plan make_plan(long BH, int N, int dk, int dv, int chunk, int dtype, bool is_bwd
     return p;
 }
 
-// The fp32 backward is one launch of three forward-shaped sweeps: three workgroups per segment share the GPU, so it is
-// split like a forward over three times as many sequences, with two states per segment and sequence.  The scratch it
+// The fp32 backward is one launch of three forward-shaped sweeps: three workgroups per segment share the GPU.  Up to one
+// round of single chunks it is split like a forward over three times as many sequences; beyond, by a model of its own,
+// because the matrix instructions bound it and not the memory: a round costs its chunk steps whether the one before was
+// full or not, several rounds are no slower than one, and the pre-pass and the states are small change.  Measured, us,
+// by segments per sequence: 96 x 4096 tokens, 64 x 128: one 1286, two 1136, four 964, eight 911; 64 x 64: 602, 565, 472,
+// (five) 442; 112 x 1000, 128 x 64: 314, 291, 294.  (The forward's rule takes one from 256 workgroups on.)
+static long f32_bwd_segments(long wgs_per_seg, long n_chunks, long slots, size_t state_elems)
+{
+    long best = 1;
+    double best_cost = 1e300;
+    for (long n = 1; n <= n_chunks / 4 && n <= 4096; ++n) {
+        const long cps = (n_chunks + n - 1) / n;
+        if ((n_chunks + cps - 1) / cps != n) continue;                  // same split as a smaller n
+        const long wgs = wgs_per_seg * n;
+        double cost = (double)((wgs + slots - 1) / slots) * ((double)cps + 0.5);
+        if (n > 1) cost += 0.0006 * (double)state_elems / 4096.0 * (512.0 / (double)slots) * (double)wgs
+                         + 0.17 * (double)(n_chunks * wgs_per_seg) / (double)slots + 1.5;
+        if (cost < best_cost) { best_cost = cost; best = n; }
+    }
+    return best;
+}
+
+// Two states per segment and sequence.  The scratch it
 // insists on is what one array of states takes when the sequences are split on their own; a caller-owned buffer between
 // that and the full need gets fewer segments.
 Plan make_f32_bwd_plan(long BH, int N, int dk, int dv, int chunk, size_t ws_limit)
 {
     Plan p = make_plan(3 * BH, N, dk, dv, chunk, CHELA_DTYPE_F32, false, false);
+    const long chunks = ((long)(N > 0 ? N : 0) + chunk - 1) / chunk, slots = sweep_slots(dk, dv, chunk, CHELA_DTYPE_F32, true);
+    if (BH > 0 && chunks > 4 && 3 * BH * chunks > slots && env_int("CHELA_SEG_TOKENS", 0) <= 0) {
+        const long n = f32_bwd_segments(3 * BH, chunks, slots, p.state_elems);
+        const long cps = std::max((chunks + n - 1) / n, (chunks + 32767) / 32768);
+        p.seg_len = (int)(cps * chunk);
+        p.n_seg = (int)((chunks + cps - 1) / cps);
+    }
     const size_t least = make_plan(BH, N, dk, dv, chunk, CHELA_DTYPE_F32, true, false).ws_bytes;
     const size_t state = BH > 0 ? (size_t)BH * p.state_elems * sizeof(float) : 0;
     // (and never more than one state per sequence and 32 tokens)

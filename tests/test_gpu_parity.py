@@ -438,6 +438,22 @@ def test_f32_backward_takes_fewer_segments_in_a_smaller_scratch_buffer(dims):
     assert refused >= 1
 
 
+@pytest.mark.parametrize("shape", [(96, 1029, 64, 128), (96, 2047, 64, 64), (112, 1000, 128, 64), (90, 1025, 128, 128)])
+def test_f32_backward_split_where_one_segment_would_fill_the_gpu(shape):
+    # three workgroups per segment and 256 or more at one segment per sequence: split all the same, ragged ends included.
+    # Four heads are compared: the last token's dK is one dot product times one row, whose relative error is the
+    # rounding (about 1e-7) over how far the product cancels, and over n products the worst cancels to about 1/n.
+    BH, N, dk, dv = shape
+    w = _small("f32", N=N, B=1, H=BH, dk=dk, dv=dv, seed=300 + BH)
+    x = make_inputs(w)
+    d = _dev(x)
+    got = binding.chela_linattn_bwd(d["Q"], d["K"], d["V"], d["dO"])
+    heads = [0, 1, BH // 2, BH - 1]
+    refs = oracle.bwd_recurrent(*(to_f64_numpy(x[n][:, heads]) for n in ("Q", "K", "V", "dO")))
+    for name, g, r in zip(("dQ", "dK", "dV"), got, refs):
+        _check(name, g[:, heads], r, "f32")
+
+
 def test_two_streams_with_a_scratch_buffer_each():
     # calls that overlap in time on two streams, each enqueued while its own buffer is the one in force
     wa, wb = _small("bf16", N=5000, B=2, H=3, seed=41), _small("bf16", N=7000, B=1, H=5, seed=42)
