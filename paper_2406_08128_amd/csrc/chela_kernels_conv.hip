@@ -14,6 +14,7 @@
 // Arithmetic is fp32 on the vector ALU: with one kernel per channel there is no operand shared across channels
 // except the DFT matrix itself, and fp32 matrix instructions are no faster than the ALU on this chip.
 #include "chela_internal.h"
+#include <cfloat>
 #include <cstdlib>
 
 namespace chela {
@@ -472,7 +473,6 @@ struct PairTwiddle {
 // The product with a kernel's spectrum K, packed again, is linear in (A, B).  With P = (K[k] + conj K[M-k])/2, D =
 // (K[k] - conj K[M-k])/2 and w = c - i s it comes to
 //     A' = P A + D r,  r = -s A + i c B;      B' = P B + D q,  q = s B - i c A
-// (The entries (P, D) are stored divided by M, which closes the way back.)
 // -- 24 multiply-adds per pair; untangling to V, multiplying and packing again took over 50.  (P, D) of a kernel are E and
 // w O of its own packed transform.  Correlation: conj P, conj D.
 // Gradient of the kernel, sums over sequences of G conj(V) for two packed spectra (A, B) and (a, b), r and q of (a, b):
@@ -535,14 +535,14 @@ __device__ __forceinline__ void pair_pack(float4 S, cplx w, bool self, cplx& A, 
     B = csub(al, be);
 }
 
-// The kernel's entry from its own packed transform.
-template <int M>
+// The kernel's entry from its own packed transform.  (1/M, which closes the way back, is not in the entries but in the
+// stores behind it: a kernel of 1e-36, an ordinary fp32 number, would leave subnormal entries, with fewer bits the
+// larger the transform: 8e-6 instead of 3e-7 of error in Z at 5000 steps, 1.5e-5 at 16384.)
 __device__ __forceinline__ float4 pair_kernel(cplx A, cplx B, cplx w, bool self)
 {
-    constexpr float S = 1.f / (float)M, H = 0.5f * S;
-    if (self) return make_float4(S * A.x, S * A.y, S * B.x, S * B.y);
-    const cplx D = cmul(w, mul_neg_i(mk(H * (A.x - B.x), H * (A.y - B.y))));
-    return make_float4(H * (A.x + B.x), H * (A.y + B.y), D.x, D.y);
+    if (self) return make_float4(A.x, A.y, B.x, B.y);
+    const cplx D = cmul(w, mul_neg_i(mk(0.5f * (A.x - B.x), 0.5f * (A.y - B.y))));
+    return make_float4(0.5f * (A.x + B.x), 0.5f * (A.y + B.y), D.x, D.y);
 }
 
 // One sequence of L <= M steps in registers: the pairs (x[2n], x[2n+1]) for n = tid + T i.  Only n < M/2 can lie
@@ -664,7 +664,8 @@ __device__ __forceinline__ int fresh(int tid) { asm volatile("" : "+v"(tid)); re
 // MX (M = 16384): also the copy that the matrix-core kernels read, bin k = k1 + 32 k2 + 1024 k3 of the 32768-point
 // transform, divided by 4 |k|_1, as half-precision (re, im) words, stored where the lane that holds it after their forward
 // passes will look: word ((k1 * 4 + s) * 64 + lane) * 4 + i with lane = k2 + 32 h and k3 = 8 s + 4 h + i (the upper half of
-// the bins are the conjugates of the lower); scale[c] = 4 |k|_1.  The words change order through LDS: a kernel of its own
+// the bins are the conjugates of the lower); scale[c] = 4 |k|_1 (both zero where 0.25 / |k|_1 is no finite number, below
+// 7.4e-40).  The words change order through LDS: a kernel of its own
 // that gathered them from the pairs in memory took 77 us for 768 channels (the pairs alone 51); together: 63.
 template <int M, bool MX>
 __global__ __launch_bounds__(conv_threads(M)) void longconv_spectrum_kernel(const float* __restrict__ k,
@@ -701,8 +702,10 @@ __global__ __launch_bounds__(conv_threads(M)) void longconv_spectrum_kernel(cons
     if constexpr (MX) {
         float n1 = 0.f;
         for (int i = 0; i < T / 64; ++i) n1 += red[i];
-        inv = n1 > 0.f ? 0.25f / n1 * (float)M : 0.f;           // (the entries are divided by M)
-        if (tid == 0) scale[c] = n1 > 0.f ? 4.f * n1 : 0.f;
+        inv = n1 > 0.f ? 0.25f / n1 : 0.f;
+        const bool nothing = inv > FLT_MAX;
+        if (nothing) inv = 0.f;
+        if (tid == 0) scale[c] = n1 > 0.f && !nothing ? 4.f * n1 : 0.f;
     }
     typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
     auto half2 = [&](float re, float im) __attribute__((always_inline)) {
@@ -718,7 +721,7 @@ __global__ __launch_bounds__(conv_threads(M)) void longconv_spectrum_kernel(cons
     cplx w = pw.first;
 #pragma unroll
     for (int i = 0; i < NP; ++i) {
-        const float4 e = pair_kernel<M>(a[pos.first(i)], conj(a[pos.second(i)]), w, i == 0 && tid == 0);
+        const float4 e = pair_kernel(a[pos.first(i)], conj(a[pos.second(i)]), w, i == 0 && tid == 0);
         out[tid + T * i] = e;
         if constexpr (MX) {
             if (i == 0 && tid == 0) {
@@ -816,7 +819,7 @@ void shortlong_conv_kernel(const IN* __restrict__ X,
         __syncthreads();
         tp = fresh(tid);
         fft_inverse<M, T>(a, z, lo, hi, tp);
-        store_steps<M, T, OUT>(z, Y + bc * (long)L, L, (L & 1) == 0, 1.0f, tp);
+        store_steps<M, T, OUT>(z, Y + bc * (long)L, L, (L & 1) == 0, 1.0f / (float)M, tp);
     }
 }
 
@@ -929,8 +932,9 @@ void longconv_bwd_kernel(const IO* __restrict__ X,
                 const int t = 2 * (tp + T * i);
                 const float s0 = __builtin_amdgcn_rcpf(1.f + __expf(-u[i].x)), s1 = __builtin_amdgcn_rcpf(1.f + __expf(-u[i].y));
                 const bool two = t + 1 < L;
-                z[i].x = t < L ? z[i].x * s0 * (1.f + u[i].x * (1.f - s0)) : 0.f;
-                z[i].y = two ? z[i].y * s1 * (1.f + u[i].y * (1.f - s1)) : 0.f;
+                // (silu'(u) times 1/M, which is a power of two, at the cost of silu'(u))
+                z[i].x = t < L ? z[i].x * s0 * fmaf(u[i].x, fmaf(-scale, s0, scale), scale) : 0.f;
+                z[i].y = two ? z[i].y * s1 * fmaf(u[i].y, fmaf(-scale, s1, scale), scale) : 0.f;
                 *reinterpret_cast<float2*>(su + t) = make_float2(z[i].x, z[i].y);
                 u[i].x = t < L ? u[i].x * s0 : 0.f;
                 u[i].y = two ? u[i].y * s1 : 0.f;
@@ -992,7 +996,7 @@ void longconv_bwd_kernel(const IO* __restrict__ X,
 #pragma unroll
             for (int i = 0; i < HELD; ++i) z[i] = u[i];
         } else {
-            store_steps<M, T, DVT>(z, dV + row, L, vec_ok, 1.0f, tp);
+            store_steps<M, T, DVT>(z, dV + row, L, vec_ok, scale, tp);
             if (wc != nullptr) __syncthreads();      // a[] has been read out
             // ---- v = silu(K_s x) (x itself without a short stage)
             stage_input<M, T, IO>(xr, wc, m, L, a, tp, z);
@@ -1396,7 +1400,7 @@ __global__ __launch_bounds__(kBlkT) void longconv_spectrum_blocked_kernel(const 
         cplx w = pw.first;
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
-            const float4 v = pair_kernel<M>(a[pos.first(i)], conj(a[pos.second(i)]), w, i == 0 && tid == 0);
+            const float4 v = pair_kernel(a[pos.first(i)], conj(a[pos.second(i)]), w, i == 0 && tid == 0);
             sum[i].x += sg * v.x; sum[i].y += sg * v.y; sum[i].z += sg * v.z; sum[i].w += sg * v.w;
             w = cmul(w, PairTwiddle<M, T>::step);
         }
@@ -1475,7 +1479,7 @@ __global__ __launch_bounds__(kBlkT) void longconv_blocked_kernel(const IN* __res
         __syncthreads();
         const int tp = fresh(tid);
         fft_inverse<M, T>(a, z, lo, hi, tp);
-        store_steps<M, T, OUT>(z, Y + bc * (long)L + (long)blk * M, min(M, L - blk * M), row_vec, 1.0f, tp);
+        store_steps<M, T, OUT>(z, Y + bc * (long)L + (long)blk * M, min(M, L - blk * M), row_vec, 1.0f / (float)M, tp);
     }
 }
 

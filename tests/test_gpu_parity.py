@@ -1117,6 +1117,35 @@ def test_matrix_core_conv_gradient_scales_with_its_inputs():
     assert float(dX.float().abs().max()) == 0.0 and float(dk.abs().max()) == 0.0 and float(dw.abs().max()) == 0.0
 
 
+@pytest.mark.parametrize("case", [(1000, "bf16"), (4104, "bf16"), (16384, "bf16"), (5000, "f32"), (16384, "f32"),
+                                  (20000, "f32")])
+def test_conv_channels_whose_long_kernel_has_decayed_to_almost_nothing(case):
+    # kernels of 1e-30, 1e-37 and 0 beside an ordinary one: finite, and right to each channel's own scale (fp32 spectra
+    # must not become subnormal on the way, the half-precision ones are scaled by a number that must not overflow)
+    L, dtype = case
+    B, d, m = 2, 4, 9
+    x = make_conv_inputs(B, d, L, m, L + 29, dtype)
+    x["k_long"] = (x["k_long"] * torch.tensor([1.0, 1e-30, 1e-37, 0.0])[:, None]).contiguous()
+    g = torch.Generator(device="cpu")
+    g.manual_seed(L + 3029)
+    dZ = torch.randn(B, d, L, generator=g, dtype=torch.float32).to(x["X"].dtype)
+    dev = _dev(x)
+    spec = binding.chela_longconv_spectrum(dev["k_long"])
+    Z = binding.chela_shortlong_conv_fwd(dev["X"], dev["w_short"], spec)
+    dX, dw, dk = binding.chela_shortlong_conv_bwd(dev["X"], dev["w_short"], spec, dZ.cuda())
+    torch.cuda.synchronize()
+    Xn, wn, kn = (to_f64_numpy(x[n]) for n in ("X", "w_short", "k_long"))
+    rZ = oracle_conv.short_long_conv(Xn, wn, kn)
+    rX, rw, rk = oracle_conv.short_long_conv_bwd(Xn, wn, kn, to_f64_numpy(dZ))
+    _check("dk", dk, rk, dtype)
+    for c in range(3):
+        _check("Z[c=%d]" % c, Z[:, c:c + 1], rZ[:, c:c + 1], dtype)
+        _check("dX[c=%d]" % c, dX[:, c:c + 1], rX[:, c:c + 1], dtype)
+        assert oracle.rel_l2(to_f64_numpy(dw[c]), rw[c]) <= BAR[dtype], c
+    for t in (Z[:, 3], dX[:, 3], dw[3]):
+        assert float(t.float().abs().max()) == 0.0
+
+
 @pytest.mark.parametrize("L", [300, 4096])
 def test_long_conv_alone_bwd(L):
     _run_conv_bwd_case(2, 3, L, 3, "f32", seed=L + 12, short=False)
