@@ -300,12 +300,16 @@ int chela_linattn_step_gated(const void *q, const void *k, const void *v, const 
 
 /* Bytes of device scratch one call with these arguments needs, with or without
  * carried states (0 if the arguments are invalid; the training pair has its own query,
- * chela_linattn_train_workspace_bytes).  The size is B*H*dk*dv*4 bytes per segment.
+ * chela_linattn_train_workspace_bytes).  The size is B*H*dk*dv*4 bytes per segment, twice that for
+ * the backward calls (two states per segment).
  * Forward: the number of segments per (b,h) is set by the GPU, not by N, so the scratch
  * does not grow with N once the GPU is full -- the fixed-memory property claimed in
  * Sec. 1.  bf16 backward: in addition no segment is longer than 8192 tokens (see
  * chela_linattn_bwd), i.e. at least two states per 8192 tokens of a sequence: 0.4 % of
- * the bytes of the tensors themselves. */
+ * the bytes of the tensors themselves.  fp32 backward: long sequences are cut finer the longer they are (48 pairs, 64 x 64:
+ * 7 segments at 16384 tokens, 32 at 65536, again 32 at a million); a caller-owned buffer smaller than this size is
+ * accepted down to what one state per segment of the forward's split takes, with fewer segments.  fp32 calls with 256
+ * or more pairs are not cut and take no scratch. */
 size_t chela_linattn_workspace_bytes(int B, int H, int N, int dk, int dv, int chunk,
                                      int is_bwd, int dtype);
 

@@ -136,12 +136,17 @@ Plan make_plan(long BH, int N, int dk, int dv, int chunk, int dtype, bool is_bwd
     return p;
 }
 
-// The fp32 backward is one launch of three forward-shaped sweeps: three workgroups per segment share the GPU.  Up to one
-// round of single chunks it is split like a forward over three times as many sequences; beyond, by a model of its own,
+// The fp32 backward is one launch of three forward-shaped sweeps: three workgroups per segment share the GPU.  From 256
+// (b,h) pairs on it is not split, like every other fp32 call, and takes no scratch.  Below that, up to one round of single
+// chunks it is split like a forward over three times as many sequences; beyond, by a model of its own,
 // because the matrix instructions bound it and not the memory: a round costs its chunk steps whether the one before was
 // full or not, several rounds are no slower than one, and the pre-pass and the states are small change.  Measured, us,
-// by segments per sequence: 96 x 4096 tokens, 64 x 128: one 1286, two 1136, four 964, eight 911; 64 x 64: 602, 565, 472,
-// (five) 442; 112 x 1000, 128 x 64: 314, 291, 294.  (The forward's rule takes one from 256 workgroups on.)
+// by segments per sequence: 96 x 4096 tokens, 64 x 128: one 1282, two 1132, four 961, eight 906; 64 x 64: 600, 564, 470,
+// (five) 436; 112 x 1000, 128 x 64: 314, 291, 295.  The model is not always right: 40 x 4096, 128 x 128: 736 with the two
+// it takes, 653 with four; 16 x 8192, 64 x 128: 345 with its five, 299 with sixteen.  256 pairs and more, one segment
+// against the best of two to sixteen: 256 x 2048, 64 x 64: 491, 531; 257 x 2048: 600, 604; 340 x 2048: 623, 717; 300 x
+// 1000: 304, 343; 384 x 1024, 128 x 128: 1352, 1425; 512 x 700, 64 x 128: 676, 785; only where the last round is
+// nearly empty is one behind: 260 x 4096, 64 x 128: 2587, 2439.
 static long f32_bwd_segments(long wgs_per_seg, long n_chunks, long slots, size_t state_elems)
 {
     long best = 1;
@@ -158,14 +163,13 @@ static long f32_bwd_segments(long wgs_per_seg, long n_chunks, long slots, size_t
     return best;
 }
 
-// Two states per segment and sequence.  The scratch it
-// insists on is what one array of states takes when the sequences are split on their own; a caller-owned buffer between
-// that and the full need gets fewer segments.
+// Two states per segment and sequence.  The scratch it insists on is what one array of states takes when the sequences are
+// split on their own; a caller-owned buffer between that and the full need gets fewer segments.
 Plan make_f32_bwd_plan(long BH, int N, int dk, int dv, int chunk, size_t ws_limit)
 {
     Plan p = make_plan(3 * BH, N, dk, dv, chunk, CHELA_DTYPE_F32, false, false);
     const long chunks = ((long)(N > 0 ? N : 0) + chunk - 1) / chunk, slots = sweep_slots(dk, dv, chunk, CHELA_DTYPE_F32, true);
-    if (BH > 0 && chunks > 4 && 3 * BH * chunks > slots && env_int("CHELA_SEG_TOKENS", 0) <= 0) {
+    if (BH > 0 && BH < 256 && chunks > 4 && 3 * BH * chunks > slots && env_int("CHELA_SEG_TOKENS", 0) <= 0) {
         const long n = f32_bwd_segments(3 * BH, chunks, slots, p.state_elems);
         const long cps = std::max((chunks + n - 1) / n, (chunks + 32767) / 32768);
         p.seg_len = (int)(cps * chunk);

@@ -306,6 +306,17 @@ def test_planner_stays_within_its_bounds_over_random_shapes(L):
                     assert tw % per_state == 0 and (tw >= sv or sv == per_state)
 
 
+def test_f32_calls_of_256_pairs_and_more_take_no_scratch(L):
+    # one segment per sequence, forward and backward: such calls run without an allocation, under stream capture too
+    w = L.chela_linattn_workspace_bytes
+    for pairs in (256, 257, 260, 384, 1600):
+        for N in (1, 64, 1000, 4096, 16384, 1 << 20):
+            for dk, dv in ((64, 64), (64, 128), (128, 64), (128, 128)):
+                for bwd in (0, 1):
+                    assert w(1, pairs, N, dk, dv, 64, bwd, 1) == 0, (pairs, N, dk, dv, bwd)
+    assert w(1, 255, 2048, 64, 64, 64, 1, 1) > 0              # (below that the backward may cut a sequence)
+
+
 def test_forward_query_covers_the_training_pairs_forward(L):
     # 96 (b,h) pairs of 65536 tokens: the plain forward plans 5 segments, the forward that saves states for the backward
     # cuts where the backward will (whose walk is capped at 8192 tokens), 10 times per sequence: a query of its own
