@@ -308,7 +308,8 @@ int chela_linattn_step_gated(const void *q, const void *k, const void *v, const 
  * chela_linattn_bwd), i.e. at least two states per 8192 tokens of a sequence: 0.4 % of
  * the bytes of the tensors themselves.  fp32 backward: long sequences are cut finer the longer they are (48 pairs, 64 x 64:
  * 7 segments at 16384 tokens, 32 at 65536, again 32 at a million); a caller-owned buffer smaller than this size is
- * accepted down to what one state per segment of the forward's split takes, with fewer segments.  fp32 calls with 256
+ * accepted down to what one state per segment of the forward's split takes, with fewer segments; the same goes for the
+ * scratch earlier calls left where nothing can be allocated (under stream capture, or when memory is short).  fp32 calls with 256
  * or more pairs are not cut and take no scratch. */
 size_t chela_linattn_workspace_bytes(int B, int H, int N, int dk, int dv, int chunk,
                                      int is_bwd, int dtype);

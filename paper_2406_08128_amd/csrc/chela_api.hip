@@ -295,8 +295,24 @@ struct OwnWs { hipStream_t stream; void* ptr; size_t bytes; };
 static constexpr size_t kMaxOwnStreams = 64;    // per device
 static std::vector<OwnWs> g_own_ws[kMaxDev];
 
-// What a call may ask get_workspace() for without being refused on account of a caller-owned buffer.
-static size_t workspace_limit() { return t_user_ws ? t_user_bytes : ~(size_t)0; }
+// What a call that would like `bytes` and can do with less may ask get_workspace() for: a caller-owned buffer is as large
+// as it is, and nothing can be allocated while the stream is being captured.
+static size_t workspace_limit(size_t bytes, hipStream_t stream)
+{
+    if (bytes == 0) return 0;
+    if (t_user_ws) return t_user_bytes;
+    int dev = 0;
+    size_t have = 0;
+    if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDev) {
+        std::lock_guard<std::mutex> lk(g_mu);
+        for (const OwnWs& x : g_own_ws[dev]) if (x.stream == stream) { have = x.bytes; break; }
+    }
+    if (have >= bytes) return bytes;
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    const bool capturing = hipStreamIsCapturing(stream, &status) == hipSuccess && status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return capturing ? have : bytes;
+}
 
 static int get_workspace(size_t bytes, void* stream, float** out)
 {
@@ -495,9 +511,18 @@ static int bwd_common(const void* Q, const void* K, const void* V, const void* d
         hipError_t e = launch_bf16_bwd(Q, K, V, dO, S_in, dS_out, dQ, dK, dV, dS_in, nullptr, BH, N, dk, dv, plan, ws, st);
         return e == hipSuccess ? CHELA_OK : CHELA_ERR_HIP;
     }
-    const Plan plan = make_f32_bwd_plan(BH, N, dk, dv, f32_effective_chunk(dk, dv, chunk), workspace_limit());
+    // The split takes more scratch than the call insists on (none, for many shapes): where that cannot be had, under
+    // capture, from a smaller caller-owned buffer or because the allocation is refused, there are fewer segments.
+    const int c = f32_effective_chunk(dk, dv, chunk);
+    Plan plan = make_f32_bwd_plan(BH, N, dk, dv, c, ~(size_t)0);
+    const size_t limit = workspace_limit(plan.ws_bytes, st);
+    if (limit < plan.ws_bytes) plan = make_f32_bwd_plan(BH, N, dk, dv, c, limit);
     float* ws = nullptr;
     rc = get_workspace(plan.ws_bytes, stream, &ws);
+    if (rc == CHELA_ERR_WORKSPACE) {
+        plan = make_f32_bwd_plan(BH, N, dk, dv, c, 0);
+        rc = get_workspace(plan.ws_bytes, stream, &ws);
+    }
     if (rc != CHELA_OK) return rc;
     hipError_t e = launch_f32_bwd((const float*)Q, (const float*)K, (const float*)V, (const float*)dO, (float*)dQ,
                                   (float*)dK, (float*)dV, BH, N, dk, dv, plan, ws, st);

@@ -1488,6 +1488,41 @@ def test_training_step_replays_from_a_hip_graph():
         binding.chela_set_workspace(None)
 
 
+@pytest.mark.parametrize("shape, eager_N", [((5, 7, 451, 64, 64), 0), ((5, 7, 245, 128, 128), 0),
+                                            ((2, 12, 3001, 64, 64), 1200)])
+def test_f32_backward_captures_with_the_scratch_there_is(shape, eager_N):
+    # The split of these shapes takes scratch that the call does not insist on: as the first call of all, or behind a
+    # shorter call whose scratch is enough for fewer segments only, it is captured with what there is, allocating nothing.
+    B, H, N, dk, dv = shape
+    w = _small("f32", N=N, B=B, H=H, dk=dk, dv=dv, seed=91)
+    x = make_inputs(w)
+    d = _dev(x)
+    refs = oracle.bwd_recurrent(*(to_f64_numpy(x[n]) for n in ("Q", "K", "V", "dO")))
+    outs = [torch.empty_like(d[n]) for n in ("Q", "K", "V")]
+    torch.cuda.synchronize()
+    binding.chela_shutdown()                                    # the library's own scratch, all of it
+    assert binding.chela_linattn_workspace_bytes(B, H, N, dk, dv, 64, True, binding.DTYPE_F32) > 0
+    s = torch.cuda.Stream()
+    if eager_N:
+        small = {n: t[:, :, :eager_N].contiguous() for n, t in d.items()}
+        with torch.cuda.stream(s):
+            binding.chela_linattn_bwd(small["Q"], small["K"], small["V"], small["dO"])
+        s.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        binding.chela_linattn_bwd(d["Q"], d["K"], d["V"], d["dO"], dQ=outs[0], dK=outs[1], dV=outs[2])
+    for rep in range(3):
+        for t in outs:
+            t.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for name, g, r in zip(("dQ", "dK", "dV"), outs, refs):
+            _check(name, g, r, "f32")
+        binding.chela_linattn_bwd(d["Q"], d["K"], d["V"], d["dO"])    # eager, with the split the size asks for
+        torch.cuda.synchronize()
+
+
 @pytest.mark.parametrize("shape", NC_SHAPES)
 def test_noncausal_fwd_gated(shape):
     B, H, N, dk, dv = shape
