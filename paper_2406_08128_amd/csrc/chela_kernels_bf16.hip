@@ -642,8 +642,7 @@ struct FwdLds {
 template <int C, int DK, int DV, bool ZQK, bool SAVE, bool GATE = false, bool STAGE = false>
 __device__ __forceinline__ void fwd_sweep_body(const bf16* __restrict__ Qb, const bf16* __restrict__ Kb,
                                                const bf16* __restrict__ Vb, bf16* __restrict__ Ob,
-                                               const float* __restrict__ S0, int n_s0, bool s0_acc,
-                                               float* __restrict__ S_final,
+                                               const float* S0, int n_s0, bool s0_acc, float* S_final,
                                                float* __restrict__ S_final_T, const float* __restrict__ aff,
                                                size_t aff_stride, int ldk, int ldv, int ntok, unsigned char* lds,
                                                int tid, int w, int lane, const bf16* __restrict__ Gb = nullptr,
@@ -1458,10 +1457,10 @@ __global__ __launch_bounds__(256)
 __attribute__((amdgpu_waves_per_eu((C == 64 && DK == 64 && DV == 64) ? 3 : 1)))
 void bf16_fwd_sweep_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ K,
                                                             const bf16* __restrict__ V, bf16* __restrict__ O,
-                                                            const float* __restrict__ S0, float* __restrict__ S_out,
+                                                            const float* __restrict__ S0, float* S_out,
                                                             const float* __restrict__ aff, int H,
                                                             float* __restrict__ saved, int save_every,
-                                                            const float* __restrict__ S_first, size_t first_stride,
+                                                            const float* S_first, size_t first_stride,
                                                             int N, int seg_len, int n_seg, int fold)
 {
     // whole-row streaming stores through a staging tile: every 64-token shape but 128 x 128 (there the tile costs
@@ -1482,7 +1481,8 @@ void bf16_fwd_sweep_kernel(const bf16* __restrict__ Q, const bf16* __restrict__ 
     const size_t rk = row_offset<DK>(NH, bh, H, N, p0), rv = row_offset<DV>(NH, bh, H, N, p0);
     // S0: scanned start states of the segments behind the first; S_first: the state carried in, which the first segment
     // starts from (null: zero), `first_stride` floats from head to head;
-    // S_out: final state of the whole sequence, written by the last segment's workgroup
+    // S_out: final state of the whole sequence, written by the last segment's workgroup.  With one segment it may be the
+    // array at S_first (a state updated in place), so neither is __restrict__, here or in the sweep's body.
     // saved: the running state at the end of every save_every-th segment (and of the last one), transposed, for a
     // backward call that walks segments save_every times as long: [bh][ceil(n_seg / save_every)][dv][dk]
     float* save_to = nullptr;

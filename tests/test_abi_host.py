@@ -386,6 +386,17 @@ def test_set_workspace_alignment(L):
     assert L.chela_set_workspace(None, 0) == 0
 
 
+def test_states_that_may_be_one_array_are_not_declared_free_of_aliases():
+    # chela_linattn_fwd_state accepts S_out == S_in, and with one segment the sweep reads and writes that very array:
+    # the compiler must not be promised that the two do not overlap
+    src = open(os.path.join(ROOT, "paper_2406_08128_amd", "csrc", "chela_kernels_bf16.hip")).read()
+    for func, names in (("fwd_sweep_body", ("S0", "S_final")), ("bf16_fwd_sweep_kernel", ("S_first", "S_out"))):
+        args = re.search(r"void %s\((.*?)\)\s*\{" % func, src, re.S).group(1)
+        for name in names:
+            decl = [a for a in args.split(",") if re.search(r"\b%s$" % name, a.strip())]
+            assert len(decl) == 1 and "*" in decl[0] and "__restrict__" not in decl[0], (func, decl)
+
+
 def test_shutdown_is_idempotent(L):
     L.chela_shutdown()
     L.chela_shutdown()

@@ -629,7 +629,8 @@ def test_state_carry_forward_and_backward(shape):
 
 
 @pytest.mark.parametrize("shape", [(1, 2, 64, 64, 64), (3, 12, 1531, 64, 64), (1, 3, 9000, 64, 64), (2, 3, 1000, 64, 128),
-                                   (2, 3, 1000, 128, 64), (1, 2, 1500, 128, 128), (300, 1, 130, 64, 64)])
+                                   (2, 3, 1000, 128, 64), (1, 2, 1500, 128, 128), (300, 1, 130, 64, 64),
+                                   (260, 1, 70, 64, 128), (260, 1, 70, 128, 64), (260, 1, 70, 128, 128)])
 def test_state_carried_in_place_or_not_gives_the_same(shape):
     # one segment, segments whose totals the sweeps add up (not in place), scanned ones (in place; many segments): the
     # sums are added in one order either way, so the results agree bit for bit, and the untouched state stays as it was
