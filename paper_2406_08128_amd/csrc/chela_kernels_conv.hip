@@ -111,29 +111,29 @@ __host__ __device__ constexpr int conv_threads(int M) { return M / 16 < 64 ? 64 
 __host__ __device__ constexpr bool conv_lead4(int M) { return M == 1024 || M == 16384; }
 __host__ __device__ constexpr int conv_pad(int i) { return i + (i >> 4); }
 
+// Place of W^e in the table of powers: the passes walk it by 1, by 4, by 16 or (M = 16384) by 64, and sixteen neighbours
+// of any such walk lie in sixteen different places of the 256 bytes that the banks span.
+template <int M>
+__host__ __device__ constexpr int power_pos(int e) { return e + (e >> 4) + (M == 16384 ? e >> 6 : 0); }
+
 template <int M>
 struct ConvLds {
     // complex slots; 16 more than the transform needs, so that two real sequences with 32 steps of margin each fit
     static constexpr int DATA = conv_pad(M) + 16;
-    // + twiddles: up to M = 4096 the powers W^e that the passes ask for (e < M / 16), each with its square, which leaves
-    // room for four waves per SIMD; beyond that two tables of 128 to multiply up from
-    static constexpr int POWERS = M / 16 + M / 256;          // one of padding per 16: the passes walk it by 1 or by 16
-    static constexpr int BYTES = DATA * 8 + (M <= 4096 ? POWERS * 16 : 2 * 128 * 8);
+    // + twiddles: the powers W^e that the passes ask for (e < M / 16), each with its square
+    static constexpr int BYTES = DATA * 8 + (power_pos<M>(M / 16 - 1) + 1) * 16;
 };
 
-// w = exp(-2 pi i e / M) (INV: its conjugate) and w2 = w^2.
+// w = exp(-2 pi i e / M) (INV: its conjugate) and w2 = w^2, e < M / 16.  The square comes from the table as well: dft16
+// squares on to w^8, and every squaring doubles the error it is handed.  Where w was multiplied up from two tables of 128
+// and squared here (M = 16384), the gradient of 128 channels x 16384 steps, fp32, was 6.3 .. 7.7e-7 from 64 bits; with the
+// table 4.0 .. 4.7e-7, and 4 x 256 channels take 209 us instead of 250.
 template <int M, bool INV>
-__device__ __forceinline__ void twiddle(const cplx* lo, const cplx* hi, int e, cplx& w, cplx& w2)
+__device__ __forceinline__ void twiddle(const float4* tw, int e, cplx& w, cplx& w2)
 {
-    if constexpr (M <= 4096) {
-        const float4 t = reinterpret_cast<const float4*>(lo)[conv_pad(e)];
-        w = mk(t.x, INV ? -t.y : t.y);
-        w2 = mk(t.z, INV ? -t.w : t.w);
-    } else {
-        w = cmul(lo[e & 127], hi[e >> 7]);
-        if (INV) w = conj(w);
-        w2 = mk(fmaf(w.x, w.x, -w.y * w.y), 2.f * w.x * w.y);
-    }
+    const float4 t = tw[power_pos<M>(e)];
+    w = mk(t.x, INV ? -t.y : t.y);
+    w2 = mk(t.z, INV ? -t.w : t.w);
 }
 
 // Storage position of spectrum bin k (0 <= k < M) after the forward passes.
@@ -167,7 +167,7 @@ __device__ __forceinline__ int block_bin(int block)
 //   inverse, point j of the sub-transform:   sum_q X_q conj(W_N16^(q j)) conj(w16^(p q))
 // so the first pass either way has none.  HALF: forward, inputs 8 .. 15 are zero; inverse, outputs 8 .. 15 are not wanted.
 template <int M, int T, int N16, bool INV, bool HALF>
-__device__ __forceinline__ void pass16(cplx* a, const cplx* lo, const cplx* hi, int tid)
+__device__ __forceinline__ void pass16(cplx* a, const float4* tw, int tid)
 {
     constexpr int S = N16 / 16;
     constexpr int STEP = S >= 16 ? S + S / 16 : 1;                 // padded distance between the transform's points
@@ -177,7 +177,7 @@ __device__ __forceinline__ void pass16(cplx* a, const cplx* lo, const cplx* hi, 
         cplx* p0 = a + (S >= 16 ? conv_pad(block * N16 + j) : 17 * g);
         cplx v[16];
         cplx w = mk(1.f, 0.f), w2 = w;
-        if (!UNIT) twiddle<M, INV>(lo, hi, INV ? j * (M / N16) : block_bin<M, N16>(block) * S, w, w2);
+        if (!UNIT) twiddle<M, INV>(tw, INV ? j * (M / N16) : block_bin<M, N16>(block) * S, w, w2);
 #pragma unroll
         for (int q = 0; q < (HALF && !INV ? 8 : 16); ++q) v[q] = p0[q * STEP];
         dft16<INV, UNIT, HALF && !INV, HALF && INV>(v, w, w2);
@@ -191,13 +191,13 @@ __device__ __forceinline__ void pass16(cplx* a, const cplx* lo, const cplx* hi, 
 // pass forward and the last one back never go through LDS.  A __syncthreads() separates the passes; the caller
 // synchronises before and after.
 template <int M, int T>
-__device__ __forceinline__ void fft_forward(const cplx (&z)[M / T / 2], cplx* a, const cplx* lo, const cplx* hi, int tid)
+__device__ __forceinline__ void fft_forward(const cplx (&z)[M / T / 2], cplx* a, const float4* tw, int tid)
 {
     if constexpr (M == 256) {               // (16 of a wave's threads work in a pass: the input is dealt out again)
 #pragma unroll
         for (int i = 0; i < M / T / 2; ++i) a[conv_pad(tid + T * i)] = z[i];
         __syncthreads();
-        pass16<M, T, 256, false, true>(a, lo, hi, tid);
+        pass16<M, T, 256, false, true>(a, tw, tid);
     } else {
         static_assert(M / T == 16, "sixteen points per thread");
         if constexpr (conv_lead4(M)) {
@@ -212,7 +212,7 @@ __device__ __forceinline__ void fft_forward(const cplx (&z)[M / T / 2], cplx* a,
                 p0[3 * sp] = csub(v0, r);
             }
             __syncthreads();
-            if constexpr (M == 16384) { pass16<M, T, 4096, false, false>(a, lo, hi, tid); __syncthreads(); }
+            if constexpr (M == 16384) { pass16<M, T, 4096, false, false>(a, tw, tid); __syncthreads(); }
         } else {
             constexpr int S = M / 16, STEP = S + S / 16;
             cplx v[16];
@@ -224,40 +224,37 @@ __device__ __forceinline__ void fft_forward(const cplx (&z)[M / T / 2], cplx* a,
             for (int p = 0; p < 16; ++p) p0[p * STEP] = v[rev4(p)];
             __syncthreads();
         }
-        pass16<M, T, 256, false, false>(a, lo, hi, tid);
+        pass16<M, T, 256, false, false>(a, tw, tid);
     }
     __syncthreads();
-    pass16<M, T, 16, false, false>(a, lo, hi, tid);
+    pass16<M, T, 16, false, false>(a, tw, tid);
 }
 
 template <int M, int T>
-__device__ __forceinline__ void fft_inverse(cplx* a, cplx (&y)[M / T / 2], const cplx* lo, const cplx* hi, int tid)
+__device__ __forceinline__ void fft_inverse(cplx* a, cplx (&y)[M / T / 2], const float4* tw, int tid)
 {
-    pass16<M, T, 16, true, false>(a, lo, hi, tid);
+    pass16<M, T, 16, true, false>(a, tw, tid);
     __syncthreads();
     if constexpr (M == 256) {
-        pass16<M, T, 256, true, true>(a, lo, hi, tid);
+        pass16<M, T, 256, true, true>(a, tw, tid);
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < M / T / 2; ++i) y[i] = a[conv_pad(tid + T * i)];
     } else {
-        pass16<M, T, 256, true, false>(a, lo, hi, tid);
+        pass16<M, T, 256, true, false>(a, tw, tid);
         __syncthreads();
         if constexpr (conv_lead4(M)) {
-            if constexpr (M == 16384) { pass16<M, T, 4096, true, false>(a, lo, hi, tid); __syncthreads(); }
+            if constexpr (M == 16384) { pass16<M, T, 4096, true, false>(a, tw, tid); __syncthreads(); }
             constexpr int s = M / 4, sp = s + s / 16;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const cplx* p0 = a + conv_pad(tid + T * j);
                 cplx t1, t2;
-                if constexpr (M == 1024) {      // W^tid times sixteenth roots
-                    constexpr float C1 = 0.92387953251128674f, S1 = 0.38268343236508977f, R2 = 0.70710678118654752f;
-                    twiddle<M, true>(lo, hi, tid, t1, t2);
-                    t1 = j == 0 ? t1 : cmul(t1, j == 1 ? mk(C1, S1) : j == 2 ? mk(R2, R2) : mk(S1, C1));
-                    t2 = j == 0 ? t2 : j == 2 ? mul_pos_i(t2) : cmul(t2, j == 1 ? mk(R2, R2) : mk(-R2, R2));
-                } else {
-                    twiddle<M, true>(lo, hi, tid + T * j, t1, t2);
-                }
+                // W^(tid + j M/16): W^tid times sixteenth roots
+                constexpr float C1 = 0.92387953251128674f, S1 = 0.38268343236508977f, R2 = 0.70710678118654752f;
+                twiddle<M, true>(tw, tid, t1, t2);
+                t1 = j == 0 ? t1 : cmul(t1, j == 1 ? mk(C1, S1) : j == 2 ? mk(R2, R2) : mk(S1, C1));
+                t2 = j == 0 ? t2 : j == 2 ? mul_pos_i(t2) : cmul(t2, j == 1 ? mk(R2, R2) : mk(-R2, R2));
                 const cplx t3 = cmul(t2, t1);
                 cplx v0 = p0[0], v1 = cmul(p0[sp], t1), v2 = p0[2 * sp], v3 = p0[3 * sp];
                 bfly(v0, v2, t2.x, t2.y);
@@ -272,7 +269,7 @@ __device__ __forceinline__ void fft_inverse(cplx* a, cplx (&y)[M / T / 2], const
 #pragma unroll
             for (int q = 0; q < 16; ++q) v[q] = p0[q * STEP];
             cplx w, w2;
-            twiddle<M, true>(lo, hi, tid, w, w2);
+            twiddle<M, true>(tw, tid, w, w2);
             dft16<true, false, false, true>(v, w, w2);
 #pragma unroll
             for (int p = 0; p < 8; ++p) y[p] = v[rev4(p)];
@@ -384,22 +381,13 @@ __device__ __forceinline__ void store8(bf16* p, const float (&v)[8])
 }
 
 template <int M, int T>
-__device__ __forceinline__ void build_tables(cplx* lo, cplx* hi, int tid)
+__device__ __forceinline__ void build_tables(float4* tw, int tid)
 {
     float s, c, s2, c2;
-    if constexpr (M <= 4096) {
-        for (int e = tid; e < M / 16; e += T) {
-            sincospif(-2.0f * (float)e / (float)M, &s, &c);
-            sincospif(-4.0f * (float)e / (float)M, &s2, &c2);
-            reinterpret_cast<float4*>(lo)[conv_pad(e)] = make_float4(c, s, c2, s2);
-        }
-    } else {
-        for (int t = tid; t < 128; t += T) {
-            sincospif(-2.0f * (float)t / (float)M, &s, &c);
-            lo[t] = mk(c, s);
-            sincospif(-2.0f * (float)(t * 128 % M) / (float)M, &s, &c);
-            hi[t] = mk(c, s);
-        }
+    for (int e = tid; e < M / 16; e += T) {
+        sincospif(-2.0f * (float)e / (float)M, &s, &c);
+        sincospif(-4.0f * (float)e / (float)M, &s2, &c2);
+        tw[power_pos<M>(e)] = make_float4(c, s, c2, s2);
     }
 }
 
@@ -678,11 +666,10 @@ __global__ __launch_bounds__(conv_threads(M)) void longconv_spectrum_kernel(cons
     __shared__ __attribute__((aligned(16))) unsigned char lds[ConvLds<M>::BYTES];
     __shared__ float red[MX ? T / 64 : 1];
     cplx* a = reinterpret_cast<cplx*>(lds);
-    cplx* lo = a + ConvLds<M>::DATA;
-    cplx* hi = lo + 128;
+    float4* tw = reinterpret_cast<float4*>(a + ConvLds<M>::DATA);
     const int tid = threadIdx.x;
     const long c = blockIdx.x;
-    build_tables<M, T>(lo, hi, tid);
+    build_tables<M, T>(tw, tid);
     SeqRegs<M, T, float> kr;
     kr.load(k + c * (long)L, L, tid);
     cplx z[M / T / 2];
@@ -696,7 +683,7 @@ __global__ __launch_bounds__(conv_threads(M)) void longconv_spectrum_kernel(cons
         if ((tid & 63) == 0) red[tid >> 6] = n1;
     }
     __syncthreads();
-    fft_forward<M, T>(z, a, lo, hi, tid);
+    fft_forward<M, T>(z, a, tw, tid);
     __syncthreads();
     float inv = 0.f;
     if constexpr (MX) {
@@ -783,10 +770,9 @@ void shortlong_conv_kernel(const IN* __restrict__ X,
     constexpr int T = conv_threads(M), NP = PairPos<M, T>::NP;
     __shared__ __attribute__((aligned(16))) unsigned char lds[ConvLds<M>::BYTES];
     cplx* a = reinterpret_cast<cplx*>(lds);
-    cplx* lo = a + ConvLds<M>::DATA;
-    cplx* hi = lo + 128;
+    float4* tw = reinterpret_cast<float4*>(a + ConvLds<M>::DATA);
     const int tid = threadIdx.x;
-    build_tables<M, T>(lo, hi, tid);
+    build_tables<M, T>(tw, tid);
     const PairPos<M, T> pos(tid);
     const PairTwiddle<M, T> pw(tid);
     SeqRegs<M, T, IN> xr;
@@ -803,7 +789,7 @@ void shortlong_conv_kernel(const IN* __restrict__ X,
 #pragma unroll
         for (int i = 0; i < NP; ++i) kq[i] = Kc[tp + T * i];
         tp = fresh(tid);
-        fft_forward<M, T>(z, a, lo, hi, tp);
+        fft_forward<M, T>(z, a, tw, tp);
         __syncthreads();
         cplx w = pw.first;
 #pragma unroll
@@ -818,7 +804,7 @@ void shortlong_conv_kernel(const IN* __restrict__ X,
         if (bc + gridDim.x < total) xr.load(X + (bc + gridDim.x) * (long)L, L, tp);     // the next sequence, in flight
         __syncthreads();
         tp = fresh(tid);
-        fft_inverse<M, T>(a, z, lo, hi, tp);
+        fft_inverse<M, T>(a, z, tw, tp);
         store_steps<M, T, OUT>(z, Y + bc * (long)L, L, (L & 1) == 0, 1.0f / (float)M, tp);
     }
 }
@@ -838,7 +824,7 @@ void shortlong_conv_kernel(const IN* __restrict__ X,
 // dU = dV silu'(u) meets its neighbours through LDS: dX out (dV is DVT = IO dX here), the taps' sums into `part`
 // ([d][grid.y][kShortMaxTaps]).  As a kernel of its own that stage reads x again, and dV, 4 bytes a step written here and
 // read there, and works u out once more: 512 channels x 32 sequences of 4096 steps, bf16, the two kernels 527 + 150 us,
-// in one 475.  bf16 I/O asks for three workgroups per compute unit (168 registers, 31 values spilled; training step 655 us
+// in one 475.  bf16 I/O asks for three workgroups per compute unit (168 registers, 4 or 5 values spilled; training step 645 us
 // against 707 with two and nothing spilled), fp32 I/O, which holds twice the fetched words, for two (234 against 262 us at
 // 512 x 8 x 4000).
 constexpr int kFuseTaps = 16, kShortMaxTaps = 32;
@@ -860,13 +846,13 @@ void longconv_bwd_kernel(const IO* __restrict__ X,
     float4* accm = (ACC_MEM || SPLIT) ? acc_ws + ((long)blockIdx.y * d + blockIdx.x) * (M / 2 + 1) : nullptr;
     __shared__ __attribute__((aligned(16))) unsigned char lds[ConvLds<M>::BYTES];
     cplx* a = reinterpret_cast<cplx*>(lds);
-    cplx* lo = a + ConvLds<M>::DATA;
-    cplx* hi = lo + 128;
+    float4* tw = reinterpret_cast<float4*>(a + ConvLds<M>::DATA);
     const int tid = threadIdx.x;
     const int c = blockIdx.x;
-    build_tables<M, T>(lo, hi, tid);
-    const PairPos<M, T> pos(tid);
-    const PairTwiddle<M, T> pw(tid);
+    build_tables<M, T>(tw, tid);
+    // the pairs' places and twiddles: worked out once, at the largest size, where the six registers would be spilled ones,
+    // wherever they are used
+    auto stage_tid = [&]() __attribute__((always_inline)) { return ACC_MEM ? fresh(tid) : tid; };
     const float4* Kc = Kf + (long)c * (M / 2 + 1);
     const float* wc = w_short ? w_short + (long)c * m : nullptr;
     const bool vec_ok = (L & 1) == 0;
@@ -892,22 +878,34 @@ void longconv_bwd_kernel(const IO* __restrict__ X,
         int tp = fresh(tid);
         // ---- spectrum of dZ; correlation with the kernel: DZ conj(K)
         stage_input<M, T, IO>(zr, nullptr, 0, L, a, tp, z);
-        float4 kq[NP];
+        // the kernel's entries: in flight during the transform, at the largest size, where they would spill, a few at a
+        // time behind it
+        constexpr int KU = ACC_MEM ? 4 : NP;
+        float4 kq[KU];
+        if constexpr (!ACC_MEM) {
 #pragma unroll
-        for (int i = 0; i < NP; ++i) kq[i] = Kc[tp + T * i];
+            for (int i = 0; i < NP; ++i) kq[i] = Kc[tp + T * i];
+        }
         __syncthreads();        // the tables are built / a[] has been read out
-        fft_forward<M, T>(z, a, lo, hi, tp);
+        fft_forward<M, T>(z, a, tw, tp);
         __syncthreads();
         tp = fresh(tid);
         xr.load(X + row, L, tp);
         {
+            const int ts = stage_tid();
+            const PairPos<M, T> pos(ts);
+            const PairTwiddle<M, T> pw(ts);
 #pragma unroll
             for (int i = 0; i < NP; ++i) { GA[i] = a[pos.first(i)]; GB[i] = conj(a[pos.second(i)]); }
             cplx w = pw.first;
 #pragma unroll
             for (int i = 0; i < NP; ++i) {
+                if (ACC_MEM && i % KU == 0) {
+#pragma unroll
+                    for (int u = 0; u < KU; ++u) kq[u] = Kc[tp + T * (i + u)];
+                }
                 cplx A = GA[i], B = GB[i];
-                pair_mul<true>(A, B, w, kq[i], i == 0 && tid == 0);
+                pair_mul<true>(A, B, w, kq[i % KU], i == 0 && tid == 0);
                 a[pos.first(i)] = A;
                 a[pos.second(i)] = conj(B);
                 w = cmul(w, PairTwiddle<M, T>::step);
@@ -916,7 +914,7 @@ void longconv_bwd_kernel(const IO* __restrict__ X,
         }
         __syncthreads();
         tp = fresh(tid);
-        fft_inverse<M, T>(a, z, lo, hi, tp);
+        fft_inverse<M, T>(a, z, tw, tp);
         tp = fresh(tid);
         if constexpr (SHORT) {
             float* sx = reinterpret_cast<float*>(a);
@@ -1005,9 +1003,12 @@ void longconv_bwd_kernel(const IO* __restrict__ X,
         __syncthreads();
         tp = fresh(tid);
         // ---- its spectrum; running sums of DZ conj(V)
-        fft_forward<M, T>(z, a, lo, hi, tp);
+        fft_forward<M, T>(z, a, tw, tp);
         __syncthreads();
         {
+            const int ts = stage_tid();
+            const PairPos<M, T> pos(ts);
+            const PairTwiddle<M, T> pw(ts);
             cplx w = pw.first;
             constexpr int U = NP < 4 ? NP : 4;       // pairs read together
 #pragma unroll
@@ -1054,6 +1055,9 @@ void longconv_bwd_kernel(const IO* __restrict__ X,
         return;
     }
     {
+        const int ts = stage_tid();
+        const PairPos<M, T> pos(ts);
+        const PairTwiddle<M, T> pw(ts);
         cplx w = pw.first;
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
@@ -1068,7 +1072,7 @@ void longconv_bwd_kernel(const IO* __restrict__ X,
         }
     }
     __syncthreads();
-    fft_inverse<M, T>(a, z, lo, hi, tid);
+    fft_inverse<M, T>(a, z, tw, tid);
     store_steps<M, T, float>(z, dk + (long)c * L, L, vec_ok, scale, tid);
 }
 
@@ -1373,13 +1377,12 @@ __global__ __launch_bounds__(kBlkT) void longconv_spectrum_blocked_kernel(const 
     constexpr int M = kBlkM, T = kBlkT, NP = PairPos<M, T>::NP;
     __shared__ __attribute__((aligned(16))) unsigned char lds[ConvLds<M>::BYTES];
     cplx* a = reinterpret_cast<cplx*>(lds);
-    cplx* lo = a + ConvLds<M>::DATA;
-    cplx* hi = lo + 128;
+    float4* tw = reinterpret_cast<float4*>(a + ConvLds<M>::DATA);
     const int tid = threadIdx.x;
     const long c = blockIdx.x;
     const int mb = blockIdx.y;
     const bool row_vec = (L & 1) == 0;
-    build_tables<M, T>(lo, hi, tid);
+    build_tables<M, T>(tw, tid);
     const PairPos<M, T> pos(tid);
     const PairTwiddle<M, T> pw(tid);
     // the block before sits in the upper half of the period: (-1)^bin (a thread's bins, k and M - k, all have one parity)
@@ -1394,7 +1397,7 @@ __global__ __launch_bounds__(kBlkT) void longconv_spectrum_blocked_kernel(const 
         cplx z[M / T / 2];
         stage_input<M, T, float>(kr, nullptr, 0, len, a, tid, z);
         __syncthreads();                  // tables built / the block before has been read out of a[]
-        fft_forward<M, T>(z, a, lo, hi, tid);
+        fft_forward<M, T>(z, a, tw, tid);
         __syncthreads();
         const float sg = which < mb ? odd : 1.f;
         cplx w = pw.first;
@@ -1424,11 +1427,10 @@ __global__ __launch_bounds__(kBlkT) void longconv_blocked_kernel(const IN* __res
     constexpr int M = kBlkM, T = kBlkT, NP = PairPos<M, T>::NP;
     __shared__ __attribute__((aligned(16))) unsigned char lds[ConvLds<M>::BYTES];
     cplx* a = reinterpret_cast<cplx*>(lds);
-    cplx* lo = a + ConvLds<M>::DATA;
-    cplx* hi = lo + 128;
+    float4* tw = reinterpret_cast<float4*>(a + ConvLds<M>::DATA);
     const int tid = threadIdx.x;
     const bool row_vec = (L & 1) == 0;
-    build_tables<M, T>(lo, hi, tid);
+    build_tables<M, T>(tw, tid);
     const PairPos<M, T> pos(tid);
     const PairTwiddle<M, T> pw(tid);
     const long items = BD * nb;
@@ -1452,7 +1454,7 @@ __global__ __launch_bounds__(kBlkT) void longconv_blocked_kernel(const IN* __res
             stage_input<M, T, IN>(xr, wc, m, min(M, L - o * M), a, tp, z, (wc && o > 0) ? xrow + (long)o * M : nullptr);
             if (o < o1) xr.load(xrow + (long)(o + 1) * M, min(M, L - (o + 1) * M), tp, row_vec);   // the next block, in flight
             tp = fresh(tid);
-            fft_forward<M, T>(z, a, lo, hi, tp);
+            fft_forward<M, T>(z, a, tw, tp);
             __syncthreads();
             tp = fresh(tid);
             const float4* Gc = Gf + ((long)c * nb + (CORR ? o - blk : blk - o)) * (long)(M / 2 + 1);
@@ -1478,7 +1480,7 @@ __global__ __launch_bounds__(kBlkT) void longconv_blocked_kernel(const IN* __res
         }
         __syncthreads();
         const int tp = fresh(tid);
-        fft_inverse<M, T>(a, z, lo, hi, tp);
+        fft_inverse<M, T>(a, z, tw, tp);
         store_steps<M, T, OUT>(z, Y + bc * (long)L + (long)blk * M, min(M, L - blk * M), row_vec, 1.0f / (float)M, tp);
     }
 }
@@ -1496,18 +1498,15 @@ __global__ __launch_bounds__(kBlkT) void longconv_dk_blocked_kernel(const IO* __
     constexpr int M = kBlkM, T = kBlkT, NP = PairPos<M, T>::NP;
     __shared__ __attribute__((aligned(16))) unsigned char lds[ConvLds<M>::BYTES];
     cplx* a = reinterpret_cast<cplx*>(lds);
-    cplx* lo = a + ConvLds<M>::DATA;
-    cplx* hi = lo + 128;
+    float4* tw = reinterpret_cast<float4*>(a + ConvLds<M>::DATA);
     const int tid = threadIdx.x;
     const int c = blockIdx.x, mb = blockIdx.y;
     const bool row_vec = (L & 1) == 0;
-    build_tables<M, T>(lo, hi, tid);
+    build_tables<M, T>(tw, tid);
     float4* accm = acc_ws + ((long)c * nb + mb) * (long)(M / 2 + 1);
     const float* wc = w_short ? w_short + (long)c * m : nullptr;
     const int n_i = nb - mb;                     // block pairs (i, i + mb) per sequence
     const long n_pairs = (long)B * n_i;
-    const PairPos<M, T> pos(tid);
-    const PairTwiddle<M, T> pw(tid);
     cplx GA[NP], GB[NP], z[M / T / 2];
     SeqRegs<M, T, IO> zr, xr;
     zr.load(dZ + (long)c * L + (long)mb * M, min(M, L - mb * M), tid, row_vec);      // pair 0: b = 0, i = 0
@@ -1518,10 +1517,13 @@ __global__ __launch_bounds__(kBlkT) void longconv_dk_blocked_kernel(const IO* __
         stage_input<M, T, IO>(zr, nullptr, 0, min(M, L - j * M), a, tp, z);
         xr.load(X + row + (long)i * M, min(M, L - i * M), tp, row_vec);
         __syncthreads();        // tables built / a[] has been read out
-        fft_forward<M, T>(z, a, lo, hi, tp);
+        fft_forward<M, T>(z, a, tw, tp);
         __syncthreads();
+        {
+            const PairPos<M, T> pos(fresh(tid));
 #pragma unroll
-        for (int q = 0; q < NP; ++q) { GA[q] = a[pos.first(q)]; GB[q] = conj(a[pos.second(q)]); }
+            for (int q = 0; q < NP; ++q) { GA[q] = a[pos.first(q)]; GB[q] = conj(a[pos.second(q)]); }
+        }
         __syncthreads();
         tp = fresh(tid);
         stage_input<M, T, IO>(xr, wc, m, min(M, L - i * M), a, tp, z, (wc && i > 0) ? X + row + (long)i * M : nullptr);
@@ -1530,8 +1532,11 @@ __global__ __launch_bounds__(kBlkT) void longconv_dk_blocked_kernel(const IO* __
             zr.load(dZ + ((long)b2 * d + c) * (long)L + (long)(i2 + mb) * M, min(M, L - (i2 + mb) * M), tp, row_vec);
         }
         tp = fresh(tid);
-        fft_forward<M, T>(z, a, lo, hi, tp);
+        fft_forward<M, T>(z, a, tw, tp);
         __syncthreads();
+        tp = fresh(tid);
+        const PairPos<M, T> pos(tp);
+        const PairTwiddle<M, T> pw(tp);
         cplx w = pw.first;
 #pragma unroll
         for (int q = 0; q < NP; ++q) {
@@ -1553,11 +1558,10 @@ __global__ __launch_bounds__(kBlkT) void longconv_dk_blocked_finish_kernel(const
     constexpr int M = kBlkM, T = kBlkT;
     __shared__ __attribute__((aligned(16))) unsigned char lds[ConvLds<M>::BYTES];
     cplx* a = reinterpret_cast<cplx*>(lds);
-    cplx* lo = a + ConvLds<M>::DATA;
-    cplx* hi = lo + 128;
+    float4* tw = reinterpret_cast<float4*>(a + ConvLds<M>::DATA);
     const int tid = threadIdx.x;
     const int c = blockIdx.x, mb = blockIdx.y;
-    build_tables<M, T>(lo, hi, tid);
+    build_tables<M, T>(tw, tid);
     const float4* D0 = acc_ws + ((long)c * nb + mb) * (long)(M / 2 + 1);
     const float4* D1 = mb + 1 < nb ? D0 + (M / 2 + 1) : nullptr;
     const PairPos<M, T> pos(tid);
@@ -1579,7 +1583,7 @@ __global__ __launch_bounds__(kBlkT) void longconv_dk_blocked_finish_kernel(const
     }
     __syncthreads();
     cplx z[M / T / 2];
-    fft_inverse<M, T>(a, z, lo, hi, tid);
+    fft_inverse<M, T>(a, z, tw, tid);
     store_steps<M, T, float>(z, dk + (long)c * L + (long)mb * M, min(M, L - mb * M), (L & 1) == 0, 1.0f / (float)M, tid);
 }
 
@@ -1681,11 +1685,10 @@ __global__ __launch_bounds__(conv_threads(M)) void longconv_dk_finish_kernel(con
     constexpr int T = conv_threads(M);
     __shared__ __attribute__((aligned(16))) unsigned char lds[ConvLds<M>::BYTES];
     cplx* a = reinterpret_cast<cplx*>(lds);
-    cplx* lo = a + ConvLds<M>::DATA;
-    cplx* hi = lo + 128;
+    float4* tw = reinterpret_cast<float4*>(a + ConvLds<M>::DATA);
     const int tid = threadIdx.x;
     const int c = blockIdx.x;
-    build_tables<M, T>(lo, hi, tid);
+    build_tables<M, T>(tw, tid);
     const PairPos<M, T> pos(tid);
     const PairTwiddle<M, T> pw(tid);
     cplx w = pw.first;
@@ -1704,7 +1707,7 @@ __global__ __launch_bounds__(conv_threads(M)) void longconv_dk_finish_kernel(con
     }
     __syncthreads();
     cplx z[M / T / 2];
-    fft_inverse<M, T>(a, z, lo, hi, tid);
+    fft_inverse<M, T>(a, z, tw, tid);
     store_steps<M, T, float>(z, dk + (long)c * L, L, (L & 1) == 0, 1.0f / (float)M, tid);
 }
 

@@ -1147,6 +1147,27 @@ def test_conv_channels_whose_long_kernel_has_decayed_to_almost_nothing(case):
         assert float(t.float().abs().max()) == 0.0
 
 
+@pytest.mark.parametrize("L", [4097, 9001, 16384, 20001])
+def test_error_of_the_largest_transform(L):
+    # fp32 gradient through 16384-point transforms: three in a row.  With u = 2^-24: fifteen levels of fused butterflies
+    # of about 0.6 u each, sqrt(3 * 15) * 0.6 u = 2.4e-7, and three passes each whose twiddles w^8, w^4, w^2, w carry 2.1,
+    # 1, 0.4 and 0.4 u and meet half of what passes through, sqrt(9) * 1.7 u = 3.0e-7: 3.9e-7 together, half as much
+    # again for the short stage.  (Twiddles that are products, and squares of products, of table entries: 7.7e-7.)
+    B, d, m = 1, 3, 9
+    x = make_conv_inputs(B, d, L, m, L + 41, "f32")
+    g = torch.Generator(device="cpu")
+    g.manual_seed(L + 3041)
+    dZ = torch.randn(B, d, L, generator=g, dtype=torch.float32)
+    dev = _dev(x)
+    spec = binding.chela_longconv_spectrum(dev["k_long"])
+    got = binding.chela_shortlong_conv_bwd(dev["X"], dev["w_short"], spec, dZ.cuda())
+    ref = oracle_conv.short_long_conv_bwd(*(to_f64_numpy(x[n]) for n in ("X", "w_short", "k_long")), to_f64_numpy(dZ))
+    for name, a, r in zip(("dX", "dw", "dk"), got, ref):
+        err = oracle.rel_l2(to_f64_numpy(a), r)
+        print("%s L%d: %.3g" % (name, L, err), flush=True)
+        assert err <= 5.8e-7, (name, err)
+
+
 @pytest.mark.parametrize("L", [300, 4096])
 def test_long_conv_alone_bwd(L):
     _run_conv_bwd_case(2, 3, L, 3, "f32", seed=L + 12, short=False)
