@@ -142,8 +142,8 @@ Plan make_plan(long BH, int N, int dk, int dv, int chunk, int dtype, bool is_bwd
 // because the matrix instructions bound it and not the memory: a round costs its chunk steps whether the one before was
 // full or not, several rounds are no slower than one, and the pre-pass and the states are small change.  Measured, us,
 // by segments per sequence: 96 x 4096 tokens, 64 x 128: one 1282, two 1132, four 961, eight 906; 64 x 64: 600, 564, 470,
-// (five) 436; 112 x 1000, 128 x 64: 314, 291, 295.  The model is not always right: 40 x 4096, 128 x 128: 736 with the two
-// it takes, 653 with four; 16 x 8192, 64 x 128: 345 with its five, 299 with sixteen.  256 pairs and more, one segment
+// (five) 436; 112 x 1000, 128 x 64: 314, 291, 295.  The model is not always right: 40 x 4096, 128 x 128: 754 with the two
+// it takes, 653 with four; 16 x 8192, 64 x 128: 349 with its five, 299 with sixteen.  256 pairs and more, one segment
 // against the best of two to sixteen: 256 x 2048, 64 x 64: 491, 531; 257 x 2048: 600, 604; 340 x 2048: 623, 717; 300 x
 // 1000: 304, 343; 384 x 1024, 128 x 128: 1352, 1425; 512 x 700, 64 x 128: 676, 785; only where the last round is
 // nearly empty is one behind: 260 x 4096, 64 x 128: 2587, 2439.
@@ -175,7 +175,8 @@ Plan make_f32_bwd_plan(long BH, int N, int dk, int dv, int chunk, size_t ws_limi
         p.seg_len = (int)(cps * chunk);
         p.n_seg = (int)((chunks + cps - 1) / cps);
     }
-    const size_t least = make_plan(BH, N, dk, dv, chunk, CHELA_DTYPE_F32, true, false).ws_bytes;
+    const Plan own = make_plan(BH, N, dk, dv, chunk, CHELA_DTYPE_F32, true, false);
+    const size_t least = own.ws_bytes;
     const size_t state = BH > 0 ? (size_t)BH * p.state_elems * sizeof(float) : 0;
     // (and never more than one state per sequence and 32 tokens)
     const size_t room = std::max(least, std::min(ws_limit, state * (((size_t)(N > 0 ? N : 0) + 31) / 32)));
@@ -186,6 +187,7 @@ Plan make_f32_bwd_plan(long BH, int N, int dk, int dv, int chunk, size_t ws_limi
         p.n_seg = (int)((n_chunks + cps - 1) / cps);
     }
     p.ws_bytes = std::max(least, p.n_seg > 1 ? (size_t)p.n_seg * 2 * state : 0);
+    p.by_chunk = std::min(p.seg_len, N) > std::min(own.seg_len, N);
     return p;
 }
 

@@ -17,6 +17,7 @@ struct Plan {
     size_t ws_bytes;     // scratch bytes for the whole call
     int ckpt_every;      // bf16 backward with a single segment: the sweep's first pass leaves the running state every
                          // ckpt_every chunks and its walk back picks those copies up again (0: none needed)
+    bool by_chunk;       // fp32 backward: running sums take a chunk's products as one number (longer segments)
 };
 
 // The sweeps add the segment totals up themselves (no scan kernel) while one (b,h) pair's totals stay below this:

@@ -307,13 +307,29 @@ struct TileRegsF32 {
     }
 };
 
+// S + K^T V over K2 tokens, one 32 x 32 tile.  BY_CHUNK: the tokens are summed up by themselves and added to the running
+// sum in one go; as operands of one chain of matrix instructions each is rounded to the last place of the running sum.
+// The backward does so where its segments are longer than sequences split on their own would have (Plan::by_chunk), which
+// would lose accuracy: 4 x 16384 tokens, 128 x 128, 4.7e-7 from 64 bits in their own segments, 7.3e-7 in the longer ones,
+// 3.0e-7 in these by chunks; 24 x 3001, 64 x 64, 4.6, 5.2, 2.6e-7.  It costs up to 3 % (128 x 128; 64 x 64 below 1 %).
+template <int K2, bool BY_CHUNK>
+__device__ __forceinline__ f32x16 state_tile(f32x16 acc, const float* k, int ldk, const float* v, int ldv, int lane)
+{
+    // A[m=i][k=s] = K[s][i]: contiguous in i;  B[k=s][n=j] = V[s][j]: contiguous in j
+    if (!BY_CHUNK) return gemm_tile<K2>(acc, k, 1, ldk, v, ldv, 1, lane);
+    const f32x16 t = gemm_tile<K2>(zero16f(), k, 1, ldk, v, ldv, 1, lane);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] += t[e];
+    return acc;
+}
+
 // ------------------------------------------------------------------------------------------------ segment totals
 // out[bh][seg][i*DV + j] = sum over the segment's tokens of K[t][i] * V[t][j].  The last segment's total is never
 // used by an exclusive prefix, so its workgroups leave at once.  Wave w owns output tiles w, w+4, ...
 constexpr int kF32SegRows = 64;                 // tokens staged per step
 constexpr int f32_seg_lds(int dk, int dv) { return kF32SegRows * (dk + dv + 2); }     // floats
 
-template <int DK, int DV>
+template <int DK, int DV, bool BY_CHUNK>
 __device__ __forceinline__ void f32_seg_state_body(const float* __restrict__ K, const float* __restrict__ V,
                                                    float* __restrict__ out, int N, int seg_len, int n_seg, bool rev,
                                                    float* lds)
@@ -355,8 +371,7 @@ __device__ __forceinline__ void f32_seg_state_body(const float* __restrict__ K, 
 #pragma unroll
             for (int n = 0; n < NT; ++n) {
                 const int id = w + 4 * n, ib = id / JB, jb = id % JB;
-                // A[m=i][k=s] = K[s][i]: contiguous in i;  B[k=s][n=j] = V[s][j]: contiguous in j
-                acc[n] = gemm_tile<R>(acc[n], sK + ib * 32, 1, LDK, sV + jb * 32, LDV, 1, lane);
+                acc[n] = state_tile<R, BY_CHUNK>(acc[n], sK + ib * 32, LDK, sV + jb * 32, LDV, lane);
             }
         }
     }
@@ -377,19 +392,19 @@ __global__ __launch_bounds__(256) void f32_seg_state_kernel(const float* __restr
                                                            float* __restrict__ out, int N, int seg_len, int n_seg)
 {
     __shared__ float lds[f32_seg_lds(DK, DV)];
-    f32_seg_state_body<DK, DV>(K, V, out, N, seg_len, n_seg, false, lds);
+    f32_seg_state_body<DK, DV, false>(K, V, out, N, seg_len, n_seg, false, lds);
 }
 
 // The backward's two sets of totals, V^T K in reading order and Q^T dO from the end, side by side on grid.z.
-template <int DK, int DV>
+template <int DK, int DV, bool BY_CHUNK>
 __global__ __launch_bounds__(256) void f32_bwd_seg_state_kernel(const float* __restrict__ Q, const float* __restrict__ K,
                                                                const float* __restrict__ V, const float* __restrict__ dO,
                                                                float* __restrict__ out, size_t array_stride, int N,
                                                                int seg_len, int n_seg)
 {
     __shared__ float lds[f32_seg_lds(DK, DV)];
-    if (blockIdx.z == 0) f32_seg_state_body<DV, DK>(V, K, out, N, seg_len, n_seg, false, lds);
-    else f32_seg_state_body<DK, DV>(Q, dO, out + array_stride, N, seg_len, n_seg, true, lds);
+    if (blockIdx.z == 0) f32_seg_state_body<DV, DK, BY_CHUNK>(V, K, out, N, seg_len, n_seg, false, lds);
+    else f32_seg_state_body<DK, DV, BY_CHUNK>(Q, dO, out + array_stride, N, seg_len, n_seg, true, lds);
 }
 
 // ------------------------------------------------------------------------------------------------ main sweep
@@ -405,7 +420,7 @@ constexpr int f32_sweep_lds(int dk, int dv)                                     
     return c * (dk + 1) + f32_sweep_kp(c, dk) + c * (dv + 1) + dk * (dv + 1);
 }
 
-template <int C, int DK, int DV>
+template <int C, int DK, int DV, bool BY_CHUNK>
 __device__ __forceinline__ void f32_sweep_body(const float* __restrict__ Q, const float* __restrict__ K,
                                                const float* __restrict__ V, float* __restrict__ O,
                                                const float* __restrict__ S0, int N, int seg_len, int n_seg, bool rev,
@@ -501,7 +516,7 @@ __device__ __forceinline__ void f32_sweep_body(const float* __restrict__ Q, cons
 #pragma unroll
             for (int n = 0; n < NS; ++n) {
                 const int id = w + 4 * n, ib = id / JB, jb = id % JB;
-                accS[n] = gemm_tile<C>(accS[n], sK + ib * 32, 1, LDK, sV + jb * 32, LDV, 1, lane);
+                accS[n] = state_tile<C, BY_CHUNK>(accS[n], sK + ib * 32, LDK, sV + jb * 32, LDV, lane);
             }
         }
         __syncthreads();   // K has been read for the last time: its place now takes the scores
@@ -549,7 +564,7 @@ __global__ __launch_bounds__(256) void f32_sweep_kernel(const float* __restrict_
                                                        const float* __restrict__ S0, int N, int seg_len, int n_seg)
 {
     __shared__ float lds[f32_sweep_lds(DK, DV)];
-    f32_sweep_body<f32_sweep_chunk(DK, DV), DK, DV>(Q, K, V, O, S0, N, seg_len, n_seg, false, false, lds);
+    f32_sweep_body<f32_sweep_chunk(DK, DV), DK, DV, false>(Q, K, V, O, S0, N, seg_len, n_seg, false, false, lds);
 }
 
 // The gradient is three instances of the forward map (time-reversal duality), independent of one another, so they ride
@@ -560,7 +575,7 @@ __global__ __launch_bounds__(256) void f32_sweep_kernel(const float* __restrict_
 // Bound by the fp32 matrix rate (24 heads x 3001 tokens, 64 x 64: 97 M matrix cycles of 197 M that the launch lasts; the
 // rest is barriers and the unequal shares of the causal triangle): as three launches, each with its own pre-pass and
 // scan and 240 workgroups for 512 places, the gradient took 148 us, side by side with 504 workgroups 104 us.
-template <int DK, int DV>
+template <int DK, int DV, bool BY_CHUNK>
 __global__ __launch_bounds__(256) void f32_bwd_sweep_kernel(const float* __restrict__ Q, const float* __restrict__ K,
                                                            const float* __restrict__ V, const float* __restrict__ dO,
                                                            float* __restrict__ dQ, float* __restrict__ dK,
@@ -573,13 +588,13 @@ __global__ __launch_bounds__(256) void f32_bwd_sweep_kernel(const float* __restr
     const int z = blockIdx.z;
     const float* S1 = S0 != nullptr ? S0 + array_stride : nullptr;
     if constexpr (DK == DV) {
-        f32_sweep_body<C, DK, DV>(z == 0 ? dO : z == 1 ? V : K, z == 0 ? V : z == 1 ? dO : Q, z == 0 ? K : z == 1 ? Q : dO,
+        f32_sweep_body<C, DK, DV, BY_CHUNK>(z == 0 ? dO : z == 1 ? V : K, z == 0 ? V : z == 1 ? dO : Q, z == 0 ? K : z == 1 ? Q : dO,
                                   z == 0 ? dQ : z == 1 ? dK : dV, z == 0 ? S0 : S1, N, seg_len, n_seg, z != 0, z == 1, lds);
     } else if (z < 2) {
-        f32_sweep_body<C, DV, DK>(z == 0 ? dO : V, z == 0 ? V : dO, z == 0 ? K : Q, z == 0 ? dQ : dK, z == 0 ? S0 : S1, N,
+        f32_sweep_body<C, DV, DK, BY_CHUNK>(z == 0 ? dO : V, z == 0 ? V : dO, z == 0 ? K : Q, z == 0 ? dQ : dK, z == 0 ? S0 : S1, N,
                                   seg_len, n_seg, z != 0, z == 1, lds);
     } else {
-        f32_sweep_body<C, DK, DV>(K, Q, dO, dV, S1, N, seg_len, n_seg, true, false, lds);
+        f32_sweep_body<C, DK, DV, BY_CHUNK>(K, Q, dO, dV, S1, N, seg_len, n_seg, true, false, lds);
     }
 }
 
@@ -605,26 +620,34 @@ static hipError_t f32_fwd_impl(const float* Q, const float* K, const float* V, f
     return hipGetLastError();
 }
 
-template <int DK, int DV>
-static hipError_t f32_bwd_impl(const float* Q, const float* K, const float* V, const float* dO, float* dQ, float* dK,
-                               float* dV, long BH, int N, const Plan& plan, float* ws, hipStream_t st)
+template <int DK, int DV, bool BY_CHUNK>
+static hipError_t f32_bwd_launches(const float* Q, const float* K, const float* V, const float* dO, float* dQ, float* dK,
+                                   float* dV, long BH, int N, const Plan& plan, float* ws, hipStream_t st)
 {
     hipError_t e;
     const size_t stride = (size_t)BH * plan.n_seg * DK * DV;
     if (plan.n_seg > 1) {
         {
             ProfScope prof(KID_SEG_STATE_F32, st);
-            hipLaunchKernelGGL((f32_bwd_seg_state_kernel<DK, DV>), dim3((unsigned)BH, plan.n_seg, 2), dim3(256), 0, st, Q, K,
-                               V, dO, ws, stride, N, plan.seg_len, plan.n_seg);
+            hipLaunchKernelGGL((f32_bwd_seg_state_kernel<DK, DV, BY_CHUNK>), dim3((unsigned)BH, plan.n_seg, 2), dim3(256), 0,
+                               st, Q, K, V, dO, ws, stride, N, plan.seg_len, plan.n_seg);
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
         const int modes[2] = {SCAN_EXCL_PREFIX, SCAN_EXCL_PREFIX};
         if ((e = scan_states(ws, stride, 2, modes, nullptr, 0, BH, plan.n_seg, DK * DV, st)) != hipSuccess) return e;
     }
     ProfScope prof(KID_SWEEP_F32, st);
-    hipLaunchKernelGGL((f32_bwd_sweep_kernel<DK, DV>), dim3((unsigned)BH, plan.n_seg, 3), dim3(256), 0, st, Q, K, V, dO, dQ,
-                       dK, dV, plan.n_seg > 1 ? ws : nullptr, stride, N, plan.seg_len, plan.n_seg);
+    hipLaunchKernelGGL((f32_bwd_sweep_kernel<DK, DV, BY_CHUNK>), dim3((unsigned)BH, plan.n_seg, 3), dim3(256), 0, st, Q, K,
+                       V, dO, dQ, dK, dV, plan.n_seg > 1 ? ws : nullptr, stride, N, plan.seg_len, plan.n_seg);
     return hipGetLastError();
+}
+
+template <int DK, int DV>
+static hipError_t f32_bwd_impl(const float* Q, const float* K, const float* V, const float* dO, float* dQ, float* dK,
+                               float* dV, long BH, int N, const Plan& plan, float* ws, hipStream_t st)
+{
+    return plan.by_chunk ? f32_bwd_launches<DK, DV, true>(Q, K, V, dO, dQ, dK, dV, BH, N, plan, ws, st)
+                         : f32_bwd_launches<DK, DV, false>(Q, K, V, dO, dQ, dK, dV, BH, N, plan, ws, st);
 }
 
 #define CHELA_F32_DIMS(F_, ...)                                                                                        \

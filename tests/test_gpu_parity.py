@@ -454,6 +454,27 @@ def test_f32_backward_split_where_one_segment_would_fill_the_gpu(shape):
         _check(name, g[:, heads], r, "f32")
 
 
+@pytest.mark.parametrize("shape", [(24, 3001, 64), (32, 2048, 64), (8, 777, 128)])
+def test_f32_backward_running_sums_keep_their_accuracy(shape):
+    # segments longer than the forward's: a chunk's C tokens are summed up first and then added to the running sum.
+    # Sums of n steps of equal size, each rounded (twice in a matrix instruction of two tokens), are off by about
+    # 0.58 u sqrt(n / 2) of the result, u = 2^-24: n = C / 2 in a chunk, N / C over the chunks, (d + C) / 2 in an output;
+    # a quarter on top.  In one chain over N / 2 steps: 5.2, 5.1 and 3.6e-7 here.
+    BH, N, d = shape
+    C = 32 if d == 128 else 64
+    bound = 1.25 * 0.58 * 2.0 ** -24 * (C / 4 + N / C / 2 + (d + C) / 4) ** 0.5
+    w = _small("f32", N=N, B=1, H=BH, dk=d, dv=d, seed=900 + BH)
+    x = make_inputs(w)
+    dev = _dev(x)
+    got = binding.chela_linattn_bwd(dev["Q"], dev["K"], dev["V"], dev["dO"])
+    heads = [0, BH // 2, BH - 1]
+    refs = oracle.bwd_recurrent(*(to_f64_numpy(x[n][:, heads]) for n in ("Q", "K", "V", "dO")))
+    for name, g, r in zip(("dQ", "dK", "dV"), got, refs):
+        err = oracle.rel_l2(to_f64_numpy(g[:, heads]), r)
+        print("%s %s: %.3g (bound %.3g)" % (name, shape, err, bound), flush=True)
+        assert err <= bound, (name, err)
+
+
 def test_two_streams_with_a_scratch_buffer_each():
     # calls that overlap in time on two streams, each enqueued while its own buffer is the one in force
     wa, wb = _small("bf16", N=5000, B=2, H=3, seed=41), _small("bf16", N=7000, B=1, H=5, seed=42)
