@@ -979,20 +979,12 @@ int chela_shortlong_conv_fwd_f32(const void* X, const float* w_short, int m, con
     return shortlong_common(X, w_short, m, spectrum, Y, B, d, L, CHELA_DTYPE_F32, stream);
 }
 
-static size_t conv_bwd_ws_bytes(int B, int d, int L, int dtype, bool has_short)
-{
-    if (B <= 0 || d <= 0 || L <= 0) return 0;
-    const size_t acc = conv_bwd_acc_floats(B, d, L, dtype == CHELA_DTYPE_BF16) * sizeof(float);      // running sums of the long-kernel gradient
-    if (!has_short) return acc;
-    const size_t n = (size_t)B * d * L, tiles = ((size_t)L + 2047) / 2048;
-    (void)dtype;
-    return acc + n * sizeof(float) + (size_t)B * d * tiles * 32 * sizeof(float);
-}
-
+// (the query does not know the tap count: it answers for the short kernels that take the most)
 size_t chela_shortlong_conv_bwd_workspace_bytes(int B, int d, int L, int has_short_kernel, int dtype)
 {
     if (dtype != CHELA_DTYPE_BF16 && dtype != CHELA_DTYPE_F32) return 0;
-    return conv_bwd_ws_bytes(B, d, L, dtype, has_short_kernel != 0);
+    if (B <= 0 || d <= 0 || L <= 0) return 0;
+    return conv_bwd_ws_floats(B, d, L, has_short_kernel != 0 ? kConvMaxTaps : 0, dtype == CHELA_DTYPE_BF16) * sizeof(float);
 }
 
 static int shortlong_bwd_common(const void* X, const float* w_short, int m, const void* spectrum, const void* dZ,
@@ -1028,7 +1020,7 @@ static int shortlong_bwd_common(const void* X, const float* w_short, int m, cons
         for (int o2 = o + 1; o2 < 3; ++o2) if (overlap(out[o], out[o2])) return CHELA_ERR_ALIASING;
     }
     float* ws = nullptr;
-    int rc = get_workspace(conv_bwd_ws_bytes(B, d, L, dtype, w_short != nullptr), stream, &ws);
+    int rc = get_workspace(conv_bwd_ws_floats(B, d, L, w_short ? m : 0, dtype == CHELA_DTYPE_BF16) * sizeof(float), stream, &ws);
     if (rc != CHELA_OK) return rc;
     return launch_shortlong_conv_bwd(X, w_short, m, spectrum, dZ, dX, d_w_short, d_k_long, ws, B, d, L,
                                      dtype == CHELA_DTYPE_BF16 ? 0 : 1, st) == hipSuccess ? CHELA_OK : CHELA_ERR_HIP;

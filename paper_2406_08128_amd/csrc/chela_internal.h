@@ -153,9 +153,9 @@ inline size_t conv_pairs_bytes(int d, int L)       // the pairs: where the matri
 hipError_t launch_shortlong_conv(const void* X, const float* w_short, int m, const void* Kf, void* Y, long BD, int d,
                                  int L, int dtype, hipStream_t st);
 // Gradient: dX [B][d][L] (I/O dtype), dw [d][m] (only with a short kernel, m <= 32), dk [d][L] fp32.
-// ws: conv_bwd_acc_floats(B, d, L) floats (running sums of the long-kernel gradient: at the largest transform size
-// they no longer fit the registers of 1024 threads, and workgroups that share a channel leave their shares there), then, with a short kernel, B*d*L floats (dV) and the workgroups' tap
-// sums.
+// ws: conv_bwd_ws_floats() floats: conv_bwd_acc_floats() (running sums of the long-kernel gradient: at the largest transform
+// size they no longer fit the registers of 1024 threads, and workgroups that share a channel leave their shares there), then,
+// with a short kernel, B*d*L floats (dV; not where the short stage is fused) and the workgroups' tap sums.
 // Workgroups that share a channel in the long-stage gradient kernel (each takes every G-th sequence): more than one
 // when the channels alone would leave the GPU underfilled.
 constexpr int kConvMxMaxWgs = 256;       // workgroups of the matrix-core gradient kernel at most
@@ -179,6 +179,18 @@ inline size_t conv_bwd_acc_floats(int B, int d, int L, bool bf16_io)
     // pairs per workgroup; sized for either kernel, whichever runs)
     const size_t mx = (bf16_io && M >= 16384 && (L & 7) == 0) ? (size_t)kConvMxMaxWgs * 32768 : 0;
     return pairs > mx ? pairs : mx;
+}
+// The short stage's gradient inside the long stage's kernel: its tap sums fit kConvFuseTaps rows of LDS, and a sequence of
+// one transform of up to 4096 points leaves dV in registers.
+constexpr int kConvFuseTaps = 16, kConvMaxTaps = 32;
+inline bool conv_bwd_fused(int m, int L) { return m > 0 && m <= kConvFuseTaps && L <= 4096; }
+// m: taps of the short kernel, 0 for none
+inline size_t conv_bwd_ws_floats(int B, int d, int L, int m, bool bf16_io)
+{
+    const size_t acc = conv_bwd_acc_floats(B, d, L, bf16_io);
+    if (m == 0) return acc;
+    if (conv_bwd_fused(m, L)) return acc + (size_t)d * conv_bwd_groups(B, d, L) * kConvMaxTaps;
+    return acc + (size_t)B * d * L + (size_t)B * d * (((size_t)L + 2047) / 2048) * kConvMaxTaps;
 }
 hipError_t launch_shortlong_conv_bwd(const void* X, const float* w_short, int m, const void* Kf, const void* dZ,
                                      void* dX, float* dw, float* dk, float* ws_dV, int B, int d, int L, int dtype,

@@ -827,7 +827,7 @@ void shortlong_conv_kernel(const IN* __restrict__ X,
 // in one 475.  bf16 I/O asks for three workgroups per compute unit (168 registers, 4 or 5 values spilled; training step 645 us
 // against 707 with two and nothing spilled), fp32 I/O, which holds twice the fetched words, for two (234 against 262 us at
 // 512 x 8 x 4000).
-constexpr int kFuseTaps = 16, kShortMaxTaps = 32;
+constexpr int kFuseTaps = kConvFuseTaps, kShortMaxTaps = kConvMaxTaps;
 
 template <int M, typename IO, typename DVT, bool SPLIT, bool SHORT>
 __global__ __launch_bounds__(conv_threads(M)) __attribute__((amdgpu_waves_per_eu(M == 256 || M == 16384 ? 4 : sizeof(IO) == 2 ? 3 : 2)))
@@ -1749,8 +1749,7 @@ static hipError_t conv_longbwd_dispatch(const IO* X, const float* w, int m, cons
     return hipGetLastError();
 }
 
-// ws: the running sums of the long-kernel gradient (largest transform size only), then, with a short kernel,
-// B*d*L floats (dV) and the workgroups' tap sums.
+// ws: conv_bwd_ws_floats() floats, laid out as said there.
 template <typename IO>
 static hipError_t conv_bwd_impl(const IO* X, const float* w_short, int m, const float4* Kf, const IO* dZ, IO* dX,
                                 float* dw, float* dk, float* ws, int B, int d, int L, hipStream_t st)
@@ -1766,22 +1765,22 @@ static hipError_t conv_bwd_impl(const IO* X, const float* w_short, int m, const 
         if (mx) return launch_convmx_longbwd(X, nullptr, 0, mx_spec, dZ, dX, false, dk, (float*)acc_ws, B, d, L, st);
         return conv_longbwd_dispatch<IO, IO, false>(X, nullptr, 0, Kf, dZ, dX, dk, acc_ws, nullptr, B, d, L, st);
     }
+    if (conv_bwd_fused(m, L)) {
+        const int G = conv_bwd_groups(B, d, L);                             // workgroups that share a channel (<= B)
+        e = conv_longbwd_dispatch<IO, IO, true>(X, w_short, m, Kf, dZ, dX, dk, acc_ws, ws, B, d, L, st);
+        if (e != hipSuccess) return e;
+        ProfScope prof(KID_CONV_SHORT_BWD, st);
+        hipLaunchKernelGGL(shortconv_dw_kernel, dim3(d), dim3(64), 0, st, ws, dw, m, G);
+        return hipGetLastError();
+    }
     float* ws_dV = ws;
+    float* ws_part = ws + (size_t)BD * L;                                   // [d][n_share][32] (room for [d][B * tiles][32])
     // workgroups per channel: (batch entry, strip) or (batch entry, tile) pairs over what one takes
     const bool strips = m <= 16;
     const long n_items = (long)B * (strips ? (L + strip_steps(m) - 1) / strip_steps(m) : (L + kShortTile - 1) / kShortTile);
     const long per_wg = strips ? 4 * kStripsPerWave : kShortTilesPerWg;
     const int n_share = (int)((n_items + per_wg - 1) / per_wg);
     if ((long)d * n_share > 0x7fffffffL || n_items > 0x7ffffff0L) return hipErrorInvalidValue;
-    float* ws_part = ws + (size_t)BD * L;                                   // [d][n_share][32] (room for [d][B * tiles][32])
-    if (m <= kFuseTaps && L <= 4096) {
-        const int G = conv_bwd_groups(B, d, L);                             // workgroups that share a channel (<= B)
-        e = conv_longbwd_dispatch<IO, IO, true>(X, w_short, m, Kf, dZ, dX, dk, acc_ws, ws_part, B, d, L, st);
-        if (e != hipSuccess) return e;
-        ProfScope prof(KID_CONV_SHORT_BWD, st);
-        hipLaunchKernelGGL(shortconv_dw_kernel, dim3(d), dim3(64), 0, st, ws_part, dw, m, G);
-        return hipGetLastError();
-    }
     e = mx ? launch_convmx_longbwd(X, w_short, m, mx_spec, dZ, ws_dV, true, dk, (float*)acc_ws, B, d, L, st)
            : conv_longbwd_dispatch<IO, float, false>(X, w_short, m, Kf, dZ, ws_dV, dk, acc_ws, nullptr, B, d, L, st);
     if (e != hipSuccess) return e;

@@ -1068,6 +1068,31 @@ def test_conv_gradient_short_stage_in_and_out_of_the_transform_kernel(Lm, dtype)
     _run_conv_bwd_case(3, 2, Lm[0], Lm[1], dtype, seed=Lm[0] + Lm[1])
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [(3, 2, 200, 9), (2, 700, 1024, 3), (5, 3, 4096, 16)])
+def test_conv_gradient_inside_the_transform_kernel_takes_no_room_for_dv(shape, dtype):
+    # the running sums, and 32 tap sums per sequence at most: a buffer of that size, with nothing written behind it, is
+    # enough up to 16 taps; a longer short kernel, whose dV does pass through memory, is refused
+    B, d, L, m = shape
+    x = _dev(make_conv_inputs(B, d, L, m, L + 51, dtype))
+    dZ = torch.randn(B, d, L, device="cuda").to(x["X"].dtype)
+    spec = binding.chela_longconv_spectrum(x["k_long"])
+    ref = binding.chela_shortlong_conv_bwd(x["X"], x["w_short"], spec, dZ)
+    need = binding.lib().chela_shortlong_conv_bwd_workspace_bytes(B, d, L, 0, 0 if dtype == "bf16" else 1) + B * d * 32 * 4
+    buf = torch.full((need + 4096,), 0x5a, dtype=torch.uint8, device="cuda")
+    wide = torch.full((d, 17), 1.0 / 17, device="cuda")
+    try:
+        binding.chela_set_workspace(buf[:need])
+        got = binding.chela_shortlong_conv_bwd(x["X"], x["w_short"], spec, dZ)
+        with pytest.raises(binding.ChelaError) as ei:
+            binding.chela_shortlong_conv_bwd(x["X"], wide, spec, dZ)
+        assert ei.value.status == -7
+    finally:
+        binding.chela_set_workspace(None)
+    assert all(torch.equal(a, b) for a, b in zip(got, ref))
+    assert bool((buf[need:] == 0x5a).all())
+
+
 def _run_conv_bwd_case(B, d, L, m, dtype, seed, short=True):
     print("\nconv bwd B%d d%d L%d m%d %s short=%s" % (B, d, L, m, dtype, short), flush=True)
     x = make_conv_inputs(B, d, L, m, seed, dtype)
