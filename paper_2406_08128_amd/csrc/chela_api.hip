@@ -126,7 +126,9 @@ Plan make_plan(long BH, int N, int dk, int dv, int chunk, int dtype, bool is_bwd
     p.seg_len = (int)(cps * chunk);
     p.n_seg = (int)((n_chunks + cps - 1) / cps);
     const int n_states = (dtype == CHELA_DTYPE_BF16 && is_bwd) ? 2 : 1;   // (the fp32 backward: make_f32_bwd_plan)
-    // a carried-in state goes through the scan even when there is a single segment
+    // (with a state carried in the forward's single segment touches no scratch -- the sweep starts from S_in -- and its
+    // folded segments need no scan; the size asked for and the price of a split above are those of the general flow, in
+    // which the scan runs: in place, with Eq. 11-12 or the [B,N,H,d] layout, and in the backward)
     if (p.n_seg > 1 || stateful) {
         p.ckpt_every = 0;
         p.ws_bytes = (size_t)BH * p.n_seg * p.state_elems * sizeof(float) * n_states;

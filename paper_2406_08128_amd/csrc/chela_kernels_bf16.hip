@@ -1416,7 +1416,8 @@ __device__ __forceinline__ size_t row_offset(bool nh, long bh, int H, int N, int
 // NT: the two tensors are not read again after this kernel (streaming hint on their loads).
 // NT1: the hint on the second pair's loads only (see bwd_impl).
 // SEED: args.seed is used.  A variant of its own: as a branch of the common kernel it made stateless calls, which never
-// take it, half a per cent slower (8 x 12 heads, 4096 tokens, 64 x 128, forward + backward: 241.8 against 240.8 us).
+// take it, half a per cent slower (8 x 12 heads, 4096 tokens, 64 x 128, forward + backward, in turn on one card, twice:
+// 246.1 against 244.7 us, runs of one side within 0.1 %; 64 x 64 shapes level).
 template <int DA, int DB, int AFF, bool NH, bool NT, bool NT1 = false, bool SEED = false>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu((DA == 64 && DB == 64) ? (AFF == 0 ? 6 : 5) : 1)))
 void bf16_seg_state_kernel(SegStateArgs args, int N, int seg_len, int n_seg)
@@ -1641,8 +1642,8 @@ __device__ __forceinline__ void stg16(bf16* p, uint4 v)
 // Gradient: dG is nobody's input soon and always leaves with the streaming hint, so that its lines are not written
 // back out of the memory-side cache while the next kernel reads; dO, which the attention's backward reads next, does so
 // too (NT0) where the five tensors exceed that cache and its lines would be gone by then anyway.  256 heads x 3517
-// tokens (576 MB), whole training step: neither 434, dG 420, both 414 us; 48 heads x 2048 tokens (63 MB): 73.4, 72.9,
-// 74.4 us.
+// tokens (576 MB), whole training step: neither 434, dG 420, both 414 us; 48 heads x 2048 tokens (63 MB), in turn on one
+// card, three times: dG 73.7, both 75.0 us, runs of one side within 0.1 %.
 template <int DV, bool BWD, bool NT0>
 __global__ __launch_bounds__(256) void gate_norm_kernel(const bf16* __restrict__ O, const bf16* __restrict__ G,
                                                        const bf16* __restrict__ dY, bf16* __restrict__ out0,

@@ -4,12 +4,13 @@
 // owns one (batch, channel) sequence and never leaves the chip between load and store:
 //   load x, short kernel + silu  ->  real sequence v, zero-padded to N = 2M >= 2L (so that the circular product of
 //   Eq. 7 equals the causal sum), packed as M complex numbers z[n] = v[2n] + i v[2n+1]  ->  complex FFT of length M
-//   in LDS  ->  untangle to the spectrum of v, multiply by the kernel's spectrum, tangle back  ->  inverse FFT
+//   in LDS  ->  product with the kernel's spectrum, linear in the pair of packed bins (k, M - k)  ->  inverse FFT
 //   ->  y[2n], y[2n+1] = Re, Im.
 // FFT: in place, decimation in frequency forward (natural order in, digit-reversed out) and the exact inverse of
 // every pass in reverse order (digit-reversed in, natural out), so no reordering pass exists; the point-wise
 // stage addresses the spectrum through the digit reversal.  M = 4^a 16^b: an optional leading radix-4 pass, then
-// radix-16 passes with one 16-point transform per thread held in registers (two layers of radix 4).  The LDS
+// radix-16 passes with one 16-point transform per thread held in registers (four layers of radix 2, the twiddles worked
+// into the butterflies); the first pass forward and the last one back need no LDS on their outer side.  The LDS
 // array carries one complex of padding per 16, which makes the stride-1 and stride-16 passes conflict-free.
 // Arithmetic is fp32 on the vector ALU: with one kernel per channel there is no operand shared across channels
 // except the DFT matrix itself, and fp32 matrix instructions are no faster than the ALU on this chip.
@@ -824,8 +825,8 @@ void shortlong_conv_kernel(const IN* __restrict__ X,
 // dU = dV silu'(u) meets its neighbours through LDS: dX out (dV is DVT = IO dX here), the taps' sums into `part`
 // ([d][grid.y][kShortMaxTaps]).  As a kernel of its own that stage reads x again, and dV, 4 bytes a step written here and
 // read there, and works u out once more: 512 channels x 32 sequences of 4096 steps, bf16, the two kernels 527 + 150 us,
-// in one 475.  bf16 I/O asks for three workgroups per compute unit (168 registers, 4 or 5 values spilled; training step 645 us
-// against 707 with two and nothing spilled), fp32 I/O, which holds twice the fetched words, for two (234 against 262 us at
+// in one 475.  bf16 I/O asks for three workgroups per compute unit (168 registers; values spilled: 30 with shared channels, 45
+// with one workgroup per channel, at M = 1024 31 and 48; training step 645 us against 707 with two and nothing spilled), fp32 I/O, which holds twice the fetched words, for two (234 against 262 us at
 // 512 x 8 x 4000).
 constexpr int kFuseTaps = kConvFuseTaps, kShortMaxTaps = kConvMaxTaps;
 
