@@ -337,7 +337,8 @@ const char *chela_status_string(int status);
 /* CHELA_VERSION of the loaded library. */
 int chela_version(void);
 
-/* Free the internal workspace (synchronises the device).  Safe to call twice. */
+/* Free the internal workspace (synchronises the device), also what captured graphs were captured with: scratch a captured
+ * call was given otherwise stays where it is when its stream needs more.  Safe to call twice. */
 void chela_shutdown(void);
 
 #ifdef __cplusplus

@@ -295,9 +295,21 @@ static std::mutex g_mu;
 static thread_local void* t_user_ws = nullptr;
 static thread_local size_t t_user_bytes = 0;
 static constexpr int kMaxDev = 64;
-struct OwnWs { hipStream_t stream; void* ptr; size_t bytes; };
+// A captured graph holds the address it was captured with: a buffer that a captured call was given is kept, when the stream
+// needs a larger one, until chela_shutdown() (each is larger than the one before by a quarter at least, so that all of them
+// together are no more than five times the last).
+struct OwnWs { hipStream_t stream; void* ptr; size_t bytes; bool captured; std::vector<void*> kept; };
 static constexpr size_t kMaxOwnStreams = 64;    // per device
 static std::vector<OwnWs> g_own_ws[kMaxDev];
+
+// (the default stream cannot be captured)
+static bool being_captured(hipStream_t stream)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (stream == nullptr) return false;
+    if (hipStreamIsCapturing(stream, &status) != hipSuccess) { (void)hipGetLastError(); return false; }
+    return status != hipStreamCaptureStatusNone;
+}
 
 // What a call that would like `bytes` and can do with less may ask get_workspace() for: a caller-owned buffer is as large
 // as it is, and nothing can be allocated while the stream is being captured.
@@ -312,10 +324,7 @@ static size_t workspace_limit(size_t bytes, hipStream_t stream)
         for (const OwnWs& x : g_own_ws[dev]) if (x.stream == stream) { have = x.bytes; break; }
     }
     if (have >= bytes) return bytes;
-    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    const bool capturing = hipStreamIsCapturing(stream, &status) == hipSuccess && status != hipStreamCaptureStatusNone;
-    (void)hipGetLastError();
-    return capturing ? have : bytes;
+    return being_captured(stream) ? have : bytes;
 }
 
 static int get_workspace(size_t bytes, void* stream, float** out)
@@ -338,17 +347,19 @@ static int get_workspace(size_t bytes, void* stream, float** out)
         // pointer it has not launched with yet): a caller that goes through more streams than this hands in
         // buffers of its own, or calls chela_shutdown() at a quiet moment.
         if (g_own_ws[dev].size() >= kMaxOwnStreams) return CHELA_ERR_WORKSPACE;
-        g_own_ws[dev].push_back(OwnWs{(hipStream_t)stream, nullptr, 0});
+        g_own_ws[dev].push_back(OwnWs{(hipStream_t)stream, nullptr, 0, false, {}});
         w = &g_own_ws[dev].back();
     }
     if (w->bytes < bytes) {
-        if (w->ptr) { (void)hipDeviceSynchronize(); (void)hipFree(w->ptr); }
-        w->ptr = nullptr; w->bytes = 0;
+        if (w->ptr && w->captured) w->kept.push_back(w->ptr);
+        else if (w->ptr) { (void)hipDeviceSynchronize(); (void)hipFree(w->ptr); }
+        w->ptr = nullptr; w->bytes = 0; w->captured = false;
         const size_t want = bytes + bytes / 4;
         void* p = nullptr;
         if (hipMalloc(&p, want) != hipSuccess) { (void)hipGetLastError(); return CHELA_ERR_WORKSPACE; }
         w->ptr = p; w->bytes = want;
     }
+    if (!w->captured) w->captured = being_captured((hipStream_t)stream);
     *out = (float*)w->ptr;
     return CHELA_OK;
 }
@@ -1217,7 +1228,10 @@ void chela_shutdown(void)
         if (!have_cur) { have_cur = (hipGetDevice(&cur) == hipSuccess); }
         if (hipSetDevice(d) == hipSuccess) {
             (void)hipDeviceSynchronize();
-            for (OwnWs& w : g_own_ws[d]) if (w.ptr) (void)hipFree(w.ptr);
+            for (OwnWs& w : g_own_ws[d]) {
+                if (w.ptr) (void)hipFree(w.ptr);
+                for (void* p : w.kept) (void)hipFree(p);
+            }
         }
         g_own_ws[d].clear();
     }

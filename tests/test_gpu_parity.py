@@ -1591,6 +1591,40 @@ def test_f32_backward_captures_with_the_scratch_there_is(shape, eager_N):
         torch.cuda.synchronize()
 
 
+@pytest.mark.parametrize("dtype, N, warm_N, more_N", [("f32", 3001, 1200, 3001), ("bf16", 2000, 2000, 16384)])
+def test_captured_scratch_outlives_a_larger_eager_call_on_its_stream(dtype, N, warm_N, more_N):
+    # The graph holds the scratch its stream had; an eager call on that stream that needs more gets another buffer, and the
+    # first stays where it is.  (fp32: the eager call is the captured one, which would like more than there was.)
+    w = _small(dtype, N=N, B=2, H=12, seed=92)
+    x = make_inputs(w)
+    d = _dev(x)
+    refs = oracle.bwd_recurrent(*(to_f64_numpy(x[n]) for n in ("Q", "K", "V", "dO")))
+    more = _dev(make_inputs(_small(dtype, N=more_N, B=2, H=12, seed=93)))
+    outs = [torch.empty_like(d[n]) for n in ("Q", "K", "V")]
+    torch.cuda.synchronize()
+    binding.chela_shutdown()
+    s = torch.cuda.Stream()
+    warm = {n: t[:, :, :warm_N].contiguous() for n, t in d.items()}
+    torch.cuda.synchronize()
+    with torch.cuda.stream(s):
+        binding.chela_linattn_bwd(warm["Q"], warm["K"], warm["V"], warm["dO"])
+    s.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=s):
+        binding.chela_linattn_bwd(d["Q"], d["K"], d["V"], d["dO"], dQ=outs[0], dK=outs[1], dV=outs[2])
+    for rep in range(3):
+        with torch.cuda.stream(s):
+            binding.chela_linattn_bwd(more["Q"], more["K"], more["V"], more["dO"])
+        s.synchronize()
+        for t in outs:
+            t.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for name, g, r in zip(("dQ", "dK", "dV"), outs, refs):
+            _check(name, g, r, dtype)
+
+
 @pytest.mark.parametrize("shape", NC_SHAPES)
 def test_noncausal_fwd_gated(shape):
     B, H, N, dk, dv = shape
