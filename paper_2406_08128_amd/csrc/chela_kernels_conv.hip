@@ -752,9 +752,9 @@ __global__ __launch_bounds__(conv_threads(M)) void longconv_spectrum_kernel(cons
     }
 }
 
-// Bound by vector instruction issue: 1770 instructions per wave and sequence of 4096 steps (2900 before the pairs became
+// Bound by vector instruction issue: 1785 instructions per wave and sequence of 4096 steps (2900 before the pairs became
 // linear in the packed bins, their places constant offsets, the outer passes stayed in registers and the rows' ends were
-// left to buffer loads and stores), issuing 95 % of the time: 512 channels x 32 sequences, bf16, 320 -> 242 us.
+// left to buffer loads and stores), issuing 92 .. 95 % of the time: 512 channels x 32 sequences, bf16, 320 -> 207 us.
 // Workgroup g takes the sequences (b, c) = g, g + gridDim.x, ... of the B d in turn (w_short == nullptr: no short
 // kernel and no activation, the plain long convolution).  The launch holds no more workgroups than are resident
 // at once, so that the tables are built once per workgroup, a sequence's input is fetched while the inverse transform
@@ -825,7 +825,8 @@ void shortlong_conv_kernel(const IN* __restrict__ X,
 // dU = dV silu'(u) meets its neighbours through LDS: dX out (dV is DVT = IO dX here), the taps' sums into `part`
 // ([d][grid.y][kShortMaxTaps]).  As a kernel of its own that stage reads x again, and dV, 4 bytes a step written here and
 // read there, and works u out once more: 512 channels x 32 sequences of 4096 steps, bf16, the two kernels 527 + 150 us,
-// in one 475.  bf16 I/O asks for three workgroups per compute unit (168 registers; values spilled: 30 with shared channels, 45
+// in one 475, and 407 .. 416 with what came after (3080 instructions per wave and sequence, issuing 82 % of the time).
+// bf16 I/O asks for three workgroups per compute unit (168 registers; values spilled: 30 with shared channels, 45
 // with one workgroup per channel, at M = 1024 31 and 48; training step 645 us against 707 with two and nothing spilled), fp32 I/O, which holds twice the fetched words, for two (234 against 262 us at
 // 512 x 8 x 4000).
 constexpr int kFuseTaps = kConvFuseTaps, kShortMaxTaps = kConvMaxTaps;
