@@ -826,9 +826,9 @@ void shortlong_conv_kernel(const IN* __restrict__ X,
 // ([d][grid.y][kShortMaxTaps]).  As a kernel of its own that stage reads x again, and dV, 4 bytes a step written here and
 // read there, and works u out once more: 512 channels x 32 sequences of 4096 steps, bf16, the two kernels 527 + 150 us,
 // in one 475, and 407 .. 416 with what came after (3080 instructions per wave and sequence, issuing 82 % of the time).
-// bf16 I/O asks for three workgroups per compute unit (168 registers; values spilled: 30 with shared channels, 45
-// with one workgroup per channel, at M = 1024 31 and 48; training step 645 us against 707 with two and nothing spilled), fp32 I/O, which holds twice the fetched words, for two (234 against 262 us at
-// 512 x 8 x 4000).
+// bf16 I/O asks for three workgroups per compute unit (168 registers; values spilled: 30 with shared channels, 45 with one
+// workgroup per channel, at M = 1024 31 and 48; training step 645 us against 707 with two and nothing spilled), fp32 I/O,
+// which holds twice the fetched words, for two (234 against 262 us at 512 x 8 x 4000).
 constexpr int kFuseTaps = kConvFuseTaps, kShortMaxTaps = kConvMaxTaps;
 
 template <int M, typename IO, typename DVT, bool SPLIT, bool SHORT>
@@ -1365,10 +1365,10 @@ __global__ __launch_bounds__(64) void shortconv_dw_kernel(const float* __restric
 // The work per sequence grows with nb (nb + 1) / 2 block pairs, against nb log nb for one long transform held in
 // memory: this path is here so that no length is refused, not to be the fastest way to convolve a million steps.
 constexpr int kBlkM = 16384;                 // transform length and block length (steps)
-// Threads per workgroup of the blocked kernels.  1024 leave each thread 128 registers, which the 36 accumulators of the
-// forward kernel overflow (40-70 spilled registers); 512 threads with 256 registers each spill nothing and were
-// measured slower all the same (2.39 against 1.94 ms at B1 d2048 L65536): sixteen waves hide the transforms' LDS
-// latencies better than eight.
+// Threads per workgroup of the blocked kernels.  1024 leave each thread 128 registers, which hold the accumulators since
+// the bin pairs' places are no longer kept across the transforms (up to 3 values spilled).  When they did not (40 to 70
+// spilled), 512 threads with 256 registers each were slower all the same (2.39 against 1.94 ms at B1 d2048 L65536; now
+// 1.15): sixteen waves hide the transforms' LDS latencies better than eight.
 constexpr int kBlkT = conv_threads(kBlkM);
 
 // Spectra G_m of the blocks of the long kernel; one workgroup per (channel, block).
