@@ -351,12 +351,17 @@ static int get_workspace(size_t bytes, void* stream, float** out)
         w = &g_own_ws[dev].back();
     }
     if (w->bytes < bytes) {
-        if (w->ptr && w->captured) w->kept.push_back(w->ptr);
-        else if (w->ptr) { (void)hipDeviceSynchronize(); (void)hipFree(w->ptr); }
-        w->ptr = nullptr; w->bytes = 0; w->captured = false;
+        if (w->ptr && !w->captured) {
+            (void)hipDeviceSynchronize();
+            (void)hipFree(w->ptr);
+            w->ptr = nullptr; w->bytes = 0;
+        }
         const size_t want = bytes + bytes / 4;
         void* p = nullptr;
+        // (refused behind a captured call: its buffer is still this stream's scratch, for calls that do with less)
         if (hipMalloc(&p, want) != hipSuccess) { (void)hipGetLastError(); return CHELA_ERR_WORKSPACE; }
+        if (w->ptr) w->kept.push_back(w->ptr);
+        w->captured = false;
         w->ptr = p; w->bytes = want;
     }
     if (!w->captured) w->captured = being_captured((hipStream_t)stream);

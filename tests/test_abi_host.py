@@ -381,6 +381,93 @@ def test_caller_scratch_is_per_host_thread(L):
     assert L.chela_get_workspace(ctypes.byref(p), ctypes.byref(n)) == 0 and p.value is None and n.value == 0
 
 
+# Stands in for the HIP runtime in a child process without a GPU: memory is counted, launches do nothing.
+FAKE_HIP = r"""
+#include <stddef.h>
+#include <stdlib.h>
+static size_t live, room = (size_t)1 << 40; static int capturing, mallocs;
+static struct { void *p; size_t n; } a[64];
+void fake_set(size_t r, int c) { room = r; capturing = c; }
+size_t fake_live(void) { return live; }
+int fake_mallocs(void) { return mallocs; }
+int hipGetDevice(int *d) { *d = 0; return 0; }
+int hipSetDevice(int d) { (void)d; return 0; }
+int hipDeviceSynchronize(void) { return 0; }
+int hipGetLastError(void) { return 0; }
+int hipStreamIsCapturing(void *s, int *c) { (void)s; *c = capturing; return 0; }
+int hipLaunchKernel(void) { return 0; }
+int hipMalloc(void **p, size_t n)
+{
+    if (capturing || live + n > room) return 2;
+    for (int i = 0; i < 64; ++i) if (!a[i].p) { *p = a[i].p = aligned_alloc(256, 256); a[i].n = n; live += n; ++mallocs; return 0; }
+    return 2;
+}
+int hipFree(void *p)
+{
+    for (int i = 0; i < 64; ++i) if (a[i].p == p) { live -= a[i].n; a[i].p = 0; free(p); return 0; }
+    return 1;
+}
+"""
+
+SCRATCH_CHILD = r"""
+import ctypes, sys
+fake = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)          # in front of the library's own dependencies
+L = ctypes.CDLL(sys.argv[2])
+fake.fake_live.restype = ctypes.c_size_t
+fake.fake_set.argtypes = [ctypes.c_size_t, ctypes.c_int]
+L.chela_linattn_workspace_bytes.restype = ctypes.c_size_t
+P, I = ctypes.c_void_p, ctypes.c_int
+L.chela_linattn_bwd_f32.argtypes = [P] * 7 + [I] * 6 + [P]
+L.chela_linattn_fwd_f32.argtypes = [P] * 4 + [I] * 6 + [P]
+ROOM, SHAPE = 1 << 40, (1, 48, 65536, 64, 64, 64)
+T = [0x10000 + (i << 40) for i in range(7)]
+fwd = lambda stream: L.chela_linattn_fwd_f32(*T[:4], *SHAPE, stream)
+bwd = lambda stream: L.chela_linattn_bwd_f32(*T, *SHAPE, stream)     # would like more than the forward, does with as much
+small, large = (L.chela_linattn_workspace_bytes(*SHAPE, d, 1) for d in (0, 1))
+assert 0 < small and 2 * small < large
+for stream in (0x1000, 0x2000):
+    before = fake.fake_live()
+    assert fwd(stream) == 0
+    first = fake.fake_live() - before
+    captured = stream == 0x1000
+    if captured:                                    # a graph is captured with the stream's scratch
+        fake.fake_set(ROOM, 1)
+        assert fwd(stream) == 0 and bwd(stream) == 0
+    n = fake.fake_mallocs()
+    fake.fake_set(fake.fake_live() + first, 0)      # no room for the backward's full split
+    rc = [bwd(stream) for _ in range(4)] + [fwd(stream)]
+    print(hex(stream), "refused growth", rc, first, fake.fake_live() - before, fake.fake_mallocs() - n, flush=True)
+    assert rc == [0] * 5
+    if captured:
+        assert fake.fake_live() - before == first and fake.fake_mallocs() == n
+    fake.fake_set(ROOM, 0)
+    assert bwd(stream) == 0                         # room again: the full split, and the graph's buffer stays
+    assert fake.fake_live() - before >= large + (first if captured else 0)
+L.chela_shutdown()
+assert fake.fake_live() == 0
+print("ok")
+"""
+
+
+def test_scratch_of_a_captured_call_survives_a_refused_growth(L, tmp_path):
+    # A buffer that a captured call was given stays when its stream needs more.  Where the larger one is refused, it is still
+    # the stream's scratch: the next calls find it, and nothing piles up behind refused calls.
+    import shutil
+    import subprocess
+    import sys
+    from paper_2406_08128_amd import binding
+    cc = shutil.which("gcc") or shutil.which("cc")
+    if cc is None:
+        pytest.skip("no C compiler")
+    src, lib = tmp_path / "fake_hip.c", tmp_path / "libfake_hip.so"
+    src.write_text(FAKE_HIP)
+    subprocess.run([cc, "-shared", "-fPIC", "-O1", "-o", str(lib), str(src)], check=True)
+    chela = os.environ.get("CHELA_LIB") or binding.LIB_PATH
+    r = subprocess.run([sys.executable, "-c", SCRATCH_CHILD, str(lib), chela], stdout=subprocess.PIPE,
+                       stderr=subprocess.STDOUT, text=True, timeout=120)
+    assert r.returncode == 0 and r.stdout.splitlines()[-1] == "ok", r.stdout
+
+
 def test_set_workspace_alignment(L):
     assert L.chela_set_workspace(ctypes.c_void_p(0x1001), 1024) == -5
     assert L.chela_set_workspace(None, 0) == 0
