@@ -141,10 +141,11 @@ bool convmx_applies(int L, int dtype);
 size_t convmx_spectrum_bytes(int d, int L);
 hipError_t launch_convmx_fwd(const void* X, const float* w_short, int m, const void* extra, void* Y, int B, int d, int L,
                              hipStream_t st);
-// The two long-stage gradients (dV: fp32 for the short-stage kernel, or dX itself in bf16 when there is no short stage;
-// Hs: 32768 words of scratch for each of up to kConvMxMaxWgs workgroups).
+// The two long-stage gradients (dV: fp32 for the short-stage kernel, or dX itself in bf16 when there is no short stage).
+// part: room for max_share slices [d][L] of dk, for channels whose sequences are shared out to several workgroups.
 hipError_t launch_convmx_longbwd(const void* X, const float* w_short, int m, const void* extra, const void* dZ, void* dV,
-                                 bool dv_is_f32, float* dk, float* Hs, int B, int d, int L, hipStream_t st);
+                                 bool dv_is_f32, float* dk, float* part, int max_share, int B, int d, int L,
+                                 hipStream_t st);
 inline size_t conv_pairs_bytes(int d, int L)       // the pairs: where the matrix-core copy starts
 {
     const int M = conv_fft_size(L);
@@ -158,7 +159,6 @@ hipError_t launch_shortlong_conv(const void* X, const float* w_short, int m, con
 // with a short kernel, B*d*L floats (dV; not where the short stage is fused) and the workgroups' tap sums.
 // Workgroups that share a channel in the long-stage gradient kernel (each takes every G-th sequence): more than one
 // when the channels alone would leave the GPU underfilled.
-constexpr int kConvMxMaxWgs = 256;       // workgroups of the matrix-core gradient kernel at most
 inline int conv_bwd_groups(int B, int d, int L)
 {
     const int M = conv_fft_size(L);
@@ -175,9 +175,9 @@ inline size_t conv_bwd_acc_floats(int B, int d, int L, bool bf16_io)
     if (conv_blocks(L)) return conv_blocked_spectrum_bytes(d, L) / sizeof(float);    // one sum per channel and block distance
     const int M = conv_fft_size(L), G = conv_bwd_groups(B, d, L);
     const size_t pairs = (M >= 16384 || G > 1) ? (size_t)G * d * (M / 2 + 1) * 4 : 0;
-    // (the matrix-core kernel -- bf16 I/O, 4096 < L <= 16384, L a multiple of 8 -- parks one spectrum of half-precision
-    // pairs per workgroup; sized for either kernel, whichever runs)
-    const size_t mx = (bf16_io && M >= 16384 && (L & 7) == 0) ? (size_t)kConvMxMaxWgs * 32768 : 0;
+    // (the matrix-core kernel -- bf16 I/O, 4096 < L <= 16384, L a multiple of 8 -- keeps slices of dk here instead, [d][L] each:
+    // sized for either kernel, whichever runs, and for 256 workgroups' slices at least)
+    const size_t mx = (bf16_io && M >= 16384 && (L & 7) == 0) ? (size_t)256 * 32768 : 0;
     return pairs > mx ? pairs : mx;
 }
 // The short stage's gradient inside the long stage's kernel: its tap sums fit kConvFuseTaps rows of LDS, and a sequence of

@@ -15,6 +15,7 @@
 // Arithmetic is fp32 on the vector ALU: with one kernel per channel there is no operand shared across channels
 // except the DFT matrix itself, and fp32 matrix instructions are no faster than the ALU on this chip.
 #include "chela_internal.h"
+#include <algorithm>
 #include <cfloat>
 #include <cstdlib>
 
@@ -191,9 +192,11 @@ __device__ __forceinline__ void pass16(cplx* a, const float4* tw, int tid)
 // registers into a[], and the way back, of which only the first M/2 results are wanted, into registers again: the first
 // pass forward and the last one back never go through LDS.  A __syncthreads() separates the passes; the caller
 // synchronises before and after.
-template <int M, int T>
-__device__ __forceinline__ void fft_forward(const cplx (&z)[M / T / 2], cplx* a, const float4* tw, int tid)
+// FULL (M = 16384): z[n] is given for all n = tid + T i < M.
+template <int M, int T, bool FULL = false>
+__device__ __forceinline__ void fft_forward(const cplx (&z)[FULL ? M / T : M / T / 2], cplx* a, const float4* tw, int tid)
 {
+    static_assert(!FULL || conv_lead4(M), "the leading radix-4 pass only");
     if constexpr (M == 256) {               // (16 of a wave's threads work in a pass: the input is dealt out again)
 #pragma unroll
         for (int i = 0; i < M / T / 2; ++i) a[conv_pad(tid + T * i)] = z[i];
@@ -206,7 +209,19 @@ __device__ __forceinline__ void fft_forward(const cplx (&z)[M / T / 2], cplx* a,
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 cplx* p0 = a + conv_pad(tid + T * j);
-                const cplx v0 = z[j], v1 = z[j + 4], r = mul_neg_i(v1);
+                cplx v0 = z[j], v1 = z[j + 4], r = mul_neg_i(v1);
+                if constexpr (FULL) {
+                    const cplx v2 = z[j + 8], v3 = z[j + 12];
+                    r = mul_neg_i(csub(v1, v3));
+                    v1 = cadd(v1, v3);
+                    const cplx e = csub(v0, v2);
+                    v0 = cadd(v0, v2);
+                    p0[sp] = cadd(e, r);
+                    p0[3 * sp] = csub(e, r);
+                    p0[0] = cadd(v0, v1);
+                    p0[2 * sp] = csub(v0, v1);
+                    continue;
+                }
                 p0[0] = cadd(v0, v1);
                 p0[sp] = cadd(v0, r);
                 p0[2 * sp] = csub(v0, v1);
@@ -650,12 +665,10 @@ __device__ __forceinline__ float quad_sum(float v)
 __device__ __forceinline__ int fresh(int tid) { asm volatile("" : "+v"(tid)); return tid; }
 
 // Kernel spectrum of one channel: the entries of the M/2 pairs in pair order (the buffer has room for one more).
-// MX (M = 16384): also the copy that the matrix-core kernels read, bin k = k1 + 32 k2 + 1024 k3 of the 32768-point
-// transform, divided by 4 |k|_1, as half-precision (re, im) words, stored where the lane that holds it after their forward
-// passes will look: word ((k1 * 4 + s) * 64 + lane) * 4 + i with lane = k2 + 32 h and k3 = 8 s + 4 h + i (the upper half of
-// the bins are the conjugates of the lower); scale[c] = 4 |k|_1 (both zero where 0.25 / |k|_1 is no finite number, below
-// 7.4e-40).  The words change order through LDS: a kernel of its own
-// that gathered them from the pairs in memory took 77 us for 768 channels (the pairs alone 51); together: 63.
+// MX (M = 16384): also the copy that the matrix-core kernels read, the bins at exp(-2 pi i (k + 1/4) / M) (a transform of its
+// own, of the sequence turned by exp(-2 pi i n / (4 M))), divided by 4 |k|_1, as half-precision (re, im) words, stored where
+// the lane that holds bin k = k1 + 16 k2 + 512 k3 will look: word ((k1 * 4 + a) * 64 + lane) * 4 + b with lane = k2 + 32 h and
+// k3 = 8 a + 4 h + b; scale[c] = 4 |k|_1 (both zero where 0.25 / |k|_1 is no finite number, below 7.4e-40).
 template <int M, bool MX>
 __global__ __launch_bounds__(conv_threads(M)) void longconv_spectrum_kernel(const float* __restrict__ k,
                                                                            float4* __restrict__ Kf,
@@ -702,50 +715,40 @@ __global__ __launch_bounds__(conv_threads(M)) void longconv_spectrum_kernel(cons
         v[1] = (_Float16)(im * inv);
         return __builtin_bit_cast(unsigned, v);
     };
-    unsigned h1[MX ? NP : 1], h2[MX ? NP : 1], hm = 0;          // K[k], K[M - k]; K[M/2]
     float4* out = Kf + c * (long)(M / 2 + 1);
     const PairPos<M, T> pos(tid);
     const PairTwiddle<M, T> pw(tid);
     cplx w = pw.first;
 #pragma unroll
     for (int i = 0; i < NP; ++i) {
-        const float4 e = pair_kernel(a[pos.first(i)], conj(a[pos.second(i)]), w, i == 0 && tid == 0);
-        out[tid + T * i] = e;
-        if constexpr (MX) {
-            if (i == 0 && tid == 0) {
-                h1[i] = half2(e.x + e.y, 0.f);
-                h2[i] = half2(e.x - e.y, 0.f);
-                hm = half2(e.z, e.w);
-            } else {
-                h1[i] = half2(e.x + e.z, e.y + e.w);
-                h2[i] = half2(e.x - e.z, e.w - e.y);
-            }
-        }
+        out[tid + T * i] = pair_kernel(a[pos.first(i)], conj(a[pos.second(i)]), w, i == 0 && tid == 0);
         w = cmul(w, PairTwiddle<M, T>::step);
     }
     if constexpr (MX) {
-        // (padded so that neither the writers, 128 bins from lane to lane, nor the readers, 32, share banks)
-        auto at = [](int kk) __attribute__((always_inline)) { return kk + (kk >> 5) + (kk >> 7); };
-        unsigned* H = reinterpret_cast<unsigned*>(lds);
-        __syncthreads();                                            // a[] has been read out
+        // steps tid + T i this time, turned by exp(-2 pi i (tid + T i) / (4 M)), T i / (4 M) = i / 64
+        cplx z2[M / T];
+        const __amdgpu_buffer_rsrc_t row = row_rsrc(k + c * (long)L, L * 4);
+        float s, co;
+        sincospif(-(float)tid / (float)(2 * M), &s, &co);
+        cplx t = mk(co, s);
 #pragma unroll
-        for (int i = 0; i < NP; ++i) {
-            const int kk = pair_bin<M>(tid + T * i);
-            H[at(kk)] = h1[i];
-            H[at(M - kk)] = h2[i];
+        for (int i = 0; i < M / T; ++i) {
+            const float x = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(row, 4 * (tid + T * i), 0, 0));
+            z2[i] = mk(x * t.x, x * t.y);
+            t = cmul(t, mk(0.99518472667219693f, -0.098017140329560602f));
         }
-        if (tid == 0) H[at(M / 2)] = hm;
+        __syncthreads();                                            // a[] has been read out
+        fft_forward<M, T, true>(z2, a, tw, tid);
         __syncthreads();
-        uint4* dst = Ks + c * (long)(2 * M / 4);
+        uint4* dst = Ks + c * (long)(M / 4);
 #pragma unroll
-        for (int j = 0; j < 2 * M / 4 / T; ++j) {
-            const int o = tid + T * j, ln = o & 63, k0 = (o >> 8) + 32 * (ln & 31) + 1024 * (8 * ((o >> 6) & 3) + 4 * (ln >> 5));
+        for (int j = 0; j < M / 4 / T; ++j) {
+            const int o = tid + T * j, ln = o & 63, k0 = (o >> 8) + 16 * (ln & 31) + 512 * (8 * ((o >> 6) & 3) + 4 * (ln >> 5));
             unsigned v[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int kk = k0 + 1024 * i;
-                const bool upper = kk > M;
-                v[i] = H[at(upper ? 2 * M - kk : kk)] ^ (upper ? 0x80000000u : 0u);
+                const cplx x = a[conv_pad(spectrum_pos<M>(k0 + 512 * i))];
+                v[i] = half2(x.x, x.y);
             }
             dst[o] = make_uint4(v[0], v[1], v[2], v[3]);
         }
@@ -1608,12 +1611,16 @@ hipError_t launch_longconv_spectrum(const float* k, void* Kf, int d, int L, hipS
         return hipGetLastError();
     }
     uint4* mx = (uint4*)((char*)Kf + conv_pairs_bytes(d, L));
-    float* scale = (float*)((char*)mx + (size_t)d * 32768 * sizeof(unsigned));
+    float* scale = (float*)((char*)mx + (size_t)d * 16384 * sizeof(unsigned));
 #define CHELA_SPECTRUM(M_, MX_)                                                                                         \
     case M_: hipLaunchKernelGGL((longconv_spectrum_kernel<M_, MX_>), dim3(d), dim3(conv_threads(M_)), 0, st, k, out, mx,  \
                                 scale, L); break;
     switch (M) {
-        CHELA_SPECTRUM(256, false) CHELA_SPECTRUM(1024, false) CHELA_SPECTRUM(4096, false) CHELA_SPECTRUM(16384, true)
+        CHELA_SPECTRUM(256, false) CHELA_SPECTRUM(1024, false) CHELA_SPECTRUM(4096, false)
+        case 16384:     // (rows that are no multiple of 8 steps never meet the matrix-core kernels)
+            if ((L & 7) != 0) { switch (M) { CHELA_SPECTRUM(16384, false) } }
+            else { switch (M) { CHELA_SPECTRUM(16384, true) } }
+            break;
         default: return hipErrorInvalidValue;
     }
 #undef CHELA_SPECTRUM
@@ -1763,8 +1770,10 @@ static hipError_t conv_bwd_impl(const IO* X, const float* w_short, int m, const 
     // bf16 I/O at the lengths the matrix-core kernels serve: its own copy of the spectrum lies behind the pairs
     const bool mx = sizeof(IO) == 2 && convmx_applies(L, 0);
     const void* mx_spec = (const char*)Kf + conv_pairs_bytes(d, L);
+    // slices of dk that the sums' scratch has room for
+    const int share = mx ? (int)std::min<size_t>(conv_bwd_acc_floats(B, d, L, true) / ((size_t)d * L), 64) : 0;
     if (w_short == nullptr) { // no short stage: v = x and dX is the correlation of dZ with the long kernel itself
-        if (mx) return launch_convmx_longbwd(X, nullptr, 0, mx_spec, dZ, dX, false, dk, (float*)acc_ws, B, d, L, st);
+        if (mx) return launch_convmx_longbwd(X, nullptr, 0, mx_spec, dZ, dX, false, dk, (float*)acc_ws, share, B, d, L, st);
         return conv_longbwd_dispatch<IO, IO, false>(X, nullptr, 0, Kf, dZ, dX, dk, acc_ws, nullptr, B, d, L, st);
     }
     if (conv_bwd_fused(m, L)) {
@@ -1783,7 +1792,7 @@ static hipError_t conv_bwd_impl(const IO* X, const float* w_short, int m, const 
     const long per_wg = strips ? 4 * kStripsPerWave : kShortTilesPerWg;
     const int n_share = (int)((n_items + per_wg - 1) / per_wg);
     if ((long)d * n_share > 0x7fffffffL || n_items > 0x7ffffff0L) return hipErrorInvalidValue;
-    e = mx ? launch_convmx_longbwd(X, w_short, m, mx_spec, dZ, ws_dV, true, dk, (float*)acc_ws, B, d, L, st)
+    e = mx ? launch_convmx_longbwd(X, w_short, m, mx_spec, dZ, ws_dV, true, dk, (float*)acc_ws, share, B, d, L, st)
            : conv_longbwd_dispatch<IO, float, false>(X, w_short, m, Kf, dZ, ws_dV, dk, acc_ws, nullptr, B, d, L, st);
     if (e != hipSuccess) return e;
     {

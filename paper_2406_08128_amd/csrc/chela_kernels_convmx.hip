@@ -1,26 +1,35 @@
 // Long convolution of Eq. 7-8 (Sec. 4.2) with the transforms on the matrix cores, for bf16 I/O and sequences of
 // 4097 .. 16384 steps.
 //
-// Two sequences of one channel ride in one complex signal z = v_a + i v_b (the kernel is real, so the convolution of
-// z has the two results as its real and imaginary part: nothing has to be untangled), zero-padded to N = 32768 = 32^3
-// points so that the circular product equals the causal sum.  With n = 1024 n1 + 32 n2 + n3 and k = k1 + 32 k2 +
-// 1024 k3 the transform is three passes of the SAME 32-point transform, one along each axis of a 32 x 32 x 32 cube,
-// with an element-wise rotation after the first two:
-//     X1[k1,n2,n3] = W_N^(k1 (32 n2 + n3)) sum_n1 w^(k1 n1) z[n1,n2,n3]          (w = exp(-2 pi i / 32))
-//     X2[k1,k2,n3] = W_1024^(k2 n3)        sum_n2 w^(k2 n2) X1[k1,n2,n3]
-//     X [k1,k2,k3] =                       sum_n3 w^(k3 n3) X2[k1,k2,n3]
-// The way back is conj(T'(conj P)) where T' takes the axes in the opposite order (3, 2, 1) with the same matrix and
-// the same rotations, so one pass routine serves all six passes and nothing is ever reordered.  A 32-point complex
-// transform of 32 columns is a real 64 x 64 matrix times a 64 x 32 tile: v_mfma_f32_32x32x16_f16, the matrix in
-// registers for the whole kernel (fp16, entries cos / sin of multiples of pi/16), the data as fp16 pairs (re, im)
-// in LDS, sums in fp32.  The rows of the matrix are ordered so that the lane that receives a set of results is the
-// lane that would have to supply them as operands of a pass along the same axis: the third pass forward, the product
-// with the kernel's spectrum and the first pass back happen in registers, without a trip through LDS.
-// Ranges: the pair is scaled by 1 / max|v| on the way in (|z| <= sqrt 2, so no sum on the way forward exceeds
-// 23171), the kernel's spectrum is stored divided by 4 |k|_1 (so that no sum on the way back exceeds 32768 either:
-// the half-precision range ends at 65504); both factors are put back on the way out.  Measured against the fp64
-// definition on the workload's recipe: 4.8e-4 relative before the rounding of the output to bf16 (2.3e-3 on its own).
+// A real sequence x of N = 16384 steps (zero beyond L) is evaluated at the N points exp(-2 pi i (k + 1/4) / N), the roots
+// of z^N = -i: there the product of two real sequences is (low half) - i (high half) of their causal sum, so the real part
+// of the way back is the causal result with no zero-padding, no pair of sequences to share a transform and nothing to
+// untangle, and the quarter step costs nothing, because every twiddle below sits in a matrix or in a rotation anyway.
+// With n = 1024 n1 + 32 n2 + n3 and k = k1 + 16 k2 + 512 k3 (n1, k1 < 16, the others < 32):
+//     X1[k1,n2,n3] = e((k1 + 1/4) (32 n2 + n3) / N) sum_n1 e((k1 + 1/4) n1 / 16) x[n1,n2,n3]         e(t) = exp(-2 pi i t)
+//     X2[k1,k2,n3] = e(k2 n3 / 1024)                sum_n2 e(k2 n2 / 32) X1[k1,n2,n3]
+//     X [k1,k2,k3] =                                sum_n3 e(k3 n3 / 32) X2[k1,k2,n3]
+// The way back is the conjugate of the same sums over the conjugate bins in the opposite order (the real part does not
+// care about the last conjugation).  All sums are matrix products (fp16 operands, fp32 sums); rotations are applied in
+// fp32, the part of the first one that differs from step to step of a lane's eight (e((k1 + 1/4) (n3 & 7) / N)) is worked
+// into eight versions of the first matrix.
+//
+// Bound by vector instructions (short kernel, silu and conversions take about half of them), so the layout is chosen to
+// spend none on moving data:
+//   - First pass: a lane loads eight consecutive steps of four rows n1, which is its operand of
+//     v_mfma_f32_16x16x16_f16 (contraction over n1), and gets four k1 of the same eight columns.
+//   - Tile k1 (32 x 32 columns) then belongs to one wave, which takes it through both other passes, the product with the
+//     kernel's spectrum and both passes back without leaving its registers: a product of 32x32x16 with the data as first
+//     operand leaves a lane the rows it has to supply as second operand of the next, and the other way round.
+//   - Last pass: LDS transposing reads hand a lane its operand for the eight columns it loaded, the results leave as 16-byte
+//     stores.
+// So a sequence crosses LDS twice (64 KB of fp16, re and im planes), with three barriers.
+// Ranges: the input is scaled by a power of two to max|v| < 1 (no sum on the way forward exceeds 16384), the kernel's spectrum is stored divided
+// by 4 |k|_1 (no finished sum on the way back exceeds 4096, no partial one, by Parseval, 16400): half precision ends at 65504.
+// Both factors are put back on the way out.  Error against the fp64 definition on the workload's recipe: 4.2e-4 relative
+// before the rounding of the output to bf16 (1.7e-3 on its own).
 #include "chela_internal.h"
+#include <cfloat>
 #include <cstdlib>
 
 namespace chela {
@@ -28,34 +37,48 @@ namespace chela {
 typedef __bf16 bf16;
 typedef _Float16 f16;
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
+typedef __attribute__((ext_vector_type(4))) _Float16 f16x4;
 typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
-typedef __attribute__((ext_vector_type(2))) float f32x2;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
+typedef __attribute__((ext_vector_type(4))) short s16x4;
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
-constexpr int MX_N = 32768;                  // points of the complex transform
-constexpr int MX_L_MAX = 16384;              // steps of a sequence at most
-constexpr int MX_PLANE = 1032;               // words (one complex fp16 pair each) from one n1 plane to the next
-constexpr int MX_CUBE = 32 * MX_PLANE;       // 132 096 bytes
-constexpr int MX_T = 512;                    // threads: each owns one row of the lower half of the cube (32 steps)
-constexpr int MX_W = MX_T / 64;              // waves
+constexpr int MX_N = 16384;                  // points of the transform = steps of a sequence at most
+constexpr int MX_T = 512;                    // threads: each owns eight columns of four rows n1 (32 steps)
+constexpr int MX_W = MX_T / 64;              // waves; wave w owns columns 128 w .. 128 w + 127 and tiles w, w + 8
+constexpr int MX_NT = 16 / MX_W;             // tiles per wave
+constexpr int MX_PLANE = 16 * 2048;          // bytes of the re (or im) plane of a cube: [k1][n2][n3] fp16
+constexpr int MX_CUBE = 2 * MX_PLANE;
 
-// Word of cube element (d1, d2, d3).  Rows (d1, d2) of 32 words; passes along an axis read, per instruction, the same
-// columns of two rows that lie 4 apart along that axis (the two half-waves): the plane stride (4 x 1032 = 32 mod 64)
-// and the order of the rows within a plane (bit 2 of d2 stored as bit 0) put those on the two halves of the banks.
-// The pass along d3 reads and writes 16 bytes per lane with the lanes on consecutive rows: the 16-byte pieces of a
-// row are exchanged by the row number so that 16 lanes meet 16 different pieces.
-__device__ __forceinline__ int mx_addr(int d1, int d2, int d3)
+// One word of two halves, round to nearest even.
+__device__ __forceinline__ unsigned mx_pack(float lo, float hi)
 {
-    const int r = (d2 & 24) | ((d2 & 3) << 1) | ((d2 >> 2) & 1);
-    return d1 * MX_PLANE + r * 32 + ((((d3 >> 2) ^ (r >> 1)) & 7) << 2) + (d3 & 3);
+    f16x2 v;
+    v[0] = (f16)lo;
+    v[1] = (f16)hi;
+    return __builtin_bit_cast(unsigned, v);
+}
+__device__ __forceinline__ void mx_unpack(unsigned w, float& lo, float& hi)
+{
+    const f16x2 v = __builtin_bit_cast(f16x2, w);
+    lo = (float)v[0];
+    hi = (float)v[1];
+}
+__device__ __forceinline__ f16x8 mx_h8(u32x4 v) { return __builtin_bit_cast(f16x8, v); }
+
+// Within a group of 16 lanes the transposing read hands lane p element p % 4 of the 8-byte pieces that lanes p / 4,
+// p / 4 + 4, p / 4 + 8, p / 4 + 12 address.
+__device__ __forceinline__ u32x2 mx_tr(const unsigned char* p)
+{
+    return __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)p));
 }
 
-__device__ __forceinline__ f32x16 mx_mfma(f16x8 a, f16x8 b, f32x16 c)
-{
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
-}
+// What depends on the lane only (LDS addresses, table entries) is worked out afresh by every stage behind an opaque copy of
+// the lane index: kept from stage to stage it would fill the register file.
+__device__ __forceinline__ int mx_fresh(int lane) { asm volatile("" : "+v"(lane)); return lane; }
 
 __device__ __forceinline__ f32x16 mx_zero()
 {
@@ -65,610 +88,634 @@ __device__ __forceinline__ f32x16 mx_zero()
     return z;
 }
 
-// (re, im) -> one word of two halves, round to nearest even
-__device__ __forceinline__ unsigned mx_pack(float re, float im)
+// Tables in LDS.
+//   T: the first matrix, [j][re, im][k1][n1] fp16: e((k1 + 1/4) (n1 / 16 + j / N))
+//   R: e(sigma r / 1024), [sigma - 1][r] fp32 pairs, sigma = 1 .. 31 (row 0 would be ones)
+struct MxTables {
+    f16 T[8 * 2 * 16 * 16];
+    float2 R[31 * 32];
+    float red[2 * MX_W];
+};
+// e(num * unit), num * unit exact: the hardware's sine and cosine take turns; what they are off by (1e-6) is nothing beside
+// the fp16 that every rotated value and matrix entry is rounded to.
+__device__ __forceinline__ float2 mx_e(int num, float unit)
 {
-    f16x2 v;
-    v[0] = (f16)re;
-    v[1] = (f16)im;
-    return __builtin_bit_cast(unsigned, v);
+    const float t = (float)num * unit;
+    return make_float2(__builtin_amdgcn_cosf(t), -__builtin_amdgcn_sinf(t));
 }
-__device__ __forceinline__ void mx_unpack(unsigned w, float& re, float& im)
-{
-    const f16x2 v = __builtin_bit_cast(f16x2, w);
-    re = (float)v[0];
-    im = (float)v[1];
-}
-
-// The matrix operand.  Real form of the 32-point transform F[p][q] = exp(-2 pi i p q / 32) acting on (re, im) pairs:
-// contraction index kk = 2 q + c_in, rows 2 p + c_out in an order of our choosing.  Accumulator register 4a + b of
-// lane (r, h) is row 8a + 4h + b of a 32-row block: we let block rb, row 8a + 4h + b stand for
-//     p = 16 rb + 8 (a >> 1) + 4 h + 2 (a & 1) + (b >> 1),   c_out = b & 1,
-// so that a lane ends up with the complex results p = 8 s + 4 h + i (s = 2 rb + (a >> 1) = 0..3, i = 0..3): exactly the
-// inputs q = 8 s + 4 h + i it has to supply, as four (re, im) words, for step s of a contraction over the same axis.
-// Operand layout of the instruction: lane (r, h) holds row r, contraction indices 16 s + 8 h + 0..7.
-__device__ __forceinline__ void mx_build_matrix(f16x8 (&A)[2][4], int lane)
-{
-    const int r = lane & 31, hh = lane >> 5;
-    const int a = r >> 3, h = (r >> 2) & 1, b = r & 3;
-#pragma unroll
-    for (int rb = 0; rb < 2; ++rb) {
-        const int p = 16 * rb + 8 * (a >> 1) + 4 * h + 2 * (a & 1) + (b >> 1), c_out = b & 1;
-#pragma unroll
-        for (int s = 0; s < 4; ++s)
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int kk = 16 * s + 8 * hh + j, q = kk >> 1, c_in = kk & 1;
-                float sn, cs;
-                sincospif((float)((p * q) & 31) * 0.0625f, &sn, &cs);      // F = cs - i sn
-                // re_out = cs x_re + sn x_im ;  im_out = -sn x_re + cs x_im
-                const float v = c_out == 0 ? (c_in == 0 ? cs : sn) : (c_in == 0 ? -sn : cs);
-                A[rb][s][j] = (f16)v;
-            }
-    }
-}
-
-enum { MX_AX1 = 1, MX_AX2 = 2, MX_AX3 = 3 };
-enum { MX_TW_NONE = 0, MX_TW_F1 = 1, MX_TW_T2 = 2, MX_TW_I2 = 3 };
-
-// Element q of column `col` of tile t along the axis: tiles are (n2 | columns n3) along axis 1, (d1 | columns n3)
-// along axis 2, (d1 | columns d2) along axis 3.
-template <int AX>
-__device__ __forceinline__ int mx_word(int t, int col, int q)
-{
-    return AX == MX_AX1 ? mx_addr(q, t, col) : AX == MX_AX2 ? mx_addr(t, q, col) : mx_addr(t, col, q);
-}
-
-template <int AX, int KS>
-__device__ __forceinline__ void mx_load(const unsigned* cube, int t, int col, int h, f16x8 (&Bv)[4])
-{
-#pragma unroll
-    for (int s = 0; s < KS; ++s) {
-        u32x4 v;
-        if (AX == MX_AX3) {
-            v = *reinterpret_cast<const u32x4*>(cube + mx_addr(t, col, 8 * s + 4 * h));
-        } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) v[i] = cube[mx_word<AX>(t, col, 8 * s + 4 * h + i)];
-        }
-        Bv[s] = __builtin_bit_cast(f16x8, v);
-    }
-}
-
-template <int KS, int RB>
-__device__ __forceinline__ void mx_mul(const f16x8 (&A)[2][4], const f16x8 (&Bv)[4], f32x16 (&acc)[2])
-{
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-        acc[rb] = mx_zero();
-#pragma unroll
-        for (int s = 0; s < KS; ++s) acc[rb] = mx_mfma(A[rb][s], Bv[s], acc[rb]);
-    }
-}
-
-// complex result i (0..3) of step s (0..3) in a lane's accumulators: p = 8 s + 4 h + i
-__device__ __forceinline__ float mx_re(const f32x16 (&acc)[2], int s, int i) { return acc[s >> 1][4 * (2 * (s & 1) + (i >> 1)) + 2 * (i & 1)]; }
-__device__ __forceinline__ float mx_im(const f32x16 (&acc)[2], int s, int i) { return acc[s >> 1][4 * (2 * (s & 1) + (i >> 1)) + 2 * (i & 1) + 1]; }
-
-// The rotations that follow a pass are kept in registers, one per result a lane owns (index 4 s + i for row
-// p = 8 s + 4 h + i); reading them from LDS per tile cost more LDS time than the data itself.  With T2[a][b] =
-// W_1024^(a b) and T1[a][b] = W_32768^(a b) (32 x 32 tables in LDS, read a few times per pair only):
-//   fixed (forward after axis 2: rows k2, columns n3; back after axis 3: rows n3, columns k2):  T2[p][col], the same
-//         sixteen numbers for every tile and every pair
-//   F1 (forward after axis 1: rows k1 = p, tile n2 = t, columns n3):  W_N^(k1 (32 n2 + n3)) = T1[p][col] T2[p][t]
-//   I2 (back after axis 2: rows n2 = p, tile k1 = t, columns n3):     W_N^(k1 (32 n2 + n3)) = T2[p][t] T1[t][col]
-//   a wave's tiles are t = w, w + MX_W, ...: the running values are set for t = w and multiplied by the step to the
-//   next tile (T2[p][MX_W], times T1[MX_W][col] for I2) after each tile.
-struct MxRot { float2 v[16]; };
-
 __device__ __forceinline__ float2 mx_cmul(float2 a, float2 b) { return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x); }
-
-__device__ __forceinline__ void mx_rot_fixed(MxRot& r, const float2* T2, int col, int h)
+__device__ __forceinline__ void mx_build_tables(MxTables& tb, int tid)
 {
 #pragma unroll
-    for (int j = 0; j < 16; ++j) r.v[j] = T2[(8 * (j >> 2) + 4 * h + (j & 3)) * 32 + col];
+    for (int x = tid; x < 8 * 256; x += MX_T) {
+        const int j = x >> 8, k1 = (x >> 4) & 15, n1 = x & 15;
+        // (4 k1 + 1) (1024 n1 + j) / (4 N) of a turn, the whole turns taken off
+        const float2 e = mx_e(((4 * k1 + 1) * (1024 * n1 + j)) & (4 * MX_N - 1), 1.0f / (4.0f * MX_N));
+        tb.T[(2 * j) * 256 + (x & 255)] = (f16)e.x;
+        tb.T[(2 * j + 1) * 256 + (x & 255)] = (f16)e.y;
+    }
+    for (int x = tid; x < 31 * 32; x += MX_T) tb.R[x] = mx_e(((x >> 5) + 1) * (x & 31), 1.0f / 1024.0f);
 }
-template <int TW>
-__device__ __forceinline__ void mx_rot_start(MxRot& cur, MxRot& step, const float2* T2, const float2* T1, int w, int col, int h)
+
+// The 32-point matrix, times a number for which cos(k pi / 16), k < 8, lie as close to half precision as they get: a third of
+// the rounding error of the entries themselves (2.6e-5 against 8.3e-5 root mean square).  MX_GAIN: what the rounded entries
+// come to (least squares), taken out at the stores, once per product.
+constexpr float MX_ENTRY = 1.11529f, MX_GAIN = 1.11520299f;
+constexpr float MX_GAIN2 = MX_GAIN * MX_GAIN, MX_GAIN4 = MX_GAIN2 * MX_GAIN2;
+
+// The 32-point matrix e(r sigma / 32) = c - i s as an operand (first or second: it is symmetric): lane (r, h), element e of
+// step t stands for sigma = 16 t + 8 (e / 4) + 4 h + e % 4, the order in which a lane holds the rows of a result.
+struct MxMat { f16x8 c[2], s[2], ns[2]; };
+__device__ __forceinline__ void mx_build_matrix(MxMat& m, int lane)
 {
-    const float2 c0 = T1[w * 32 + col], c1 = T1[MX_W * 32 + col];       // (I2 only)
+    const int r = lane & 31, h = lane >> 5;
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        const int p = 8 * (j >> 2) + 4 * h + (j & 3);
-        if (TW == MX_TW_F1) {
-            cur.v[j] = mx_cmul(T1[p * 32 + col], T2[p * 32 + w]);
-            step.v[j] = T2[p * 32 + MX_W];
-        } else {
-            cur.v[j] = mx_cmul(T2[p * 32 + w], c0);
-            step.v[j] = mx_cmul(T2[p * 32 + MX_W], c1);
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const int sigma = 16 * t + 8 * (e >> 2) + 4 * h + (e & 3);
+            const float2 p = mx_e((r * sigma) & 31, 1.0f / 32.0f);
+            m.c[t][e] = (f16)(MX_ENTRY * p.x);
+            m.s[t][e] = (f16)(MX_ENTRY * -p.y);
+            m.ns[t][e] = (f16)(MX_ENTRY * p.y);
+        }
+}
+
+// What a lane needs besides: rho = e((4 q + 1/4) (128 w + 8 c) / N) and g = e((128 w + 8 c) / N) for the first pass
+// (lane = 16 q + c), u = e(r / 2048) for the way back (lane = 32 h + r).
+struct MxLane { float2 rho, g, u; };
+__device__ __forceinline__ void mx_build_lane(MxLane& c, int lane, int w)
+{
+    const int col = 128 * w + 8 * (lane & 15);
+    c.rho = mx_e((16 * (lane >> 4) + 1) * col, 1.0f / (4.0f * MX_N));
+    c.g = mx_e(col, 1.0f / MX_N);
+    c.u = mx_e(lane & 31, 1.0f / 2048.0f);
+}
+// e((k1 + 1/4) 8 / N), the same in all lanes
+__device__ __forceinline__ float2 mx_step(int k1)
+{
+    const float2 st = mx_e((4 * k1 + 1) * 8, 1.0f / (4.0f * MX_N));
+    return make_float2(__builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, st.x))),
+                       __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, st.y))));
+}
+
+// ---- first pass: v[i][j] = step 1024 (4 q + i) + 128 w + 8 c + j, times s, into the cube.  EXACT: v are bf16 numbers, which
+// times a power of two are half-precision ones; else what they lose in rounding goes through the same product (the rounding of
+// the input weighs as much as any two others: it is not averaged over a pass).
+template <bool EXACT>
+__device__ __forceinline__ void mx_first(unsigned char* cube, const MxTables& tb, const MxLane& lc, const float (&v)[4][8],
+                                         float s, int w, int lane)
+{
+    lane = mx_fresh(lane);
+    const int c = lane & 15, q = lane >> 4;
+    float2 rho[4];
+    rho[0] = lc.rho;
+#pragma unroll
+    for (int k = 1; k < 4; ++k) rho[k] = mx_cmul(rho[k - 1], lc.g);
+    // rows of 64 bytes (n3) in natural order
+    unsigned char* p = cube + 4 * q * 2048 + (4 * w + (c >> 2)) * 64 + (c & 3) * 16;
+    u32x2 out[2][4];
+#pragma unroll
+    for (int j = 0; j < 8; j += 2) {
+        __builtin_amdgcn_sched_barrier(0);
+        float re[2][4], im[2][4];
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            const f16* t = tb.T + (2 * (j + u)) * 256 + c * 16 + 4 * q;
+            const f16x4 ar = *reinterpret_cast<const f16x4*>(t), ai = *reinterpret_cast<const f16x4*>(t + 256);
+            u32x2 bw;
+            bw[0] = mx_pack(v[0][j + u] * s, v[1][j + u] * s);
+            bw[1] = mx_pack(v[2][j + u] * s, v[3][j + u] * s);
+            const f16x4 b = __builtin_bit_cast(f16x4, bw);
+            const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+            f32x4 xr = __builtin_amdgcn_mfma_f32_16x16x16f16(ar, b, z, 0, 0, 0);
+            f32x4 xi = __builtin_amdgcn_mfma_f32_16x16x16f16(ai, b, z, 0, 0, 0);
+            if constexpr (!EXACT) {
+                u32x2 lw;
+                lw[0] = mx_pack(fmaf(v[0][j + u], s, -(float)b[0]), fmaf(v[1][j + u], s, -(float)b[1]));
+                lw[1] = mx_pack(fmaf(v[2][j + u], s, -(float)b[2]), fmaf(v[3][j + u], s, -(float)b[3]));
+                const f16x4 lo = __builtin_bit_cast(f16x4, lw);
+                xr = __builtin_amdgcn_mfma_f32_16x16x16f16(ar, lo, xr, 0, 0, 0);
+                xi = __builtin_amdgcn_mfma_f32_16x16x16f16(ai, lo, xi, 0, 0, 0);
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                re[u][k] = xr[k] * rho[k].x - xi[k] * rho[k].y;
+                im[u][k] = xr[k] * rho[k].y + xi[k] * rho[k].x;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            out[0][k][(j >> 1) & 1] = mx_pack(re[0][k], re[1][k]);
+            out[1][k][(j >> 1) & 1] = mx_pack(im[0][k], im[1][k]);
+            if (j & 2) {
+                *reinterpret_cast<u32x2*>(p + k * 2048 + (j >> 2) * 8) = out[0][k];
+                *reinterpret_cast<u32x2*>(p + MX_PLANE + k * 2048 + (j >> 2) * 8) = out[1][k];
+            }
         }
     }
 }
 
-template <int AX, bool ROT, int RB>
-__device__ __forceinline__ void mx_store(unsigned* cube, const f32x16 (&acc)[2], const MxRot& rot, int t, int col, int h)
+// (re, im) = data times the 32-point matrix; DATA_FIRST: the data's lanes are the rows of the result.
+template <bool DATA_FIRST>
+__device__ __forceinline__ void mx_mul(const MxMat& m, const u32x4 (&re)[2], const u32x4 (&im)[2], f32x16& xr, f32x16& xi)
 {
+    auto mul = [](f16x8 d, f16x8 k, f32x16 acc) __attribute__((always_inline)) {
+        return DATA_FIRST ? __builtin_amdgcn_mfma_f32_32x32x16_f16(d, k, acc, 0, 0, 0)
+                          : __builtin_amdgcn_mfma_f32_32x32x16_f16(k, d, acc, 0, 0, 0);
+    };
+    xr = mul(mx_h8(re[0]), m.c[0], mx_zero());
+    xi = mul(mx_h8(im[0]), m.c[0], mx_zero());
+    xr = mul(mx_h8(re[1]), m.c[1], xr);
+    xi = mul(mx_h8(im[1]), m.c[1], xi);
+    xr = mul(mx_h8(im[0]), m.s[0], xr);
+    xi = mul(mx_h8(re[0]), m.ns[0], xi);
+    xr = mul(mx_h8(im[1]), m.s[1], xr);
+    xi = mul(mx_h8(re[1]), m.ns[1], xi);
+}
+
+// Register 4 a + b of lane (r, h) is row sigma = 8 a + 4 h + b, column r: turn by e(sigma r / 1024) and pack as operand.
+__device__ __forceinline__ void mx_rotate(const f32x16& xr, const f32x16& xi, const float2* R, int lane, u32x4 (&re)[2],
+                                          u32x4 (&im)[2])
+{
+    lane = mx_fresh(lane);
+    const int r = lane & 31, h = lane >> 5;
 #pragma unroll
-    for (int s = 0; s < 2 * RB; ++s) {
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; b += 2) {
+            float x[2], y[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int sigma = 8 * a + 4 * h + b + u, i = 4 * a + b + u;
+                float2 p = R[(sigma > 0 ? sigma - 1 : 0) * 32 + r];
+                if (a == 0 && b + u == 0) p = h == 0 ? make_float2(1.f, 0.f) : p;
+                x[u] = xr[i] * p.x - xi[i] * p.y;
+                y[u] = xr[i] * p.y + xi[i] * p.x;
+            }
+            re[a >> 1][2 * (a & 1) + (b >> 1)] = mx_pack(x[0], x[1]);
+            im[a >> 1][2 * (a & 1) + (b >> 1)] = mx_pack(y[0], y[1]);
+        }
+}
+
+// ---- tile k1 through the second and third pass: register 4 a + b of lane (r, h) ends as bin k2 = r, k3 = 8 a + 4 h + b
+__device__ __forceinline__ void mx_tile_in(const unsigned char* cube, const MxTables& tb, const MxMat& m, int k1, int lane,
+                                           f32x16& xr, f32x16& xi)
+{
+    lane = mx_fresh(lane);
+    const int h = lane >> 5, p = lane & 15, g = (lane >> 4) & 1;
+    u32x4 re[2], im[2];
+    const unsigned char* t = cube + k1 * 2048 + (4 * h + (p >> 2)) * 64 + (4 * g + (p & 3)) * 8;
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        const u32x2 a = mx_tr(t + s * 1024), b = mx_tr(t + s * 1024 + 512);
+        re[s] = u32x4{a[0], a[1], b[0], b[1]};
+        const u32x2 c = mx_tr(t + MX_PLANE + s * 1024), d = mx_tr(t + MX_PLANE + s * 1024 + 512);
+        im[s] = u32x4{c[0], c[1], d[0], d[1]};
+    }
+    mx_mul<true>(m, re, im, xr, xi);              // rows n3, columns k2
+    mx_rotate(xr, xi, tb.R, lane, re, im);
+    mx_mul<false>(m, re, im, xr, xi);             // rows k3, columns k2
+}
+
+// ---- the way back of tile k1 from its (conjugate) bins, packed along k3, into the cube: row n2 of 64 bytes holds n3 = 8 a + j at
+// place 4 j + a, its 8-byte pieces (one j each) exchanged by k1 and n2 so that neither the writers here (32 rows) nor the
+// readers of the last pass (4 rows of 8 tiles) share banks.
+__device__ __forceinline__ int mx_swizzle(int k1, int n2) { return ((k1 & 3) | (k1 >> 3) << 2) ^ (n2 >> 2); }
+__device__ __forceinline__ void mx_tile_out(unsigned char* cube, const MxTables& tb, const MxMat& m, float2 u, float2 st,
+                                            int k1, int lane, u32x4 (&re)[2], u32x4 (&im)[2])
+{
+    lane = mx_fresh(lane);
+    const int r = lane & 31, h = lane >> 5;
+    f32x16 xr, xi;
+    mx_mul<true>(m, re, im, xr, xi);              // rows k2, columns n3
+    mx_rotate(xr, xi, tb.R, lane, re, im);
+    mx_mul<true>(m, re, im, xr, xi);              // rows n3, columns n2
+    // e((k1 + 1/4) (32 n2 + 8 a) / N), the first factor being e(2 k1 n2 / 1024) e(n2 / 2048)
+    float2 e[4];
+    e[0] = tb.R[(k1 > 0 ? 2 * k1 - 1 : 0) * 32 + r];
+    if (k1 == 0) e[0] = make_float2(1.f, 0.f);
+    e[0] = mx_cmul(e[0], u);
+#pragma unroll
+    for (int a = 1; a < 4; ++a) e[a] = mx_cmul(e[a - 1], st);
+    unsigned char* row = cube + k1 * 2048 + r * 64;
+    const int sw = mx_swizzle(k1, r);
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+        float x[4], y[4];                         // Re, -Im
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
+            const float ur = xr[4 * a + b], ui = xi[4 * a + b];
+            x[a] = ur * e[a].x - ui * e[a].y;
+            y[a] = -ur * e[a].y - ui * e[a].x;
+        }
+        u32x2 vx, vy;
+        vx[0] = mx_pack(x[0], x[1]); vx[1] = mx_pack(x[2], x[3]);
+        vy[0] = mx_pack(y[0], y[1]); vy[1] = mx_pack(y[2], y[3]);
+        unsigned char* d = row + ((4 * h + b) ^ sw) * 8;
+        *reinterpret_cast<u32x2*>(d) = vx;
+        *reinterpret_cast<u32x2*>(d + MX_PLANE) = vy;
+    }
+}
+
+// ---- last pass: y[i][j] = N times step 1024 (4 q + i) + 128 w + 8 c + j, up to the scales
+__device__ __forceinline__ void mx_last(const unsigned char* cube, const MxTables& tb, int w, int lane, float (&y)[4][8])
+{
+    lane = mx_fresh(lane);
+    const int p = lane & 15, q = lane >> 4;
+    const int k0 = 8 * (q & 1) + (p >> 2);                                  // k1 of this lane's first piece; + 4: the second
+    const unsigned char* pl = cube + (q >> 1) * MX_PLANE + k0 * 2048 + (4 * w + (p & 3)) * 64;
+    const int sw = mx_swizzle(k0, 4 * w);                                   // (the same for k0 + 4, and for the four rows)
+    const f16* t = tb.T + (q >> 1) * 256 + k0 * 16 + 4 * (p & 3);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const unsigned char* tj = reinterpret_cast<const unsigned char*>(t + 2 * j * 256);
+        const u32x2 a0 = mx_tr(tj), a1 = mx_tr(tj + 4 * 16 * 2);
+        const unsigned char* d = pl + ((j ^ sw) & 7) * 8;
+        const u32x2 b0 = mx_tr(d), b1 = mx_tr(d + 4 * 2048);
+        const f32x4 z = {0.f, 0.f, 0.f, 0.f};
+        const f32x4 r = __builtin_amdgcn_mfma_f32_16x16x32_f16(mx_h8(u32x4{a0[0], a0[1], a1[0], a1[1]}),
+                                                               mx_h8(u32x4{b0[0], b0[1], b1[0], b1[1]}), z, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) y[i][j] = r[i];
+    }
+}
+
+// A lane's steps are t0 + 1024 i + j, i < 4, j < 8.
+__device__ __forceinline__ int mx_first_step(int w, int lane) { return 4096 * (lane >> 4) + 128 * w + 8 * (lane & 15); }
+
+// ---- a sequence in registers: 16-byte pieces of rows n1 = 4 q + i, steps t0 + 1024 i .. + 7, and the HALO steps in front of
+// each (the taps' history).  Buffer loads: what lies before the row's start or beyond its end reads as zero.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t mx_rsrc(const void* row, int bytes)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(row), 0, bytes, 0x00020000);
+}
+// History comes from the registers of the lanes in front; the first lanes of a row's 16 get theirs from the lanes that have
+// fetched it for them: lane 16 (D - 1) + 4 q + i the piece 8 D steps in front of this wave's part of row 4 q + i.
+template <int HALO>
+struct MxSeq {
+    static_assert(HALO % 8 == 0 && HALO <= 32, "");
+    static constexpr int NH = HALO / 8;
+    u32x4 r[4], front;
+    __device__ __forceinline__ void load(const bf16* row, int L, int w, int lane)
+    {
+        lane = mx_fresh(lane);
+        const int t0 = mx_first_step(w, lane);
+        const __amdgpu_buffer_rsrc_t rs = mx_rsrc(row, 2 * L);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) r[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, 2 * (t0 + 1024 * i), 0, 0));
+        if (HALO > 0)
+            front = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, 2 * (1024 * (lane & 15) + 128 * w - 8 - 8 * (lane >> 4)), 0, 0));
+    }
+    // the piece 8 D steps in front of row i's
+    template <int D>
+    __device__ __forceinline__ u32x4 piece(int i, int lane) const
+    {
+        const int from = 16 * (D - 1 - (lane & 15)) + 4 * (lane >> 4) + i;         // (of use to the first D lanes only)
         u32x4 v;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            float re = mx_re(acc, s, i), im = mx_im(acc, s, i);
-            if (ROT) {
-                const float2 w = rot.v[4 * s + i];
-                const float x = re * w.x - im * w.y, y = re * w.y + im * w.x;
-                re = x;
-                im = y;
-            }
-            v[i] = mx_pack(re, im);
-        }
-        if (AX == MX_AX3) {
-            *reinterpret_cast<u32x4*>(cube + mx_addr(t, col, 8 * s + 4 * h)) = v;
-        } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) cube[mx_word<AX>(t, col, 8 * s + 4 * h + i)] = v[i];
-        }
+        for (int e = 0; e < 4; ++e)
+            v[e] = (unsigned)__builtin_amdgcn_update_dpp(__builtin_amdgcn_ds_bpermute(4 * from, (int)front[e]), (int)r[i][e],
+                                                         0x110 + D, 0xf, 0xf, false);      // row_shr:D
+        return v;
     }
-}
-
-// One pass over the cube in place: wave w takes tiles w, w + MX_W, ... (32 columns each).  KS: steps of the contraction
-// (2 when only the first 16 inputs along the axis can be non-zero), RB: row blocks wanted (1: results 0..15 only).
-// TW: MX_TW_NONE, MX_TW_T2 (the same rotations for every tile) or MX_TW_F1 / MX_TW_I2 (stepped from tile to tile).
-template <int AX, int TW, int KS, int RB>
-__device__ __forceinline__ void mx_pass(unsigned* cube, const f16x8 (&A)[2][4], const float2* T2, const float2* T1, int w,
-                                        int lane)
-{
-    const int col = lane & 31, h = lane >> 5;
-    constexpr bool RUN = TW == MX_TW_F1 || TW == MX_TW_I2;
-    MxRot cur, step;
-    if (RUN) mx_rot_start<TW>(cur, step, T2, T1, w, col, h);
-    if (TW == MX_TW_T2) mx_rot_fixed(cur, T2, col, h);
-#pragma unroll 1
-    for (int t = w; t < 32; t += MX_W) {
-        f16x8 Bv[4];
-        f32x16 acc[2];
-        mx_load<AX, KS>(cube, t, col, h, Bv);
-        mx_mul<KS, RB>(A, Bv, acc);
-        mx_store<AX, TW != MX_TW_NONE, RB>(cube, acc, cur, t, col, h);
-        if (RUN) {
-#pragma unroll
-            for (int j = 0; j < 16; ++j) cur.v[j] = mx_cmul(cur.v[j], step.v[j]);
-        }
-    }
-}
-
-// 32 consecutive steps [t0, t0 + 32) of one sequence (t0 = 32 tid: one row of the cube) through the short kernel and
-// the activation, from registers only: the steps themselves and the HALO steps in front of them (the taps' history;
-// zero in front of the sequence) come in as 16-byte pieces.  L is a multiple of 8 (so are the rows' starts), pieces
-// beyond L read as zero, steps beyond L give zero.  HALO = 0: no short kernel, v = x.
-template <int HALO>
-__device__ __forceinline__ void mx_steps(const bf16* __restrict__ row, bool present, int t0, int L,
-                                         const float* __restrict__ wc, int m, float (&v)[32])
-{
-    float x[HALO + 32];
-#pragma unroll
-    for (int k = 0; k < (HALO + 32) / 8; ++k) {
-        const int pos = t0 - HALO + 8 * k;
-        u32x4 r = {0u, 0u, 0u, 0u};
-        if (present && pos >= 0 && pos < L) r = *reinterpret_cast<const u32x4*>(row + pos);
+    __device__ __forceinline__ static void unpack8(u32x4 v, float* x)
+    {
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            x[8 * k + 2 * e] = __builtin_bit_cast(float, r[e] << 16);
-            x[8 * k + 2 * e + 1] = __builtin_bit_cast(float, r[e] & 0xffff0000u);
+            x[2 * e] = __builtin_bit_cast(float, v[e] << 16);
+            x[2 * e + 1] = __builtin_bit_cast(float, v[e] & 0xffff0000u);
         }
     }
-    if (HALO == 0) {
+    // The wave's largest magnitude (of the steps themselves).
+    __device__ __forceinline__ float wave_max() const
+    {
+        typedef __attribute__((ext_vector_type(2))) unsigned short u16x2;
+        u16x2 mx = {0, 0};
 #pragma unroll
-        for (int o = 0; o < 32; ++o) v[o] = x[o];
-        return;
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                mx = __builtin_elementwise_max(mx, __builtin_bit_cast(u16x2, r[i][e] & 0x7fff7fffu));
+        float v = __builtin_bit_cast(float, (unsigned)(mx[0] > mx[1] ? mx[0] : mx[1]) << 16);
+        v = v > FLT_MAX ? FLT_MAX : v == v ? v : 0.f;
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
+        return v;
     }
+    // v = silu(K_s x) (HALO = 0: v = x).  Steps beyond the sequence's end come out as whatever their history gives: a
+    // causal sum does not hand them back to earlier steps, and the gradient meets them with dZ = 0.
+    __device__ __forceinline__ void values(const float* __restrict__ wc, int m, int lane, float (&v)[4][8]) const
+    {
+        lane = mx_fresh(lane);
 #pragma unroll
-    for (int o = 0; o < 32; ++o) v[o] = 0.f;
+        for (int i = 0; i < 4; ++i) {
+            float x[HALO + 8];
+            unpack8(r[i], x + HALO);
+            if constexpr (HALO >= 8) unpack8(piece<1>(i, lane), x + HALO - 8);
+            if constexpr (HALO >= 16) unpack8(piece<2>(i, lane), x + HALO - 16);
+            if constexpr (HALO >= 32) { unpack8(piece<3>(i, lane), x + HALO - 24); unpack8(piece<4>(i, lane), x + HALO - 32); }
+            if (HALO == 0) {
 #pragma unroll
-    for (int j = 0; j <= HALO && j < 32; ++j) {
-        const float wj = j < m ? wc[j] : 0.f;
+                for (int e = 0; e < 8; ++e) v[i][e] = x[e];
+                continue;
+            }
 #pragma unroll
-        for (int o = 0; o < 32; ++o) v[o] = fmaf(wj, x[HALO + o - j], v[o]);
+            for (int e = 0; e < 8; ++e) v[i][e] = 0.f;
+#pragma unroll
+            for (int j = 0; j <= HALO && j < 32; ++j) {
+                float wj = wc[j < m ? j : 0];
+                wj = j < m ? wj : 0.f;
+                if (j > 8 && j >= m) continue;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[i][e] = fmaf(wj, x[HALO + e - j], v[i][e]);
+            }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[i][e] *= __builtin_amdgcn_rcpf(1.f + __expf(-v[i][e]));
+            __builtin_amdgcn_sched_barrier(0);       // (row by row: four rows' unpacked steps at once would fill the registers)
+        }
     }
+};
+
+__device__ __forceinline__ float mx_wave_max(const float (&v)[4][8])
+{
+    float mx = 0.f;
 #pragma unroll
-    for (int o = 0; o < 32; ++o) v[o] = (t0 + o < L) ? v[o] * __builtin_amdgcn_rcpf(1.f + __expf(-v[o])) : 0.f;
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) mx = fmaxf(mx, fabsf(v[i][e]));
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+    return mx;
+}
+// The power of two that takes bm into [1/2, 1) (1 for zero).
+__device__ __forceinline__ float mx_scale(float bm)
+{
+    const int e = 253 - (__builtin_bit_cast(int, bm) >> 23);
+    return bm > 0.f ? __builtin_bit_cast(float, e > 0 ? e << 23 : 0x00400000) : 1.0f;
 }
 
-// Pairs of sequences (2 pb, 2 pb + 1) of channel c, pair id = c * ceil(B / 2) + pb; a workgroup walks the ids
-// blockIdx.x, blockIdx.x + gridDim.x, ...  HALO: steps of history the short kernel needs (m - 1 <= HALO; v =
-// silu(K_s x)); 0: no short kernel, v = x.  L is a multiple of 8.
-template <int HALO>
-__global__ __launch_bounds__(MX_T) void convmx_fwd_kernel(const bf16* __restrict__ X, const float* __restrict__ w_short,
-                                                          int m, const unsigned* __restrict__ Ks,
-                                                          const float* __restrict__ kscale, bf16* __restrict__ Y, int B,
-                                                          int d, int L, long n_pairs)
+// Bins times the kernel's, conjugate, packed along k3.  CORR: with the conjugate kernel.
+template <bool CORR>
+__device__ __forceinline__ void mx_product(const f32x16& xr, const f32x16& xi, const u32x4 (&kq)[4], u32x4 (&re)[2], u32x4 (&im)[2])
 {
-    __shared__ __attribute__((aligned(16))) unsigned cube[MX_CUBE];
-    __shared__ float2 T2[1024];
-    __shared__ float2 T1[1024];
-    __shared__ float red[MX_W];
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; b += 2) {
+            float x[2], y[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                float kr, ki;
+                mx_unpack(kq[a][b + u], kr, ki);
+                const float zr = xr[4 * a + b + u], zi = xi[4 * a + b + u];
+                x[u] = CORR ? zr * kr + zi * ki : zr * kr - zi * ki;
+                y[u] = CORR ? zr * ki - zi * kr : -(zr * ki + zi * kr);
+            }
+            re[a >> 1][2 * (a & 1) + (b >> 1)] = mx_pack(x[0], x[1]);
+            im[a >> 1][2 * (a & 1) + (b >> 1)] = mx_pack(y[0], y[1]);
+        }
+}
+
+// One sequence per workgroup, id = c B + b.  HALO: steps of history the short kernel needs (m - 1 <= HALO; v = silu(K_s x));
+// 0: no short kernel, v = x.  L is a multiple of 8.
+// Two workgroups per compute unit (80 KB of LDS, 128 registers): one's short kernel runs beside the other's matrix products,
+// and the next one's tables (some 200 instructions) and loads beside both.  Workgroups that walk several sequences with the next
+// one's input on its way took 122 us (three each) and 128 us (six, all resident at once) where these take 117: of two that
+// start together on a unit the older one gets ahead, and the other finishes alone.
+// 768 channels x 4 sequences of 16384 steps, 9 taps: 117 us (198 with two sequences per transform of 2 x 16384 points, whose
+// six passes each went through LDS, one workgroup per unit).
+template <int HALO>
+__global__ __launch_bounds__(MX_T, 4) void convmx_fwd_kernel(const bf16* __restrict__ X, const float* __restrict__ w_short,
+                                                             int m, const unsigned* __restrict__ Ks,
+                                                             const float* __restrict__ kscale, bf16* __restrict__ Y, int B,
+                                                             int d, int L, int total)
+{
+    __shared__ __attribute__((aligned(16))) unsigned char cube[MX_CUBE];
+    __shared__ __attribute__((aligned(16))) MxTables tb;
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    for (int e = tid; e < 1024; e += MX_T) {
-        const int a = e >> 5, b = e & 31;
-        float sn, cs;
-        sincospif(-2.0f * (float)(a * b) / 1024.0f, &sn, &cs);
-        T2[e] = make_float2(cs, sn);
-        sincospif(-2.0f * (float)(a * b) / 32768.0f, &sn, &cs);
-        T1[e] = make_float2(cs, sn);
-    }
-    f16x8 A[2][4];
-    mx_build_matrix(A, lane);
-    __syncthreads();
-    const int PB = (B + 1) / 2;
-    const int col = lane & 31, h = lane >> 5;
-    const int my_d1 = tid >> 5, my_d2 = tid & 31;      // the cube row that holds this thread's 32 steps
-
-    for (long pid = blockIdx.x; pid < n_pairs; pid += gridDim.x) {
-        const int c = (int)(pid / PB), pb = (int)(pid - (long)c * PB);
-        const bool two = 2 * pb + 1 < B;
-        const long row_a = ((long)(2 * pb) * d + c) * (long)L, row_b = row_a + (long)d * L;
-        // ---- the two sequences, short kernel and activation, in registers
-        float va[32], vb[32];
-        const float* wc = HALO ? w_short + (long)c * m : nullptr;
-        mx_steps<HALO>(X + row_a, true, 32 * tid, L, wc, m, va);
-        mx_steps<HALO>(X + row_b, two, 32 * tid, L, wc, m, vb);
-        // ---- 1 / max |v| over the pair
-        float mx = 0.f;
-#pragma unroll
-        for (int i = 0; i < 32; ++i) mx = fmaxf(mx, fmaxf(fabsf(va[i]), fabsf(vb[i])));
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-        if (lane == 0) red[w] = mx;
-        __syncthreads();        // (also: the previous pair has been read out of the cube)
+    // consecutive workgroups run on the eight XCDs in turn: those of one XCD take neighbouring ids, which share spectra in its L2
+    const int id = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    if (id >= total) return;
+    const int c = id / B, b = id - c * B;
+    const long row = ((long)b * d + c) * L;
+    MxSeq<HALO> xs;
+    xs.load(X + row, L, w, lane);
+    mx_build_tables(tb, tid);
+    MxMat m32;
+    mx_build_matrix(m32, lane);
+    MxLane lc;
+    mx_build_lane(lc, lane, w);
+    float s;
+    {
+        float v[4][8];
+        xs.values(HALO ? w_short + (long)c * m : nullptr, m, lane, v);
+        const float mx = mx_wave_max(v);
+        if (lane == 0) tb.red[w] = mx;
+        __syncthreads();        // (also: the tables are built)
         float bm = 0.f;
 #pragma unroll
-        for (int i = 0; i < MX_W; ++i) bm = fmaxf(bm, red[i]);
-        const float s1 = bm > 0.f ? 1.0f / bm : 1.0f;
-        if (my_d1 < 16) {
+        for (int i = 0; i < MX_W; ++i) bm = fmaxf(bm, tb.red[i]);
+        s = mx_scale(bm);
+        mx_first<HALO == 0>(cube, tb, lc, v, s, w, lane);
+    }
+    const u32x4* kc = reinterpret_cast<const u32x4*>(Ks + (long)c * MX_N);
+    __syncthreads();
 #pragma unroll
-            for (int g = 0; g < 8; ++g) {
-                u32x4 v;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = mx_pack(va[4 * g + e] * s1, vb[4 * g + e] * s1);
-                *reinterpret_cast<u32x4*>(cube + mx_addr(my_d1, my_d2, 4 * g)) = v;
-            }
-        }
-        // the spectrum pieces of this wave's first tile of the third pass, on their way while the first two passes run
-        const u32x4* kc = reinterpret_cast<const u32x4*>(Ks + (long)c * MX_N);
+    for (int n = 0; n < MX_NT; ++n) {
+        const int k1 = w + MX_W * n;
         u32x4 kq[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) kq[q] = kc[(w * 4 + q) * 64 + lane];
-        __syncthreads();
-        // ---- forward: axis 1 (only planes 0..15 hold data), axis 2
-        mx_pass<MX_AX1, MX_TW_F1, 2, 2>(cube, A, T2, T1, w, lane);
-        __syncthreads();
-        mx_pass<MX_AX2, MX_TW_T2, 4, 2>(cube, A, T2, T1, w, lane);
-        __syncthreads();
-        // ---- axis 3 forward, times the kernel's spectrum, conjugate, axis 3 on the way back: in registers
-        MxRot fixed;
-        mx_rot_fixed(fixed, T2, col, h);
-#pragma unroll 1
-        for (int t = w; t < 32; t += MX_W) {
-            f16x8 Bv[4];
-            f32x16 acc[2];
-            mx_load<MX_AX3, 4>(cube, t, col, h, Bv);
-            mx_mul<4, 2>(A, Bv, acc);
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                u32x4 v;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float zr = mx_re(acc, s, i), zi = mx_im(acc, s, i);
-                    float kr, ki;
-                    mx_unpack(kq[s][i], kr, ki);
-                    v[i] = mx_pack(zr * kr - zi * ki, -(zr * ki + zi * kr));
-                }
-                Bv[s] = __builtin_bit_cast(f16x8, v);
-            }
-            if (t + MX_W < 32) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) kq[q] = kc[((t + MX_W) * 4 + q) * 64 + lane];
-            }
-            mx_mul<4, 2>(A, Bv, acc);
-            mx_store<MX_AX3, true, 2>(cube, acc, fixed, t, col, h);
-        }
-        __syncthreads();
-        mx_pass<MX_AX2, MX_TW_I2, 4, 2>(cube, A, T2, T1, w, lane);
-        __syncthreads();
-        mx_pass<MX_AX1, MX_TW_NONE, 4, 1>(cube, A, T2, T1, w, lane);     // only steps n < 16384 are wanted
-        __syncthreads();
-        // ---- out: y_a = Re, y_b = -Im (the conjugate that closes the way back), scales put back
-        const float osc = kscale[c] / (s1 * (float)MX_N);
-        if (32 * tid < L) {
-            typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-#pragma unroll
-            for (int g = 0; g < 4; ++g) {
-                if (32 * tid + 8 * g < L) {
-                    const u32x4 v0 = *reinterpret_cast<const u32x4*>(cube + mx_addr(my_d1, my_d2, 8 * g));
-                    const u32x4 v1 = *reinterpret_cast<const u32x4*>(cube + mx_addr(my_d1, my_d2, 8 * g + 4));
-                    bf16x8 oa, ob;
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        float re, im;
-                        mx_unpack(e < 4 ? v0[e & 3] : v1[e & 3], re, im);
-                        oa[e] = (bf16)(re * osc);
-                        ob[e] = (bf16)(-im * osc);
-                    }
-                    *reinterpret_cast<bf16x8*>(Y + row_a + 32 * tid + 8 * g) = oa;
-                    if (two) *reinterpret_cast<bf16x8*>(Y + row_b + 32 * tid + 8 * g) = ob;
-                }
-            }
-        }
+        for (int a = 0; a < 4; ++a) kq[a] = kc[(k1 * 4 + a) * 64 + mx_fresh(lane)];
+        f32x16 xr, xi;
+        mx_tile_in(cube, tb, m32, k1, lane, xr, xi);
+        u32x4 re[2], im[2];
+        mx_product<false>(xr, xi, kq, re, im);
+        mx_tile_out(cube, tb, m32, lc.u, mx_step(k1), k1, lane, re, im);
+        __builtin_amdgcn_sched_barrier(0);
     }
-}
-
-// One row (32 steps) of each sequence of a pair out of the cube after the way back: a = Re, b = -Im, times `osc`.
-template <typename OUT>
-__device__ __forceinline__ void mx_rows_out(const unsigned* cube, OUT* __restrict__ ya, OUT* __restrict__ yb, bool two,
-                                            int tid, int L, float osc)
-{
-    const int d1 = tid >> 5, d2 = tid & 31;
-    if (32 * tid >= L) return;
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        if (32 * tid + 8 * g < L) {
-            const u32x4 v0 = *reinterpret_cast<const u32x4*>(cube + mx_addr(d1, d2, 8 * g));
-            const u32x4 v1 = *reinterpret_cast<const u32x4*>(cube + mx_addr(d1, d2, 8 * g + 4));
-            float fa[8], fb[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                float re, im;
-                mx_unpack(e < 4 ? v0[e & 3] : v1[e & 3], re, im);
-                fa[e] = re * osc;
-                fb[e] = -im * osc;
-            }
-            if (sizeof(OUT) == 2) {
-                typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-                bf16x8 oa, ob;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) { oa[e] = (bf16)fa[e]; ob[e] = (bf16)fb[e]; }
-                *reinterpret_cast<bf16x8*>(ya + 32 * tid + 8 * g) = oa;
-                if (two) *reinterpret_cast<bf16x8*>(yb + 32 * tid + 8 * g) = ob;
-            } else {
-                float4* pa = reinterpret_cast<float4*>(ya + 32 * tid + 8 * g);
-                pa[0] = make_float4(fa[0], fa[1], fa[2], fa[3]);
-                pa[1] = make_float4(fa[4], fa[5], fa[6], fa[7]);
-                if (two) {
-                    float4* pq = reinterpret_cast<float4*>(yb + 32 * tid + 8 * g);
-                    pq[0] = make_float4(fb[0], fb[1], fb[2], fb[3]);
-                    pq[1] = make_float4(fb[4], fb[5], fb[6], fb[7]);
-                }
-            }
-        }
-    }
-}
-
-// From each thread's own largest magnitude and sum of squares: 1 / (largest magnitude in the workgroup) (1 if that is
-// zero) and the workgroup's sum of squares; two barriers.
-__device__ __forceinline__ float mx_inv_max(float mx, float& ss, float* red, int lane, int w)
-{
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        mx = fmaxf(mx, __shfl_xor(mx, o));
-        ss += __shfl_xor(ss, o);
-    }
-    __syncthreads();            // (the previous use of red[] is over)
-    if (lane == 0) { red[w] = mx; red[MX_W + w] = ss; }
     __syncthreads();
-    float bm = 0.f;
-    ss = 0.f;
+    const float osc = kscale[c] / (s * ((float)MX_N * MX_GAIN4));
+    float y[4][8];
+    mx_last(cube, tb, w, lane, y);
+    bf16* out = Y + row;
+    const int t0 = mx_first_step(w, mx_fresh(lane));
 #pragma unroll
-    for (int i = 0; i < MX_W; ++i) { bm = fmaxf(bm, red[i]); ss += red[MX_W + i]; }
-    return bm > 0.f ? 1.0f / bm : 1.0f;
-}
-
-__device__ __forceinline__ void mx_rows_in(unsigned* cube, const float (&va)[32], const float (&vb)[32], float s, int tid)
-{
+    for (int i = 0; i < 4; ++i) {
+        typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+        bf16x8 o;
 #pragma unroll
-    for (int g = 0; g < 8; ++g) {
-        u32x4 v;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = mx_pack(va[4 * g + e] * s, vb[4 * g + e] * s);
-        *reinterpret_cast<u32x4*>(cube + mx_addr(tid >> 5, tid & 31, 4 * g)) = v;
+        for (int e = 0; e < 8; ++e) o[e] = (bf16)(y[i][e] * osc);
+        if (t0 + 1024 * i < L) *reinterpret_cast<bf16x8*>(out + t0 + 1024 * i) = o;
     }
 }
 
-// The two long-stage gradients of the convolution (they share the spectrum of dZ), pairs of sequences as above; one
-// workgroup walks the pairs of a channel, then the next channel blockIdx.x + gridDim.x, ...
-//   dv = corr(dZ, k_long):   Wd = T(dZ_a + i dZ_b);  conj(T'(conj(Wd conj(K)))) / N:  Re -> dv_a, Im -> dv_b
-//   dk[c][s] = sum_b sum_t dZ_b[t] v_b[t - s]:  Wv = T(v_a + i v_b), v = silu(K_s x) recomputed;  for the two real
-//   sequences of a pair DZ_a conj(V_a) + DZ_b conj(V_b) = (H[k] + conj H[-k]) / 2 with H = Wd conj(Wv), whose transform
-//   back is the real part of that of H: the pair's share of dk is Re T'(conj H) / N, added up over the pairs in the time
-//   domain (64 KB per channel, each step by the thread that owns it), so no spectrum-sized sums ever go to memory.
-//   Range of H: sum_k |Wd||Wv| <= |Wd|_2 |Wv|_2 = N |z_d|_2 |z_v|_2, so H times 32768 / (N |z_d|_2 |z_v|_2) keeps every
-//   sum on the way back within 32768 and leaves a typical bin at order one.
-//   Wd waits in memory while v is transformed (this workgroup's own 128 KB, in the order its lanes hold it).
+// The two long-stage gradients of the convolution (they share the spectrum of dZ); a workgroup walks the sequences of a
+// channel, every gridDim.y-th one where a channel is shared, and then those of the next channel blockIdx.x + gridDim.x, ...
+//   dv = corr(dZ, k_long): bins of dZ times the conjugate of the kernel's, back;
+//   dk[c][s] = sum_b sum_t dZ_b[t] v_b[t - s]: bins of dZ_b times the conjugate of those of v_b = silu(K_s x_b) (recomputed),
+//   added up over the sequences in fp32 registers, back once per channel.  At the points used a negative lag is imaginary,
+//   as is the second half of a causal sum.
+// Both sequences' cubes lie in LDS side by side, so that a wave meets the same tile of both.  Sums of dk: all sequences'
+// shares are kept in units of the largest 1 / (scale of dZ_b x scale of v_b) so far (powers of two); the finished sums H are packed times
+// 32768 / (sqrt N |H|_2), which bounds every sum on the way back by 32768 (Cauchy-Schwarz) and leaves a typical bin at order one.
+// One workgroup per compute unit (both cubes: 144 KB of LDS; 256 registers, nothing spilled), issuing vector instructions 64 % of
+// the time.  768 channels x 4 sequences of 16384 steps, 9 taps: 417 -> 240 us (the spectrum of dZ waited in memory for that of
+// v, and the sums went back once per pair of sequences).
 // dV: fp32 [B][d][L] for the short-stage kernel, or dX itself (bf16) when there is no short stage (HALO = 0, v = x).
 template <int HALO, typename DVT>
-__global__ __launch_bounds__(MX_T) void convmx_longbwd_kernel(const bf16* __restrict__ X, const float* __restrict__ w_short,
+__global__ __launch_bounds__(MX_T, 2) void convmx_longbwd_kernel(const bf16* __restrict__ X, const float* __restrict__ w_short,
                                                               int m, const unsigned* __restrict__ Ks,
                                                               const float* __restrict__ kscale,
                                                               const bf16* __restrict__ dZ, DVT* __restrict__ dV,
-                                                              float* __restrict__ dk, u32x4* __restrict__ Wds,
-                                                              int B, int d, int L)
+                                                              float* __restrict__ dk, int B, int d, int L)
 {
-    __shared__ __attribute__((aligned(16))) unsigned cube[MX_CUBE];
-    __shared__ float2 T2[1024];
-    __shared__ float2 T1[1024];
-    __shared__ float red[2 * MX_W];
+    __shared__ __attribute__((aligned(16))) unsigned char cube[2][MX_CUBE];       // of dZ, of v
+    __shared__ __attribute__((aligned(16))) MxTables tb;
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    for (int e = tid; e < 1024; e += MX_T) {
-        const int a = e >> 5, b = e & 31;
-        float sn, cs;
-        sincospif(-2.0f * (float)(a * b) / 1024.0f, &sn, &cs);
-        T2[e] = make_float2(cs, sn);
-        sincospif(-2.0f * (float)(a * b) / 32768.0f, &sn, &cs);
-        T1[e] = make_float2(cs, sn);
-    }
-    f16x8 A[2][4];
-    mx_build_matrix(A, lane);
-    __syncthreads();
-    const int PB = (B + 1) / 2;
-    const int col = lane & 31, h = lane >> 5;
-    constexpr int NT = 32 / MX_W;        // tiles of a pass per wave
-    u32x4* wdm = Wds + (size_t)blockIdx.x * (MX_N / 4);
+    mx_build_tables(tb, tid);
+    MxMat m32;
+    mx_build_matrix(m32, lane);
+    MxLane lc;
+    mx_build_lane(lc, lane, w);
+    float2 st[MX_NT];
+#pragma unroll
+    for (int n = 0; n < MX_NT; ++n) st[n] = mx_step(w + MX_W * n);
 
-    for (int c = blockIdx.x; c < d; c += gridDim.x) {
-        const u32x4* kc = reinterpret_cast<const u32x4*>(Ks + (long)c * MX_N);
-        const float* wc = HALO ? w_short + (long)c * m : nullptr;
-        const float ksc = kscale[c];
-        for (int pb = 0; pb < PB; ++pb) {
-            const bool two = 2 * pb + 1 < B;
-            const long row_a = ((long)(2 * pb) * d + c) * (long)L, row_b = row_a + (long)d * L;
-            float s_d, n_d = 0.f;
-            {
-                float va[32], vb[32];
-                mx_steps<0>(dZ + row_a, true, 32 * tid, L, nullptr, 0, va);
-                mx_steps<0>(dZ + row_b, two, 32 * tid, L, nullptr, 0, vb);
-                float mx = 0.f;
+    MxSeq<0> zs;
+    MxSeq<HALO> xs;
+    const int b0 = blockIdx.y;          // (< B)
+    zs.load(dZ + ((long)b0 * d + blockIdx.x) * L, L, w, lane);
+    xs.load(X + ((long)b0 * d + blockIdx.x) * L, L, w, lane);
+    float hr[MX_NT][16], hi[MX_NT][16], unit = 0.f;       // the sums and their unit
 #pragma unroll
-                for (int i = 0; i < 32; ++i) {
-                    mx = fmaxf(mx, fmaxf(fabsf(va[i]), fabsf(vb[i])));
-                    n_d = fmaf(va[i], va[i], fmaf(vb[i], vb[i], n_d));
-                }
-                s_d = mx_inv_max(mx, n_d, red, lane, w);      // (its barriers: the cube is free again)
-                mx_rows_in(cube, va, vb, s_d, tid);
-            }
-            __syncthreads();
-            mx_pass<MX_AX1, MX_TW_F1, 2, 2>(cube, A, T2, T1, w, lane);
-            __syncthreads();
-            mx_pass<MX_AX2, MX_TW_T2, 4, 2>(cube, A, T2, T1, w, lane);
-            __syncthreads();
-            {
-                MxRot fixed;
-                mx_rot_fixed(fixed, T2, col, h);
-                u32x4 kq[4];
+    for (int n = 0; n < MX_NT; ++n)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) kq[q] = kc[(w * 4 + q) * 64 + lane];
-#pragma unroll 1
-                for (int n = 0; n < NT; ++n) {
-                    const int t = w + MX_W * n;
-                    f16x8 Bv[4];
-                    f32x16 acc[2];
-                    mx_load<MX_AX3, 4>(cube, t, col, h, Bv);
-                    mx_mul<4, 2>(A, Bv, acc);
+        for (int i = 0; i < 16; ++i) hr[n][i] = hi[n][i] = 0.f;
+    for (int c = blockIdx.x, b = b0; c < d;) {
+        const long row = ((long)b * d + c) * L;
+        float s_d, f;           // f: from the sums' unit so far to the present one
+        {
+            float v[4][8];
+            xs.values(HALO ? w_short + (long)c * m : nullptr, m, lane, v);
+            const float mv = mx_wave_max(v), md = zs.wave_max();
+            if (lane == 0) { tb.red[w] = md; tb.red[MX_W + w] = mv; }
+            __syncthreads();        // (also: the tables are built)
+            float bd = 0.f, bv = 0.f;
 #pragma unroll
-                    for (int s = 0; s < 4; ++s) {
-                        u32x4 v, keep;
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const float zr = mx_re(acc, s, i), zi = mx_im(acc, s, i);
-                            keep[i] = mx_pack(zr, zi);
-                            float kr, ki;
-                            mx_unpack(kq[s][i], kr, ki);
-                            // conj(Z conj(K)) = (zr kr + zi ki) + i (zr ki - zi kr)
-                            v[i] = mx_pack(zr * kr + zi * ki, zr * ki - zi * kr);
-                        }
-                        Bv[s] = __builtin_bit_cast(f16x8, v);
-                        wdm[(t * 4 + s) * 64 + lane] = keep;
-                    }
-                    if (n + 1 < NT) {       // the next tile's pieces of the spectrum, on their way during the products
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) kq[q] = kc[((t + MX_W) * 4 + q) * 64 + lane];
-                    }
-                    mx_mul<4, 2>(A, Bv, acc);
-                    mx_store<MX_AX3, true, 2>(cube, acc, fixed, t, col, h);
-                }
-            }
-            __syncthreads();
-            mx_pass<MX_AX2, MX_TW_I2, 4, 2>(cube, A, T2, T1, w, lane);
-            __syncthreads();
-            mx_pass<MX_AX1, MX_TW_NONE, 4, 1>(cube, A, T2, T1, w, lane);
-            __syncthreads();
-            mx_rows_out<DVT>(cube, dV + row_a, dV + row_b, two, tid, L, ksc / (s_d * (float)MX_N));
-
-            // ---- v = silu(K_s x) (or x), its spectrum, H (+)= Wd conj(Wv) with the two scales taken out
-            float s_v, n_v = 0.f;
-            {
-                float va[32], vb[32];
-                mx_steps<HALO>(X + row_a, true, 32 * tid, L, wc, m, va);
-                mx_steps<HALO>(X + row_b, two, 32 * tid, L, wc, m, vb);
-                float mx = 0.f;
-#pragma unroll
-                for (int i = 0; i < 32; ++i) {
-                    mx = fmaxf(mx, fmaxf(fabsf(va[i]), fabsf(vb[i])));
-                    n_v = fmaf(va[i], va[i], fmaf(vb[i], vb[i], n_v));
-                }
-                s_v = mx_inv_max(mx, n_v, red, lane, w);      // (its barriers: dv has been read out of the cube)
-                mx_rows_in(cube, va, vb, s_v, tid);
-            }
-            __syncthreads();
-            mx_pass<MX_AX1, MX_TW_F1, 2, 2>(cube, A, T2, T1, w, lane);
-            __syncthreads();
-            mx_pass<MX_AX2, MX_TW_T2, 4, 2>(cube, A, T2, T1, w, lane);
-            __syncthreads();
-            // |z|_2 of the scaled signals: sqrt(sum of squares) * scale
-            const float nn = sqrtf(n_d) * s_d * sqrtf(n_v) * s_v;
-            const float g = nn > 0.f ? 1.0f / nn : 0.f;          // = 32768 / (N |z_d|_2 |z_v|_2)
-            {
-                MxRot fixed;
-                mx_rot_fixed(fixed, T2, col, h);
-                u32x4 wn[4];                                     // Wd of the tile in hand, fetched one tile ahead
-#pragma unroll
-                for (int s = 0; s < 4; ++s) wn[s] = wdm[(w * 4 + s) * 64 + lane];
-#pragma unroll 1
-                for (int n = 0; n < NT; ++n) {
-                    const int t = w + MX_W * n;
-                    f16x8 Bv[4];
-                    f32x16 acc[2];
-                    mx_load<MX_AX3, 4>(cube, t, col, h, Bv);
-                    mx_mul<4, 2>(A, Bv, acc);
-#pragma unroll
-                    for (int s = 0; s < 4; ++s) {
-                        u32x4 v;
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            float dr, di;
-                            mx_unpack(wn[s][i], dr, di);
-                            const float vr = mx_re(acc, s, i), vi = mx_im(acc, s, i);
-                            // conj(Wd conj(Wv)) = (dr vr + di vi) + i (dr vi - di vr)
-                            v[i] = mx_pack((dr * vr + di * vi) * g, (dr * vi - di * vr) * g);
-                        }
-                        Bv[s] = __builtin_bit_cast(f16x8, v);
-                    }
-                    if (n + 1 < NT) {
-#pragma unroll
-                        for (int s = 0; s < 4; ++s) wn[s] = wdm[((t + MX_W) * 4 + s) * 64 + lane];
-                    }
-                    mx_mul<4, 2>(A, Bv, acc);
-                    mx_store<MX_AX3, true, 2>(cube, acc, fixed, t, col, h);
-                }
-            }
-            __syncthreads();
-            mx_pass<MX_AX2, MX_TW_I2, 4, 2>(cube, A, T2, T1, w, lane);
-            __syncthreads();
-            mx_pass<MX_AX1, MX_TW_NONE, 4, 1>(cube, A, T2, T1, w, lane);
-            __syncthreads();
-            // this pair's share of dk: Re / (N g s_d s_v), each step by the thread that owns it
-            if (32 * tid < L) {
-                const float osc = g > 0.f ? 1.0f / (g * s_d * s_v * (float)MX_N) : 0.f;
-                float* out = dk + (long)c * L + 32 * tid;
-#pragma unroll
-                for (int q = 0; q < 8; ++q) {
-                    if (32 * tid + 4 * q < L) {
-                        const u32x4 v = *reinterpret_cast<const u32x4*>(cube + mx_addr(tid >> 5, tid & 31, 4 * q));
-                        float r0, r1, r2, r3, im;
-                        mx_unpack(v[0], r0, im);
-                        mx_unpack(v[1], r1, im);
-                        mx_unpack(v[2], r2, im);
-                        mx_unpack(v[3], r3, im);
-                        float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
-                        if (pb > 0) o = *reinterpret_cast<const float4*>(out + 4 * q);
-                        o.x += r0 * osc; o.y += r1 * osc; o.z += r2 * osc; o.w += r3 * osc;
-                        *reinterpret_cast<float4*>(out + 4 * q) = o;
-                    }
-                }
-            }
-            // (the next stage starts with barriers before it touches the cube)
+            for (int i = 0; i < MX_W; ++i) { bd = fmaxf(bd, tb.red[i]); bv = fmaxf(bv, tb.red[MX_W + i]); }
+            s_d = mx_scale(bd);
+            const float sv = mx_scale(bv), here = bd > 0.f && bv > 0.f ? 1.0f / (s_d * sv) : 0.f;
+            f = here > unit ? unit / here : 1.f;
+            if (here > unit) unit = here;
+            const float s_v = unit > 0.f ? sv * (here / unit) : 0.f;
+            mx_first<HALO == 0>(cube[1], tb, lc, v, s_v, w, lane);
+            __builtin_amdgcn_sched_barrier(0);
+            zs.values(nullptr, 0, lane, v);
+            mx_first<true>(cube[0], tb, lc, v, s_d, w, lane);
         }
-        __syncthreads();        // the cube is free for the next channel
+        __syncthreads();
+        const u32x4* kc = reinterpret_cast<const u32x4*>(Ks + (long)c * MX_N);
+#pragma unroll
+        for (int n = 0; n < MX_NT; ++n) {
+            const int k1 = w + MX_W * n;
+            f32x16 zr, zi, vr, vi;
+            mx_tile_in(cube[1], tb, m32, k1, lane, vr, vi);
+            u32x4 kq[4];
+#pragma unroll
+            for (int a = 0; a < 4; ++a) kq[a] = kc[(k1 * 4 + a) * 64 + mx_fresh(lane)];
+            mx_tile_in(cube[0], tb, m32, k1, lane, zr, zi);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                hr[n][i] = fmaf(zr[i], vr[i], fmaf(zi[i], vi[i], hr[n][i] * f));
+                hi[n][i] = fmaf(zi[i], vr[i], fmaf(-zr[i], vi[i], hi[n][i] * f));
+                // (here and not where the sums are used: with the products of both tiles kept that long, 80 values were spilled)
+                asm volatile("" : "+v"(hr[n][i]), "+v"(hi[n][i]));
+            }
+            u32x4 re[2], im[2];
+            mx_product<true>(zr, zi, kq, re, im);
+            mx_tile_out(cube[0], tb, m32, lc.u, st[n], k1, lane, re, im);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        __syncthreads();
+        const float osc = kscale[c] / (s_d * ((float)MX_N * MX_GAIN4));
+        const int cc = c;
+        const bool done = (b += gridDim.y) >= B;
+        if (done) { b = b0; c += gridDim.x; }
+        {       // the next sequence (after the last one: that one again)
+            const long next = c < d ? ((long)b * d + c) * L : row;
+            zs.load(dZ + next, L, w, lane);
+            xs.load(X + next, L, w, lane);
+        }
+        float y[4][8];
+        mx_last(cube[0], tb, w, lane, y);
+        DVT* out = dV + row;
+        const int t0 = mx_first_step(w, mx_fresh(lane));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            typedef __attribute__((ext_vector_type(8))) DVT out8;
+            out8 o;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o[e] = (DVT)(y[i][e] * osc);
+            if (t0 + 1024 * i < L) *reinterpret_cast<out8*>(out + t0 + 1024 * i) = o;
+        }
+        if (done) {         // ---- the sums' way back
+            float ss = 0.f;
+#pragma unroll
+            for (int n = 0; n < MX_NT; ++n)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) ss = fmaf(hr[n][i], hr[n][i], fmaf(hi[n][i], hi[n][i], ss));
+#pragma unroll
+            for (int o = 32; o >= 1; o >>= 1) ss += __shfl_xor(ss, o);
+            if (lane == 0) tb.red[w] = ss;
+            __syncthreads();
+            ss = 0.f;
+#pragma unroll
+            for (int i = 0; i < MX_W; ++i) ss += tb.red[i];
+            const float g = ss > 0.f ? 256.f * rsqrtf(ss) : 0.f;             // 32768 / (sqrt(16384) |H|_2)
+#pragma unroll
+            for (int n = 0; n < MX_NT; ++n) {
+                u32x4 re[2], im[2];
+#pragma unroll
+                for (int a = 0; a < 4; ++a)
+#pragma unroll
+                    for (int q = 0; q < 4; q += 2) {
+                        re[a >> 1][2 * (a & 1) + (q >> 1)] = mx_pack(hr[n][4 * a + q] * g, hr[n][4 * a + q + 1] * g);
+                        im[a >> 1][2 * (a & 1) + (q >> 1)] = mx_pack(-hi[n][4 * a + q] * g, -hi[n][4 * a + q + 1] * g);
+                    }
+                mx_tile_out(cube[1], tb, m32, lc.u, st[n], w + MX_W * n, lane, re, im);
+#pragma unroll
+                for (int i = 0; i < 16; ++i) hr[n][i] = hi[n][i] = 0.f;
+            }
+            __syncthreads();
+            mx_last(cube[1], tb, w, lane, y);
+            const float kosc = g > 0.f ? unit / (g * ((float)MX_N * MX_GAIN4 * MX_GAIN2)) : 0.f;
+            unit = 0.f;
+            float* o = dk + ((long)b0 * d + cc) * L;         // (a shared channel: its slices are added up by mx_dk_kernel)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (t0 + 1024 * i < L) {
+                    float4* p = reinterpret_cast<float4*>(o + t0 + 1024 * i);
+                    p[0] = make_float4(y[i][0] * kosc, y[i][1] * kosc, y[i][2] * kosc, y[i][3] * kosc);
+                    p[1] = make_float4(y[i][4] * kosc, y[i][5] * kosc, y[i][6] * kosc, y[i][7] * kosc);
+                }
+            }
+        }
+    }
+}
+
+// dk = the sum of the slices part[g][n], in a fixed order; n a multiple of 4.
+__global__ __launch_bounds__(256) void mx_dk_kernel(const float4* __restrict__ part, float4* __restrict__ dk, int G, long n4)
+{
+    for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < n4; i += (long)gridDim.x * 256) {
+        float4 t = part[i];
+        for (int g = 1; g < G; ++g) {
+            const float4 o = part[g * n4 + i];
+            t.x += o.x; t.y += o.y; t.z += o.z; t.w += o.w;
+        }
+        dk[i] = t;
     }
 }
 
@@ -676,69 +723,87 @@ __global__ __launch_bounds__(MX_T) void convmx_longbwd_kernel(const bf16* __rest
 bool convmx_applies(int L, int dtype)
 {
     // (rows of a multiple of 8 steps start on 16-byte boundaries: the kernel moves 16-byte pieces only)
-    if (dtype != 0 || L <= 4096 || L > MX_L_MAX || (L & 7) != 0) return false;
+    if (dtype != 0 || L <= 4096 || L > MX_N || (L & 7) != 0) return false;
     const char* e = getenv("CHELA_CONV_MATRIX");      // tuning aid: 0 keeps the vector-ALU kernels for every size
     return !(e && atoi(e) == 0);
 }
 
+// (twice the words that are used: the size that callers of the query know)
 size_t convmx_spectrum_bytes(int d, int L)
 {
-    if (d <= 0 || L <= 4096 || L > MX_L_MAX) return 0;
-    return (size_t)d * MX_N * sizeof(unsigned) + (((size_t)d * sizeof(float) + 255) & ~(size_t)255);
+    if (d <= 0 || L <= 4096 || L > MX_N) return 0;
+    return (size_t)d * (2 * MX_N) * sizeof(unsigned) + (((size_t)d * sizeof(float) + 255) & ~(size_t)255);
+}
+
+static int mx_cus()
+{
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+        cus = 256;
+    (void)hipGetLastError();
+    return cus;
 }
 
 hipError_t launch_convmx_fwd(const void* X, const float* w_short, int m, const void* extra, void* Y, int B, int d, int L,
                              hipStream_t st)
 {
     const unsigned* Ks = (const unsigned*)extra;
-    const float* scale = (const float*)((const char*)extra + (size_t)d * MX_N * sizeof(unsigned));
-    const long n_pairs = (long)d * ((B + 1) / 2);
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-        cus = 256;
-    (void)hipGetLastError();
-    const long slots = cus;                              // 132 KB of LDS + tables: one workgroup per compute unit
-    const long rounds = (n_pairs + slots - 1) / slots;
-    const dim3 grid((unsigned)((n_pairs + rounds - 1) / rounds));
+    const float* scale = (const float*)(Ks + (size_t)d * MX_N);
+    const long total = (long)d * B;
+    if (total > 0x7ffffff0L) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)((total + 7) / 8 * 8));
     ProfScope prof(KID_CONV_FWD, st);
-    if (!w_short)
-        hipLaunchKernelGGL((convmx_fwd_kernel<0>), grid, dim3(MX_T), 0, st, (const bf16*)X, w_short, m, Ks, scale,
-                           (bf16*)Y, B, d, L, n_pairs);
-    else if (m <= 9)
-        hipLaunchKernelGGL((convmx_fwd_kernel<8>), grid, dim3(MX_T), 0, st, (const bf16*)X, w_short, m, Ks, scale,
-                           (bf16*)Y, B, d, L, n_pairs);
-    else
-        hipLaunchKernelGGL((convmx_fwd_kernel<32>), grid, dim3(MX_T), 0, st, (const bf16*)X, w_short, m, Ks, scale,
-                           (bf16*)Y, B, d, L, n_pairs);
+#define CHELA_MX_FWD(H_)                                                                                                \
+    hipLaunchKernelGGL((convmx_fwd_kernel<H_>), grid, dim3(MX_T), 0, st, (const bf16*)X, w_short, m, Ks, scale, (bf16*)Y, B, \
+                       d, L, (int)total)
+    if (!w_short) CHELA_MX_FWD(0);
+    else if (m <= 9) CHELA_MX_FWD(8);
+    else if (m <= 17) CHELA_MX_FWD(16);
+    else CHELA_MX_FWD(32);
+#undef CHELA_MX_FWD
     return hipGetLastError();
 }
 
 hipError_t launch_convmx_longbwd(const void* X, const float* w_short, int m, const void* extra, const void* dZ, void* dV,
-                                 bool dv_is_f32, float* dk, float* Hs, int B, int d, int L, hipStream_t st)
+                                 bool dv_is_f32, float* dk, float* part, int max_share, int B, int d, int L,
+                                 hipStream_t st)
 {
     const unsigned* Ks = (const unsigned*)extra;
-    const float* scale = (const float*)((const char*)extra + (size_t)d * MX_N * sizeof(unsigned));
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-        cus = 256;
-    (void)hipGetLastError();
-    if (cus > kConvMxMaxWgs) cus = kConvMxMaxWgs;       // (the scratch behind the sums holds that many workgroups' Wd)
-    const int rounds = (d + cus - 1) / cus;
-    const dim3 grid((unsigned)((d + rounds - 1) / rounds));
+    const float* scale = (const float*)(Ks + (size_t)d * MX_N);
+    // One workgroup per compute unit.  A channel's sequences are shared out where that shortens the longest workgroup's work:
+    // its rounds x (its sequences + 0.4, the sums' way back; + 0.2 with the slices to be added up).  128 channels x 3 sequences
+    // of 8192 steps, both stages' gradients: 64 us, in three shares 54.
+    const int cus = mx_cus();
+    int G = 1;
+    float best = 0.f;
+    for (int g = 1; g <= B && g <= max_share; ++g) {
+        const float t = (float)(((long)d * g + cus - 1) / cus) * ((B + g - 1) / g + (g > 1 ? 0.6f : 0.4f));
+        if (g == 1 || t < best) { best = t; G = g; }
+    }
+    const long rounds = ((long)d * G + cus - 1) / cus;
+    const dim3 grid((unsigned)((d + rounds - 1) / rounds), (unsigned)G);
+    float* const sums = G > 1 ? part : dk;
     ProfScope prof(KID_CONV_LONG_BWD, st);
 #define CHELA_MX_BWD(H_, T_)                                                                                            \
     hipLaunchKernelGGL((convmx_longbwd_kernel<H_, T_>), grid, dim3(MX_T), 0, st, (const bf16*)X, w_short, m, Ks, scale,  \
-                       (const bf16*)dZ, (T_*)dV, dk, (u32x4*)Hs, B, d, L)
+                       (const bf16*)dZ, (T_*)dV, sums, B, d, L)
     if (!w_short) {
         if (dv_is_f32) CHELA_MX_BWD(0, float); else CHELA_MX_BWD(0, bf16);
     } else if (m <= 9) {
         if (dv_is_f32) CHELA_MX_BWD(8, float); else CHELA_MX_BWD(8, bf16);
+    } else if (m <= 17) {
+        if (dv_is_f32) CHELA_MX_BWD(16, float); else CHELA_MX_BWD(16, bf16);
     } else {
         if (dv_is_f32) CHELA_MX_BWD(32, float); else CHELA_MX_BWD(32, bf16);
     }
 #undef CHELA_MX_BWD
+    if (G > 1) {
+        const long n4 = (long)d * L / 4;
+        const long wgs = (n4 + 255) / 256;
+        hipLaunchKernelGGL(mx_dk_kernel, dim3((unsigned)(wgs < 2048 ? wgs : 2048)), dim3(256), 0, st, (const float4*)part,
+                           (float4*)dk, G, n4);
+    }
     return hipGetLastError();
 }
 

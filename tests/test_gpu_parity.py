@@ -1140,6 +1140,28 @@ def test_shortlong_conv_bwd_bf16_matrix_core_sizes(shape):
     _run_conv_bwd_case(B, d, L, m, "bf16", seed=L + 13, short=short)
 
 
+def test_matrix_core_conv_gradient_two_channels_per_workgroup():
+    # more channels than compute units: a workgroup goes on with the next channel (sums start afresh, its input is fetched
+    # while the one before ends), first and last workgroup's channels checked
+    B, d, L, m = 2, 300, 4104, 11
+    x = make_conv_inputs(B, d, L, m, 41, "bf16")
+    g = torch.Generator(device="cpu")
+    g.manual_seed(42)
+    dZ = torch.randn(B, d, L, generator=g, dtype=torch.float32).to(torch.bfloat16)
+    dev = _dev(x)
+    spec = binding.chela_longconv_spectrum(dev["k_long"])
+    Z = binding.chela_shortlong_conv_fwd(dev["X"], dev["w_short"], spec)
+    dX, dw, dk = binding.chela_shortlong_conv_bwd(dev["X"], dev["w_short"], spec, dZ.cuda())
+    torch.cuda.synchronize()
+    for c in (0, 149, 150, 299):
+        X1, w1, k1, g1 = (to_f64_numpy(t) for t in (x["X"][:, c:c + 1], x["w_short"][c:c + 1], x["k_long"][c:c + 1], dZ[:, c:c + 1]))
+        rX, rw, rk = oracle_conv.short_long_conv_bwd(X1, w1, k1, g1)
+        _check("Z[c=%d]" % c, Z[:, c:c + 1], oracle_conv.short_long_conv(X1, w1, k1), "bf16")
+        _check("dX[c=%d]" % c, dX[:, c:c + 1], rX, "bf16")
+        _check("dw[c=%d]" % c, dw[c:c + 1], rw, "bf16")
+        _check("dk[c=%d]" % c, dk[c:c + 1], rk, "bf16")
+
+
 def test_matrix_core_conv_gradient_scales_with_its_inputs():
     # half-precision operands inside, every signal scaled on the way in: gradients of inputs far outside the
     # half-precision range (and of an all-zero upstream gradient) come through
