@@ -14,7 +14,7 @@
 // array carries one complex of padding per 16, which makes the stride-1 and stride-16 passes conflict-free.
 // Arithmetic is fp32 on the vector ALU: with one kernel per channel there is no operand shared across channels
 // except the DFT matrix itself, and fp32 matrix instructions are no faster than the ALU on this chip.
-#include "chela_internal.h"
+#include "chela_convmx.h"
 #include <algorithm>
 #include <cfloat>
 #include <cstdlib>
@@ -668,12 +668,14 @@ __device__ __forceinline__ int fresh(int tid) { asm volatile("" : "+v"(tid)); re
 // MX (M = 16384): also the copy that the matrix-core kernels read, the bins at exp(-2 pi i (k + 1/4) / M) (a transform of its
 // own, of the sequence turned by exp(-2 pi i n / (4 M))), divided by 4 |k|_1, as half-precision (re, im) words, stored where
 // the lane that holds bin k = k1 + 16 k2 + 512 k3 will look: word ((k1 * 4 + a) * 64 + lane) * 4 + b with lane = k2 + 32 h and
-// k3 = 8 a + 4 h + b; scale[c] = 4 |k|_1 (both zero where 0.25 / |k|_1 is no finite number, below 7.4e-40).
+// k3 = 8 a + 4 h + b; scale[c] = 4 |k|_1 (both zero where 0.25 / |k|_1 is no finite number, below 7.4e-40); one workgroup
+// more than there are channels writes those kernels' tables.
 template <int M, bool MX>
 __global__ __launch_bounds__(conv_threads(M)) void longconv_spectrum_kernel(const float* __restrict__ k,
                                                                            float4* __restrict__ Kf,
                                                                            uint4* __restrict__ Ks,
-                                                                           float* __restrict__ scale, int L)
+                                                                           float* __restrict__ scale,
+                                                                           MxTables* __restrict__ tables, int L)
 {
     static_assert(!MX || M == 16384, "the matrix-core kernels' transform has 2 x 16384 points");
     constexpr int T = conv_threads(M), NP = PairPos<M, T>::NP;
@@ -683,6 +685,9 @@ __global__ __launch_bounds__(conv_threads(M)) void longconv_spectrum_kernel(cons
     float4* tw = reinterpret_cast<float4*>(a + ConvLds<M>::DATA);
     const int tid = threadIdx.x;
     const long c = blockIdx.x;
+    if constexpr (MX) {
+        if (c == gridDim.x - 1) { mx_write_tables(tables, tid); return; }       // (one workgroup more than channels)
+    }
     build_tables<M, T>(tw, tid);
     SeqRegs<M, T, float> kr;
     kr.load(k + c * (long)L, L, tid);
@@ -1611,10 +1616,11 @@ hipError_t launch_longconv_spectrum(const float* k, void* Kf, int d, int L, hipS
         return hipGetLastError();
     }
     uint4* mx = (uint4*)((char*)Kf + conv_pairs_bytes(d, L));
-    float* scale = (float*)((char*)mx + (size_t)d * 16384 * sizeof(unsigned));
+    float* scale = (float*)(mx + (size_t)d * (MX_N / 4));
+    MxTables* tables = mx_tables(mx, d);
 #define CHELA_SPECTRUM(M_, MX_)                                                                                         \
-    case M_: hipLaunchKernelGGL((longconv_spectrum_kernel<M_, MX_>), dim3(d), dim3(conv_threads(M_)), 0, st, k, out, mx,  \
-                                scale, L); break;
+    case M_: hipLaunchKernelGGL((longconv_spectrum_kernel<M_, MX_>), dim3(d + (MX_ ? 1 : 0)), dim3(conv_threads(M_)), 0, st, \
+                                k, out, mx, scale, tables, L); break;
     switch (M) {
         CHELA_SPECTRUM(256, false) CHELA_SPECTRUM(1024, false) CHELA_SPECTRUM(4096, false)
         case 16384:     // (rows that are no multiple of 8 steps never meet the matrix-core kernels)

@@ -14,7 +14,7 @@
 // fp32, the part of the first one that differs from step to step of a lane's eight (e((k1 + 1/4) (n3 & 7) / N)) is worked
 // into eight versions of the first matrix.
 //
-// Bound by vector instructions (short kernel, silu and conversions take about half of them), so the layout is chosen to
+// Bound by vector instructions (issuing 83 % of the time in the forward kernel), so the layout is chosen to
 // spend none on moving data:
 //   - First pass: a lane loads eight consecutive steps of four rows n1, which is its operand of
 //     v_mfma_f32_16x16x16_f16 (contraction over n1), and gets four k1 of the same eight columns.
@@ -28,15 +28,13 @@
 // by 4 |k|_1 (no finished sum on the way back exceeds 4096, no partial one, by Parseval, 16400): half precision ends at 65504.
 // Both factors are put back on the way out.  Error against the fp64 definition on the workload's recipe: 4.2e-4 relative
 // before the rounding of the output to bf16 (1.7e-3 on its own).
-#include "chela_internal.h"
+#include "chela_convmx.h"
 #include <cfloat>
 #include <cstdlib>
 
 namespace chela {
 
 typedef __bf16 bf16;
-typedef _Float16 f16;
-typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 typedef __attribute__((ext_vector_type(4))) _Float16 f16x4;
 typedef __attribute__((ext_vector_type(2))) _Float16 f16x2;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
@@ -44,9 +42,9 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
 
-constexpr int MX_N = 16384;                  // points of the transform = steps of a sequence at most
 constexpr int MX_T = 512;                    // threads: each owns eight columns of four rows n1 (32 steps)
 constexpr int MX_W = MX_T / 64;              // waves; wave w owns columns 128 w .. 128 w + 127 and tiles w, w + 8
 constexpr int MX_NT = 16 / MX_W;             // tiles per wave
@@ -88,73 +86,54 @@ __device__ __forceinline__ f32x16 mx_zero()
     return z;
 }
 
-// Tables in LDS.
-//   T: the first matrix, [j][re, im][k1][n1] fp16: e((k1 + 1/4) (n1 / 16 + j / N))
-//   R: e(sigma r / 1024), [sigma - 1][r] fp32 pairs, sigma = 1 .. 31 (row 0 would be ones)
-struct MxTables {
+__device__ __forceinline__ float2 mx_cmul(float2 a, float2 b) { return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x); }
+
+// T and R as they lie in LDS, and room to exchange maxima.
+struct MxLds {
     f16 T[8 * 2 * 16 * 16];
     float2 R[31 * 32];
     float red[2 * MX_W];
 };
-// e(num * unit), num * unit exact: the hardware's sine and cosine take turns; what they are off by (1e-6) is nothing beside
-// the fp16 that every rotated value and matrix entry is rounded to.
-__device__ __forceinline__ float2 mx_e(int num, float unit)
+struct MxMat { f16x8 c[2], s[2], ns[2]; };
+__device__ __forceinline__ void mx_fetch_tables(MxLds& tb, const MxTables* __restrict__ src, int tid)
+{
+    constexpr int n16 = (int)((sizeof(src->T) + sizeof(src->R)) / 16);
+    const u32x4* s = reinterpret_cast<const u32x4*>(src);
+    u32x4* d = reinterpret_cast<u32x4*>(&tb);
+#pragma unroll
+    for (int k = 0; k < (n16 + MX_T - 1) / MX_T; ++k)
+        if (tid + MX_T * k < n16) d[tid + MX_T * k] = s[tid + MX_T * k];
+}
+__device__ __forceinline__ void mx_fetch_matrix(MxMat& m, const MxTables* __restrict__ src, int lane)
+{
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        m.c[t] = src->M[64 * t + lane];
+        m.s[t] = src->M[64 * (2 + t) + lane];
+        m.ns[t] = -m.s[t];
+    }
+}
+
+// What a lane needs besides: rho = e((4 q + 1/4) (128 w + 8 c) / N) and g = e((128 w + 8 c) / N) for the first pass
+// (lane = 16 q + c), u = e(r / 2048) for the way back (lane = 32 h + r).  By the hardware's sine and cosine of turns: what they
+// are off by (1e-6) is nothing beside the fp16 that every rotated value is rounded to.
+struct MxLane { float2 rho, g, u; };
+__device__ __forceinline__ float2 mx_e_fast(int num, float unit)
 {
     const float t = (float)num * unit;
     return make_float2(__builtin_amdgcn_cosf(t), -__builtin_amdgcn_sinf(t));
 }
-__device__ __forceinline__ float2 mx_cmul(float2 a, float2 b) { return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x); }
-__device__ __forceinline__ void mx_build_tables(MxTables& tb, int tid)
-{
-#pragma unroll
-    for (int x = tid; x < 8 * 256; x += MX_T) {
-        const int j = x >> 8, k1 = (x >> 4) & 15, n1 = x & 15;
-        // (4 k1 + 1) (1024 n1 + j) / (4 N) of a turn, the whole turns taken off
-        const float2 e = mx_e(((4 * k1 + 1) * (1024 * n1 + j)) & (4 * MX_N - 1), 1.0f / (4.0f * MX_N));
-        tb.T[(2 * j) * 256 + (x & 255)] = (f16)e.x;
-        tb.T[(2 * j + 1) * 256 + (x & 255)] = (f16)e.y;
-    }
-    for (int x = tid; x < 31 * 32; x += MX_T) tb.R[x] = mx_e(((x >> 5) + 1) * (x & 31), 1.0f / 1024.0f);
-}
-
-// The 32-point matrix, times a number for which cos(k pi / 16), k < 8, lie as close to half precision as they get: a third of
-// the rounding error of the entries themselves (2.6e-5 against 8.3e-5 root mean square).  MX_GAIN: what the rounded entries
-// come to (least squares), taken out at the stores, once per product.
-constexpr float MX_ENTRY = 1.11529f, MX_GAIN = 1.11520299f;
-constexpr float MX_GAIN2 = MX_GAIN * MX_GAIN, MX_GAIN4 = MX_GAIN2 * MX_GAIN2;
-
-// The 32-point matrix e(r sigma / 32) = c - i s as an operand (first or second: it is symmetric): lane (r, h), element e of
-// step t stands for sigma = 16 t + 8 (e / 4) + 4 h + e % 4, the order in which a lane holds the rows of a result.
-struct MxMat { f16x8 c[2], s[2], ns[2]; };
-__device__ __forceinline__ void mx_build_matrix(MxMat& m, int lane)
-{
-    const int r = lane & 31, h = lane >> 5;
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int sigma = 16 * t + 8 * (e >> 2) + 4 * h + (e & 3);
-            const float2 p = mx_e((r * sigma) & 31, 1.0f / 32.0f);
-            m.c[t][e] = (f16)(MX_ENTRY * p.x);
-            m.s[t][e] = (f16)(MX_ENTRY * -p.y);
-            m.ns[t][e] = (f16)(MX_ENTRY * p.y);
-        }
-}
-
-// What a lane needs besides: rho = e((4 q + 1/4) (128 w + 8 c) / N) and g = e((128 w + 8 c) / N) for the first pass
-// (lane = 16 q + c), u = e(r / 2048) for the way back (lane = 32 h + r).
-struct MxLane { float2 rho, g, u; };
 __device__ __forceinline__ void mx_build_lane(MxLane& c, int lane, int w)
 {
     const int col = 128 * w + 8 * (lane & 15);
-    c.rho = mx_e((16 * (lane >> 4) + 1) * col, 1.0f / (4.0f * MX_N));
-    c.g = mx_e(col, 1.0f / MX_N);
-    c.u = mx_e(lane & 31, 1.0f / 2048.0f);
+    c.rho = mx_e_fast((16 * (lane >> 4) + 1) * col, 1.0f / (4.0f * MX_N));
+    c.g = mx_e_fast(col, 1.0f / MX_N);
+    c.u = mx_e_fast(lane & 31, 1.0f / 2048.0f);
 }
 // e((k1 + 1/4) 8 / N), the same in all lanes
 __device__ __forceinline__ float2 mx_step(int k1)
 {
-    const float2 st = mx_e((4 * k1 + 1) * 8, 1.0f / (4.0f * MX_N));
+    const float2 st = mx_e_fast((4 * k1 + 1) * 8, 1.0f / (4.0f * MX_N));
     return make_float2(__builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, st.x))),
                        __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, st.y))));
 }
@@ -163,7 +142,7 @@ __device__ __forceinline__ float2 mx_step(int k1)
 // times a power of two are half-precision ones; else what they lose in rounding goes through the same product (the rounding of
 // the input weighs as much as any two others: it is not averaged over a pass).
 template <bool EXACT>
-__device__ __forceinline__ void mx_first(unsigned char* cube, const MxTables& tb, const MxLane& lc, const float (&v)[4][8],
+__device__ __forceinline__ void mx_first(unsigned char* cube, const MxLds& tb, const MxLane& lc, const float (&v)[4][8],
                                          float s, int w, int lane)
 {
     lane = mx_fresh(lane);
@@ -259,7 +238,7 @@ __device__ __forceinline__ void mx_rotate(const f32x16& xr, const f32x16& xi, co
 }
 
 // ---- tile k1 through the second and third pass: register 4 a + b of lane (r, h) ends as bin k2 = r, k3 = 8 a + 4 h + b
-__device__ __forceinline__ void mx_tile_in(const unsigned char* cube, const MxTables& tb, const MxMat& m, int k1, int lane,
+__device__ __forceinline__ void mx_tile_in(const unsigned char* cube, const MxLds& tb, const MxMat& m, int k1, int lane,
                                            f32x16& xr, f32x16& xi)
 {
     lane = mx_fresh(lane);
@@ -282,7 +261,7 @@ __device__ __forceinline__ void mx_tile_in(const unsigned char* cube, const MxTa
 // place 4 j + a, its 8-byte pieces (one j each) exchanged by k1 and n2 so that neither the writers here (32 rows) nor the
 // readers of the last pass (4 rows of 8 tiles) share banks.
 __device__ __forceinline__ int mx_swizzle(int k1, int n2) { return ((k1 & 3) | (k1 >> 3) << 2) ^ (n2 >> 2); }
-__device__ __forceinline__ void mx_tile_out(unsigned char* cube, const MxTables& tb, const MxMat& m, float2 u, float2 st,
+__device__ __forceinline__ void mx_tile_out(unsigned char* cube, const MxLds& tb, const MxMat& m, float2 u, float2 st,
                                             int k1, int lane, u32x4 (&re)[2], u32x4 (&im)[2])
 {
     lane = mx_fresh(lane);
@@ -319,7 +298,7 @@ __device__ __forceinline__ void mx_tile_out(unsigned char* cube, const MxTables&
 }
 
 // ---- last pass: y[i][j] = N times step 1024 (4 q + i) + 128 w + 8 c + j, up to the scales
-__device__ __forceinline__ void mx_last(const unsigned char* cube, const MxTables& tb, int w, int lane, float (&y)[4][8])
+__device__ __forceinline__ void mx_last(const unsigned char* cube, const MxLds& tb, int w, int lane, float (&y)[4][8])
 {
     lane = mx_fresh(lane);
     const int p = lane & 15, q = lane >> 4;
@@ -344,6 +323,30 @@ __device__ __forceinline__ void mx_last(const unsigned char* cube, const MxTable
 // A lane's steps are t0 + 1024 i + j, i < 4, j < 8.
 __device__ __forceinline__ int mx_first_step(int w, int lane) { return 4096 * (lane >> 4) + 128 * w + 8 * (lane & 15); }
 
+// The short kernel's taps as operands of v_mfma_f32_16x16x32_bf16, whose other operand is x as it lies in memory: lane 16 q + c
+// supplies eight steps of row 4 q + i (contraction index 8 q + e), result 4 q + b of column c is step 4 blk + b of row 4 q + i, so the
+// matrix is block-diagonal in q: row (q, b), index (q, e): w[8 D + 4 blk + b - e] for the piece D pieces in front.  The taps
+// go in as three bf16 parts each, cut off, not rounded: all 24 bits (products with bf16 x are exact, sums fp32).  A quarter of the
+// matrix is of use, and still: 48 of these instructions replace 288 multiply-adds and some 60 unpackings per wave (9 taps:
+// forward of 768 x 4 x 16384 steps 125 -> 118 us, long-stage gradients 243 -> 225; 32 taps: forward 165 -> 134).
+//   [part][D][blk][b][e], then eight zeros for the lanes off the diagonal
+#define MX_TAP_WORDS(nh) (3 * ((nh) + 1) * 2 * 4 * 8)
+template <int HALO>
+__device__ __forceinline__ void mx_write_taps(unsigned short* taps, const float* __restrict__ wc, int m, int tid)
+{
+    constexpr int NH = HALO / 8, WORDS = MX_TAP_WORDS(NH);
+#pragma unroll
+    for (int k = 0; k < (WORDS + 8 + MX_T - 1) / MX_T; ++k) {
+        const int x = tid + MX_T * k, e = x & 7, b = (x >> 3) & 3, blk = (x >> 5) & 1, pd = x >> 6;
+        if (x >= WORDS + 8) break;
+        const int part = pd / (NH + 1), j = 8 * (pd - part * (NH + 1)) + 4 * blk + b - e;
+        const float w = x < WORDS && j >= 0 && j < m ? wc[j] : 0.f;
+        auto cut = [](float v) __attribute__((always_inline)) { return __builtin_bit_cast(float, __builtin_bit_cast(unsigned, v) & 0xffff0000u); };
+        const float hi = cut(w), mid = cut(w - hi), lo = w - hi - mid;
+        taps[x] = (unsigned short)(__builtin_bit_cast(unsigned, part == 0 ? hi : part == 1 ? mid : lo) >> 16);
+    }
+}
+
 // ---- a sequence in registers: 16-byte pieces of rows n1 = 4 q + i, steps t0 + 1024 i .. + 7, and the HALO steps in front of
 // each (the taps' history).  Buffer loads: what lies before the row's start or beyond its end reads as zero.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t mx_rsrc(const void* row, int bytes)
@@ -367,25 +370,17 @@ struct MxSeq {
         if (HALO > 0)
             front = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, 2 * (1024 * (lane & 15) + 128 * w - 8 - 8 * (lane >> 4)), 0, 0));
     }
-    // the piece 8 D steps in front of row i's
+    // the pieces 8 D steps in front of the rows'
     template <int D>
-    __device__ __forceinline__ u32x4 piece(int i, int lane) const
+    __device__ __forceinline__ void pieces(int lane, u32x4 (&x)[4]) const
     {
-        const int from = 16 * (D - 1 - (lane & 15)) + 4 * (lane >> 4) + i;         // (of use to the first D lanes only)
-        u32x4 v;
+        const int from = 16 * (D - 1 - (lane & 15)) + 4 * (lane >> 4);         // (of use to the first D lanes only)
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-            v[e] = (unsigned)__builtin_amdgcn_update_dpp(__builtin_amdgcn_ds_bpermute(4 * from, (int)front[e]), (int)r[i][e],
-                                                         0x110 + D, 0xf, 0xf, false);      // row_shr:D
-        return v;
-    }
-    __device__ __forceinline__ static void unpack8(u32x4 v, float* x)
-    {
+        for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            x[2 * e] = __builtin_bit_cast(float, v[e] << 16);
-            x[2 * e + 1] = __builtin_bit_cast(float, v[e] & 0xffff0000u);
-        }
+            for (int e = 0; e < 4; ++e)
+                x[i][e] = (unsigned)__builtin_amdgcn_update_dpp(__builtin_amdgcn_ds_bpermute(4 * (from + i), (int)front[e]),
+                                                                (int)r[i][e], 0x110 + D, 0xf, 0xf, false);      // row_shr:D
     }
     // The wave's largest magnitude (of the steps themselves).
     __device__ __forceinline__ float wave_max() const
@@ -403,36 +398,60 @@ struct MxSeq {
         for (int o = 32; o >= 1; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
         return v;
     }
-    // v = silu(K_s x) (HALO = 0: v = x).  Steps beyond the sequence's end come out as whatever their history gives: a
-    // causal sum does not hand them back to earlier steps, and the gradient meets them with dZ = 0.
-    __device__ __forceinline__ void values(const float* __restrict__ wc, int m, int lane, float (&v)[4][8]) const
+    // the steps themselves
+    __device__ __forceinline__ void values(float (&v)[4][8]) const
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                v[i][2 * e] = __builtin_bit_cast(float, r[i][e] << 16);
+                v[i][2 * e + 1] = __builtin_bit_cast(float, r[i][e] & 0xffff0000u);
+            }
+    }
+    // u = K_s x.  Steps beyond the sequence's end come out as whatever their history gives: a causal sum does not hand them back
+    // to earlier steps, and the gradient meets them with dZ = 0.
+    __device__ __forceinline__ void short_conv(const unsigned short* taps, int lane, float (&v)[4][8]) const
     {
         lane = mx_fresh(lane);
+        f32x4 acc[4][2];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            float x[HALO + 8];
-            unpack8(r[i], x + HALO);
-            if constexpr (HALO >= 8) unpack8(piece<1>(i, lane), x + HALO - 8);
-            if constexpr (HALO >= 16) unpack8(piece<2>(i, lane), x + HALO - 16);
-            if constexpr (HALO >= 32) { unpack8(piece<3>(i, lane), x + HALO - 24); unpack8(piece<4>(i, lane), x + HALO - 32); }
-            if (HALO == 0) {
+        for (int i = 0; i < 4; ++i) acc[i][0] = acc[i][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+        const bool mine = (lane >> 4) == ((lane & 15) >> 2);
+        const unsigned short* t = taps + (mine ? 8 * (lane & 3) : MX_TAP_WORDS(NH));
+        auto add = [&](const u32x4 (&x)[4], int D) __attribute__((always_inline)) {
 #pragma unroll
-                for (int e = 0; e < 8; ++e) v[i][e] = x[e];
-                continue;
-            }
+            for (int part = 0; part < 3; ++part)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[i][e] = 0.f;
+                for (int blk = 0; blk < 2; ++blk) {
+                    const int at = ((part * (NH + 1) + D) * 2 + blk) * 32;
+                    const bf16x8 a = *reinterpret_cast<const bf16x8*>(t + (mine ? at : 0));
 #pragma unroll
-            for (int j = 0; j <= HALO && j < 32; ++j) {
-                float wj = wc[j < m ? j : 0];
-                wj = j < m ? wj : 0.f;
-                if (j > 8 && j >= m) continue;
+                    for (int i = 0; i < 4; ++i)
+                        acc[i][blk] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, __builtin_bit_cast(bf16x8, x[i]), acc[i][blk], 0, 0, 0);
+                }
+        };
+        add(r, 0);
+        u32x4 x[4];
+        if constexpr (NH >= 1) { pieces<1>(lane, x); add(x, 1); }
+        if constexpr (NH >= 2) { pieces<2>(lane, x); add(x, 2); }
+        if constexpr (NH >= 4) { pieces<3>(lane, x); add(x, 3); pieces<4>(lane, x); add(x, 4); }
 #pragma unroll
-                for (int e = 0; e < 8; ++e) v[i][e] = fmaf(wj, x[HALO + e - j], v[i][e]);
-            }
+        for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[i][e] *= __builtin_amdgcn_rcpf(1.f + __expf(-v[i][e]));
-            __builtin_amdgcn_sched_barrier(0);       // (row by row: four rows' unpacked steps at once would fill the registers)
+            for (int e = 0; e < 8; ++e) v[i][e] = acc[i][e >> 2][e & 3];
+    }
+    // v = silu(K_s x); HALO = 0: v = x
+    __device__ __forceinline__ void activated(const unsigned short* taps, int lane, float (&v)[4][8]) const
+    {
+        if constexpr (HALO == 0) {
+            values(v);
+        } else {
+            short_conv(taps, lane, v);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[i][e] *= __builtin_amdgcn_rcpf(1.f + __expf(-v[i][e]));
         }
     }
 };
@@ -479,8 +498,8 @@ __device__ __forceinline__ void mx_product(const f32x16& xr, const f32x16& xi, c
 
 // One sequence per workgroup, id = c B + b.  HALO: steps of history the short kernel needs (m - 1 <= HALO; v = silu(K_s x));
 // 0: no short kernel, v = x.  L is a multiple of 8.
-// Two workgroups per compute unit (80 KB of LDS, 128 registers): one's short kernel runs beside the other's matrix products,
-// and the next one's tables (some 200 instructions) and loads beside both.  Workgroups that walk several sequences with the next
+// Two workgroups per compute unit (80 KB of LDS, 128 registers): one's activation runs beside the other's matrix products.
+// Workgroups that walk several sequences with the next
 // one's input on its way took 122 us (three each) and 128 us (six, all resident at once) where these take 117: of two that
 // start together on a unit the older one gets ahead, and the other finishes alone.
 // 768 channels x 4 sequences of 16384 steps, 9 taps: 117 us (198 with two sequences per transform of 2 x 16384 points, whose
@@ -488,11 +507,12 @@ __device__ __forceinline__ void mx_product(const f32x16& xr, const f32x16& xi, c
 template <int HALO>
 __global__ __launch_bounds__(MX_T, 4) void convmx_fwd_kernel(const bf16* __restrict__ X, const float* __restrict__ w_short,
                                                              int m, const unsigned* __restrict__ Ks,
-                                                             const float* __restrict__ kscale, bf16* __restrict__ Y, int B,
+                                                             const float* __restrict__ kscale, const MxTables* __restrict__ tables,
+                                                             bf16* __restrict__ Y, int B,
                                                              int d, int L, int total)
 {
     __shared__ __attribute__((aligned(16))) unsigned char cube[MX_CUBE];
-    __shared__ __attribute__((aligned(16))) MxTables tb;
+    __shared__ __attribute__((aligned(16))) MxLds tb;
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     // consecutive workgroups run on the eight XCDs in turn: those of one XCD take neighbouring ids, which share spectra in its L2
@@ -502,18 +522,19 @@ __global__ __launch_bounds__(MX_T, 4) void convmx_fwd_kernel(const bf16* __restr
     const long row = ((long)b * d + c) * L;
     MxSeq<HALO> xs;
     xs.load(X + row, L, w, lane);
-    mx_build_tables(tb, tid);
-    MxMat m32;
-    mx_build_matrix(m32, lane);
+    unsigned short* taps = reinterpret_cast<unsigned short*>(cube);       // (until the first pass)
+    if (HALO > 0) mx_write_taps<HALO>(taps, w_short + (long)c * m, m, tid);
+    mx_fetch_tables(tb, tables, tid);
+    __syncthreads();
     MxLane lc;
     mx_build_lane(lc, lane, w);
     float s;
     {
         float v[4][8];
-        xs.values(HALO ? w_short + (long)c * m : nullptr, m, lane, v);
+        xs.activated(taps, lane, v);
         const float mx = mx_wave_max(v);
         if (lane == 0) tb.red[w] = mx;
-        __syncthreads();        // (also: the tables are built)
+        __syncthreads();
         float bm = 0.f;
 #pragma unroll
         for (int i = 0; i < MX_W; ++i) bm = fmaxf(bm, tb.red[i]);
@@ -521,6 +542,8 @@ __global__ __launch_bounds__(MX_T, 4) void convmx_fwd_kernel(const bf16* __restr
         mx_first<HALO == 0>(cube, tb, lc, v, s, w, lane);
     }
     const u32x4* kc = reinterpret_cast<const u32x4*>(Ks + (long)c * MX_N);
+    MxMat m32;
+    mx_fetch_matrix(m32, tables, lane);
     __syncthreads();
 #pragma unroll
     for (int n = 0; n < MX_NT; ++n) {
@@ -568,16 +591,20 @@ template <int HALO, typename DVT>
 __global__ __launch_bounds__(MX_T, 2) void convmx_longbwd_kernel(const bf16* __restrict__ X, const float* __restrict__ w_short,
                                                               int m, const unsigned* __restrict__ Ks,
                                                               const float* __restrict__ kscale,
+                                                              const MxTables* __restrict__ tables,
                                                               const bf16* __restrict__ dZ, DVT* __restrict__ dV,
                                                               float* __restrict__ dk, int B, int d, int L)
 {
     __shared__ __attribute__((aligned(16))) unsigned char cube[2][MX_CUBE];       // of dZ, of v
-    __shared__ __attribute__((aligned(16))) MxTables tb;
+    __shared__ __attribute__((aligned(16))) MxLds tb;
+    __shared__ __attribute__((aligned(16))) unsigned short taps[HALO > 0 ? MX_TAP_WORDS(HALO / 8) + 8 : 8];
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    mx_build_tables(tb, tid);
+    mx_fetch_tables(tb, tables, tid);
     MxMat m32;
-    mx_build_matrix(m32, lane);
+    mx_fetch_matrix(m32, tables, lane);
+    if (HALO > 0) mx_write_taps<HALO>(taps, w_short + (long)blockIdx.x * m, m, tid);
+    __syncthreads();
     MxLane lc;
     mx_build_lane(lc, lane, w);
     float2 st[MX_NT];
@@ -599,10 +626,10 @@ __global__ __launch_bounds__(MX_T, 2) void convmx_longbwd_kernel(const bf16* __r
         float s_d, f;           // f: from the sums' unit so far to the present one
         {
             float v[4][8];
-            xs.values(HALO ? w_short + (long)c * m : nullptr, m, lane, v);
+            xs.activated(taps, lane, v);
             const float mv = mx_wave_max(v), md = zs.wave_max();
             if (lane == 0) { tb.red[w] = md; tb.red[MX_W + w] = mv; }
-            __syncthreads();        // (also: the tables are built)
+            __syncthreads();
             float bd = 0.f, bv = 0.f;
 #pragma unroll
             for (int i = 0; i < MX_W; ++i) { bd = fmaxf(bd, tb.red[i]); bv = fmaxf(bv, tb.red[MX_W + i]); }
@@ -613,7 +640,7 @@ __global__ __launch_bounds__(MX_T, 2) void convmx_longbwd_kernel(const bf16* __r
             const float s_v = unit > 0.f ? sv * (here / unit) : 0.f;
             mx_first<HALO == 0>(cube[1], tb, lc, v, s_v, w, lane);
             __builtin_amdgcn_sched_barrier(0);
-            zs.values(nullptr, 0, lane, v);
+            zs.values(v);
             mx_first<true>(cube[0], tb, lc, v, s_d, w, lane);
         }
         __syncthreads();
@@ -662,6 +689,7 @@ __global__ __launch_bounds__(MX_T, 2) void convmx_longbwd_kernel(const bf16* __r
             if (t0 + 1024 * i < L) *reinterpret_cast<out8*>(out + t0 + 1024 * i) = o;
         }
         if (done) {         // ---- the sums' way back
+            if (HALO > 0 && c < d) mx_write_taps<HALO>(taps, w_short + (long)c * m, m, tid);      // (barriers before and behind)
             float ss = 0.f;
 #pragma unroll
             for (int n = 0; n < MX_NT; ++n)
@@ -750,13 +778,14 @@ hipError_t launch_convmx_fwd(const void* X, const float* w_short, int m, const v
 {
     const unsigned* Ks = (const unsigned*)extra;
     const float* scale = (const float*)(Ks + (size_t)d * MX_N);
+    const MxTables* tables = mx_tables((void*)extra, d);
     const long total = (long)d * B;
     if (total > 0x7ffffff0L) return hipErrorInvalidValue;
     const dim3 grid((unsigned)((total + 7) / 8 * 8));
     ProfScope prof(KID_CONV_FWD, st);
 #define CHELA_MX_FWD(H_)                                                                                                \
-    hipLaunchKernelGGL((convmx_fwd_kernel<H_>), grid, dim3(MX_T), 0, st, (const bf16*)X, w_short, m, Ks, scale, (bf16*)Y, B, \
-                       d, L, (int)total)
+    hipLaunchKernelGGL((convmx_fwd_kernel<H_>), grid, dim3(MX_T), 0, st, (const bf16*)X, w_short, m, Ks, scale, tables,    \
+                       (bf16*)Y, B, d, L, (int)total)
     if (!w_short) CHELA_MX_FWD(0);
     else if (m <= 9) CHELA_MX_FWD(8);
     else if (m <= 17) CHELA_MX_FWD(16);
@@ -771,6 +800,7 @@ hipError_t launch_convmx_longbwd(const void* X, const float* w_short, int m, con
 {
     const unsigned* Ks = (const unsigned*)extra;
     const float* scale = (const float*)(Ks + (size_t)d * MX_N);
+    const MxTables* tables = mx_tables((void*)extra, d);
     // One workgroup per compute unit.  A channel's sequences are shared out where that shortens the longest workgroup's work:
     // its rounds x (its sequences + 0.4, the sums' way back; + 0.2 with the slices to be added up).  128 channels x 3 sequences
     // of 8192 steps, both stages' gradients: 64 us, in three shares 54.
@@ -786,8 +816,8 @@ hipError_t launch_convmx_longbwd(const void* X, const float* w_short, int m, con
     float* const sums = G > 1 ? part : dk;
     ProfScope prof(KID_CONV_LONG_BWD, st);
 #define CHELA_MX_BWD(H_, T_)                                                                                            \
-    hipLaunchKernelGGL((convmx_longbwd_kernel<H_, T_>), grid, dim3(MX_T), 0, st, (const bf16*)X, w_short, m, Ks, scale,  \
-                       (const bf16*)dZ, (T_*)dV, sums, B, d, L)
+    hipLaunchKernelGGL((convmx_longbwd_kernel<H_, T_>), grid, dim3(MX_T), 0, st, (const bf16*)X, w_short, m, Ks, scale, \
+                       tables, (const bf16*)dZ, (T_*)dV, sums, B, d, L)
     if (!w_short) {
         if (dv_is_f32) CHELA_MX_BWD(0, float); else CHELA_MX_BWD(0, bf16);
     } else if (m <= 9) {
