@@ -59,12 +59,6 @@ __device__ __forceinline__ unsigned mx_pack(float lo, float hi)
     v[1] = (f16)hi;
     return __builtin_bit_cast(unsigned, v);
 }
-__device__ __forceinline__ void mx_unpack(unsigned w, float& lo, float& hi)
-{
-    const f16x2 v = __builtin_bit_cast(f16x2, w);
-    lo = (float)v[0];
-    hi = (float)v[1];
-}
 __device__ __forceinline__ f16x8 mx_h8(u32x4 v) { return __builtin_bit_cast(f16x8, v); }
 
 // Within a group of 16 lanes the transposing read hands lane p element p % 4 of the 8-byte pieces that lanes p / 4,
@@ -219,6 +213,7 @@ __device__ __forceinline__ void mx_rotate(const f32x16& xr, const f32x16& xi, co
 {
     lane = mx_fresh(lane);
     const int r = lane & 31, h = lane >> 5;
+    const float2* Rl = R + h * (4 * 32) + r;
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
@@ -226,9 +221,12 @@ __device__ __forceinline__ void mx_rotate(const f32x16& xr, const f32x16& xi, co
             float x[2], y[2];
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-                const int sigma = 8 * a + 4 * h + b + u, i = 4 * a + b + u;
-                float2 p = R[(sigma > 0 ? sigma - 1 : 0) * 32 + r];
-                if (a == 0 && b + u == 0) p = h == 0 ? make_float2(1.f, 0.f) : p;
+                const int i = 4 * a + b + u;
+                float2 p = a > 0 || b + u > 0 ? Rl[(8 * a + b + u - 1) * 32] : R[3 * 32 + r];
+                if (a == 0 && b + u == 0) {
+                    p.x = h == 0 ? 1.f : p.x;
+                    p.y = h == 0 ? 0.f : p.y;
+                }
                 x[u] = xr[i] * p.x - xi[i] * p.y;
                 y[u] = xr[i] * p.y + xi[i] * p.x;
             }
@@ -478,6 +476,8 @@ __device__ __forceinline__ float mx_scale(float bm)
 template <bool CORR>
 __device__ __forceinline__ void mx_product(const f32x16& xr, const f32x16& xi, const u32x4 (&kq)[4], u32x4 (&re)[2], u32x4 (&im)[2])
 {
+    float none = 0.f;
+    asm("" : "+s"(none));
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
@@ -485,11 +485,13 @@ __device__ __forceinline__ void mx_product(const f32x16& xr, const f32x16& xi, c
             float x[2], y[2];
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-                float kr, ki;
-                mx_unpack(kq[a][b + u], kr, ki);
+                const unsigned kw = kq[a][b + u];
+                const f16x2 k = __builtin_bit_cast(f16x2, kw);
                 const float zr = xr[4 * a + b + u], zi = xi[4 * a + b + u];
-                x[u] = CORR ? zr * kr + zi * ki : zr * kr - zi * ki;
-                y[u] = CORR ? zr * ki - zi * kr : -(zr * ki + zi * kr);
+                // (multiply-adds all: the mixed-precision ones take the half-precision factor as it is)
+                const float p = fmaf(zi, (float)k[1], none), q = fmaf(zi, (float)k[0], none);
+                x[u] = CORR ? fmaf(zr, (float)k[0], p) : fmaf(zr, (float)k[0], -p);
+                y[u] = CORR ? fmaf(zr, (float)k[1], -q) : -fmaf(zr, (float)k[1], q);
             }
             re[a >> 1][2 * (a & 1) + (b >> 1)] = mx_pack(x[0], x[1]);
             im[a >> 1][2 * (a & 1) + (b >> 1)] = mx_pack(y[0], y[1]);
