@@ -5,6 +5,8 @@ the computation runs in the library's kernels.  There is no fallback: if the lib
 returns an error status, an exception is raised.
 """
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 from typing import Optional, Tuple
 
@@ -17,6 +19,8 @@ DTYPE_BF16 = 0
 DTYPE_F32 = 1
 
 _lib = None
+_step_host = None           # the host module's step(), once a decode step has been made
+_step_fn = (0, 0)           # addresses of chela_linattn_step, chela_linattn_step_gated for it
 
 
 class ChelaError(RuntimeError):
@@ -174,6 +178,24 @@ _current = _CurrentDevice()
 def _on(t: torch.Tensor):
     """Context in which t's device is the current one."""
     return _current if t.get_device() == torch.cuda.current_device() else torch.cuda.device(t.device)
+
+
+def _load_step():
+    """The host module's step() and the addresses it calls; a step() that declines every call where the module is not built
+    (the lines of the two functions below then do the same, in 8.9 us instead of 4.7 per step)."""
+    global _step_host, _step_fn
+    L = lib()
+    _step_fn = tuple(ctypes.cast(f, ctypes.c_void_p).value for f in (L.chela_linattn_step, L.chela_linattn_step_gated))
+    path = os.path.join(_HERE, "_chela_host.so")
+    if os.path.exists(path):
+        spec = importlib.util.spec_from_file_location("_chela_host", path,
+                                                      loader=importlib.machinery.ExtensionFileLoader("_chela_host", path))
+        module = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(module)
+        _step_host = module.step
+    else:
+        _step_host = lambda *a: None        # noqa: E731
+    return _step_host
 
 
 def _suffix(t: torch.Tensor) -> Tuple[str, int]:
@@ -618,6 +640,11 @@ def chela_shortlong_conv_bwd(X, w_short, spectrum, dZ, stream=None):
 
 def chela_linattn_step(q, k, v, S, o=None, stream=None):
     """One decode step: S += k v^T in place, returns o = S^T q.  q,k: [B,H,dk] bf16, v: [B,H,dv] bf16, S fp32."""
+    r = (_step_host or _load_step())(_step_fn[0], q, k, v, None, S, 0.0, o, stream)
+    if r is not None:
+        if type(r) is int:
+            _check(r)
+        return r
     B, H, dk = q.shape
     dv = v.shape[2]
     if o is None:
@@ -633,6 +660,11 @@ def chela_linattn_step(q, k, v, S, o=None, stream=None):
 
 def chela_linattn_step_gated(q, k, v, g, S, eps, y=None, stream=None):
     """One decode step with the Eq. 9 epilogue: S += k v^T in place, returns y = Norm(S^T q) * g (g: [B,H,dv] bf16)."""
+    r = (_step_host or _load_step())(_step_fn[1], q, k, v, g, S, eps, y, stream)
+    if r is not None:
+        if type(r) is int:
+            _check(r)
+        return r
     B, H, dk = q.shape
     dv = v.shape[2]
     if y is None:

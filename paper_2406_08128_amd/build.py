@@ -11,6 +11,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libchela.so")
+HOST_MODULE = os.path.join(HERE, "_chela_host.so")
 SOURCES = ["chela_api.hip", "chela_kernels_f32.hip", "chela_kernels_bf16.hip", "chela_kernels_conv.hip",
            "chela_kernels_convmx.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -33,10 +34,29 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _build_host_module() -> str:
+    """The decode step's host path as a Python module (csrc/chela_host.cpp): host code only, against torch's headers."""
+    import sysconfig
+    import torch
+    tdir = os.path.dirname(os.path.abspath(torch.__file__))
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-I" + os.path.join(tdir, "include"),
+           "-I" + os.path.join(tdir, "include", "torch", "csrc", "api", "include"),
+           "-I" + os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), "-I" + sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "chela_host.cpp"), "-o", HOST_MODULE, "-L" + os.path.join(tdir, "lib"),
+           "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("host module failed:\n" + r.stdout)
+    return HOST_MODULE
+
+
 def build(verbose: bool = True) -> str:
     os.makedirs(OBJ_DIR, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=min(4, len(SOURCES))) as ex:
+    with ThreadPoolExecutor(max_workers=min(4, len(SOURCES) + 1)) as ex:
+        host = ex.submit(_build_host_module)
         objs = list(ex.map(_compile, SOURCES))
+        host.result()
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     if r.returncode != 0:

@@ -916,6 +916,34 @@ def test_training_pair_many_heads_single_segment():
         _check(name, sel(got), r, "bf16")
 
 
+@pytest.mark.parametrize("dk,dv,gated", [(64, 64, True), (64, 128, False), (128, 64, True)])
+def test_decode_step_host_path_and_the_bindings_own_lines_agree(dk, dv, gated):
+    # with the current stream passed in, the native host path declines and the binding's own lines make the call
+    g = torch.Generator(device="cuda")
+    g.manual_seed(dk + dv)
+    r = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    q, k, v, gate = ((r(3, 5, n) / 8).to(torch.bfloat16) for n in (dk, dk, dv, dv))
+    S0 = r(3, 5, dk, dv)
+    call = (lambda S, **kw: binding.chela_linattn_step_gated(q, k, v, gate, S, 1e-5, **kw)) if gated else \
+           (lambda S, **kw: binding.chela_linattn_step(q, k, v, S, **kw))
+    S1, S2, S3 = S0.clone(), S0.clone(), S0.clone()
+    a, b = call(S1), call(S2, stream=torch.cuda.current_stream())
+    out = torch.empty(3, 5, dv, dtype=torch.bfloat16, device="cuda")
+    c = call(S3, **{"y" if gated else "o": out})
+    assert c is out and a.shape == b.shape and a.dtype == b.dtype and not a.requires_grad
+    assert torch.equal(a, b) and torch.equal(a, c) and torch.equal(S1, S2) and torch.equal(S1, S3)
+    # what was refused is refused still, before anything has been done
+    q = q.transpose(0, 1)
+    with pytest.raises(ValueError):
+        call(S1)
+    q = q.transpose(0, 1)
+    with pytest.raises(ValueError):
+        call(S1[:, :, :-1])
+    with pytest.raises(binding.ChelaError):
+        call(S1, **{"y" if gated else "o": S1.view(torch.bfloat16).view(-1)[:15 * dv].view(3, 5, dv)})       # output inside the state
+    assert torch.equal(S1, S2)
+
+
 # ------------------------------------------------------------------------------------------ short-long convolution
 def _run_conv_case(B, d, L, m, dtype, seed=0, short=True):
     print("\nconv B%d d%d L%d m%d %s short=%s" % (B, d, L, m, dtype, short), flush=True)
