@@ -587,3 +587,14 @@ def test_noncausal_gated_argument_errors(L):
     assert f(Q, K, V, G, O, Y, float("nan"), 1, 1, 64, 64, 64, None) == -2
     assert f(Q, K, V, G, O, Y, 1e-5, 1, 1, 64, 64, 100, None) == -3
     assert f(None, None, None, None, None, None, 1e-5, 1, 0, 64, 64, 64, None) == 0
+
+
+def test_host_module_brings_no_per_thread_data(L):
+    # (a thread-local variable in a library loaded late makes every later look-up of older ones slow, in the whole process)
+    import struct
+    with open(os.path.join(ROOT, "paper_2406_08128_amd", "_chela_host.so"), "rb") as f:
+        data = f.read()
+    off, = struct.unpack_from("<Q", data, 32)
+    size, count = struct.unpack_from("<HH", data, 54)
+    kinds = [struct.unpack_from("<I", data, off + i * size)[0] for i in range(count)]
+    assert 1 in kinds and 7 not in kinds          # loadable segments, and no PT_TLS
