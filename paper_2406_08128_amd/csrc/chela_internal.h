@@ -141,11 +141,13 @@ bool convmx_applies(int L, int dtype);
 size_t convmx_spectrum_bytes(int d, int L);
 hipError_t launch_convmx_fwd(const void* X, const float* w_short, int m, const void* extra, void* Y, int B, int d, int L,
                              hipStream_t st);
-// The two long-stage gradients (dV: fp32 for the short-stage kernel, or dX itself in bf16 when there is no short stage).
-// part: room for max_share slices [d][L] of dk, for channels whose sequences are shared out to several workgroups.
+// The two long-stage gradients, and where convmx_bwd_short() the short stage's with them (dV is dX then, dw is written; else dV:
+// fp32 for the short-stage kernel, or dX itself in bf16 when there is no short stage, and dw is left alone).
+// part: room for conv_mx_share() slices [d][L] of dk, for channels whose sequences are shared out to several workgroups;
+// tap_part: as many slices [d][kConvMaxTaps] of dw.  shares (where true): the slices there will be.
+bool convmx_bwd_short(int m, int B, int d, int L, int* shares = nullptr);
 hipError_t launch_convmx_longbwd(const void* X, const float* w_short, int m, const void* extra, const void* dZ, void* dV,
-                                 bool dv_is_f32, float* dk, float* part, int max_share, int B, int d, int L,
-                                 hipStream_t st);
+                                 float* dw, float* dk, float* part, float* tap_part, int B, int d, int L, hipStream_t st);
 inline size_t conv_pairs_bytes(int d, int L)       // the pairs: where the matrix-core copy starts
 {
     const int M = conv_fft_size(L);
@@ -184,12 +186,21 @@ inline size_t conv_bwd_acc_floats(int B, int d, int L, bool bf16_io)
 // one transform of up to 4096 points leaves dV in registers.
 constexpr int kConvFuseTaps = 16, kConvMaxTaps = 32;
 inline bool conv_bwd_fused(int m, int L) { return m > 0 && m <= kConvFuseTaps && L <= 4096; }
+// The matrix-core gradient kernel's workgroups per channel at most: as many slices of dk as the sums' scratch has room for.
+inline int conv_mx_share(int B, int d, int L)
+{
+    size_t n = conv_bwd_acc_floats(B, d, L, true) / ((size_t)d * L);
+    if (n > 64) n = 64;
+    if (n > (size_t)B) n = B;
+    return n < 1 ? 1 : (int)n;
+}
 // m: taps of the short kernel, 0 for none
 inline size_t conv_bwd_ws_floats(int B, int d, int L, int m, bool bf16_io)
 {
     const size_t acc = conv_bwd_acc_floats(B, d, L, bf16_io);
     if (m == 0) return acc;
     if (conv_bwd_fused(m, L)) return acc + (size_t)d * conv_bwd_groups(B, d, L) * kConvMaxTaps;
+    if (bf16_io && convmx_applies(L, 0) && convmx_bwd_short(m, B, d, L)) return acc + (size_t)d * conv_mx_share(B, d, L) * kConvMaxTaps;
     return acc + (size_t)B * d * L + (size_t)B * d * (((size_t)L + 2047) / 2048) * kConvMaxTaps;
 }
 hipError_t launch_shortlong_conv_bwd(const void* X, const float* w_short, int m, const void* Kf, const void* dZ,

@@ -1776,10 +1776,8 @@ static hipError_t conv_bwd_impl(const IO* X, const float* w_short, int m, const 
     // bf16 I/O at the lengths the matrix-core kernels serve: its own copy of the spectrum lies behind the pairs
     const bool mx = sizeof(IO) == 2 && convmx_applies(L, 0);
     const void* mx_spec = (const char*)Kf + conv_pairs_bytes(d, L);
-    // slices of dk that the sums' scratch has room for
-    const int share = mx ? (int)std::min<size_t>(conv_bwd_acc_floats(B, d, L, true) / ((size_t)d * L), 64) : 0;
     if (w_short == nullptr) { // no short stage: v = x and dX is the correlation of dZ with the long kernel itself
-        if (mx) return launch_convmx_longbwd(X, nullptr, 0, mx_spec, dZ, dX, false, dk, (float*)acc_ws, share, B, d, L, st);
+        if (mx) return launch_convmx_longbwd(X, nullptr, 0, mx_spec, dZ, dX, nullptr, dk, (float*)acc_ws, nullptr, B, d, L, st);
         return conv_longbwd_dispatch<IO, IO, false>(X, nullptr, 0, Kf, dZ, dX, dk, acc_ws, nullptr, B, d, L, st);
     }
     if (conv_bwd_fused(m, L)) {
@@ -1790,6 +1788,8 @@ static hipError_t conv_bwd_impl(const IO* X, const float* w_short, int m, const 
         hipLaunchKernelGGL(shortconv_dw_kernel, dim3(d), dim3(64), 0, st, ws, dw, m, G);
         return hipGetLastError();
     }
+    if (mx && convmx_bwd_short(m, B, d, L))
+        return launch_convmx_longbwd(X, w_short, m, mx_spec, dZ, dX, dw, dk, (float*)acc_ws, ws, B, d, L, st);
     float* ws_dV = ws;
     float* ws_part = ws + (size_t)BD * L;                                   // [d][n_share][32] (room for [d][B * tiles][32])
     // workgroups per channel: (batch entry, strip) or (batch entry, tile) pairs over what one takes
@@ -1798,7 +1798,7 @@ static hipError_t conv_bwd_impl(const IO* X, const float* w_short, int m, const 
     const long per_wg = strips ? 4 * kStripsPerWave : kShortTilesPerWg;
     const int n_share = (int)((n_items + per_wg - 1) / per_wg);
     if ((long)d * n_share > 0x7fffffffL || n_items > 0x7ffffff0L) return hipErrorInvalidValue;
-    e = mx ? launch_convmx_longbwd(X, w_short, m, mx_spec, dZ, ws_dV, true, dk, (float*)acc_ws, share, B, d, L, st)
+    e = mx ? launch_convmx_longbwd(X, w_short, m, mx_spec, dZ, ws_dV, nullptr, dk, (float*)acc_ws, nullptr, B, d, L, st)
            : conv_longbwd_dispatch<IO, float, false>(X, w_short, m, Kf, dZ, ws_dV, dk, acc_ws, nullptr, B, d, L, st);
     if (e != hipSuccess) return e;
     {

@@ -31,6 +31,7 @@
 #include "chela_convmx.h"
 #include <cfloat>
 #include <cstdlib>
+#include <type_traits>
 
 namespace chela {
 
@@ -368,17 +369,23 @@ struct MxSeq {
         if (HALO > 0)
             front = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, 2 * (1024 * (lane & 15) + 128 * w - 8 - 8 * (lane >> 4)), 0, 0));
     }
-    // the pieces 8 D steps in front of the rows'
+    // the piece 8 D steps in front of row i's
+    template <int D>
+    __device__ __forceinline__ u32x4 piece(int lane, int i) const
+    {
+        const int from = 16 * (D - 1 - (lane & 15)) + 4 * (lane >> 4);         // (of use to the first D lanes only)
+        u32x4 x;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            x[e] = (unsigned)__builtin_amdgcn_update_dpp(__builtin_amdgcn_ds_bpermute(4 * (from + i), (int)front[e]),
+                                                         (int)r[i][e], 0x110 + D, 0xf, 0xf, false);      // row_shr:D
+        return x;
+    }
     template <int D>
     __device__ __forceinline__ void pieces(int lane, u32x4 (&x)[4]) const
     {
-        const int from = 16 * (D - 1 - (lane & 15)) + 4 * (lane >> 4);         // (of use to the first D lanes only)
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                x[i][e] = (unsigned)__builtin_amdgcn_update_dpp(__builtin_amdgcn_ds_bpermute(4 * (from + i), (int)front[e]),
-                                                                (int)r[i][e], 0x110 + D, 0xf, 0xf, false);      // row_shr:D
+        for (int i = 0; i < 4; ++i) x[i] = piece<D>(lane, i);
     }
     // The wave's largest magnitude (of the steps themselves).
     __device__ __forceinline__ float wave_max() const
@@ -576,6 +583,108 @@ __global__ __launch_bounds__(MX_T, 4) void convmx_fwd_kernel(const bf16* __restr
     }
 }
 
+// ---- the short stage's gradient of one sequence, dV = osc y still in registers (y as mx_last leaves it):
+//   du = dV silu'(u), u = K_s x worked out again;  dX[t] = sum_j w[j] du[t + j];  dw[j] += sum_t du[t] x[t - j], all fp32.
+// A lane's look-ahead comes from the lanes behind it in its row of 16, for the last of them by way of LDS: `edge` holds the first
+// HALO steps of each wave's 128 of each row n1, in the order of the steps, and zeros behind the last.
+// As a kernel of its own this stage read dV (fp32, written by this one) and x again: 768 channels x 4 sequences of 16384 steps, both
+// stages' gradients, 9 taps: 319 -> 279 us (1 tap 313 -> 250, 16 taps 359 -> 340, 17, which that kernel stages, 650 -> 340).
+// TAPS: the number of taps, so that the tap loops are as long as it takes (branches around single taps' products spilled 36 values).
+// Below zero: dV leaves for a kernel of its own, and -TAPS is the history that v needs.
+constexpr int MX_SHORT_TAPS = 17;
+constexpr bool mx_bwd_short(int taps) { return taps > 0 && taps <= MX_SHORT_TAPS; }
+constexpr int mx_halo(int taps) { return taps <= 0 ? -taps : taps <= 9 ? 8 : taps <= 17 ? 16 : 32; }
+template <int TAPS> using mx_dv_t = std::conditional_t<(TAPS >= 0), bf16, float>;
+__device__ __forceinline__ float mx_quad_sum(float v)
+{
+    v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xb1, 0xf, 0xf, true));     // lanes 1 0 3 2
+    return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4e, 0xf, 0xf, true));   // 2 3 0 1
+}
+template <int TAPS>
+__device__ __forceinline__ void mx_short_bwd(const MxSeq<mx_halo(TAPS)>& xs, const unsigned short* taps, const float* __restrict__ wc,
+                                             float (&y)[4][8], float osc, float* edge, float* tsum, bf16* out, int L, int w,
+                                             int tid)
+{
+    constexpr int HALO = mx_halo(TAPS), NH = HALO / 8;
+    static_assert(NH == 1 || NH == 2, "");
+    const int lane = mx_fresh(tid & 63), c = lane & 15, q = lane >> 4;
+    const int t0 = mx_first_step(w, lane);
+    {
+        float u[4][8];
+        xs.short_conv(taps, lane, u);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const bool in = t0 + 1024 * i < L;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float sg = __builtin_amdgcn_rcpf(1.f + __expf(-u[i][e]));
+                float du = (y[i][e] * osc) * sg * (1.f + u[i][e] * (1.f - sg));
+                asm("" : "+v"(du));                  // (a select, not a branch around each exponential)
+                y[i][e] = in ? du : 0.f;
+            }
+        }
+    }
+    if (c < NH) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float4* p = reinterpret_cast<float4*>(edge + (((4 * q + i) * MX_W + w) * NH + c) * 8);
+            p[0] = make_float4(y[i][0], y[i][1], y[i][2], y[i][3]);
+            p[1] = make_float4(y[i][4], y[i][5], y[i][6], y[i][7]);
+        }
+    }
+    if (tid < 8 * NH) edge[16 * MX_W * HALO + tid] = 0.f;
+    __syncthreads();
+    float acc[TAPS], wj[TAPS];
+#pragma unroll
+    for (int j = 0; j < TAPS; ++j) { acc[j] = 0.f; wj[j] = wc[j]; }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        __builtin_amdgcn_sched_barrier(0);
+        float x[8 * (NH + 1)], du[8 * (NH + 1)], dx[8];
+        auto unpack = [&](u32x4 p, int at) __attribute__((always_inline)) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                x[at + 2 * e] = __builtin_bit_cast(float, p[e] << 16);
+                x[at + 2 * e + 1] = __builtin_bit_cast(float, p[e] & 0xffff0000u);
+            }
+        };
+        unpack(xs.r[i], HALO);
+        unpack(xs.template piece<1>(lane, i), HALO - 8);
+        if constexpr (NH == 2) unpack(xs.template piece<2>(lane, i), 0);
+        const float* next = edge + ((4 * q + i) * MX_W + w + 1) * HALO;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) { du[e] = y[i][e]; dx[e] = 0.f; }
+        auto ahead = [&](auto D) __attribute__((always_inline)) {
+            constexpr int dd = decltype(D)::value;
+            const float4* p = reinterpret_cast<const float4*>(next + (c + dd >= 16 ? c + dd - 16 : 0) * 8);
+            const float4 a = p[0], b = p[1];
+            const float o[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                du[8 * dd + e] = __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, o[e]),
+                                                    __builtin_bit_cast(int, y[i][e]), 0x100 + dd, 0xf, 0xf, false));   // row_shl
+        };
+        ahead(std::integral_constant<int, 1>());
+        if constexpr (NH == 2) ahead(std::integral_constant<int, 2>());
+#pragma unroll
+        for (int j = 0; j < TAPS; ++j)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                dx[e] = fmaf(wj[j], du[e + j], dx[e]);
+                acc[j] = fmaf(du[e], x[HALO + e - j], acc[j]);
+            }
+        bf16x8 o;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] = (bf16)dx[e];
+        if (t0 + 1024 * i < L) *reinterpret_cast<bf16x8*>(out + t0 + 1024 * i) = o;
+    }
+#pragma unroll
+    for (int j = 0; j < TAPS; ++j) {
+        const float v = mx_quad_sum(acc[j]);
+        if ((lane & 3) == 0) tsum[j * (MX_T / 4) + (tid >> 2)] += v;
+    }
+}
+
 // The two long-stage gradients of the convolution (they share the spectrum of dZ); a workgroup walks the sequences of a
 // channel, every gridDim.y-th one where a channel is shared, and then those of the next channel blockIdx.x + gridDim.x, ...
 //   dv = corr(dZ, k_long): bins of dZ times the conjugate of the kernel's, back;
@@ -585,23 +694,32 @@ __global__ __launch_bounds__(MX_T, 4) void convmx_fwd_kernel(const bf16* __restr
 // Both sequences' cubes lie in LDS side by side, so that a wave meets the same tile of both.  Sums of dk: all sequences'
 // shares are kept in units of the largest 1 / (scale of dZ_b x scale of v_b) so far (powers of two); the finished sums H are packed times
 // 32768 / (sqrt N |H|_2), which bounds every sum on the way back by 32768 (Cauchy-Schwarz) and leaves a typical bin at order one.
-// One workgroup per compute unit (both cubes: 144 KB of LDS; 256 registers, nothing spilled), issuing vector instructions 64 % of
-// the time.  768 channels x 4 sequences of 16384 steps, 9 taps: 417 -> 240 us (the spectrum of dZ waited in memory for that of
+// One workgroup per compute unit (both cubes: 144 KB of LDS; 256 registers, nothing spilled without the short stage, 5 .. 28 values
+// with it, most of them used at a channel's end only), issuing vector instructions 64 % of the time.  768 channels x 4 sequences of 16384 steps, 9 taps: 417 -> 240 us (the spectrum of dZ waited in memory for that of
 // v, and the sums went back once per pair of sequences).
-// dV: fp32 [B][d][L] for the short-stage kernel, or dX itself (bf16) when there is no short stage (HALO = 0, v = x).
-template <int HALO, typename DVT>
+// mx_bwd_short(TAPS): the short stage's gradient too (dV is dX then, and the taps' sums go to dw): see mx_short_bwd.  Else dV is fp32
+// [B][d][L] for the short-stage kernel, or dX itself when there is no short stage (TAPS = 0, v = x).
+template <int TAPS>
 __global__ __launch_bounds__(MX_T, 2) void convmx_longbwd_kernel(const bf16* __restrict__ X, const float* __restrict__ w_short,
                                                               int m, const unsigned* __restrict__ Ks,
                                                               const float* __restrict__ kscale,
                                                               const MxTables* __restrict__ tables,
-                                                              const bf16* __restrict__ dZ, DVT* __restrict__ dV,
+                                                              const bf16* __restrict__ dZ, mx_dv_t<TAPS>* __restrict__ dV,
+                                                              float* __restrict__ dw, int dw_stride,
                                                               float* __restrict__ dk, int B, int d, int L)
 {
+    typedef mx_dv_t<TAPS> DVT;
+    constexpr int HALO = mx_halo(TAPS);
+    constexpr bool SHORT = mx_bwd_short(TAPS);
+    if (SHORT) m = TAPS;
     __shared__ __attribute__((aligned(16))) unsigned char cube[2][MX_CUBE];       // of dZ, of v
     __shared__ __attribute__((aligned(16))) MxLds tb;
     __shared__ __attribute__((aligned(16))) unsigned short taps[HALO > 0 ? MX_TAP_WORDS(HALO / 8) + 8 : 8];
+    __shared__ float tsum[SHORT ? TAPS * (MX_T / 4) : 1];                   // the taps' sums, a slot per tap and four lanes
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if constexpr (SHORT)
+        for (int x = tid; x < TAPS * (MX_T / 4); x += MX_T) tsum[x] = 0.f;
     mx_fetch_tables(tb, tables, tid);
     MxMat m32;
     mx_fetch_matrix(m32, tables, lane);
@@ -673,22 +791,29 @@ __global__ __launch_bounds__(MX_T, 2) void convmx_longbwd_kernel(const bf16* __r
         const int cc = c;
         const bool done = (b += gridDim.y) >= B;
         if (done) { b = b0; c += gridDim.x; }
-        {       // the next sequence (after the last one: that one again)
-            const long next = c < d ? ((long)b * d + c) * L : row;
-            zs.load(dZ + next, L, w, lane);
-            xs.load(X + next, L, w, lane);
-        }
+        MxSeq<HALO> xc;         // the sequence once more: kept in registers past the tiles it would push others out
+        if constexpr (SHORT) xc.load(X + row, L, w, lane);
+        // the next sequence (after the last one: that one again)
+        const long next = c < d ? ((long)b * d + c) * L : row;
+        xs.load(X + next, L, w, lane);
+        if constexpr (!SHORT) zs.load(dZ + next, L, w, lane);
         float y[4][8];
         mx_last(cube[0], tb, w, lane, y);
         DVT* out = dV + row;
         const int t0 = mx_first_step(w, mx_fresh(lane));
+        if constexpr (SHORT) {
+            // (cube[1] is free from the tiles' barrier on)
+            mx_short_bwd<TAPS>(xc, taps, w_short + (long)cc * TAPS, y, osc, reinterpret_cast<float*>(cube[1]), tsum, out, L, w, tid);
+            zs.load(dZ + next, L, w, lane);     // (not before: there are no registers for it, and v comes first)
+        } else {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            typedef __attribute__((ext_vector_type(8))) DVT out8;
-            out8 o;
+            for (int i = 0; i < 4; ++i) {
+                typedef __attribute__((ext_vector_type(8))) DVT out8;
+                out8 o;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) o[e] = (DVT)(y[i][e] * osc);
-            if (t0 + 1024 * i < L) *reinterpret_cast<out8*>(out + t0 + 1024 * i) = o;
+                for (int e = 0; e < 8; ++e) o[e] = (DVT)(y[i][e] * osc);
+                if (t0 + 1024 * i < L) *reinterpret_cast<out8*>(out + t0 + 1024 * i) = o;
+            }
         }
         if (done) {         // ---- the sums' way back
             if (HALO > 0 && c < d) mx_write_taps<HALO>(taps, w_short + (long)c * m, m, tid);      // (barriers before and behind)
@@ -704,6 +829,16 @@ __global__ __launch_bounds__(MX_T, 2) void convmx_longbwd_kernel(const bf16* __r
             ss = 0.f;
 #pragma unroll
             for (int i = 0; i < MX_W; ++i) ss += tb.red[i];
+            if constexpr (SHORT) {
+                for (int j = w; j < m; j += MX_W) {
+                    float* slot = tsum + j * (MX_T / 4) + lane;
+                    float v = slot[0] + slot[64];
+                    slot[0] = slot[64] = 0.f;
+#pragma unroll
+                    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+                    if (lane == 0) dw[((long)cc * gridDim.y + blockIdx.y) * dw_stride + j] = v;
+                }
+            }
             const float g = ss > 0.f ? 256.f * rsqrtf(ss) : 0.f;             // 32768 / (sqrt(16384) |H|_2)
 #pragma unroll
             for (int n = 0; n < MX_NT; ++n) {
@@ -747,6 +882,16 @@ __global__ __launch_bounds__(256) void mx_dk_kernel(const float4* __restrict__ p
         }
         dk[i] = t;
     }
+}
+
+// dw likewise, of the slices part[c][g][kConvMaxTaps]
+__global__ __launch_bounds__(64) void mx_dw_kernel(const float* __restrict__ part, float* __restrict__ dw, int m, int G)
+{
+    const int c = blockIdx.x, j = threadIdx.x;
+    if (j >= m) return;
+    float t = 0.f;
+    for (int g = 0; g < G; ++g) t += part[((long)c * G + g) * kConvMaxTaps + j];
+    dw[(long)c * m + j] = t;
 }
 
 // ------------------------------------------------------------------------------------------------ host side
@@ -796,38 +941,66 @@ hipError_t launch_convmx_fwd(const void* X, const float* w_short, int m, const v
     return hipGetLastError();
 }
 
+// The gradient kernel's workgroups, one per compute unit.  A channel's sequences are shared out where that shortens the longest
+// workgroup's work: its rounds x (its sequences + 0.4, the sums' way back; + 0.2 with the slices to be added up).  128 channels
+// x 3 sequences of 8192 steps, both stages' gradients: 64 us, in three shares 54.
+static int mx_bwd_shares(int B, int d, int L)
+{
+    const int cus = mx_cus(), max_share = conv_mx_share(B, d, L);
+    int G = 1;
+    float best = 0.f;
+    for (int g = 1; g <= max_share; ++g) {
+        const float t = (float)(((long)d * g + cus - 1) / cus) * ((B + g - 1) / g + (g > 1 ? 0.6f : 0.4f));
+        if (g == 1 || t < best) { best = t; G = g; }
+    }
+    return G;
+}
+
+// The short stage inside that kernel costs the same whatever L is (2 us a sequence with few taps, 3.3 with 9, 5 with 16: the
+// layout's lanes are there for 16384 steps), the kernel of its own and dV on its way through memory go with L and cost two launches.
+// Both stages' gradients, apart and in one, us:
+//   taps                    1            4            9           12           16           17
+//   512 x 4 x  8192    160  161     162  166     164  182     180  205     184  219     284  219
+//   512 x 4 x 10240    174  163     176  168     181  185     198  207     208  222
+//   512 x 4 x 12288    185  166     188  171     191  187     209  211     218  223
+//   512 x 4 x 14336    197  165     198  172     206  186     222  210     234  223
+//   256 x 1 x  4104     33   27      34   27      36   31      38   33      40   36
+//   256 x 1 x 14336     37   30      39   30      40   34      43   36      45   38
+// so: where every workgroup has one sequence, and from a length on that goes with the taps.
+bool convmx_bwd_short(int m, int B, int d, int L, int* shares)
+{
+    if (!mx_bwd_short(m)) return false;
+    const int G = mx_bwd_shares(B, d, L);
+    if (shares) *shares = G;
+    if ((long)d * G <= mx_cus() && G >= B) return true;
+    return L >= (m <= 4 ? 9216 : m <= 9 ? 11264 : m <= 16 ? 13312 : 0);
+}
+
 hipError_t launch_convmx_longbwd(const void* X, const float* w_short, int m, const void* extra, const void* dZ, void* dV,
-                                 bool dv_is_f32, float* dk, float* part, int max_share, int B, int d, int L,
-                                 hipStream_t st)
+                                 float* dw, float* dk, float* part, float* tap_part, int B, int d, int L, hipStream_t st)
 {
     const unsigned* Ks = (const unsigned*)extra;
     const float* scale = (const float*)(Ks + (size_t)d * MX_N);
     const MxTables* tables = mx_tables((void*)extra, d);
-    // One workgroup per compute unit.  A channel's sequences are shared out where that shortens the longest workgroup's work:
-    // its rounds x (its sequences + 0.4, the sums' way back; + 0.2 with the slices to be added up).  128 channels x 3 sequences
-    // of 8192 steps, both stages' gradients: 64 us, in three shares 54.
+    int G;
+    const bool fused = w_short && convmx_bwd_short(m, B, d, L, &G);
+    if (!fused) G = mx_bwd_shares(B, d, L);
     const int cus = mx_cus();
-    int G = 1;
-    float best = 0.f;
-    for (int g = 1; g <= B && g <= max_share; ++g) {
-        const float t = (float)(((long)d * g + cus - 1) / cus) * ((B + g - 1) / g + (g > 1 ? 0.6f : 0.4f));
-        if (g == 1 || t < best) { best = t; G = g; }
-    }
     const long rounds = ((long)d * G + cus - 1) / cus;
     const dim3 grid((unsigned)((d + rounds - 1) / rounds), (unsigned)G);
     float* const sums = G > 1 ? part : dk;
     ProfScope prof(KID_CONV_LONG_BWD, st);
-#define CHELA_MX_BWD(H_, T_)                                                                                            \
-    hipLaunchKernelGGL((convmx_longbwd_kernel<H_, T_>), grid, dim3(MX_T), 0, st, (const bf16*)X, w_short, m, Ks, scale, \
-                       tables, (const bf16*)dZ, (T_*)dV, sums, B, d, L)
-    if (!w_short) {
-        if (dv_is_f32) CHELA_MX_BWD(0, float); else CHELA_MX_BWD(0, bf16);
-    } else if (m <= 9) {
-        if (dv_is_f32) CHELA_MX_BWD(8, float); else CHELA_MX_BWD(8, bf16);
-    } else if (m <= 17) {
-        if (dv_is_f32) CHELA_MX_BWD(16, float); else CHELA_MX_BWD(16, bf16);
-    } else {
-        if (dv_is_f32) CHELA_MX_BWD(32, float); else CHELA_MX_BWD(32, bf16);
+    float* const taps = G > 1 ? tap_part : dw;
+    const int tap_stride = G > 1 ? kConvMaxTaps : m;
+#define CHELA_MX_BWD(T_)                                                                                                \
+    case T_:                                                                                                            \
+        hipLaunchKernelGGL((convmx_longbwd_kernel<T_>), grid, dim3(MX_T), 0, st, (const bf16*)X, w_short, m, Ks, scale, \
+                           tables, (const bf16*)dZ, (mx_dv_t<T_>*)dV, taps, tap_stride, sums, B, d, L);                 \
+        break;
+    switch (!w_short ? 0 : fused ? m : -mx_halo(m)) {
+        CHELA_MX_BWD(-8) CHELA_MX_BWD(-16) CHELA_MX_BWD(-32) CHELA_MX_BWD(0) CHELA_MX_BWD(1) CHELA_MX_BWD(2) CHELA_MX_BWD(3) CHELA_MX_BWD(4) CHELA_MX_BWD(5) CHELA_MX_BWD(6)
+        CHELA_MX_BWD(7) CHELA_MX_BWD(8) CHELA_MX_BWD(9) CHELA_MX_BWD(10) CHELA_MX_BWD(11) CHELA_MX_BWD(12) CHELA_MX_BWD(13)
+        CHELA_MX_BWD(14) CHELA_MX_BWD(15) CHELA_MX_BWD(16) CHELA_MX_BWD(17)
     }
 #undef CHELA_MX_BWD
     if (G > 1) {
@@ -835,6 +1008,8 @@ hipError_t launch_convmx_longbwd(const void* X, const float* w_short, int m, con
         const long wgs = (n4 + 255) / 256;
         hipLaunchKernelGGL(mx_dk_kernel, dim3((unsigned)(wgs < 2048 ? wgs : 2048)), dim3(256), 0, st, (const float4*)part,
                            (float4*)dk, G, n4);
+        if (fused)
+            hipLaunchKernelGGL(mx_dw_kernel, dim3(d), dim3(64), 0, st, tap_part, dw, m, G);
     }
     return hipGetLastError();
 }

@@ -1190,6 +1190,39 @@ def test_matrix_core_conv_gradient_two_channels_per_workgroup():
         _check("dk[c=%d]" % c, dk[c:c + 1], rk, "bf16")
 
 
+@pytest.mark.parametrize("m", range(1, 18))         # every tap count has its own kernel
+def test_matrix_core_conv_gradient_short_stage_in_and_out_of_the_transform_kernel(m):
+    # up to 17 taps the short stage's gradient is part of the transform kernel; the same taps with zeros behind them, 18 in all,
+    # go through memory.  dV has the same bits in both, so dX differs by the order of some fp32 sums of m terms and by the ties
+    # this decides in its rounding to bf16 (one place, 2^-7 at most); dw by the order of its fp32 sums (d channels shared out to
+    # B workgroups, and one workgroup's).  Whole and ragged rows of 1024 steps, look-ahead over the ends of waves and rows;
+    # workgroups that go on with a second channel (the sums start afresh).
+    for B, d, L in ((1, 2, 4096 + 8 * m), (3, 2, 16384 - 8 * (m % 3)), (2, 2, 9216 + 1024 * (m % 2)), (2, 300, 16376)):
+        print("\nm%d B%d d%d L%d" % (m, B, d, L), flush=True)
+        x = _dev(make_conv_inputs(B, d, L, m, L + m, "bf16"))
+        g = torch.Generator(device="cuda")
+        g.manual_seed(L + m + 1)
+        dZ = torch.randn(B, d, L, generator=g, device="cuda").to(torch.bfloat16)
+        spec = binding.chela_longconv_spectrum(x["k_long"])
+        wide = torch.cat([x["w_short"], torch.zeros(d, 18 - m, device="cuda")], 1).contiguous()
+        dX, dw, dk = binding.chela_shortlong_conv_bwd(x["X"], x["w_short"], spec, dZ)
+        rX, rw, rk = binding.chela_shortlong_conv_bwd(x["X"], wide, spec, dZ)
+        a, b = dX.double(), rX.double()
+        assert bool(((a - b).abs() <= 2.0 ** -7 * b.abs() + 1e-6 * b.abs().max()).all()), float((a - b).abs().max())
+        assert float((a - b).norm() / b.norm()) < 2e-4            # (one value in some thousands meets a tie)
+        assert float((dw - rw[:, :m]).norm() / rw[:, :m].norm()) < 2e-5
+        assert float((dk - rk).norm() / rk.norm()) < 1e-5
+        # scratch: the slices of dk and of the taps' sums, nothing for dV and nothing behind
+        need = binding.lib().chela_shortlong_conv_bwd_workspace_bytes(B, d, L, 0, 0) + B * d * 32 * 4
+        buf = torch.full((need + 4096,), 0x5a, dtype=torch.uint8, device="cuda")
+        try:
+            binding.chela_set_workspace(buf[:need])
+            got = binding.chela_shortlong_conv_bwd(x["X"], x["w_short"], spec, dZ)
+        finally:
+            binding.chela_set_workspace(None)
+        assert all(torch.equal(u, v) for u, v in zip(got, (dX, dw, dk))) and bool((buf[need:] == 0x5a).all())
+
+
 def test_matrix_core_conv_gradient_scales_with_its_inputs():
     # half-precision operands inside, every signal scaled on the way in: gradients of inputs far outside the
     # half-precision range (and of an all-zero upstream gradient) come through
