@@ -571,15 +571,14 @@ __global__ __launch_bounds__(MX_T, 4) void convmx_fwd_kernel(const bf16* __restr
     const float osc = kscale[c] / (s * ((float)MX_N * MX_GAIN4));
     float y[4][8];
     mx_last(cube, tb, w, lane, y);
-    bf16* out = Y + row;
+    const __amdgpu_buffer_rsrc_t rs = mx_rsrc(Y + row, 2 * L);        // (stores beyond the row's end are dropped)
     const int t0 = mx_first_step(w, mx_fresh(lane));
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
         bf16x8 o;
 #pragma unroll
         for (int e = 0; e < 8; ++e) o[e] = (bf16)(y[i][e] * osc);
-        if (t0 + 1024 * i < L) *reinterpret_cast<bf16x8*>(out + t0 + 1024 * i) = o;
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), rs, 2 * (t0 + 1024 * i), 0, 0);
     }
 }
 
@@ -588,7 +587,7 @@ __global__ __launch_bounds__(MX_T, 4) void convmx_fwd_kernel(const bf16* __restr
 // A lane's look-ahead comes from the lanes behind it in its row of 16, for the last of them by way of LDS: `edge` holds the first
 // HALO steps of each wave's 128 of each row n1, in the order of the steps, and zeros behind the last.
 // As a kernel of its own this stage read dV (fp32, written by this one) and x again: 768 channels x 4 sequences of 16384 steps, both
-// stages' gradients, 9 taps: 319 -> 279 us (1 tap 313 -> 250, 16 taps 359 -> 340, 17, which that kernel stages, 650 -> 340).
+// stages' gradients, 9 taps: 329 -> 290 us (1 tap 323 -> 261, 12 taps 353 -> 315, 17, which that kernel stages, 675 -> 345; one card, in turn).
 // TAPS: the number of taps, so that the tap loops are as long as it takes (branches around single taps' products spilled 36 values).
 // Below zero: dV leaves for a kernel of its own, and -TAPS is the history that v needs.
 constexpr int MX_SHORT_TAPS = 17;
@@ -634,6 +633,7 @@ __device__ __forceinline__ void mx_short_bwd(const MxSeq<mx_halo(TAPS)>& xs, con
     }
     if (tid < 8 * NH) edge[16 * MX_W * HALO + tid] = 0.f;
     __syncthreads();
+    const __amdgpu_buffer_rsrc_t rs = mx_rsrc(out, 2 * L);        // (stores beyond the row's end are dropped)
     float acc[TAPS], wj[TAPS];
 #pragma unroll
     for (int j = 0; j < TAPS; ++j) { acc[j] = 0.f; wj[j] = wc[j]; }
@@ -676,12 +676,20 @@ __device__ __forceinline__ void mx_short_bwd(const MxSeq<mx_halo(TAPS)>& xs, con
         bf16x8 o;
 #pragma unroll
         for (int e = 0; e < 8; ++e) o[e] = (bf16)dx[e];
-        if (t0 + 1024 * i < L) *reinterpret_cast<bf16x8*>(out + t0 + 1024 * i) = o;
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), rs, 2 * (t0 + 1024 * i), 0, 0);
     }
 #pragma unroll
     for (int j = 0; j < TAPS; ++j) {
-        const float v = mx_quad_sum(acc[j]);
-        if ((lane & 3) == 0) tsum[j * (MX_T / 4) + (tid >> 2)] += v;
+        asm volatile("" : "+v"(acc[j]));          // (summed up by now, all of them side by side, not one after the other below)
+        acc[j] = mx_quad_sum(acc[j]);
+    }
+    if ((lane & 3) == 0) {
+        float* slot = tsum + (tid >> 2);
+        float t[TAPS];
+#pragma unroll
+        for (int j = 0; j < TAPS; ++j) t[j] = slot[j * (MX_T / 4)];
+#pragma unroll
+        for (int j = 0; j < TAPS; ++j) slot[j * (MX_T / 4)] = t[j] + acc[j];
     }
 }
 
@@ -694,7 +702,7 @@ __device__ __forceinline__ void mx_short_bwd(const MxSeq<mx_halo(TAPS)>& xs, con
 // Both sequences' cubes lie in LDS side by side, so that a wave meets the same tile of both.  Sums of dk: all sequences'
 // shares are kept in units of the largest 1 / (scale of dZ_b x scale of v_b) so far (powers of two); the finished sums H are packed times
 // 32768 / (sqrt N |H|_2), which bounds every sum on the way back by 32768 (Cauchy-Schwarz) and leaves a typical bin at order one.
-// One workgroup per compute unit (both cubes: 144 KB of LDS; 256 registers, nothing spilled without the short stage, 5 .. 28 values
+// One workgroup per compute unit (both cubes: 144 KB of LDS; 256 registers, nothing spilled without the short stage, 5 .. 16 values
 // with it, most of them used at a channel's end only), issuing vector instructions 64 % of the time.  768 channels x 4 sequences of 16384 steps, 9 taps: 417 -> 240 us (the spectrum of dZ waited in memory for that of
 // v, and the sums went back once per pair of sequences).
 // mx_bwd_short(TAPS): the short stage's gradient too (dV is dX then, and the taps' sums go to dw): see mx_short_bwd.  Else dV is fp32
@@ -956,24 +964,22 @@ static int mx_bwd_shares(int B, int d, int L)
     return G;
 }
 
-// The short stage inside that kernel costs the same whatever L is (2 us a sequence with few taps, 3.3 with 9, 5 with 16: the
-// layout's lanes are there for 16384 steps), the kernel of its own and dV on its way through memory go with L and cost two launches.
-// Both stages' gradients, apart and in one, us:
-//   taps                    1            4            9           12           16           17
-//   512 x 4 x  8192    160  161     162  166     164  182     180  205     184  219     284  219
-//   512 x 4 x 10240    174  163     176  168     181  185     198  207     208  222
-//   512 x 4 x 12288    185  166     188  171     191  187     209  211     218  223
-//   512 x 4 x 14336    197  165     198  172     206  186     222  210     234  223
-//   256 x 1 x  4104     33   27      34   27      36   31      38   33      40   36
-//   256 x 1 x 14336     37   30      39   30      40   34      43   36      45   38
-// so: where every workgroup has one sequence, and from a length on that goes with the taps.
+// The short stage inside that kernel costs the same whatever L is (the layout's lanes are there for 16384 steps), the kernel of its
+// own and dV on its way through memory go with L and cost two launches.  Both stages' gradients, apart and in one, us:
+//   taps                    1            4            9           10           12           16
+//   512 x 4 x  8192    165  160     160  153     161  160     167  171     172  178     179  187
+//   512 x 4 x  9216    160  149     166  151     169  162     179  172     185  178     190  187
+//   512 x 4 x 11264    176  151     181  154     182  164     191  174     194  180     205  191
+//   512 x 4 x 13312    188  154     190  159     194  168     206  178     212  187     226  201
+// one sequence per workgroup (256 x 1 x 4104): 33 and 27 us with one tap, 40 and 36 with 16; 17 taps (512 x 4 x 4104): 243 and 213.
+// So: where every workgroup has one sequence, and from a length on that goes with the taps.
 bool convmx_bwd_short(int m, int B, int d, int L, int* shares)
 {
     if (!mx_bwd_short(m)) return false;
     const int G = mx_bwd_shares(B, d, L);
     if (shares) *shares = G;
     if ((long)d * G <= mx_cus() && G >= B) return true;
-    return L >= (m <= 4 ? 9216 : m <= 9 ? 11264 : m <= 16 ? 13312 : 0);
+    return L >= (m <= 9 ? 8192 : m <= 16 ? 9216 : 0);
 }
 
 hipError_t launch_convmx_longbwd(const void* X, const float* w_short, int m, const void* extra, const void* dZ, void* dV,
