@@ -35,29 +35,25 @@ __device__ __forceinline__ float2 mx_e(int num, float unit)       // e(num * uni
     sincospif((float)num * (2.0f * unit), &sn, &cs);
     return make_float2(cs, -sn);
 }
-// by 1024 threads
-__device__ __forceinline__ void mx_write_tables(MxTables* __restrict__ tb, int tid)
+// entries i of each, i < MX_TABLE_STEPS
+constexpr int MX_TABLE_STEPS = 8 * 256;
+__device__ __forceinline__ void mx_write_tables(MxTables* __restrict__ tb, int i)
 {
-#pragma unroll 1
-    for (int i = tid; i < 8 * 256; i += 1024) {
-        if (i < 8 * 256) {
-            const int j = i >> 8, k1 = (i >> 4) & 15, n1 = i & 15;
-            // (4 k1 + 1) (1024 n1 + j) / (4 N) of a turn, the whole turns taken off
-            const float2 e = mx_e(((4 * k1 + 1) * (1024 * n1 + j)) & (4 * MX_N - 1), 1.0f / (4.0f * MX_N));
-            tb->T[(2 * j) * 256 + (i & 255)] = (f16)e.x;
-            tb->T[(2 * j + 1) * 256 + (i & 255)] = (f16)e.y;
-        }
-        if (i < 31 * 32) tb->R[i] = mx_e(((i >> 5) + 1) * (i & 31), 1.0f / 1024.0f);
-        if (i < 4 * 64) {
-            const int r = i & 31, h = (i >> 5) & 1, t = (i >> 6) & 1;
-            f16x8 v;
+    const int j = i >> 8, k1 = (i >> 4) & 15, n1 = i & 15;
+    // (4 k1 + 1) (1024 n1 + j) / (4 N) of a turn, the whole turns taken off
+    const float2 e = mx_e(((4 * k1 + 1) * (1024 * n1 + j)) & (4 * MX_N - 1), 1.0f / (4.0f * MX_N));
+    tb->T[(2 * j) * 256 + (i & 255)] = (f16)e.x;
+    tb->T[(2 * j + 1) * 256 + (i & 255)] = (f16)e.y;
+    if (i < 31 * 32) tb->R[i] = mx_e(((i >> 5) + 1) * (i & 31), 1.0f / 1024.0f);
+    if (i < 4 * 64) {
+        const int r = i & 31, h = (i >> 5) & 1, t = (i >> 6) & 1;
+        f16x8 v;
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const float2 p = mx_e((r * (16 * t + 8 * (e >> 2) + 4 * h + (e & 3))) & 31, 1.0f / 32.0f);
-                v[e] = (f16)(MX_ENTRY * (i < 128 ? p.x : -p.y));
-            }
-            tb->M[i] = v;
+        for (int e8 = 0; e8 < 8; ++e8) {
+            const float2 p = mx_e((r * (16 * t + 8 * (e8 >> 2) + 4 * h + (e8 & 3))) & 31, 1.0f / 32.0f);
+            v[e8] = (f16)(MX_ENTRY * (i < 128 ? p.x : -p.y));
         }
+        tb->M[i] = v;
     }
 }
 

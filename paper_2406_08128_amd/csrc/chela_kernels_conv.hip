@@ -668,14 +668,16 @@ __device__ __forceinline__ int fresh(int tid) { asm volatile("" : "+v"(tid)); re
 // MX (M = 16384): also the copy that the matrix-core kernels read, the bins at exp(-2 pi i (k + 1/4) / M) (a transform of its
 // own, of the sequence turned by exp(-2 pi i n / (4 M))), divided by 4 |k|_1, as half-precision (re, im) words, stored where
 // the lane that holds bin k = k1 + 16 k2 + 512 k3 will look: word ((k1 * 4 + a) * 64 + lane) * 4 + b with lane = k2 + 32 h and
-// k3 = 8 a + 4 h + b; scale[c] = 4 |k|_1 (both zero where 0.25 / |k|_1 is no finite number, below 7.4e-40); one workgroup
-// more than there are channels writes those kernels' tables.
+// k3 = 8 a + 4 h + b; scale[c] = 4 |k|_1 (both zero where 0.25 / |k|_1 is no finite number, below 7.4e-40); those kernels'
+// tables are written by one workgroup more than there are channels where that has a compute unit to itself, else by the first
+// channels' on the side (as one more it starts last: 768 channels 69 us, 63 without it and with the loads of the second transform in
+// front of the first one's stores; a single channel 16, with the tables on its side 17).
 template <int M, bool MX>
 __global__ __launch_bounds__(conv_threads(M)) void longconv_spectrum_kernel(const float* __restrict__ k,
                                                                            float4* __restrict__ Kf,
                                                                            uint4* __restrict__ Ks,
                                                                            float* __restrict__ scale,
-                                                                           MxTables* __restrict__ tables, int L)
+                                                                           MxTables* __restrict__ tables, int d, int L)
 {
     static_assert(!MX || M == 16384, "the matrix-core kernels' transform has 2 x 16384 points");
     constexpr int T = conv_threads(M), NP = PairPos<M, T>::NP;
@@ -686,11 +688,18 @@ __global__ __launch_bounds__(conv_threads(M)) void longconv_spectrum_kernel(cons
     const int tid = threadIdx.x;
     const long c = blockIdx.x;
     if constexpr (MX) {
-        if (c == gridDim.x - 1) { mx_write_tables(tables, tid); return; }       // (one workgroup more than channels)
+        if (c >= d) {
+            for (int i = tid; i < MX_TABLE_STEPS; i += T) mx_write_tables(tables, i);
+            return;
+        }
     }
-    build_tables<M, T>(tw, tid);
     SeqRegs<M, T, float> kr;
     kr.load(k + c * (long)L, L, tid);
+    if constexpr (MX) {
+        if ((int)gridDim.x == d)
+            for (long i = c * T + tid; i < MX_TABLE_STEPS; i += (long)d * T) mx_write_tables(tables, (int)i);
+    }
+    build_tables<M, T>(tw, tid);
     cplx z[M / T / 2];
     stage_input<M, T, float>(kr, nullptr, 0, L, a, tid, z);
     if constexpr (MX) {
@@ -720,6 +729,15 @@ __global__ __launch_bounds__(conv_threads(M)) void longconv_spectrum_kernel(cons
         v[1] = (_Float16)(im * inv);
         return __builtin_bit_cast(unsigned, v);
     };
+    // the second transform's input: asked for in front of the stores (a load behind them comes back when they are done)
+    float x2[MX ? M / T : 1];
+    if constexpr (MX) {
+        const __amdgpu_buffer_rsrc_t row = row_rsrc(k + c * (long)L, L * 4);
+#pragma unroll
+        for (int i = 0; i < M / T; ++i)
+            x2[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(row, 4 * (tid + T * i), 0, 0));
+        __builtin_amdgcn_sched_barrier(0);
+    }
     float4* out = Kf + c * (long)(M / 2 + 1);
     const PairPos<M, T> pos(tid);
     const PairTwiddle<M, T> pw(tid);
@@ -732,14 +750,12 @@ __global__ __launch_bounds__(conv_threads(M)) void longconv_spectrum_kernel(cons
     if constexpr (MX) {
         // steps tid + T i this time, turned by exp(-2 pi i (tid + T i) / (4 M)), T i / (4 M) = i / 64
         cplx z2[M / T];
-        const __amdgpu_buffer_rsrc_t row = row_rsrc(k + c * (long)L, L * 4);
         float s, co;
         sincospif(-(float)tid / (float)(2 * M), &s, &co);
         cplx t = mk(co, s);
 #pragma unroll
         for (int i = 0; i < M / T; ++i) {
-            const float x = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(row, 4 * (tid + T * i), 0, 0));
-            z2[i] = mk(x * t.x, x * t.y);
+            z2[i] = mk(x2[i] * t.x, x2[i] * t.y);
             t = cmul(t, mk(0.99518472667219693f, -0.098017140329560602f));
         }
         __syncthreads();                                            // a[] has been read out
@@ -1619,8 +1635,8 @@ hipError_t launch_longconv_spectrum(const float* k, void* Kf, int d, int L, hipS
     float* scale = (float*)(mx + (size_t)d * (MX_N / 4));
     MxTables* tables = mx_tables(mx, d);
 #define CHELA_SPECTRUM(M_, MX_)                                                                                         \
-    case M_: hipLaunchKernelGGL((longconv_spectrum_kernel<M_, MX_>), dim3(d + (MX_ ? 1 : 0)), dim3(conv_threads(M_)), 0, st, \
-                                k, out, mx, scale, tables, L); break;
+    case M_: hipLaunchKernelGGL((longconv_spectrum_kernel<M_, MX_>), dim3(d + (MX_ && d < 256 ? 1 : 0)), dim3(conv_threads(M_)), 0, st, \
+                                k, out, mx, scale, tables, d, L); break;
     switch (M) {
         CHELA_SPECTRUM(256, false) CHELA_SPECTRUM(1024, false) CHELA_SPECTRUM(4096, false)
         case 16384:     // (rows that are no multiple of 8 steps never meet the matrix-core kernels)
