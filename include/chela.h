@@ -281,8 +281,8 @@ int chela_shortlong_conv_fwd_f32(const void *X, const float *w_short, int m, con
  * 3e-4 .. 8e-4 of relative error instead of 1e-6 (CHELA_CONV_MATRIX=0: the vector-ALU kernels, fp32 throughout).
  * Nothing is saved by the forward call: u and v are recomputed from X.  With w_short = NULL (no short stage) dX = dv,
  * v = X and d_w_short is ignored.  m <= 32 as in the forward.  Scratch (library workspace):
- * chela_shortlong_conv_bwd_workspace_bytes(), the most that any tap count takes (up to 16 taps and 4096 steps: without
- * its B*d*L floats).  Sums over batch and time are taken in a fixed order (deterministic). */
+ * chela_shortlong_conv_bwd_workspace_bytes(), the most that any tap count takes (up to 16 taps and 4096 steps, and up to 17
+ * taps on the matrix cores from 9216 steps on at the latest: without its B*d*L floats).  Sums over batch and time are taken in a fixed order (deterministic). */
 int chela_shortlong_conv_bwd(const void *X, const float *w_short, int m, const void *spectrum, const void *dZ,
                              void *dX, float *d_w_short, float *d_k_long, int B, int d, int L, void *stream);
 int chela_shortlong_conv_bwd_f32(const void *X, const float *w_short, int m, const void *spectrum, const void *dZ,

@@ -14,7 +14,7 @@
 // fp32, the part of the first one that differs from step to step of a lane's eight (e((k1 + 1/4) (n3 & 7) / N)) is worked
 // into eight versions of the first matrix.
 //
-// Bound by vector instructions (issuing 83 % of the time in the forward kernel), so the layout is chosen to
+// Bound by vector instructions (issuing three quarters of the time in the forward kernel), so the layout is chosen to
 // spend none on moving data:
 //   - First pass: a lane loads eight consecutive steps of four rows n1, which is its operand of
 //     v_mfma_f32_16x16x16_f16 (contraction over n1), and gets four k1 of the same eight columns.
@@ -703,7 +703,8 @@ __device__ __forceinline__ void mx_short_bwd(const MxSeq<mx_halo(TAPS)>& xs, con
 // shares are kept in units of the largest 1 / (scale of dZ_b x scale of v_b) so far (powers of two); the finished sums H are packed times
 // 32768 / (sqrt N |H|_2), which bounds every sum on the way back by 32768 (Cauchy-Schwarz) and leaves a typical bin at order one.
 // One workgroup per compute unit (both cubes: 144 KB of LDS; 256 registers, nothing spilled without the short stage, 5 .. 16 values
-// with it, most of them used at a channel's end only), issuing vector instructions 64 % of the time.  768 channels x 4 sequences of 16384 steps, 9 taps: 417 -> 240 us (the spectrum of dZ waited in memory for that of
+// with it, most of them used at a channel's end only), issuing vector instructions 69 % of
+// the time with the short stage.  768 channels x 4 sequences of 16384 steps, 9 taps: 417 -> 240 us (the spectrum of dZ waited in memory for that of
 // v, and the sums went back once per pair of sequences).
 // mx_bwd_short(TAPS): the short stage's gradient too (dV is dX then, and the taps' sums go to dw): see mx_short_bwd.  Else dV is fp32
 // [B][d][L] for the short-stage kernel, or dX itself when there is no short stage (TAPS = 0, v = x).

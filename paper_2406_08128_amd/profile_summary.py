@@ -36,9 +36,9 @@ def demangle(name: str) -> str:
         if rest.startswith("I"):
             rest = rest[1:]
             while True:
-                a = re.match(r"L([ib])(\d+)E", rest)
+                a = re.match(r"L([ib])(n?\d+)E", rest)
                 if a:
-                    args.append(a.group(2) if a.group(1) == "i" else ("true" if a.group(2) == "1" else "false"))
+                    args.append(a.group(2).replace("n", "-") if a.group(1) == "i" else ("true" if a.group(2) == "1" else "false"))
                     rest = rest[a.end():]
                     continue
                 t = re.match(r"DF16b|f", rest)           # type arguments: bfloat16, float
