@@ -847,8 +847,8 @@ void shortlong_conv_kernel(const IN* __restrict__ X,
 // Used when there are too few channels to fill the GPU.
 // SHORT: the short stage's gradient as well (m <= kFuseTaps): dV stays in registers, u = K_s x is there already for v,
 // dU = dV silu'(u) meets its neighbours through LDS: dX out (dV is DVT = IO dX here), the taps' sums into `part`
-// ([d][grid.y][kShortMaxTaps]).  As a kernel of its own that stage reads x again, and dV, 4 bytes a step written here and
-// read there, and works u out once more: 512 channels x 32 sequences of 4096 steps, bf16, the two kernels 527 + 150 us,
+// (dw itself; SPLIT: [d][grid.y][kShortMaxTaps], added up by longconv_dk_finish_kernel).  As a kernel of its own that stage reads
+// x again, and dV, 4 bytes a step written here and read there, and works u out once more: 512 channels x 32 sequences of 4096 steps, bf16, the two kernels 527 + 150 us,
 // in one 475, and 407 .. 416 with what came after (3080 instructions per wave and sequence, issuing 82 % of the time).
 // bf16 I/O asks for three workgroups per compute unit (168 registers; values spilled: 30 with shared channels, 45 with one
 // workgroup per channel, at M = 1024 31 and 48; training step 645 us against 707 with two and nothing spilled), fp32 I/O,
@@ -1068,7 +1068,7 @@ void longconv_bwd_kernel(const IO* __restrict__ X,
             for (int x = tid & 63; x < T / 4; x += 64) v += taps[j * (T / 4) + x];
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-            if ((tid & 63) == 0) part[((long)c * gridDim.y + blockIdx.y) * kShortMaxTaps + j] = v;
+            if ((tid & 63) == 0) part[((long)c * gridDim.y + blockIdx.y) * (SPLIT ? kShortMaxTaps : m) + j] = v;
         }
     }
     if constexpr (SPLIT) {
@@ -1708,10 +1708,14 @@ hipError_t launch_shortlong_conv(const void* X, const float* w_short, int m, con
     return conv_dispatch<float, float>((const float*)X, w_short, m, (const float4*)Kf, (float*)Y, BD, d, L, st);
 }
 
-// Second step of the split long-stage gradient: add up the G slices of a channel's sums, transform back, store dk.
+// Second step of the split long-stage gradient: add up the G slices of a channel's sums, transform back, store dk.  dw (may be
+// null): the tap sums' shares part_w[d][G][kShortMaxTaps] as well; with a launch of its own for them 128 channels x 3 sequences
+// of 1000 steps took 25.3 us, so 23.7 (512 x 1 x 4096, whose kernel writes dw itself: 28.4, 26.1; 32 x 512 x 4096: 423.5, 422.3).
 template <int M>
 __global__ __launch_bounds__(conv_threads(M)) void longconv_dk_finish_kernel(const float4* __restrict__ part,
-                                                                            float* __restrict__ dk, int G, int d, int L)
+                                                                            float* __restrict__ dk, int G, int d, int L,
+                                                                            const float* __restrict__ part_w,
+                                                                            float* __restrict__ dw, int m)
 {
     constexpr int T = conv_threads(M);
     __shared__ __attribute__((aligned(16))) unsigned char lds[ConvLds<M>::BYTES];
@@ -1719,6 +1723,11 @@ __global__ __launch_bounds__(conv_threads(M)) void longconv_dk_finish_kernel(con
     float4* tw = reinterpret_cast<float4*>(a + ConvLds<M>::DATA);
     const int tid = threadIdx.x;
     const int c = blockIdx.x;
+    if (M <= 4096 && dw != nullptr && tid < m) {        // (beyond, the short stage is not part of the kernel in front)
+        float t = 0.f;
+        for (int g = 0; g < G; ++g) t += part_w[((long)c * G + g) * kShortMaxTaps + tid];
+        dw[(long)c * m + tid] = t;
+    }
     build_tables<M, T>(tw, tid);
     const PairPos<M, T> pos(tid);
     const PairTwiddle<M, T> pw(tid);
@@ -1742,10 +1751,10 @@ __global__ __launch_bounds__(conv_threads(M)) void longconv_dk_finish_kernel(con
     store_steps<M, T, float>(z, dk + (long)c * L, L, (L & 1) == 0, 1.0f / (float)M, tid);
 }
 
-// SHORT: the short stage's gradient in the same kernel (dV is dX then, `part` takes the tap sums).
+// SHORT: the short stage's gradient in the same kernel (dV is dX then, `part` is scratch for the tap sums of shared channels).
 template <typename IO, typename DVT, bool SHORT>
 static hipError_t conv_longbwd_dispatch(const IO* X, const float* w, int m, const float4* Kf, const IO* dZ, DVT* dV,
-                                        float* dk, float4* acc_ws, float* part, int B, int d, int L, hipStream_t st)
+                                        float* dk, float* dw, float4* acc_ws, float* part, int B, int d, int L, hipStream_t st)
 {
     const int M = conv_fft_size(L), G = conv_bwd_groups(B, d, L);
     ProfScope prof(KID_CONV_LONG_BWD, st);
@@ -1767,10 +1776,11 @@ static hipError_t conv_longbwd_dispatch(const IO* X, const float* w, int m, cons
         if (G > 1) {                                                                                                    \
             hipLaunchKernelGGL((longconv_bwd_kernel<M_, IO, DVT, true, SHORT_>), grid, dim3(conv_threads(M_)), 0, st, X, w, \
                                m, Kf, dZ, dV, dk, acc_ws, part, B, d, L);                                               \
-            hipLaunchKernelGGL((longconv_dk_finish_kernel<M_>), dim3(d), dim3(conv_threads(M_)), 0, st, acc_ws, dk, G, d, L); \
+            hipLaunchKernelGGL((longconv_dk_finish_kernel<M_>), dim3(d), dim3(conv_threads(M_)), 0, st, acc_ws, dk, G, d, L, \
+                               part, SHORT_ ? dw : nullptr, m);                                                         \
         } else                                                                                                          \
             hipLaunchKernelGGL((longconv_bwd_kernel<M_, IO, DVT, false, SHORT_>), grid, dim3(conv_threads(M_)), 0, st, X, w, \
-                               m, Kf, dZ, dV, dk, acc_ws, part, B, d, L);                                               \
+                               m, Kf, dZ, dV, dk, acc_ws, dw, B, d, L);                                                 \
         break;
     switch (M) {
         CHELA_LONGBWD(256, SHORT) CHELA_LONGBWD(1024, SHORT) CHELA_LONGBWD(4096, SHORT) CHELA_LONGBWD(16384, false)
@@ -1794,16 +1804,10 @@ static hipError_t conv_bwd_impl(const IO* X, const float* w_short, int m, const 
     const void* mx_spec = (const char*)Kf + conv_pairs_bytes(d, L);
     if (w_short == nullptr) { // no short stage: v = x and dX is the correlation of dZ with the long kernel itself
         if (mx) return launch_convmx_longbwd(X, nullptr, 0, mx_spec, dZ, dX, nullptr, dk, (float*)acc_ws, nullptr, B, d, L, st);
-        return conv_longbwd_dispatch<IO, IO, false>(X, nullptr, 0, Kf, dZ, dX, dk, acc_ws, nullptr, B, d, L, st);
+        return conv_longbwd_dispatch<IO, IO, false>(X, nullptr, 0, Kf, dZ, dX, dk, nullptr, acc_ws, nullptr, B, d, L, st);
     }
-    if (conv_bwd_fused(m, L)) {
-        const int G = conv_bwd_groups(B, d, L);                             // workgroups that share a channel (<= B)
-        e = conv_longbwd_dispatch<IO, IO, true>(X, w_short, m, Kf, dZ, dX, dk, acc_ws, ws, B, d, L, st);
-        if (e != hipSuccess) return e;
-        ProfScope prof(KID_CONV_SHORT_BWD, st);
-        hipLaunchKernelGGL(shortconv_dw_kernel, dim3(d), dim3(64), 0, st, ws, dw, m, G);
-        return hipGetLastError();
-    }
+    if (conv_bwd_fused(m, L))
+        return conv_longbwd_dispatch<IO, IO, true>(X, w_short, m, Kf, dZ, dX, dk, dw, acc_ws, ws, B, d, L, st);
     if (mx && convmx_bwd_short(m, B, d, L))
         return launch_convmx_longbwd(X, w_short, m, mx_spec, dZ, dX, dw, dk, (float*)acc_ws, ws, B, d, L, st);
     float* ws_dV = ws;
@@ -1815,7 +1819,7 @@ static hipError_t conv_bwd_impl(const IO* X, const float* w_short, int m, const 
     const int n_share = (int)((n_items + per_wg - 1) / per_wg);
     if ((long)d * n_share > 0x7fffffffL || n_items > 0x7ffffff0L) return hipErrorInvalidValue;
     e = mx ? launch_convmx_longbwd(X, w_short, m, mx_spec, dZ, ws_dV, nullptr, dk, (float*)acc_ws, nullptr, B, d, L, st)
-           : conv_longbwd_dispatch<IO, float, false>(X, w_short, m, Kf, dZ, ws_dV, dk, acc_ws, nullptr, B, d, L, st);
+           : conv_longbwd_dispatch<IO, float, false>(X, w_short, m, Kf, dZ, ws_dV, dk, nullptr, acc_ws, nullptr, B, d, L, st);
     if (e != hipSuccess) return e;
     {
         ProfScope prof(KID_CONV_SHORT_BWD, st);

@@ -880,9 +880,16 @@ __global__ __launch_bounds__(MX_T, 2) void convmx_longbwd_kernel(const bf16* __r
     }
 }
 
-// dk = the sum of the slices part[g][n], in a fixed order; n a multiple of 4.
-__global__ __launch_bounds__(256) void mx_dk_kernel(const float4* __restrict__ part, float4* __restrict__ dk, int G, long n4)
+// dk = the sum of the slices part[g][n], in a fixed order; n a multiple of 4.  dw (may be null): likewise, of part_w[c][g][kConvMaxTaps].
+__global__ __launch_bounds__(256) void mx_dk_kernel(const float4* __restrict__ part, float4* __restrict__ dk, int G, long n4,
+                                                    const float* __restrict__ part_w, float* __restrict__ dw, int d, int m)
 {
+    if (dw != nullptr && threadIdx.x < m)
+        for (long c = blockIdx.x; c < d; c += gridDim.x) {
+            float t = 0.f;
+            for (int g = 0; g < G; ++g) t += part_w[(c * G + g) * kConvMaxTaps + threadIdx.x];
+            dw[c * m + threadIdx.x] = t;
+        }
     for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < n4; i += (long)gridDim.x * 256) {
         float4 t = part[i];
         for (int g = 1; g < G; ++g) {
@@ -891,16 +898,6 @@ __global__ __launch_bounds__(256) void mx_dk_kernel(const float4* __restrict__ p
         }
         dk[i] = t;
     }
-}
-
-// dw likewise, of the slices part[c][g][kConvMaxTaps]
-__global__ __launch_bounds__(64) void mx_dw_kernel(const float* __restrict__ part, float* __restrict__ dw, int m, int G)
-{
-    const int c = blockIdx.x, j = threadIdx.x;
-    if (j >= m) return;
-    float t = 0.f;
-    for (int g = 0; g < G; ++g) t += part[((long)c * G + g) * kConvMaxTaps + j];
-    dw[(long)c * m + j] = t;
 }
 
 // ------------------------------------------------------------------------------------------------ host side
@@ -1014,9 +1011,7 @@ hipError_t launch_convmx_longbwd(const void* X, const float* w_short, int m, con
         const long n4 = (long)d * L / 4;
         const long wgs = (n4 + 255) / 256;
         hipLaunchKernelGGL(mx_dk_kernel, dim3((unsigned)(wgs < 2048 ? wgs : 2048)), dim3(256), 0, st, (const float4*)part,
-                           (float4*)dk, G, n4);
-        if (fused)
-            hipLaunchKernelGGL(mx_dw_kernel, dim3(d), dim3(64), 0, st, tap_part, dw, m, G);
+                           (float4*)dk, G, n4, tap_part, fused ? dw : nullptr, d, m);
     }
     return hipGetLastError();
 }
