@@ -191,10 +191,12 @@ def bench_conv(args, w, torch, binding):
     flops = B * d * (2 * 5 * M * math.log2(M) + 20 * M / 2 + 2 * m * L)       # one launch of the forward kernel
     alg = B * d * L * es * 2 + d * ((nb * 8193) if nb else (M // 2 + 1)) * 16   # X in, Z out, the kernel spectrum once
     achieved = flops / (us * 1e-6) / 1e12
-    # bf16 I/O at 4096 < L <= 16384 (L a multiple of 8) runs the transforms on the matrix cores: 1280 instructions of
-    # 32768 flop per pair of sequences and forward call, fp16 operands, fp32 sums
+    # bf16 I/O at 4096 < L <= 16384 (L a multiple of 8) runs the transforms on the matrix cores, fp16 operands, fp32 sums: per
+    # sequence and forward call eight waves of 64 instructions of 32768 flop, 32 of 8192 and, for the last pass and the short
+    # kernel's pieces of 8 steps, 8 + 24 each of 16384
     matrix = dt == "bf16" and 4096 < L <= 16384 and L % 8 == 0 and os.environ.get("CHELA_CONV_MATRIX", "1") != "0"
-    mfma_flop = d * ((B + 1) // 2) * 1280 * 32768 if matrix else 0
+    pieces = 2 if m <= 9 else 3 if m <= 17 else 5
+    mfma_flop = d * B * 8 * (64 * 32768 + 32 * 8192 + (8 + 24 * pieces) * 16384) if matrix else 0
     cpu = None
     if not args.no_cpu_baseline:
         from oracle import conv as oracle_conv
