@@ -709,7 +709,11 @@ __device__ __forceinline__ void mx_short_bwd(const MxSeq<mx_halo(TAPS)>& xs, con
 //   added up over the sequences in fp32 registers, back once per channel.  At the points used a negative lag is imaginary,
 //   as is the second half of a causal sum.
 // Both sequences' cubes lie in LDS side by side, so that a wave meets the same tile of both.  Sums of dk: all sequences'
-// shares are kept in units of the largest 1 / (scale of dZ_b x scale of v_b) so far (powers of two); the finished sums H are packed times
+// shares are kept in units of the largest 1 / (scale of dZ_b x scale of v_b) so far (powers of two).  A quieter sequence's factor
+// goes with v's scale down to 1/16 (half precision has the exponents), for what is left of it the sums change their unit for the
+// time: all of it in v's scale, a sequence entered with fewer and fewer bits (2^23 below the loudest its share of dk came out 0.3
+// times what it is, now right to the loud one's rounding).  Below 2^-64 the way back's half precision has nothing left of it.
+// The finished sums H are packed times
 // 32768 / (sqrt N |H|_2), which bounds every sum on the way back by 32768 (Cauchy-Schwarz) and leaves a typical bin at order one.
 // One workgroup per compute unit (both cubes: 144 KB of LDS; 256 registers, nothing spilled without the short stage, 5 .. 16 values
 // with it, most of them used at a channel's end only), issuing vector instructions 69 % of
@@ -761,7 +765,7 @@ __global__ __launch_bounds__(MX_T, 2) void convmx_longbwd_kernel(const bf16* __r
         for (int i = 0; i < 16; ++i) hr[n][i] = hi[n][i] = 0.f;
     for (int c = blockIdx.x, b = b0; c < d;) {
         const long row = ((long)b * d + c) * L;
-        float s_d, f;           // f: from the sums' unit so far to the present one
+        float s_d, f, rest;     // f: from the sums' unit so far to that of v's scale; rest: from there to the present one
         {
             float v[4][8];
             xs.activated(taps, L, w, lane, v);
@@ -775,8 +779,11 @@ __global__ __launch_bounds__(MX_T, 2) void convmx_longbwd_kernel(const bf16* __r
             const float sv = mx_scale(bv), here = bd > 0.f && bv > 0.f ? 1.0f / (s_d * sv) : 0.f;
             f = here > unit ? unit / here : 1.f;
             if (here > unit) unit = here;
-            const float s_v = unit > 0.f ? sv * (here / unit) : 0.f;
-            mx_first<HALO == 0>(cube[1], tb, lc, v, s_v, w, lane);
+            const float rel = unit > 0.f ? here / unit : 0.f;
+            rest = rel < 0x1p-4f && rel >= 0x1p-64f ? rel * 0x1p4f : 1.f;
+            rest = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, rest)));
+            if (rest != 1.f) f = 1.f / rest;
+            mx_first<HALO == 0>(cube[1], tb, lc, v, sv * (rel / rest), w, lane);
             __builtin_amdgcn_sched_barrier(0);
             zs.values(v);
             mx_first<true>(cube[0], tb, lc, v, s_d, w, lane);
@@ -803,6 +810,12 @@ __global__ __launch_bounds__(MX_T, 2) void convmx_longbwd_kernel(const bf16* __r
             mx_product<true>(zr, zi, kq, re, im);
             mx_tile_out(cube[0], tb, m32, lc.u, st[n], k1, lane, re, im);
             __builtin_amdgcn_sched_barrier(0);
+        }
+        if (rest != 1.f) {
+#pragma unroll
+            for (int n = 0; n < MX_NT; ++n)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) { hr[n][i] *= rest; hi[n][i] *= rest; }
         }
         __syncthreads();
         const float osc = kscale[c] / (s_d * ((float)MX_N * MX_GAIN4));

@@ -1282,6 +1282,36 @@ def test_matrix_core_conv_when_the_taps_cancel_everywhere_but_behind_the_end(sha
         assert oracle.rel_l2(to_f64_numpy(dk[c]), rk[0]) <= 1e-3, c
 
 
+@pytest.mark.parametrize("loud", [0, 5])
+@pytest.mark.parametrize("bits", [3, 6, 16, 23])
+def test_matrix_core_conv_gradient_keeps_a_quiet_sequences_share(bits, loud):
+    # one workgroup takes all sequences of a channel: a pair of impulses, an all-zero sequence and four that are quieter by 2^-bits
+    # (products of dZ's and v's magnitudes; the kernel keeps the sums in the loudest one's unit).  The impulses' share of dk is one
+    # lag, over the others the quiet ones' share shows.  Both may be off by the 8e-4 the header states at most.  That of the impulses
+    # is 5 times the quiet share at 2^-23, but projected on 16384 lags 0.04 a channel, in the mean of 256 channels 0.002.
+    B, d, L, zero = 6, 256, 16384, 2
+    x = make_conv_inputs(B, d, L, 1, 71, "bf16")
+    g = torch.Generator(device="cpu")
+    g.manual_seed(72)
+    dZ = torch.randn(B, d, L, generator=g, dtype=torch.float32) * 2.0 ** -(bits // 2)
+    X = x["X"].float() * 2.0 ** -(bits - bits // 2)
+    X[zero], dZ[zero], X[loud], dZ[loud] = 0, 0, 0, 0
+    X, dZ = X.to(torch.bfloat16), dZ.to(torch.bfloat16)
+    v, gz = np.fft.rfft(to_f64_numpy(X), 2 * L), np.fft.rfft(to_f64_numpy(dZ), 2 * L)
+    quiet = np.fft.irfft((gz * v.conj()).sum(0), 2 * L)[:, :L]
+    X[loud, :, 100], dZ[loud, :, 3000] = 4, 4
+    spec = binding.chela_longconv_spectrum(x["k_long"].cuda())
+    _, _, dk = binding.chela_shortlong_conv_bwd(X.cuda(), None, spec, dZ.cuda())
+    err = to_f64_numpy(dk) - quiet
+    err[:, 2900] -= 16                     # (the impulses: 4 x 4 at lag 3000 - 100)
+    off = (err * quiet).sum(1) / (quiet * quiet).sum(1)
+    print("quiet by 2^-%d, loud at %d: share off by %.2e in the mean, %.2e rms; error / share %.2e"
+          % (bits, loud, off.mean(), np.sqrt((off ** 2).mean()), np.linalg.norm(err) / np.linalg.norm(quiet)), flush=True)
+    noise = 8e-4 * 16 * d ** 0.5 / np.linalg.norm(quiet)
+    rms, mean, whole = float(np.sqrt((off ** 2).mean())), float(abs(off.mean())), float(np.linalg.norm(err) / np.linalg.norm(quiet))
+    assert rms <= noise / 64 + 1e-4 and mean <= noise / 512 + 1e-4 and whole <= noise + 8e-4
+
+
 @pytest.mark.parametrize("case", [(1000, "bf16"), (4104, "bf16"), (16384, "bf16"), (5000, "f32"), (16384, "f32"),
                                   (20000, "f32")])
 def test_conv_channels_whose_long_kernel_has_decayed_to_almost_nothing(case):
