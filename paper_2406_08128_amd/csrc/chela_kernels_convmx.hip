@@ -514,7 +514,7 @@ __device__ __forceinline__ void mx_product(const f32x16& xr, const f32x16& xi, c
         }
 }
 
-// One sequence per workgroup, id = c B + b.  HALO: steps of history the short kernel needs (m - 1 <= HALO; v = silu(K_s x));
+// One sequence per workgroup, id = c B + b, ids first .. end - 1.  HALO: steps of history the short kernel needs (m - 1 <= HALO; v = silu(K_s x));
 // 0: no short kernel, v = x.  L is a multiple of 8.
 // Two workgroups per compute unit (80 KB of LDS, 128 registers): one's activation runs beside the other's matrix products.
 // Workgroups that walk several sequences with the next
@@ -527,15 +527,15 @@ __global__ __launch_bounds__(MX_T, 4) void convmx_fwd_kernel(const bf16* __restr
                                                              int m, const unsigned* __restrict__ Ks,
                                                              const float* __restrict__ kscale, const MxTables* __restrict__ tables,
                                                              bf16* __restrict__ Y, int B,
-                                                             int d, int L, int total)
+                                                             int d, int L, int first, int end)
 {
     __shared__ __attribute__((aligned(16))) unsigned char cube[MX_CUBE];
     __shared__ __attribute__((aligned(16))) MxLds tb;
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     // consecutive workgroups run on the eight XCDs in turn: those of one XCD take neighbouring ids, which share spectra in its L2
-    const int id = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-    if (id >= total) return;
+    const int id = first + (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    if (id >= end) return;
     const int c = id / B, b = id - c * B;
     const long row = ((long)b * d + c) * L;
     MxSeq<HALO> xs;
@@ -996,17 +996,24 @@ hipError_t launch_convmx_fwd(const void* X, const float* w_short, int m, const v
     const MxTables* tables = mx_tables((void*)extra, d);
     const long total = (long)d * B;
     if (total > 0x7ffffff0L) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)((total + 7) / 8 * 8));
     ProfScope prof(KID_CONV_FWD, st);
+    // (a launch has less than 2^32 threads: 2^23 sequences are one too many)
+    constexpr long most = 1L << 22;
+    for (long first = 0; first < total; first += most) {
+        const long end = total - first < most ? total : first + most;
+        const dim3 grid((unsigned)((end - first + 7) / 8 * 8));
 #define CHELA_MX_FWD(H_)                                                                                                \
     hipLaunchKernelGGL((convmx_fwd_kernel<H_>), grid, dim3(MX_T), 0, st, (const bf16*)X, w_short, m, Ks, scale, tables,    \
-                       (bf16*)Y, B, d, L, (int)total)
-    if (!w_short) CHELA_MX_FWD(0);
-    else if (m <= 9) CHELA_MX_FWD(8);
-    else if (m <= 17) CHELA_MX_FWD(16);
-    else CHELA_MX_FWD(32);
+                       (bf16*)Y, B, d, L, (int)first, (int)end)
+        if (!w_short) CHELA_MX_FWD(0);
+        else if (m <= 9) CHELA_MX_FWD(8);
+        else if (m <= 17) CHELA_MX_FWD(16);
+        else CHELA_MX_FWD(32);
 #undef CHELA_MX_FWD
-    return hipGetLastError();
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // The gradient kernel's workgroups, one per compute unit.  A channel's sequences are shared out where that shortens the longest

@@ -1335,6 +1335,26 @@ def test_matrix_core_conv_gradient_of_infinities_in_x_reaches_their_neighbours_o
     assert torch.equal(got[0], ref[0])
 
 
+def test_matrix_core_conv_of_more_sequences_than_one_launch_has_workgroups():
+    # 2^23 sequences and some: as one launch of 512 threads each they would be 2^32 threads, which is refused.  The same three
+    # batch entries over and over: a sequence's result does not depend on its place, so all have the bits of a small call's.
+    d, L, n = 128, 4104, 65538
+    if torch.cuda.mem_get_info()[0] < 150e9:
+        pytest.skip("needs 138 GB of device memory")
+    x = _dev(make_conv_inputs(3, d, L, 5, 91, "bf16"))
+    spec = binding.chela_longconv_spectrum(x["k_long"])
+    ref = binding.chela_shortlong_conv_fwd(x["X"], x["w_short"], spec)
+    torch.cuda.empty_cache()
+    X = torch.empty(n, d, L, dtype=torch.bfloat16, device="cuda")
+    X.view(n // 3, 3, d, L).copy_(x["X"].expand(n // 3, 3, d, L))
+    Z = binding.chela_shortlong_conv_fwd(X, x["w_short"], spec)
+    del X
+    for part in Z.view(n // 3, 3, d, L).split(1024):
+        assert bool((part == ref).all())
+    del Z, part
+    torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("case", [(1000, "bf16"), (4104, "bf16"), (16384, "bf16"), (5000, "f32"), (16384, "f32"),
                                   (20000, "f32")])
 def test_conv_channels_whose_long_kernel_has_decayed_to_almost_nothing(case):
