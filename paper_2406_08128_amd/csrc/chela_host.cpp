@@ -27,6 +27,11 @@ bool plain(PyObject* o, at::ScalarType type, c10::DeviceIndex dev)
                c10::DispatchKey::FuncTorchGradWrapper, c10::DispatchKey::Functionalize, c10::DispatchKey::Python}));
 }
 
+struct without_interpreter_lock {
+    PyThreadState* const state = PyEval_SaveThread();
+    ~without_interpreter_lock() { PyEval_RestoreThread(state); }
+};
+
 PyObject* step(PyObject*, PyObject* const* a, Py_ssize_t n)
 {
     HANDLE_TH_ERRORS
@@ -50,16 +55,22 @@ PyObject* step(PyObject*, PyObject* const* a, Py_ssize_t n)
     if (oy != Py_None && THPVariable_Unpack(oy).sizes() != v.sizes()) Py_RETURN_NONE;
     const unsigned long long fn = PyLong_AsUnsignedLongLong(a[0]);
     if (PyErr_Occurred()) return nullptr;
-    at::Tensor y = oy != Py_None ? THPVariable_Unpack(oy) : at::empty({B, H, dv}, q.options().requires_grad(false));
-    void* st = (void*)c10::hip::getCurrentHIPStream(dev).stream();
+    const void *pq = q.data_ptr(), *pk = k.data_ptr(), *pv = v.data_ptr();
+    const void* pg = og != Py_None ? THPVariable_Unpack(og).data_ptr() : nullptr;
+    float *pS = (float*)S.data_ptr(), eps = (float)PyFloat_AS_DOUBLE(a[6]);
+    const at::TensorOptions like = q.options().requires_grad(false);
+    at::Tensor y;
+    if (oy != Py_None) y = THPVariable_Unpack(oy);
     int rc;
-    if (og == Py_None)
-        rc = reinterpret_cast<step_fn>(fn)(q.data_ptr(), k.data_ptr(), v.data_ptr(), (float*)S.data_ptr(), y.data_ptr(), (int)B, (int)H,
-                                           (int)dk, (int)dv, st);
-    else
-        rc = reinterpret_cast<step_gated_fn>(fn)(q.data_ptr(), k.data_ptr(), v.data_ptr(), THPVariable_Unpack(og).data_ptr(),
-                                                 (float*)S.data_ptr(), y.data_ptr(), (float)PyFloat_AS_DOUBLE(a[6]), (int)B, (int)H,
-                                                 (int)dk, (int)dv, st);
+    {
+        // (both may wait for the GPU, the launch for room in a queue: other threads go on, as they do through ctypes)
+        const without_interpreter_lock free;
+        if (oy == Py_None) y = at::empty({B, H, dv}, like);
+        void *py = y.data_ptr(), *st = (void*)c10::hip::getCurrentHIPStream(dev).stream();
+        rc = og == Py_None
+                 ? reinterpret_cast<step_fn>(fn)(pq, pk, pv, pS, py, (int)B, (int)H, (int)dk, (int)dv, st)
+                 : reinterpret_cast<step_gated_fn>(fn)(pq, pk, pv, pg, pS, py, eps, (int)B, (int)H, (int)dk, (int)dv, st);
+    }
     if (rc != 0) return PyLong_FromLong(rc);
     if (oy != Py_None) { Py_INCREF(oy); return oy; }
     return THPVariable_Wrap(std::move(y));

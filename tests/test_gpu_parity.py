@@ -944,6 +944,16 @@ def test_decode_step_host_path_and_the_bindings_own_lines_agree(dk, dv, gated):
     assert torch.equal(S1, S2)
 
 
+def test_decode_step_host_path_lets_other_threads_run():
+    # as the library's "function" one that says whether this thread holds the interpreter's lock: 0 is the library's OK
+    import ctypes
+    q, k, v = (torch.zeros(1, 2, 64, dtype=torch.bfloat16, device="cuda") for _ in range(3))
+    S = torch.zeros(1, 2, 64, 64, device="cuda")
+    held = ctypes.cast(ctypes.pythonapi.PyGILState_Check, ctypes.c_void_p).value
+    for g in (None, v):
+        assert torch.is_tensor(binding._load_step()(held, q, k, v, g, S, 1e-5, None, None))
+
+
 # ------------------------------------------------------------------------------------------ short-long convolution
 def _run_conv_case(B, d, L, m, dtype, seed=0, short=True):
     print("\nconv B%d d%d L%d m%d %s short=%s" % (B, d, L, m, dtype, short), flush=True)
