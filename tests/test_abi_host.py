@@ -598,3 +598,14 @@ def test_host_module_brings_no_per_thread_data(L):
     size, count = struct.unpack_from("<HH", data, 54)
     kinds = [struct.unpack_from("<I", data, off + i * size)[0] for i in range(count)]
     assert 1 in kinds and 7 not in kinds          # loadable segments, and no PT_TLS
+
+
+def test_host_module_that_does_not_load_leaves_the_bindings_own_path(L, monkeypatch, tmp_path):
+    from paper_2406_08128_amd import binding
+    binding.lib()
+    monkeypatch.setattr(binding, "_HERE", str(tmp_path))
+    monkeypatch.setattr(binding, "_step_host", None)
+    (tmp_path / "_chela_host.so").write_bytes(b"built for something else")
+    with pytest.warns(RuntimeWarning, match="slower host path"):
+        step = binding._load_step()
+    assert step(0, None, None, None, None, None, 0.0, None, None) is None and binding._step_host is step
