@@ -34,26 +34,34 @@ def _compile(src: str) -> str:
     return obj
 
 
-def _build_host_module() -> str:
-    """The decode step's host path as a Python module (csrc/chela_host.cpp): host code only, against torch's headers.
+def _build_host_module() -> bool:
+    """The decode step's host path as a Python module (csrc/chela_host.cpp): host code only, against torch's headers.  It is a
+    shortcut: where there is no compiler for it or no headers the library is built all the same, and no module of an earlier build
+    stays beside it.
     NDEBUG keeps a per-thread counter of pybind11's reference counting out of it: once a library with per-thread data of its
     own that nothing reads has been loaded, this C library looks up the per-thread data of every older library the slow way,
     and each call into torch took a fifth to a third longer for the rest of the process (an attention call's host side 12.0 us,
     without it 10.0)."""
     import sysconfig
-    import torch
-    tdir = os.path.dirname(os.path.abspath(torch.__file__))
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-DNDEBUG", "-D__HIP_PLATFORM_AMD__=1",
-           "-DUSE_ROCM=1",
-           "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-I" + os.path.join(tdir, "include"),
-           "-I" + os.path.join(tdir, "include", "torch", "csrc", "api", "include"),
-           "-I" + os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), "-I" + sysconfig.get_paths()["include"],
-           os.path.join(CSRC, "chela_host.cpp"), "-o", HOST_MODULE, "-L" + os.path.join(tdir, "lib"),
-           "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
-    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
-    if r.returncode != 0:
-        raise RuntimeError("host module failed:\n" + r.stdout)
-    return HOST_MODULE
+    if os.path.exists(HOST_MODULE):
+        os.remove(HOST_MODULE)
+    try:
+        import torch
+        tdir = os.path.dirname(os.path.abspath(torch.__file__))
+        cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-DNDEBUG", "-D__HIP_PLATFORM_AMD__=1",
+               "-DUSE_ROCM=1",
+               "-D_GLIBCXX_USE_CXX11_ABI=%d" % int(torch._C._GLIBCXX_USE_CXX11_ABI), "-I" + os.path.join(tdir, "include"),
+               "-I" + os.path.join(tdir, "include", "torch", "csrc", "api", "include"),
+               "-I" + os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "include"), "-I" + sysconfig.get_paths()["include"],
+               os.path.join(CSRC, "chela_host.cpp"), "-o", HOST_MODULE, "-L" + os.path.join(tdir, "lib"),
+               "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+        r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+        failed = r.stdout if r.returncode != 0 else None
+    except (ImportError, OSError) as e:
+        failed = str(e)
+    if failed is not None:
+        print("host module not built, decode steps take the slower host path:\n" + failed, file=sys.stderr)
+    return failed is None
 
 
 def build(verbose: bool = True) -> str:

@@ -609,3 +609,14 @@ def test_host_module_that_does_not_load_leaves_the_bindings_own_path(L, monkeypa
     with pytest.warns(RuntimeWarning, match="slower host path"):
         step = binding._load_step()
     assert step(0, None, None, None, None, None, 0.0, None, None) is None and binding._step_host is step
+
+
+def test_host_module_that_cannot_be_built_takes_nothing_else_with_it(monkeypatch, tmp_path, capfd):
+    from paper_2406_08128_amd import build
+    old = tmp_path / "_chela_host.so"
+    monkeypatch.setattr(build, "HOST_MODULE", str(old))
+    for cxx in ("false", str(tmp_path / "no-such-compiler")):
+        old.write_bytes(b"an earlier build's")
+        monkeypatch.setenv("CXX", cxx)
+        assert not build._build_host_module()
+        assert not old.exists() and "host module not built" in capfd.readouterr().err
