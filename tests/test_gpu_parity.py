@@ -944,6 +944,39 @@ def test_decode_step_host_path_and_the_bindings_own_lines_agree(dk, dv, gated):
     assert torch.equal(S1, S2)
 
 
+def test_decode_step_host_path_takes_plain_calls_and_declines_the_others():
+    # called by itself: it serves plain tensors, and leaves everything else, untouched, to the binding's own lines
+    from torch.utils._python_dispatch import TorchDispatchMode
+
+    class Mode(TorchDispatchMode):
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            return func(*args, **(kwargs or {}))
+
+    step = binding._load_step()
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    q, k, v, gate = ((torch.randn(2, 3, 64, generator=g, device="cuda") / 8).to(torch.bfloat16) for _ in range(4))
+    S0 = torch.randn(2, 3, 64, 64, generator=g, device="cuda")
+    for fn, gt in zip(binding._step_fn, (None, gate)):
+        S1, S2 = S0.clone(), S0.clone()
+        y = step(fn, q, k, v, gt, S1, 1e-5, None, None)
+        assert torch.is_tensor(y) and y.shape == v.shape
+        here = torch.cuda.current_stream()
+        want = binding.chela_linattn_step(q, k, v, S2, stream=here) if gt is None else \
+            binding.chela_linattn_step_gated(q, k, v, gt, S2, 1e-5, stream=here)
+        assert torch.equal(y, want) and torch.equal(S1, S2) and not torch.equal(S1, S0)
+        for args in ((q, k, v, gt, S2, 1e-5, None, here),                                          # a stream of the caller's
+                     (q.transpose(1, 2), k.transpose(1, 2), v, gt, S2, 1e-5, None, None),          # not contiguous
+                     (q, k, v, gt, S2, 1, None, None),                                             # eps no float
+                     (q, k, v, gt, S2[:, :, :-1], 1e-5, None, None), (q, k, v[:1], gt, S2, 1e-5, None, None),
+                     (q.float(), k, v, gt, S2, 1e-5, None, None), (q.cpu(), k, v, gt, S2, 1e-5, None, None),
+                     (q, k, v, gt, S2, 1e-5, v[:1], None)):
+            assert step(fn, *args) is None
+        with Mode():
+            assert step(fn, q, k, v, gt, S2, 1e-5, None, None) is None
+        assert torch.equal(S1, S2)
+
+
 def test_decode_step_host_path_lets_other_threads_run():
     # as the library's "function" one that says whether this thread holds the interpreter's lock: 0 is the library's OK
     import ctypes
@@ -986,9 +1019,8 @@ def test_shortlong_conv_bf16(shape):
 @pytest.mark.parametrize("shape", [(3, 2, 5000, 9, True), (1, 1, 4104, 3, True), (2, 3, 9000, 5, False),
                                    (4, 5, 16384, 32, True), (1, 3, 12344, 1, True), (5, 2, 8200, 17, True)])
 def test_shortlong_conv_bf16_matrix_core_sizes(shape):
-    # 4096 < L <= 16384 with L a multiple of 8: the kernel whose transforms run on the matrix cores (pairs of
-    # sequences of a channel as one complex signal; odd batch sizes leave one alone), every tap count class, with and
-    # without the short stage
+    # 4096 < L <= 16384 with L a multiple of 8: the kernel whose transforms run on the matrix cores, every tap count
+    # class, with and without the short stage
     B, d, L, m, short = shape
     _run_conv_case(B, d, L, m, "bf16", seed=L + 5, short=short)
 
@@ -1171,11 +1203,79 @@ def test_shortlong_conv_bwd_bf16(shape):
                                    (4, 1, 16376, 10, True), (6, 1, 8216, 9, True), (4, 2, 4128, 12, True),
                                    (7, 1, 12296, 1, True), (4, 1, 8200, 5, False), (2, 2, 16384, 9, True)])
 def test_shortlong_conv_bwd_bf16_matrix_core_sizes(shape):
-    # the gradient kernel whose transforms run on the matrix cores (4096 < L <= 16384, L a multiple of 8): odd batch
-    # sizes, several pairs per channel (dk adds up over them), every tap count class, with and without the short stage,
-    # lengths whose last row of 32 steps is partly filled
+    # the gradient kernel whose transforms run on the matrix cores (4096 < L <= 16384, L a multiple of 8): every tap count
+    # class, with and without the short stage, lengths whose last row of 1024 steps is partly filled; so few channels that
+    # every sequence has a workgroup, whose shares of dk and dw are added up behind it
     B, d, L, m, short = shape
     _run_conv_bwd_case(B, d, L, m, "bf16", seed=L + 13, short=short)
+
+
+def _mx_gradient_launch(B, d, L):
+    """(workgroups that share a channel, channels a workgroup walks) of the matrix-core gradient kernel, by its rule."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    groups = max(1, min(64, B, -(-512 // d))) if B > 1 else 1
+    room = max(groups * d * 8193 * 4, 256 * 32768) // (d * L)
+    best, G = None, 1
+    for g in range(1, max(1, min(64, B, room)) + 1):
+        t = -(-d * g // cus) * (-(-B // g) + (0.6 if g > 1 else 0.4))
+        if best is None or t < best:
+            best, G = t, g
+    return G, -(-d * G // cus)
+
+
+@pytest.mark.parametrize("shape,launch", [((16, 128, 8192, 9), (2, 1)), ((5, 96, 16384, 12), (5, 2)), ((6, 300, 4104, 17), (3, 4)),
+                                          ((6, 256, 8192, 0), (1, 1)), ((9, 200, 5000, 9), (1, 1)), ((5, 300, 9000, 4), (5, 6))])
+def test_matrix_core_conv_gradient_launch_shapes(shape, launch):
+    # several sequences per workgroup, with and without other workgroups at the same channel, and several channels one after the
+    # other: which slice of dk and dw is whose, and that sums, taps and scales start afresh.  With the short stage in the same
+    # kernel, with dV through memory, without.  The first and last channel, and those on either side of a workgroup's change.
+    B, d, L, m = shape
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert _mx_gradient_launch(B, d, L) == launch
+    x = make_conv_inputs(B, d, L, max(m, 1), L + 43, "bf16")
+    g = torch.Generator(device="cpu")
+    g.manual_seed(L + 3043)
+    dZ = torch.randn(B, d, L, generator=g, dtype=torch.float32).to(torch.bfloat16)
+    dev = _dev(x)
+    spec = binding.chela_longconv_spectrum(dev["k_long"])
+    dX, dw, dk = binding.chela_shortlong_conv_bwd(dev["X"], dev["w_short"] if m else None, spec, dZ.cuda())
+    torch.cuda.synchronize()
+    step = -(-d // launch[1])
+    ch = sorted({0, step - 1, step % d, d - 1})
+    rX, rw, rk = oracle_conv.short_long_conv_bwd(to_f64_numpy(x["X"][:, ch]), to_f64_numpy(x["w_short"][ch]) if m else None,
+                                                 to_f64_numpy(x["k_long"][ch]), to_f64_numpy(dZ[:, ch]))
+    for i, c in enumerate(ch):
+        _check("dX[c=%d]" % c, dX[:, c:c + 1], rX[:, i:i + 1], "bf16")
+        _check("dk[c=%d]" % c, dk[c], rk[i], "bf16")
+        if m:
+            _check("dw[c=%d]" % c, dw[c], rw[i], "bf16")
+
+
+@pytest.mark.parametrize("m", [0, 5])
+@pytest.mark.parametrize("order", [(1e4, 1e2, 0.0, 1.0, 1e-2, 1e-4), (1e-4, 1e-2, 1.0, 0.0, 1e2, 1e4)])
+def test_matrix_core_conv_gradient_of_sequences_of_unlike_loudness(order, m):
+    # one workgroup takes six sequences of a channel whose X and dZ differ by 1e4 either way, with an all-zero one among them, in
+    # falling and in rising order (the sums of dk change their unit, up and for the time of a quiet one): each one's dX to its own scale
+    B, d, L = 6, 256, 8192
+    x = make_conv_inputs(B, d, L, max(m, 1), 97, "bf16")
+    g = torch.Generator(device="cpu")
+    g.manual_seed(98)
+    f = torch.tensor(order)[:, None, None]
+    X = (x["X"].float() * f).to(torch.bfloat16)
+    dZ = (torch.randn(B, d, L, generator=g, dtype=torch.float32) * f).to(torch.bfloat16)
+    dev = _dev(x)
+    spec = binding.chela_longconv_spectrum(dev["k_long"])
+    dX, dw, dk = binding.chela_shortlong_conv_bwd(X.cuda(), dev["w_short"] if m else None, spec, dZ.cuda())
+    torch.cuda.synchronize()
+    for c in (0, 255):
+        rX, rw, rk = oracle_conv.short_long_conv_bwd(to_f64_numpy(X[:, c:c + 1]),
+                                                     to_f64_numpy(x["w_short"][c:c + 1]) if m else None,
+                                                     to_f64_numpy(x["k_long"][c:c + 1]), to_f64_numpy(dZ[:, c:c + 1]))
+        for b in range(B):
+            _check("dX[b=%d,c=%d]" % (b, c), dX[b, c], rX[b, 0], "bf16")
+        _check("dk[c=%d]" % c, dk[c], rk[0], "bf16")
+        if m:
+            _check("dw[c=%d]" % c, dw[c], rw[0], "bf16")
 
 
 def test_matrix_core_conv_gradient_two_channels_per_workgroup():
@@ -1421,12 +1521,13 @@ def test_long_conv_alone_bwd(L):
 
 
 @pytest.mark.parametrize("shape", [(40, 700, 100, 5, "f32"), (9, 1100, 1000, 5, "bf16"), (5, 512, 3000, 9, "bf16"),
-                                   (4, 200, 9000, 9, "bf16"), (3, 10300, 100, 5, "f32"), (4, 768, 16384, 9, "bf16")])
+                                   (5, 200, 9001, 9, "bf16"), (4, 200, 9000, 9, "bf16"),
+                                   (3, 10300, 100, 5, "f32"), (4, 768, 16384, 9, "bf16")])
 def test_conv_bwd_sequences_dealt_over_workgroups(shape):
     # widths and batch sizes at which the long-stage gradient kernel gives each channel several workgroups, each with
     # more than one sequence to take (15, 6, 3 and 3 workgroups at the four transform sizes), a width served by one
-    # workgroup per channel at a batch size above one and, last, the LM-shaped width as the benchmark launches it (one
-    # workgroup per channel, running sums kept in memory); channels are independent, so the oracle takes a sample
+    # workgroup per channel at a batch size above one and the matrix-core kernel, by its own rule: 200 channels of 9000
+    # steps and, last, the LM-shaped width as the benchmark launches it; channels are independent, so the oracle takes a sample
     B, d, L, m, dtype = shape
     print("\nconv bwd dealt B%d d%d L%d m%d %s" % (B, d, L, m, dtype), flush=True)
     x = make_conv_inputs(B, d, L, m, L + 13, dtype)
