@@ -470,9 +470,8 @@ struct MxSeq {
     }
 };
 
-__device__ __forceinline__ float mx_wave_max(const float (&v)[4][8])
+__device__ __forceinline__ float mx_wave_max(const float (&v)[4][8], float mx = 0.f)
 {
-    float mx = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
 #pragma unroll
@@ -594,8 +593,7 @@ __global__ __launch_bounds__(MX_T, 4) void convmx_fwd_kernel(const bf16* __restr
 // ---- the short stage's gradient of one sequence, dV = osc y still in registers (y as mx_last leaves it):
 //   du = dV silu'(u), u = K_s x worked out again;  dX[t] = sum_j w[j] du[t + j];  dw[j] += sum_t du[t] x[t - j], all fp32.
 // A lane's look-ahead comes from the lanes behind it in its row of 16, for the last of them by way of LDS: `edge` holds the first
-// HALO steps of each wave's 128 of each row n1, in the order of the steps, and zeros behind the last.  `rows`: room for
-// mx_short_conv_alone().
+// HALO steps of each wave's 128 of each row n1, in the order of the steps, and zeros behind the last.
 // As a kernel of its own this stage read dV (fp32, written by this one) and x again: 768 channels x 4 sequences of 16384 steps, both
 // stages' gradients, 9 taps: 329 -> 290 us (1 tap 323 -> 261, 12 taps 353 -> 315, 17, which that kernel stages, 675 -> 345; one card, in turn).
 // TAPS: the number of taps, so that the tap loops are as long as it takes (branches around single taps' products spilled 36 values).
@@ -609,40 +607,15 @@ __device__ __forceinline__ float mx_quad_sum(float v)
     v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xb1, 0xf, 0xf, true));     // lanes 1 0 3 2
     return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4e, 0xf, 0xf, true));   // 2 3 0 1
 }
-// u = K_s x without the matrix: the wave's part of the 16 rows and the history in front of each by way of LDS (`rows`, this wave's
-// own room), one tap after the other, in a loop, so that it takes no registers from the way that is taken otherwise.
-constexpr int mx_rows_halves(int halo) { return 16 * (128 + halo); }
-template <int TAPS>
-__device__ __forceinline__ void mx_short_conv_alone(const MxSeq<mx_halo(TAPS)>& xs, const float* __restrict__ wc,
-                                                    unsigned short* rows, int lane, float (&u)[4][8])
+__device__ __forceinline__ float mx_silu_grad(float u)
 {
-    constexpr int HALO = mx_halo(TAPS), PITCH = 128 + HALO;
-    const int c = lane & 15, q = lane >> 4;
-    unsigned short* own = rows + 4 * q * PITCH + HALO + 8 * c;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x4*>(own + i * PITCH) = xs.r[i];
-    if (q < HALO / 8) *reinterpret_cast<u32x4*>(rows + c * PITCH + HALO - 8 - 8 * q) = xs.front;
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) u[i][e] = 0.f;
-#pragma unroll 1
-    for (int j = 0; j < TAPS; ++j) {
-        const float wj = wc[j];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int e = 0; e < 8; ++e)
-                u[i][e] = fmaf(wj, __builtin_bit_cast(float, (unsigned)own[i * PITCH + e - j] << 16), u[i][e]);
-        }
-    }
+    const float sg = __builtin_amdgcn_rcpf(1.f + __expf(-u));
+    return sg * (1.f + u * (1.f - sg));
 }
 template <int TAPS>
 __device__ __forceinline__ void mx_short_bwd(const MxSeq<mx_halo(TAPS)>& xs, const unsigned short* taps, const float* __restrict__ wc,
-                                             float (&y)[4][8], float osc, float* edge, unsigned short* rows, float* tsum,
-                                             bf16* out, int L, int w, int tid)
+                                             float (&y)[4][8], float osc, float* edge, float* tsum, bf16* out, int L, int w,
+                                             int tid)
 {
     constexpr int HALO = mx_halo(TAPS), NH = HALO / 8;
     static_assert(NH == 1 || NH == 2, "");
@@ -651,19 +624,12 @@ __device__ __forceinline__ void mx_short_bwd(const MxSeq<mx_halo(TAPS)>& xs, con
     {
         float u[4][8];
         xs.short_conv(taps, lane, u);
-        // An infinity or a NaN in x meets the zeros of the taps' matrix and spoils its column: 32 steps, three quarters of them in other
-        // rows of 1024 (where it shows in the first result).  Such a wave works u out on the vector ALU, so that only the steps that x
-        // has a part in are lost.
-        const float any = (u[0][0] + u[1][0]) + (u[2][0] + u[3][0]);
-        if (__builtin_expect(__builtin_amdgcn_ballot_w64(any != any) != 0, 0))
-            mx_short_conv_alone<TAPS>(xs, wc, rows + w * mx_rows_halves(HALO), lane, u);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const bool in = t0 + 1024 * i < L;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                const float sg = __builtin_amdgcn_rcpf(1.f + __expf(-u[i][e]));
-                float du = (y[i][e] * osc) * sg * (1.f + u[i][e] * (1.f - sg));
+                float du = (y[i][e] * osc) * mx_silu_grad(u[i][e]);
                 asm("" : "+v"(du));                  // (a select, not a branch around each exponential)
                 y[i][e] = in ? du : 0.f;
             }
@@ -739,6 +705,47 @@ __device__ __forceinline__ void mx_short_bwd(const MxSeq<mx_halo(TAPS)>& xs, con
     }
 }
 
+// The same for a sequence with an infinity or a NaN in x.  Those meet the zeros of the taps' matrix, which spoils u in eight columns of
+// three other rows of 1024 steps; here, on the vector ALU, only the steps of dX that x has a part in are lost (dw is lost anyway).
+// It comes second and writes dX again, because a branch in front of it, or one in the middle to another way to u, cost all
+// sequences 2 % of the kernel with 9 taps and up to 7 % with more.  dv: 64 KB, cube: where mx_last() took y from.
+template <int TAPS>
+__device__ __forceinline__ void mx_short_bwd_alone(const bf16* x, const float* __restrict__ wc, const unsigned char* cube,
+                                                   const MxLds& tb, float osc, float* dv, bf16* out, int L, int w, int tid)
+{
+    const int lane = tid & 63, t0 = mx_first_step(w, lane);
+    __syncthreads();            // (all have read what lay in dv)
+    {
+        float y[4][8];
+        mx_last(cube, tb, w, lane, y);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float4* p = reinterpret_cast<float4*>(dv + t0 + 1024 * i);
+            p[0] = make_float4(y[i][0] * osc, y[i][1] * osc, y[i][2] * osc, y[i][3] * osc);
+            p[1] = make_float4(y[i][4] * osc, y[i][5] * osc, y[i][6] * osc, y[i][7] * osc);
+        }
+    }
+#pragma unroll 1
+    for (int k = 0; k < 32; ++k) {
+        const int t = t0 + 1024 * (k >> 3) + (k & 7);
+        float u = 0.f;
+#pragma unroll
+        for (int j = 0; j < TAPS; ++j)
+            if (t >= j && t < L) u = fmaf(wc[j], (float)x[t - j], u);
+        dv[t] = t < L ? dv[t] * mx_silu_grad(u) : 0.f;
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int k = 0; k < 32; ++k) {      // (the lane that has written these steps before)
+        const int t = t0 + 1024 * (k >> 3) + (k & 7);
+        float s = 0.f;
+#pragma unroll
+        for (int j = 0; j < TAPS; ++j)
+            if (t + j < L) s = fmaf(wc[j], dv[t + j], s);
+        if (t < L) out[t] = (bf16)s;
+    }
+}
+
 // The two long-stage gradients of the convolution (they share the spectrum of dZ); a workgroup walks the sequences of a
 // channel, every gridDim.y-th one where a channel is shared, and then those of the next channel blockIdx.x + gridDim.x, ...
 //   dv = corr(dZ, k_long): bins of dZ times the conjugate of the kernel's, back;
@@ -802,16 +809,20 @@ __global__ __launch_bounds__(MX_T, 2) void convmx_longbwd_kernel(const bf16* __r
         for (int i = 0; i < 16; ++i) hr[n][i] = hi[n][i] = 0.f;
     for (int c = blockIdx.x, b = b0; c < d;) {
         const long row = ((long)b * d + c) * L;
+        bool lost;
         float s_d, f, rest;     // f: from the sums' unit so far to that of v's scale; rest: from there to the present one
         {
             float v[4][8];
             xs.activated(taps, L, w, lane, v);
-            const float mv = mx_wave_max(v), md = zs.wave_max();
+            // (an infinity or a NaN in x leaves neither of the results of its column finite: mx_short_bwd_alone)
+            const float any = (v[0][0] + v[1][0]) + (v[2][0] + v[3][0]);
+            const float mv = mx_wave_max(v, SHORT && any - any != 0.f ? INFINITY : 0.f), md = zs.wave_max();
             if (lane == 0) { tb.red[w] = md; tb.red[MX_W + w] = mv; }
             __syncthreads();
             float bd = 0.f, bv = 0.f;
 #pragma unroll
             for (int i = 0; i < MX_W; ++i) { bd = fmaxf(bd, tb.red[i]); bv = fmaxf(bv, tb.red[MX_W + i]); }
+            lost = SHORT && __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, bv)) == 0x7f800000;
             s_d = mx_scale(bd);
             const float sv = mx_scale(bv), here = bd > 0.f && bv > 0.f ? 1.0f / (s_d * sv) : 0.f;
             f = here > unit ? unit / here : 1.f;
@@ -871,11 +882,11 @@ __global__ __launch_bounds__(MX_T, 2) void convmx_longbwd_kernel(const bf16* __r
         const int t0 = mx_first_step(w, mx_fresh(lane));
         if constexpr (SHORT) {
             // (cube[1] is free from the tiles' barrier on)
-            constexpr int edge_bytes = (16 * MX_W + 1) * HALO * 4;
-            static_assert(edge_bytes % 16 == 0 && edge_bytes + MX_W * mx_rows_halves(HALO) * 2 <= MX_CUBE, "");
-            mx_short_bwd<TAPS>(xc, taps, w_short + (long)cc * TAPS, y, osc, reinterpret_cast<float*>(cube[1]),
-                               reinterpret_cast<unsigned short*>(cube[1] + edge_bytes), tsum, out, L, w, tid);
+            mx_short_bwd<TAPS>(xc, taps, w_short + (long)cc * TAPS, y, osc, reinterpret_cast<float*>(cube[1]), tsum, out, L, w, tid);
             zs.load(dZ + next, L, w, lane);     // (not before: there are no registers for it, and v comes first)
+            if (__builtin_expect(lost, 0))
+                mx_short_bwd_alone<TAPS>(X + row, w_short + (long)cc * TAPS, cube[0], tb, osc, reinterpret_cast<float*>(cube[1]), out,
+                                         L, w, tid);
         } else {
 #pragma unroll
             for (int i = 0; i < 4; ++i) {

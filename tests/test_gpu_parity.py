@@ -1422,27 +1422,29 @@ def test_matrix_core_conv_gradient_keeps_a_quiet_sequences_share(bits, loud):
     assert rms <= noise / 64 + 1e-4 and mean <= noise / 512 + 1e-4 and whole <= noise + 8e-4
 
 
-@pytest.mark.parametrize("m", [1, 4, 9, 12, 17])
-def test_matrix_core_conv_gradient_of_infinities_in_x_reaches_their_neighbours_only(m):
+@pytest.mark.parametrize("shape", [(2, 3, 16384, 1), (2, 3, 4104, 4), (3, 256, 16384, 9), (2, 3, 4104, 9), (2, 3, 16384, 12),
+                                   (3, 256, 9216, 12), (3, 256, 16376, 17)])
+def test_matrix_core_conv_gradient_of_infinities_in_x_reaches_their_neighbours_only(shape):
     # dv is made of dZ alone, so an infinity or a NaN in x takes away the steps of dX that are less than m from it and no others: not
     # the rest of its 8, and not the other rows of 1024 steps that meet it in one product of matrices with zeros.  In the first and
-    # the last step, beside the ends of rows and of pieces of 8 and 128, and two at once; the other sequence is untouched.
-    B, d, L = 2, 3, 16384
+    # the last step, beside the ends of rows and of pieces of 8 and 128, and two at once; the other sequences and channels, before
+    # it and after it in the same workgroup, are untouched.
+    B, d, L, m = shape
     x = _dev(make_conv_inputs(B, d, L, m, 81 + m, "bf16"))
     dZ = torch.randn(B, d, L, generator=torch.Generator(device="cuda").manual_seed(82), device="cuda").to(torch.bfloat16)
     spec = binding.chela_longconv_spectrum(x["k_long"])
-    ref = binding.chela_shortlong_conv_bwd(x["X"], x["w_short"], spec, dZ)[0]
-    at = [[0, 5003], [1023, 8192], [3 * 1024 + 127, 16383]]
+    ref, _, rk = binding.chela_shortlong_conv_bwd(x["X"], x["w_short"], spec, dZ)
     X, lost = x["X"].clone(), torch.zeros(B, d, L, dtype=torch.bool, device="cuda")
-    for c, steps in enumerate(at):
+    for c, steps in enumerate([[0, L // 3], [1023, 2048], [3 * 1024 + 127, L - 1]]):
         for p, v in zip(steps, (float("inf"), float("nan"))):
             X[1, c, p] = v
             lost[1, c, max(0, p - m + 1):p + m] = True
-    got = binding.chela_shortlong_conv_bwd(X, x["w_short"], spec, dZ)[0]
+    got, _, dk = binding.chela_shortlong_conv_bwd(X, x["w_short"], spec, dZ)
     assert torch.equal(torch.isfinite(got), ~lost)
     a, b = got.double()[~lost], ref.double()[~lost]     # (u by another order of its fp32 sums: a tie of the last rounding at most)
     assert bool(((a - b).abs() <= 2.0 ** -7 * b.abs() + 1e-6 * b.abs().max()).all())
-    assert torch.equal(got[0], ref[0])
+    same = ~lost.any(2)
+    assert torch.equal(got[same], ref[same]) and torch.equal(dk[3:], rk[3:])
 
 
 def test_matrix_core_conv_of_more_sequences_than_one_launch_has_workgroups():
