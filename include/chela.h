@@ -262,7 +262,8 @@ int chela_gate_norm_bwd(const void *O, const void *G, const void *dY, void *dO, 
  * with the blocks of the kernel that reach from it into an output block are added up on the spectra, and one inverse
  * transform per output block follows (fp32 arithmetic for either I/O type; exact up to rounding like the single
  * transform, but its work grows with the square of the number of blocks, and `spectrum` holds one spectrum per
- * channel and block: 128 KB each).  L > 1048576 is rejected (CHELA_ERR_BAD_SHAPE).  The forward needs no scratch.  Pointers 16-byte aligned; Z must not overlap an input.  Everything else as for the calls above.
+ * channel and block: 128 KB each).  L > 1048576 is rejected (CHELA_ERR_BAD_SHAPE).  The forward needs no scratch.
+ * Pointers 16-byte aligned; Z must not overlap an input.  Everything else as for the calls above.
  * Environment (read per call, tuning aid): CHELA_CONV_MATRIX=0 keeps the vector-ALU kernels for every size. */
 size_t chela_longconv_spectrum_bytes(int d, int L);
 int chela_longconv_spectrum(const float *k_long, void *spectrum, int d, int L, void *stream);
@@ -282,7 +283,8 @@ int chela_shortlong_conv_fwd_f32(const void *X, const float *w_short, int m, con
  * Nothing is saved by the forward call: u and v are recomputed from X.  With w_short = NULL (no short stage) dX = dv,
  * v = X and d_w_short is ignored.  m <= 32 as in the forward.  Scratch (library workspace):
  * chela_shortlong_conv_bwd_workspace_bytes(), the most that any tap count takes (up to 16 taps and 4096 steps, and up to 17
- * taps on the matrix cores from 9216 steps on at the latest: without its B*d*L floats).  Sums over batch and time are taken in a fixed order (deterministic). */
+ * taps on the matrix cores from 9216 steps on at the latest: without its B*d*L floats).  Sums over batch and time are taken
+ * in a fixed order (deterministic). */
 int chela_shortlong_conv_bwd(const void *X, const float *w_short, int m, const void *spectrum, const void *dZ,
                              void *dX, float *d_w_short, float *d_k_long, int B, int d, int L, void *stream);
 int chela_shortlong_conv_bwd_f32(const void *X, const float *w_short, int m, const void *spectrum, const void *dZ,

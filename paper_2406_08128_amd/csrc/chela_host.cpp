@@ -43,7 +43,8 @@ PyObject* step(PyObject*, PyObject* const* a, Py_ssize_t n)
     if (!q.defined() || !q.is_cuda()) Py_RETURN_NONE;
     const c10::DeviceIndex dev = c10::hip::current_device();
     if (!plain(oq, at::kBFloat16, dev) || !plain(ok, at::kBFloat16, dev) || !plain(ov, at::kBFloat16, dev) ||
-        !plain(oS, at::kFloat, dev) || (og != Py_None && !plain(og, at::kBFloat16, dev)) || (oy != Py_None && !plain(oy, at::kBFloat16, dev)))
+        !plain(oS, at::kFloat, dev) || (og != Py_None && !plain(og, at::kBFloat16, dev)) ||
+        (oy != Py_None && !plain(oy, at::kBFloat16, dev)))
         Py_RETURN_NONE;
     const at::Tensor &k = THPVariable_Unpack(ok), &v = THPVariable_Unpack(ov), &S = THPVariable_Unpack(oS);
     if (q.dim() != 3 || k.sizes() != q.sizes() || v.dim() != 3) Py_RETURN_NONE;

@@ -671,7 +671,9 @@ __device__ __forceinline__ int fresh(int tid) { asm volatile("" : "+v"(tid)); re
 // k3 = 8 a + 4 h + b; scale[c] = 4 |k|_1 (both zero where 0.25 / |k|_1 is no finite number, below 7.4e-40); those kernels'
 // tables are written by one workgroup more than there are channels where that has a compute unit to itself, else by the first
 // channels' on the side (as one more it starts last: 768 channels 69 us, 63 without it and with the loads of the second transform in
-// front of the first one's stores; a single channel 16, with the tables on its side 17).
+// front of the first one's stores; a single channel 16, with the tables on its side 17).  Without the copy 768 channels take 42 us;
+// fp32 I/O, which does not read it, pays for it all the same, because this call does not know what the spectrum is for (4 % of a
+// fp32 training step of 2 x 768 x 16384).
 template <int M, bool MX>
 __global__ __launch_bounds__(conv_threads(M)) void longconv_spectrum_kernel(const float* __restrict__ k,
                                                                            float4* __restrict__ Kf,
@@ -1634,14 +1636,17 @@ hipError_t launch_longconv_spectrum(const float* k, void* Kf, int d, int L, hipS
     uint4* mx = (uint4*)((char*)Kf + conv_pairs_bytes(d, L));
     float* scale = (float*)(mx + (size_t)d * (MX_N / 4));
     MxTables* tables = mx_tables(mx, d);
+    const bool copy = M == 16384 && (L & 7) == 0;       // (rows of other lengths never meet the matrix-core kernels)
+    const dim3 grid(d + (copy && d < 256 ? 1 : 0));
 #define CHELA_SPECTRUM(M_, MX_)                                                                                         \
-    case M_: hipLaunchKernelGGL((longconv_spectrum_kernel<M_, MX_>), dim3(d + (MX_ && d < 256 ? 1 : 0)), dim3(conv_threads(M_)), 0, st, \
-                                k, out, mx, scale, tables, d, L); break;
+    hipLaunchKernelGGL((longconv_spectrum_kernel<M_, MX_>), grid, dim3(conv_threads(M_)), 0, st, k, out, mx, scale, tables, d, L)
     switch (M) {
-        CHELA_SPECTRUM(256, false) CHELA_SPECTRUM(1024, false) CHELA_SPECTRUM(4096, false)
-        case 16384:     // (rows that are no multiple of 8 steps never meet the matrix-core kernels)
-            if ((L & 7) != 0) { switch (M) { CHELA_SPECTRUM(16384, false) } }
-            else { switch (M) { CHELA_SPECTRUM(16384, true) } }
+        case 256: CHELA_SPECTRUM(256, false); break;
+        case 1024: CHELA_SPECTRUM(1024, false); break;
+        case 4096: CHELA_SPECTRUM(4096, false); break;
+        case 16384:
+            if (copy) CHELA_SPECTRUM(16384, true);
+            else CHELA_SPECTRUM(16384, false);
             break;
         default: return hipErrorInvalidValue;
     }

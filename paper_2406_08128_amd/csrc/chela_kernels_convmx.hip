@@ -24,9 +24,10 @@
 //   - Last pass: LDS transposing reads hand a lane its operand for the eight columns it loaded, the results leave as 16-byte
 //     stores.
 // So a sequence crosses LDS twice (64 KB of fp16, re and im planes), with three barriers.
-// Ranges: the input is scaled by a power of two to max|v| < 1 (no sum on the way forward exceeds 16384), the kernel's spectrum is stored divided
-// by 4 |k|_1 (no finished sum on the way back exceeds 4096, no partial one, by Parseval, 16400): half precision ends at 65504.
-// Both factors are put back on the way out.  Error against the fp64 definition on the workload's recipe: 4.2e-4 relative
+// Ranges: the input is scaled by a power of two to max|v| < 1 and the kernel's spectrum is stored divided by 4 |k|_1, so that the
+// result of a pass is at most 16384 on the way forward and N / 4 = 4096 on the way back (every pass there is a transform of the
+// result), but for what the 32-point matrix is stored times, MX_ENTRY per pass: 20380 and 6337; half precision ends at 65504.
+// All factors are put back on the way out.  Error against the fp64 definition on the workload's recipe: 4.2e-4 relative
 // before the rounding of the output to bf16 (1.7e-3 on its own).
 #include "chela_convmx.h"
 #include <cfloat>
@@ -51,6 +52,7 @@ constexpr int MX_W = MX_T / 64;              // waves; wave w owns columns 128 w
 constexpr int MX_NT = 16 / MX_W;             // tiles per wave
 constexpr int MX_PLANE = 16 * 2048;          // bytes of the re (or im) plane of a cube: [k1][n2][n3] fp16
 constexpr int MX_CUBE = 2 * MX_PLANE;
+static_assert(32768 * MX_ENTRY * MX_ENTRY < 65504, "the largest packed value: the sums of dk on their way back");
 
 // One word of two halves, round to nearest even.
 __device__ __forceinline__ unsigned mx_pack(float lo, float hi)
@@ -340,7 +342,9 @@ __device__ __forceinline__ void mx_write_taps(unsigned short* taps, const float*
         if (x >= WORDS + 8) break;
         const int part = pd / (NH + 1), j = 8 * (pd - part * (NH + 1)) + 4 * blk + b - e;
         const float w = x < WORDS && j >= 0 && j < m ? wc[j] : 0.f;
-        auto cut = [](float v) __attribute__((always_inline)) { return __builtin_bit_cast(float, __builtin_bit_cast(unsigned, v) & 0xffff0000u); };
+        auto cut = [](float v) __attribute__((always_inline)) {
+            return __builtin_bit_cast(float, __builtin_bit_cast(unsigned, v) & 0xffff0000u);
+        };
         const float hi = cut(w), mid = cut(w - hi), lo = w - hi - mid;
         taps[x] = (unsigned short)(__builtin_bit_cast(unsigned, part == 0 ? hi : part == 1 ? mid : lo) >> 16);
     }
@@ -367,7 +371,8 @@ struct MxSeq {
 #pragma unroll
         for (int i = 0; i < 4; ++i) r[i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, 2 * (t0 + 1024 * i), 0, 0));
         if (HALO > 0)
-            front = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, 2 * (1024 * (lane & 15) + 128 * w - 8 - 8 * (lane >> 4)), 0, 0));
+            front = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                                                  rs, 2 * (1024 * (lane & 15) + 128 * w - 8 - 8 * (lane >> 4)), 0, 0));
     }
     // the piece 8 D steps in front of row i's
     template <int D>
@@ -513,8 +518,8 @@ __device__ __forceinline__ void mx_product(const f32x16& xr, const f32x16& xi, c
         }
 }
 
-// One sequence per workgroup, id = c B + b, ids first .. end - 1.  HALO: steps of history the short kernel needs (m - 1 <= HALO; v = silu(K_s x));
-// 0: no short kernel, v = x.  L is a multiple of 8.
+// One sequence per workgroup, id = c B + b, ids first .. end - 1.  HALO: steps of history the short kernel needs (m - 1 <= HALO;
+// v = silu(K_s x)); 0: no short kernel, v = x.  L is a multiple of 8.
 // Two workgroups per compute unit (80 KB of LDS, 128 registers): one's activation runs beside the other's matrix products.
 // Workgroups that walk several sequences with the next
 // one's input on its way took 122 us (three each) and 128 us (six, all resident at once) where these take 117: of two that
@@ -595,7 +600,8 @@ __global__ __launch_bounds__(MX_T, 4) void convmx_fwd_kernel(const bf16* __restr
 // A lane's look-ahead comes from the lanes behind it in its row of 16, for the last of them by way of LDS: `edge` holds the first
 // HALO steps of each wave's 128 of each row n1, in the order of the steps, and zeros behind the last.
 // As a kernel of its own this stage read dV (fp32, written by this one) and x again: 768 channels x 4 sequences of 16384 steps, both
-// stages' gradients, 9 taps: 329 -> 290 us (1 tap 323 -> 261, 12 taps 353 -> 315, 17, which that kernel stages, 675 -> 345; one card, in turn).
+// stages' gradients, 9 taps: 329 -> 290 us (1 tap 323 -> 261, 12 taps 353 -> 315, 17, which that kernel stages, 675 -> 345; one
+// card, in turn).
 // TAPS: the number of taps, so that the tap loops are as long as it takes (branches around single taps' products spilled 36 values).
 // Below zero: dV leaves for a kernel of its own, and -TAPS is the history that v needs.
 constexpr int MX_SHORT_TAPS = 17;
@@ -607,10 +613,11 @@ __device__ __forceinline__ float mx_quad_sum(float v)
     v += __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xb1, 0xf, 0xf, true));     // lanes 1 0 3 2
     return v + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x4e, 0xf, 0xf, true));   // 2 3 0 1
 }
-__device__ __forceinline__ float mx_silu_grad(float u)
+// dv silu'(u)
+__device__ __forceinline__ float mx_du(float dv, float u)
 {
     const float sg = __builtin_amdgcn_rcpf(1.f + __expf(-u));
-    return sg * (1.f + u * (1.f - sg));
+    return dv * sg * (1.f + u * (1.f - sg));
 }
 template <int TAPS>
 __device__ __forceinline__ void mx_short_bwd(const MxSeq<mx_halo(TAPS)>& xs, const unsigned short* taps, const float* __restrict__ wc,
@@ -629,7 +636,7 @@ __device__ __forceinline__ void mx_short_bwd(const MxSeq<mx_halo(TAPS)>& xs, con
             const bool in = t0 + 1024 * i < L;
 #pragma unroll
             for (int e = 0; e < 8; ++e) {
-                float du = (y[i][e] * osc) * mx_silu_grad(u[i][e]);
+                float du = mx_du(y[i][e] * osc, u[i][e]);
                 asm("" : "+v"(du));                  // (a select, not a branch around each exponential)
                 y[i][e] = in ? du : 0.f;
             }
@@ -732,7 +739,7 @@ __device__ __forceinline__ void mx_short_bwd_alone(const bf16* x, const float* _
 #pragma unroll
         for (int j = 0; j < TAPS; ++j)
             if (t >= j && t < L) u = fmaf(wc[j], (float)x[t - j], u);
-        dv[t] = t < L ? dv[t] * mx_silu_grad(u) : 0.f;
+        dv[t] = t < L ? mx_du(dv[t], u) : 0.f;
     }
     __syncthreads();
 #pragma unroll 1
@@ -757,12 +764,12 @@ __device__ __forceinline__ void mx_short_bwd_alone(const bf16* x, const float* _
 // goes with v's scale down to 1/16 (half precision has the exponents), for what is left of it the sums change their unit for the
 // time: all of it in v's scale, a sequence entered with fewer and fewer bits (2^23 below the loudest its share of dk came out 0.3
 // times what it is, now right to the loud one's rounding).  Below 2^-64 the way back's half precision has nothing left of it.
-// The finished sums H are packed times
-// 32768 / (sqrt N |H|_2), which bounds every sum on the way back by 32768 (Cauchy-Schwarz) and leaves a typical bin at order one.
-// One workgroup per compute unit (both cubes: 144 KB of LDS; 256 registers, nothing spilled without the short stage, 5 .. 16 values
-// with it, most of them used at a channel's end only), issuing vector instructions 69 % of
-// the time with the short stage.  768 channels x 4 sequences of 16384 steps, 9 taps: 417 -> 240 us (the spectrum of dZ waited in memory for that of
-// v, and the sums went back once per pair of sequences).
+// The finished sums H are packed times 32768 / (sqrt N |H|_2), which bounds every sum on the way back by 32768 (Cauchy-Schwarz),
+// times MX_ENTRY^2 = 40760, and leaves a typical bin at order one.
+// One workgroup per compute unit (144 KB of LDS, with the taps and their sums up to 153; 256 registers, up to 3 values spilled
+// without the short stage, 7 .. 16 with it, most of them used at a channel's end only), issuing vector instructions 69 % of the
+// time with the short stage.  768 channels x 4 sequences of 16384 steps, 9 taps: 417 -> 240 us (the spectrum of dZ waited in memory
+// for that of v, and the sums went back once per pair of sequences).
 // mx_bwd_short(TAPS): the short stage's gradient too (dV is dX then, and the taps' sums go to dw): see mx_short_bwd.  Else dV is fp32
 // [B][d][L] for the short-stage kernel, or dX itself when there is no short stage (TAPS = 0, v = x).
 template <int TAPS>
@@ -1082,9 +1089,10 @@ hipError_t launch_convmx_longbwd(const void* X, const float* w_short, int m, con
                            tables, (const bf16*)dZ, (mx_dv_t<T_>*)dV, taps, tap_stride, sums, B, d, L);                 \
         break;
     switch (!w_short ? 0 : fused ? m : -mx_halo(m)) {
-        CHELA_MX_BWD(-8) CHELA_MX_BWD(-16) CHELA_MX_BWD(-32) CHELA_MX_BWD(0) CHELA_MX_BWD(1) CHELA_MX_BWD(2) CHELA_MX_BWD(3) CHELA_MX_BWD(4) CHELA_MX_BWD(5) CHELA_MX_BWD(6)
-        CHELA_MX_BWD(7) CHELA_MX_BWD(8) CHELA_MX_BWD(9) CHELA_MX_BWD(10) CHELA_MX_BWD(11) CHELA_MX_BWD(12) CHELA_MX_BWD(13)
-        CHELA_MX_BWD(14) CHELA_MX_BWD(15) CHELA_MX_BWD(16) CHELA_MX_BWD(17)
+        CHELA_MX_BWD(-32) CHELA_MX_BWD(-16) CHELA_MX_BWD(-8) CHELA_MX_BWD(0)
+        CHELA_MX_BWD(1) CHELA_MX_BWD(2) CHELA_MX_BWD(3) CHELA_MX_BWD(4) CHELA_MX_BWD(5) CHELA_MX_BWD(6)
+        CHELA_MX_BWD(7) CHELA_MX_BWD(8) CHELA_MX_BWD(9) CHELA_MX_BWD(10) CHELA_MX_BWD(11) CHELA_MX_BWD(12)
+        CHELA_MX_BWD(13) CHELA_MX_BWD(14) CHELA_MX_BWD(15) CHELA_MX_BWD(16) CHELA_MX_BWD(17)
     }
 #undef CHELA_MX_BWD
     if (G > 1) {
