@@ -760,10 +760,10 @@ __device__ __forceinline__ void mx_short_bwd_alone(const bf16* x, const float* _
 //   added up over the sequences in fp32 registers, back once per channel.  At the points used a negative lag is imaginary,
 //   as is the second half of a causal sum.
 // Both sequences' cubes lie in LDS side by side, so that a wave meets the same tile of both.  Sums of dk: all sequences'
-// shares are kept in units of the largest 1 / (scale of dZ_b x scale of v_b) so far (powers of two).  A quieter sequence's factor
-// goes with v's scale down to 1/16 (half precision has the exponents), for what is left of it the sums change their unit for the
-// time: all of it in v's scale, a sequence entered with fewer and fewer bits (2^23 below the loudest its share of dk came out 0.3
-// times what it is, now right to the loud one's rounding).  Below 2^-64 the way back's half precision has nothing left of it.
+// shares are kept in one unit, a power of two: the largest 1 / (scale of dZ_b x scale of v_b) so far, for a quieter sequence's time
+// 16 times that of its own.  (A factor of 1/16 goes with v's scale, half precision has the exponents.  All of it in v's scale, a
+// sequence entered with fewer and fewer bits: 2^23 below the loudest its share of dk came out 0.3 times what it is, now right to
+// the loud one's rounding.  Below 2^-60 the way back's half precision has nothing left of it.)
 // The finished sums H are packed times 32768 / (sqrt N |H|_2), which bounds every sum on the way back by 32768 (Cauchy-Schwarz),
 // times MX_ENTRY^2 = 40760, and leaves a typical bin at order one.
 // One workgroup per compute unit (144 KB of LDS, with the taps and their sums up to 153; 256 registers, up to 3 values spilled
@@ -809,7 +809,7 @@ __global__ __launch_bounds__(MX_T, 2) void convmx_longbwd_kernel(const bf16* __r
     const int b0 = blockIdx.y;          // (< B)
     zs.load(dZ + ((long)b0 * d + blockIdx.x) * L, L, w, lane);
     xs.load(X + ((long)b0 * d + blockIdx.x) * L, L, w, lane);
-    float hr[MX_NT][16], hi[MX_NT][16], unit = 0.f;       // the sums and their unit
+    float hr[MX_NT][16], hi[MX_NT][16], unit = 0.f, top = 0.f;       // the sums, their unit, the largest it was
 #pragma unroll
     for (int n = 0; n < MX_NT; ++n)
 #pragma unroll
@@ -817,7 +817,7 @@ __global__ __launch_bounds__(MX_T, 2) void convmx_longbwd_kernel(const bf16* __r
     for (int c = blockIdx.x, b = b0; c < d;) {
         const long row = ((long)b * d + c) * L;
         bool lost;
-        float s_d, f, rest;     // f: from the sums' unit so far to that of v's scale; rest: from there to the present one
+        float s_d, f;           // f: from the sums' unit so far to the present one
         {
             float v[4][8];
             xs.activated(taps, L, w, lane, v);
@@ -832,13 +832,12 @@ __global__ __launch_bounds__(MX_T, 2) void convmx_longbwd_kernel(const bf16* __r
             lost = SHORT && __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, bv)) == 0x7f800000;
             s_d = mx_scale(bd);
             const float sv = mx_scale(bv), here = bd > 0.f && bv > 0.f ? 1.0f / (s_d * sv) : 0.f;
-            f = here > unit ? unit / here : 1.f;
-            if (here > unit) unit = here;
-            const float rel = unit > 0.f ? here / unit : 0.f;
-            rest = rel < 0x1p-4f && rel >= 0x1p-64f ? rel * 0x1p4f : 1.f;
-            rest = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, rest)));
-            if (rest != 1.f) f = 1.f / rest;
-            mx_first<HALO == 0>(cube[1], tb, lc, v, sv * (rel / rest), w, lane);
+            const float next = here >= unit || here == 0.f ? fmaxf(here, unit) : fmaxf(fminf(unit, here * 0x1p4f), top * 0x1p-60f);
+            f = next > 0.f ? unit / next : 1.f;
+            const float s_v = next > 0.f ? sv * (here / next) : 0.f;
+            unit = next;
+            top = fmaxf(top, unit);
+            mx_first<HALO == 0>(cube[1], tb, lc, v, s_v, w, lane);
             __builtin_amdgcn_sched_barrier(0);
             zs.values(v);
             mx_first<true>(cube[0], tb, lc, v, s_d, w, lane);
@@ -865,12 +864,6 @@ __global__ __launch_bounds__(MX_T, 2) void convmx_longbwd_kernel(const bf16* __r
             mx_product<true>(zr, zi, kq, re, im);
             mx_tile_out(cube[0], tb, m32, lc.u, st[n], k1, lane, re, im);
             __builtin_amdgcn_sched_barrier(0);
-        }
-        if (rest != 1.f) {
-#pragma unroll
-            for (int n = 0; n < MX_NT; ++n)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) { hr[n][i] *= rest; hi[n][i] *= rest; }
         }
         __syncthreads();
         const float osc = kscale[c] / (s_d * ((float)MX_N * MX_GAIN4));
@@ -907,10 +900,15 @@ __global__ __launch_bounds__(MX_T, 2) void convmx_longbwd_kernel(const bf16* __r
         if (done) {         // ---- the sums' way back
             if (HALO > 0 && c < d) mx_write_taps<HALO>(taps, w_short + (long)c * m, m, tid);      // (barriers before and behind)
             float ss = 0.f;
+            const float back = top > 0.f ? unit / top : 0.f;
 #pragma unroll
             for (int n = 0; n < MX_NT; ++n)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) ss = fmaf(hr[n][i], hr[n][i], fmaf(hi[n][i], hi[n][i], ss));
+                for (int i = 0; i < 16; ++i) {
+                    hr[n][i] *= back;
+                    hi[n][i] *= back;
+                    ss = fmaf(hr[n][i], hr[n][i], fmaf(hi[n][i], hi[n][i], ss));
+                }
 #pragma unroll
             for (int o = 32; o >= 1; o >>= 1) ss += __shfl_xor(ss, o);
             if (lane == 0) tb.red[w] = ss;
@@ -945,8 +943,8 @@ __global__ __launch_bounds__(MX_T, 2) void convmx_longbwd_kernel(const bf16* __r
             }
             __syncthreads();
             mx_last(cube[1], tb, w, lane, y);
-            const float kosc = g > 0.f ? unit / (g * ((float)MX_N * MX_GAIN4 * MX_GAIN2)) : 0.f;
-            unit = 0.f;
+            const float kosc = g > 0.f ? top / (g * ((float)MX_N * MX_GAIN4 * MX_GAIN2)) : 0.f;
+            unit = top = 0.f;
             float* o = dk + ((long)b0 * d + cc) * L;         // (a shared channel: its slices are added up by mx_dk_kernel)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
