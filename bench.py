@@ -689,7 +689,7 @@ def main():
         whole["stream_floor"] = stream_floor
     target = None
     if headline:
-        target = {"north_star": ">= 50 % of peak bf16 MFMA at B4 H12 N16384 d64, as shown by rocprof",
+        target = {"aim": ">= 50 % of peak bf16 MFMA at B4 H12 N16384 d64, as shown by rocprof",
                   "met": False,
                   "mfma_frac_whole_step_full_tile_model": whole["mfma_frac"],
                   "mfma_frac_dominant_kernel_counted": (mfma_counted or {}).get("frac_of_peak"),

@@ -15,7 +15,7 @@ HOST_MODULE = os.path.join(HERE, "_chela_host.so")
 SOURCES = ["chela_api.hip", "chela_kernels_f32.hip", "chela_kernels_bf16.hip", "chela_kernels_conv.hip",
            "chela_kernels_convmx.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-# packed-fp32 VALU forms are switched off for every device compile (they have given wrong results on this pool)
+# packed-fp32 VALU forms are switched off for every device compile (they have given wrong results on this chip now and then)
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          # keep MFMA accumulators in architectural VGPRs: every accumulator here is read back by the vector ALU

@@ -1,7 +1,7 @@
 """The comparator of the GPU parity tests: one output tensor of the HIP path against the fp64 oracle's.
 
 Three measures, all of ||got - ref||_2 / ||ref||_2 kind, on the same pair of arrays:
-  whole   over the whole tensor                           (the bar the benchmark spec states: 1e-5 fp32 I/O, 2e-2 bf16 I/O)
+  whole   over the whole tensor                           (the stated bar: 1e-5 fp32 I/O, 2e-2 bf16 I/O)
   group   per leading index -- per (b,h) pair of a [B,H,N,d] tensor, per batch entry of a [B,d,L] one --, worst one
   row     per row of the last axis (one token's features): the row's error over the larger of the row's own norm and
           the root-mean-square row norm of the BLOCK rows of the reference around it, worst one
@@ -25,13 +25,13 @@ spread of about 1/sqrt(2 d) ~ 9 % from row to row (measured: whole 2.3e-3 .. 2.5
 the whole tensor and for every group.  The worst single row among a million is another matter: a row's error is a
 weighted sum of d element errors, and where the weights are uneven -- Y = Norm(O) * G with a silu gate, whose few
 large entries may sit on small entries of Norm(O) -- the tail reaches 5x the typical row (measured: 1.1e-2 .. 1.3e-2
-on the gated outputs, 3e-3 .. 7e-3 on the plain ones).  ROW_BAR is therefore the bar the benchmark spec states for the whole
+on the gated outputs, 3e-3 .. 7e-3 on the plain ones).  ROW_BAR is therefore the bar stated for the whole
 tensor, 2e-2, now demanded of every single row; a row that is wrong rather than rounded reads 0.1 .. 1.  fp32 I/O:
 sums of up to 1e5 terms in fp32 give ~1e-7 .. 5e-7 (worst row 2e-6); every measure is held to the 1e-5 bar.
 """
 import numpy as np
 
-BAR = {"f32": 1e-5, "bf16": 2e-2}          # north_star, whole tensor
+BAR = {"f32": 1e-5, "bf16": 2e-2}          # as stated, whole tensor
 EXPECT = {"f32": 2e-6, "bf16": 6e-3}       # what rounding explains (whole tensor and every group), with margin
 ROW_BAR = {"f32": 1e-5, "bf16": 2e-2}      # worst single row: the stated bar, row by row
 BLOCK = 64                                 # rows whose root-mean-square norm is the scale of a short row
