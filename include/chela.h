@@ -114,7 +114,8 @@ int chela_linattn_bwd(const void *Q, const void *K, const void *V, const void *d
 int chela_linattn_fwd_noalloc(const void *Q, const void *K, const void *V, void *O,
                               int B, int H, int N, int dk, int dv, int chunk, void *stream);
 
-/* The same two maps with fp32 tensors and fp32 arithmetic throughout. */
+/* The same two maps with fp32 tensors and fp32 accuracy: operands keep all 24 bits (as three bf16 parts each on the matrix
+ * cores), sums are fp32.  An infinity counts as a NaN; results below 2^-100 lose bits as their smallest parts run out of range. */
 int chela_linattn_fwd_f32(const void *Q, const void *K, const void *V, void *O,
                           int B, int H, int N, int dk, int dv, int chunk, void *stream);
 int chela_linattn_bwd_f32(const void *Q, const void *K, const void *V, const void *dO,
@@ -309,7 +310,8 @@ int chela_linattn_step_gated(const void *q, const void *k, const void *v, const 
  * does not grow with N once the GPU is full -- the fixed-memory property claimed in
  * Sec. 1.  bf16 backward: in addition no segment is longer than 8192 tokens (see
  * chela_linattn_bwd), i.e. at least two states per 8192 tokens of a sequence: 0.4 % of
- * the bytes of the tensors themselves.  fp32 backward: long sequences are cut finer the longer they are (48 pairs, 64 x 64:
+ * the bytes of the tensors themselves.  fp32 forward with 64 x 64 states: a smaller caller-owned buffer is accepted down to
+ * what the general split takes.  fp32 backward: long sequences are cut finer the longer they are (48 pairs, 64 x 64:
  * 7 segments at 16384 tokens, 32 at 65536, again 32 at a million); a caller-owned buffer smaller than this size is
  * accepted down to what one state per segment of the forward's split takes, with fewer segments; the same goes for the
  * scratch earlier calls left where nothing can be allocated (under stream capture, or when memory is short).  fp32 calls with 256

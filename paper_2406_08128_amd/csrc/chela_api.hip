@@ -26,7 +26,7 @@ constexpr long kMaxBwdWalkTokens = 8192;   // longest stretch the bf16 backward 
 static long sweep_slots(int dk, int dv, int chunk, int dtype, bool is_bwd)
 {
     const bool narrow = (dk == 64 && dv == 64), wide = (dk == 128 && dv == 128);
-    if (dtype != CHELA_DTYPE_BF16) return narrow ? 512 : 256;     // fp32 sweep: 66 KB of LDS at the 64-wide shape, > 80 KB else
+    if (dtype != CHELA_DTYPE_BF16) return narrow ? 512 : 256;     // fp32 sweep: 72 KB of LDS at the 64-wide shape, > 80 KB else
     int per_cu;
     if (is_bwd) per_cu = (chunk == 64 && !wide) ? 2 : 1;      // (one width of 128: the two states share an LDS tile)
     // (the 64-wide forward sweep holds four per unit, but is planned for two: filling the other two with shorter
@@ -138,22 +138,59 @@ Plan make_plan(long BH, int N, int dk, int dv, int chunk, int dtype, bool is_bwd
     return p;
 }
 
+// The fp32 forward with 64 x 64 states, of fewer than 256 (b,h) pairs: bound by instruction issue, not by memory, so a workgroup
+// alone on its compute unit takes three quarters of the time per chunk step that one of two takes (4.5 and 5.7 .. 7 us), and the
+// pre-pass's steps, a third as long, count too.  A workgroup adds up half its sequence's totals, or the scan is a launch more.
+// Segments of less than three chunks only where one round holds all chunks.  us by chunks per segment, the general
+// model's choice first: 24 x 3001 tokens: six 43.3, five (taken) 36.7, four 41.6, three 37.8; 64 x 777: five 31.5, four 29.1,
+// three (taken) 24.9, two 26.9; 4 x 16384: (five) 48.8, four (taken) 47.2, three 53.7; 64 x 4096: eight (both) 84.3, five 96.8,
+// four 93.4, sixteen 97.9; 16 x 1025: (three) 20.5, two (taken) 16.6, one 17.7.  The wider states: nothing to gain.
+static long f32_fwd_segments(long BH, long n_chunks, size_t state_elems)
+{
+    long best = 1;
+    double best_cost = 1e300;
+    const long least = BH * n_chunks <= 512 ? 1 : 3;
+    for (long n = 1; n <= (n_chunks + least - 1) / least && n <= 4096; ++n) {
+        const long cps = (n_chunks + n - 1) / n;
+        if ((n_chunks + cps - 1) / cps != n) continue;                  // same split as a smaller n
+        const long wgs = BH * n, rounds = (wgs + 511) / 512;
+        double cost = (wgs <= 256 ? 0.76 : (double)rounds * (1.0 + 0.09 * (double)(rounds - 1))) * ((double)cps + 0.5);
+        const bool folded = (size_t)n * state_elems * sizeof(float) <= kMaxFoldedStateBytes;
+        if (n > 1) cost += 0.35 * (double)cps + (double)wgs * (folded ? 0.0004 * (double)n : 0.0033) + (folded ? 2.0 : 4.0);
+        if (cost < best_cost) { best_cost = cost; best = n; }
+    }
+    return best;
+}
+
+// ws_limit: scratch there is.  Where the split takes more, it is the one every fp32 call was given before, or in fewer segments.
+Plan make_f32_fwd_plan(long BH, int N, int dk, int dv, int chunk, size_t ws_limit)
+{
+    const Plan own = make_plan(BH, N, dk, dv, chunk, CHELA_DTYPE_F32, false, false);
+    const long chunks = ((long)(N > 0 ? N : 0) + chunk - 1) / chunk;
+    if (dk != 64 || dv != 64 || BH <= 0 || BH >= 256 || chunks <= 4 || env_int("CHELA_SEG_TOKENS", 0) > 0) return own;
+    Plan p = own;
+    const long n = f32_fwd_segments(BH, chunks, p.state_elems);
+    const long cps = (chunks + n - 1) / n;
+    p.seg_len = (int)(cps * chunk);
+    p.n_seg = (int)((chunks + cps - 1) / cps);
+    p.ws_bytes = p.n_seg > 1 ? (size_t)BH * p.n_seg * p.state_elems * sizeof(float) : 0;
+    return p.ws_bytes > ws_limit ? own : p;
+}
+
 // The fp32 backward is one launch of three forward-shaped sweeps: three workgroups per segment share the GPU.  From 256
-// (b,h) pairs on it is not split, like every other fp32 call, and takes no scratch.  Below that, up to one round of single
-// chunks it is split like a forward over three times as many sequences; beyond, by a model of its own,
-// because the matrix instructions bound it and not the memory: a round costs its chunk steps whether the one before was
-// full or not, several rounds are no slower than one, and the pre-pass and the states are small change.  Measured, us,
-// by segments per sequence: 96 x 4096 tokens, 64 x 128: one 1282, two 1132, four 961, eight 906; 64 x 64: 600, 564, 470,
-// (five) 436; 112 x 1000, 128 x 64: 314, 291, 295.  The model is not always right: 40 x 4096, 128 x 128: 754 with the two
-// it takes, 653 with four; 16 x 8192, 64 x 128: 349 with its five, 299 with sixteen.  256 pairs and more, one segment
-// against the best of two to sixteen: 256 x 2048, 64 x 64: 491, 531; 257 x 2048: 600, 604; 340 x 2048: 623, 717; 300 x
-// 1000: 304, 343; 384 x 1024, 128 x 128: 1352, 1425; 512 x 700, 64 x 128: 676, 785; only where the last round is
-// nearly empty is one behind: 260 x 4096, 64 x 128: 2587, 2439.
+// (b,h) pairs on it is not split, like every other fp32 call, and takes no scratch.  Below that it is split by a model of its
+// own, because the instructions bound it and not the memory: a round costs its chunk steps whether the one before was
+// full or not, several rounds are no slower than one, and the pre-pass and the states are small change.  Segments of less
+// than four chunks only where two rounds hold all chunks, single ones where one does.  Measured, us, 64 x 64, by chunks
+// per segment: 24 x 3001 tokens: four 79, five 77, six 81, eight (taken) 74, twelve 92; 64 x 4096: eight (taken) 226, six 240,
+// sixteen 222; 16 x 1025: one 25.2, two (taken) 24.5, three 28.0, five 34.0; 4 x 4096: one 38.8, two (taken) 30.2, three 33.7,
+// five 37.1; 16 x 400: one (taken) 17.8, two 17.8, three 23.0, the whole sequence 29.1.
 static long f32_bwd_segments(long wgs_per_seg, long n_chunks, long slots, size_t state_elems)
 {
     long best = 1;
     double best_cost = 1e300;
-    for (long n = 1; n <= n_chunks / 4 && n <= 4096; ++n) {
+    const long least = wgs_per_seg * n_chunks <= slots ? 1 : wgs_per_seg * n_chunks <= 2 * slots ? 2 : 4;
+    for (long n = 1; n <= (n_chunks + least - 1) / least && n <= 4096; ++n) {
         const long cps = (n_chunks + n - 1) / n;
         if ((n_chunks + cps - 1) / cps != n) continue;                  // same split as a smaller n
         const long wgs = wgs_per_seg * n;
@@ -171,7 +208,7 @@ Plan make_f32_bwd_plan(long BH, int N, int dk, int dv, int chunk, size_t ws_limi
 {
     Plan p = make_plan(3 * BH, N, dk, dv, chunk, CHELA_DTYPE_F32, false, false);
     const long chunks = ((long)(N > 0 ? N : 0) + chunk - 1) / chunk, slots = sweep_slots(dk, dv, chunk, CHELA_DTYPE_F32, true);
-    if (BH > 0 && BH < 256 && chunks > 4 && 3 * BH * chunks > slots && env_int("CHELA_SEG_TOKENS", 0) <= 0) {
+    if (BH > 0 && BH < 256 && chunks > 4 && env_int("CHELA_SEG_TOKENS", 0) <= 0) {
         const long n = f32_bwd_segments(3 * BH, chunks, slots, p.state_elems);
         const long cps = std::max((chunks + n - 1) / n, (chunks + 32767) / 32768);
         p.seg_len = (int)(cps * chunk);
@@ -189,7 +226,6 @@ Plan make_f32_bwd_plan(long BH, int N, int dk, int dv, int chunk, size_t ws_limi
         p.n_seg = (int)((n_chunks + cps - 1) / cps);
     }
     p.ws_bytes = std::max(least, p.n_seg > 1 ? (size_t)p.n_seg * 2 * state : 0);
-    p.by_chunk = std::min(p.seg_len, N) > std::min(own.seg_len, N);
     return p;
 }
 
@@ -480,13 +516,22 @@ static int fwd_common(const void* Q, const void* K, const void* V, void* O, cons
         return CHELA_OK;
     }
     if (dtype == CHELA_DTYPE_F32) chunk = f32_effective_chunk(dk, dv, chunk);
-    Plan plan = make_plan(BH, N, dk, dv, chunk, dtype, false, S_in != nullptr);
+    Plan plan = dtype == CHELA_DTYPE_F32 ? make_f32_fwd_plan(BH, N, dk, dv, chunk, ~(size_t)0)
+                                         : make_plan(BH, N, dk, dv, chunk, dtype, false, S_in != nullptr);
+    if (dtype == CHELA_DTYPE_F32) {
+        const size_t limit = static_ws ? kStaticScratchBytes : workspace_limit(plan.ws_bytes, (hipStream_t)stream);
+        if (limit < plan.ws_bytes) plan = make_f32_fwd_plan(BH, N, dk, dv, chunk, limit);
+    }
     float* ws = nullptr;
     if (static_ws) {
         if (plan.ws_bytes > kStaticScratchBytes) return CHELA_ERR_WORKSPACE;
         rc = plan.ws_bytes ? static_scratch(&ws) : CHELA_OK;
     } else {
         rc = get_workspace(plan.ws_bytes, stream, &ws);
+        if (rc == CHELA_ERR_WORKSPACE && dtype == CHELA_DTYPE_F32) {       // (refused: the smaller need, as under capture)
+            plan = make_f32_fwd_plan(BH, N, dk, dv, chunk, 0);
+            rc = get_workspace(plan.ws_bytes, stream, &ws);
+        }
     }
     if (rc != CHELA_OK) return rc;
     hipError_t e = dtype == CHELA_DTYPE_BF16
@@ -1105,7 +1150,7 @@ size_t chela_linattn_workspace_bytes(int B, int H, int N, int dk, int dv, int ch
     if (!(chunk == 16 || chunk == 32 || chunk == 64)) return 0;
     const int c = f32_effective_chunk(dk, dv, chunk);
     return is_bwd ? make_f32_bwd_plan((long)B * H, N, dk, dv, c, ~(size_t)0).ws_bytes
-                  : make_plan((long)B * H, N, dk, dv, c, dtype, false, false).ws_bytes;
+                  : make_f32_fwd_plan((long)B * H, N, dk, dv, c, ~(size_t)0).ws_bytes;
 }
 
 size_t chela_linattn_train_workspace_bytes(int B, int H, int N, int dk, int dv, int chunk, int is_bwd)

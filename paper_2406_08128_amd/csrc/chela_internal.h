@@ -17,7 +17,6 @@ struct Plan {
     size_t ws_bytes;     // scratch bytes for the whole call
     int ckpt_every;      // bf16 backward with a single segment: the sweep's first pass leaves the running state every
                          // ckpt_every chunks and its walk back picks those copies up again (0: none needed)
-    bool by_chunk;       // fp32 backward: running sums take a chunk's products as one number (longer segments)
 };
 
 // The sweeps add the segment totals up themselves (no scan kernel) while one (b,h) pair's totals stay below this:
@@ -60,8 +59,9 @@ hipError_t launch_stream_probe(const void* const* in, int n_in, void* const* out
 // Matrix-core rate probe: blocks * 4 waves, each issuing iters * 16 bf16 32x32x16 matrix instructions; out: blocks * 256 floats.
 hipError_t launch_mfma_probe(float* out, int blocks, int iters, hipStream_t st);
 
-// fp32 path.  The backward's three maps share one plan (make_f32_bwd_plan) and, with more than one segment, two arrays of
+// fp32 path.  The forward has a plan of its own for 64 x 64 states.  The backward's three maps share one plan (make_f32_bwd_plan) and, with more than one segment, two arrays of
 // states.  ws_limit: scratch there is.
+Plan make_f32_fwd_plan(long BH, int N, int dk, int dv, int chunk, size_t ws_limit);
 Plan make_f32_bwd_plan(long BH, int N, int dk, int dv, int chunk, size_t ws_limit);
 hipError_t launch_f32_fwd(const float* Q, const float* K, const float* V, float* O, long BH, int N, int dk, int dv,
                           const Plan& plan, float* ws, hipStream_t st);

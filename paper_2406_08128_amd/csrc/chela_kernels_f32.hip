@@ -1,16 +1,23 @@
-// fp32 kernels: causal linear attention with fp32 I/O and fp32 arithmetic on the fp32 matrix instruction
-// v_mfma_f32_32x32x2_f32 (products and sums in IEEE fp32; the path exists for accuracy, the bf16 path for speed).
-// Also the state scan and the copy probe shared by both paths.
+// fp32 kernels: causal linear attention with fp32 I/O and fp32 accuracy on the bf16 matrix instruction
+// v_mfma_f32_32x32x16_bf16 (the path exists for accuracy, the bf16 path for speed).  Also the state scan and the copy probe
+// shared by both paths.
 //
 // Structure (Sec. 4.1): a (b,h) sequence is cut into segments; within a segment one workgroup walks the
 // chunks in order with the d_k x d_v state S in accumulator registers.  Per chunk: masked left product
 // P = (Q K^T) o M, O = P V + Q S (both parts summed in the same accumulators), then S += K^T V.  Segment start
-// states come from a pre-pass (segment totals of K^T V) and a scan over segments.
+// states come from a pre-pass (segment totals of K^T V), added up by the sweeps or by a scan.
 //
-// Operand plumbing is simpler than in the bf16 kernels: with k = 2 per instruction a lane supplies ONE float of A
-// (row lane%32, k = lane/32) and ONE of B, so every operand is a 4-byte LDS read -- along a row of a row-major tile
-// (stride = leading dimension, kept odd so the 32 rows fall into 32 different banks) or along its columns
-// (contiguous).  Nothing is ever transposed.
+// Arithmetic.  Every operand (tiles, scores, published state) is three bf16 parts that together hold all of its 24 bits, and a
+// product is the six products of parts that matter, each exact, summed in fp32: 6 x 32 cycles of the matrix pipe for 16 steps
+// of a 32 x 32 tile where the fp32 instruction takes 512.  Errors against 64 bits, 24 x 3001 tokens, 64 x 64: O 4.95e-7 with the
+// fp32 instruction, now 1.6e-7, gradients 2.6e-7, now 1.6e-7; the same or better over 7 shapes x 4 state sizes but for dK
+// of all-positive inputs with 128-wide values (3.0e-7, now 4.8e-7: the matrix unit cuts products off below the largest
+// of an instruction's).  What bounds it: instruction issue -- splitting a value takes 5.5 vector instructions -- and, with
+// the GPU full, power (1.5 .. 2.1 GHz).  Measured, us, fp32 instruction -> three parts: 24 x 3001, 64 x 64: forward 52.9 -> 39,
+// backward 94.9 -> 74; 64 x 4096, 64 x 64: 110 -> 84, 286 -> 224; 24 x 3001, 128 x 128: 127 -> 98, 343 -> 247; 16 x 400, 64 x 64:
+// 39 -> 11.6, 41 -> 18.4 (of these two 25 are the plan's).
+// Two halves in fp16 would be half the instructions, but 22 bits, and a token 2^30 louder than its chunk would cost the others
+// theirs.
 #include "chela_internal.h"
 
 namespace chela {
@@ -231,11 +238,6 @@ hipError_t launch_mfma_probe(float* out, int blocks, int iters, hipStream_t st)
     return hipGetLastError();
 }
 
-__device__ __forceinline__ f32x16 mfma_f32(float a, float b, f32x16 c)
-{
-    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
-}
-
 __device__ __forceinline__ f32x16 zero16f()
 {
     f32x16 z;
@@ -244,100 +246,212 @@ __device__ __forceinline__ f32x16 zero16f()
     return z;
 }
 
-// Logical position p (0 = first token the causal sum sees) to physical row of the [N, d] matrix.
-__device__ __forceinline__ int phys_row(int p, int N, bool rev) { return rev ? (N - 1 - p) : p; }
+// ------------------------------------------------------------------------------------------------ three bf16 parts
+typedef __bf16 bf16;
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
+typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
+typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
+typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
+typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 
-// acc[32x32] += A B over K2 values of k (a multiple of 16).
-//   A element (m, k): a_base[(m) * a_rs + (k) * a_ks]   B element (k, n): b_base[(k) * b_ks + (n) * b_ns]
-// with m = lane%32 (+ tile offset folded into the base), n = lane%32, k = k0 + lane/32, k0 stepping by 2.
-// The operands of the next eight instructions are read while the current eight run: a wave has one or two others
-// on its SIMD to hide behind, and an LDS round trip costs as much as two of the instructions.
-template <int K2>
-__device__ __forceinline__ f32x16 gemm_tile(f32x16 acc, const float* a_base, int a_rs, int a_ks, const float* b_base,
-                                            int b_ks, int b_ns, int lane)
+// Two fp32 values as the sums of three bf16 ones, packed in pairs (first value in the low half): the leading part is cut
+// off, not rounded, so that it stays finite for every finite value; its remainder is exact, 16 bits wide, and leaves 8 bits
+// or fewer behind the second part.  All 24 bits are there: h + m + l is the value.
+struct Pair3 { unsigned h, m, l; };
+__device__ __forceinline__ unsigned cvt_pk_bf16(float lo, float hi)      // round to nearest even
 {
-    constexpr int G = 8, NG = K2 / (2 * G);
-    const int r = lane & 31, h = lane >> 5;
-    const float* pa = a_base + r * a_rs + h * a_ks;
-    const float* pb = b_base + h * b_ks + r * b_ns;
-    float a[2][G], b[2][G];
-#pragma unroll
-    for (int u = 0; u < G; ++u) { a[0][u] = pa[2 * u * a_ks]; b[0][u] = pb[2 * u * b_ks]; }
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-        if (g + 1 < NG) {
-#pragma unroll
-            for (int u = 0; u < G; ++u) {
-                a[(g + 1) & 1][u] = pa[2 * (G * (g + 1) + u) * a_ks];
-                b[(g + 1) & 1][u] = pb[2 * (G * (g + 1) + u) * b_ks];
-            }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int u = 0; u < G; ++u) acc = mfma_f32(a[g & 1][u], b[g & 1][u], acc);
-        __builtin_amdgcn_sched_barrier(0);
-    }
+    // (written out: the compiler would convert the low half a second time where its value is wanted as a float again)
+    unsigned d;
+    asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(d) : "v"(lo), "v"(hi));
+    return d;
+}
+__device__ __forceinline__ Pair3 split_pair(float x0, float x1)
+{
+    const unsigned u0 = __builtin_bit_cast(unsigned, x0), u1 = __builtin_bit_cast(unsigned, x1);
+    const float r0 = x0 - __builtin_bit_cast(float, u0 & 0xffff0000u), r1 = x1 - __builtin_bit_cast(float, u1 & 0xffff0000u);
+    const unsigned m = cvt_pk_bf16(r0, r1);
+    const unsigned l = cvt_pk_bf16(r0 - __builtin_bit_cast(float, m << 16), r1 - __builtin_bit_cast(float, m & 0xffff0000u));
+    return {__builtin_amdgcn_perm(u1, u0, 0x07060302u), m, l};
+}
+
+// An operand of the 32x32x16 instruction in its three parts.
+struct Op3 { bf16x8 h, m, l; };
+
+// acc += A B with the six products of parts that reach 2^-24 of the whole, the small ones first.  What is left out
+// (m l, l m, l l) is below 2^-25 of a product and of either sign; a product of two parts is exact in fp32.
+__device__ __forceinline__ f32x16 mul3(const Op3& a, const Op3& b, f32x16 acc)
+{
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.l, b.h, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.l, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.m, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.h, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.m, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.h, acc, 0, 0, 0);
     return acc;
 }
 
-// C rows of a row-major [N][D] fp32 matrix, starting at logical position c0 -> LDS tile with leading dimension D+1,
-// in two steps so that the loads of the next chunk can be in flight while the current one is worked on: fetch() brings
-// a thread's share of the tile into registers, stash() puts it into LDS.  Rows at or beyond p_end read as zero.
+// The same with the leading products in a sum of their own: the others, below 2^-8 of them, then round 2^-8 finer.
+__device__ __forceinline__ void mul3(const Op3& a, const Op3& b, f32x16& hi, f32x16& lo)
+{
+    lo = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.l, b.h, lo, 0, 0, 0);
+    lo = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.l, lo, 0, 0, 0);
+    lo = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.m, lo, 0, 0, 0);
+    hi = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.h, hi, 0, 0, 0);
+    lo = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.h, lo, 0, 0, 0);
+    lo = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.m, lo, 0, 0, 0);
+}
+
+// Eight consecutive values as an operand.
+__device__ __forceinline__ Op3 split8(const float (&x)[8])
+{
+    u32x4 h, m, l;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const Pair3 p = split_pair(x[2 * q], x[2 * q + 1]);
+        h[q] = p.h; m[q] = p.m; l[q] = p.l;
+    }
+    return {__builtin_bit_cast(bf16x8, h), __builtin_bit_cast(bf16x8, m), __builtin_bit_cast(bf16x8, l)};
+}
+
+// A tile in LDS: three planes of ROWS x D bf16, one per part.  The 16-byte pieces of a row are permuted by an XOR with bits of the
+// row number, chosen so that neither a read along rows (16 lanes, 16 rows, one piece) nor a transposing read (4 rows, four
+// pieces side by side) meets a bank twice: neighbouring 128-byte rows already lie in different halves of the banks.
+template <int D>
+__device__ __forceinline__ int piece_xor(int row)
+{
+    if (D == 64) return ((row >> 3) & 1) | ((row >> 1) & 2) | ((row << 1) & 4);
+    return ((row >> 2) & 3) | ((row << 2) & 12);
+}
+template <int D>
+__device__ __forceinline__ int tile_at(int row, int piece) { return row * D + ((piece ^ piece_xor<D>(row)) << 3); }
+
+// Lane (r = lane%32, h = lane/32) gets X[row0 + r][k0 + 8h .. +7]; row0 is a multiple of 32, k0 of 16.
+template <int ROWS, int D>
+__device__ __forceinline__ Op3 ld3_nat(const bf16* X, int row0, int k0, int lane)
+{
+    const bf16* p = X + row0 * D + tile_at<D>(lane & 31, (k0 >> 3) + (lane >> 5));
+    return {*reinterpret_cast<const bf16x8*>(p), *reinterpret_cast<const bf16x8*>(p + ROWS * D),
+            *reinterpret_cast<const bf16x8*>(p + 2 * ROWS * D)};
+}
+
+__device__ __forceinline__ bf16x8 tr_pair(const bf16* lo, const bf16* hi)
+{
+    const bf16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)lo);
+    const bf16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_bf16x4*)hi);
+    return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
+// The operand whose contraction index is the ROW: slot e of lane (r, h) is T[k0 + 8h + e][m0 + r], or with PERM, the order
+// in which an accumulator tile re-used as an operand holds its rows, T[k0 + 8 (e/4) + 4h + e%4][m0 + r].  Within 16 lanes the
+// transposing read hands lane p the column p of a 4 x 16 block whose rows the lanes address as p / 4, 8-byte pieces as p % 4.
+template <int ROWS, int D, bool PERM>
+__device__ __forceinline__ Op3 ld3_tr(const bf16* T, int k0, int m0, int lane)
+{
+    const int p = lane & 15, g = (lane >> 4) & 1, h = lane >> 5;
+    const int row = (PERM ? 4 : 8) * h + (p >> 2), row2 = row + (PERM ? 8 : 4);
+    const int piece = (m0 >> 3) + 2 * g + ((p >> 1) & 1);
+    const bf16* a = T + k0 * D + tile_at<D>(row, piece) + 4 * (p & 1);
+    const bf16* b = T + k0 * D + tile_at<D>(row2, piece) + 4 * (p & 1);
+    return {tr_pair(a, b), tr_pair(a + ROWS * D, b + ROWS * D), tr_pair(a + 2 * ROWS * D, b + 2 * ROWS * D)};
+}
+
+// The rows of one chunk: logical positions c0 .. c0 + C of a row-major [N][D] matrix (in reverse where rev), as a buffer that ends
+// with the chunk's last row below p_end.  What lies beyond reads as zero and is not written, without a branch, so that
+// the compiler can count what is outstanding (s_waitcnt vmcnt(n)) across loads and stores; a chunk at or behind p_end is empty.
+template <int C, int D>
+struct ChunkRows {
+    __amdgpu_buffer_rsrc_t rs;
+    int last;                    // -1: ascending; else the row number of logical row 0
+    __device__ __forceinline__ ChunkRows(const float* base, int c0, int p_end, int N, bool rev)
+    {
+        const int rows = __builtin_amdgcn_readfirstlane(max(0, min(C, p_end - c0)));
+        rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(base) + (size_t)(rev ? N - c0 - rows : c0) * D, 0, rows * D * 4, 0x00020000);
+        last = rev ? rows - 1 : -1;
+    }
+    // byte offset of a row: negative, that is beyond every end, for rows that a reversed chunk does not have
+    __device__ __forceinline__ int at(int row) const { return (last >= 0 ? last - row : row) * (D * 4); }
+    __device__ __forceinline__ float4 load4(int off) const
+    {
+        return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
+    }
+};
+
+// One chunk's tile -> three planes in LDS, in two steps so that the loads of the next chunk can be in flight while the current one
+// is worked on: fetch() brings a thread's share of the tile into registers, stash() splits it and puts it into LDS.
 template <int C, int D>
 struct TileRegsF32 {
     static constexpr int V4 = D / 4, NV = C * V4 / 256;
     float4 v[NV];
-    __device__ __forceinline__ void fetch(const float* base, int c0, int p_end, int N, bool rev, int tid)
+    __device__ __forceinline__ void fetch(const ChunkRows<C, D>& rows, unsigned tid)
     {
 #pragma unroll
-        for (int n = 0; n < NV; ++n) {
-            const int x = tid + 256 * n, row = x / V4, c4 = x % V4, p = c0 + row;
-            v[n] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (p < p_end) v[n] = *reinterpret_cast<const float4*>(base + (size_t)phys_row(p, N, rev) * D + c4 * 4);
-        }
+        for (int n = 0; n < NV; ++n) v[n] = rows.load4(rows.at(tid / V4 + 256 / V4 * n) + (int)(tid % V4) * 16);
     }
-    __device__ __forceinline__ void stash(float* lds, int tid) const
+    __device__ __forceinline__ void stash(bf16* lds, unsigned tid) const
     {
 #pragma unroll
         for (int n = 0; n < NV; ++n) {
-            const int x = tid + 256 * n, row = x / V4, c4 = x % V4;
-            float* d = lds + row * (D + 1) + c4 * 4;
-            d[0] = v[n].x; d[1] = v[n].y; d[2] = v[n].z; d[3] = v[n].w;
+            const int row = tid / V4 + 256 / V4 * n, c4 = tid % V4;
+            const Pair3 p0 = split_pair(v[n].x, v[n].y), p1 = split_pair(v[n].z, v[n].w);
+            bf16* d = lds + tile_at<D>(row, c4 >> 1) + 4 * (c4 & 1);
+            *reinterpret_cast<u32x2*>(d) = u32x2{p0.h, p1.h};
+            *reinterpret_cast<u32x2*>(d + C * D) = u32x2{p0.m, p1.m};
+            *reinterpret_cast<u32x2*>(d + 2 * C * D) = u32x2{p0.l, p1.l};
         }
     }
 };
 
-// S + K^T V over K2 tokens, one 32 x 32 tile.  BY_CHUNK: the tokens are summed up by themselves and added to the running
-// sum in one go; as operands of one chain of matrix instructions each is rounded to the last place of the running sum.
-// The backward does so where its segments are longer than sequences split on their own would have (Plan::by_chunk), which
-// would lose accuracy: 4 x 16384 tokens, 128 x 128, 4.7e-7 from 64 bits in their own segments, 7.3e-7 in the longer ones,
-// 3.0e-7 in these by chunks; 24 x 3001, 64 x 64, 4.6, 5.2, 2.6e-7.  It costs up to 3 % (128 x 128; 64 x 64 below 1 %).
-template <int K2, bool BY_CHUNK>
-__device__ __forceinline__ f32x16 state_tile(f32x16 acc, const float* k, int ldk, const float* v, int ldv, int lane)
+// acc[n] + K^T V over K2 tokens for NT 32 x 32 tiles (i0(n), j0(n)).  The tokens are summed up by themselves and added to the running
+// sum in one go: as operands of one chain of matrix instructions each would be rounded to the last place of the running
+// sum.  The operands of the next step are read while the current one's six instructions run.
+template <int K2, int DK, int DV, int NT, class I0, class J0>
+__device__ __forceinline__ void state_tiles(f32x16* acc, const bf16* k, const bf16* v, int lane, I0 i0, J0 j0)
 {
-    // A[m=i][k=s] = K[s][i]: contiguous in i;  B[k=s][n=j] = V[s][j]: contiguous in j
-    if (!BY_CHUNK) return gemm_tile<K2>(acc, k, 1, ldk, v, ldv, 1, lane);
-    const f32x16 t = gemm_tile<K2>(zero16f(), k, 1, ldk, v, ldv, 1, lane);
+    constexpr int STEPS = K2 / 16 * NT;
+    f32x16 t[NT];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) acc[e] += t[e];
-    return acc;
+    for (int n = 0; n < NT; ++n) t[n] = zero16f();
+    Op3 a[2], b[2];
+    a[0] = ld3_tr<K2, DK, false>(k, 0, i0(0), lane);
+    b[0] = ld3_tr<K2, DV, false>(v, 0, j0(0), lane);
+    int cur = 0;                 // (which b is in use: a step whose tile shares the step before's columns of V reads none)
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) {
+        int nxt = cur;
+        if (s + 1 < STEPS) {
+            const int s0 = (s + 1) / NT * 16, n = (s + 1) % NT;
+            a[(s + 1) & 1] = ld3_tr<K2, DK, false>(k, s0, i0(n), lane);
+            if (n == 0 || j0(n) != j0(n - 1)) {
+                nxt = cur ^ 1;
+                b[nxt] = ld3_tr<K2, DV, false>(v, s0, j0(n), lane);
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        t[s % NT] = mul3(a[s & 1], b[cur], t[s % NT]);
+        __builtin_amdgcn_sched_barrier(0);
+        cur = nxt;
+    }
+#pragma unroll
+    for (int n = 0; n < NT; ++n)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[n][e] += t[n][e];
 }
 
 // ------------------------------------------------------------------------------------------------ segment totals
 // out[bh][seg][i*DV + j] = sum over the segment's tokens of K[t][i] * V[t][j].  The last segment's total is never
 // used by an exclusive prefix, so its workgroups leave at once.  Wave w owns output tiles w, w+4, ...
 constexpr int kF32SegRows = 64;                 // tokens staged per step
-constexpr int f32_seg_lds(int dk, int dv) { return kF32SegRows * (dk + dv + 2); }     // floats
+constexpr int f32_seg_lds(int dk, int dv) { return kF32SegRows * (dk + dv) * 3; }     // bf16 elements
 
-template <int DK, int DV, bool BY_CHUNK>
+template <int DK, int DV>
 __device__ __forceinline__ void f32_seg_state_body(const float* __restrict__ K, const float* __restrict__ V,
                                                    float* __restrict__ out, int N, int seg_len, int n_seg, bool rev,
-                                                   float* lds)
+                                                   bf16* lds)
 {
     constexpr int R = kF32SegRows;
-    constexpr int LDK = DK + 1, LDV = DV + 1;
-    float* sK = lds;
-    float* sV = lds + R * LDK;
+    bf16* sK = lds;
+    bf16* sV = lds + 3 * R * DK;
     const int seg = blockIdx.y;
     const long bh = blockIdx.x;
     if (seg == n_seg - 1) return;
@@ -354,7 +468,11 @@ __device__ __forceinline__ void f32_seg_state_body(const float* __restrict__ K, 
     TileRegsF32<R, DK> rk[2];
     TileRegsF32<R, DV> rv[2];
 #pragma unroll
-    for (int u = 0; u < 2; ++u) { rk[u].fetch(Kb, p0 + u * R, p1, N, rev, tid); rv[u].fetch(Vb, p0 + u * R, p1, N, rev, tid); }
+    for (int u = 0; u < 2; ++u) {
+        rk[u].fetch(ChunkRows<R, DK>(Kb, p0 + u * R, p1, N, rev), tid);
+        rv[u].fetch(ChunkRows<R, DV>(Vb, p0 + u * R, p1, N, rev), tid);
+        __builtin_amdgcn_sched_barrier(0);
+    }
     for (int cc = p0; cc < p1; cc += 2 * R) {
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
@@ -364,15 +482,10 @@ __device__ __forceinline__ void f32_seg_state_body(const float* __restrict__ K, 
             rk[u].stash(sK, tid);
             rv[u].stash(sV, tid);
             __syncthreads();
-            if (c0 + 2 * R < p1) {
-                rk[u].fetch(Kb, c0 + 2 * R, p1, N, rev, tid);
-                rv[u].fetch(Vb, c0 + 2 * R, p1, N, rev, tid);
-            }
-#pragma unroll
-            for (int n = 0; n < NT; ++n) {
-                const int id = w + 4 * n, ib = id / JB, jb = id % JB;
-                acc[n] = state_tile<R, BY_CHUNK>(acc[n], sK + ib * 32, LDK, sV + jb * 32, LDV, lane);
-            }
+            rk[u].fetch(ChunkRows<R, DK>(Kb, c0 + 2 * R, p1, N, rev), tid);
+            rv[u].fetch(ChunkRows<R, DV>(Vb, c0 + 2 * R, p1, N, rev), tid);
+            state_tiles<R, DK, DV, NT>(acc, sK, sV, lane, [&](int n) { return ((w + 4 * n) / JB) * 32; },
+                                       [&](int n) { return ((w + 4 * n) % JB) * 32; });
         }
     }
     float* o = out + ((size_t)bh * n_seg + seg) * DK * DV;
@@ -391,180 +504,251 @@ template <int DK, int DV>
 __global__ __launch_bounds__(256) void f32_seg_state_kernel(const float* __restrict__ K, const float* __restrict__ V,
                                                            float* __restrict__ out, int N, int seg_len, int n_seg)
 {
-    __shared__ float lds[f32_seg_lds(DK, DV)];
-    f32_seg_state_body<DK, DV, false>(K, V, out, N, seg_len, n_seg, false, lds);
+    __shared__ __attribute__((aligned(16))) bf16 lds[f32_seg_lds(DK, DV)];
+    f32_seg_state_body<DK, DV>(K, V, out, N, seg_len, n_seg, false, lds);
 }
 
 // The backward's two sets of totals, V^T K in reading order and Q^T dO from the end, side by side on grid.z.
-template <int DK, int DV, bool BY_CHUNK>
+template <int DK, int DV>
 __global__ __launch_bounds__(256) void f32_bwd_seg_state_kernel(const float* __restrict__ Q, const float* __restrict__ K,
                                                                const float* __restrict__ V, const float* __restrict__ dO,
                                                                float* __restrict__ out, size_t array_stride, int N,
                                                                int seg_len, int n_seg)
 {
-    __shared__ float lds[f32_seg_lds(DK, DV)];
-    if (blockIdx.z == 0) f32_seg_state_body<DV, DK, BY_CHUNK>(V, K, out, N, seg_len, n_seg, false, lds);
-    else f32_seg_state_body<DK, DV, BY_CHUNK>(Q, dO, out + array_stride, N, seg_len, n_seg, true, lds);
+    __shared__ __attribute__((aligned(16))) bf16 lds[f32_seg_lds(DK, DV)];
+    if (blockIdx.z == 0) f32_seg_state_body<DV, DK>(V, K, out, N, seg_len, n_seg, false, lds);
+    else f32_seg_state_body<DK, DV>(Q, dO, out + array_stride, N, seg_len, n_seg, true, lds);
 }
 
 // ------------------------------------------------------------------------------------------------ main sweep
-// One workgroup (4 waves) per (segment, bh).  Wave w owns output rows [32*tb, +32) with tb = w % WT and NJ column
-// tiles, and the state tiles w, w+4, ...  LDS: Q, K [C][DK+1]; V [C][DV+1]; S [DK][DV+1]; P [C][C+1] in K's place.
+// One workgroup (4 waves) per (segment, bh).  Wave w owns output rows [32*tb, +32) with tb = w % TB and NJ column
+// tiles.  LDS: K [C][DK], V [C][DV] and S^T [DV][DK], each as three planes.  Queries come straight from memory in
+// operand order; the scores of a row block stay in the registers of the waves that need them.
 constexpr int f32_sweep_chunk(int dk, int dv) { return dk == 128 && dv == 128 ? 32 : 64; }   // what fits 160 KB of LDS
-// The score tile P takes over K's place once K has done its two jobs (scores, state update): five tiles would be
-// 83 KB at the 64-wide shape and leave a compute unit to a single workgroup, four leave room for two.
-constexpr int f32_sweep_kp(int c, int dk) { return c * (dk + 1) > c * (c + 1) ? c * (dk + 1) : c * (c + 1); }
-constexpr int f32_sweep_lds(int dk, int dv)                                                  // floats
+constexpr int f32_sweep_lds(int dk, int dv)                                                  // bf16 elements
 {
     const int c = f32_sweep_chunk(dk, dv);
-    return c * (dk + 1) + f32_sweep_kp(c, dk) + c * (dv + 1) + dk * (dv + 1);
+    return 3 * (c * dk + c * dv + dk * dv);
 }
 
-template <int C, int DK, int DV, bool BY_CHUNK>
+template <int C, int DK, int DV>
 __device__ __forceinline__ void f32_sweep_body(const float* __restrict__ Q, const float* __restrict__ K,
                                                const float* __restrict__ V, float* __restrict__ O,
                                                const float* __restrict__ S0, int N, int seg_len, int n_seg, bool rev,
-                                               bool s0_transposed, float* lds)
+                                               bool s0_transposed, bool folded, bf16* lds)
 {
-    constexpr int LDK = DK + 1, LDV = DV + 1, LDP = C + 1;
-    constexpr int TB = C / 32, JB = DV / 32, IB = DK / 32;
-    constexpr int WT = TB < 4 ? TB : 4, WJ = 4 / WT, NJ = JB / WJ;
-    constexpr int NS = IB * JB / 4;
-    static_assert(JB % WJ == 0, "unsupported tile shape");
-    float* sQ = lds;
-    float* sKP = sQ + C * LDK;
-    float* sV = sKP + f32_sweep_kp(C, DK);
-    float* sS = sV + C * LDV;
-    float* sK = sKP;
-    float* sP = sKP;
+    constexpr int TB = C / 32, JB = DV / 32, IB = DK / 32, KK = DK / 16;
+    constexpr int WJ = 4 / TB, NJ = JB / WJ;
+    // State tiles: column tiles jg*NJ .. of S belong to the TB waves that share jg, in equal parts.
+    constexpr int NS = IB * NJ / TB;
+    static_assert(JB % WJ == 0 && (TB == 1 || TB == 2), "unsupported tile shape");
+    bf16* sK = lds;
+    bf16* sV = sK + 3 * C * DK;
+    bf16* sS = sV + 3 * C * DV;
     const int seg = blockIdx.y;
     const long bh = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int tb = w % WT, jg = w / WT;
+    const int tb = w % TB, jg = w / TB;
     const int r = lane & 31, h = lane >> 5;
     const float* Qb = Q + (size_t)bh * N * DK;
     const float* Kb = K + (size_t)bh * N * DK;
     const float* Vb = V + (size_t)bh * N * DV;
     float* Ob = O + (size_t)bh * N * DV;
     const int p0 = seg * seg_len, p1 = min(N, p0 + seg_len);
+    const int q_own = tb * NS;
 
-    // start state of this segment (exclusive prefix over earlier segments, zero for the first), as accumulator tiles;
-    // s0_transposed: the array holds the states as [DV][DK] (left there by a call with keys and values exchanged)
-    f32x16 accS[NS];
-    const float* s0 = (S0 != nullptr && seg > 0) ? S0 + ((size_t)bh * n_seg + seg) * DK * DV : nullptr;
     // (the first chunk's tiles are asked for first: they are what the loop waits for)
-    TileRegsF32<C, DK> rq, rk;
+    TileRegsF32<C, DK> rk;
     TileRegsF32<C, DV> rv;
-    rq.fetch(Qb, p0, p1, N, rev, tid);
-    rk.fetch(Kb, p0, p1, N, rev, tid);
-    rv.fetch(Vb, p0, p1, N, rev, tid);
+    float4 rq[DK / 8];
+    auto fetch_q = [&](int c0) __attribute__((always_inline)) {      // row r of the wave's 32, features 16 kk + 8 h ..
+        const ChunkRows<C, DK> rows(Qb, c0, p1, N, rev);
+        const int off = rows.at(tb * 32 + r) + 32 * h;
+#pragma unroll
+        for (int x = 0; x < DK / 8; ++x) rq[x] = rows.load4(off + (x >> 1) * 64 + (x & 1) * 16);
+    };
+    rk.fetch(ChunkRows<C, DK>(Kb, p0, p1, N, rev), tid);
+    rv.fetch(ChunkRows<C, DV>(Vb, p0, p1, N, rev), tid);
+    __builtin_amdgcn_sched_barrier(0);
+    fetch_q(p0);
+    // start state of this segment, as accumulator tiles: the sum of the n_s0 states that lie one behind the other at s0, in their order
+    // (the one a scan has left, or the totals of the segments in front; none for the first segment).  s0_transposed: they
+    // are stored as [DV][DK] (left there by a call with keys and values exchanged).  Four states' loads are in flight.
+    f32x16 accS[NS];
+    const int n_s0 = S0 == nullptr || seg == 0 ? 0 : folded ? seg : 1;
+    const float* s0 = S0 + ((size_t)bh * n_seg + (folded ? 0 : seg)) * DK * DV;
 #pragma unroll
     for (int n = 0; n < NS; ++n) {
-        const int id = w + 4 * n, ib = id / JB, jb = id % JB;
-        // (one uniform branch around each unrolled set of loads, so that the 16 loads of a tile are issued together)
-        if (s0 == nullptr) {
-            accS[n] = zero16f();
-        } else if (s0_transposed) {
+        const int q = q_own + n, ib = q % IB, jb = jg * NJ + q / IB;
+        accS[n] = zero16f();
+        constexpr int U = 4;
+        for (int k = 0; k < n_s0; k += U) {
+            f32x16 x[U];
 #pragma unroll
-            for (int a = 0; a < 4; ++a)
+            for (int u = 0; u < U; ++u) {
+                const float* p = s0 + (size_t)min(k + u, n_s0 - 1) * (DK * DV);
+                // (one uniform branch around each unrolled set of loads, so that the loads of a tile are issued together)
+                if (s0_transposed) {
 #pragma unroll
-                for (int b = 0; b < 4; ++b)
-                    accS[n][4 * a + b] = s0[(jb * 32 + r) * DK + ib * 32 + 8 * a + 4 * h + b];
-        } else {
-#pragma unroll
-            for (int a = 0; a < 4; ++a)
-#pragma unroll
-                for (int b = 0; b < 4; ++b)
-                    accS[n][4 * a + b] = s0[(ib * 32 + 8 * a + 4 * h + b) * DV + jb * 32 + r];
-        }
-    }
-    for (int c0 = p0; c0 < p1; c0 += C) {
-        __syncthreads();   // previous chunk fully consumed
-        rq.stash(sQ, tid);
-        rk.stash(sK, tid);
-        rv.stash(sV, tid);
-        // publish the state before this chunk, [i][j]
-#pragma unroll
-        for (int n = 0; n < NS; ++n) {
-            const int id = w + 4 * n, ib = id / JB, jb = id % JB;
-#pragma unroll
-            for (int a = 0; a < 4; ++a)
-#pragma unroll
-                for (int b = 0; b < 4; ++b) sS[(ib * 32 + 8 * a + 4 * h + b) * LDV + jb * 32 + r] = accS[n][4 * a + b];
-        }
-        __syncthreads();
-        if (c0 + C < p1) {     // the next chunk, in flight during the arithmetic
-            rq.fetch(Qb, c0 + C, p1, N, rev, tid);
-            rk.fetch(Kb, c0 + C, p1, N, rev, tid);
-            rv.fetch(Vb, c0 + C, p1, N, rev, tid);
-        }
-        // masked scores P[t][s] = q_t . k_s for s <= t, held in registers for now.  The WJ waves that share a row block
-        // share its score tiles out among themselves (tile sb goes to wave sb % WJ); all of them read the whole row
-        // block back from LDS below.
-        constexpr int NPT = (TB + WJ - 1) / WJ;
-        f32x16 pt[NPT];
-#pragma unroll
-        for (int sb = 0; sb < TB; ++sb) {
-            // A[m=t][k=i] = Q[t][i] (row walk), B[k=i][n=s] = K[s][i] (row walk)
-            if (sb <= tb && sb % WJ == jg)
-                pt[sb / WJ] = gemm_tile<DK>(zero16f(), sQ + tb * 32 * LDK, LDK, 1, sK + sb * 32 * LDK, 1, LDK, lane);
-        }
-        // state update S += K^T V (not needed after the segment's last chunk); the published copy in sS is the state
-        // BEFORE this chunk, which is what the output below needs
-        if (c0 + C < p1) {
-#pragma unroll
-            for (int n = 0; n < NS; ++n) {
-                const int id = w + 4 * n, ib = id / JB, jb = id % JB;
-                accS[n] = state_tile<C, BY_CHUNK>(accS[n], sK + ib * 32, LDK, sV + jb * 32, LDV, lane);
-            }
-        }
-        __syncthreads();   // K has been read for the last time: its place now takes the scores
-#pragma unroll
-        for (int sb = 0; sb < TB; ++sb) {
-            if (sb <= tb && sb % WJ == jg) {
-#pragma unroll
-                for (int a = 0; a < 4; ++a)
-#pragma unroll
-                    for (int b = 0; b < 4; ++b) {
-                        const int row = 8 * a + 4 * h + b;   // query within the block; r = key within the block
-                        const float v = (sb == tb && r > row) ? 0.f : pt[sb / WJ][4 * a + b];
-                        sP[(tb * 32 + row) * LDP + sb * 32 + r] = v;
+                    for (int a = 0; a < 4; ++a) {
+                        const float4 v = *reinterpret_cast<const float4*>(p + (jb * 32 + r) * DK + ib * 32 + 8 * a + 4 * h);
+                        x[u][4 * a] = v.x; x[u][4 * a + 1] = v.y; x[u][4 * a + 2] = v.z; x[u][4 * a + 3] = v.w;
                     }
+                } else {
+#pragma unroll
+                    for (int a = 0; a < 4; ++a)
+#pragma unroll
+                        for (int b = 0; b < 4; ++b) x[u][4 * a + b] = p[(ib * 32 + 8 * a + 4 * h + b) * DV + jb * 32 + r];
+                }
             }
-        }
-        __syncthreads();   // the row blocks are complete; now every wave may read them
-        f32x16 accO[NJ];
 #pragma unroll
-        for (int n = 0; n < NJ; ++n) {
-            const int j0 = (jg * NJ + n) * 32;
-            // inter-chunk part Q S_prev: A = Q rows (row walk), B[k=i][n=j] = S[i][j] (contiguous)
-            accO[n] = gemm_tile<DK>(zero16f(), sQ + tb * 32 * LDK, LDK, 1, sS + j0, LDV, 1, lane);
-            // intra-chunk part P V over the key blocks sb <= tb: A = P rows (row walk), B[k=s][n=j] = V[s][j]
-            #pragma unroll
-            for (int sb = 0; sb < TB; ++sb)
-                if (sb <= tb)
-                    accO[n] = gemm_tile<32>(accO[n], sP + tb * 32 * LDP + sb * 32, LDP, 1, sV + sb * 32 * LDV + j0, LDV, 1, lane);
+            for (int u = 0; u < U; ++u)
+                if (k + u < n_s0) {
 #pragma unroll
-            for (int a = 0; a < 4; ++a)
-#pragma unroll
-                for (int b = 0; b < 4; ++b) {
-                    const int pp = c0 + tb * 32 + 8 * a + 4 * h + b;
-                    // (a streaming store: 32 lanes write one whole 128-byte line, and nothing here reads it again)
-                    if (pp < p1)
-                        __builtin_nontemporal_store(accO[n][4 * a + b], &Ob[(size_t)phys_row(pp, N, rev) * DV + j0 + r]);
+                    for (int e = 0; e < 16; ++e) accS[n][e] += x[u][e];
                 }
         }
     }
+    // One chunk's products as a list of steps: the operand of the next step is read from LDS while the current one's instructions
+    // run, and the splitting of queries and scores goes in between those.  Keys of the wave's own row block (the masked
+    // tile), the state before the chunk, then, for the second row block, the keys of the first.
+    auto products = [&](int c0, int more) __attribute__((always_inline)) {
+        constexpr int NA = KK, NB = NJ * KK, NC = 2 * NJ;
+        int ln = lane;      // (opaque: what depends on the lane alone would otherwise be kept in registers across the loop)
+        asm volatile("" : "+v"(ln));
+        Op3 aQ[KK], aP[2], op[2];
+        f32x16 pT, hi[NJ], lo[NJ];
+        auto split_q = [&](int kk) __attribute__((always_inline)) {
+            const float4 x = rq[2 * kk], y = rq[2 * kk + 1];
+            const float e[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+            aQ[kk] = split8(e);
+        };
+        // scores of keys 16 x .. 16 x + 15 of the block as first operand: the accumulator tile holds them as it wants them
+        auto split_p = [&](int x, bool mask) __attribute__((always_inline)) {
+            float e[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const int row = 16 * x + 8 * (q >> 2) + 4 * (ln >> 5) + (q & 3);        // key within the block; ln & 31 = query
+                const float v = pT[8 * x + q];
+                e[q] = !mask || row <= (ln & 31) ? v : 0.f;
+            }
+            aP[x] = split8(e);
+        };
+        auto keys = [&](int sb, int kk) __attribute__((always_inline)) { return ld3_nat<C, DK>(sK + sb * 32 * DK, 0, kk * 16, ln); };
+        auto state = [&](int s) __attribute__((always_inline)) { return ld3_nat<DV, DK>(sS, (jg * NJ + s / KK) * 32, s % KK * 16, ln); };
+        auto vals = [&](int sb, int s) __attribute__((always_inline)) {
+            return ld3_tr<C, DV, true>(sV + sb * 32 * DV, s / NJ * 16, (jg * NJ + s % NJ) * 32, ln);
+        };
+        split_q(0);
+        op[0] = keys(tb, 0);
+        pT = zero16f();
+#pragma unroll
+        for (int n = 0; n < NJ; ++n) { hi[n] = zero16f(); lo[n] = zero16f(); }
+#pragma unroll
+        for (int s = 0; s < NA + NB + NC; ++s) {
+            if (s + 1 < NA) op[(s + 1) & 1] = keys(tb, s + 1);
+            else if (s + 1 < NA + NB) op[(s + 1) & 1] = state(s + 1 - NA);
+            else if (s + 1 < NA + NB + NC) op[(s + 1) & 1] = vals(tb, s + 1 - NA - NB);
+            __builtin_amdgcn_sched_barrier(0);
+            if (s < NA) {                    // P^T[s][t] = k_s . q_t (each of the WJ waves of a row block for itself)
+                if (s + 1 < KK) split_q(s + 1);
+                pT = mul3(op[s & 1], aQ[s], pT);
+            } else if (s < NA + NB) {        // inter-chunk part Q S_prev
+                const int n = (s - NA) / KK;
+                mul3(aQ[(s - NA) % KK], op[s & 1], hi[n], lo[n]);
+                if (s == NA) split_p(0, true);
+                if (s == NA + 1) split_p(1, true);
+            } else {                         // intra-chunk part P V
+                const int x = (s - NA - NB) / NJ, n = (s - NA - NB) % NJ;
+                mul3(aP[x], op[s & 1], hi[n], lo[n]);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if (s + 1 == NA) fetch_q(c0 + C);
+        }
+        if (TB > 1 && tb > 0) {
+            op[0] = keys(0, 0);
+            pT = zero16f();
+#pragma unroll
+            for (int s = 0; s < NA + NC; ++s) {
+                if (s + 1 < NA) op[(s + 1) & 1] = keys(0, s + 1);
+                else if (s + 1 < NA + NC) op[(s + 1) & 1] = vals(0, s + 1 - NA);
+                __builtin_amdgcn_sched_barrier(0);
+                if (s < NA) {
+                    pT = mul3(op[s & 1], aQ[s], pT);
+                } else {
+                    const int x = (s - NA) / NJ, n = (s - NA) % NJ;
+                    if (s == NA) split_p(0, false);
+                    mul3(aP[x], op[s & 1], hi[n], lo[n]);
+                    if (s == NA) split_p(1, false);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        const ChunkRows<C, DV> rows(Ob, c0, p1, N, rev);
+        int off = rows.at(tb * 32 + 4 * (ln >> 5)) + (jg * NJ * 32 + (ln & 31)) * 4;
+        const int step = rev ? -DV * 4 : DV * 4;
+#pragma unroll
+        for (int n = 0; n < NJ; ++n)
+#pragma unroll
+            for (int a = 0; a < 4; ++a)
+#pragma unroll
+                for (int b = 0; b < 4; ++b)
+                    // (a streaming store: 32 lanes write one whole 128-byte line, and nothing here reads it again)
+                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, hi[n][4 * a + b] + lo[n][4 * a + b]), rows.rs,
+                                                          off + (8 * a + b) * step + n * 128, 0, 2);
+        // state update S += K^T V (not needed after the segment's last chunk)
+        if (more)
+            state_tiles<C, DK, DV, NS>(accS, sK, sV, ln, [&](int n) { return (q_own + n) % IB * 32; },
+                                        [&](int n) { return (jg * NJ + (q_own + n) / IB) * 32; });
+    };
+    // (nothing outstanding on the way into the loop: what a chunk waits for at its start is then counted from the chunk before,
+    // whose output stores, younger than its loads, need not have arrived)
+    __builtin_amdgcn_s_waitcnt(0x0f70);     // vmcnt(0)
+    int c0 = p0;
+    do {
+        unsigned tv = tid;       // (opaque, as in products())
+        asm volatile("" : "+v"(tv));
+        __syncthreads();   // previous chunk fully consumed
+        rk.stash(sK, tv);
+        rv.stash(sV, tv);
+        // publish the state before this chunk, [j][i]: a lane holds four consecutive i of one j
+#pragma unroll
+        for (int n = 0; n < NS; ++n) {
+            {
+                const int q = q_own + n, ib = q % IB, jb = jg * NJ + q / IB;
+#pragma unroll
+                for (int a = 0; a < 4; ++a) {
+                    const Pair3 x = split_pair(accS[n][4 * a], accS[n][4 * a + 1]), y = split_pair(accS[n][4 * a + 2], accS[n][4 * a + 3]);
+                    bf16* d = sS + jb * 32 * DK + tile_at<DK>(tv & 31, ib * 4 + a) + 4 * (tv >> 5 & 1);
+                    *reinterpret_cast<u32x2*>(d) = u32x2{x.h, y.h};
+                    *reinterpret_cast<u32x2*>(d + DK * DV) = u32x2{x.m, y.m};
+                    *reinterpret_cast<u32x2*>(d + 2 * DK * DV) = u32x2{x.l, y.l};
+                }
+            }
+        }
+        __syncthreads();
+        // the next chunk, in flight during the arithmetic
+        rk.fetch(ChunkRows<C, DK>(Kb, c0 + C, p1, N, rev), tid);
+        rv.fetch(ChunkRows<C, DV>(Vb, c0 + C, p1, N, rev), tid);
+        __builtin_amdgcn_sched_barrier(0);
+        // (opaque: known to be the loop's own condition, the loads above would be moved behind the branch on it)
+        int more = c0 + C < p1;
+        more = __builtin_amdgcn_readfirstlane(more);
+        asm volatile("" : "+s"(more));
+        products(c0, more);
+        c0 += C;
+    } while (c0 < p1);
 }
 
+// (64 x 64: two workgroups fit a compute unit's LDS, so the registers have to allow for two waves per SIMD)
 template <int DK, int DV>
-__global__ __launch_bounds__(256) void f32_sweep_kernel(const float* __restrict__ Q, const float* __restrict__ K,
-                                                       const float* __restrict__ V, float* __restrict__ O,
-                                                       const float* __restrict__ S0, int N, int seg_len, int n_seg)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DK == 64 && DV == 64 ? 2 : 1)))
+void f32_sweep_kernel(const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V, float* __restrict__ O,
+                      const float* __restrict__ S0, int N, int seg_len, int n_seg, bool folded)
 {
-    __shared__ float lds[f32_sweep_lds(DK, DV)];
-    f32_sweep_body<f32_sweep_chunk(DK, DV), DK, DV, false>(Q, K, V, O, S0, N, seg_len, n_seg, false, false, lds);
+    __shared__ __attribute__((aligned(16))) bf16 lds[f32_sweep_lds(DK, DV)];
+    f32_sweep_body<f32_sweep_chunk(DK, DV), DK, DV>(Q, K, V, O, S0, N, seg_len, n_seg, false, false, folded, lds);
 }
 
 // The gradient is three instances of the forward map (time-reversal duality), independent of one another, so they ride
@@ -572,30 +756,33 @@ __global__ __launch_bounds__(256) void f32_sweep_kernel(const float* __restrict_
 //   dQ = LinAttn(query dO, key V, value K)             causal          states V^T K   (first array)
 //   dK = LinAttn(query V,  key dO, value Q)            anti-causal     states dO^T Q  (the second array, transposed)
 //   dV = LinAttn(query K,  key Q, value dO)            anti-causal     states Q^T dO  (second array)
-// Bound by the fp32 matrix rate (24 heads x 3001 tokens, 64 x 64: 97 M matrix cycles of 197 M that the launch lasts; the
-// rest is barriers and the unequal shares of the causal triangle): as three launches, each with its own pre-pass and
-// scan and 240 workgroups for 512 places, the gradient took 148 us, side by side with 504 workgroups 104 us.
-template <int DK, int DV, bool BY_CHUNK>
-__global__ __launch_bounds__(256) void f32_bwd_sweep_kernel(const float* __restrict__ Q, const float* __restrict__ K,
-                                                           const float* __restrict__ V, const float* __restrict__ dO,
-                                                           float* __restrict__ dQ, float* __restrict__ dK,
-                                                           float* __restrict__ dV, const float* __restrict__ S0,
-                                                           size_t array_stride, int N, int seg_len, int n_seg)
+template <int DK, int DV>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DK == 64 && DV == 64 ? 2 : 1)))
+void f32_bwd_sweep_kernel(const float* __restrict__ Q, const float* __restrict__ K, const float* __restrict__ V,
+                          const float* __restrict__ dO, float* __restrict__ dQ, float* __restrict__ dK, float* __restrict__ dV,
+                          const float* __restrict__ S0, size_t array_stride, int N, int seg_len, int n_seg, bool folded)
 {
     constexpr int C = f32_sweep_chunk(DK, DV);
     constexpr int LA = f32_sweep_lds(DK, DV), LB = f32_sweep_lds(DV, DK);
-    __shared__ float lds[LA > LB ? LA : LB];
+    __shared__ __attribute__((aligned(16))) bf16 lds[LA > LB ? LA : LB];
     const int z = blockIdx.z;
     const float* S1 = S0 != nullptr ? S0 + array_stride : nullptr;
     if constexpr (DK == DV) {
-        f32_sweep_body<C, DK, DV, BY_CHUNK>(z == 0 ? dO : z == 1 ? V : K, z == 0 ? V : z == 1 ? dO : Q, z == 0 ? K : z == 1 ? Q : dO,
-                                  z == 0 ? dQ : z == 1 ? dK : dV, z == 0 ? S0 : S1, N, seg_len, n_seg, z != 0, z == 1, lds);
+        f32_sweep_body<C, DK, DV>(z == 0 ? dO : z == 1 ? V : K, z == 0 ? V : z == 1 ? dO : Q, z == 0 ? K : z == 1 ? Q : dO,
+                                  z == 0 ? dQ : z == 1 ? dK : dV, z == 0 ? S0 : S1, N, seg_len, n_seg, z != 0, z == 1, folded, lds);
     } else if (z < 2) {
-        f32_sweep_body<C, DV, DK, BY_CHUNK>(z == 0 ? dO : V, z == 0 ? V : dO, z == 0 ? K : Q, z == 0 ? dQ : dK, z == 0 ? S0 : S1, N,
-                                  seg_len, n_seg, z != 0, z == 1, lds);
+        f32_sweep_body<C, DV, DK>(z == 0 ? dO : V, z == 0 ? V : dO, z == 0 ? K : Q, z == 0 ? dQ : dK, z == 0 ? S0 : S1, N,
+                                  seg_len, n_seg, z != 0, z == 1, folded, lds);
     } else {
-        f32_sweep_body<C, DK, DV, BY_CHUNK>(K, Q, dO, dV, S1, N, seg_len, n_seg, true, false, lds);
+        f32_sweep_body<C, DK, DV>(K, Q, dO, dV, S1, N, seg_len, n_seg, true, false, folded, lds);
     }
+}
+
+// The sweeps add the segments' totals up themselves while a sequence's come to no more than kMaxFoldedStateBytes; a scan of
+// its own otherwise.
+static bool f32_fold(const Plan& plan)
+{
+    return (size_t)plan.n_seg * plan.state_elems * sizeof(float) <= kMaxFoldedStateBytes;
 }
 
 template <int DK, int DV>
@@ -604,6 +791,7 @@ static hipError_t f32_fwd_impl(const float* Q, const float* K, const float* V, f
 {
     hipError_t e;
     const dim3 grid((unsigned)BH, plan.n_seg);
+    const bool folded = f32_fold(plan);
     if (plan.n_seg > 1) {
         {
             ProfScope prof(KID_SEG_STATE_F32, st);
@@ -612,33 +800,11 @@ static hipError_t f32_fwd_impl(const float* Q, const float* K, const float* V, f
         }
         if ((e = hipGetLastError()) != hipSuccess) return e;
         const int mode = SCAN_EXCL_PREFIX;
-        if ((e = scan_states(ws, 0, 1, &mode, nullptr, 0, BH, plan.n_seg, DK * DV, st)) != hipSuccess) return e;
+        if (!folded && (e = scan_states(ws, 0, 1, &mode, nullptr, 0, BH, plan.n_seg, DK * DV, st)) != hipSuccess) return e;
     }
     ProfScope prof(KID_SWEEP_F32, st);
     hipLaunchKernelGGL((f32_sweep_kernel<DK, DV>), grid, dim3(256), 0, st, Q, K, V, O, plan.n_seg > 1 ? ws : nullptr, N,
-                       plan.seg_len, plan.n_seg);
-    return hipGetLastError();
-}
-
-template <int DK, int DV, bool BY_CHUNK>
-static hipError_t f32_bwd_launches(const float* Q, const float* K, const float* V, const float* dO, float* dQ, float* dK,
-                                   float* dV, long BH, int N, const Plan& plan, float* ws, hipStream_t st)
-{
-    hipError_t e;
-    const size_t stride = (size_t)BH * plan.n_seg * DK * DV;
-    if (plan.n_seg > 1) {
-        {
-            ProfScope prof(KID_SEG_STATE_F32, st);
-            hipLaunchKernelGGL((f32_bwd_seg_state_kernel<DK, DV, BY_CHUNK>), dim3((unsigned)BH, plan.n_seg, 2), dim3(256), 0,
-                               st, Q, K, V, dO, ws, stride, N, plan.seg_len, plan.n_seg);
-        }
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        const int modes[2] = {SCAN_EXCL_PREFIX, SCAN_EXCL_PREFIX};
-        if ((e = scan_states(ws, stride, 2, modes, nullptr, 0, BH, plan.n_seg, DK * DV, st)) != hipSuccess) return e;
-    }
-    ProfScope prof(KID_SWEEP_F32, st);
-    hipLaunchKernelGGL((f32_bwd_sweep_kernel<DK, DV, BY_CHUNK>), dim3((unsigned)BH, plan.n_seg, 3), dim3(256), 0, st, Q, K,
-                       V, dO, dQ, dK, dV, plan.n_seg > 1 ? ws : nullptr, stride, N, plan.seg_len, plan.n_seg);
+                       plan.seg_len, plan.n_seg, folded);
     return hipGetLastError();
 }
 
@@ -646,8 +812,23 @@ template <int DK, int DV>
 static hipError_t f32_bwd_impl(const float* Q, const float* K, const float* V, const float* dO, float* dQ, float* dK,
                                float* dV, long BH, int N, const Plan& plan, float* ws, hipStream_t st)
 {
-    return plan.by_chunk ? f32_bwd_launches<DK, DV, true>(Q, K, V, dO, dQ, dK, dV, BH, N, plan, ws, st)
-                         : f32_bwd_launches<DK, DV, false>(Q, K, V, dO, dQ, dK, dV, BH, N, plan, ws, st);
+    hipError_t e;
+    const size_t stride = (size_t)BH * plan.n_seg * DK * DV;
+    const bool folded = f32_fold(plan);
+    if (plan.n_seg > 1) {
+        {
+            ProfScope prof(KID_SEG_STATE_F32, st);
+            hipLaunchKernelGGL((f32_bwd_seg_state_kernel<DK, DV>), dim3((unsigned)BH, plan.n_seg, 2), dim3(256), 0, st, Q, K, V,
+                               dO, ws, stride, N, plan.seg_len, plan.n_seg);
+        }
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        const int modes[2] = {SCAN_EXCL_PREFIX, SCAN_EXCL_PREFIX};
+        if (!folded && (e = scan_states(ws, stride, 2, modes, nullptr, 0, BH, plan.n_seg, DK * DV, st)) != hipSuccess) return e;
+    }
+    ProfScope prof(KID_SWEEP_F32, st);
+    hipLaunchKernelGGL((f32_bwd_sweep_kernel<DK, DV>), dim3((unsigned)BH, plan.n_seg, 3), dim3(256), 0, st, Q, K, V, dO, dQ, dK,
+                       dV, plan.n_seg > 1 ? ws : nullptr, stride, N, plan.seg_len, plan.n_seg, folded);
+    return hipGetLastError();
 }
 
 #define CHELA_F32_DIMS(F_, ...)                                                                                        \

@@ -438,6 +438,91 @@ def test_f32_backward_takes_fewer_segments_in_a_smaller_scratch_buffer(dims):
     assert refused >= 1
 
 
+def test_f32_forward_takes_the_smaller_split_in_a_smaller_scratch_buffer():
+    # 24 x 3001: ten segments where there is room, the eight it is sure of otherwise, below that refused
+    w = _small("f32", N=3001, B=2, H=12, seed=78)
+    x = make_inputs(w)
+    d = _dev(x)
+    state = w.B * w.H * w.dk * w.dv * 4
+    full = binding.chela_linattn_workspace_bytes(w.B, w.H, w.N, w.dk, w.dv, 64, False, binding.DTYPE_F32)
+    assert full == 10 * state
+    ref = oracle.fwd_recurrent(*(to_f64_numpy(x[n]) for n in "QKV"))
+    buf = torch.empty(full, dtype=torch.uint8, device="cuda")
+    try:
+        for n in (full, full - 1, 8 * state):
+            binding.chela_set_workspace(buf[:n])
+            _check("O", binding.chela_linattn_fwd(d["Q"], d["K"], d["V"]), ref, "f32")
+        binding.chela_set_workspace(buf[:8 * state - 1])
+        with pytest.raises(binding.ChelaError) as ei:
+            binding.chela_linattn_fwd(d["Q"], d["K"], d["V"])
+        assert ei.value.status == -7
+    finally:
+        binding.chela_set_workspace(None)
+
+
+@pytest.mark.parametrize("seg", [None, 64, 192])
+@pytest.mark.parametrize("dims", [(64, 64), (64, 128), (128, 64), (128, 128)])
+def test_f32_edges_of_row_blocks_chunks_and_segments(dims, seg, monkeypatch):
+    # (20 chunks of 64 in single segments: more states than the sweeps add up by themselves)
+    if seg:
+        monkeypatch.setenv("CHELA_SEG_TOKENS", str(seg))
+    for N in (1, 31, 32, 33, 63, 64, 65, 97, 129, 385, 1251):
+        w = _small("f32", N=N, B=1, H=3, dk=dims[0], dv=dims[1], seed=500 + N)
+        _run_case(w, 64, True)
+
+
+@pytest.mark.parametrize("dims", [(64, 64), (128, 128)])
+def test_f32_parts_hold_every_exponent(dims):
+    # All 24 bits of an operand are in its three parts whatever its exponent: inputs times powers of two give the same
+    # bits times their product, and a token 2^60 louder than the others of its chunk takes nothing from those before it.
+    w = _small("f32", N=300, B=1, H=2, dk=dims[0], dv=dims[1], seed=61)
+    d = _dev(make_inputs(w))
+    Q, K, V, G = (d[n] for n in ("Q", "K", "V", "dO"))
+    O, g = binding.chela_linattn_fwd(Q, K, V), binding.chela_linattn_bwd(Q, K, V, G)
+    for a, b, c, e in ((-70, 90, -60, 40), (60, -70, 70, -60)):      # (every result above 2^-100, its smallest part then normal)
+        f = [2.0 ** k for k in (a, b, c, e)]
+        q, k, v, u = Q * f[0], K * f[1], V * f[2], G * f[3]
+        assert torch.equal(binding.chela_linattn_fwd(q, k, v), O * (f[0] * f[1] * f[2]))
+        for got, ref, s in zip(binding.chela_linattn_bwd(q, k, v, u), g, (f[1] * f[2] * f[3], f[0] * f[2] * f[3], f[0] * f[1] * f[3])):
+            assert torch.equal(got, ref * s)
+    for t in (40, 95, 200):
+        k, v = K.clone(), V.clone()
+        k[:, :, t] *= 2.0 ** 30
+        v[:, :, t] *= 2.0 ** 30
+        loud = binding.chela_linattn_fwd(Q, k, v)
+        assert torch.equal(loud[:, :, :t], O[:, :, :t])
+        ref = oracle.fwd_recurrent(*(to_f64_numpy(x) for x in (Q, k, v)))
+        _check("O loud", loud[:, :, t:], ref[:, :, t:], "f32")
+
+
+@pytest.mark.parametrize("dims", [(64, 64), (64, 128), (128, 128)])
+@pytest.mark.parametrize("bad", [float("inf"), float("-inf"), float("nan")])
+def test_f32_non_finite_values_stay_where_they_belong(dims, bad):
+    w = _small("f32", N=450, B=1, H=2, dk=dims[0], dv=dims[1], seed=62)
+    d = _dev(make_inputs(w))
+    Q, K, V, G = (d[n] for n in ("Q", "K", "V", "dO"))
+    O = binding.chela_linattn_fwd(Q, K, V)
+    for t in (0, 37, 64, 130, 449):
+        q, k, v = Q.clone(), K.clone(), V.clone()
+        q[0, 0, t, 5] = bad                      # a query: its own row
+        got = binding.chela_linattn_fwd(q, K, V)
+        rest = torch.ones(w.N, dtype=torch.bool)
+        rest[t] = False
+        assert not torch.isfinite(got[0, 0, t]).any()
+        assert torch.equal(got[0, 0, rest], O[0, 0, rest]) and torch.equal(got[0, 1], O[0, 1])
+        k[0, 0, t, 5] = bad                      # a key: its own and later rows
+        got = binding.chela_linattn_fwd(Q, k, V)
+        assert not torch.isfinite(got[0, 0, t:]).any()
+        assert torch.equal(got[0, 0, :t], O[0, 0, :t]) and torch.equal(got[0, 1], O[0, 1])
+        v[0, 0, t, 7] = bad                      # a value: its own column, from its block of 32 rows on (0 times it is NaN)
+        got = binding.chela_linattn_fwd(Q, K, v)
+        cols = torch.arange(w.dv) != 7
+        assert not torch.isfinite(got[0, 0, t:, 7]).any()
+        assert torch.equal(got[0, 0][:, cols], O[0, 0][:, cols])
+        assert torch.equal(got[0, 0, :t // 32 * 32], O[0, 0, :t // 32 * 32])
+        assert torch.equal(got[0, 1], O[0, 1])
+
+
 @pytest.mark.parametrize("shape", [(96, 1029, 64, 128), (96, 2047, 64, 64), (112, 1000, 128, 64), (90, 1025, 128, 128)])
 def test_f32_backward_split_where_one_segment_would_fill_the_gpu(shape):
     # three workgroups per segment and 256 or more at one segment per sequence: split all the same, ragged ends included.
