@@ -992,6 +992,22 @@ __device__ __forceinline__ void bwd_sweep_body(const bf16* __restrict__ Qb, cons
         else sum_states<DV, DK, false>(accRT, Rnext, n_rnext, w, lane);
     }
 
+    // The state after chunk ci as the first pass left it, in place of the one walked back to here.  It is waited for here: left to
+    // the compiler the wait stands behind the branch, where it also holds up every chunk that takes none, until the loads
+    // of the chunk after it, just sent out, have come back.
+    auto take_ckpt = [&](int ci) __attribute__((always_inline)) {
+        if (ckpt == nullptr || (ci + 1) % ckpt_every != 0 || ci + 1 >= n_ch) return;
+        const float4* src = reinterpret_cast<const float4*>(ckpt + (size_t)((ci + 1) / ckpt_every - 1) * (DK * DV)) +
+                            ((size_t)(w * NS) * 64 + lane) * 4;
+#pragma unroll
+        for (int n = 0; n < NS; ++n)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const float4 v = src[(size_t)n * 256 + q];
+                accNS[n][4 * q] = v.x; accNS[n][4 * q + 1] = v.y; accNS[n][4 * q + 2] = v.z; accNS[n][4 * q + 3] = v.w;
+            }
+        __builtin_amdgcn_s_waitcnt(0x0f70);     // vmcnt(0)
+    };
     for (int ci = n_ch - 1; ci >= 0; --ci) {
         const int c0 = ci * C;
         if constexpr (SHARE && !ZQK) {
@@ -1006,22 +1022,12 @@ __device__ __forceinline__ void bwd_sweep_body(const bf16* __restrict__ Qb, cons
             rg.store(sG, tid);
             state_to_lds_T<DV, DK, false>(sR, accRT, w, lane);      // R: the state after this chunk
             __syncthreads();
+            take_ckpt(ci);
             if (ci > 0) {
                 rq.load(Qb + (size_t)(c0 - C) * ldk, ldk, C, tid);
                 rk.load(Kb + (size_t)(c0 - C) * ldk, ldk, C, tid);
                 rv.load(Vb + (size_t)(c0 - C) * ldv, ldv, C, tid);
                 rg.load(Gb + (size_t)(c0 - C) * ldv, ldv, C, tid);
-            }
-            if (ckpt != nullptr && (ci + 1) % ckpt_every == 0 && ci + 1 < n_ch) {
-                const float4* src = reinterpret_cast<const float4*>(ckpt + (size_t)((ci + 1) / ckpt_every - 1) * (DK * DV)) +
-                                    ((size_t)(w * NS) * 64 + lane) * 4;
-#pragma unroll
-                for (int n = 0; n < NS; ++n)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const float4 v = src[(size_t)n * 256 + q];
-                        accNS[n][4 * q] = v.x; accNS[n][4 * q + 1] = v.y; accNS[n][4 * q + 2] = v.z; accNS[n][4 * q + 3] = v.w;
-                    }
             }
             const int valid = ntok - (c0 + rb * 32);
             {   // dK^T for key block sb = rb:  dK^T = Q^T dP + R V^T
@@ -1168,23 +1174,12 @@ __device__ __forceinline__ void bwd_sweep_body(const bf16* __restrict__ Qb, cons
         // R (state after this chunk) is already final: publish it as bf16 [i][j]
         if (!SHARE) state_to_lds_T<DV, DK, false>(sR, accRT, w, lane);
         __syncthreads();
+        take_ckpt(ci);
         if (ci > 0) {   // every chunk but a segment's last is complete
             rq.load(Qb + (size_t)(c0 - C) * ldk, ldk, C, tid);
             if (!ZQK) rk.load(Kb + (size_t)(c0 - C) * ldk, ldk, C, tid);
             rv.load(Vb + (size_t)(c0 - C) * ldv, ldv, C, tid);
             rg.load(Gb + (size_t)(c0 - C) * ldv, ldv, C, tid);
-        }
-        if (ckpt != nullptr && (ci + 1) % ckpt_every == 0 && ci + 1 < n_ch) {
-            // the state after this chunk as the first pass left it, in place of the one walked back to here
-            const float4* src = reinterpret_cast<const float4*>(ckpt + (size_t)((ci + 1) / ckpt_every - 1) * (DK * DV)) +
-                                ((size_t)(w * NS) * 64 + lane) * 4;
-#pragma unroll
-            for (int n = 0; n < NS; ++n)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const float4 v = src[(size_t)n * 256 + q];
-                    accNS[n][4 * q] = v.x; accNS[n][4 * q + 1] = v.y; accNS[n][4 * q + 2] = v.z; accNS[n][4 * q + 3] = v.w;
-                }
         }
         // roll S back over this chunk: (-S^T) += V^T K, then publish S (state before this chunk)
 #pragma unroll
