@@ -162,6 +162,22 @@ struct AffineCols {
 
 // A C x D bf16 tile (C consecutive rows of a row-major [N][D] matrix, i.e. one contiguous block of memory) travels
 // HBM -> registers (16-byte vectors, NV per thread) -> LDS (row stride D + PAD).
+// Rows of a [B,H,N,d] tensor, the first valid_rows of those at `tile`, as a buffer: what lies beyond reads as zero and is not
+// written.  No branch and no exec mask stands around such an access, so the compiler can count what is outstanding
+// (s_waitcnt vmcnt(n) with the exact n) across chunks, and a chunk's loads are not waited for together with the
+// stores of the one before: lm shape, forward + backward, 285 -> 280 us, layer 2048 tokens x 48 heads 72.3 -> 70.1, prefill
+// 36 x 1531 15.9 -> 15.1.  tile and valid_rows are the same for all lanes.  ([B,N,H,d] tensors, whose 64 rows may lie more
+// than 4 GB apart, keep addresses and predicates.)
+// packed<D>(ld): rows lie one behind the other, known at compile time (after inlining).
+template <int D>
+__device__ __forceinline__ bool packed(int ld) { return __builtin_constant_p(ld) && ld == D; }
+
+template <int D>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_buffer(const bf16* tile, int valid_rows)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16*>(tile), 0, __builtin_amdgcn_readfirstlane(max(valid_rows, 0)) * (D * 2), 0x00020000);
+}
+
 // 16-byte global load, optionally with the streaming ("non-temporal") hint.  The hint is for streams that nobody
 // reads again soon (the forward sweep's Q, the gate): they then do not push the K and V tiles that the pre-pass
 // has just brought into the memory-side cache out before the sweep re-reads them.  Measured: forward sweep 74.0 ->
@@ -197,16 +213,18 @@ struct TileRegs {
     }
     __device__ __forceinline__ void load(const bf16* tile, int ld, int valid_rows, int tid)
     {
-        if (valid_rows >= C) {
+        if (packed<D>(ld)) {
+            const __amdgpu_buffer_rsrc_t rs = row_buffer<D>(tile, min(valid_rows, C));
+#pragma unroll
+            for (int n = 0; n < NV; ++n)
+                v[n] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rs, (tid + 256 * n) * 16, 0, NTL ? 2 : 0));
+        } else if (valid_rows >= C) {
 #pragma unroll
             for (int n = 0; n < NV; ++n) v[n] = ldg16<NTL>(at(tile, ld, tid, n));
         } else {
             const int lim = valid_rows * VPR;
 #pragma unroll
-            for (int n = 0; n < NV; ++n) {
-                const int x = tid + 256 * n;
-                v[n] = x < lim ? ldg16<NTL>(at(tile, ld, tid, n)) : make_uint4(0, 0, 0, 0);
-            }
+            for (int n = 0; n < NV; ++n) v[n] = tid + 256 * n < lim ? ldg16<NTL>(at(tile, ld, tid, n)) : make_uint4(0, 0, 0, 0);
         }
     }
     // All C rows exist: no predicate, so the loads are issued unconditionally and the compiler can count them
@@ -240,10 +258,12 @@ struct TileRegs {
 // Store a TRANSPOSED 32x32 accumulator tile (register 4a+b of lane (r,h) = feature 8a+4h+b of token r) as bf16 into
 // rows [0,32) x columns [col0, col0+32) of the row-major matrix at `rows` (leading dimension ld).  The two half-waves
 // trade registers so that every lane ends up with 8 consecutive features of its token: two 16-byte stores per lane.
+template <int D>
 __device__ __forceinline__ void store_tile_T(bf16* rows, int ld, int col0, const f32x16& acc, int valid_rows, int lane)
 {
     const int r = lane & 31, h = lane >> 5;
     bf16* dst = rows + ((unsigned)r * (unsigned)ld + (unsigned)(col0 + 8 * h));   // uniform base + 32-bit lane offset
+    const __amdgpu_buffer_rsrc_t rs = row_buffer<D>(rows, min(valid_rows, 32));
 #pragma unroll
     for (int ap = 0; ap < 2; ++ap) {
         const unsigned x0 = pack2(acc[8 * ap + 0], acc[8 * ap + 1]), x1 = pack2(acc[8 * ap + 2], acc[8 * ap + 3]);
@@ -251,7 +271,10 @@ __device__ __forceinline__ void store_tile_T(bf16* rows, int ld, int col0, const
         // lanes 32..63 of x <-> lanes 0..31 of y
         const u32x2 s0 = __builtin_amdgcn_permlane32_swap(x0, y0, false, false);
         const u32x2 s1 = __builtin_amdgcn_permlane32_swap(x1, y1, false, false);
-        if (r < valid_rows) *reinterpret_cast<uint4*>(dst + 16 * ap) = make_uint4(s0[0], s1[0], s0[1], s1[1]);
+        u32x4 t;
+        t[0] = s0[0]; t[1] = s1[0]; t[2] = s0[1]; t[3] = s1[1];
+        if (packed<D>(ld)) __builtin_amdgcn_raw_buffer_store_b128(t, rs, (r * D + col0 + 8 * h) * 2 + 32 * ap, 0, 0);
+        else if (r < valid_rows) *reinterpret_cast<u32x4*>(dst + 16 * ap) = t;
     }
 }
 
@@ -288,20 +311,19 @@ template <int ROWS, int D, bool NTS = true>
 __device__ __forceinline__ void flush_stage(const bf16* stage, bf16* out, int ld, int valid_rows, int tid)
 {
     constexpr int PPR = D / 8;      // 16-byte pieces per row
+    const __amdgpu_buffer_rsrc_t rs = row_buffer<D>(out, min(valid_rows, ROWS));
 #pragma unroll
     for (int n = 0; n < ROWS * PPR / 256; ++n) {
-        const int x = tid + 256 * n, row = x / PPR, piece = x % PPR;
-        if (row < valid_rows) {
-            // streaming ("non-temporal") stores: nothing here reads an output again, whole 128-byte lines leave at
-            // once, and lines that do not linger in the memory-side cache do not push the inputs out of it
-            const uint4 t = *reinterpret_cast<const uint4*>(stage + stage_at<D>(row, piece));
-            if (NTS) {
-                u32x4v tv;
-                tv[0] = t.x; tv[1] = t.y; tv[2] = t.z; tv[3] = t.w;
-                __builtin_nontemporal_store(tv, reinterpret_cast<u32x4v*>(out + ((unsigned)row * (unsigned)ld + (unsigned)piece * 8u)));
-            } else {
-                *reinterpret_cast<uint4*>(out + ((unsigned)row * (unsigned)ld + (unsigned)piece * 8u)) = t;
-            }
+        const int x = tid + 256 * n, row = (unsigned)x / PPR, piece = (unsigned)x % PPR;
+        // streaming ("non-temporal") stores: nothing here reads an output again, whole 128-byte lines leave at
+        // once, and lines that do not linger in the memory-side cache do not push the inputs out of it
+        if (packed<D>(ld)) {
+            __builtin_amdgcn_raw_buffer_store_b128(*reinterpret_cast<const u32x4*>(stage + stage_at<D>(row, piece)), rs, x * 16, 0, NTS ? 2 : 0);
+        } else if (row < valid_rows) {
+            const u32x4 t = *reinterpret_cast<const u32x4*>(stage + stage_at<D>(row, piece));
+            u32x4* dst = reinterpret_cast<u32x4*>(out + ((unsigned)row * (unsigned)ld + (unsigned)piece * 8u));
+            if (NTS) __builtin_nontemporal_store(t, dst);
+            else *dst = t;
         }
     }
 }
@@ -686,6 +708,7 @@ __device__ __forceinline__ void fwd_sweep_body(const bf16* __restrict__ Qb, cons
     // staging tiles (STAGE): O, or with GATE: Y then O
     bf16* sOutY = reinterpret_cast<bf16*>(lds + FwdLds<C, DK, DV, ZQK, GATE>::BYTES);
     bf16* sOutO = GATE ? sOutY + C * DV : sOutY;
+    __builtin_amdgcn_s_waitcnt(0x0f70);         // (vmcnt(0): as in the backward sweep)
     for (int c0 = 0; c0 < ntok; c0 += C) {
         if (ZQK) {
             rq.store_affine(sQ, sAff, sAff + DK, tid);
@@ -701,12 +724,14 @@ __device__ __forceinline__ void fwd_sweep_body(const bf16* __restrict__ Qb, cons
         if (GATE && STAGE && c0 > 0)    // the chunk before's gated output, complete in its staging tile since that barrier
             flush_stage<C, DV>(sOutY, Yb + (size_t)(c0 - C) * ldv, ldv, C, tid);
         const bool more = c0 + C < ntok;
-        if (more) {
+        // (the branch is worth its keep without the gate: 128 x 128, one sequence of 65536 tokens, 16 heads, 317 us with it, 332
+        // with loads of an empty buffer after the last chunk; with the gate it costs 1 %)
+        if (GATE || more) {
             rq.load(Qb + (size_t)(c0 + C) * ldk, ldk, ntok - c0 - C, tid);
             if (!ZQK) rk.load(Kb + (size_t)(c0 + C) * ldk, ldk, ntok - c0 - C, tid);
             rv.load(Vb + (size_t)(c0 + C) * ldv, ldv, ntok - c0 - C, tid);
-            if (GATE) rg.load(Gb + (size_t)(c0 + C) * ldv, ldv, ntok - c0 - C, tid);
         }
+        if (GATE) rg.load(Gb + (size_t)(c0 + C) * ldv, ldv, ntok - c0 - C, tid);
         bf16x8 bQ[DK / 16];   // Q rows of this wave's token block: the B operand (n = token, k = feature i)
 #pragma unroll
         for (int kk = 0; kk < DK / 16; ++kk) bQ[kk] = ld_nat(sQ, LDK, tb * 32, kk * 16, lane);
@@ -743,7 +768,7 @@ __device__ __forceinline__ void fwd_sweep_body(const bf16* __restrict__ Qb, cons
         } else if (!GATE || Ob != nullptr) {
             bf16* rows = Ob + (size_t)(c0 + tb * 32) * ldv;
 #pragma unroll
-            for (int n = 0; n < NJ; ++n) store_tile_T(rows, ldv, (jg * NJ + n) * 32, accO[n], valid, lane);
+            for (int n = 0; n < NJ; ++n) store_tile_T<DV>(rows, ldv, (jg * NJ + n) * 32, accO[n], valid, lane);
         }
         uint4 gate[GATE ? NJ : 1][2];   // this chunk's gate, in the order the output tile is stored in
         if (GATE) {
@@ -793,7 +818,7 @@ __device__ __forceinline__ void fwd_sweep_body(const bf16* __restrict__ Qb, cons
                 bf16* rows = Yb + (size_t)(c0 + tb * 32) * ldv;
 #pragma unroll
                 for (int n = 0; n < NJ; ++n)
-                    store_tile_T(rows, ldv, (jg * NJ + n) * 32, gate_tile(accO[n], gate[n], rinv), valid, lane);
+                    store_tile_T<DV>(rows, ldv, (jg * NJ + n) * 32, gate_tile(accO[n], gate[n], rinv), valid, lane);
             }
         }
     }
@@ -1008,6 +1033,9 @@ __device__ __forceinline__ void bwd_sweep_body(const bf16* __restrict__ Qb, cons
             }
         __builtin_amdgcn_s_waitcnt(0x0f70);     // vmcnt(0)
     };
+    // (nothing outstanding on the way into the loop: what a chunk waits for at its start is then counted from the chunk before,
+    // whose output stores, younger than its loads, need not have arrived)
+    __builtin_amdgcn_s_waitcnt(0x0f70);         // vmcnt(0)
     for (int ci = n_ch - 1; ci >= 0; --ci) {
         const int c0 = ci * C;
         if constexpr (SHARE && !ZQK) {
@@ -1023,11 +1051,11 @@ __device__ __forceinline__ void bwd_sweep_body(const bf16* __restrict__ Qb, cons
             state_to_lds_T<DV, DK, false>(sR, accRT, w, lane);      // R: the state after this chunk
             __syncthreads();
             take_ckpt(ci);
-            if (ci > 0) {
-                rq.load(Qb + (size_t)(c0 - C) * ldk, ldk, C, tid);
-                rk.load(Kb + (size_t)(c0 - C) * ldk, ldk, C, tid);
-                rv.load(Vb + (size_t)(c0 - C) * ldv, ldv, C, tid);
-                rg.load(Gb + (size_t)(c0 - C) * ldv, ldv, C, tid);
+            if (ci > 0) {          // (every chunk but a segment's last is complete)
+                rq.load(Qb + ((ptrdiff_t)c0 - C) * ldk, ldk, C, tid);
+                rk.load(Kb + ((ptrdiff_t)c0 - C) * ldk, ldk, C, tid);
+                rv.load(Vb + ((ptrdiff_t)c0 - C) * ldv, ldv, C, tid);
+                rg.load(Gb + ((ptrdiff_t)c0 - C) * ldv, ldv, C, tid);
             }
             const int valid = ntok - (c0 + rb * 32);
             {   // dK^T for key block sb = rb:  dK^T = Q^T dP + R V^T
@@ -1062,7 +1090,7 @@ __device__ __forceinline__ void bwd_sweep_body(const bf16* __restrict__ Qb, cons
 #pragma unroll
                 for (int n = 0; n < NI; ++n) {
                     if (DK == 64) stage_tile_T<64>(sSt, rb * 32, (cg * NI + n) * 32, acc[n], lane);
-                    else store_tile_T(rows, ldk, (cg * NI + n) * 32, acc[n], valid, lane);
+                    else store_tile_T<DK>(rows, ldk, (cg * NI + n) * 32, acc[n], valid, lane);
                 }
             }
             {   // dV^T for key block sb = rb:  dV^T = dO^T P + R^T K^T
@@ -1096,7 +1124,7 @@ __device__ __forceinline__ void bwd_sweep_body(const bf16* __restrict__ Qb, cons
                 bf16* rows = dVb + (size_t)(c0 + rb * 32) * ldv;
 #pragma unroll
                 for (int n = 0; n < NJ; ++n) {
-                    store_tile_T(rows, ldv, (cg * NJ + n) * 32, acc[n], valid, lane);
+                    store_tile_T<DV>(rows, ldv, (cg * NJ + n) * 32, acc[n], valid, lane);
                 }
             }
             // R^T += dO^T Q (after the segment's first chunk only if the final state is asked for), and S rolled back
@@ -1154,7 +1182,7 @@ __device__ __forceinline__ void bwd_sweep_body(const bf16* __restrict__ Qb, cons
                 for (int n = 0; n < NI; ++n) {
                     // (the staging tile was last read by the flush above, before the barrier that let S in)
                     if (DK == 64) stage_tile_T<64>(sSt, rb * 32, (cg * NI + n) * 32, acc[n], lane);
-                    else store_tile_T(rows, ldk, (cg * NI + n) * 32, acc[n], valid, lane);
+                    else store_tile_T<DK>(rows, ldk, (cg * NI + n) * 32, acc[n], valid, lane);
                 }
             }
             __syncthreads();            // tiles, S and the staged dQ are done with
@@ -1175,11 +1203,12 @@ __device__ __forceinline__ void bwd_sweep_body(const bf16* __restrict__ Qb, cons
         if (!SHARE) state_to_lds_T<DV, DK, false>(sR, accRT, w, lane);
         __syncthreads();
         take_ckpt(ci);
-        if (ci > 0) {   // every chunk but a segment's last is complete
-            rq.load(Qb + (size_t)(c0 - C) * ldk, ldk, C, tid);
-            if (!ZQK) rk.load(Kb + (size_t)(c0 - C) * ldk, ldk, C, tid);
-            rv.load(Vb + (size_t)(c0 - C) * ldv, ldv, C, tid);
-            rg.load(Gb + (size_t)(c0 - C) * ldv, ldv, C, tid);
+        // (every chunk but a segment's last is complete; where buffers bound the loads, those behind the first chunk are of none)
+        if (ci > 0 || packed<DK>(ldk)) {
+            rq.load(Qb + ((ptrdiff_t)c0 - C) * ldk, ldk, ci > 0 || !packed<DK>(ldk) ? C : 0, tid);
+            if (!ZQK) rk.load(Kb + ((ptrdiff_t)c0 - C) * ldk, ldk, ci > 0 || !packed<DK>(ldk) ? C : 0, tid);
+            rv.load(Vb + ((ptrdiff_t)c0 - C) * ldv, ldv, ci > 0 || !packed<DK>(ldk) ? C : 0, tid);
+            rg.load(Gb + ((ptrdiff_t)c0 - C) * ldv, ldv, ci > 0 || !packed<DK>(ldk) ? C : 0, tid);
         }
         // roll S back over this chunk: (-S^T) += V^T K, then publish S (state before this chunk)
 #pragma unroll
@@ -1228,7 +1257,7 @@ __device__ __forceinline__ void bwd_sweep_body(const bf16* __restrict__ Qb, cons
 #pragma unroll
                 for (int n = 0; n < NI; ++n) {
                     if (STAGE) stage_tile_T<64>(sOutQ, rb * 32, (cg * NI + n) * 32, acc[n], lane);
-                    else store_tile_T(rows, ldk, (cg * NI + n) * 32, acc[n], valid, lane);
+                    else store_tile_T<DK>(rows, ldk, (cg * NI + n) * 32, acc[n], valid, lane);
                 }
             }
         }
@@ -1271,7 +1300,7 @@ __device__ __forceinline__ void bwd_sweep_body(const bf16* __restrict__ Qb, cons
 #pragma unroll
                 for (int n = 0; n < NI; ++n) {
                     if (STAGE) stage_tile_T<64>(sOutK, rb * 32, (cg * NI + n) * 32, acc[n], lane);
-                    else store_tile_T(rows, ldk, (cg * NI + n) * 32, acc[n], valid, lane);
+                    else store_tile_T<DK>(rows, ldk, (cg * NI + n) * 32, acc[n], valid, lane);
                 }
             } else {
                 // dZ = alpha_q dQ + alpha_k dK; the lane owns features f0 + 8a + 4h + b of token rb*32 + r
@@ -1298,7 +1327,7 @@ __device__ __forceinline__ void bwd_sweep_body(const bf16* __restrict__ Qb, cons
                         }
                     }
                     if (STAGE) stage_tile_T<64>(sOutQ, rb * 32, f0, dz, lane);
-                    else store_tile_T(rows, ldk, f0, dz, valid, lane);
+                    else store_tile_T<DK>(rows, ldk, f0, dz, valid, lane);
                     pg[0][n] += sum_tokens16(qz, lane);
                     pg[1][n] += sum_tokens16(accQ[n], lane);
                     pg[2][n] += sum_tokens16(kz, lane);
@@ -1339,7 +1368,7 @@ __device__ __forceinline__ void bwd_sweep_body(const bf16* __restrict__ Qb, cons
 #pragma unroll
             for (int n = 0; n < NJ; ++n) {
                 if (STAGE) stage_tile_T<64>(sOutV, rb * 32, (cg * NJ + n) * 32, acc[n], lane);
-                else store_tile_T(rows, ldv, (cg * NJ + n) * 32, acc[n], valid, lane);
+                else store_tile_T<DV>(rows, ldv, (cg * NJ + n) * 32, acc[n], valid, lane);
             }
         }
         // ---------------- R^T += dO^T Q (after the segment's first chunk only if the final state is asked for)
@@ -2089,7 +2118,7 @@ __device__ __forceinline__ void apply_body(const bf16* __restrict__ X, bf16* __r
         const int valid = ntok - (held_c0 + tb * 32);
 #pragma unroll
         for (int n = 0; n < NJ; ++n)
-            store_tile_T(rows, DB, (jg * NJ + n) * 32, gate_tile(held[n], gate[n], rinv), valid, lane);
+            store_tile_T<DB>(rows, DB, (jg * NJ + n) * 32, gate_tile(held[n], gate[n], rinv), valid, lane);
     };
 
     constexpr bool STAGE = ApplyLds<DA, DB, GATE>::STAGE;
@@ -2131,7 +2160,7 @@ __device__ __forceinline__ void apply_body(const bf16* __restrict__ X, bf16* __r
             bf16* rows = Yb + (size_t)(c0 + tb * 32) * DB;
             const int valid = ntok - (c0 + tb * 32);
 #pragma unroll
-            for (int n = 0; n < NJ; ++n) store_tile_T(rows, DB, (jg * NJ + n) * 32, acc[n], valid, lane);
+            for (int n = 0; n < NJ; ++n) store_tile_T<DB>(rows, DB, (jg * NJ + n) * 32, acc[n], valid, lane);
         }
         if (GATE) {
             float ss = 0.f;
