@@ -1734,16 +1734,32 @@ __global__ __launch_bounds__(conv_threads(M)) void longconv_dk_finish_kernel(con
         dw[(long)c * m + tid] = t;
     }
     build_tables<M, T>(tw, tid);
+    constexpr int NP = PairPos<M, T>::NP;
+    // (slice by slice, all of a thread's pairs of U slices in flight together; pair by pair, every read waited for the one before:
+    // 17 x 256 channels x 448 steps, fp32, 44 us of a training step of 108, now 14; the call of 32 x 512 x 4096, bf16, 421 -> 416)
+    constexpr int U = 2;
+    float4 sum[NP];
+#pragma unroll
+    for (int i = 0; i < NP; ++i) sum[i] = make_float4(0.f, 0.f, 0.f, 0.f);
+    const float4* slice = part + (long)c * (M / 2 + 1) + tid;
+    for (int g = 0; g < G; g += U) {       // fixed order: deterministic
+        float4 o[U][NP];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int i = 0; i < NP; ++i)
+                o[u][i] = g + u < G ? slice[(long)(g + u) * d * (M / 2 + 1) + T * i] : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int i = 0; i < NP; ++i) { sum[i].x += o[u][i].x; sum[i].y += o[u][i].y; sum[i].z += o[u][i].z; sum[i].w += o[u][i].w; }
+    }
     const PairPos<M, T> pos(tid);
     const PairTwiddle<M, T> pw(tid);
     cplx w = pw.first;
 #pragma unroll
-    for (int i = 0; i < PairPos<M, T>::NP; ++i) {
-        float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
-        for (int g = 0; g < G; ++g) {      // fixed order: deterministic
-            const float4 o = part[((long)g * d + c) * (M / 2 + 1) + tid + T * i];
-            t.x += o.x; t.y += o.y; t.z += o.z; t.w += o.w;
-        }
+    for (int i = 0; i < NP; ++i) {
+        const float4 t = sum[i];
         cplx A, B;
         pair_pack(t, w, i == 0 && tid == 0, A, B);
         a[pos.first(i)] = A;
