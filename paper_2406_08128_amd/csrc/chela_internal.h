@@ -122,8 +122,10 @@ hipError_t launch_bf16_noncausal_bwd(const void* Q, const void* K, const void* V
 hipError_t launch_bf16_step(const void* q, const void* k, const void* v, float* S, void* o, const void* gate, float eps,
                             long BH, int dk, int dv, hipStream_t st);
 
-// Short-long convolutions (Sec. 4.2).  conv_fft_size(L): length M of the complex transform used for sequences of
-// L steps (0: L too long); the kernel spectrum is [d][M/2 + 1] float4, one per pair of bins.  dtype 0: bf16 I/O, 1: fp32 I/O.
+// Short-long convolutions (Sec. 4.2).  conv_points(L): length M of the complex transform used for sequences of L steps (0: L too
+// long); the kernel spectrum is [d][M/2 + 1] float4, one per pair of bins.  dtype 0: bf16 I/O, 1: fp32 I/O.
+// conv_fft_size(L): the next power of four from M on, for which buffers are sized and laid out, and shared channels dealt out.
+int conv_points(int L);
 int conv_fft_size(int L);
 // Longer sequences (16384 < L <= kConvMaxL) are convolved block by block, 16384 steps per block: the number of
 // blocks (0: L is served by one transform, or too long).  The spectrum buffer then holds one spectrum per channel

@@ -8,7 +8,7 @@
 //   ->  y[2n], y[2n+1] = Re, Im.
 // FFT: in place, decimation in frequency forward (natural order in, digit-reversed out) and the exact inverse of
 // every pass in reverse order (digit-reversed in, natural out), so no reordering pass exists; the point-wise
-// stage addresses the spectrum through the digit reversal.  M = 4^a 16^b: an optional leading radix-4 pass, then
+// stage addresses the spectrum through the digit reversal.  M = 2^a 16^b, a < 4: an optional leading pass of radix 2, 4 or 8, then
 // radix-16 passes with one 16-point transform per thread held in registers (four layers of radix 2, the twiddles worked
 // into the butterflies); the first pass forward and the last one back need no LDS on their outer side.  The LDS
 // array carries one complex of padding per 16, which makes the stride-1 and stride-16 passes conflict-free.
@@ -28,6 +28,11 @@ __device__ __forceinline__ cplx mk(float x, float y) { cplx c; c.x = x; c.y = y;
 __device__ __forceinline__ cplx cadd(cplx a, cplx b) { return mk(a.x + b.x, a.y + b.y); }
 __device__ __forceinline__ cplx csub(cplx a, cplx b) { return mk(a.x - b.x, a.y - b.y); }
 __device__ __forceinline__ cplx cmul(cplx a, cplx b) { return mk(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x); }
+// s + a b
+__device__ __forceinline__ cplx cfma(cplx a, cplx b, cplx s)
+{
+    return mk(fmaf(-a.y, b.y, fmaf(a.x, b.x, s.x)), fmaf(a.y, b.x, fmaf(a.x, b.y, s.y)));
+}
 __device__ __forceinline__ cplx conj(cplx a) { return mk(a.x, -a.y); }
 __device__ __forceinline__ cplx mul_neg_i(cplx a) { return mk(a.y, -a.x); }   // a * (-i)
 __device__ __forceinline__ cplx mul_pos_i(cplx a) { return mk(-a.y, a.x); }   // a * (+i)
@@ -53,16 +58,19 @@ template <bool INV> __device__ __forceinline__ void bfly1_q(cplx& a, cplx& b)
     a = cadd(a, r);
 }
 
+// w^2 of a w on the unit circle and not far from 1
+__device__ __forceinline__ cplx unit_square(cplx w) { const float y2 = 2.f * w.y; return mk(fmaf(-y2, w.y, 1.f), y2 * w.x); }
+
 // 16-point DFT in registers with the twiddles of its INPUTS taken along:  X_p = sum_q x_q (w w16^p)^q, w16 =
 // exp(-2 pi i / 16) (INV: conjugate).  In: v[q] = x_q.  Out: X_p sits in slot rev4(p) (the four bits of p reversed).
-// w2 = w^2.  Radix 2 over q: 16 values of a polynomial, and level by level only the powers w^8, w^4, w^2 and w of the base are met,
-// times eighth and sixteenth roots: eight distinct complex twiddles (25 instructions from w, w2) for 32 butterflies of six
+// w2 = w^2, w4 = w^4, w8 = w^8.  Radix 2 over q: 16 values of a polynomial, and level by level only the powers w^8, w^4, w^2 and w of the base are met,
+// times eighth and sixteenth roots: eight distinct complex twiddles (21 instructions from those) for 32 butterflies of six
 // instructions, 220 in all, where a plain 16-point transform with fifteen twiddles in front of or behind it takes 290
 // (its chain of powers 56, its products 60).  UNIT: w = 1 (148 instructions).  HALF_IN: x_8 .. x_15 are zero (not read).
 // HALF_OUT: only X_0 .. X_7 are wanted.
 __host__ __device__ constexpr int rev4(int p) { return ((p & 1) << 3) | ((p & 2) << 1) | ((p & 4) >> 1) | ((p & 8) >> 3); }
 template <bool INV, bool UNIT, bool HALF_IN = false, bool HALF_OUT = false>
-__device__ __forceinline__ void dft16(cplx (&v)[16], cplx w, cplx w2)
+__device__ __forceinline__ void dft16(cplx (&v)[16], cplx w, cplx w2, cplx w4, cplx w8)
 {
     constexpr float C1 = 0.92387953251128674f, S1 = 0.38268343236508977f, R2 = 0.70710678118654752f;
     constexpr float SG = INV ? 1.f : -1.f;
@@ -77,9 +85,7 @@ __device__ __forceinline__ void dft16(cplx (&v)[16], cplx w, cplx w2)
 #pragma unroll
         for (int q = 0; q < 4; ++q) { bfly1(v[q], v[q + 4]); bfly1_q<INV>(v[q + 8], v[q + 12]); }
     } else {
-        const cplx w4 = mk(fmaf(w2.x, w2.x, -w2.y * w2.y), 2.f * w2.x * w2.y);
         if (!HALF_IN) {
-            const cplx w8 = mk(fmaf(w4.x, w4.x, -w4.y * w4.y), 2.f * w4.x * w4.y);
 #pragma unroll
             for (int q = 0; q < 8; ++q) bfly(v[q], v[q + 8], w8.x, w8.y);
         }
@@ -110,32 +116,55 @@ __device__ __forceinline__ void dft16(cplx (&v)[16], cplx w, cplx w2)
 }
 
 __host__ __device__ constexpr int conv_threads(int M) { return M / 16 < 64 ? 64 : M / 16; }
-__host__ __device__ constexpr bool conv_lead4(int M) { return M == 1024 || M == 16384; }
+// radix of the pass that leads where M is no power of 16 (1: none)
+__host__ __device__ constexpr int conv_lead(int M) { return M == 1024 || M == 16384 ? 4 : M == 2048 ? 8 : M == 8192 ? 2 : 1; }
 __host__ __device__ constexpr int conv_pad(int i) { return i + (i >> 4); }
 
-// Place of W^e in the table of powers: the passes walk it by 1, by 4, by 16 or (M = 16384) by 64, and sixteen neighbours
-// of any such walk lie in sixteen different places of the 256 bytes that the banks span.
+// 2048 and 8192 points: twiddles that cost no more and are nearer what they should be (see twiddle, PairTwiddle).  A sequence fills
+// more of a smaller transform, so more of its rounding errors lies on the steps that are wanted; this makes up for it.  The
+// others stay as they were: the gradient kernel of 4096 points then spilled more, 420 -> 480 us at 32 x 512 x 4096.
+__host__ __device__ constexpr bool conv_fine(int M) { return M == 2048 || M == 8192; }
+
+// Place of W^e in the table of powers: the passes walk it by 1, by 4, by 8, by 16, (M = 8192) by 32 or (M = 16384) by 64, and
+// sixteen neighbours of any such walk lie in sixteen different places of the 256 bytes that the banks span.  (M = 2048: with no
+// room in between, see ConvLds.)
 template <int M>
-__host__ __device__ constexpr int power_pos(int e) { return e + (e >> 4) + (M == 16384 ? e >> 6 : 0); }
+__host__ __device__ constexpr int power_pos(int e)
+{
+    return M == 2048 ? e ^ (e >> 4) : e + (e >> 4) + (M == 16384 ? e >> 6 : M == 8192 ? e >> 5 : 0);
+}
 
 template <int M>
 struct ConvLds {
-    // complex slots; 16 more than the transform needs, so that two real sequences with 32 steps of margin each fit
-    static constexpr int DATA = conv_pad(M) + 16;
-    // + twiddles: the powers W^e that the passes ask for (e < M / 16), each with its square
-    static constexpr int BYTES = DATA * 8 + (power_pos<M>(M / 16 - 1) + 1) * 16;
+    // complex slots; at the smallest size 16 more than the transform needs, so that two real sequences with 32 steps of margin
+    // each fit (others have that room in their padding; it is not used only where the 128 bytes count)
+    static constexpr int DATA = conv_pad(M) + (M == 2048 ? 0 : 16);
+    // + twiddles: the powers W^e that the passes ask for (e < M / 16), each with its square or fourth power
+    // (M = 2048: 20 KB with the eighth powers, see twiddle: just so much that the forward kernel's eight workgroups fit a unit; with
+    // seven, 32 x 512 x 2048 took 119 us, so 103)
+    static constexpr int POWERS = M == 2048 ? M / 16 : power_pos<M>(M / 16 - 1) + 1;
+    static constexpr int BYTES = DATA * 8 + POWERS * (M == 2048 ? 24 : 16);
 };
 
-// w = exp(-2 pi i e / M) (INV: its conjugate) and w2 = w^2, e < M / 16.  The square comes from the table as well: dft16
-// squares on to w^8, and every squaring doubles the error it is handed.  Where w was multiplied up from two tables of 128
+// w = exp(-2 pi i e / M) (INV: its conjugate), w2 = w^2 and w4 = w^4, e < M / 16.  One of the powers comes from the table as well:
+// dft16 squares on to w^8, and every squaring doubles the error it is handed.  Where w was multiplied up from two tables of 128
 // and squared here (M = 16384), the gradient of 128 channels x 16384 steps, fp32, was 6.3 .. 7.7e-7 from 64 bits; with the
-// table 4.0 .. 4.7e-7, and 4 x 256 channels take 209 us instead of 250.
+// square from the table 4.0 .. 4.7e-7, and 4 x 256 channels take 209 us instead of 250.  With the fourth power from it, and the
+// square by a formula that holds on the unit circle only (conv_fine), the last square is one step from the table and not two:
+// 64 channels x 6001 steps 4.2e-7 -> 3.4e-7.  M = 2048: the eighth power, too (64 x 2048 steps 3.3e-7 -> 3.1e-7, what it was in a
+// transform of 4096 points).
 template <int M, bool INV>
-__device__ __forceinline__ void twiddle(const float4* tw, int e, cplx& w, cplx& w2)
+__device__ __forceinline__ void twiddle(const float4* tw, int e, cplx& w, cplx& w2, cplx& w4, cplx& w8)
 {
     const float4 t = tw[power_pos<M>(e)];
     w = mk(t.x, INV ? -t.y : t.y);
-    w2 = mk(t.z, INV ? -t.w : t.w);
+    const cplx p = mk(t.z, INV ? -t.w : t.w);
+    w2 = conv_fine(M) ? unit_square(w) : p;
+    w4 = conv_fine(M) ? p : mk(fmaf(p.x, p.x, -p.y * p.y), 2.f * p.x * p.y);
+    if (M == 2048) {
+        const float2 q = reinterpret_cast<const float2*>(tw + ConvLds<M>::POWERS)[power_pos<M>(e)];
+        w8 = mk(q.x, INV ? -q.y : q.y);
+    } else w8 = mk(fmaf(w4.x, w4.x, -w4.y * w4.y), 2.f * w4.x * w4.y);
 }
 
 // Storage position of spectrum bin k (0 <= k < M) after the forward passes.
@@ -143,7 +172,8 @@ template <int M>
 __device__ __forceinline__ int spectrum_pos(int k)
 {
     int pos = 0, span = M;
-    if (conv_lead4(M)) { span /= 4; pos += (k & 3) * span; k >>= 2; }
+    constexpr int R = conv_lead(M);
+    if (R > 1) { span /= R; pos += (k & (R - 1)) * span; k >>= R == 2 ? 1 : R == 4 ? 2 : 3; }
 #pragma unroll
     for (int s = span; s > 1; s /= 16) { pos += (k & 15) * (s / 16); k >>= 4; }
     return pos;
@@ -154,11 +184,11 @@ __device__ __forceinline__ int spectrum_pos(int k)
 template <int M, int N16>
 __device__ __forceinline__ int block_bin(int block)
 {
-    constexpr int NB = M / N16;                    // blocks: 1, 4, 16, 64, 256 or 1024
-    if (NB <= 16) return block;                    // one digit
-    if (NB == 64) return (block >> 4) | (block & 15) << 2;
-    if (NB == 256) return (block >> 4) | (block & 15) << 4;
-    return (block >> 8) | (block & 0xf0) >> 2 | (block & 15) << 6;
+    constexpr int NB = M / N16, R = conv_lead(M) > 1 ? conv_lead(M) : 16;      // blocks; what the first digit counts to
+    if (NB <= 16) return block;                                                // one digit
+    if (NB == 16 * R) return (block >> 4) + (block & 15) * R;
+    static_assert(NB <= 16 || NB == 16 * R || NB == 256 * R, "");
+    return (block >> 8) + ((block >> 4) & 15) * R + (block & 15) * (16 * R);
 }
 
 // One radix-16 pass over sub-transforms of length N16 (stride N16 / 16), forward or inverse, 16-point transforms
@@ -178,11 +208,11 @@ __device__ __forceinline__ void pass16(cplx* a, const float4* tw, int tid)
         const int block = g / S, j = g - block * S;
         cplx* p0 = a + (S >= 16 ? conv_pad(block * N16 + j) : 17 * g);
         cplx v[16];
-        cplx w = mk(1.f, 0.f), w2 = w;
-        if (!UNIT) twiddle<M, INV>(tw, INV ? j * (M / N16) : block_bin<M, N16>(block) * S, w, w2);
+        cplx w = mk(1.f, 0.f), w2 = w, w4 = w, w8 = w;
+        if (!UNIT) twiddle<M, INV>(tw, INV ? j * (M / N16) : block_bin<M, N16>(block) * S, w, w2, w4, w8);
 #pragma unroll
         for (int q = 0; q < (HALF && !INV ? 8 : 16); ++q) v[q] = p0[q * STEP];
-        dft16<INV, UNIT, HALF && !INV, HALF && INV>(v, w, w2);
+        dft16<INV, UNIT, HALF && !INV, HALF && INV>(v, w, w2, w4, w8);
 #pragma unroll
         for (int p = 0; p < (HALF && INV ? 8 : 16); ++p) p0[p * STEP] = v[rev4(p)];
     }
@@ -196,7 +226,7 @@ __device__ __forceinline__ void pass16(cplx* a, const float4* tw, int tid)
 template <int M, int T, bool FULL = false>
 __device__ __forceinline__ void fft_forward(const cplx (&z)[FULL ? M / T : M / T / 2], cplx* a, const float4* tw, int tid)
 {
-    static_assert(!FULL || conv_lead4(M), "the leading radix-4 pass only");
+    static_assert(!FULL || conv_lead(M) == 4, "the leading radix-4 pass only");
     if constexpr (M == 256) {               // (16 of a wave's threads work in a pass: the input is dealt out again)
 #pragma unroll
         for (int i = 0; i < M / T / 2; ++i) a[conv_pad(tid + T * i)] = z[i];
@@ -204,7 +234,48 @@ __device__ __forceinline__ void fft_forward(const cplx (&z)[FULL ? M / T : M / T
         pass16<M, T, 256, false, true>(a, tw, tid);
     } else {
         static_assert(M / T == 16, "sixteen points per thread");
-        if constexpr (conv_lead4(M)) {
+        if constexpr (conv_lead(M) == 2) {
+            // (with its partner zero a point goes into both halves as it is)
+            constexpr int sp = M / 2 + M / 32;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                cplx* p0 = a + conv_pad(tid + T * j);
+                p0[0] = z[j];
+                p0[sp] = z[j];
+            }
+            __syncthreads();
+            pass16<M, T, 4096, false, false>(a, tw, tid);
+            __syncthreads();
+        } else if constexpr (conv_lead(M) == 8) {
+            // x_0 .. x_3 of two columns, x_4 .. x_7 being zero: even bins from x_q, odd ones from x_q w8^q
+            constexpr int s = M / 8, sp = s + s / 16;
+            constexpr float R2 = 0.70710678118654752f;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                cplx* p0 = a + conv_pad(tid + T * j);
+                cplx v[4], u[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) v[q] = z[2 * q + j];
+                u[0] = v[0];
+                u[1] = cmul(v[1], mk(R2, -R2));
+                u[2] = mul_neg_i(v[2]);
+                u[3] = cmul(v[3], mk(-R2, -R2));
+                bfly1(v[0], v[2]);
+                bfly1(v[1], v[3]);
+                bfly1(u[0], u[2]);
+                bfly1(u[1], u[3]);
+                const cplx r = mul_neg_i(v[3]), t = mul_neg_i(u[3]);
+                p0[0] = cadd(v[0], v[1]);
+                p0[sp] = cadd(u[0], u[1]);
+                p0[2 * sp] = cadd(v[2], r);
+                p0[3 * sp] = cadd(u[2], t);
+                p0[4 * sp] = csub(v[0], v[1]);
+                p0[5 * sp] = csub(u[0], u[1]);
+                p0[6 * sp] = csub(v[2], r);
+                p0[7 * sp] = csub(u[2], t);
+            }
+            __syncthreads();
+        } else if constexpr (conv_lead(M) == 4) {
             constexpr int s = M / 4, sp = s + s / 16;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
@@ -234,7 +305,7 @@ __device__ __forceinline__ void fft_forward(const cplx (&z)[FULL ? M / T : M / T
             cplx v[16];
 #pragma unroll
             for (int q = 0; q < 8; ++q) v[q] = z[q];
-            dft16<false, true, true>(v, mk(1.f, 0.f), mk(1.f, 0.f));
+            dft16<false, true, true>(v, mk(1.f, 0.f), mk(1.f, 0.f), mk(1.f, 0.f), mk(1.f, 0.f));
             cplx* p0 = a + conv_pad(tid);
 #pragma unroll
             for (int p = 0; p < 16; ++p) p0[p * STEP] = v[rev4(p)];
@@ -259,16 +330,58 @@ __device__ __forceinline__ void fft_inverse(cplx* a, cplx (&y)[M / T / 2], const
     } else {
         pass16<M, T, 256, true, false>(a, tw, tid);
         __syncthreads();
-        if constexpr (conv_lead4(M)) {
+        if constexpr (conv_lead(M) == 2) {
+            pass16<M, T, 4096, true, false>(a, tw, tid);
+            __syncthreads();
+            // y = x_0 + conj(W^(tid + T j)) x_1: W^T is a sixteenth root
+            constexpr int sp = M / 2 + M / 32;
+            constexpr float C1 = 0.92387953251128674f, S1 = 0.38268343236508977f, R2 = 0.70710678118654752f;
+            constexpr float CX[8] = {1.f, C1, R2, S1, 0.f, -S1, -R2, -C1}, CY[8] = {0.f, S1, R2, C1, 1.f, C1, R2, S1};
+            cplx t, t2, t4, t8;
+            twiddle<M, true>(tw, tid, t, t2, t4, t8);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const cplx* p0 = a + conv_pad(tid + T * j);
+                const cplx c = j == 0 ? t : j == 4 ? mul_pos_i(t) : cmul(t, mk(CX[j], CY[j]));
+                y[j] = cfma(c, p0[sp], p0[0]);
+            }
+        } else if constexpr (conv_lead(M) == 8) {
+            // y_p = sum_q x_q t^q conj(w8)^(p q), p < 4, t = conj(W^(tid + T j)), W^T a sixteenth root: even and odd q apart
+            constexpr int s = M / 8, sp = s + s / 16;
+            constexpr float C1 = 0.92387953251128674f, S1 = 0.38268343236508977f, R2 = 0.70710678118654752f;
+            cplx t, t2, t4, t8;
+            twiddle<M, true>(tw, tid, t, t2, t4, t8);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const cplx* p0 = a + conv_pad(tid + T * j);
+                if (j == 1) { t = cmul(t, mk(C1, S1)); t2 = cmul(t2, mk(R2, R2)); t4 = mul_pos_i(t4); }
+                cplx v[4], u[4];
+#pragma unroll
+                for (int q = 0; q < 4; ++q) { v[q] = p0[2 * q * sp]; u[q] = p0[(2 * q + 1) * sp]; }
+                bfly(v[0], v[2], t4.x, t4.y);
+                bfly(v[1], v[3], t4.x, t4.y);
+                bfly(u[0], u[2], t4.x, t4.y);
+                bfly(u[1], u[3], t4.x, t4.y);
+                bfly(v[0], v[1], t2.x, t2.y);
+                bfly_q<true>(v[2], v[3], t2.x, t2.y);
+                bfly(u[0], u[1], t2.x, t2.y);
+                bfly_q<true>(u[2], u[3], t2.x, t2.y);
+                // (slots 0, 2, 1, 3 now hold p = 0, 1, 2, 3)
+                y[j] = cfma(t, u[0], v[0]);
+                y[j + 2] = cfma(cmul(t, mk(R2, R2)), u[2], v[2]);
+                y[j + 4] = cfma(mul_pos_i(t), u[1], v[1]);
+                y[j + 6] = cfma(cmul(t, mk(-R2, R2)), u[3], v[3]);
+            }
+        } else if constexpr (conv_lead(M) == 4) {
             if constexpr (M == 16384) { pass16<M, T, 4096, true, false>(a, tw, tid); __syncthreads(); }
             constexpr int s = M / 4, sp = s + s / 16;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const cplx* p0 = a + conv_pad(tid + T * j);
-                cplx t1, t2;
+                cplx t1, t2, t4, t8;
                 // W^(tid + j M/16): W^tid times sixteenth roots
                 constexpr float C1 = 0.92387953251128674f, S1 = 0.38268343236508977f, R2 = 0.70710678118654752f;
-                twiddle<M, true>(tw, tid, t1, t2);
+                twiddle<M, true>(tw, tid, t1, t2, t4, t8);
                 t1 = j == 0 ? t1 : cmul(t1, j == 1 ? mk(C1, S1) : j == 2 ? mk(R2, R2) : mk(S1, C1));
                 t2 = j == 0 ? t2 : j == 2 ? mul_pos_i(t2) : cmul(t2, j == 1 ? mk(R2, R2) : mk(-R2, R2));
                 const cplx t3 = cmul(t2, t1);
@@ -284,9 +397,9 @@ __device__ __forceinline__ void fft_inverse(cplx* a, cplx (&y)[M / T / 2], const
             cplx v[16];
 #pragma unroll
             for (int q = 0; q < 16; ++q) v[q] = p0[q * STEP];
-            cplx w, w2;
-            twiddle<M, true>(tw, tid, w, w2);
-            dft16<true, false, false, true>(v, w, w2);
+            cplx w, w2, w4, w8;
+            twiddle<M, true>(tw, tid, w, w2, w4, w8);
+            dft16<true, false, false, true>(v, w, w2, w4, w8);
 #pragma unroll
             for (int p = 0; p < 8; ++p) y[p] = v[rev4(p)];
         }
@@ -402,8 +515,12 @@ __device__ __forceinline__ void build_tables(float4* tw, int tid)
     float s, c, s2, c2;
     for (int e = tid; e < M / 16; e += T) {
         sincospif(-2.0f * (float)e / (float)M, &s, &c);
-        sincospif(-4.0f * (float)e / (float)M, &s2, &c2);
+        sincospif((conv_fine(M) ? -8.0f : -4.0f) * (float)e / (float)M, &s2, &c2);
         tw[power_pos<M>(e)] = make_float4(c, s, c2, s2);
+        if (M == 2048) {
+            sincospif(-16.0f * (float)e / (float)M, &s, &c);
+            reinterpret_cast<float2*>(tw + ConvLds<M>::POWERS)[power_pos<M>(e)] = make_float2(c, s);
+        }
     }
 }
 
@@ -429,7 +546,7 @@ template <int M, int T>
 struct PairPos {
     static constexpr int NP = M / 2 / T;                  // pairs per thread: 8 (2 at M = 256)
     static constexpr bool LIN = NP == 8;
-    static constexpr int SA = M == 1024 ? 272 : 1088;     // padded distance of i and i + 1; 17 of i and i + 4
+    static constexpr int SA = M == 1024 ? 272 : M == 2048 ? 544 : 1088;     // padded distance of i and i + 1; 17 of i and i + 4
     int a1[LIN ? 1 : NP], a2[LIN ? 3 : NP];
     static __device__ __forceinline__ int bin_pos(int k) { return conv_pad(spectrum_pos<M>(k & (M - 1))); }
     __device__ __forceinline__ PairPos(int tid)
@@ -457,13 +574,22 @@ struct PairPos {
 };
 
 // W_2M^k = exp(-i pi k / M) for the bins a thread meets when it walks its pairs: k = k(0) + (T/64) i, one sincospi per
-// thread and one rotation per pair, by exp(-i pi / 1024) (M = 256: exp(-i pi / 256)).
+// thread and one rotation per pair, by exp(-i pi / 1024) (M = 256: exp(-i pi / 256)); conv_fine: from the first each time.
 template <int M, int T>
 struct PairTwiddle {
     static_assert(M / T == 16 || (M == 256 && T == 64), "the rotation below");
     cplx first;
     static constexpr cplx step = M == 256 ? cplx{0.99992470183914454f, -0.012271538285719925f}
                                           : cplx{0.99999529380957617f, -0.0030679567629659763f};
+    // of pair i + 1, w being that of pair i
+    __device__ __forceinline__ cplx after(int i, cplx w) const
+    {
+        constexpr float CX[8] = {0.99999529380957619f, 0.99998117528260111f, 0.99995764455196390f, 0.99992470183914450f,
+                                 0.99988234745421256f, 0.99983058179582340f, 0.99976940535121528f, 0.99969881869620425f};
+        constexpr float CY[8] = {-0.00306795676296598f, -0.00613588464915448f, -0.00920375478205982f, -0.01227153828571993f,
+                                 -0.01533920628498810f, -0.01840672990580482f, -0.02147408027546951f, -0.02454122852291229f};
+        return conv_fine(M) ? cmul(first, mk(CX[i & 7], CY[i & 7])) : cmul(w, step);
+    }
     __device__ __forceinline__ PairTwiddle(int tid)
     {
         float s, c;
@@ -488,11 +614,7 @@ __device__ __forceinline__ void pair_rot(cplx A, cplx B, cplx w, cplx& r, cplx& 
     r = mk(fmaf(w.y, A.x, -w.x * B.y), fmaf(w.y, A.y, w.x * B.x));
     q = mk(fmaf(-w.y, B.x, w.x * A.y), fmaf(-w.y, B.y, -w.x * A.x));
 }
-// s + a b and s + a conj(b)
-__device__ __forceinline__ cplx cfma(cplx a, cplx b, cplx s)
-{
-    return mk(fmaf(-a.y, b.y, fmaf(a.x, b.x, s.x)), fmaf(a.y, b.x, fmaf(a.x, b.y, s.y)));
-}
+// s + a conj(b)
 __device__ __forceinline__ cplx cfmac(cplx a, cplx b, cplx s)
 {
     return mk(fmaf(a.y, b.y, fmaf(a.x, b.x, s.x)), fmaf(a.y, b.x, fmaf(-a.x, b.y, s.y)));
@@ -665,6 +787,7 @@ __device__ __forceinline__ float quad_sum(float v)
 __device__ __forceinline__ int fresh(int tid) { asm volatile("" : "+v"(tid)); return tid; }
 
 // Kernel spectrum of one channel: the entries of the M/2 pairs in pair order (the buffer has room for one more).
+// PAIRS: not the entries where they have fewer points than the copy (a launch of their own then, see conv_points).
 // MX (M = 16384): also the copy that the matrix-core kernels read, the bins at exp(-2 pi i (k + 1/4) / M) (a transform of its
 // own, of the sequence turned by exp(-2 pi i n / (4 M))), divided by 4 |k|_1, as half-precision (re, im) words, stored where
 // the lane that holds bin k = k1 + 16 k2 + 512 k3 will look: word ((k1 * 4 + a) * 64 + lane) * 4 + b with lane = k2 + 32 h and
@@ -674,7 +797,7 @@ __device__ __forceinline__ int fresh(int tid) { asm volatile("" : "+v"(tid)); re
 // front of the first one's stores; a single channel 16, with the tables on its side 17).  Without the copy 768 channels take 42 us;
 // fp32 I/O, which does not read it, pays for it all the same, because this call does not know what the spectrum is for (4 % of a
 // fp32 training step of 2 x 768 x 16384).
-template <int M, bool MX>
+template <int M, bool MX, bool PAIRS = true>
 __global__ __launch_bounds__(conv_threads(M)) void longconv_spectrum_kernel(const float* __restrict__ k,
                                                                            float4* __restrict__ Kf,
                                                                            uint4* __restrict__ Ks,
@@ -713,8 +836,10 @@ __global__ __launch_bounds__(conv_threads(M)) void longconv_spectrum_kernel(cons
         if ((tid & 63) == 0) red[tid >> 6] = n1;
     }
     __syncthreads();
-    fft_forward<M, T>(z, a, tw, tid);
-    __syncthreads();
+    if constexpr (PAIRS) {
+        fft_forward<M, T>(z, a, tw, tid);
+        __syncthreads();
+    }
     float inv = 0.f;
     if constexpr (MX) {
         float n1 = 0.f;
@@ -740,14 +865,16 @@ __global__ __launch_bounds__(conv_threads(M)) void longconv_spectrum_kernel(cons
             x2[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(row, 4 * (tid + T * i), 0, 0));
         __builtin_amdgcn_sched_barrier(0);
     }
-    float4* out = Kf + c * (long)(M / 2 + 1);
-    const PairPos<M, T> pos(tid);
-    const PairTwiddle<M, T> pw(tid);
-    cplx w = pw.first;
+    if constexpr (PAIRS) {
+        float4* out = Kf + c * (long)(M / 2 + 1);
+        const PairPos<M, T> pos(tid);
+        const PairTwiddle<M, T> pw(tid);
+        cplx w = pw.first;
 #pragma unroll
-    for (int i = 0; i < NP; ++i) {
-        out[tid + T * i] = pair_kernel(a[pos.first(i)], conj(a[pos.second(i)]), w, i == 0 && tid == 0);
-        w = cmul(w, PairTwiddle<M, T>::step);
+        for (int i = 0; i < NP; ++i) {
+            out[tid + T * i] = pair_kernel(a[pos.first(i)], conj(a[pos.second(i)]), w, i == 0 && tid == 0);
+            w = pw.after(i, w);
+        }
     }
     if constexpr (MX) {
         // steps tid + T i this time, turned by exp(-2 pi i (tid + T i) / (4 M)), T i / (4 M) = i / 64
@@ -826,7 +953,7 @@ void shortlong_conv_kernel(const IN* __restrict__ X,
             pair_mul<false>(A, B, w, kq[i], i == 0 && tid == 0);
             p1 = A;
             p2 = conj(B);
-            w = cmul(w, PairTwiddle<M, T>::step);
+            w = pw.after(i, w);
         }
         if (bc + gridDim.x < total) xr.load(X + (bc + gridDim.x) * (long)L, L, tp);     // the next sequence, in flight
         __syncthreads();
@@ -858,7 +985,7 @@ void shortlong_conv_kernel(const IN* __restrict__ X,
 constexpr int kFuseTaps = kConvFuseTaps, kShortMaxTaps = kConvMaxTaps;
 
 template <int M, typename IO, typename DVT, bool SPLIT, bool SHORT>
-__global__ __launch_bounds__(conv_threads(M)) __attribute__((amdgpu_waves_per_eu(M == 256 || M == 16384 ? 4 : sizeof(IO) == 2 ? 3 : 2)))
+__global__ __launch_bounds__(conv_threads(M)) __attribute__((amdgpu_waves_per_eu(M == 256 || M >= 8192 ? 4 : sizeof(IO) == 2 ? 3 : 2)))
 void longconv_bwd_kernel(const IO* __restrict__ X,
                                                                       const float* __restrict__ w_short, int m,
                                                                       const float4* __restrict__ Kf,
@@ -868,9 +995,9 @@ void longconv_bwd_kernel(const IO* __restrict__ X,
                                                                       int B, int d, int L)
 {
     constexpr int T = conv_threads(M), NP = PairPos<M, T>::NP, HELD = M / T / 2;
-    // At the largest size 1024 threads share the register file: the running sums then live in a scratch array in
+    // At the two largest sizes sixteen waves share the register file: the running sums then live in a scratch array in
     // memory ([d][M/2 + 1] pairs; every thread only ever touches its own pairs, between uses they sit in the caches).
-    constexpr bool ACC_MEM = M >= 16384;
+    constexpr bool ACC_MEM = M >= 8192;
     float4* accm = (ACC_MEM || SPLIT) ? acc_ws + ((long)blockIdx.y * d + blockIdx.x) * (M / 2 + 1) : nullptr;
     __shared__ __attribute__((aligned(16))) unsigned char lds[ConvLds<M>::BYTES];
     cplx* a = reinterpret_cast<cplx*>(lds);
@@ -936,7 +1063,7 @@ void longconv_bwd_kernel(const IO* __restrict__ X,
                 pair_mul<true>(A, B, w, kq[i % KU], i == 0 && tid == 0);
                 a[pos.first(i)] = A;
                 a[pos.second(i)] = conj(B);
-                w = cmul(w, PairTwiddle<M, T>::step);
+                w = pw.after(i, w);
                 __builtin_amdgcn_sched_barrier(0);   // one pair at a time: the unrolled pairs must not pile up in registers
             }
         }
@@ -1056,7 +1183,7 @@ void longconv_bwd_kernel(const IO* __restrict__ X,
                     } else {
                         pair_acc(sums[i], GA[i], GB[i], A[u], Bc[u], w, self);
                     }
-                    w = cmul(w, PairTwiddle<M, T>::step);
+                    w = pw.after(i, w);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -1096,7 +1223,7 @@ void longconv_bwd_kernel(const IO* __restrict__ X,
             pair_pack(t, w, i == 0 && tid == 0, A, Bc);
             a[pos.first(i)] = A;
             a[pos.second(i)] = conj(Bc);
-            w = cmul(w, PairTwiddle<M, T>::step);
+            w = pw.after(i, w);
         }
     }
     __syncthreads();
@@ -1433,7 +1560,7 @@ __global__ __launch_bounds__(kBlkT) void longconv_spectrum_blocked_kernel(const 
         for (int i = 0; i < NP; ++i) {
             const float4 v = pair_kernel(a[pos.first(i)], conj(a[pos.second(i)]), w, i == 0 && tid == 0);
             sum[i].x += sg * v.x; sum[i].y += sg * v.y; sum[i].z += sg * v.z; sum[i].w += sg * v.w;
-            w = cmul(w, PairTwiddle<M, T>::step);
+            w = pw.after(i, w);
         }
     }
     float4* out = Gf + (c * nb + mb) * (long)(M / 2 + 1);
@@ -1496,7 +1623,7 @@ __global__ __launch_bounds__(kBlkT) void longconv_blocked_kernel(const IN* __res
                 pair_mul<CORR>(A, B, w, kq[i], i == 0 && tid == 0);
                 accA[i] = cadd(accA[i], A);
                 accB[i] = cadd(accB[i], B);
-                w = cmul(w, PairTwiddle<M, T>::step);
+                w = pw.after(i, w);
                 __builtin_amdgcn_sched_barrier(0);   // one pair at a time: the unrolled pairs must not pile up in registers
             }
         }
@@ -1572,7 +1699,7 @@ __global__ __launch_bounds__(kBlkT) void longconv_dk_blocked_kernel(const IO* __
             if (pr > 0) t = accm[tid + T * q];
             pair_acc(t, GA[q], GB[q], a[pos.first(q)], conj(a[pos.second(q)]), w, q == 0 && tid == 0);
             accm[tid + T * q] = t;
-            w = cmul(w, PairTwiddle<M, T>::step);
+            w = pw.after(i, w);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
@@ -1607,12 +1734,21 @@ __global__ __launch_bounds__(kBlkT) void longconv_dk_blocked_finish_kernel(const
         pair_pack(t, w, i == 0 && tid == 0, A, B);
         a[pos.first(i)] = A;
         a[pos.second(i)] = conj(B);
-        w = cmul(w, PairTwiddle<M, T>::step);
+        w = pw.after(i, w);
     }
     __syncthreads();
     cplx z[M / T / 2];
     fft_inverse<M, T>(a, z, tw, tid);
     store_steps<M, T, float>(z, dk + (long)c * L + (long)mb * M, min(M, L - mb * M), (L & 1) == 0, 1.0f / (float)M, tid);
+}
+
+// Between the powers of four from 1024 on the size in the middle as well: half the work for half of all lengths.  Training steps, us:
+// 32 x 512 x 2048, bf16, in 4096 points 622, in 2048 312; 16 x 256 x 1874 195, 104; 8 x 768 x 1500, fp32, 291, 162; 10 x 512 x 4591,
+// fp32, in 16384 points 1205, in 8192 715; 2 x 128 x 4652, bf16, 94, 68; 4 x 768 x 8192, fp32, 777, 470.  (512 points would have 32
+// threads' worth of 16-point transforms, and cost a wave what 1024 do.)
+int conv_points(int L)
+{
+    return L > 1024 && L <= 2048 ? 2048 : L > 4096 && L <= 8192 ? 8192 : conv_fft_size(L);
 }
 
 int conv_fft_size(int L)
@@ -1626,7 +1762,7 @@ int conv_fft_size(int L)
 
 hipError_t launch_longconv_spectrum(const float* k, void* Kf, int d, int L, hipStream_t st)
 {
-    const int M = conv_fft_size(L);
+    const int M = conv_points(L);
     ProfScope prof(KID_CONV_SPECTRUM, st);
     float4* out = (float4*)Kf;
     if (const int nb = conv_blocks(L)) {
@@ -1636,14 +1772,22 @@ hipError_t launch_longconv_spectrum(const float* k, void* Kf, int d, int L, hipS
     uint4* mx = (uint4*)((char*)Kf + conv_pairs_bytes(d, L));
     float* scale = (float*)(mx + (size_t)d * (MX_N / 4));
     MxTables* tables = mx_tables(mx, d);
-    const bool copy = M == 16384 && (L & 7) == 0;       // (rows of other lengths never meet the matrix-core kernels)
-    const dim3 grid(d + (copy && d < 256 ? 1 : 0));
-#define CHELA_SPECTRUM(M_, MX_)                                                                                         \
-    hipLaunchKernelGGL((longconv_spectrum_kernel<M_, MX_>), grid, dim3(conv_threads(M_)), 0, st, k, out, mx, scale, tables, d, L)
+    const bool copy = L > 4096 && (L & 7) == 0;       // (rows of other lengths never meet the matrix-core kernels)
+#define CHELA_SPECTRUM(M_, ...)                                                                                         \
+    hipLaunchKernelGGL((longconv_spectrum_kernel<M_, __VA_ARGS__>), grid, dim3(conv_threads(M_)), 0, st, k, out, mx, scale, tables, d, L)
+    if (copy && M == 8192) {
+        const dim3 grid(d + (d < 256 ? 1 : 0));
+        CHELA_SPECTRUM(16384, true, false);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    const dim3 grid(d + (copy && M == 16384 && d < 256 ? 1 : 0));
     switch (M) {
         case 256: CHELA_SPECTRUM(256, false); break;
         case 1024: CHELA_SPECTRUM(1024, false); break;
+        case 2048: CHELA_SPECTRUM(2048, false); break;
         case 4096: CHELA_SPECTRUM(4096, false); break;
+        case 8192: CHELA_SPECTRUM(8192, false); break;
         case 16384:
             if (copy) CHELA_SPECTRUM(16384, true);
             else CHELA_SPECTRUM(16384, false);
@@ -1685,7 +1829,7 @@ template <typename IN, typename OUT>
 static hipError_t conv_dispatch(const IN* X, const float* w, int m, const float4* Kf, OUT* Y, long BD, int d, int L,
                                 hipStream_t st)
 {
-    const int M = conv_fft_size(L);
+    const int M = conv_points(L);
     ProfScope prof(KID_CONV_FWD, st);
     if (conv_blocks(L)) return conv_blocked_launch<IN, OUT, false>(X, w, m, Kf, Y, BD, d, L, st);
     // no more workgroups than are resident at once, each with an equal share of the sequences
@@ -1698,7 +1842,7 @@ static hipError_t conv_dispatch(const IN* X, const float* w, int m, const float4
                            L, BD);                                                                                      \
     } break;
     switch (M) {
-        CHELA_CONV_FWD(256) CHELA_CONV_FWD(1024) CHELA_CONV_FWD(4096) CHELA_CONV_FWD(16384)
+        CHELA_CONV_FWD(256) CHELA_CONV_FWD(1024) CHELA_CONV_FWD(2048) CHELA_CONV_FWD(4096) CHELA_CONV_FWD(8192) CHELA_CONV_FWD(16384)
         default: return hipErrorInvalidValue;
     }
 #undef CHELA_CONV_FWD
@@ -1764,7 +1908,7 @@ __global__ __launch_bounds__(conv_threads(M)) void longconv_dk_finish_kernel(con
         pair_pack(t, w, i == 0 && tid == 0, A, B);
         a[pos.first(i)] = A;
         a[pos.second(i)] = conj(B);
-        w = cmul(w, PairTwiddle<M, T>::step);
+        w = pw.after(i, w);
     }
     __syncthreads();
     cplx z[M / T / 2];
@@ -1777,7 +1921,7 @@ template <typename IO, typename DVT, bool SHORT>
 static hipError_t conv_longbwd_dispatch(const IO* X, const float* w, int m, const float4* Kf, const IO* dZ, DVT* dV,
                                         float* dk, float* dw, float4* acc_ws, float* part, int B, int d, int L, hipStream_t st)
 {
-    const int M = conv_fft_size(L), G = conv_bwd_groups(B, d, L);
+    const int M = conv_points(L), G = conv_bwd_groups(B, d, L);
     ProfScope prof(KID_CONV_LONG_BWD, st);
     if (const int nb = conv_blocks(L)) {
         // dV block by block (correlation with the kernel's blocks), then the sums of the kernel gradient per block
@@ -1804,7 +1948,8 @@ static hipError_t conv_longbwd_dispatch(const IO* X, const float* w, int m, cons
                                m, Kf, dZ, dV, dk, acc_ws, dw, B, d, L);                                                 \
         break;
     switch (M) {
-        CHELA_LONGBWD(256, SHORT) CHELA_LONGBWD(1024, SHORT) CHELA_LONGBWD(4096, SHORT) CHELA_LONGBWD(16384, false)
+        CHELA_LONGBWD(256, SHORT) CHELA_LONGBWD(1024, SHORT) CHELA_LONGBWD(2048, SHORT) CHELA_LONGBWD(4096, SHORT)
+        CHELA_LONGBWD(8192, false) CHELA_LONGBWD(16384, false)
         default: return hipErrorInvalidValue;
     }
 #undef CHELA_LONGBWD

@@ -1295,6 +1295,24 @@ def test_shortlong_conv_bwd_bf16_matrix_core_sizes(shape):
     _run_conv_bwd_case(B, d, L, m, "bf16", seed=L + 13, short=short)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [(1, 3, 1025, 9, True), (3, 2, 2047, 16, True), (1, 2, 2048, 1, True), (2, 600, 1500, 3, True),
+                                   (3, 2, 1026, 5, False), (1, 2, 4097, 9, True), (3, 2, 8191, 17, True), (2, 2, 8192, 4, True),
+                                   (2, 300, 5003, 3, True), (1, 2, 6000, 5, False)])
+def test_conv_of_2048_and_8192_points(shape, dtype):
+    # the transforms with a leading pass of radix 8 and of radix 2, forward and gradient: their whole range of lengths, channels of one
+    # workgroup and shared ones, with and without the short stage, rows on and off 16-byte boundaries
+    B, d, L, m, short = shape
+    x = make_conv_inputs(B, d, L, m, L + 61, dtype)
+    dev = _dev(x)
+    spec = binding.chela_longconv_spectrum(dev["k_long"])
+    Z = binding.chela_shortlong_conv_fwd(dev["X"], dev["w_short"] if short else None, spec)
+    torch.cuda.synchronize()
+    Xn, kn = to_f64_numpy(x["X"]), to_f64_numpy(x["k_long"])
+    _check("Z", Z, oracle_conv.short_long_conv(Xn, to_f64_numpy(x["w_short"]), kn) if short else oracle_conv.long_conv(Xn, kn), dtype)
+    _run_conv_bwd_case(B, d, L, m, dtype, seed=L + 61, short=short)
+
+
 def _mx_gradient_launch(B, d, L):
     """(workgroups that share a channel, channels a workgroup walks) of the matrix-core gradient kernel, by its rule."""
     cus = torch.cuda.get_device_properties(0).multi_processor_count
