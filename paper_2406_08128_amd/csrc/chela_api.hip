@@ -82,7 +82,59 @@ static long choose_segments(long BH, long n_chunks, long slots, double g_min, do
     return best;
 }
 
-Plan make_plan(long BH, int N, int dk, int dv, int chunk, int dtype, bool is_bwd, bool stateful, bool can_checkpoint)
+// Calls of up to 2048 chunks in all, bf16 (but the 64 x 64 forward, where nothing is to be gained): the general model counts in chunk steps of a full GPU, all of one length, and takes a
+// pre-pass for three of them.  In a short call a step takes what it takes a workgroup that has its unit to itself, 1.3 us (forward,
+// 64 x 64) to 6 (backward, 128 x 128, whose single segment walks twice: 7.7), and the pre-pass 4 whatever the widths are; under
+// some 11 us (forward) or 13 (backward) the host's launches are the time, and one costs less than two.  So this is a model in us,
+// fitted to the times of 21 shapes per pair of widths over all segment lengths (geometric mean of what the choice costs over the
+// best one, general model -> this one: forward 1.08 -> 1.01, backward 1.14 -> 1.01, worst 1.44 -> 1.05 and 1.99 -> 1.10).
+// On 21 other shapes per pair of widths: backward 1.13 to 1.16 times as fast as with the general model, forward 1.04 to 1.06.
+// Beyond, where memory is the bound, it is no better than the general one.  us, by chunks per segment, the general choice, this
+// one's: backward 8 x 272 tokens, 128 x 128, one 18.5 (taken), two 24.3, all five 36.8 (general); 4 x 8192, 64 x 64, one 48.4
+// (general), two 32.0, three 29.2 (taken), four 27.3; 24 x 900 one 20.1 (general), two 15.0 (taken); forward 16 x 1467, 128 x 128,
+// two 20.7 (taken), four 23.9, six 27.7 (general).
+constexpr long kSmallCallChunks = 2048;
+static long small_bf16_segments(long BH, long n_chunks, int dk, int dv, bool is_bwd, long max_cps)
+{
+    // step of a workgroup alone on its unit and of two that share it; what the pre-pass costs per 512 chunks; step of a single segment
+    struct Widths { double alone, shared, prepass, single; };
+    static constexpr Widths kFwd[3] = {{1.3, 1.7, 0.4, 1.1}, {2.0, 3.0, 0.63, 1.7}, {2.6, 2.6, 2.2, 2.4}};
+    static constexpr Widths kBwd[3] = {{2.5, 3.8, 1.4, 2.9}, {3.9, 6.3, 3.7, 4.9}, {6.0, 6.0, 6.6, 7.7}};
+    const int size = (dk == 128) + (dv == 128);
+    const Widths& w = (is_bwd ? kBwd : kFwd)[size];
+    const double state = (double)(dk * dv) / 4096.0, per_state = is_bwd ? 0.012 : 0.004, per_sum = is_bwd ? 0.4 : 0.32;
+    const double scan = is_bwd ? 6.0 : 5.0, host = is_bwd ? 13.3 : 11.2;
+    const long max_folded = (long)(kMaxFoldedStateBytes / ((size_t)dk * dv * sizeof(float)));
+    auto step = [&](double alone, double shared, double load) {       // load: workgroups per unit
+        if (size == 2) return alone * std::max(1.0, std::ceil(load));          // (one at a time)
+        if (load <= 1.0) return alone;
+        if (load <= 2.0) return alone + (shared - alone) * 0.5 * load;
+        const double full = std::floor(load / 2.0), rest = load / 2.0 - full;
+        return shared * full + (rest > 0.0 ? std::max(alone, std::min(shared, shared * rest / 0.75)) : 0.0);
+    };
+    long best = 1;
+    double best_cost = 1e300;
+    long next = 1;
+    for (long n = 1; n <= n_chunks; n = next) {
+        const long cps = (n_chunks + n - 1) / n;
+        next = cps > 1 ? (n_chunks + cps - 2) / (cps - 1) : n_chunks + 1;      // the fewest segments that are shorter
+        if (n > 1 && max_cps > 0 && cps > max_cps) continue;
+        const double load = (double)(BH * n) / 256.0, steps = (double)cps;
+        double cost;
+        if (n == 1) {
+            cost = 2.0 + steps * step(w.single, w.single * w.shared / w.alone, load);
+        } else {
+            cost = 4.3 + steps * step(w.alone, w.shared, load) + w.prepass * (double)(BH * n_chunks) / 512.0 +
+                   per_state * state * (double)(BH * n) +
+                   (n <= max_folded ? per_sum * state * (double)n : scan + 0.075 * state * (double)n);
+        }
+        cost = std::max(n == 1 ? host - 2.5 : host, cost) + 0.05 * cost;       // (hidden behind the host: the shorter all the same)
+        if (cost < best_cost) { best_cost = cost; best = n; }
+    }
+    return best;
+}
+
+Plan make_plan(long BH, int N, int dk, int dv, int chunk, int dtype, bool is_bwd, bool stateful, bool can_checkpoint, bool general)
 {
     Plan p{};
     p.chunk = chunk;
@@ -95,7 +147,7 @@ Plan make_plan(long BH, int N, int dk, int dv, int chunk, int dtype, bool is_bwd
     const double w_state = (is_bwd ? 0.0019 : 0.0033) * ((double)dk * dv / 4096.0) * (512.0 / (double)slots);
     const long max_walk = kMaxBwdWalkTokens / chunk;
     const bool walk_capped = is_bwd && dtype == CHELA_DTYPE_BF16;
-    const long max_folded = stateful ? 0 : (long)(kMaxFoldedStateBytes / (p.state_elems * sizeof(float)));
+    const long folded = (long)(kMaxFoldedStateBytes / (p.state_elems * sizeof(float))), max_folded = stateful ? 0 : folded;
     // A forward workgroup runs faster with fewer neighbours (the GPU's bandwidth is what it shares); a backward
     // workgroup does not: its chunk step took 5.0 .. 5.1 us with 192, 384 and 480 workgroups on the GPU alike
     // (192 sequences of 16384 tokens: one segment each 1307 us, two 839 us).
@@ -103,8 +155,13 @@ Plan make_plan(long BH, int N, int dk, int dv, int chunk, int dtype, bool is_bwd
     // 4096 tokens: 272 us against 337 us), while the forward is at its best there with one.
     const bool lone_is_slow = is_bwd && dtype == CHELA_DTYPE_BF16;
     const double g_min = (slots > 256 && !lone_is_slow) ? 0.55 : 1.0;
-    long n_seg = choose_segments(BH, n_chunks, slots, g_min, w_state, walk_capped ? max_walk : 0, max_folded,
-                                 lone_is_slow && slots > 256 ? 257 : 256);
+    const bool small = !general && dtype == CHELA_DTYPE_BF16 && chunk == 64 && BH < 256 && BH * n_chunks <= kSmallCallChunks;
+    // (64 x 64 forward: the general model, but with a state carried in the scan is not part of the call any more: 60 x 1000 tokens
+    // 22.2 -> 15.0 us, 12 x 700 16.1 -> 14.0)
+    const long n_seg = small && (is_bwd || dk != 64 || dv != 64)
+        ? small_bf16_segments(BH, n_chunks, dk, dv, is_bwd, walk_capped ? max_walk : 0)
+        : choose_segments(BH, n_chunks, slots, g_min, w_state, walk_capped ? max_walk : 0, small ? folded : max_folded,
+                          lone_is_slow && slots > 256 ? 257 : 256);
     long cps = (n_chunks + n_seg - 1) / n_seg;
     const int forced = env_int("CHELA_SEG_TOKENS", 0);
     if (forced > 0) cps = (forced + chunk - 1) / chunk;
@@ -232,12 +289,12 @@ Plan make_f32_bwd_plan(long BH, int N, int dk, int dv, int chunk, size_t ws_limi
 // Training pair.  The backward's segments are fixed first (its sweep is the dominant kernel); the forward then cuts
 // each of them into save_every equal pieces, as close as the chunk grid allows to the split it would have chosen
 // for itself, so that every backward boundary is also a forward boundary.
-TrainPlans make_train_plans(long BH, int N, int dk, int dv, int chunk)
+TrainPlans make_train_plans(long BH, int N, int dk, int dv, int chunk, bool general)
 {
     TrainPlans t{};
     const int cb = (chunk == 128 && dk == 64 && dv == 64) ? 128 : 64;      // the backward's chunk
-    t.bwd = make_plan(BH, N, dk, dv, cb, CHELA_DTYPE_BF16, true, false);
-    t.fwd = make_plan(BH, N, dk, dv, cb, CHELA_DTYPE_BF16, false, false);   // both calls tile with the same chunk
+    t.bwd = make_plan(BH, N, dk, dv, cb, CHELA_DTYPE_BF16, true, false, false, general);
+    t.fwd = make_plan(BH, N, dk, dv, cb, CHELA_DTYPE_BF16, false, false, false, general);   // both calls tile with the same chunk
     t.save_every = 1;
     if (BH <= 0 || N <= 0) return t;
     // 256 sequences: the plain backward gains from cutting each in two; the pair gains less, since its backward has
@@ -249,6 +306,14 @@ TrainPlans make_train_plans(long BH, int N, int dk, int dv, int chunk)
         t.bwd.seg_len = (int)(n_chunks * cb);
         t.bwd.n_seg = 1;
         t.bwd.ckpt_every = 0;
+    }
+    // The pair's backward does not walk a single segment twice, and a call without a pre-pass is a launch less for either of them:
+    // 64 x 64, layer step, us, uncut and cut by the rule for short calls: 4 x 200 tokens 33.1, 37.8; 12 x 256 32.9, 38.2; 8 x 272 35.2,
+    // 38.2; 48 x 300 37.1, 38.3; but 12 x 350 40.0, 39.1 and 96 x 448 49.4, 42.7.  (64 x 128, 4 x 200: 41.2, 38.0.)
+    if (!general && dk == 64 && dv == 64 && n_chunks <= 5 && BH * n_chunks <= kSmallCallChunks && BH < 256 &&
+        env_int("CHELA_SEG_TOKENS", 0) <= 0) {
+        t.bwd.seg_len = t.fwd.seg_len = (int)(n_chunks * cb);
+        t.bwd.n_seg = t.fwd.n_seg = 1;
     }
     const long cps_b = t.bwd.seg_len / cb;             // chunks per backward segment
     const double want = (double)t.fwd.n_seg / (double)t.bwd.n_seg;
@@ -363,7 +428,8 @@ static size_t workspace_limit(size_t bytes, hipStream_t stream)
     return being_captured(stream) ? have : bytes;
 }
 
-static int get_workspace(size_t bytes, void* stream, float** out)
+// less_will_do: while the stream is being captured, what there is or nothing.
+static int get_workspace(size_t bytes, void* stream, float** out, bool less_will_do = false)
 {
     *out = nullptr;
     if (bytes == 0) return CHELA_OK;
@@ -387,6 +453,7 @@ static int get_workspace(size_t bytes, void* stream, float** out)
         w = &g_own_ws[dev].back();
     }
     if (w->bytes < bytes) {
+        if (less_will_do && being_captured((hipStream_t)stream)) return CHELA_ERR_WORKSPACE;
         if (w->ptr && !w->captured) {
             (void)hipDeviceSynchronize();
             (void)hipFree(w->ptr);
@@ -403,6 +470,49 @@ static int get_workspace(size_t bytes, void* stream, float** out)
     if (!w->captured) w->captured = being_captured((hipStream_t)stream);
     *out = (float*)w->ptr;
     return CHELA_OK;
+}
+
+// The split of a bf16 call and its scratch.  Small calls may take more than the general split, which is then what they get where the
+// scratch cannot be had: from a smaller caller-owned buffer, under capture, because the allocation is refused.  extra(plan): bytes
+// beside the plan's own.
+template <typename Extra>
+static int plan_bf16(long BH, int N, int dk, int dv, int chunk, bool is_bwd, bool stateful, bool can_checkpoint, void* stream,
+                     Plan* plan, float** ws, Extra extra)
+{
+    *plan = make_plan(BH, N, dk, dv, chunk, CHELA_DTYPE_BF16, is_bwd, stateful, can_checkpoint);
+    const int rc = get_workspace(plan->ws_bytes + extra(*plan), stream, ws, true);
+    if (rc != CHELA_ERR_WORKSPACE) return rc;
+    *plan = make_plan(BH, N, dk, dv, chunk, CHELA_DTYPE_BF16, is_bwd, stateful, can_checkpoint, true);
+    return get_workspace(plan->ws_bytes + extra(*plan), stream, ws);
+}
+static size_t nothing_extra(const Plan&) { return 0; }
+
+// The same for a call of the training pair, whose two calls have to agree on the segments that `saved` stands for whatever scratch
+// each of them finds.  *alone: less than t's split takes, but what the general one would: the forward then runs in one segment and
+// has the boundary states made in `saved` itself, the backward runs in one segment and works the states out.
+template <typename Extra>
+static int pair_workspace(const TrainPlans& t, bool is_bwd, long BH, int N, int dk, int dv, int chunk, void* stream, float** ws,
+                          Plan* alone, bool* use_alone, Extra extra)
+{
+    *use_alone = false;
+    const Plan& plan = is_bwd ? t.bwd : t.fwd;
+    const size_t need = plan.ws_bytes + extra(plan);
+    int rc = get_workspace(need, stream, ws, true);
+    if (rc != CHELA_ERR_WORKSPACE) return rc;
+    const TrainPlans g = make_train_plans(BH, N, dk, dv, chunk, true);
+    const Plan& before = is_bwd ? g.bwd : g.fwd;
+    const size_t least = before.ws_bytes + extra(before);
+    if (least >= need) return get_workspace(need, stream, ws);
+    if (least > 0 && (rc = get_workspace(least, stream, ws)) != CHELA_OK) return rc;
+    Plan p = t.bwd;
+    const long n_chunks = ((long)N + p.chunk - 1) / p.chunk, max_walk = kMaxBwdWalkTokens / p.chunk;
+    p.seg_len = (int)(n_chunks * p.chunk);
+    p.n_seg = 1;
+    p.ckpt_every = is_bwd && n_chunks > max_walk ? (int)max_walk : 0;
+    p.ws_bytes = (size_t)BH * (size_t)plan_n_ckpt(p, N) * p.state_elems * sizeof(float);
+    *alone = p;
+    *use_alone = true;
+    return p.ws_bytes + extra(p) <= least ? CHELA_OK : CHELA_ERR_WORKSPACE;
 }
 
 // ------------------------------------------------------------------ scratch that is never allocated
@@ -524,11 +634,15 @@ static int fwd_common(const void* Q, const void* K, const void* V, void* O, cons
     }
     float* ws = nullptr;
     if (static_ws) {
+        if (plan.ws_bytes > kStaticScratchBytes && dtype == CHELA_DTYPE_BF16)
+            plan = make_plan(BH, N, dk, dv, chunk, dtype, false, S_in != nullptr, false, true);
         if (plan.ws_bytes > kStaticScratchBytes) return CHELA_ERR_WORKSPACE;
         rc = plan.ws_bytes ? static_scratch(&ws) : CHELA_OK;
+    } else if (dtype == CHELA_DTYPE_BF16) {
+        rc = plan_bf16(BH, N, dk, dv, chunk, false, S_in != nullptr, false, stream, &plan, &ws, nothing_extra);
     } else {
         rc = get_workspace(plan.ws_bytes, stream, &ws);
-        if (rc == CHELA_ERR_WORKSPACE && dtype == CHELA_DTYPE_F32) {       // (refused: the smaller need, as under capture)
+        if (rc == CHELA_ERR_WORKSPACE) {       // (refused: the smaller need, as under capture)
             plan = make_f32_fwd_plan(BH, N, dk, dv, chunk, 0);
             rc = get_workspace(plan.ws_bytes, stream, &ws);
         }
@@ -568,10 +682,10 @@ static int bwd_common(const void* Q, const void* K, const void* V, const void* d
         return CHELA_OK;
     }
     if (dtype == CHELA_DTYPE_BF16) {
-        Plan plan = make_plan(BH, N, dk, dv, bf16_bwd_effective_chunk(dk, dv, chunk), dtype, true,
-                              S_in != nullptr || dS_out != nullptr, true);
+        Plan plan;
         float* ws = nullptr;
-        rc = get_workspace(plan.ws_bytes, stream, &ws);
+        rc = plan_bf16(BH, N, dk, dv, bf16_bwd_effective_chunk(dk, dv, chunk), true, S_in != nullptr || dS_out != nullptr, true,
+                       stream, &plan, &ws, nothing_extra);
         if (rc != CHELA_OK) return rc;
         hipError_t e = launch_bf16_bwd(Q, K, V, dO, S_in, dS_out, dQ, dK, dV, dS_in, nullptr, BH, N, dk, dv, plan, ws, st);
         return e == hipSuccess ? CHELA_OK : CHELA_ERR_HIP;
@@ -614,10 +728,17 @@ static int zfwd_common(const void* Z, const float* aff, const void* V, void* O, 
     bool empty = false;
     int rc = validate(in_v, inb, 3, out_v, outb, 2, B, H, N, dk, dv, chunk, CHELA_DTYPE_BF16, &empty);
     if (rc != CHELA_OK || empty) return rc;
-    Plan plan = want_saved ? t.fwd : make_plan(BH, N, dk, dv, 64, CHELA_DTYPE_BF16, false, false);
+    Plan plan = t.fwd;
     float* ws = nullptr;
-    rc = get_workspace(plan.ws_bytes, stream, &ws);
+    bool alone = false;
+    rc = want_saved ? pair_workspace(t, false, BH, N, dk, dv, 64, stream, &ws, &plan, &alone, nothing_extra)
+                    : plan_bf16(BH, N, dk, dv, 64, false, false, false, stream, &plan, &ws, nothing_extra);
     if (rc != CHELA_OK) return rc;
+    if (alone) {
+        if (launch_bf16_boundary_states(Z, V, aff, (float*)saved, BH, H, N, dk, dv, t.bwd, (hipStream_t)stream) != hipSuccess)
+            return CHELA_ERR_HIP;
+        want_saved = false;
+    }
     return launch_bf16_zfwd(Z, aff, V, O, want_saved ? (float*)saved : nullptr, want_saved ? t.save_every : 1, B, H, N,
                             dk, dv, plan, ws, (hipStream_t)stream) == hipSuccess ? CHELA_OK : CHELA_ERR_HIP;
 }
@@ -645,10 +766,14 @@ static int zbwd_common(const void* Z, const float* aff, const void* V, const voi
         if (d_aff && ab) return launch_zero_fill(d_aff, ab / sizeof(float), (hipStream_t)stream) == hipSuccess ? CHELA_OK : CHELA_ERR_HIP;
         return CHELA_OK;
     }
-    Plan plan = want_saved ? t.bwd : make_plan(BH, N, dk, dv, 64, CHELA_DTYPE_BF16, true, false, true);
+    Plan plan = t.bwd;
     float* ws = nullptr;
-    rc = get_workspace(plan.ws_bytes + zbwd_extra_ws_bytes(BH, plan, dk), stream, &ws);
+    bool alone = false;
+    auto extra = [&](const Plan& p) { return zbwd_extra_ws_bytes(BH, p, dk); };
+    rc = want_saved ? pair_workspace(t, true, BH, N, dk, dv, 64, stream, &ws, &plan, &alone, extra)
+                    : plan_bf16(BH, N, dk, dv, 64, true, false, true, stream, &plan, &ws, extra);
     if (rc != CHELA_OK) return rc;
+    if (alone) want_saved = false;
     return launch_bf16_zbwd(Z, aff, V, dO, dZ, d_aff, dV, want_saved ? (const float*)saved : nullptr, B, H, N, dk, dv,
                             plan, ws, (hipStream_t)stream) == hipSuccess ? CHELA_OK : CHELA_ERR_HIP;
 }
@@ -669,9 +794,13 @@ static int fwd_save_common(const void* Q, const void* K, const void* V, void* O,
     int rc = validate(in_v, inb, 3, out_v, outb, 2, B, H, N, dk, dv, chunk, CHELA_DTYPE_BF16, &empty);
     if (rc != CHELA_OK || empty) return rc;
     float* ws = nullptr;
-    rc = get_workspace(t.fwd.ws_bytes, stream, &ws);
+    Plan plan = t.fwd;
+    bool alone = false;
+    rc = pair_workspace(t, false, BH, N, dk, dv, chunk, stream, &ws, &plan, &alone, nothing_extra);
     if (rc != CHELA_OK) return rc;
-    return launch_bf16_fwd(Q, K, V, O, nullptr, nullptr, (float*)saved, t.save_every, BH, N, dk, dv, t.fwd, ws,
+    if (alone && launch_bf16_boundary_states(K, V, nullptr, (float*)saved, BH, H, N, dk, dv, t.bwd, (hipStream_t)stream) != hipSuccess)
+        return CHELA_ERR_HIP;
+    return launch_bf16_fwd(Q, K, V, O, nullptr, nullptr, alone ? nullptr : (float*)saved, t.save_every, BH, N, dk, dv, plan, ws,
                            (hipStream_t)stream) == hipSuccess ? CHELA_OK : CHELA_ERR_HIP;
 }
 
@@ -691,10 +820,12 @@ static int bwd_saved_common(const void* Q, const void* K, const void* V, const v
     int rc = validate(in_v, inb, 5, out_v, outb, 3, B, H, N, dk, dv, chunk, CHELA_DTYPE_BF16, &empty);
     if (rc != CHELA_OK || empty) return rc;
     float* ws = nullptr;
-    rc = get_workspace(t.bwd.ws_bytes, stream, &ws);
+    Plan plan = t.bwd;
+    bool alone = false;
+    rc = pair_workspace(t, true, BH, N, dk, dv, chunk, stream, &ws, &plan, &alone, nothing_extra);
     if (rc != CHELA_OK) return rc;
-    return launch_bf16_bwd(Q, K, V, dO, nullptr, nullptr, dQ, dK, dV, nullptr, (const float*)saved, BH, N, dk, dv,
-                           t.bwd, ws, (hipStream_t)stream) == hipSuccess ? CHELA_OK : CHELA_ERR_HIP;
+    return launch_bf16_bwd(Q, K, V, dO, nullptr, nullptr, dQ, dK, dV, nullptr, alone ? nullptr : (const float*)saved, BH, N, dk, dv,
+                           plan, ws, (hipStream_t)stream) == hipSuccess ? CHELA_OK : CHELA_ERR_HIP;
 }
 
 // Forward with the Eq. 9 epilogue; aff non-null: Z in place of Q and K.  O and saved are optional outputs.
@@ -717,10 +848,18 @@ static int fwd_gated_common(const void* Q, const void* K, const float* aff, bool
     bool empty = false;
     int rc = validate(in_v, inb, 4, out_v, outb, 3, B, H, N, dk, dv, chunk, CHELA_DTYPE_BF16, &empty);
     if (rc != CHELA_OK || empty) return rc;
-    Plan plan = saved ? t.fwd : make_plan(BH, N, dk, dv, 64, CHELA_DTYPE_BF16, false, false);
+    Plan plan = t.fwd;
     float* ws = nullptr;
-    rc = get_workspace(plan.ws_bytes, stream, &ws);
+    bool alone = false;
+    rc = saved ? pair_workspace(t, false, BH, N, dk, dv, 64, stream, &ws, &plan, &alone, nothing_extra)
+               : plan_bf16(BH, N, dk, dv, 64, false, false, false, stream, &plan, &ws, nothing_extra);
     if (rc != CHELA_OK) return rc;
+    if (alone) {
+        if (launch_bf16_boundary_states(zqk ? Q : K, V, zqk ? aff : nullptr, (float*)saved, BH, H, N, dk, dv, t.bwd,
+                                        (hipStream_t)stream) != hipSuccess)
+            return CHELA_ERR_HIP;
+        saved = nullptr;
+    }
     return launch_bf16_fwd_gated(Q, K, V, G, O, Y, eps, zqk ? aff : nullptr, (float*)saved, saved ? t.save_every : 1, B,
                                  H, N, dk, dv, plan, ws, (hipStream_t)stream) == hipSuccess ? CHELA_OK : CHELA_ERR_HIP;
 }
@@ -764,9 +903,9 @@ static int bnhd_common(const void* Q, const void* K, const void* V, const void* 
     bool empty = false;
     int rc = validate(in_v, inb, 4, out_v, outb, 3, B, H, N, dk, dv, chunk, CHELA_DTYPE_BF16, &empty);
     if (rc != CHELA_OK || empty) return rc;
-    Plan plan = make_plan((long)B * H, N, dk, dv, 64, CHELA_DTYPE_BF16, is_bwd, false, true);
+    Plan plan;
     float* ws = nullptr;
-    rc = get_workspace(plan.ws_bytes, stream, &ws);
+    rc = plan_bf16((long)B * H, N, dk, dv, 64, is_bwd, false, true, stream, &plan, &ws, nothing_extra);
     if (rc != CHELA_OK) return rc;
     hipError_t e = is_bwd ? launch_bf16_bwd_nh(Q, K, V, dO, O_or_dQ, dK, dV, B, H, N, dk, dv, plan, ws, (hipStream_t)stream)
                           : launch_bf16_fwd_nh(Q, K, V, O_or_dQ, B, H, N, dk, dv, plan, ws, (hipStream_t)stream);

@@ -37,8 +37,9 @@ inline long plan_n_ckpt(const Plan& p, int N)
 
 // can_checkpoint: the caller's backward builds the state itself in a first pass over the sequence when there is a
 // single segment (the plain calls without carried or saved states), so long single segments are allowed.
+// general: not the split that small bf16 calls have of their own.
 Plan make_plan(long BH, int N, int dk, int dv, int chunk, int dtype, bool is_bwd, bool stateful,
-               bool can_checkpoint = false);
+               bool can_checkpoint = false, bool general = false);
 
 // scan modes for scan_states()
 enum { SCAN_EXCL_PREFIX = 0, SCAN_INCL_PREFIX = 1, SCAN_EXCL_SUFFIX = 2 };
@@ -81,7 +82,11 @@ hipError_t launch_bf16_bwd(const void* Q, const void* K, const void* V, const vo
 // The two plans of a forward call that saves states and the backward call that uses them: the backward's segment
 // length is save_every times the forward's.
 struct TrainPlans { Plan fwd, bwd; int save_every; };
-TrainPlans make_train_plans(long BH, int N, int dk, int dv, int chunk);
+TrainPlans make_train_plans(long BH, int N, int dk, int dv, int chunk, bool general = false);
+// The states that `saved` stands for, one at the end of each segment of the backward's plan, made in it with no other scratch.
+// aff non-null: K is Z.
+hipError_t launch_bf16_boundary_states(const void* K, const void* V, const float* aff, float* saved, long BH, int H, int N, int dk,
+                                       int dv, const Plan& bwd_plan, hipStream_t st);
 // The same two maps for [B,N,H,d] tensors; plan.chunk must be 64.
 hipError_t launch_bf16_fwd_nh(const void* Q, const void* K, const void* V, void* O, int B, int H, int N, int dk, int dv,
                               const Plan& plan, float* ws, hipStream_t st);

@@ -2413,6 +2413,32 @@ hipError_t launch_bf16_zfwd(const void* Z, const float* aff, const void* V, void
     return hipErrorInvalidValue;
 }
 
+template <int DK, int DV, bool ZQK>
+static hipError_t boundary_states_impl(const bf16* K, const bf16* V, const float* aff, float* saved, long BH, int H, int N,
+                                       const Plan& plan, hipStream_t st)
+{
+    SegStateArgs a{};
+    a.X[0] = V; a.Y[0] = K; a.out[0] = saved; a.skip_seg[0] = -1;       // S^T = V^T K, [dv][dk]
+    a.H = H;
+    if (ZQK) { a.alpha[0] = aff + 2 * (size_t)H * DK; a.beta[0] = aff + 3 * (size_t)H * DK; }
+    const int mode = SCAN_INCL_PREFIX;
+    const float* init[2] = {nullptr, nullptr};
+    return run_seg_state<DV, DK, ZQK ? 2 : 0>(a, 1, &mode, init, false, BH, N, plan, st);
+}
+
+hipError_t launch_bf16_boundary_states(const void* K, const void* V, const float* aff, float* saved, long BH, int H, int N, int dk,
+                                       int dv, const Plan& plan, hipStream_t st)
+{
+    const bf16 *k = (const bf16*)K, *v = (const bf16*)V;
+#define CHELA_BOUNDARY(DK_, DV_)                                                                                    \
+    if (dk == DK_ && dv == DV_)                                                                                      \
+        return aff ? boundary_states_impl<DK_, DV_, true>(k, v, aff, saved, BH, H, N, plan, st)                      \
+                   : boundary_states_impl<DK_, DV_, false>(k, v, nullptr, saved, BH, H, N, plan, st);
+    CHELA_BOUNDARY(64, 64) CHELA_BOUNDARY(64, 128) CHELA_BOUNDARY(128, 64) CHELA_BOUNDARY(128, 128)
+#undef CHELA_BOUNDARY
+    return hipErrorInvalidValue;
+}
+
 hipError_t launch_bf16_zbwd(const void* Z, const float* aff, const void* V, const void* dO, void* dZ, float* d_aff,
                             void* dV, const float* saved, int B, int H, int N, int dk, int dv, const Plan& plan,
                             float* ws, hipStream_t st)

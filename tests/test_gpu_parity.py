@@ -410,6 +410,61 @@ def test_caller_workspace_and_side_stream():
         binding.chela_set_workspace(None)
 
 
+@pytest.mark.parametrize("less", ["forward", "backward", "both"])
+@pytest.mark.parametrize("shape", [(8, 272, 128, 128), (16, 435, 128, 128), (3, 200, 64, 128), (96, 448, 64, 64), (2, 9000, 128, 128)])
+def test_small_bf16_calls_in_less_scratch_than_their_split_takes(shape, less):
+    # a few hundred chunks in all: such calls have a split of their own, which may take more scratch than the general one; in a buffer
+    # that is too small for it they take the general one, and the calls of a training pair agree whichever of them had less
+    H, N, dk, dv = shape
+    w = shrink(WORKLOADS["lm_bf16"], B=1, H=H, N=N, dk=dk, dv=dv, seed=N + 7)
+    x, z = make_inputs(w), make_z_inputs(w, with_dO=True)
+    d, e = _dev(x), _dev(z)
+    L = binding.lib()
+    n = lambda t: to_f64_numpy(t)
+
+    def call(small, query, is_bwd, f):
+        q = getattr(L, query)
+        need = q(1, H, N, dk, dv, 64, is_bwd, 0) if query == "chela_linattn_workspace_bytes" else q(1, H, N, dk, dv, 64, is_bwd)
+        assert need > 0
+        buf = torch.full((need + 4096,), 0x5a, dtype=torch.uint8, device="cuda")
+        room = need - 16 if small else need
+        try:
+            binding.chela_set_workspace(buf[:room])
+            out = f()
+        finally:
+            binding.chela_set_workspace(None)
+        torch.cuda.synchronize()
+        assert bool((buf[room:] == 0x5a).all())
+        return out
+
+    sf, sb = less != "backward", less != "forward"
+    O, saved = call(sf, "chela_linattn_train_workspace_bytes", 0, lambda: binding.chela_linattn_fwd_save(d["Q"], d["K"], d["V"]))
+    grads = call(sb, "chela_linattn_train_workspace_bytes", 1,
+                 lambda: binding.chela_linattn_bwd_saved(d["Q"], d["K"], d["V"], d["dO"], saved))
+    ref = oracle.fwd_recurrent(n(x["Q"]), n(x["K"]), n(x["V"])), oracle.bwd_recurrent(n(x["Q"]), n(x["K"]), n(x["V"]), n(x["dO"]))
+    plain = call(sb, "chela_linattn_workspace_bytes", 1, lambda: binding.chela_linattn_bwd(d["Q"], d["K"], d["V"], d["dO"]))
+    _check("O", O, ref[0], "bf16")
+    for name, got, other, r in zip(("dQ", "dK", "dV"), grads, plain, ref[1]):
+        _check(name, got, r, "bf16")
+        _check(name, other, r, "bf16")
+    O, saved = call(sf, "chela_linattn_z_workspace_bytes", 0, lambda: binding.chela_linattn_zfwd_save(e["Z"], e["affine"], e["V"]))
+    dZ, dA, dV = call(sb, "chela_linattn_z_workspace_bytes", 1,
+                      lambda: binding.chela_linattn_zbwd_saved(e["Z"], e["affine"], e["V"], e["dO"], saved))
+    _check("O", O, oracle_layer.zqk_fwd(n(z["Z"]), n(z["affine"]), n(z["V"])), "bf16")
+    rZ, rA, rV = oracle_layer.zqk_bwd(n(z["Z"]), n(z["affine"]), n(z["V"]), n(z["dO"]))
+    _check("dZ", dZ, rZ, "bf16")
+    _check("dV", dV, rV, "bf16")
+    for q in range(4):
+        _check("d_affine[%d]" % q, dA[q], rA[q], "bf16")
+    G = torch.ones_like(e["V"])
+    Y, O, saved = call(sf, "chela_linattn_z_workspace_bytes", 0, lambda: binding.chela_linattn_zfwd_gated(
+        e["Z"], e["affine"], e["V"], G, 1e-5, want_O=True, want_saved=True))
+    dZ, dA, dV = call(sb, "chela_linattn_z_workspace_bytes", 1,
+                      lambda: binding.chela_linattn_zbwd_saved(e["Z"], e["affine"], e["V"], e["dO"], saved))
+    _check("dZ", dZ, rZ, "bf16")
+    _check("dV", dV, rV, "bf16")
+
+
 @pytest.mark.parametrize("dims", [(64, 64), (64, 128), (128, 64), (128, 128)])
 def test_f32_backward_takes_fewer_segments_in_a_smaller_scratch_buffer(dims):
     # the full need and ever less: fewer segments and the same gradient, down to where the call is refused
