@@ -20,8 +20,14 @@ DTYPE_BF16 = 0
 DTYPE_F32 = 1
 
 _lib = None
-_step_host = None           # the host module's step(), once a decode step has been made
+_step_host = None           # the host module's step(), once a call has been made
 _step_fn = (0, 0)           # addresses of chela_linattn_step, chela_linattn_step_gated for it
+_host_modules = {}          # by _step_host: the same module, None where there is none
+_fn = {}                    # addresses of the library's functions for it, by name
+
+
+def _decline(*a):
+    return None
 
 
 class ChelaError(RuntimeError):
@@ -182,25 +188,43 @@ def _on(t: torch.Tensor):
 
 
 def _load_step():
-    """The host module's step() and the addresses it calls; a step() that declines every call where the module is not built or
-    does not load, for instance beside another torch than it was built for (the lines of the two functions below then do the same,
-    in 8.9 us instead of 4.7 per step)."""
+    """Loads the host module and looks up the addresses of the library's functions it calls.  Returns its step(), or one that
+    declines every call where the module is not built or does not load, for instance beside another torch than it was built for (the
+    functions below then do the same by their own lines, a decode step in 8.9 us instead of 4.7, a short prompt in 10 instead of 5)."""
     global _step_host, _step_fn
     L = lib()
     _step_fn = tuple(ctypes.cast(f, ctypes.c_void_p).value for f in (L.chela_linattn_step, L.chela_linattn_step_gated))
+    for name in ("linattn_fwd", "linattn_fwd_f32", "linattn_fwd_state", "linattn_bwd", "linattn_bwd_f32", "linattn_fwd_gated",
+                 "linattn_zfwd_gated", "linattn_saved_bytes", "gate_norm_bwd", "linattn_zbwd_saved", "linattn_noncausal_fwd_gated",
+                 "linattn_noncausal_bwd", "longconv_spectrum", "longconv_spectrum_bytes", "shortlong_conv_fwd",
+                 "shortlong_conv_fwd_f32", "shortlong_conv_bwd", "shortlong_conv_bwd_f32"):
+        _fn[name] = ctypes.cast(getattr(L, "chela_" + name), ctypes.c_void_p).value
     path = os.path.join(_HERE, "_chela_host.so")
     step = lambda *a: None        # noqa: E731
+    module = None
     if os.path.exists(path):
         spec = importlib.util.spec_from_file_location("_chela_host", path,
                                                       loader=importlib.machinery.ExtensionFileLoader("_chela_host", path))
         try:
-            module = importlib.util.module_from_spec(spec)
-            spec.loader.exec_module(module)
-            step = module.step
+            m = importlib.util.module_from_spec(spec)
+            spec.loader.exec_module(m)
+            step, module = m.step, m
         except ImportError as e:
-            warnings.warn("decode steps take the slower host path: %s does not load (%s)" % (path, e), RuntimeWarning)
+            warnings.warn("calls take the slower host path: %s does not load (%s)" % (path, e), RuntimeWarning)
+    _host_modules[step] = module        # (first: whoever sees _step_host looks here)
     _step_host = step
     return step
+
+
+def _host(name):
+    """The host module's function of that name, as _load_step()'s for the decode step."""
+    return getattr(_host_modules[_step_host if _step_host is not None else _load_step()], name, _decline)
+
+
+def _host_result(r):
+    if type(r) is int:
+        _check(r)
+    return r
 
 
 def _suffix(t: torch.Tensor) -> Tuple[str, int]:
@@ -225,6 +249,10 @@ def _dims(Q, K, V):
 
 def chela_linattn_fwd(Q, K, V, O=None, chunk: int = 64, stream=None):
     """O = causal linear attention of (Q, K, V); enqueues on the current (or given) stream."""
+    if O is None:
+        r = _host("forward")(_fn["linattn_fwd"], _fn["linattn_fwd_f32"], Q, K, V, None, None, chunk, stream)
+        if r is not None:
+            return _host_result(r)
     B, H, N, dk, dv = _dims(Q, K, V)
     sfx, _ = _suffix(Q)
     if O is None:
@@ -251,6 +279,10 @@ def chela_linattn_fwd_noalloc(Q, K, V, O, chunk: int = 64, stream=None):
 
 def chela_linattn_bwd(Q, K, V, dO, dQ=None, dK=None, dV=None, chunk: int = 64, stream=None):
     """(dQ, dK, dV) for upstream gradient dO; nothing from the forward call is needed."""
+    if dQ is None and dK is None and dV is None:
+        r = _host("backward")(_fn["linattn_bwd"], _fn["linattn_bwd_f32"], Q, K, V, dO, chunk, stream)
+        if r is not None:
+            return _host_result(r)
     B, H, N, dk, dv = _dims(Q, K, V)
     if dO.shape != V.shape or dO.dtype != Q.dtype or not dO.is_contiguous():
         raise ValueError("dO must match V")
@@ -308,6 +340,10 @@ def _state_ptr(S, B, H, dk, dv, name):
 
 def chela_linattn_fwd_state(Q, K, V, S_in=None, O=None, S_out=None, chunk: int = 64, stream=None):
     """(O, S_out): forward with the running state started at S_in; S_out may be S_in (in place)."""
+    if O is None:
+        r = _host("forward")(_fn["linattn_fwd_state"], None, Q, K, V, S_in, S_out, chunk, stream)
+        if r is not None:
+            return _host_result(r)
     B, H, N, dk, dv = _dims(Q, K, V)
     if Q.dtype != torch.bfloat16:
         raise TypeError("the stateful entry points are bf16")
@@ -395,6 +431,9 @@ def chela_linattn_noncausal_fwd(Q, K, V, O=None, stream=None):
 
 def chela_linattn_noncausal_bwd(Q, K, V, dO, stream=None):
     """(dQ, dK, dV) of chela_linattn_noncausal_fwd."""
+    r = _host("backward")(_fn["linattn_noncausal_bwd"], None, Q, K, V, dO, None, stream)
+    if r is not None:
+        return _host_result(r)
     B, H, N, dk, dv = _dims(Q, K, V)
     _bf16_only(Q, "the non-causal form")
     if dO.shape != V.shape or dO.dtype != Q.dtype or not dO.is_contiguous():
@@ -467,6 +506,9 @@ def chela_linattn_zfwd_save(Z, affine, V, O=None, saved=None, stream=None):
 
 def chela_linattn_zbwd_saved(Z, affine, V, dO, saved, stream=None):
     """(dZ, d_affine, dV) using the states chela_linattn_zfwd_save left for the same inputs."""
+    r = _host("zbwd_saved")(_fn["linattn_zbwd_saved"], Z, affine, V, dO, saved, stream)
+    if r is not None:
+        return _host_result(r)
     B, H, N, dk, dv = _zdims(Z, affine, V)
     if dO.shape != V.shape or dO.dtype != V.dtype or not dO.is_contiguous():
         raise ValueError("dO must match V")
@@ -506,6 +548,10 @@ def _ptr(t):
 def chela_linattn_fwd_gated(Q, K, V, G, eps, want_O=False, want_saved=False, Y=None, O=None, saved=None, stream=None):
     """(Y, O, saved) with Y = Norm(O) * G (Eq. 9) formed inside the forward.  O and saved are produced when asked for
     (want_*) or when a buffer for them is passed; otherwise they come back as None."""
+    if Y is None and O is None and saved is None and type(K) is torch.Tensor and K.dtype == torch.bfloat16:
+        r = _host("gated")(_fn["linattn_fwd_gated"], _fn["linattn_saved_bytes"], Q, K, V, G, eps, want_O, want_saved, stream)
+        if r is not None:
+            return _host_result(r)
     B, H, N, dk, dv = _dims(Q, K, V)
     _bf16_only(Q, "the gated forward")
     Y, O, saved = _gated_outputs(V, G, want_O, want_saved, dk, Y, O, saved)
@@ -519,6 +565,10 @@ def chela_linattn_fwd_gated(Q, K, V, G, eps, want_O=False, want_saved=False, Y=N
 def chela_linattn_zfwd_gated(Z, affine, V, G, eps, want_O=False, want_saved=False, Y=None, O=None, saved=None,
                              stream=None):
     """chela_linattn_fwd_gated with Q and K formed from Z (Eq. 11-12)."""
+    if Y is None and O is None and saved is None and type(affine) is torch.Tensor and affine.dtype == torch.float32:
+        r = _host("gated")(_fn["linattn_zfwd_gated"], _fn["linattn_saved_bytes"], Z, affine, V, G, eps, want_O, want_saved, stream)
+        if r is not None:
+            return _host_result(r)
     B, H, N, dk, dv = _zdims(Z, affine, V)
     Y, O, saved = _gated_outputs(V, G, want_O, want_saved, dk, Y, O, saved)
     with _on(Z):
@@ -530,6 +580,10 @@ def chela_linattn_zfwd_gated(Z, affine, V, G, eps, want_O=False, want_saved=Fals
 
 def chela_linattn_noncausal_fwd_gated(Q, K, V, G, eps, want_O=False, Y=None, O=None, stream=None):
     """(Y, O) with Y = Norm(Q (K^T V)) * G, the non-causal form with the Eq. 9 epilogue; O is None unless asked for."""
+    if Y is None and O is None:
+        r = _host("gated")(_fn["linattn_noncausal_fwd_gated"], None, Q, K, V, G, eps, want_O, False, stream)
+        if r is not None:
+            return _host_result(r)[:2]
     B, H, N, dk, dv = _dims(Q, K, V)
     _bf16_only(Q, "the gated non-causal forward")
     Y, O, _ = _gated_outputs(V, G, want_O, False, dk, Y, O, None)
@@ -564,6 +618,10 @@ def chela_gate_norm_fwd(O, G, eps, Y=None, stream=None):
 
 def chela_gate_norm_bwd(O, G, dY, eps, in_place=False, dO=None, dG=None, stream=None):
     """(dO, dG) of chela_gate_norm_fwd; in_place=True writes dO over dY."""
+    if dO is None and dG is None and not in_place:
+        r = _host("gate_norm_bwd")(_fn["gate_norm_bwd"], O, G, dY, eps, stream)
+        if r is not None:
+            return _host_result(r)
     rows, dv = _gate_rows(O, G)
     if dY.shape != O.shape or dY.dtype != O.dtype or not dY.is_cuda or not dY.is_contiguous():
         raise ValueError("dY must match O")
@@ -588,6 +646,9 @@ def chela_linattn_z_workspace_bytes(B, H, N, dk, dv, chunk, is_bwd) -> int:
 
 def chela_longconv_spectrum(k_long, stream=None):
     """Spectrum buffer of a long kernel k_long [d, L] (float32): computed once, reused for every batch."""
+    r = _host("spectrum")(_fn["longconv_spectrum"], _fn["longconv_spectrum_bytes"], k_long, stream)
+    if r is not None:
+        return _host_result(r)
     if k_long.dim() != 2 or k_long.dtype != torch.float32 or not k_long.is_cuda or not k_long.is_contiguous():
         raise ValueError("k_long must be a contiguous float32 device tensor [d, L]")
     d, Lseq = k_long.shape
@@ -603,6 +664,10 @@ def chela_longconv_spectrum(k_long, stream=None):
 def chela_shortlong_conv_fwd(X, w_short, spectrum, Z=None, stream=None):
     """Z = K_l(silu(K_s(X))) for X [B, d, L] (bf16 or float32); w_short [d, m] float32 or None; spectrum from
     chela_longconv_spectrum for the same d and L."""
+    if Z is None:
+        r = _host("conv_fwd")(_fn["shortlong_conv_fwd"], _fn["shortlong_conv_fwd_f32"], X, w_short, spectrum, stream)
+        if r is not None:
+            return _host_result(r)
     if X.dim() != 3 or not X.is_cuda or not X.is_contiguous():
         raise ValueError("X must be a contiguous device tensor [B, d, L]")
     sfx, _ = _suffix(X)
@@ -624,6 +689,9 @@ def chela_shortlong_conv_fwd(X, w_short, spectrum, Z=None, stream=None):
 def chela_shortlong_conv_bwd(X, w_short, spectrum, dZ, stream=None):
     """(dX, d_w_short, d_k_long) of chela_shortlong_conv_fwd for the upstream gradient dZ (d_w_short is None
     without a short kernel)."""
+    r = _host("conv_bwd")(_fn["shortlong_conv_bwd"], _fn["shortlong_conv_bwd_f32"], X, w_short, spectrum, dZ, stream)
+    if r is not None:
+        return _host_result(r)
     if X.dim() != 3 or not X.is_cuda or not X.is_contiguous() or dZ.shape != X.shape or dZ.dtype != X.dtype \
             or not dZ.is_contiguous():
         raise ValueError("X and dZ must be contiguous device tensors [B, d, L] of one dtype")

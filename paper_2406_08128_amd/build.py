@@ -35,7 +35,7 @@ def _compile(src: str) -> str:
 
 
 def _build_host_module() -> bool:
-    """The decode step's host path as a Python module (csrc/chela_host.cpp): host code only, against torch's headers.  It is a
+    """The host path of the plain calls as a Python module (csrc/chela_host.cpp): host code only, against torch's headers.  It is a
     shortcut: where there is no compiler for it or no headers the library is built all the same, and no module of an earlier build
     stays beside it.
     NDEBUG keeps a per-thread counter of pybind11's reference counting out of it: once a library with per-thread data of its
@@ -60,7 +60,7 @@ def _build_host_module() -> bool:
     except (ImportError, OSError) as e:
         failed = str(e)
     if failed is not None:
-        print("host module not built, decode steps take the slower host path:\n" + failed, file=sys.stderr)
+        print("host module not built, calls take the slower host path:\n" + failed, file=sys.stderr)
     return failed is None
 
 

@@ -1127,6 +1127,112 @@ def test_decode_step_host_path_lets_other_threads_run():
         assert torch.is_tensor(binding._load_step()(held, q, k, v, g, S, 1e-5, None, None))
 
 
+@pytest.mark.parametrize("dk,dv,dtype", [(64, 64, torch.bfloat16), (128, 64, torch.bfloat16), (64, 128, torch.float32)])
+def test_sequence_host_path_and_the_bindings_own_lines_agree(dk, dv, dtype):
+    # with the current stream passed in, the native host path declines and the binding's own lines make the call; whatever is no
+    # plain call goes there too, and is refused there as before
+    from torch.utils._python_dispatch import TorchDispatchMode
+
+    class Mode(TorchDispatchMode):
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            return func(*args, **(kwargs or {}))
+
+    here = torch.cuda.current_stream()
+    g = torch.Generator(device="cuda")
+    g.manual_seed(dk + dv)
+    r = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    Q, K, V, dO = ((r(2, 3, 150, n) / 8).to(dtype) for n in (dk, dk, dv, dv))
+    S = r(2, 3, dk, dv)
+    binding._load_step()
+    fwd, bwd = binding._host("forward"), binding._host("backward")
+    f = {k[len("linattn_"):]: v for k, v in binding._fn.items() if k.startswith("linattn_")}
+    a = fwd(f["fwd"], f["fwd_f32"], Q, K, V, None, None, 64, None)
+    b = binding.chela_linattn_fwd(Q.requires_grad_(), K, V, stream=here)
+    assert torch.is_tensor(a) and torch.equal(a, b) and a.dtype == b.dtype and not a.requires_grad
+    ga, gb = bwd(f["bwd"], f["bwd_f32"], Q, K, V, dO, 64, None), binding.chela_linattn_bwd(Q, K, V, dO, stream=here)
+    assert len(ga) == 3 and all(torch.equal(x, y) and not x.requires_grad for x, y in zip(ga, gb))
+    if dtype == torch.bfloat16:
+        for s_in in (None, S):
+            (o1, s1), (o2, s2) = (binding.chela_linattn_fwd_state(Q, K, V, S_in=s_in, stream=st) for st in (None, here))
+            assert torch.equal(o1, o2) and torch.equal(s1, s2)
+        s3 = S.clone()
+        o3, out = binding.chela_linattn_fwd_state(Q, K, V, S_in=s3, S_out=s3)
+        assert out is s3 and torch.equal(o3, o2) and torch.equal(s3, s2)
+        assert fwd(f["fwd_state"], None, Q, K, V, S[:, :, :-1], None, 64, None) is None
+    else:
+        assert fwd(f["fwd_state"], None, Q, K, V, S, None, 64, None) is None                  # the stateful calls are bf16
+    for args in ((Q, K, V, None, None, 64, here), (Q, K, V, None, None, 64.0, None), (Q, K, V, S, None, 64, None),
+                 (Q.transpose(1, 2), K.transpose(1, 2), V, None, None, 64, None), (Q, K[:, :1], V, None, None, 64, None),
+                 (Q, K, V[:1], None, None, 64, None), (Q.cpu(), K, V, None, None, 64, None), (Q.half(), K, V, None, None, 64, None)):
+        assert fwd(f["fwd"], f["fwd_f32"], *args) is None
+    assert bwd(f["bwd"], f["bwd_f32"], Q, K, V, dO[:, :, 1:], 64, None) is None and bwd(f["bwd"], f["bwd_f32"], Q, K, V, dO, 64, here) is None
+    with Mode():
+        assert fwd(f["fwd"], f["fwd_f32"], Q, K, V, None, None, 64, None) is None and bwd(f["bwd"], f["bwd_f32"], Q, K, V, dO, 64, None) is None
+    with pytest.raises(ValueError):
+        binding.chela_linattn_fwd(Q.transpose(1, 2), K.transpose(1, 2), V.transpose(1, 2))
+    with pytest.raises(TypeError):
+        binding.chela_linattn_fwd(Q.half(), K.half(), V.half())
+    with pytest.raises(binding.ChelaError):
+        binding.chela_linattn_fwd(Q, K, V, chunk=48)
+    empty = torch.empty(2, 3, 0, dk, dtype=dtype, device="cuda")
+    assert binding.chela_linattn_fwd(empty, empty, empty).shape == (2, 3, 0, dk)
+
+
+@pytest.mark.parametrize("dk,dv", [(64, 64), (128, 64)])
+def test_layer_and_convolution_host_path_and_the_bindings_own_lines_agree(dk, dv, monkeypatch):
+    # every further call that has a native host path: that it takes the plain call, and gives what the binding's own lines give
+    taken = []
+    host = binding._host
+    monkeypatch.setattr(binding, "_host", lambda name: lambda *a: (lambda r: (taken.append((name, r is not None)), r)[1])(host(name)(*a)))
+    here = torch.cuda.current_stream()
+    g = torch.Generator(device="cuda")
+    g.manual_seed(dk)
+    r = lambda *s: torch.randn(*s, generator=g, device="cuda")
+    Q, K, V, G, dY = ((r(2, 3, 400, n) / 8).to(torch.bfloat16) for n in (dk, dk, dv, dv, dv))
+    A, X, dZ, w, k = r(4, 3, dk), r(2, 3, 300).to(torch.bfloat16), r(2, 3, 300).to(torch.bfloat16), r(3, 5), r(3, 300)
+    Yz, Oz, saved = binding.chela_linattn_zfwd_gated(Q, A, V, G, 1e-5, want_O=True, want_saved=True)
+    spec = binding.chela_longconv_spectrum(k)
+    calls = {
+        "gated": [lambda **s: binding.chela_linattn_fwd_gated(Q, K, V, G, 1e-5, **s),
+                  lambda **s: binding.chela_linattn_fwd_gated(Q, K, V, G, 1e-5, want_O=True, want_saved=True, **s),
+                  lambda **s: binding.chela_linattn_zfwd_gated(Q, A, V, G, 1e-5, want_O=True, want_saved=True, **s),
+                  lambda **s: binding.chela_linattn_noncausal_fwd_gated(Q, K, V, G, 1e-5, **s),
+                  lambda **s: binding.chela_linattn_noncausal_fwd_gated(Q, K, V, G, 1e-5, want_O=True, **s)],
+        "gate_norm_bwd": [lambda **s: binding.chela_gate_norm_bwd(Oz, G, dY, 1e-5, **s)],
+        "zbwd_saved": [lambda **s: binding.chela_linattn_zbwd_saved(Q, A, V, dY, saved, **s)],
+        "backward": [lambda **s: binding.chela_linattn_noncausal_bwd(Q, K, V, dY, **s)],
+        "spectrum": [lambda **s: (binding.chela_longconv_spectrum(k, **s),)],
+        "conv_fwd": [lambda **s: (binding.chela_shortlong_conv_fwd(X, w, spec, **s),),
+                     lambda **s: (binding.chela_shortlong_conv_fwd(X.float(), None, spec, **s),)],
+        "conv_bwd": [lambda **s: binding.chela_shortlong_conv_bwd(X, w, spec, dZ, **s),
+                     lambda **s: binding.chela_shortlong_conv_bwd(X.float(), None, spec, dZ.float(), **s)]}
+    for name, fs in calls.items():
+        for f in fs:
+            taken.clear()
+            a = f()
+            assert taken == [(name, True)]
+            b = f(stream=here)
+            assert taken == [(name, True), (name, False)]
+            assert len(a) == len(b) and type(a) is tuple
+            for x, y in zip(a, b):
+                assert (x is None) == (y is None)
+                if x is not None:
+                    assert x.shape == y.shape and x.dtype == y.dtype
+                    n = 3 * (256 // 2) * 4 if name == "spectrum" else None          # (the buffer is larger than what is written)
+                    assert n or torch.equal(x, y)
+    # refused as before: wrong shapes, types, layouts, values
+    for bad in (lambda: binding.chela_linattn_zfwd_gated(Q, A[:, :2].contiguous(), V, G, 1e-5), lambda: binding.chela_gate_norm_bwd(Oz, G, dY[:1], 1e-5),
+                lambda: binding.chela_linattn_noncausal_bwd(Q, K, V, dY[:, :, 1:].contiguous()), lambda: binding.chela_longconv_spectrum(k.t()),
+                lambda: binding.chela_linattn_fwd_gated(Q, K, V, G.float(), 1e-5),
+                lambda: binding.chela_shortlong_conv_fwd(X, w[:2], spec), lambda: binding.chela_shortlong_conv_bwd(X, w, spec, dZ[:1])):
+        with pytest.raises(ValueError):
+            bad()
+    with pytest.raises(TypeError):
+        binding.chela_linattn_noncausal_bwd(Q.float(), K.float(), V.float(), dY.float())
+    with pytest.raises(binding.ChelaError):
+        binding.chela_linattn_zfwd_gated(Q, A, V, G, -1.0)
+
+
 # ------------------------------------------------------------------------------------------ short-long convolution
 def _run_conv_case(B, d, L, m, dtype, seed=0, short=True):
     print("\nconv B%d d%d L%d m%d %s short=%s" % (B, d, L, m, dtype, short), flush=True)
