@@ -82,10 +82,10 @@ static long choose_segments(long BH, long n_chunks, long slots, double g_min, do
     return best;
 }
 
-// Calls of up to 2048 chunks in all, bf16 (but the 64 x 64 forward, where nothing is to be gained): the general model counts in chunk steps of a full GPU, all of one length, and takes a
-// pre-pass for three of them.  In a short call a step takes what it takes a workgroup that has its unit to itself, 1.3 us (forward,
+// Calls of up to 2048 chunks in all, bf16 (but the 64 x 64 forward, where nothing is to be gained): the general model counts in chunk
+// steps of a full GPU, all of one length, and takes a pre-pass for three of them.  In a short call a step takes what it takes a workgroup that has its unit to itself, 1.3 us (forward,
 // 64 x 64) to 6 (backward, 128 x 128, whose single segment walks twice: 7.7), and the pre-pass 4 whatever the widths are; under
-// some 11 us (forward) or 13 (backward) the host's launches are the time, and one costs less than two.  So this is a model in us,
+// some 7 us (forward) or 8.5 (backward) the host's launches are the time, and one costs less than two.  So this is a model in us,
 // fitted to the times of 21 shapes per pair of widths over all segment lengths (geometric mean of what the choice costs over the
 // best one, general model -> this one: forward 1.08 -> 1.01, backward 1.14 -> 1.01, worst 1.44 -> 1.05 and 1.99 -> 1.10).
 // On 21 other shapes per pair of widths: backward 1.13 to 1.16 times as fast as with the general model, forward 1.04 to 1.06.
@@ -103,7 +103,7 @@ static long small_bf16_segments(long BH, long n_chunks, int dk, int dv, bool is_
     const int size = (dk == 128) + (dv == 128);
     const Widths& w = (is_bwd ? kBwd : kFwd)[size];
     const double state = (double)(dk * dv) / 4096.0, per_state = is_bwd ? 0.012 : 0.004, per_sum = is_bwd ? 0.4 : 0.32;
-    const double scan = is_bwd ? 6.0 : 5.0, host = is_bwd ? 13.3 : 11.2;
+    const double scan = is_bwd ? 6.0 : 5.0, host = is_bwd ? 8.5 : 7.0;
     const long max_folded = (long)(kMaxFoldedStateBytes / ((size_t)dk * dv * sizeof(float)));
     auto step = [&](double alone, double shared, double load) {       // load: workgroups per unit
         if (size == 2) return alone * std::max(1.0, std::ceil(load));          // (one at a time)
@@ -128,7 +128,7 @@ static long small_bf16_segments(long BH, long n_chunks, int dk, int dv, bool is_
                    per_state * state * (double)(BH * n) +
                    (n <= max_folded ? per_sum * state * (double)n : scan + 0.075 * state * (double)n);
         }
-        cost = std::max(n == 1 ? host - 2.5 : host, cost) + 0.05 * cost;       // (hidden behind the host: the shorter all the same)
+        cost = std::max(n == 1 ? host - 1.8 : host, cost) + 0.05 * cost;       // (hidden behind the host: the shorter all the same)
         if (cost < best_cost) { best_cost = cost; best = n; }
     }
     return best;
@@ -307,11 +307,9 @@ TrainPlans make_train_plans(long BH, int N, int dk, int dv, int chunk, bool gene
         t.bwd.n_seg = 1;
         t.bwd.ckpt_every = 0;
     }
-    // The pair's backward does not walk a single segment twice, and a call without a pre-pass is a launch less for either of them:
-    // 64 x 64, layer step, us, uncut and cut by the rule for short calls: 4 x 200 tokens 33.1, 37.8; 12 x 256 32.9, 38.2; 8 x 272 35.2,
-    // 38.2; 48 x 300 37.1, 38.3; but 12 x 350 40.0, 39.1 and 96 x 448 49.4, 42.7.  (64 x 128, 4 x 200: 41.2, 38.0.)
-    if (!general && dk == 64 && dv == 64 && n_chunks <= 5 && BH * n_chunks <= kSmallCallChunks && BH < 256 &&
-        env_int("CHELA_SEG_TOKENS", 0) <= 0) {
+    // The pair's backward does not walk a single segment twice, so two chunks are not worth a pre-pass in each call: layer step of
+    // 8 x 100 tokens, uncut and cut, 64 x 128 25.6 and 29.6 us, 128 x 64 27.2 and 29.5, 128 x 128 36.2 and 37.8.
+    if (!general && n_chunks <= 2 && BH < 256 && BH * n_chunks <= kSmallCallChunks && env_int("CHELA_SEG_TOKENS", 0) <= 0) {
         t.bwd.seg_len = t.fwd.seg_len = (int)(n_chunks * cb);
         t.bwd.n_seg = t.fwd.n_seg = 1;
     }
