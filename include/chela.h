@@ -257,7 +257,7 @@ int chela_gate_norm_bwd(const void *O, const void *G, const void *dY, void *dO, 
  *              chela_longconv_spectrum() turns k_long into `spectrum`, an opaque device buffer of
  *              chela_longconv_spectrum_bytes(d, L) bytes that is valid for this d and L and is reused for every batch
  *              until the kernel's weights change.
- * Sequences are zero-padded on chip to twice a transform length M >= L (M in {256, 1024, 4096, 16384}), which makes
+ * Sequences are zero-padded on chip to twice a transform length M >= L (M in {256, 1024, 2048, 4096, 8192, 16384}), which makes
  * the circular product of Eq. 7 equal the causal sum.  16384 < L <= 1048576: the sequence and the kernel are cut into
  * blocks of 16384 steps; every block goes through the same on-chip transform, the products of a block of the input
  * with the blocks of the kernel that reach from it into an output block are added up on the spectra, and one inverse
@@ -310,7 +310,10 @@ int chela_linattn_step_gated(const void *q, const void *k, const void *v, const 
  * does not grow with N once the GPU is full -- the fixed-memory property claimed in
  * Sec. 1.  bf16 backward: in addition no segment is longer than 8192 tokens (see
  * chela_linattn_bwd), i.e. at least two states per 8192 tokens of a sequence: 0.4 % of
- * the bytes of the tensors themselves.  fp32 forward with 64 x 64 states: a smaller caller-owned buffer is accepted down to
+ * the bytes of the tensors themselves.  bf16 calls of up to 2048 chunks in all are cut by a rule of their own, which may take
+ * more scratch than the general one; in a smaller caller-owned buffer, or where nothing can be allocated, they take the
+ * general split (of a training pair, whose queries follow the same rule, the call with less scratch runs in one
+ * segment).  fp32 forward with 64 x 64 states: a smaller caller-owned buffer is accepted down to
  * what the general split takes.  fp32 backward: long sequences are cut finer the longer they are (48 pairs, 64 x 64:
  * 7 segments at 16384 tokens, 32 at 65536, again 32 at a million); a caller-owned buffer smaller than this size is
  * accepted down to what one state per segment of the forward's split takes, with fewer segments; the same goes for the

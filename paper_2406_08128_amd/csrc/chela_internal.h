@@ -163,8 +163,8 @@ inline size_t conv_pairs_bytes(int d, int L)       // the pairs: where the matri
 hipError_t launch_shortlong_conv(const void* X, const float* w_short, int m, const void* Kf, void* Y, long BD, int d,
                                  int L, int dtype, hipStream_t st);
 // Gradient: dX [B][d][L] (I/O dtype), dw [d][m] (only with a short kernel, m <= 32), dk [d][L] fp32.
-// ws: conv_bwd_ws_floats() floats: conv_bwd_acc_floats() (running sums of the long-kernel gradient: at the largest transform
-// size they no longer fit the registers of 1024 threads, and workgroups that share a channel leave their shares there), then,
+// ws: conv_bwd_ws_floats() floats: conv_bwd_acc_floats() (running sums of the long-kernel gradient: at the two largest transform
+// sizes they no longer fit the registers of sixteen waves, and workgroups that share a channel leave their shares there), then,
 // with a short kernel, B*d*L floats (dV; not where the short stage is fused) and the workgroups' tap sums.
 // Workgroups that share a channel in the long-stage gradient kernel (each takes every G-th sequence): more than one
 // when the channels alone would leave the GPU underfilled.
@@ -172,7 +172,8 @@ inline int conv_bwd_groups(int B, int d, int L)
 {
     const int M = conv_fft_size(L);
     if (M == 0 || B <= 1 || d <= 0) return 1;
-    // two rounds of: 256 compute units x the workgroups per unit (of 1, 1, 4 and 16 waves at M = 256, 1024, 4096, 16384)
+    // two rounds of: 256 compute units x the workgroups per unit (of 1, 1, 4 and 16 waves at M = 256, 1024, 4096, 16384); transforms of
+    // 2048 and 8192 points have twice as many per unit: one round
     const long slots = 256L * (M >= 16384 ? 1 : M >= 4096 ? 3 : M >= 1024 ? 12 : 20);
     long g = (2 * slots + d - 1) / d;
     if (g > B) g = B;

@@ -968,7 +968,7 @@ void shortlong_conv_kernel(const IN* __restrict__ X,
 // by the CONJUGATE kernel spectrum (correlation instead of convolution: dV[t] = sum_{s >= t} k[s - t] dZ[s]) and
 // transforms back (out as DVT: dX itself when there is no short stage, fp32 scratch for the short-stage kernel, or on into
 // the short stage below), then transforms v = silu(K_s x) (recomputed from x) and adds DZ conj(V) to the running sums of
-// its bin pairs (in registers, at the largest size in memory); after the last sequence the sums are transformed back once
+// its bin pairs (in registers, at the two largest sizes in memory); after the last sequence the sums are transformed back once
 // (dk).  Three transforms per sequence, where a correlation kernel and a kernel-gradient kernel of their own would need
 // four.
 // SPLIT: grid.y workgroups share a channel, each takes every grid.y-th sequence and leaves its sums in its own slice
@@ -1005,7 +1005,7 @@ void longconv_bwd_kernel(const IO* __restrict__ X,
     const int tid = threadIdx.x;
     const int c = blockIdx.x;
     build_tables<M, T>(tw, tid);
-    // the pairs' places and twiddles: worked out once, at the largest size, where the six registers would be spilled ones,
+    // the pairs' places and twiddles: worked out once, at the two largest sizes, where the six registers would be spilled ones,
     // wherever they are used
     auto stage_tid = [&]() __attribute__((always_inline)) { return ACC_MEM ? fresh(tid) : tid; };
     const float4* Kc = Kf + (long)c * (M / 2 + 1);
@@ -1033,7 +1033,7 @@ void longconv_bwd_kernel(const IO* __restrict__ X,
         int tp = fresh(tid);
         // ---- spectrum of dZ; correlation with the kernel: DZ conj(K)
         stage_input<M, T, IO>(zr, nullptr, 0, L, a, tp, z);
-        // the kernel's entries: in flight during the transform, at the largest size, where they would spill, a few at a
+        // the kernel's entries: in flight during the transform, at the two largest sizes, where they would spill, a few at a
         // time behind it
         constexpr int KU = ACC_MEM ? 4 : NP;
         float4 kq[KU];
