@@ -1181,6 +1181,7 @@ def test_sequence_host_path_and_the_bindings_own_lines_agree(dk, dv, dtype):
 @pytest.mark.parametrize("dk,dv", [(64, 64), (128, 64)])
 def test_layer_and_convolution_host_path_and_the_bindings_own_lines_agree(dk, dv, monkeypatch):
     # every further call that has a native host path: that it takes the plain call, and gives what the binding's own lines give
+    binding._load_step()
     taken = []
     host = binding._host
     monkeypatch.setattr(binding, "_host", lambda name: lambda *a: (lambda r: (taken.append((name, r is not None)), r)[1])(host(name)(*a)))
