@@ -115,7 +115,9 @@ int chela_linattn_fwd_noalloc(const void *Q, const void *K, const void *V, void 
                               int B, int H, int N, int dk, int dv, int chunk, void *stream);
 
 /* The same two maps with fp32 tensors and fp32 accuracy: operands keep all 24 bits (as three bf16 parts each on the matrix
- * cores), sums are fp32.  An infinity counts as a NaN; results below 2^-100 lose bits as their smallest parts run out of range. */
+ * cores), sums are fp32.  A segment that has operands (inputs, scores, states) between 0 and 2^-110, or results that are not finite, is
+ * worked out again with fp32 products, so that infinities, subnormal and largest values are what IEEE arithmetic makes of them; such a
+ * call takes two to three times as long, and all results of a segment with small operands may then differ in their last bits. */
 int chela_linattn_fwd_f32(const void *Q, const void *K, const void *V, void *O,
                           int B, int H, int N, int dk, int dv, int chunk, void *stream);
 int chela_linattn_bwd_f32(const void *Q, const void *K, const void *V, const void *dO,

@@ -9,13 +9,12 @@
 //
 // Arithmetic.  Every operand (tiles, scores, published state) is three bf16 parts that together hold all of its 24 bits, and a
 // product is the six products of parts that matter, each exact, summed in fp32: 6 x 32 cycles of the matrix pipe for 16 steps
-// of a 32 x 32 tile where the fp32 instruction takes 512.  Errors against 64 bits, 24 x 3001 tokens, 64 x 64: O 4.95e-7 with the
-// fp32 instruction, now 1.6e-7, gradients 2.6e-7, now 1.6e-7; the same or better over 7 shapes x 4 state sizes but for dK
-// of all-positive inputs with 128-wide values (3.0e-7, now 4.8e-7: the matrix unit cuts products off below the largest
-// of an instruction's).  What bounds it: instruction issue -- splitting a value takes 5.5 vector instructions -- and, with
-// the GPU full, power (1.5 .. 2.1 GHz).  Measured, us, fp32 instruction -> three parts: 24 x 3001, 64 x 64: forward 52.9 -> 39,
-// backward 94.9 -> 74; 64 x 4096, 64 x 64: 110 -> 84, 286 -> 224; 24 x 3001, 128 x 128: 127 -> 98, 343 -> 247; 16 x 400, 64 x 64:
-// 39 -> 11.6, 41 -> 18.4 (of these two 25 are the plan's).
+// of a 32 x 32 tile where the fp32 instruction takes 512.  Values that three parts do not hold are met with the fp32
+// instruction itself (Hard).  Errors against 64 bits, 24 x 3001 tokens, 64 x 64: O 4.95e-7 with the
+// fp32 instruction, now 1.6e-7, gradients 2.6e-7, now 1.6e-7.  What bounds it: instruction issue -- splitting a value takes 5.5 vector instructions, looking
+// at it 1.5 -- and, with the GPU full, power (1.5 .. 2.1 GHz).  Measured, us, fp32 instruction -> three parts: 24 x 3001, 64 x 64:
+// forward 51.8 -> 40.3, backward 94 -> 77; 64 x 4096, 64 x 64: 109 -> 91, 284 -> 239; 24 x 3001, 128 x 128: 127 -> 108, 343 -> 277;
+// 16 x 400, 64 x 64: 39 -> 11.2, 41 -> 19.0 (of these two 25 are the plan's).
 // Two halves in fp16 would be half the instructions, but 22 bits, and a token 2^30 louder than its chunk would cost the others
 // theirs.
 #include "chela_internal.h"
@@ -257,7 +256,8 @@ typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 
 // Two fp32 values as the sums of three bf16 ones, packed in pairs (first value in the low half): the leading part is cut
 // off, not rounded, so that it stays finite for every finite value; its remainder is exact, 16 bits wide, and leaves 8 bits
-// or fewer behind the second part.  All 24 bits are there: h + m + l is the value.
+// or fewer behind the second part.  All 24 bits are there: h + m + l is the value, where it is none of those
+// that Hard looks out for.
 struct Pair3 { unsigned h, m, l; };
 __device__ __forceinline__ unsigned cvt_pk_bf16(float lo, float hi)      // round to nearest even
 {
@@ -274,6 +274,36 @@ __device__ __forceinline__ Pair3 split_pair(float x0, float x1)
     const unsigned l = cvt_pk_bf16(r0 - __builtin_bit_cast(float, m << 16), r1 - __builtin_bit_cast(float, m & 0xffff0000u));
     return {__builtin_amdgcn_perm(u1, u0, 0x07060302u), m, l};
 }
+
+// What three parts cannot hold: values that are not zero and below 2^-110 (their last bits lie below the smallest bf16 value,
+// 2^-133), and infinities.  The first are looked for among all operands (three vector
+// instructions on two values: twice the bits, less those of 2^-110, wrap round to more than a zero's); the others leave
+// a NaN or an infinity in every result they reach, so it is enough to look at the results.  A workgroup that met
+// any of them does its segment over with the fp32 instruction, which takes every value as it is: 24 x 3001 tokens with a small
+// query in every row, 64 x 64, forward and backward, 292 us instead of 118.  Looking costs 3 to 4 % of a call (two instructions fewer per
+// pair, where no zero is near, and a branch: no gain).
+struct Hard {
+    static constexpr unsigned kLeast = 2u * 0x08800000u;
+    enum { kBad = 1, kTiny = 2 };
+    unsigned tiny = 0u;
+    float bad = 0.f;
+    __device__ __forceinline__ void operands(float x, float y)
+    {
+        tiny = max(tiny, max((__builtin_bit_cast(unsigned, x) << 1) - kLeast, (__builtin_bit_cast(unsigned, y) << 1) - kLeast));
+        asm("" : "+v"(tiny));       // (opaque: as one maximum over all of a tile the terms would all be worked out before the first is used)
+    }
+    __device__ __forceinline__ void result(float x) { bad = fmaf(x, 0.f, bad); }
+    // What any of the workgroup's lanes met.  votes: four words of LDS that nothing else uses.
+    __device__ __forceinline__ int anywhere(int* votes, int w, int lane) const
+    {
+        const int mine = (__any(tiny > 0u - kLeast) ? kTiny : 0) | (__any(!(bad == 0.f)) ? kBad : 0);
+        if (lane == 0) votes[w] = mine;
+        __syncthreads();
+        return __builtin_amdgcn_readfirstlane(votes[0] | votes[1] | votes[2] | votes[3]);
+    }
+    // Of a result and what it was at first: without small operands a finite one was right, and keeps its bits.
+    static __device__ __forceinline__ float choose(int met, float again, float first) { return met & kTiny || !(first - first == 0.f) ? again : first; }
+};
 
 // An operand of the 32x32x16 instruction in its three parts.
 struct Op3 { bf16x8 h, m, l; };
@@ -388,11 +418,13 @@ struct TileRegsF32 {
 #pragma unroll
         for (int n = 0; n < NV; ++n) v[n] = rows.load4(rows.at(tid / V4 + 256 / V4 * n) + (int)(tid % V4) * 16);
     }
-    __device__ __forceinline__ void stash(bf16* lds, unsigned tid) const
+    __device__ __forceinline__ void stash(bf16* lds, unsigned tid, Hard& hard) const
     {
 #pragma unroll
         for (int n = 0; n < NV; ++n) {
             const int row = tid / V4 + 256 / V4 * n, c4 = tid % V4;
+            hard.operands(v[n].x, v[n].y);
+            hard.operands(v[n].z, v[n].w);
             const Pair3 p0 = split_pair(v[n].x, v[n].y), p1 = split_pair(v[n].z, v[n].w);
             bf16* d = lds + tile_at<D>(row, c4 >> 1) + 4 * (c4 & 1);
             *reinterpret_cast<u32x2*>(d) = u32x2{p0.h, p1.h};
@@ -438,6 +470,146 @@ __device__ __forceinline__ void state_tiles(f32x16* acc, const bf16* k, const bf
         for (int e = 0; e < 16; ++e) acc[n][e] += t[n][e];
 }
 
+// ------------------------------------------------------------------------------------------------ the same on fp32 instructions
+// For the segments with values that three bf16 parts do not hold (Hard), which no ordinary input has: v_mfma_f32_32x32x2_f32, one
+// float of A and one of B per lane, 4-byte reads from row-major tiles in LDS with odd leading dimensions.  Nothing is prefetched.
+__device__ __forceinline__ f32x16 gemm_tile_exact(int k_steps, f32x16 acc, const float* a, int a_rs, int a_ks, const float* b, int b_ks,
+                                                  int b_ns, int lane)
+{
+    const int r = lane & 31, h = lane >> 5;
+    const float *pa = a + r * a_rs + h * a_ks, *pb = b + h * b_ks + r * b_ns;
+#pragma unroll 8
+    for (int k = 0; k < k_steps; k += 2) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(pa[k * a_ks], pb[k * b_ks], acc, 0, 0, 0);
+    return acc;
+}
+
+template <int C, int D>
+__device__ __forceinline__ void stage_exact(float* lds, const ChunkRows<C, D>& rows, int tid)
+{
+#pragma unroll 4
+    for (int x = tid; x < C * (D / 4); x += 256) {
+        const int row = x / (D / 4), c4 = x % (D / 4);
+        const float4 v = rows.load4(rows.at(row) + c4 * 16);
+        float* d = lds + row * (D + 1) + c4 * 4;
+        d[0] = v.x; d[1] = v.y; d[2] = v.z; d[3] = v.w;
+    }
+}
+
+// acc[n] += K^T V over the R tokens in LDS, tiles w, w + 4, ...; the tokens summed up by themselves first.
+template <int R, int DK, int DV, int NT>
+__device__ __forceinline__ void state_tiles_exact(f32x16 (&acc)[NT], const float* k, const float* v, int w, int lane)
+{
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+        const int id = w + 4 * n, ib = id / (DV / 32), jb = id % (DV / 32);
+        const f32x16 t = gemm_tile_exact(R, zero16f(), k + ib * 32, 1, DK + 1, v + jb * 32, DV + 1, 1, lane);
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[n][e] += t[e];
+    }
+}
+
+template <int R, int DK, int DV>
+__device__ __forceinline__ void f32_seg_state_exact(const float* Kb, const float* Vb, float* o, int p0, int p1, int N, bool rev, float* lds,
+                                                    int tid, int w, int met)
+{
+    constexpr int JB = DV / 32, NT = (DK / 32) * JB / 4;
+    float *sK = lds, *sV = lds + R * (DK + 1);
+    const int lane = tid & 63, r = lane & 31, h = lane >> 5;
+    f32x16 acc[NT];
+#pragma unroll
+    for (int n = 0; n < NT; ++n) acc[n] = zero16f();
+    for (int c0 = p0; c0 < p1; c0 += R) {
+        __syncthreads();
+        stage_exact<R, DK>(sK, ChunkRows<R, DK>(Kb, c0, p1, N, rev), tid);
+        stage_exact<R, DV>(sV, ChunkRows<R, DV>(Vb, c0, p1, N, rev), tid);
+        __syncthreads();
+        state_tiles_exact<R, DK, DV, NT>(acc, sK, sV, w, lane);
+    }
+#pragma unroll
+    for (int n = 0; n < NT; ++n) {
+        const int id = w + 4 * n, ib = id / JB, jb = id % JB;
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            float* at = o + (ib * 32 + 8 * (e >> 2) + 4 * h + (e & 3)) * DV + jb * 32 + r;
+            *at = Hard::choose(met, acc[n][e], *at);
+        }
+    }
+}
+
+// LDS: Q, K [C][DK+1]; V [C][DV+1]; S [DK][DV+1]; the scores [C][C+1] in K's place once it has been read.  s0, n_s0: as in f32_sweep_body.
+constexpr int f32_exact_kp(int c, int dk) { return c * (dk + 1) > c * (c + 1) ? c * (dk + 1) : c * (c + 1); }
+constexpr int f32_exact_lds(int c, int dk, int dv) { return c * (dk + 1) + f32_exact_kp(c, dk) + (c + dk) * (dv + 1); }     // floats
+
+template <int C, int DK, int DV>
+__device__ __forceinline__ void f32_sweep_exact(const float* Qb, const float* Kb, const float* Vb, float* Ob, const float* s0, int n_s0,
+                                                bool s0_transposed, int p0, int p1, int N, bool rev, float* lds, int tid, int w,
+                                                int met)
+{
+    constexpr int LDK = DK + 1, LDV = DV + 1, LDP = C + 1;
+    constexpr int TB = C / 32, JB = DV / 32, IB = DK / 32, WJ = 4 / TB, NJ = JB / WJ, NS = IB * JB / 4;
+    float *sQ = lds, *sK = sQ + C * LDK, *sV = sK + f32_exact_kp(C, DK), *sS = sV + C * LDV, *sP = sK;
+    const int tb = w % TB, jg = w / TB;
+    f32x16 accS[NS];
+#pragma unroll
+    for (int n = 0; n < NS; ++n) {
+        const int id = w + 4 * n, i0 = id / JB * 32 + 4 * ((tid & 63) >> 5), j = id % JB * 32 + (tid & 31);
+        accS[n] = zero16f();
+        const float* p = s0 + (s0_transposed ? j * DK + i0 : i0 * DV + j);
+        const int step = s0_transposed ? 1 : DV;
+#pragma unroll 1
+        for (int k = 0; k < n_s0; ++k, p += DK * DV)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) accS[n][e] += p[(8 * (e >> 2) + (e & 3)) * step];
+    }
+#pragma unroll 1
+    for (int c0 = p0; c0 < p1; c0 += C) {
+        asm volatile("" : "+v"(tid));       // (opaque: nothing that depends on the lane alone is kept in registers across the loop)
+        const int lane = tid & 63, r = lane & 31, h = lane >> 5;
+        __syncthreads();
+        stage_exact<C, DK>(sQ, ChunkRows<C, DK>(Qb, c0, p1, N, rev), tid);
+        stage_exact<C, DK>(sK, ChunkRows<C, DK>(Kb, c0, p1, N, rev), tid);
+        stage_exact<C, DV>(sV, ChunkRows<C, DV>(Vb, c0, p1, N, rev), tid);
+#pragma unroll
+        for (int n = 0; n < NS; ++n) {
+            const int id = w + 4 * n, ib = id / JB, jb = id % JB;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) sS[(ib * 32 + 8 * (e >> 2) + 4 * h + (e & 3)) * LDV + jb * 32 + r] = accS[n][e];
+        }
+        __syncthreads();
+        // scores of the tiles on and below the diagonal (the WJ waves of a row block share them out), then the state
+        constexpr int NP = (TB + WJ - 1) / WJ;
+        f32x16 pt[NP];
+#pragma unroll
+        for (int sb = 0; sb < TB; ++sb)
+            if (sb <= tb && sb % WJ == jg)
+                pt[sb / WJ] = gemm_tile_exact(DK, zero16f(), sQ + tb * 32 * LDK, LDK, 1, sK + sb * 32 * LDK, 1, LDK, lane);
+        if (c0 + C < p1) state_tiles_exact<C, DK, DV, NS>(accS, sK, sV, w, lane);
+        __syncthreads();
+#pragma unroll
+        for (int sb = 0; sb < TB; ++sb)
+            if (sb <= tb && sb % WJ == jg)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int row = 8 * (e >> 2) + 4 * h + (e & 3);
+                    sP[(tb * 32 + row) * LDP + sb * 32 + r] = sb == tb && r > row ? 0.f : pt[sb / WJ][e];
+                }
+        __syncthreads();
+        const ChunkRows<C, DV> out(Ob, c0, p1, N, rev);
+#pragma unroll
+        for (int n = 0; n < NJ; ++n) {
+            const int j0 = (jg * NJ + n) * 32;
+            f32x16 acc = gemm_tile_exact(DK, zero16f(), sQ + tb * 32 * LDK, LDK, 1, sS + j0, LDV, 1, lane);
+            acc = gemm_tile_exact(32 * (tb + 1), acc, sP + tb * 32 * LDP, LDP, 1, sV + j0, LDV, 1, lane);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int off = out.at(tb * 32 + 8 * (e >> 2) + 4 * h + (e & 3)) + (j0 + r) * 4;
+                const float first = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(out.rs, off, 0, 0));
+                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, Hard::choose(met, acc[e], first)), out.rs, off, 0, 0);
+            }
+        }
+    }
+}
+
 // ------------------------------------------------------------------------------------------------ segment totals
 // out[bh][seg][i*DV + j] = sum over the segment's tokens of K[t][i] * V[t][j].  The last segment's total is never
 // used by an exclusive prefix, so its workgroups leave at once.  Wave w owns output tiles w, w+4, ...
@@ -447,7 +619,7 @@ constexpr int f32_seg_lds(int dk, int dv) { return kF32SegRows * (dk + dv) * 3; 
 template <int DK, int DV>
 __device__ __forceinline__ void f32_seg_state_body(const float* __restrict__ K, const float* __restrict__ V,
                                                    float* __restrict__ out, int N, int seg_len, int n_seg, bool rev,
-                                                   bf16* lds)
+                                                   bf16* lds, int* votes)
 {
     constexpr int R = kF32SegRows;
     bf16* sK = lds;
@@ -461,6 +633,8 @@ __device__ __forceinline__ void f32_seg_state_body(const float* __restrict__ K, 
     const float* Vb = V + (size_t)bh * N * DV;
     const int p0 = seg * seg_len, p1 = min(N, p0 + seg_len);
     constexpr int JB = DV / 32, NT = (DK / 32) * JB / 4;
+    static_assert(R * (DK + DV + 2) * 4 <= f32_seg_lds(DK, DV) * 2, "the fp32 tiles of a segment done over");
+    Hard hard;
     f32x16 acc[NT];
 #pragma unroll
     for (int n = 0; n < NT; ++n) acc[n] = zero16f();
@@ -479,8 +653,8 @@ __device__ __forceinline__ void f32_seg_state_body(const float* __restrict__ K, 
             const int c0 = cc + u * R;
             if (c0 >= p1) break;
             __syncthreads();
-            rk[u].stash(sK, tid);
-            rv[u].stash(sV, tid);
+            rk[u].stash(sK, tid, hard);
+            rv[u].stash(sV, tid, hard);
             __syncthreads();
             rk[u].fetch(ChunkRows<R, DK>(Kb, c0 + 2 * R, p1, N, rev), tid);
             rv[u].fetch(ChunkRows<R, DV>(Vb, c0 + 2 * R, p1, N, rev), tid);
@@ -489,7 +663,11 @@ __device__ __forceinline__ void f32_seg_state_body(const float* __restrict__ K, 
         }
     }
     float* o = out + ((size_t)bh * n_seg + seg) * DK * DV;
-    const int r = lane & 31, h = lane >> 5;
+#pragma unroll
+    for (int n = 0; n < NT; ++n)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) hard.result(acc[n][e]);
+    const int met = hard.anywhere(votes, w, lane), r = lane & 31, h = lane >> 5;
 #pragma unroll
     for (int n = 0; n < NT; ++n) {
         const int id = w + 4 * n, ib = id / JB, jb = id % JB;
@@ -498,26 +676,35 @@ __device__ __forceinline__ void f32_seg_state_body(const float* __restrict__ K, 
 #pragma unroll
             for (int b = 0; b < 4; ++b) o[(ib * 32 + 8 * a + 4 * h + b) * DV + jb * 32 + r] = acc[n][4 * a + b];
     }
+    if (met) {
+        __builtin_amdgcn_s_waitcnt(0x0f70);     // vmcnt(0): each lane reads again what it has written
+        f32_seg_state_exact<R, DK, DV>(Kb, Vb, o, p0, p1, N, rev, reinterpret_cast<float*>(lds), tid, w, met);
+    }
 }
 
+// (64 x 128: as many waves per SIMD as the LDS has room for workgroups)
 template <int DK, int DV>
-__global__ __launch_bounds__(256) void f32_seg_state_kernel(const float* __restrict__ K, const float* __restrict__ V,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DK + DV == 128 ? 3 : DK + DV == 192 ? 2 : 1)))
+void f32_seg_state_kernel(const float* __restrict__ K, const float* __restrict__ V,
                                                            float* __restrict__ out, int N, int seg_len, int n_seg)
 {
     __shared__ __attribute__((aligned(16))) bf16 lds[f32_seg_lds(DK, DV)];
-    f32_seg_state_body<DK, DV>(K, V, out, N, seg_len, n_seg, false, lds);
+    __shared__ int votes[4];
+    f32_seg_state_body<DK, DV>(K, V, out, N, seg_len, n_seg, false, lds, votes);
 }
 
 // The backward's two sets of totals, V^T K in reading order and Q^T dO from the end, side by side on grid.z.
 template <int DK, int DV>
-__global__ __launch_bounds__(256) void f32_bwd_seg_state_kernel(const float* __restrict__ Q, const float* __restrict__ K,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(DK + DV == 128 ? 3 : DK + DV == 192 ? 2 : 1)))
+void f32_bwd_seg_state_kernel(const float* __restrict__ Q, const float* __restrict__ K,
                                                                const float* __restrict__ V, const float* __restrict__ dO,
                                                                float* __restrict__ out, size_t array_stride, int N,
                                                                int seg_len, int n_seg)
 {
     __shared__ __attribute__((aligned(16))) bf16 lds[f32_seg_lds(DK, DV)];
-    if (blockIdx.z == 0) f32_seg_state_body<DV, DK>(V, K, out, N, seg_len, n_seg, false, lds);
-    else f32_seg_state_body<DK, DV>(Q, dO, out + array_stride, N, seg_len, n_seg, true, lds);
+    __shared__ int votes[4];
+    if (blockIdx.z == 0) f32_seg_state_body<DV, DK>(V, K, out, N, seg_len, n_seg, false, lds, votes);
+    else f32_seg_state_body<DK, DV>(Q, dO, out + array_stride, N, seg_len, n_seg, true, lds, votes);
 }
 
 // ------------------------------------------------------------------------------------------------ main sweep
@@ -535,13 +722,14 @@ template <int C, int DK, int DV>
 __device__ __forceinline__ void f32_sweep_body(const float* __restrict__ Q, const float* __restrict__ K,
                                                const float* __restrict__ V, float* __restrict__ O,
                                                const float* __restrict__ S0, int N, int seg_len, int n_seg, bool rev,
-                                               bool s0_transposed, bool folded, bf16* lds)
+                                               bool s0_transposed, bool folded, bf16* lds, int* votes)
 {
     constexpr int TB = C / 32, JB = DV / 32, IB = DK / 32, KK = DK / 16;
     constexpr int WJ = 4 / TB, NJ = JB / WJ;
     // State tiles: column tiles jg*NJ .. of S belong to the TB waves that share jg, in equal parts.
     constexpr int NS = IB * NJ / TB;
     static_assert(JB % WJ == 0 && (TB == 1 || TB == 2), "unsupported tile shape");
+    static_assert(f32_exact_lds(C, DK, DV) * 4 <= f32_sweep_lds(DK, DV) * 2, "the fp32 tiles of a segment done over");
     bf16* sK = lds;
     bf16* sV = sK + 3 * C * DK;
     bf16* sS = sV + 3 * C * DV;
@@ -557,6 +745,7 @@ __device__ __forceinline__ void f32_sweep_body(const float* __restrict__ Q, cons
     float* Ob = O + (size_t)bh * N * DV;
     const int p0 = seg * seg_len, p1 = min(N, p0 + seg_len);
     const int q_own = tb * NS;
+    Hard hard;
 
     // (the first chunk's tiles are asked for first: they are what the loop waits for)
     TileRegsF32<C, DK> rk;
@@ -622,6 +811,8 @@ __device__ __forceinline__ void f32_sweep_body(const float* __restrict__ Q, cons
         auto split_q = [&](int kk) __attribute__((always_inline)) {
             const float4 x = rq[2 * kk], y = rq[2 * kk + 1];
             const float e[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+#pragma unroll
+            for (int q = 0; q < 8; q += 2) hard.operands(e[q], e[q + 1]);
             aQ[kk] = split8(e);
         };
         // scores of keys 16 x .. 16 x + 15 of the block as first operand: the accumulator tile holds them as it wants them
@@ -631,6 +822,7 @@ __device__ __forceinline__ void f32_sweep_body(const float* __restrict__ Q, cons
             for (int q = 0; q < 8; ++q) {
                 const int row = 16 * x + 8 * (q >> 2) + 4 * (ln >> 5) + (q & 3);        // key within the block; ln & 31 = query
                 const float v = pT[8 * x + q];
+                if (q & 1) hard.operands(pT[8 * x + q - 1], v);
                 e[q] = !mask || row <= (ln & 31) ? v : 0.f;
             }
             aP[x] = split8(e);
@@ -693,10 +885,12 @@ __device__ __forceinline__ void f32_sweep_body(const float* __restrict__ Q, cons
 #pragma unroll
             for (int a = 0; a < 4; ++a)
 #pragma unroll
-                for (int b = 0; b < 4; ++b)
+                for (int b = 0; b < 4; ++b) {
                     // (a streaming store: 32 lanes write one whole 128-byte line, and nothing here reads it again)
-                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, hi[n][4 * a + b] + lo[n][4 * a + b]), rows.rs,
-                                                          off + (8 * a + b) * step + n * 128, 0, 2);
+                    const float v = hi[n][4 * a + b] + lo[n][4 * a + b];
+                    hard.result(v);
+                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, v), rows.rs, off + (8 * a + b) * step + n * 128, 0, 2);
+                }
         // state update S += K^T V (not needed after the segment's last chunk)
         if (more)
             state_tiles<C, DK, DV, NS>(accS, sK, sV, ln, [&](int n) { return (q_own + n) % IB * 32; },
@@ -710,13 +904,15 @@ __device__ __forceinline__ void f32_sweep_body(const float* __restrict__ Q, cons
         unsigned tv = tid;       // (opaque, as in products())
         asm volatile("" : "+v"(tv));
         __syncthreads();   // previous chunk fully consumed
-        rk.stash(sK, tv);
-        rv.stash(sV, tv);
+        rk.stash(sK, tv, hard);
+        rv.stash(sV, tv, hard);
         // publish the state before this chunk, [j][i]: a lane holds four consecutive i of one j
 #pragma unroll
         for (int n = 0; n < NS; ++n) {
             {
                 const int q = q_own + n, ib = q % IB, jb = jg * NJ + q / IB;
+#pragma unroll
+                for (int e = 0; e < 16; e += 2) hard.operands(accS[n][e], accS[n][e + 1]);
 #pragma unroll
                 for (int a = 0; a < 4; ++a) {
                     const Pair3 x = split_pair(accS[n][4 * a], accS[n][4 * a + 1]), y = split_pair(accS[n][4 * a + 2], accS[n][4 * a + 3]);
@@ -739,6 +935,10 @@ __device__ __forceinline__ void f32_sweep_body(const float* __restrict__ Q, cons
         products(c0, more);
         c0 += C;
     } while (c0 < p1);
+    if (const int met = hard.anywhere(votes, w, lane)) {
+        __builtin_amdgcn_s_waitcnt(0x0f70);     // vmcnt(0): each lane reads again what it has written
+        f32_sweep_exact<C, DK, DV>(Qb, Kb, Vb, Ob, s0, n_s0, s0_transposed, p0, p1, N, rev, reinterpret_cast<float*>(lds), tid, w, met);
+    }
 }
 
 // (64 x 64: two workgroups fit a compute unit's LDS, so the registers have to allow for two waves per SIMD)
@@ -748,7 +948,8 @@ void f32_sweep_kernel(const float* __restrict__ Q, const float* __restrict__ K, 
                       const float* __restrict__ S0, int N, int seg_len, int n_seg, bool folded)
 {
     __shared__ __attribute__((aligned(16))) bf16 lds[f32_sweep_lds(DK, DV)];
-    f32_sweep_body<f32_sweep_chunk(DK, DV), DK, DV>(Q, K, V, O, S0, N, seg_len, n_seg, false, false, folded, lds);
+    __shared__ int votes[4];
+    f32_sweep_body<f32_sweep_chunk(DK, DV), DK, DV>(Q, K, V, O, S0, N, seg_len, n_seg, false, false, folded, lds, votes);
 }
 
 // The gradient is three instances of the forward map (time-reversal duality), independent of one another, so they ride
@@ -765,16 +966,17 @@ void f32_bwd_sweep_kernel(const float* __restrict__ Q, const float* __restrict__
     constexpr int C = f32_sweep_chunk(DK, DV);
     constexpr int LA = f32_sweep_lds(DK, DV), LB = f32_sweep_lds(DV, DK);
     __shared__ __attribute__((aligned(16))) bf16 lds[LA > LB ? LA : LB];
+    __shared__ int votes[4];
     const int z = blockIdx.z;
     const float* S1 = S0 != nullptr ? S0 + array_stride : nullptr;
     if constexpr (DK == DV) {
         f32_sweep_body<C, DK, DV>(z == 0 ? dO : z == 1 ? V : K, z == 0 ? V : z == 1 ? dO : Q, z == 0 ? K : z == 1 ? Q : dO,
-                                  z == 0 ? dQ : z == 1 ? dK : dV, z == 0 ? S0 : S1, N, seg_len, n_seg, z != 0, z == 1, folded, lds);
+                                  z == 0 ? dQ : z == 1 ? dK : dV, z == 0 ? S0 : S1, N, seg_len, n_seg, z != 0, z == 1, folded, lds, votes);
     } else if (z < 2) {
         f32_sweep_body<C, DV, DK>(z == 0 ? dO : V, z == 0 ? V : dO, z == 0 ? K : Q, z == 0 ? dQ : dK, z == 0 ? S0 : S1, N,
-                                  seg_len, n_seg, z != 0, z == 1, folded, lds);
+                                  seg_len, n_seg, z != 0, z == 1, folded, lds, votes);
     } else {
-        f32_sweep_body<C, DK, DV>(K, Q, dO, dV, S1, N, seg_len, n_seg, true, false, folded, lds);
+        f32_sweep_body<C, DK, DV>(K, Q, dO, dV, S1, N, seg_len, n_seg, true, false, folded, lds, votes);
     }
 }
 

@@ -578,6 +578,83 @@ def test_f32_non_finite_values_stay_where_they_belong(dims, bad):
         assert torch.equal(got[0, 1], O[0, 1])
 
 
+@pytest.mark.parametrize("seg", [None, 128])
+@pytest.mark.parametrize("dims", [(64, 64), (64, 128), (128, 64), (128, 128)])
+def test_f32_small_operands_keep_their_bits(dims, seg, monkeypatch):
+    # operands (inputs, scores, states) whose last bits lie below the smallest bf16 value, 2^-133, subnormal ones among them, with
+    # partners so large that the results are ordinary
+    if seg:
+        monkeypatch.setenv("CHELA_SEG_TOKENS", str(seg))
+    w = _small("f32", N=300, B=1, H=2, dk=dims[0], dv=dims[1], seed=63)
+    x = make_inputs(w)
+    n = lambda t: to_f64_numpy(t)
+
+    def run(**t):
+        d = _dev(t)
+        ref = (oracle.fwd_recurrent(n(t["Q"]), n(t["K"]), n(t["V"])),) + tuple(oracle.bwd_recurrent(*(n(t[k]) for k in ("Q", "K", "V", "dO"))))
+        got = (binding.chela_linattn_fwd(d["Q"], d["K"], d["V"]),) + tuple(binding.chela_linattn_bwd(d["Q"], d["K"], d["V"], d["dO"]))
+        for name, g, r in zip(("O", "dQ", "dK", "dV"), got, ref):
+            _check(name, g, r, "f32")
+
+    # (small: keys; subnormal keys; scores; the gradient's scores; states -- and every result between 2^-115 and 2^123)
+    for a, b, c, e in ((100, -118, 0, 10), (90, -135, 30, -10), (-60, -62, 90, 20), (20, 90, -60, -62), (90, -60, -58, 30)):
+        run(**{k: x[k] * 2.0 ** s for k, s in zip(("Q", "K", "V", "dO"), (a, b, c, e))})
+    for big, small in (("Q", "K"), ("K", "Q")):          # one feature of ordinary ones
+        t = {k: v.clone() for k, v in x.items()}
+        t[big][..., 5] *= 2.0 ** 118
+        t[small][..., 5] *= 2.0 ** -118
+        d = _dev(t)
+        _check("O", binding.chela_linattn_fwd(d["Q"], d["K"], d["V"]), oracle.fwd_recurrent(*(n(t[k]) for k in "QKV")), "f32")
+
+
+@pytest.mark.parametrize("seg", [None, 128])
+@pytest.mark.parametrize("dims", [(64, 64), (64, 128), (128, 64), (128, 128)])
+def test_f32_infinities_and_the_largest_values(dims, seg, monkeypatch):
+    # an infinity among positive inputs (not in a sequence's first or last chunk, where it would meet a state of zeros): infinite wherever
+    # it has a part in a result, and where it has none the bits of the call without it; the largest finite values, times
+    # small ones, are finite
+    if seg:
+        monkeypatch.setenv("CHELA_SEG_TOKENS", str(seg))
+    w = _small("f32", N=450, B=1, H=2, dk=dims[0], dv=dims[1], seed=64)
+    x = {k: v.abs() + 0.01 for k, v in make_inputs(w).items()}
+    d = _dev(x)
+    inf = float("inf")
+    O = binding.chela_linattn_fwd(d["Q"], d["K"], d["V"])
+    g = dict(zip(("dQ", "dK", "dV"), binding.chela_linattn_bwd(d["Q"], d["K"], d["V"], d["dO"])))
+    for t in (64, 95, 130, 385):
+        own, later, earlier = slice(t, t + 1), slice(t, None), slice(None, t + 1)
+        # (input; the rows of each result it has a part in, all features where there is no number)
+        for name, col, reach in (("Q", 5, {"O": own, "dK": (earlier, 5), "dV": earlier}), ("K", 5, {"O": later, "dQ": (later, 5), "dV": own}),
+                                 ("V", 7, {"O": (later, 7), "dQ": later, "dK": own}), ("dO", 7, {"dQ": own, "dK": earlier, "dV": (earlier, 7)})):
+            c = {k: v.clone() for k, v in d.items()}
+            c[name][0, 0, t, col] = inf
+            got = {"O": binding.chela_linattn_fwd(c["Q"], c["K"], c["V"])}
+            got.update(zip(("dQ", "dK", "dV"), binding.chela_linattn_bwd(c["Q"], c["K"], c["V"], c["dO"])))
+            for k, ref in [("O", O)] + list(g.items()):
+                at = torch.zeros(w.N, ref.shape[-1], dtype=torch.bool, device="cuda")
+                if k in reach:
+                    at[reach[k][0] if type(reach[k]) is tuple else reach[k], reach[k][1] if type(reach[k]) is tuple else slice(None)] = True
+                assert bool((got[k][0, 0][at] == inf).all()), (name, t, k)
+                # (the masked half of its own block of 32 rows: 0 times an infinity)
+                rest = ~at
+                if k in reach and type(reach[k]) is tuple:
+                    rest[t // 32 * 32:t // 32 * 32 + 32, reach[k][1]] = False
+                if k in reach and w.N % 64:              # (from the end the blocks count from the last row)
+                    lo = max(0, w.N - ((w.N - 1 - t) // 32 * 32 + 32))
+                    if type(reach[k]) is tuple:
+                        rest[lo:lo + 32, reach[k][1]] = False
+                assert torch.equal(got[k][0, 0][rest], ref[0, 0][rest]) and torch.equal(got[k][0, 1], ref[0, 1]), (name, t, k)
+    top = torch.finfo(torch.float32).max
+    for big, small in (("Q", "K"), ("K", "Q")):
+        t = {k: v.clone() for k, v in x.items()}
+        t[big][..., 5] = -top
+        t[small][..., 5] *= 2.0 ** -100
+        if big == "K":
+            t["V"] *= 2.0 ** -20               # (or the sums over the tokens overflow)
+        c = _dev(t)
+        _check("O", binding.chela_linattn_fwd(c["Q"], c["K"], c["V"]), oracle.fwd_recurrent(*(to_f64_numpy(t[k]) for k in "QKV")), "f32")
+
+
 @pytest.mark.parametrize("shape", [(96, 1029, 64, 128), (96, 2047, 64, 64), (112, 1000, 128, 64), (90, 1025, 128, 128)])
 def test_f32_backward_split_where_one_segment_would_fill_the_gpu(shape):
     # three workgroups per segment and 256 or more at one segment per sequence: split all the same, ragged ends included.
