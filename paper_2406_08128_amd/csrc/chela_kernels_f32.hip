@@ -254,10 +254,9 @@ typedef __attribute__((ext_vector_type(4))) unsigned u32x4;
 typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 
-// Two fp32 values as the sums of three bf16 ones, packed in pairs (first value in the low half): the leading part is cut
-// off, not rounded, so that it stays finite for every finite value; its remainder is exact, 16 bits wide, and leaves 8 bits
-// or fewer behind the second part.  All 24 bits are there: h + m + l is the value, where it is none of those
-// that Hard looks out for.
+// Two fp32 values as the sums of three bf16 ones, packed in pairs (first value in the low half), each part the remainder before it
+// rounded to nearest: |m| <= 2^-8 |x|, |l| <= 2^-17 |x|, and what is behind l is nothing, because the remainders are exact and 15 and 6
+// bits wide: h + m + l is the value, where it is none of those that Hard looks out for.
 struct Pair3 { unsigned h, m, l; };
 __device__ __forceinline__ unsigned cvt_pk_bf16(float lo, float hi)      // round to nearest even
 {
@@ -268,15 +267,15 @@ __device__ __forceinline__ unsigned cvt_pk_bf16(float lo, float hi)      // roun
 }
 __device__ __forceinline__ Pair3 split_pair(float x0, float x1)
 {
-    const unsigned u0 = __builtin_bit_cast(unsigned, x0), u1 = __builtin_bit_cast(unsigned, x1);
-    const float r0 = x0 - __builtin_bit_cast(float, u0 & 0xffff0000u), r1 = x1 - __builtin_bit_cast(float, u1 & 0xffff0000u);
+    const unsigned h = cvt_pk_bf16(x0, x1);
+    const float r0 = x0 - __builtin_bit_cast(float, h << 16), r1 = x1 - __builtin_bit_cast(float, h & 0xffff0000u);
     const unsigned m = cvt_pk_bf16(r0, r1);
     const unsigned l = cvt_pk_bf16(r0 - __builtin_bit_cast(float, m << 16), r1 - __builtin_bit_cast(float, m & 0xffff0000u));
-    return {__builtin_amdgcn_perm(u1, u0, 0x07060302u), m, l};
+    return {h, m, l};
 }
 
 // What three parts cannot hold: values that are not zero and below 2^-110 (their last bits lie below the smallest bf16 value,
-// 2^-133), and infinities.  The first are looked for among all operands (three vector
+// 2^-133), infinities, and values that round to one as bf16.  The first are looked for among all operands (three vector
 // instructions on two values: twice the bits, less those of 2^-110, wrap round to more than a zero's); the others leave
 // a NaN or an infinity in every result they reach, so it is enough to look at the results.  A workgroup that met
 // any of them does its segment over with the fp32 instruction, which takes every value as it is: 24 x 3001 tokens with a small
@@ -308,8 +307,8 @@ struct Hard {
 // An operand of the 32x32x16 instruction in its three parts.
 struct Op3 { bf16x8 h, m, l; };
 
-// acc += A B with the six products of parts that reach 2^-24 of the whole, the small ones first.  What is left out
-// (m l, l m, l l) is below 2^-25 of a product and of either sign; a product of two parts is exact in fp32.
+// acc += A B with six products of parts, the small ones first; a product of two parts is exact in fp32.  What is left out (m l, l m,
+// l l) is at most 2^-24 of a product, what rounding it once could cost; with a leading part cut off instead of rounded it was up to 2^-22.
 __device__ __forceinline__ f32x16 mul3(const Op3& a, const Op3& b, f32x16 acc)
 {
     acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.l, b.h, acc, 0, 0, 0);

@@ -655,6 +655,26 @@ def test_f32_infinities_and_the_largest_values(dims, seg, monkeypatch):
         _check("O", binding.chela_linattn_fwd(c["Q"], c["K"], c["V"]), oracle.fwd_recurrent(*(to_f64_numpy(t[k]) for k in "QKV")), "f32")
 
 
+@pytest.mark.parametrize("dims", [(64, 64), (128, 128)])
+def test_f32_single_products(dims):
+    # one product per result, x y 1, in the chunk and across chunks: it may leave out 2^-24 of itself (the products of second and third parts)
+    # and is rounded once, to 2^-24; rounding on the way costs a quarter of that
+    dk, dv = dims
+    g = torch.Generator().manual_seed(dk)
+    x, y = (torch.rand(dk, generator=g) + 1 for _ in range(2))
+    x[:6] = y[:6] = torch.tensor([1 + 2.0 ** -7 - 2.0 ** -16, 1 + 2.0 ** -7 - 2.0 ** -15, 1 + 2.0 ** -8 - 2.0 ** -17, 1 + 2.0 ** -8 - 2.0 ** -16,
+                                  1 + 2.0 ** -7 - 2.0 ** -9 - 2.0 ** -16, 1 + 2.0 ** -7 - 2.0 ** -8 - 2.0 ** -17])
+    # key t has feature t only; queries 0 .. dk - 1 ask for their own, the next dk (other chunks) for that of the query dk before
+    Q, K, V = torch.zeros(1, 1, 2 * dk, dk), torch.zeros(1, 1, 2 * dk, dk), torch.ones(1, 1, 2 * dk, dv)
+    i = torch.arange(dk)
+    Q[0, 0, i, i] = Q[0, 0, dk + i, i] = x
+    K[0, 0, i, i] = y
+    O = binding.chela_linattn_fwd(Q.cuda(), K.cuda(), V.cuda()).cpu().double()
+    want = (x.double() * y.double())[:, None].expand(dk, dv)
+    for rows in (O[0, 0, :dk], O[0, 0, dk:]):
+        assert ((rows - want).abs() / want).max().item() <= 2.25 * 2.0 ** -24
+
+
 @pytest.mark.parametrize("shape", [(96, 1029, 64, 128), (96, 2047, 64, 64), (112, 1000, 128, 64), (90, 1025, 128, 128)])
 def test_f32_backward_split_where_one_segment_would_fill_the_gpu(shape):
     # three workgroups per segment and 256 or more at one segment per sequence: split all the same, ragged ends included.
