@@ -11,7 +11,8 @@
 // product is the six products of parts that matter, each exact, summed in fp32: 6 x 32 cycles of the matrix pipe for 16 steps
 // of a 32 x 32 tile where the fp32 instruction takes 512.  Values that three parts do not hold are met with the fp32
 // instruction itself (Hard).  Errors against 64 bits, 24 x 3001 tokens, 64 x 64: O 4.95e-7 with the
-// fp32 instruction, now 1.6e-7, gradients 2.6e-7, now 1.6e-7.  What bounds it: instruction issue -- splitting a value takes 5.5 vector instructions, looking
+// fp32 instruction, now 1.1e-7, gradients 2.6e-7, now 1.1e-7; lower over 9 shapes of 64 to 262000 tokens x 4 state sizes x 9
+// distributions (of either sign, positive, constant), by a sixth where the difference is smallest.  What bounds it: instruction issue -- splitting a value takes 5.5 vector instructions, looking
 // at it 1.5 -- and, with the GPU full, power (1.5 .. 2.1 GHz).  Measured, us, fp32 instruction -> three parts: 24 x 3001, 64 x 64:
 // forward 51.8 -> 40.3, backward 94 -> 77; 64 x 4096, 64 x 64: 109 -> 91, 284 -> 239; 24 x 3001, 128 x 128: 127 -> 108, 343 -> 277;
 // 16 x 400, 64 x 64: 39 -> 11.2, 41 -> 19.0 (of these two 25 are the plan's).
@@ -258,16 +259,21 @@ typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 // rounded to nearest: |m| <= 2^-8 |x|, |l| <= 2^-17 |x|, and what is behind l is nothing, because the remainders are exact and 15 and 6
 // bits wide: h + m + l is the value, where it is none of those that Hard looks out for.
 struct Pair3 { unsigned h, m, l; };
+template <bool NEG = false>
 __device__ __forceinline__ unsigned cvt_pk_bf16(float lo, float hi)      // round to nearest even
 {
     // (written out: the compiler would convert the low half a second time where its value is wanted as a float again)
     unsigned d;
-    asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(d) : "v"(lo), "v"(hi));
+    if (NEG) asm("v_cvt_pk_bf16_f32 %0, -%1, -%2" : "=v"(d) : "v"(lo), "v"(hi));
+    else asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(d) : "v"(lo), "v"(hi));
     return d;
 }
+// NEG: of -x0 and -x1, in no more instructions.
+template <bool NEG = false>
 __device__ __forceinline__ Pair3 split_pair(float x0, float x1)
 {
-    const unsigned h = cvt_pk_bf16(x0, x1);
+    const unsigned h = cvt_pk_bf16<NEG>(x0, x1);
+    if (NEG) { x0 = -x0; x1 = -x1; }
     const float r0 = x0 - __builtin_bit_cast(float, h << 16), r1 = x1 - __builtin_bit_cast(float, h & 0xffff0000u);
     const unsigned m = cvt_pk_bf16(r0, r1);
     const unsigned l = cvt_pk_bf16(r0 - __builtin_bit_cast(float, m << 16), r1 - __builtin_bit_cast(float, m & 0xffff0000u));
@@ -307,20 +313,9 @@ struct Hard {
 // An operand of the 32x32x16 instruction in its three parts.
 struct Op3 { bf16x8 h, m, l; };
 
-// acc += A B with six products of parts, the small ones first; a product of two parts is exact in fp32.  What is left out (m l, l m,
-// l l) is at most 2^-24 of a product, what rounding it once could cost; with a leading part cut off instead of rounded it was up to 2^-22.
-__device__ __forceinline__ f32x16 mul3(const Op3& a, const Op3& b, f32x16 acc)
-{
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.l, b.h, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.l, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.m, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.h, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.m, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.h, acc, 0, 0, 0);
-    return acc;
-}
-
-// The same with the leading products in a sum of their own: the others, below 2^-8 of them, then round 2^-8 finer.
+// A B with six products of parts, the leading ones and the others in sums of their own: those, below 2^-8 of them, then round 2^-8
+// finer.  A product of two parts is exact in fp32.  What is left out (m l, l m, l l) is at most 2^-24 of a product, what rounding it
+// once could cost; with a leading part cut off instead of rounded it was up to 2^-22.
 __device__ __forceinline__ void mul3(const Op3& a, const Op3& b, f32x16& hi, f32x16& lo)
 {
     lo = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.l, b.h, lo, 0, 0, 0);
@@ -329,6 +324,16 @@ __device__ __forceinline__ void mul3(const Op3& a, const Op3& b, f32x16& hi, f32
     hi = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.h, hi, 0, 0, 0);
     lo = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.h, lo, 0, 0, 0);
     lo = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.m, lo, 0, 0, 0);
+}
+
+// acc + the five small ones.
+__device__ __forceinline__ f32x16 mul_small(const Op3& a, const Op3& b, f32x16 acc)
+{
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.l, b.h, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.l, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.m, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.m, b.h, acc, 0, 0, 0);
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.h, b.m, acc, 0, 0, 0);
 }
 
 // Eight consecutive values as an operand.
@@ -374,15 +379,18 @@ __device__ __forceinline__ bf16x8 tr_pair(const bf16* lo, const bf16* hi)
 // The operand whose contraction index is the ROW: slot e of lane (r, h) is T[k0 + 8h + e][m0 + r], or with PERM, the order
 // in which an accumulator tile re-used as an operand holds its rows, T[k0 + 8 (e/4) + 4h + e%4][m0 + r].  Within 16 lanes the
 // transposing read hands lane p the column p of a 4 x 16 block whose rows the lanes address as p / 4, 8-byte pieces as p % 4.
-template <int ROWS, int D, bool PERM>
-__device__ __forceinline__ Op3 ld3_tr(const bf16* T, int k0, int m0, int lane)
+template <int D, bool PERM>
+__device__ __forceinline__ bf16x8 ldh_tr(const bf16* T, int k0, int m0, int lane)
 {
     const int p = lane & 15, g = (lane >> 4) & 1, h = lane >> 5;
     const int row = (PERM ? 4 : 8) * h + (p >> 2), row2 = row + (PERM ? 8 : 4);
     const int piece = (m0 >> 3) + 2 * g + ((p >> 1) & 1);
-    const bf16* a = T + k0 * D + tile_at<D>(row, piece) + 4 * (p & 1);
-    const bf16* b = T + k0 * D + tile_at<D>(row2, piece) + 4 * (p & 1);
-    return {tr_pair(a, b), tr_pair(a + ROWS * D, b + ROWS * D), tr_pair(a + 2 * ROWS * D, b + 2 * ROWS * D)};
+    return tr_pair(T + k0 * D + tile_at<D>(row, piece) + 4 * (p & 1), T + k0 * D + tile_at<D>(row2, piece) + 4 * (p & 1));
+}
+template <int ROWS, int D, bool PERM>
+__device__ __forceinline__ Op3 ld3_tr(const bf16* T, int k0, int m0, int lane)
+{
+    return {ldh_tr<D, PERM>(T, k0, m0, lane), ldh_tr<D, PERM>(T + ROWS * D, k0, m0, lane), ldh_tr<D, PERM>(T + 2 * ROWS * D, k0, m0, lane)};
 }
 
 // The rows of one chunk: logical positions c0 .. c0 + C of a row-major [N][D] matrix (in reverse where rev), as a buffer that ends
@@ -417,6 +425,7 @@ struct TileRegsF32 {
 #pragma unroll
         for (int n = 0; n < NV; ++n) v[n] = rows.load4(rows.at(tid / V4 + 256 / V4 * n) + (int)(tid % V4) * 16);
     }
+    template <bool NEG = false>
     __device__ __forceinline__ void stash(bf16* lds, unsigned tid, Hard& hard) const
     {
 #pragma unroll
@@ -424,7 +433,7 @@ struct TileRegsF32 {
             const int row = tid / V4 + 256 / V4 * n, c4 = tid % V4;
             hard.operands(v[n].x, v[n].y);
             hard.operands(v[n].z, v[n].w);
-            const Pair3 p0 = split_pair(v[n].x, v[n].y), p1 = split_pair(v[n].z, v[n].w);
+            const Pair3 p0 = split_pair<NEG>(v[n].x, v[n].y), p1 = split_pair<NEG>(v[n].z, v[n].w);
             bf16* d = lds + tile_at<D>(row, c4 >> 1) + 4 * (c4 & 1);
             *reinterpret_cast<u32x2*>(d) = u32x2{p0.h, p1.h};
             *reinterpret_cast<u32x2*>(d + C * D) = u32x2{p0.m, p1.m};
@@ -433,40 +442,50 @@ struct TileRegsF32 {
     }
 };
 
-// acc[n] + K^T V over K2 tokens for NT 32 x 32 tiles (i0(n), j0(n)).  The tokens are summed up by themselves and added to the running
+// acc[n] + sign K^T V over K2 tokens for NT 32 x 32 tiles (i0(n), j0(n)).  The tokens are summed up by themselves and added to the running
 // sum in one go: as operands of one chain of matrix instructions each would be rounded to the last place of the running
-// sum.  The operands of the next step are read while the current one's six instructions run.
-template <int K2, int DK, int DV, int NT, class I0, class J0>
-__device__ __forceinline__ void state_tiles(f32x16* acc, const bf16* k, const bf16* v, int lane, I0 i0, J0 j0)
+// sum.  The operands of the next step are read while the current one's instructions run.  The small products do not go into the
+// sum of the leading ones: the instruction aligns what it adds to the largest term, and drops, always downwards, what lies far
+// below.  With all six in one sum 2 x 65000 tokens of positive keys were 2.5e-7 from 64 bits, with the fp32 instruction 2.1e-7, so 1.0e-7.
+// A sum of their own costs a tile of registers; where there is none (SMALL_FIRST, the pre-pass: 21 to 54 would be spilled) they go first,
+// over all tokens, and the leading ones on top.
+template <int K2, int DK, int DV, int NT, bool SMALL_FIRST, class I0, class J0>
+__device__ __forceinline__ void state_tiles(f32x16* acc, const bf16* k, const bf16* v, float sign, int lane, I0 i0, J0 j0)
 {
-    constexpr int STEPS = K2 / 16 * NT;
-    f32x16 t[NT];
+    constexpr int STEPS = K2 / 16 * NT, ALL = SMALL_FIRST ? 2 * STEPS : STEPS;
+    f32x16 t[NT], lo[NT];
 #pragma unroll
-    for (int n = 0; n < NT; ++n) t[n] = zero16f();
+    for (int n = 0; n < NT; ++n) { t[n] = zero16f(); lo[n] = zero16f(); }
     Op3 a[2], b[2];
     a[0] = ld3_tr<K2, DK, false>(k, 0, i0(0), lane);
     b[0] = ld3_tr<K2, DV, false>(v, 0, j0(0), lane);
     int cur = 0;                 // (which b is in use: a step whose tile shares the step before's columns of V reads none)
 #pragma unroll
-    for (int s = 0; s < STEPS; ++s) {
+    for (int s = 0; s < ALL; ++s) {
         int nxt = cur;
-        if (s + 1 < STEPS) {
-            const int s0 = (s + 1) / NT * 16, n = (s + 1) % NT;
-            a[(s + 1) & 1] = ld3_tr<K2, DK, false>(k, s0, i0(n), lane);
+        if (s + 1 < ALL) {
+            const int s0 = (s + 1) % STEPS / NT * 16, n = (s + 1) % NT;
+            const bool lead = s + 1 >= STEPS;            // (the leading parts only)
+            if (lead) a[(s + 1) & 1].h = ldh_tr<DK, false>(k, s0, i0(n), lane);
+            else a[(s + 1) & 1] = ld3_tr<K2, DK, false>(k, s0, i0(n), lane);
             if (n == 0 || j0(n) != j0(n - 1)) {
                 nxt = cur ^ 1;
-                b[nxt] = ld3_tr<K2, DV, false>(v, s0, j0(n), lane);
+                if (lead) b[nxt].h = ldh_tr<DV, false>(v, s0, j0(n), lane);
+                else b[nxt] = ld3_tr<K2, DV, false>(v, s0, j0(n), lane);
             }
         }
         __builtin_amdgcn_sched_barrier(0);
-        t[s % NT] = mul3(a[s & 1], b[cur], t[s % NT]);
+        f32x16& sum = t[s % NT];
+        if (!SMALL_FIRST) mul3(a[s & 1], b[cur], sum, lo[s % NT]);
+        else if (s < STEPS) sum = mul_small(a[s & 1], b[cur], sum);
+        else sum = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s & 1].h, b[cur].h, sum, 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
         cur = nxt;
     }
 #pragma unroll
     for (int n = 0; n < NT; ++n)
 #pragma unroll
-        for (int e = 0; e < 16; ++e) acc[n][e] += t[n][e];
+        for (int e = 0; e < 16; ++e) acc[n][e] = fmaf(sign, SMALL_FIRST ? t[n][e] : t[n][e] + lo[n][e], acc[n][e]);
 }
 
 // ------------------------------------------------------------------------------------------------ the same on fp32 instructions
@@ -653,11 +672,15 @@ __device__ __forceinline__ void f32_seg_state_body(const float* __restrict__ K, 
             if (c0 >= p1) break;
             __syncthreads();
             rk[u].stash(sK, tid, hard);
-            rv[u].stash(sV, tid, hard);
+            // (every other step with -V: what the instruction drops downwards is then as often too much as too little.  S after 262144 tokens,
+            // in 2^-24 of its size: 5.9 too small, now 0.0)
+            const bool odd = (c0 / R) & 1;
+            if (odd) rv[u].template stash<true>(sV, tid, hard);
+            else rv[u].stash(sV, tid, hard);
             __syncthreads();
             rk[u].fetch(ChunkRows<R, DK>(Kb, c0 + 2 * R, p1, N, rev), tid);
             rv[u].fetch(ChunkRows<R, DV>(Vb, c0 + 2 * R, p1, N, rev), tid);
-            state_tiles<R, DK, DV, NT>(acc, sK, sV, lane, [&](int n) { return ((w + 4 * n) / JB) * 32; },
+            state_tiles<R, DK, DV, NT, true>(acc, sK, sV, odd ? -1.f : 1.f, lane, [&](int n) { return ((w + 4 * n) / JB) * 32; },
                                        [&](int n) { return ((w + 4 * n) % JB) * 32; });
         }
     }
@@ -806,7 +829,7 @@ __device__ __forceinline__ void f32_sweep_body(const float* __restrict__ Q, cons
         int ln = lane;      // (opaque: what depends on the lane alone would otherwise be kept in registers across the loop)
         asm volatile("" : "+v"(ln));
         Op3 aQ[KK], aP[2], op[2];
-        f32x16 pT, hi[NJ], lo[NJ];
+        f32x16 pT, pL, hi[NJ], lo[NJ];
         auto split_q = [&](int kk) __attribute__((always_inline)) {
             const float4 x = rq[2 * kk], y = rq[2 * kk + 1];
             const float e[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
@@ -816,13 +839,13 @@ __device__ __forceinline__ void f32_sweep_body(const float* __restrict__ Q, cons
         };
         // scores of keys 16 x .. 16 x + 15 of the block as first operand: the accumulator tile holds them as it wants them
         auto split_p = [&](int x, bool mask) __attribute__((always_inline)) {
-            float e[8];
+            float e[8], v[8];
 #pragma unroll
             for (int q = 0; q < 8; ++q) {
                 const int row = 16 * x + 8 * (q >> 2) + 4 * (ln >> 5) + (q & 3);        // key within the block; ln & 31 = query
-                const float v = pT[8 * x + q];
-                if (q & 1) hard.operands(pT[8 * x + q - 1], v);
-                e[q] = !mask || row <= (ln & 31) ? v : 0.f;
+                v[q] = pT[8 * x + q] + pL[8 * x + q];
+                if (q & 1) hard.operands(v[q - 1], v[q]);
+                e[q] = !mask || row <= (ln & 31) ? v[q] : 0.f;
             }
             aP[x] = split8(e);
         };
@@ -834,6 +857,7 @@ __device__ __forceinline__ void f32_sweep_body(const float* __restrict__ Q, cons
         split_q(0);
         op[0] = keys(tb, 0);
         pT = zero16f();
+        pL = zero16f();
 #pragma unroll
         for (int n = 0; n < NJ; ++n) { hi[n] = zero16f(); lo[n] = zero16f(); }
 #pragma unroll
@@ -844,7 +868,7 @@ __device__ __forceinline__ void f32_sweep_body(const float* __restrict__ Q, cons
             __builtin_amdgcn_sched_barrier(0);
             if (s < NA) {                    // P^T[s][t] = k_s . q_t (each of the WJ waves of a row block for itself)
                 if (s + 1 < KK) split_q(s + 1);
-                pT = mul3(op[s & 1], aQ[s], pT);
+                mul3(op[s & 1], aQ[s], pT, pL);
             } else if (s < NA + NB) {        // inter-chunk part Q S_prev
                 const int n = (s - NA) / KK;
                 mul3(aQ[(s - NA) % KK], op[s & 1], hi[n], lo[n]);
@@ -860,13 +884,14 @@ __device__ __forceinline__ void f32_sweep_body(const float* __restrict__ Q, cons
         if (TB > 1 && tb > 0) {
             op[0] = keys(0, 0);
             pT = zero16f();
+        pL = zero16f();
 #pragma unroll
             for (int s = 0; s < NA + NC; ++s) {
                 if (s + 1 < NA) op[(s + 1) & 1] = keys(0, s + 1);
                 else if (s + 1 < NA + NC) op[(s + 1) & 1] = vals(0, s + 1 - NA);
                 __builtin_amdgcn_sched_barrier(0);
                 if (s < NA) {
-                    pT = mul3(op[s & 1], aQ[s], pT);
+                    mul3(op[s & 1], aQ[s], pT, pL);
                 } else {
                     const int x = (s - NA) / NJ, n = (s - NA) % NJ;
                     if (s == NA) split_p(0, false);
@@ -892,7 +917,7 @@ __device__ __forceinline__ void f32_sweep_body(const float* __restrict__ Q, cons
                 }
         // state update S += K^T V (not needed after the segment's last chunk)
         if (more)
-            state_tiles<C, DK, DV, NS>(accS, sK, sV, ln, [&](int n) { return (q_own + n) % IB * 32; },
+            state_tiles<C, DK, DV, NS, false>(accS, sK, sV, 1.f, ln, [&](int n) { return (q_own + n) % IB * 32; },
                                         [&](int n) { return (jg * NJ + (q_own + n) / IB) * 32; });
     };
     // (nothing outstanding on the way into the loop: what a chunk waits for at its start is then counted from the chunk before,

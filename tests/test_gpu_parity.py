@@ -675,6 +675,25 @@ def test_f32_single_products(dims):
         assert ((rows - want).abs() / want).max().item() <= 2.25 * 2.0 ** -24
 
 
+@pytest.mark.parametrize("dims", [(64, 64), (64, 128), (128, 128)])
+def test_f32_long_sums_lean_to_neither_side(dims):
+    # Positive keys, values of either sign: the state is a random walk, and what is always dropped in one direction adds up along it.  The last
+    # queries read the state out.  Rounding errors are 3 to 4 units (2^-24 of the mean value) per element and the same for
+    # a column's elements at most, so the mean over 2 x 64 columns and more lies within 3 * 4 / sqrt(128) of zero.
+    dk, dv = dims
+    N = 16384 + dk
+    g = torch.Generator().manual_seed(dk + dv)
+    K = (torch.nn.functional.elu(torch.randn(1, 2, N, dk, generator=g)) + 1) / 128
+    V = torch.randn(1, 2, N, dv, generator=g)
+    Q = torch.zeros(1, 2, N, dk)
+    K[:, :, -dk:] = 0
+    i = torch.arange(dk)
+    Q[:, :, N - dk + i, i] = 1
+    S = binding.chela_linattn_fwd(Q.cuda(), K.cuda(), V.cuda())[:, :, -dk:].cpu().double()
+    ref = K.double().transpose(2, 3) @ V.double()
+    assert ((S - ref).mean() / ref.abs().mean()).abs().item() <= 1.07 * 2.0 ** -24
+
+
 @pytest.mark.parametrize("shape", [(96, 1029, 64, 128), (96, 2047, 64, 64), (112, 1000, 128, 64), (90, 1025, 128, 128)])
 def test_f32_backward_split_where_one_segment_would_fill_the_gpu(shape):
     # three workgroups per segment and 256 or more at one segment per sequence: split all the same, ragged ends included.
