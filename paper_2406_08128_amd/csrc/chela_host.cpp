@@ -8,7 +8,7 @@
 //
 // Likewise, with the functions' addresses first and the stream last:
 //   forward(f, f32, Q, K, V, S_in, S_out, chunk, stream) -> O; with f32 = None (chela_linattn_fwd_state: bf16 only) -> (O, S_out)
-//   backward(f, f32, Q, K, V, dO, chunk, stream) -> (dQ, dK, dV); chunk = None: chela_linattn_noncausal_bwd, bf16 only
+//   backward(f, f32, Q, K, V, dO, chunk, stream) -> (dQ, dK, dV); f32 = None: chela_linattn_noncausal_bwd, bf16 only, chunk not looked at
 //   gated(f, saved_bytes, Q or Z, K or affine, V, G, eps, want_O, want_saved, stream) -> (Y, O or None, saved or None);
 //       saved_bytes = None: chela_linattn_noncausal_fwd_gated
 //   gate_norm_bwd(f, O, G, dY, eps, stream) -> (dO, dG)
@@ -123,7 +123,7 @@ struct Sequences {
         const int64_t lim = 0x7fffffff;
         int overflow = 0;
         long c = 64;
-        if (ochunk != nullptr && ochunk != Py_None) {
+        if (ochunk != nullptr) {
             if (!PyLong_CheckExact(ochunk)) return false;
             c = PyLong_AsLongAndOverflow(ochunk, &overflow);
             if (overflow || c < 0 || c > lim) return false;
@@ -210,9 +210,9 @@ PyObject* backward(PyObject*, PyObject* const* a, Py_ssize_t n)
 {
     HANDLE_TH_ERRORS
     if (n != 8) { PyErr_SetString(PyExc_TypeError, "backward takes eight arguments"); return nullptr; }
-    const bool causal = a[6] != Py_None;
+    const bool causal = a[1] != Py_None;
     Sequences x;
-    if (!x.read(a + 2, causal, a[6], a[7]) || !plain(a[5], x.type, x.dev)) Py_RETURN_NONE;
+    if (!x.read(a + 2, causal, causal ? a[6] : nullptr, a[7]) || !plain(a[5], x.type, x.dev)) Py_RETURN_NONE;
     const at::Tensor &q = THPVariable_Unpack(a[2]), &v = THPVariable_Unpack(a[4]), &d = THPVariable_Unpack(a[5]);
     if (d.sizes() != v.sizes()) Py_RETURN_NONE;
     PyObject* const of = a[x.type == at::kFloat ? 1 : 0];

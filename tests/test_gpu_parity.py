@@ -1294,6 +1294,19 @@ def test_sequence_host_path_and_the_bindings_own_lines_agree(dk, dv, dtype):
     assert binding.chela_linattn_fwd(empty, empty, empty).shape == (2, 3, 0, dk)
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+def test_sequence_calls_refuse_a_chunk_of_none(dtype):
+    # (it is not "the usual one", and does not choose another function)
+    Q = torch.zeros(1, 2, 100, 64, dtype=dtype, device="cuda")
+    binding._load_step()
+    f = binding._fn
+    assert binding._host("forward")(f["linattn_fwd"], f["linattn_fwd_f32"], Q, Q, Q, None, None, None, None) is None
+    assert binding._host("backward")(f["linattn_bwd"], f["linattn_bwd_f32"], Q, Q, Q, Q, None, None) is None
+    for call in (binding.chela_linattn_fwd, lambda *a, **k: binding.chela_linattn_bwd(*a, Q, **k), binding.chela_linattn_fwd_state):
+        with pytest.raises(TypeError):
+            call(Q, Q, Q, chunk=None)
+
+
 @pytest.mark.parametrize("dk,dv", [(64, 64), (128, 64)])
 def test_layer_and_convolution_host_path_and_the_bindings_own_lines_agree(dk, dv, monkeypatch):
     # every further call that has a native host path: that it takes the plain call, and gives what the binding's own lines give
