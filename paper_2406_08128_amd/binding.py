@@ -20,14 +20,20 @@ DTYPE_BF16 = 0
 DTYPE_F32 = 1
 
 _lib = None
-_step_host = None           # the host module's step(), once a call has been made
-_step_fn = (0, 0)           # addresses of chela_linattn_step, chela_linattn_step_gated for it
-_host_modules = {}          # by _step_host: the same module, None where there is none
-_fn = {}                    # addresses of the library's functions for it, by name
 
 
 def _decline(*a):
     return None
+
+
+_step_host = None           # the host module's step(), once a call has been made
+_step_fn = (0, 0)           # addresses of chela_linattn_step, chela_linattn_step_gated for it
+_host_module = None         # that module, None where there is none
+# addresses of the library's functions for it, by name
+_fn = dict.fromkeys(("linattn_fwd", "linattn_fwd_f32", "linattn_fwd_state", "linattn_bwd", "linattn_bwd_f32", "linattn_fwd_gated",
+                     "linattn_zfwd_gated", "linattn_saved_bytes", "gate_norm_bwd", "linattn_zbwd_saved", "linattn_noncausal_fwd_gated",
+                     "linattn_noncausal_bwd", "longconv_spectrum", "longconv_spectrum_bytes", "shortlong_conv_fwd",
+                     "shortlong_conv_fwd_f32", "shortlong_conv_bwd", "shortlong_conv_bwd_f32"), 0)
 
 
 class ChelaError(RuntimeError):
@@ -190,18 +196,18 @@ def _on(t: torch.Tensor):
 def _load_step():
     """Loads the host module and looks up the addresses of the library's functions it calls.  Returns its step(), or one that
     declines every call where the module is not built or does not load, for instance beside another torch than it was built for (the
-    functions below then do the same by their own lines, a decode step in 8.9 us instead of 4.7, a short prompt in 10 instead of 5)."""
-    global _step_host, _step_fn
-    L = lib()
+    functions below then do the same by their own lines, a decode step in 8.9 us instead of 4.7, a short prompt in 10 instead of 5).
+    So does it where there is no library, until there is one: those lines look at the arguments first."""
+    global _step_host, _step_fn, _host_module
+    try:
+        L = lib()
+    except OSError:
+        return _decline
     _step_fn = tuple(ctypes.cast(f, ctypes.c_void_p).value for f in (L.chela_linattn_step, L.chela_linattn_step_gated))
-    for name in ("linattn_fwd", "linattn_fwd_f32", "linattn_fwd_state", "linattn_bwd", "linattn_bwd_f32", "linattn_fwd_gated",
-                 "linattn_zfwd_gated", "linattn_saved_bytes", "gate_norm_bwd", "linattn_zbwd_saved", "linattn_noncausal_fwd_gated",
-                 "linattn_noncausal_bwd", "longconv_spectrum", "longconv_spectrum_bytes", "shortlong_conv_fwd",
-                 "shortlong_conv_fwd_f32", "shortlong_conv_bwd", "shortlong_conv_bwd_f32"):
+    for name in _fn:
         _fn[name] = ctypes.cast(getattr(L, "chela_" + name), ctypes.c_void_p).value
     path = os.path.join(_HERE, "_chela_host.so")
-    step = lambda *a: None        # noqa: E731
-    module = None
+    step, module = _decline, None
     if os.path.exists(path):
         spec = importlib.util.spec_from_file_location("_chela_host", path,
                                                       loader=importlib.machinery.ExtensionFileLoader("_chela_host", path))
@@ -211,14 +217,16 @@ def _load_step():
             step, module = m.step, m
         except ImportError as e:
             warnings.warn("calls take the slower host path: %s does not load (%s)" % (path, e), RuntimeWarning)
-    _host_modules[step] = module        # (first: whoever sees _step_host looks here)
+    _host_module = module        # (first: whoever sees _step_host looks here)
     _step_host = step
     return step
 
 
 def _host(name):
     """The host module's function of that name, as _load_step()'s for the decode step."""
-    return getattr(_host_modules[_step_host if _step_host is not None else _load_step()], name, _decline)
+    if _step_host is None:
+        _load_step()
+    return getattr(_host_module, name, _decline)
 
 
 def _host_result(r):

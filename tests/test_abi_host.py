@@ -611,6 +611,29 @@ def test_host_module_that_does_not_load_leaves_the_bindings_own_path(L, monkeypa
     assert step(0, None, None, None, None, None, 0.0, None, None) is None and binding._step_host is step
 
 
+def test_calls_look_at_their_arguments_before_they_look_for_the_library(monkeypatch, tmp_path):
+    # where it is absent a wrong argument is still what is said, and a right one gets the file's name
+    import torch
+    from paper_2406_08128_amd import binding
+    monkeypatch.setenv("CHELA_LIB", str(tmp_path / "libchela.so"))
+    for name, value in (("_lib", None), ("_step_host", None), ("_host_module", None)):
+        monkeypatch.setattr(binding, name, value)
+    x = torch.zeros(1, 2, 100, 64)
+    A, k = torch.zeros(4, 2, 64), torch.zeros(3, 100)
+    for call in (lambda: binding.chela_linattn_fwd(x, x[:, :1], x), lambda: binding.chela_linattn_bwd(x, x[:, :1], x, x),
+                 lambda: binding.chela_linattn_fwd_state(x, x[:, :1], x), lambda: binding.chela_linattn_noncausal_bwd(x, x[:, :1], x, x),
+                 lambda: binding.chela_linattn_fwd_gated(x.bfloat16(), x[:, :1].bfloat16(), x, x, 1e-5),
+                 lambda: binding.chela_linattn_zfwd_gated(x, A[:, :1], x, x, 1e-5), lambda: binding.chela_linattn_noncausal_fwd_gated(x, x, x[:, :1], x, 1e-5),
+                 lambda: binding.chela_linattn_zbwd_saved(x, A[:, :1], x, x, x), lambda: binding.chela_gate_norm_bwd(x, x[:, :1], x, 1e-5),
+                 lambda: binding.chela_longconv_spectrum(k), lambda: binding.chela_shortlong_conv_fwd(x[0], k, k),
+                 lambda: binding.chela_shortlong_conv_bwd(x[0], k, k, x[0, :1]), lambda: binding.chela_linattn_step(x[:, :, 0], x[:, :, 0], x[:, :, 0], x),
+                 lambda: binding.chela_linattn_step_gated(x[:, :, 0], x[:, :, 0], x[:, :, 0], x[:, :, 0], x, 1e-5)):
+        with pytest.raises(ValueError):
+            call()
+    with pytest.raises(FileNotFoundError):
+        binding.chela_linattn_workspace_bytes(1, 1, 64, 64, 64, 64, False, 0)
+
+
 def test_host_module_that_cannot_be_built_takes_nothing_else_with_it(monkeypatch, tmp_path, capfd):
     from paper_2406_08128_amd import build
     old = tmp_path / "_chela_host.so"
