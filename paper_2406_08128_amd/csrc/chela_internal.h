@@ -22,6 +22,7 @@ struct Plan {
 // The sweeps add the segment totals up themselves (no scan kernel) while one (b,h) pair's totals stay below this:
 // every workgroup re-reads, on average, half of them from the L2.
 constexpr size_t kMaxFoldedStateBytes = (size_t)256 << 10;
+bool fold_scan(const Plan& plan, bool stateful, bool is_bwd = false);
 
 // The memory-side cache holds 256 MB.  A backward call whose four input tensors come to more than this reads two of
 // them (dO, Q) with the streaming hint in its pre-pass, so that the other two stay cached for the sweep.

@@ -1828,7 +1828,7 @@ static int prepass_reverse()
 // while those reads stay small next to the segment's own tiles (measured: 64 x 64 states, 10 segments: step 0.343 ->
 // 0.337 ms; 64 x 128, step 0.280 -> 0.265 ms; 128 x 128 states, 16 segments: 0.327 -> 0.332 ms, so not there).
 // CHELA_FOLD_SCAN=0 (read per call, a tuning aid) keeps the scan.
-static bool fold_scan(const Plan& plan, bool stateful, bool is_bwd = false)
+bool fold_scan(const Plan& plan, bool stateful, bool is_bwd)
 {
     if (stateful || plan.n_seg < 2) return false;
     if ((size_t)plan.n_seg * plan.state_elems * sizeof(float) > kMaxFoldedStateBytes) return false;

@@ -1004,20 +1004,13 @@ void f32_bwd_sweep_kernel(const float* __restrict__ Q, const float* __restrict__
     }
 }
 
-// The sweeps add the segments' totals up themselves while a sequence's come to no more than kMaxFoldedStateBytes; a scan of
-// its own otherwise.
-static bool f32_fold(const Plan& plan)
-{
-    return (size_t)plan.n_seg * plan.state_elems * sizeof(float) <= kMaxFoldedStateBytes;
-}
-
 template <int DK, int DV>
 static hipError_t f32_fwd_impl(const float* Q, const float* K, const float* V, float* O, long BH, int N, const Plan& plan,
                                float* ws, hipStream_t st)
 {
     hipError_t e;
     const dim3 grid((unsigned)BH, plan.n_seg);
-    const bool folded = f32_fold(plan);
+    const bool folded = fold_scan(plan, false, false);
     if (plan.n_seg > 1) {
         {
             ProfScope prof(KID_SEG_STATE_F32, st);
@@ -1040,7 +1033,7 @@ static hipError_t f32_bwd_impl(const float* Q, const float* K, const float* V, c
 {
     hipError_t e;
     const size_t stride = (size_t)BH * plan.n_seg * DK * DV;
-    const bool folded = f32_fold(plan);
+    const bool folded = fold_scan(plan, false, true);
     if (plan.n_seg > 1) {
         {
             ProfScope prof(KID_SEG_STATE_F32, st);

@@ -321,6 +321,31 @@ def test_scan_in_a_kernel_of_its_own_or_folded_into_the_sweeps(mode, monkeypatch
         _check("Y", Y, oracle_layer.gate_norm_fwd(rO, Gn, EPS), "bf16")
 
 
+def test_f32_scan_is_folded_unless_asked_not_to(monkeypatch):
+    # seven segments per sequence: the same variable as for bf16 says who adds their totals up
+    monkeypatch.setenv("CHELA_SEG_TOKENS", "192")
+    w = _small("f32", N=1251, B=1, H=3, seed=66)
+    x = make_inputs(w)
+    d = _dev(x)
+    n = [to_f64_numpy(x[k]) for k in ("Q", "K", "V", "dO")]
+    refs = (oracle.fwd_recurrent(*n[:3]),) + tuple(oracle.bwd_recurrent(*n))
+    for mode, scans in ((None, 0), ("2", 0), ("1", 1), ("0", 2)):
+        if mode:
+            monkeypatch.setenv("CHELA_FOLD_SCAN", mode)
+        binding.chela_profile_reset()
+        binding.chela_profile_enable(True)
+        try:
+            got = (binding.chela_linattn_fwd(d["Q"], d["K"], d["V"]),) + tuple(binding.chela_linattn_bwd(d["Q"], d["K"], d["V"], d["dO"]))
+            torch.cuda.synchronize()
+            launches = binding.chela_profile_read()
+        finally:
+            binding.chela_profile_enable(False)
+            binding.chela_profile_reset()
+        assert launches.get("scan_states_kernel", (0, 0.0))[0] == scans, (mode, launches)
+        for name, g, r in zip(("O", "dQ", "dK", "dV"), got, refs):
+            _check(name, g, r, "f32")
+
+
 def test_training_pair_scratch_sized_by_its_own_query():
     # 24 (b,h) pairs of 4096 tokens: the training pair's forward cuts each sequence 16 times, the plain forward 8
     w = shrink(WORKLOADS["lm_bf16"], B=2, H=12, N=4096, seed=63)
