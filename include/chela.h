@@ -320,7 +320,9 @@ int chela_linattn_step_gated(const void *q, const void *k, const void *v, const 
  * 7 segments at 16384 tokens, 32 at 65536, again 32 at a million); a caller-owned buffer smaller than this size is
  * accepted down to what one state per segment of the forward's split takes, with fewer segments; the same goes for the
  * scratch earlier calls left where nothing can be allocated (under stream capture, or when memory is short).  fp32 calls with 256
- * or more pairs are not cut and take no scratch. */
+ * or more pairs are not cut and take no scratch.  Where a call is cut otherwise for want of scratch -- the same call eagerly and
+ * under capture, say -- its results differ by the rounding of another order of the sums; with the same scratch they have the
+ * same bits each time. */
 size_t chela_linattn_workspace_bytes(int B, int H, int N, int dk, int dv, int chunk,
                                      int is_bwd, int dtype);
 
