@@ -83,12 +83,14 @@ static long choose_segments(long BH, long n_chunks, long slots, double g_min, do
 }
 
 // Calls of up to 2048 chunks in all, bf16 (but the 64 x 64 forward, where nothing is to be gained): the general model counts in chunk
-// steps of a full GPU, all of one length, and takes a pre-pass for three of them.  In a short call a step takes what it takes a workgroup that has its unit to itself, 1.3 us (forward,
-// 64 x 64) to 6 (backward, 128 x 128, whose single segment walks twice: 7.7), and the pre-pass 4 whatever the widths are; under
-// some 7 us (forward) or 8.5 (backward) the host's launches are the time, and one costs less than two.  So this is a model in us,
-// fitted to the times of 21 shapes per pair of widths over all segment lengths (geometric mean of what the choice costs over the
-// best one, general model -> this one: forward 1.08 -> 1.01, backward 1.14 -> 1.01, worst 1.44 -> 1.05 and 1.99 -> 1.10).
-// On 21 other shapes per pair of widths: backward 1.13 to 1.16 times as fast as with the general model, forward 1.04 to 1.06.
+// steps of a full GPU, all of one length, and takes a pre-pass for three of them.  In a short call a step takes what it takes a workgroup
+// that has its unit to itself, 1.3 us (forward, 64 x 64) to 6 (backward, 128 x 128, whose single segment walks twice: 7.7), and the pre-pass 4 whatever the widths are; under
+// some 7 us (forward) or 8.5 (backward) the host's launches are the time, and one costs less than two.  So this is a model in us, fitted
+// to the times of 21 shapes per pair of widths over all segment lengths.  What the choice costs over the best split, geometric mean, general
+// model -> this one, on those shapes: forward 1.06 -> 1.02, backward 1.13 -> 1.02; on 61 others: 1.06 -> 1.02 and 1.13 -> 1.02
+// (worst 1.39 -> 1.14 and 1.67 -> 1.17).  Of these 574 choices 14 are slower than the general model's by more than 3 %, two by more than
+// 10 %: 69 x 1545, 64 x 128, forward, 13 %; 150 x 500, 64 x 64, backward, 10 %.  (Asking for 5 % of predicted gain leaves 8 such, and costs
+// the backward 0.7 % on the mean.)
 // Beyond, where memory is the bound, it is no better than the general one.  us, by chunks per segment, the general choice, this
 // one's: backward 8 x 272 tokens, 128 x 128, one 18.5 (taken), two 24.3, all five 36.8 (general); 4 x 8192, 64 x 64, one 48.4
 // (general), two 32.0, three 29.2 (taken), four 27.3; 24 x 900 one 20.1 (general), two 15.0 (taken); forward 16 x 1467, 128 x 128,
@@ -199,9 +201,9 @@ Plan make_plan(long BH, int N, int dk, int dv, int chunk, int dtype, bool is_bwd
 // alone on its compute unit takes three quarters of the time per chunk step that one of two takes (4.5 and 5.7 .. 7 us), and the
 // pre-pass's steps, a third as long, count too.  A workgroup adds up half its sequence's totals, or the scan is a launch more.
 // Segments of less than three chunks only where one round holds all chunks.  us by chunks per segment, the general
-// model's choice first: 24 x 3001 tokens: six 43.3, five (taken) 36.7, four 41.6, three 37.8; 64 x 777: five 31.5, four 29.1,
-// three (taken) 24.9, two 26.9; 4 x 16384: (five) 48.8, four (taken) 47.2, three 53.7; 64 x 4096: eight (both) 84.3, five 96.8,
-// four 93.4, sixteen 97.9; 16 x 1025: (three) 20.5, two (taken) 16.6, one 17.7.  The wider states: nothing to gain.
+// model's choice first: 24 x 3001 tokens: six 42.6, five (taken) 37.0, four 42.1, three 37.5; 64 x 777: five 33.2, four 28.7,
+// three (taken) 24.2, two 25.8; 4 x 16384: (five) 47.7, four (taken) 45.9, three 53.5; 64 x 4096: eight (both) 89.8, five 96.4,
+// four 95.4, sixteen 97.9; 16 x 1025: (three) 21.6, two (taken) 17.2, one 18.1.  The wider states: nothing to gain.
 static long f32_fwd_segments(long BH, long n_chunks, size_t state_elems)
 {
     long best = 1;
@@ -239,9 +241,9 @@ Plan make_f32_fwd_plan(long BH, int N, int dk, int dv, int chunk, size_t ws_limi
 // own, because the instructions bound it and not the memory: a round costs its chunk steps whether the one before was
 // full or not, several rounds are no slower than one, and the pre-pass and the states are small change.  Segments of less
 // than four chunks only where two rounds hold all chunks, single ones where one does.  Measured, us, 64 x 64, by chunks
-// per segment: 24 x 3001 tokens: four 79, five 77, six 81, eight (taken) 74, twelve 92; 64 x 4096: eight (taken) 226, six 240,
-// sixteen 222; 16 x 1025: one 25.2, two (taken) 24.5, three 28.0, five 34.0; 4 x 4096: one 38.8, two (taken) 30.2, three 33.7,
-// five 37.1; 16 x 400: one (taken) 17.8, two 17.8, three 23.0, the whole sequence 29.1.
+// per segment: 24 x 3001 tokens: four 80, five 80, six 85, eight (taken) 76, twelve 97; 64 x 4096: eight (taken) 235, six 246,
+// sixteen 231; 16 x 1025: one 25.5, two (taken) 25.2, three 29.2, five 36.9; 4 x 4096: one 39.5, two (taken) 31.3, three 35.7,
+// five 40.6; 16 x 400: one (taken) 19.1, two 19.1, three 24.9, the whole sequence 33.8.
 static long f32_bwd_segments(long wgs_per_seg, long n_chunks, long slots, size_t state_elems)
 {
     long best = 1;
