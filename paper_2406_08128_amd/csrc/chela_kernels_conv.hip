@@ -58,6 +58,14 @@ template <bool INV> __device__ __forceinline__ void bfly1_q(cplx& a, cplx& b)
     a = cadd(a, r);
 }
 
+// Sixteenth and eighth roots of unity: cos and sin of pi / 8, sqrt(1/2).  As fp32 numbers all three are too small, so that every root shrinks
+// what it multiplies, and a transform and back lose 1e-7 of a sequence of one sign; at 4096 and 16384 points the rounding of the
+// table of powers happens to make up for a half and for nearly all of it.  At the sizes in between (conv_fine) the first, and the
+// second part of the eighth root in w^2 w8, are the next numbers above.  64 channels, fp32, inputs of one sign, 5003 steps: Z
+// 2.3e-7 -> 1.2e-7 from 64 bits (in 16384 points 1.5e-7), dX 2.1e-7 -> 0.8e-7 (0.9e-7); of either sign: 2.7e-7 -> 2.2e-7 (2.9e-7).
+constexpr float kC1 = 0.92387953251128674f, kS1 = 0.38268343236508977f, kR2 = 0.70710678118654752f;
+constexpr float kC1Above = 0x1.d906bep-1f, kR2Above = 0x1.6a09e8p-1f;
+
 // w^2 of a w on the unit circle and not far from 1
 __device__ __forceinline__ cplx unit_square(cplx w) { const float y2 = 2.f * w.y; return mk(fmaf(-y2, w.y, 1.f), y2 * w.x); }
 
@@ -67,13 +75,12 @@ __device__ __forceinline__ cplx unit_square(cplx w) { const float y2 = 2.f * w.y
 // times eighth and sixteenth roots: eight distinct complex twiddles (21 instructions from those) for 32 butterflies of six
 // instructions, 220 in all, where a plain 16-point transform with fifteen twiddles in front of or behind it takes 290
 // (its chain of powers 56, its products 60).  UNIT: w = 1 (148 instructions).  HALF_IN: x_8 .. x_15 are zero (not read).
-// HALF_OUT: only X_0 .. X_7 are wanted.
+// HALF_OUT: only X_0 .. X_7 are wanted.  FINE: conv_fine(M).
 __host__ __device__ constexpr int rev4(int p) { return ((p & 1) << 3) | ((p & 2) << 1) | ((p & 4) >> 1) | ((p & 8) >> 3); }
-template <bool INV, bool UNIT, bool HALF_IN = false, bool HALF_OUT = false>
+template <bool INV, bool UNIT, bool FINE, bool HALF_IN = false, bool HALF_OUT = false>
 __device__ __forceinline__ void dft16(cplx (&v)[16], cplx w, cplx w2, cplx w4, cplx w8)
 {
-    constexpr float C1 = 0.92387953251128674f, S1 = 0.38268343236508977f, R2 = 0.70710678118654752f;
-    constexpr float SG = INV ? 1.f : -1.f;
+    constexpr float SG = INV ? 1.f : -1.f, C1 = FINE ? kC1Above : kC1, R2b = FINE ? kR2Above : kR2;
     if (HALF_IN) {
 #pragma unroll
         for (int q = 0; q < 8; ++q) v[q + 8] = v[q];
@@ -93,7 +100,7 @@ __device__ __forceinline__ void dft16(cplx (&v)[16], cplx w, cplx w2, cplx w4, c
         for (int q = 0; q < 4; ++q) { bfly(v[q], v[q + 4], w4.x, w4.y); bfly_q<INV>(v[q + 8], v[q + 12], w4.x, w4.y); }
     }
     // slots now: x_q sums with the bits of p seen so far (lowest first) in the top bits of the slot
-    const cplx w2b = UNIT ? mk(R2, SG * R2) : cmul(w2, mk(R2, SG * R2));             // w^2 w8
+    const cplx w2b = UNIT ? mk(kR2, SG * R2b) : cmul(w2, mk(kR2, SG * R2b));             // w^2 w8
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
         if (UNIT) { bfly1(v[q], v[q + 2]); bfly1_q<INV>(v[q + 4], v[q + 6]); }
@@ -101,9 +108,9 @@ __device__ __forceinline__ void dft16(cplx (&v)[16], cplx w, cplx w2, cplx w4, c
         bfly(v[q + 8], v[q + 10], w2b.x, w2b.y);
         bfly_q<INV>(v[q + 12], v[q + 14], w2b.x, w2b.y);
     }
-    const cplx d1 = UNIT ? mk(C1, SG * S1) : cmul(w, mk(C1, SG * S1));
-    const cplx d2 = UNIT ? mk(R2, SG * R2) : cmul(w, mk(R2, SG * R2));
-    const cplx d3 = UNIT ? mk(S1, SG * C1) : cmul(w, mk(S1, SG * C1));
+    const cplx d1 = UNIT ? mk(C1, SG * kS1) : cmul(w, mk(C1, SG * kS1));
+    const cplx d2 = UNIT ? mk(kR2, SG * kR2) : cmul(w, mk(kR2, SG * kR2));
+    const cplx d3 = UNIT ? mk(kS1, SG * C1) : cmul(w, mk(kS1, SG * C1));
     // (HALF_OUT: the differences, X_(p+8), are dead and the compiler drops them)
     if (UNIT) { bfly1(v[0], v[1]); bfly1_q<INV>(v[2], v[3]); }
     else { bfly(v[0], v[1], w.x, w.y); bfly_q<INV>(v[2], v[3], w.x, w.y); }
@@ -212,7 +219,7 @@ __device__ __forceinline__ void pass16(cplx* a, const float4* tw, int tid)
         if (!UNIT) twiddle<M, INV>(tw, INV ? j * (M / N16) : block_bin<M, N16>(block) * S, w, w2, w4, w8);
 #pragma unroll
         for (int q = 0; q < (HALF && !INV ? 8 : 16); ++q) v[q] = p0[q * STEP];
-        dft16<INV, UNIT, HALF && !INV, HALF && INV>(v, w, w2, w4, w8);
+        dft16<INV, UNIT, conv_fine(M), HALF && !INV, HALF && INV>(v, w, w2, w4, w8);
 #pragma unroll
         for (int p = 0; p < (HALF && INV ? 8 : 16); ++p) p0[p * STEP] = v[rev4(p)];
     }
@@ -249,7 +256,6 @@ __device__ __forceinline__ void fft_forward(const cplx (&z)[FULL ? M / T : M / T
         } else if constexpr (conv_lead(M) == 8) {
             // x_0 .. x_3 of two columns, x_4 .. x_7 being zero: even bins from x_q, odd ones from x_q w8^q
             constexpr int s = M / 8, sp = s + s / 16;
-            constexpr float R2 = 0.70710678118654752f;
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 cplx* p0 = a + conv_pad(tid + T * j);
@@ -257,9 +263,9 @@ __device__ __forceinline__ void fft_forward(const cplx (&z)[FULL ? M / T : M / T
 #pragma unroll
                 for (int q = 0; q < 4; ++q) v[q] = z[2 * q + j];
                 u[0] = v[0];
-                u[1] = cmul(v[1], mk(R2, -R2));
+                u[1] = cmul(v[1], mk(kR2, -kR2));
                 u[2] = mul_neg_i(v[2]);
-                u[3] = cmul(v[3], mk(-R2, -R2));
+                u[3] = cmul(v[3], mk(-kR2, -kR2));
                 bfly1(v[0], v[2]);
                 bfly1(v[1], v[3]);
                 bfly1(u[0], u[2]);
@@ -305,7 +311,7 @@ __device__ __forceinline__ void fft_forward(const cplx (&z)[FULL ? M / T : M / T
             cplx v[16];
 #pragma unroll
             for (int q = 0; q < 8; ++q) v[q] = z[q];
-            dft16<false, true, true>(v, mk(1.f, 0.f), mk(1.f, 0.f), mk(1.f, 0.f), mk(1.f, 0.f));
+            dft16<false, true, conv_fine(M), true>(v, mk(1.f, 0.f), mk(1.f, 0.f), mk(1.f, 0.f), mk(1.f, 0.f));
             cplx* p0 = a + conv_pad(tid);
 #pragma unroll
             for (int p = 0; p < 16; ++p) p0[p * STEP] = v[rev4(p)];
@@ -335,8 +341,7 @@ __device__ __forceinline__ void fft_inverse(cplx* a, cplx (&y)[M / T / 2], const
             __syncthreads();
             // y = x_0 + conj(W^(tid + T j)) x_1: W^T is a sixteenth root
             constexpr int sp = M / 2 + M / 32;
-            constexpr float C1 = 0.92387953251128674f, S1 = 0.38268343236508977f, R2 = 0.70710678118654752f;
-            constexpr float CX[8] = {1.f, C1, R2, S1, 0.f, -S1, -R2, -C1}, CY[8] = {0.f, S1, R2, C1, 1.f, C1, R2, S1};
+            constexpr float CX[8] = {1.f, kC1Above, kR2, kS1, 0.f, -kS1, -kR2, -kC1Above}, CY[8] = {0.f, kS1, kR2, kC1Above, 1.f, kC1Above, kR2, kS1};
             cplx t, t2, t4, t8;
             twiddle<M, true>(tw, tid, t, t2, t4, t8);
 #pragma unroll
@@ -348,13 +353,12 @@ __device__ __forceinline__ void fft_inverse(cplx* a, cplx (&y)[M / T / 2], const
         } else if constexpr (conv_lead(M) == 8) {
             // y_p = sum_q x_q t^q conj(w8)^(p q), p < 4, t = conj(W^(tid + T j)), W^T a sixteenth root: even and odd q apart
             constexpr int s = M / 8, sp = s + s / 16;
-            constexpr float C1 = 0.92387953251128674f, S1 = 0.38268343236508977f, R2 = 0.70710678118654752f;
             cplx t, t2, t4, t8;
             twiddle<M, true>(tw, tid, t, t2, t4, t8);
 #pragma unroll
             for (int j = 0; j < 2; ++j) {
                 const cplx* p0 = a + conv_pad(tid + T * j);
-                if (j == 1) { t = cmul(t, mk(C1, S1)); t2 = cmul(t2, mk(R2, R2)); t4 = mul_pos_i(t4); }
+                if (j == 1) { t = cmul(t, mk(kC1Above, kS1)); t2 = cmul(t2, mk(kR2, kR2)); t4 = mul_pos_i(t4); }
                 cplx v[4], u[4];
 #pragma unroll
                 for (int q = 0; q < 4; ++q) { v[q] = p0[2 * q * sp]; u[q] = p0[(2 * q + 1) * sp]; }
@@ -368,9 +372,9 @@ __device__ __forceinline__ void fft_inverse(cplx* a, cplx (&y)[M / T / 2], const
                 bfly_q<true>(u[2], u[3], t2.x, t2.y);
                 // (slots 0, 2, 1, 3 now hold p = 0, 1, 2, 3)
                 y[j] = cfma(t, u[0], v[0]);
-                y[j + 2] = cfma(cmul(t, mk(R2, R2)), u[2], v[2]);
+                y[j + 2] = cfma(cmul(t, mk(kR2, kR2)), u[2], v[2]);
                 y[j + 4] = cfma(mul_pos_i(t), u[1], v[1]);
-                y[j + 6] = cfma(cmul(t, mk(-R2, R2)), u[3], v[3]);
+                y[j + 6] = cfma(cmul(t, mk(-kR2, kR2)), u[3], v[3]);
             }
         } else if constexpr (conv_lead(M) == 4) {
             if constexpr (M == 16384) { pass16<M, T, 4096, true, false>(a, tw, tid); __syncthreads(); }
@@ -380,10 +384,9 @@ __device__ __forceinline__ void fft_inverse(cplx* a, cplx (&y)[M / T / 2], const
                 const cplx* p0 = a + conv_pad(tid + T * j);
                 cplx t1, t2, t4, t8;
                 // W^(tid + j M/16): W^tid times sixteenth roots
-                constexpr float C1 = 0.92387953251128674f, S1 = 0.38268343236508977f, R2 = 0.70710678118654752f;
                 twiddle<M, true>(tw, tid, t1, t2, t4, t8);
-                t1 = j == 0 ? t1 : cmul(t1, j == 1 ? mk(C1, S1) : j == 2 ? mk(R2, R2) : mk(S1, C1));
-                t2 = j == 0 ? t2 : j == 2 ? mul_pos_i(t2) : cmul(t2, j == 1 ? mk(R2, R2) : mk(-R2, R2));
+                t1 = j == 0 ? t1 : cmul(t1, j == 1 ? mk(kC1, kS1) : j == 2 ? mk(kR2, kR2) : mk(kS1, kC1));
+                t2 = j == 0 ? t2 : j == 2 ? mul_pos_i(t2) : cmul(t2, j == 1 ? mk(kR2, kR2) : mk(-kR2, kR2));
                 const cplx t3 = cmul(t2, t1);
                 cplx v0 = p0[0], v1 = cmul(p0[sp], t1), v2 = p0[2 * sp], v3 = p0[3 * sp];
                 bfly(v0, v2, t2.x, t2.y);
@@ -399,7 +402,7 @@ __device__ __forceinline__ void fft_inverse(cplx* a, cplx (&y)[M / T / 2], const
             for (int q = 0; q < 16; ++q) v[q] = p0[q * STEP];
             cplx w, w2, w4, w8;
             twiddle<M, true>(tw, tid, w, w2, w4, w8);
-            dft16<true, false, false, true>(v, w, w2, w4, w8);
+            dft16<true, false, conv_fine(M), false, true>(v, w, w2, w4, w8);
 #pragma unroll
             for (int p = 0; p < 8; ++p) y[p] = v[rev4(p)];
         }
