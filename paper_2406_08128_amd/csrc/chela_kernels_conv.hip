@@ -158,8 +158,8 @@ struct ConvLds {
 // and squared here (M = 16384), the gradient of 128 channels x 16384 steps, fp32, was 6.3 .. 7.7e-7 from 64 bits; with the
 // square from the table 4.0 .. 4.7e-7, and 4 x 256 channels take 209 us instead of 250.  With the fourth power from it, and the
 // square by a formula that holds on the unit circle only (conv_fine), the last square is one step from the table and not two:
-// 64 channels x 6001 steps 4.2e-7 -> 3.4e-7.  M = 2048: the eighth power, too (64 x 2048 steps 3.3e-7 -> 3.1e-7, what it was in a
-// transform of 4096 points).
+// 64 channels x 6001 steps 4.2e-7 -> 3.4e-7.  M = 2048: the eighth power, too (64 x 2048 steps 3.3e-7 -> 3.1e-7).  (Both before kC1Above and
+// kR2Above; with them 2.7e-7 and 2.6e-7.)
 template <int M, bool INV>
 __device__ __forceinline__ void twiddle(const float4* tw, int e, cplx& w, cplx& w2, cplx& w4, cplx& w8)
 {
