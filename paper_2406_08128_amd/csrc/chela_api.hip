@@ -84,8 +84,9 @@ static long choose_segments(long BH, long n_chunks, long slots, double g_min, do
 
 // Calls of up to 2048 chunks in all, bf16 (but the 64 x 64 forward, where nothing is to be gained): the general model counts in chunk
 // steps of a full GPU, all of one length, and takes a pre-pass for three of them.  In a short call a step takes what it takes a workgroup
-// that has its unit to itself, 1.3 us (forward, 64 x 64) to 6 (backward, 128 x 128, whose single segment walks twice: 7.7), and the pre-pass 4 whatever the widths are; under
-// some 7 us (forward) or 8.5 (backward) the host's launches are the time, and one costs less than two.  So this is a model in us, fitted
+// that has its unit to itself, 1.3 us (forward, 64 x 64) to 6 (backward, 128 x 128, whose single segment walks twice: 7.7), and the
+// pre-pass 4 whatever the widths are; under some 7 us (forward) or 8.5 (backward) the host's launches are the time, and one costs less
+// than two.  So this is a model in us, fitted
 // to the times of 21 shapes per pair of widths over all segment lengths.  What the choice costs over the best split, geometric mean, general
 // model -> this one, on those shapes: forward 1.06 -> 1.02, backward 1.13 -> 1.02; on 61 others: 1.06 -> 1.02 and 1.13 -> 1.02
 // (worst 1.39 -> 1.14 and 1.67 -> 1.17).  Of these 574 choices 14 are slower than the general model's by more than 3 %, two by more than

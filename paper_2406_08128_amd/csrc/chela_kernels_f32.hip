@@ -7,17 +7,18 @@
 // P = (Q K^T) o M, O = P V + Q S (both parts summed in the same accumulators), then S += K^T V.  Segment start
 // states come from a pre-pass (segment totals of K^T V), added up by the sweeps or by a scan.
 //
-// Arithmetic.  Every operand (tiles, scores, published state) is three bf16 parts that together hold all of its 24 bits, and a
-// product is the six products of parts that matter, each exact, summed in fp32: 6 x 32 cycles of the matrix pipe for 16 steps
-// of a 32 x 32 tile where the fp32 instruction takes 512.  Values that three parts do not hold are met with the fp32
-// instruction itself (Hard).  Errors against 64 bits, 24 x 3001 tokens, 64 x 64: O 4.95e-7 with the
-// fp32 instruction, now 1.1e-7, gradients 2.6e-7, now 1.1e-7; lower over 9 shapes of 64 to 262000 tokens x 4 state sizes x 9
-// distributions (of either sign, positive, constant), by a sixth where the difference is smallest.  What bounds it: instruction issue -- splitting a value takes 5.5 vector instructions, looking
-// at it 1.5 -- and, with the GPU full, power (1.5 .. 2.1 GHz).  Measured, us, fp32 instruction -> three parts: 24 x 3001, 64 x 64:
-// forward 51.8 -> 40.3, backward 94 -> 77; 64 x 4096, 64 x 64: 109 -> 91, 284 -> 239; 24 x 3001, 128 x 128: 127 -> 108, 343 -> 277;
-// 16 x 400, 64 x 64: 39 -> 11.2, 41 -> 19.0 (of these two 25 are the plan's).
-// Two halves in fp16 would be half the instructions, but 22 bits, and a token 2^30 louder than its chunk would cost the others
-// theirs.
+// Arithmetic.  Every operand (tiles, scores, published state) is three bf16 parts that together hold all of its 24 bits, and
+// a product is the six products of parts that matter, each exact, summed in fp32: 6 x 32 cycles of the matrix pipe for 16
+// steps of a 32 x 32 tile where the fp32 instruction takes 512.  Values that three parts do not hold are met with the fp32
+// instruction itself (Hard).  Errors against 64 bits, 24 x 3001 tokens, 64 x 64: O 4.95e-7 with the fp32 instruction, now
+// 1.1e-7, gradients 2.6e-7, now 1.1e-7; lower over 9 shapes of 64 to 262000 tokens x 4 state sizes x 9 distributions (of
+// either sign, positive, constant), by a sixth where the difference is smallest.  What bounds it: instruction issue --
+// splitting a value takes 5.5 vector instructions, looking at it 1.5 -- and, with the GPU full, power (1.5 .. 2.1
+// GHz).  Measured, us, fp32 instruction -> three parts: 24 x 3001, 64 x 64: forward 51.8 -> 40.3, backward 94 -> 77; 64 x
+// 4096, 64 x 64: 109 -> 91, 284 -> 239; 24 x 3001, 128 x 128: 127 -> 108, 343 -> 277; 16 x 400, 64 x 64: 39 -> 11.2, 41 ->
+// 19.0 (of these two 25 are the plan's).
+// Two halves in fp16 would be half the instructions, but 22 bits, and a token 2^30 louder than its chunk would cost the
+// others theirs.
 #include "chela_internal.h"
 
 namespace chela {
